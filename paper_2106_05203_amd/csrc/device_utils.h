@@ -27,6 +27,12 @@ __device__ __forceinline__ float4 stream_load4(const float *p) {
     const v4f t = __builtin_nontemporal_load(reinterpret_cast<const v4f *>(p));
     return make_float4(t.x, t.y, t.z, t.w);
 }
+// The same for an address that is only 4-byte aligned (gfx950 loads 16 bytes from any dword address).
+__device__ __forceinline__ float4 stream_load4_any(const float *p) {
+    typedef float v4f __attribute__((ext_vector_type(4), aligned(4)));
+    const v4f t = __builtin_nontemporal_load(reinterpret_cast<const v4f *>(p));
+    return make_float4(t.x, t.y, t.z, t.w);
+}
 __device__ __forceinline__ float stream_load(const float *p) { return __builtin_nontemporal_load(p); }
 __device__ __forceinline__ int32_t stream_load(const int32_t *p) { return __builtin_nontemporal_load(p); }
 
@@ -42,6 +48,31 @@ __device__ __forceinline__ float loss_derivative(float y, float z, int loss) {
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
     for (int o = kWave / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
+    return v;
+}
+
+// Sum over each group of LANES consecutive lanes (16, 32 or 64), the same bits in every lane of the group, in
+// vector instructions alone: neighbours by DPP inside a row of sixteen lanes, rows by the half-swaps of gfx950.
+// (__shfl_xor goes through the LDS crossbar, six dependent round trips of it for a wavefront.)
+template <int CTRL>
+__device__ __forceinline__ float dpp_move(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+template <int LANES>
+__device__ __forceinline__ float group_sum(float v) {
+    static_assert(LANES == 16 || LANES == 32 || LANES == 64, "whole rows of sixteen lanes");
+    v += dpp_move<0xB1>(v);                 // quad_perm [1,0,3,2]
+    v += dpp_move<0x4E>(v);                 // quad_perm [2,3,0,1]
+    v += dpp_move<0x141>(v);                // row_half_mirror: the other quad of eight lanes
+    v += dpp_move<0x140>(v);                // row_mirror: the other eight lanes of the row
+    if constexpr (LANES >= 32) {            // swaps the odd rows of one copy with the even rows of the other
+        const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+        v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    }
+    if constexpr (LANES == 64) {            // swaps the upper half of one copy with the lower half of the other
+        const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+        v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    }
     return v;
 }
 

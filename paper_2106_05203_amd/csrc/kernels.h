@@ -78,7 +78,7 @@ struct TopkArgs {
     float *out_val;
     float *g_i;
     GradParts parts;   // if parts.part != nullptr the rows of `a` are these unreduced gradients (`a` is not read);
-                       // launch_topk_row only, d <= 8192, b != nullptr
+                       // launch_topk_row only, d <= kRowPartsMax, b != nullptr
     int32_t warm;      // launch_topk_split only: 0, or 1 .. 2 = the row thresholds of the last call that named the
                        // same number on this workspace serve as the first guess of this call's (the result never
                        // depends on it; meant for consecutive iterations of one algorithm on one state)
@@ -88,6 +88,9 @@ struct TopkArgs {
     int32_t agg_shift;
     int64_t agg_nblk;
 };
+
+// Rows this long can be handed to launch_topk_row as unreduced gradients (TopkArgs::parts).
+constexpr int64_t kRowPartsMax = 8192;
 
 // One workgroup per row, four radix passes over the row plus an ordered emission.  Needs no
 // workspace and is correct for every input; meant for rows that one compute unit can stream

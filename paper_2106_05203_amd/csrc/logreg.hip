@@ -8,7 +8,8 @@
 // of the row in registers between the dot product (wavefront reduction, no LDS) and the rank-one
 // accumulation r_l * a_l into per-lane accumulators.  Workgroups write partial sums that a small
 // second kernel adds in a fixed order (bitwise reproducible), together with the regulariser.
-// Dense rows, larger d: z = A x, then A^T r, two passes.  (CSR rows: logreg_csr.hip.)
+// Dense rows, d up to 28672: the same with a workgroup per row (logreg_dense_wide_kernel).
+// Dense rows, larger d (and d < 4): z = A x, then A^T r, two passes.  (CSR rows: logreg_csr.hip.)
 #include "device_utils.h"
 #include "kernels.h"
 #include "logreg_dense_block.h"
@@ -34,6 +35,182 @@ __global__ __launch_bounds__(kThreads) void logreg_dense_fused_kernel(const floa
     dense_block<VEC, NQ, ROWS, BATCH>(A, y, x + worker * x_stride /* 0: one x for all workers */, part, m, d,
                                       rows_per_wg, loss, batch, m_full, worker, blockIdx.x, gridDim.x,
                                       threadIdx.x / kWave, threadIdx.x, true, red);
+}
+
+// ------------------------------------------------------------------ dense, wide rows, one pass over A
+// Rows too long for one wavefront's registers: a workgroup of 1024 threads owns whole rows, a thread NQ quads of
+// columns (quad q of thread t: columns 4 (1024 q + t) ..).  The dot product is a wavefront sum, sixteen values in
+// LDS and one barrier per group of R rows; the rank-one accumulation stays in registers, so A is read once.  HBM
+// bandwidth bounds it: the next group's loads are issued before this group is summed (two register buffers, the
+// barriers order LDS only), and one workgroup per compute unit keeps 1024 threads x R x NQ x 16 bytes in flight.
+// Rows need no alignment: the quad that straddles the end of the row is moved back onto the row's last four
+// columns, its columns that belong to the quad before it count as zero and are not written (RAGGED); quads past the
+// end read the same place and are dropped.  From NQ = 5 on x lives in LDS instead of registers.
+// The whole gradient, n = 8, m = 2000, d = 12000 (768 MB): 124 us, 6.2 TB/s, against 461 us for the two passes below;
+// n = 8, m = 1200, d = 20001: 149 against 564; n = 2, m = 100, d = 4097: 10.1 against 18.0.
+constexpr int kWideThreads = 1024, kWideWaves = kWideThreads / kWave;
+constexpr int64_t kWideMax = 7 * 4 * kWideThreads;        // columns (with eight quads the compiler spills)
+
+template <int NQ>
+constexpr int wide_rows() {                               // rows per group
+    return NQ <= 2 ? 4 : (NQ <= 4 ? 2 : 1);
+}
+
+// Chunks per workgroup: where a group is one row, half as many rows per chain of additions.
+template <int NQ>
+constexpr int wide_chunks() {
+    return wide_rows<NQ>() == 1 ? 2 : 1;
+}
+
+template <int NQ, bool RAGGED, bool BATCH>
+__global__ __launch_bounds__(kWideThreads) void logreg_dense_wide_kernel(const float *__restrict__ A,
+                                                                         const float *__restrict__ y,
+                                                                         const float *__restrict__ x,
+                                                                         float *__restrict__ part, int64_t m, int64_t d,
+                                                                         int64_t rows_per_chunk, int64_t chunks,
+                                                                         int loss, const int32_t *__restrict__ batch,
+                                                                         int64_t m_full, int64_t x_stride) {
+    constexpr int R = wide_rows<NQ>();
+    constexpr bool kXLds = NQ >= 5;
+    __shared__ float sums[2][R][kWideWaves];
+    __shared__ float4 x_lds[kXLds ? NQ * kWideThreads : 1];
+    const int64_t worker = blockIdx.y;
+    const int tid = threadIdx.x, wave = tid / kWave, lane = lane_id();
+    const float *xw = x + worker * x_stride;
+    const int32_t last = (int32_t)d - 4;
+
+    int32_t at[NQ];                // where the quad is read
+    int dup[NQ];                   // its leading columns that are another quad's; 4: past the end of the row
+    float xr[kXLds ? 1 : NQ][4], acc[NQ][4];
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+        const int32_t c0 = (q * kWideThreads + tid) * 4;
+        at[q] = c0 < last ? c0 : last;
+        dup[q] = c0 - at[q] < 4 ? c0 - at[q] : 4;
+        float xq[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            xq[t] = t >= dup[q] ? xw[at[q] + t] : 0.f;
+            acc[q][t] = 0.f;
+            if constexpr (!kXLds) xr[q][t] = xq[t];
+        }
+        if constexpr (kXLds) x_lds[q * kWideThreads + tid] = make_float4(xq[0], xq[1], xq[2], xq[3]);   // own use only
+    }
+
+    // the block's chunks of rows; each leaves its own partial sums
+    constexpr int64_t kChunks = wide_chunks<NQ>();
+    int64_t chunk = (int64_t)blockIdx.x * kChunks;
+    const int64_t l0 = chunk * rows_per_chunk;
+    const int64_t l1 = l0 + kChunks * rows_per_chunk < m ? l0 + kChunks * rows_per_chunk : m;
+    // the loads of rows l .. l + R - 1; a row past the block reads the first 16 bytes of A (one cached line)
+    auto load = [&](int64_t l, float4 (&v)[R][NQ], float (&yl)[R], bool (&live)[R]) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            live[r] = l + r < l1;
+            int64_t src = live[r] ? l + r : l0;
+            if constexpr (BATCH) {
+                src = batch_row(batch, worker * m + src, m_full);
+                if (src < 0) {
+                    src = 0;
+                    live[r] = false;
+                }
+            }
+            const float *row = live[r] ? A + (worker * m_full + src) * d : A;
+            yl[r] = y[worker * m_full + src];
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) v[r][q] = stream_load4_any(row + (live[r] ? at[q] : 0));
+        }
+    };
+    float4 av[R][NQ], next[R][NQ];
+    float yl[R], y_next[R];
+    bool live[R], live_next[R];
+    load(l0, av, yl, live);
+    int buf = 0;
+    for (int64_t l = l0; l < l1; l += R, buf ^= 1) {
+        load(l + R, next, y_next, live_next);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            float s = 0.f;
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) {
+                float4 xq;
+                if constexpr (kXLds) xq = x_lds[q * kWideThreads + tid];
+                else xq = make_float4(xr[q][0], xr[q][1], xr[q][2], xr[q][3]);
+                if constexpr (RAGGED) {                        // a straddling quad: its foreign columns are zero
+                    if (dup[q] > 0) av[r][q].x = 0.f;
+                    if (dup[q] > 1) av[r][q].y = 0.f;
+                    if (dup[q] > 2) av[r][q].z = 0.f;
+                }
+                float p = fmaf(av[r][q].x, xq.x, s);
+                p = fmaf(av[r][q].y, xq.y, p);
+                p = fmaf(av[r][q].z, xq.z, p);
+                p = fmaf(av[r][q].w, xq.w, p);
+                s = dup[q] < 4 ? p : s;
+            }
+            s = group_sum<kWave>(s);
+            if (lane == 0) sums[buf][r][wave] = s;
+        }
+        __syncthreads();           // two buffers: the next group's sums are written to the other one
+        float coef[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            float s = 0.f;
+#pragma unroll
+            for (int w = 0; w < kWideWaves; ++w) s += sums[buf][r][w];
+            coef[r] = live[r] ? loss_derivative(yl[r], s, loss) : 0.f;
+        }
+        // the group's rows are added to one another first: a shorter chain of additions per column
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            if constexpr (R == 1) {
+                acc[q][0] = fmaf(coef[0], av[0][q].x, acc[q][0]);
+                acc[q][1] = fmaf(coef[0], av[0][q].y, acc[q][1]);
+                acc[q][2] = fmaf(coef[0], av[0][q].z, acc[q][2]);
+                acc[q][3] = fmaf(coef[0], av[0][q].w, acc[q][3]);
+            } else {
+                float g[4] = {coef[0] * av[0][q].x, coef[0] * av[0][q].y, coef[0] * av[0][q].z, coef[0] * av[0][q].w};
+#pragma unroll
+                for (int r = 1; r < R; ++r) {
+                    g[0] = fmaf(coef[r], av[r][q].x, g[0]);
+                    g[1] = fmaf(coef[r], av[r][q].y, g[1]);
+                    g[2] = fmaf(coef[r], av[r][q].z, g[2]);
+                    g[3] = fmaf(coef[r], av[r][q].w, g[3]);
+                }
+#pragma unroll
+                for (int t = 0; t < 4; ++t) acc[q][t] += g[t];
+            }
+        }
+        const bool end_of_chunk = l + R >= l1 || (kChunks > 1 && l + R == (chunk + 1) * rows_per_chunk);
+        if (end_of_chunk) {
+            float *out = part + (worker * chunks + chunk) * d;
+#pragma unroll
+            for (int q = 0; q < NQ; ++q)
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    if (t >= dup[q]) out[at[q] + t] = acc[q][t];
+                    acc[q][t] = 0.f;
+                }
+            ++chunk;
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) av[r][q] = next[r][q];
+            yl[r] = y_next[r];
+            live[r] = live_next[r];
+        }
+    }
+}
+
+// Rows of a worker are cut so that all workers together have about one workgroup per compute unit, at least four
+// rows each (a chunk's partial sums cost as much traffic as one of its rows, written and read again).
+DensePlan wide_plan(int32_t n, int64_t m, int chunks_per_wg) {
+    int64_t target = 256 / n;
+    if (target < 1) target = 1;
+    target *= chunks_per_wg;
+    int64_t rows = (m + target - 1) / target;
+    if (rows < 4) rows = 4;
+    return {rows, (m + rows - 1) / rows};
 }
 
 // ------------------------------------------------------------------ dense, any d: two passes
@@ -124,6 +301,24 @@ void launch_fused(const DenseArgs &a, hipStream_t stream) {
                            a.x, a.part, a.m, a.d, a.pl.rows_per_wg, a.loss, a.batch, a.m_full, a.x_stride);
 }
 
+template <int NQ, bool RAGGED>
+void launch_wide_tile(const DenseArgs &a, hipStream_t stream) {
+    constexpr int64_t kChunks = wide_chunks<NQ>();
+    const dim3 grid((unsigned)((a.pl.chunks + kChunks - 1) / kChunks), (unsigned)a.n);
+    if (a.batch)
+        hipLaunchKernelGGL((logreg_dense_wide_kernel<NQ, RAGGED, true>), grid, dim3(kWideThreads), 0, stream, a.A, a.y,
+                           a.x, a.part, a.m, a.d, a.pl.rows_per_wg, a.pl.chunks, a.loss, a.batch, a.m_full, a.x_stride);
+    else
+        hipLaunchKernelGGL((logreg_dense_wide_kernel<NQ, RAGGED, false>), grid, dim3(kWideThreads), 0, stream, a.A, a.y,
+                           a.x, a.part, a.m, a.d, a.pl.rows_per_wg, a.pl.chunks, a.loss, a.batch, a.m_full, a.x_stride);
+}
+
+template <int NQ>
+void launch_wide(const DenseArgs &a, hipStream_t stream) {
+    if (a.d % 4 == 0) launch_wide_tile<NQ, false>(a, stream);
+    else launch_wide_tile<NQ, true>(a, stream);
+}
+
 }  // namespace
 
 size_t logreg_dense_scratch_bytes(int32_t n, int64_t m, int64_t d) {
@@ -136,13 +331,15 @@ hipError_t launch_logreg_grad_dense(const float *A, const float *y, const float 
     if (defer) *defer = GradParts();
     const int32_t *batch = rb.tau > 0 ? rb.rows : nullptr;
     const int64_t m = batch ? rb.tau : m_full;         // rows summed per worker (tau <= m_full, checked by the caller)
-    const DensePlan pl = dense_plan(n, m);
+    const bool vec4 = (d % 4 == 0) && ((uintptr_t)A % 16 == 0);
+    const DenseVariant dv = dense_variant(d, vec4);
+    const bool wide = dv.vec == 0 && d <= kWideMax && d >= 4;
+    const DensePlan pl = wide ? wide_plan(n, m, d > 4 * 4 * kWideThreads ? wide_chunks<5>() : wide_chunks<4>())
+                              : dense_plan(n, m);
     float *part = (float *)scratch;
     float *resid = part + (size_t)n * max_chunks(n, m_full) * d;
-    const bool vec4 = (d % 4 == 0) && ((uintptr_t)A % 16 == 0);
     const DenseArgs a{A, y, x, part, n, m, d, pl, loss, batch, m_full, x_stride};
-    const DenseVariant dv = dense_variant(d, vec4);
-    const bool fused = dv.vec != 0;
+    const bool fused = dv.vec != 0 || wide;
     switch (dv.vec * 100 + dv.nq) {
         case 401: launch_fused<4, 1>(a, stream); break;
         case 402: launch_fused<4, 2>(a, stream); break;
@@ -153,6 +350,17 @@ hipError_t launch_logreg_grad_dense(const float *A, const float *y, const float 
         case 108: launch_fused<1, 8>(a, stream); break;
         case 132: launch_fused<1, 32>(a, stream); break;
         default: break;
+    }
+    if (wide) {
+        switch ((d + 4 * kWideThreads - 1) / (4 * kWideThreads)) {
+            case 1: launch_wide<1>(a, stream); break;
+            case 2: launch_wide<2>(a, stream); break;
+            case 3: launch_wide<3>(a, stream); break;
+            case 4: launch_wide<4>(a, stream); break;
+            case 5: launch_wide<5>(a, stream); break;
+            case 6: launch_wide<6>(a, stream); break;
+            default: launch_wide<7>(a, stream); break;
+        }
     }
     if (!fused) {
         const int64_t rows = (int64_t)n * m;
@@ -167,7 +375,7 @@ hipError_t launch_logreg_grad_dense(const float *A, const float *y, const float 
     mk(K_GRAD_MAIN);
     hipError_t st = hipGetLastError();
     if (st != hipSuccess) return st;
-    if (defer && fused && x_stride == 0) {      // the consumer finishes the sums itself (dense_grad_entry)
+    if (defer && fused && x_stride == 0 && d <= kRowPartsMax) {      // the consumer finishes the sums itself (dense_grad_entry)
         *defer = GradParts{part, pl.chunks, m, x, lambda};
         return hipSuccess;
     }

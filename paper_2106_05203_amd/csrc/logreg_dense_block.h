@@ -29,7 +29,7 @@ inline DensePlan dense_plan(int32_t n, int64_t m) {
 inline int64_t max_chunks(int32_t n, int64_t m) {
     int64_t target = 512 / n;
     if (target < 1) target = 1;
-    const int64_t by_rows = (m + 7) / 8;
+    const int64_t by_rows = (m + 3) / 4;
     return by_rows < target ? by_rows : target;
 }
 

@@ -234,7 +234,7 @@ __device__ void row_topk(RowShared &s, const TopkArgs &p, int64_t row) {
 }
 
 // Rows of at most kRowCache entries: the row is formed once into LDS (`cache`), all passes read it there.
-constexpr int kRowCache = 8192;
+constexpr int kRowCache = (int)kRowPartsMax;
 
 template <bool DIFF, bool UPDATE>
 __device__ void row_topk_cached(RowShared &s, float *cache, const TopkArgs &p, int64_t row) {

@@ -72,6 +72,46 @@ def test_dense_gradient(gpu, oracle, n, d, m):
         assert torch.equal(h.local_grad(), got)
 
 
+# a workgroup per row: every number of quads per thread at its ends, quads that straddle the end of the row by one,
+# two and three columns, rows that are not 16-byte aligned, one row and many per block, a minibatch with an entry
+# out of range; the last two take the two passes again
+@pytest.mark.parametrize("n,d,m", [(1, 4100, 1), (2, 4101, 9), (2, 8192, 13), (3, 8194, 7), (2, 12288, 31), (1, 12291, 5),
+                                   (2, 16384, 6), (2, 16385, 6), (1, 20481, 10), (2, 24578, 5), (300, 4097, 3),
+                                   (1, 28672, 11), (1, 28673, 4), (2, 3, 5)])
+def test_dense_gradient_wide_rows(gpu, oracle, n, d, m):
+    torch, binding = gpu
+    print(f"wide dense grad case n={n} d={d} m={m}", flush=True)
+    rng = np.random.default_rng(d + m)
+    A = (rng.standard_normal((n, m, d), dtype=np.float32) / np.float32(np.sqrt(d)))
+    y = np.where(rng.random((n, m)) < 0.5, 1.0, -1.0).astype(np.float32)
+    x = rng.standard_normal(d).astype(np.float32)
+    ref = oracle.LogRegDense(A, y, 0.1).grads(x.astype(np.float64))
+    with binding.EF21(n, d, 1, 0.1) as h:
+        pad = torch.empty(A.size + 1, device="cuda")                  # A itself at an odd 4-byte address
+        Ag = pad[1:].view(n, m, d)
+        Ag.copy_(torch.from_numpy(A))
+        h.set_problem_dense(Ag, to_gpu(torch, y), 0.1)
+        got = h.local_grad(to_gpu(torch, x))
+        # additions behind one dot product: a thread's quads, six wavefront steps, sixteen wavefronts (or, in the two
+        # passes, a lane's share of the row)
+        depth = 4 * -(-d // 4096) + 22 if 4 <= d <= 28672 else d / 64 + 8
+        if d != 28673:
+            assert_grads_close(got.cpu().numpy(), ref, A, y, x, depth, 16, "wide")
+        else:                                                        # as above without the check of the floor's size
+            bound = 1e-5 * np.abs(ref[0]) + gradient_rounding_floor(A[0], y[0], x, depth, 16)
+            assert np.all(np.abs(got.cpu().numpy()[0] - ref[0]) <= bound)
+        assert torch.equal(got, h.local_grad(to_gpu(torch, x)))
+        rows = torch.arange(m, dtype=torch.int32, device="cuda").repeat(n, 1).contiguous()
+        h.set_minibatch(rows)
+        assert torch.equal(got, h.local_grad(to_gpu(torch, x))), "all rows in order"
+        if m > 1:
+            rows[:, 0] = m                                           # contributes nothing
+            part = h.local_grad(to_gpu(torch, x)).cpu().numpy()
+            z = A[:, 0].astype(np.float64) @ x.astype(np.float64)
+            one = (-y[:, 0] / (1 + np.exp(y[:, 0] * z)))[:, None] * A[:, 0].astype(np.float64) / m
+            assert np.all(np.abs(part - (ref - one)) <= 1e-5 * np.abs(ref).max() + 1e-6)
+
+
 @pytest.mark.parametrize("n,d,m,nnz", [(3, 64, 30, 7), (4, 5000, 200, 50), (2, 50_000, 100, 500), (2, 1000, 40, 130)])
 def test_csr_gradient(gpu, oracle, n, d, m, nnz):
     torch, binding = gpu
