@@ -56,7 +56,10 @@ constexpr int wide_rows() {                               // rows per group
     return NQ <= 2 ? 4 : (NQ <= 4 ? 2 : 1);
 }
 
-// Chunks per workgroup: where a group is one row, half as many rows per chain of additions.
+// Chains of additions are kept short.  Where a group is one row: two chunks per workgroup, half as many rows each.
+// Elsewhere x is in registers and LDS is free: every kFoldGroups groups the accumulators move to LDS (a slot per
+// thread, no barrier).  Error of the gradient of n = 8, m = 2000, d = 12000 against 64 bits: 1.1e-7 without the fold.
+constexpr int kFoldGroups = 8;
 template <int NQ>
 constexpr int wide_chunks() {
     return wide_rows<NQ>() == 1 ? 2 : 1;
@@ -73,7 +76,10 @@ __global__ __launch_bounds__(kWideThreads) void logreg_dense_wide_kernel(const f
     constexpr int R = wide_rows<NQ>();
     constexpr bool kXLds = NQ >= 5;
     __shared__ float sums[2][R][kWideWaves];
+    constexpr bool kFold = R > 1;
+    static_assert(!(kXLds && kFold), "x and the folded sums do not both fit LDS");
     __shared__ float4 x_lds[kXLds ? NQ * kWideThreads : 1];
+    __shared__ float4 folded[kFold ? NQ * kWideThreads : 1];
     const int64_t worker = blockIdx.y;
     const int tid = threadIdx.x, wave = tid / kWave, lane = lane_id();
     const float *xw = x + worker * x_stride;
@@ -95,6 +101,7 @@ __global__ __launch_bounds__(kWideThreads) void logreg_dense_wide_kernel(const f
             if constexpr (!kXLds) xr[q][t] = xq[t];
         }
         if constexpr (kXLds) x_lds[q * kWideThreads + tid] = make_float4(xq[0], xq[1], xq[2], xq[3]);   // own use only
+        if constexpr (kFold) folded[q * kWideThreads + tid] = make_float4(0.f, 0.f, 0.f, 0.f);
     }
 
     // the block's chunks of rows; each leaves its own partial sums
@@ -125,7 +132,7 @@ __global__ __launch_bounds__(kWideThreads) void logreg_dense_wide_kernel(const f
     float yl[R], y_next[R];
     bool live[R], live_next[R];
     load(l0, av, yl, live);
-    int buf = 0;
+    int buf = 0, unfolded = 0;
     for (int64_t l = l0; l < l1; l += R, buf ^= 1) {
         load(l + R, next, y_next, live_next);
 #pragma unroll
@@ -181,6 +188,21 @@ __global__ __launch_bounds__(kWideThreads) void logreg_dense_wide_kernel(const f
             }
         }
         const bool end_of_chunk = l + R >= l1 || (kChunks > 1 && l + R == (chunk + 1) * rows_per_chunk);
+        if (kFold && (++unfolded == kFoldGroups || end_of_chunk)) {
+            unfolded = 0;
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) {
+                float4 f = folded[q * kWideThreads + tid];
+                f.x += acc[q][0];
+                f.y += acc[q][1];
+                f.z += acc[q][2];
+                f.w += acc[q][3];
+                folded[q * kWideThreads + tid] = f;
+                const float back[4] = {f.x, f.y, f.z, f.w};
+#pragma unroll
+                for (int t = 0; t < 4; ++t) acc[q][t] = end_of_chunk ? back[t] : 0.f;
+            }
+        }
         if (end_of_chunk) {
             float *out = part + (worker * chunks + chunk) * d;
 #pragma unroll
@@ -203,11 +225,13 @@ __global__ __launch_bounds__(kWideThreads) void logreg_dense_wide_kernel(const f
 }
 
 // Rows of a worker are cut so that all workers together have about one workgroup per compute unit, at least four
-// rows each (a chunk's partial sums cost as much traffic as one of its rows, written and read again).
+// rows each (a chunk's partial sums cost as much traffic as one of its rows, written and read again).  Never more
+// chunks per worker than the partial sums have room for (max_chunks: one from n = 257 on).
 DensePlan wide_plan(int32_t n, int64_t m, int chunks_per_wg) {
     int64_t target = 256 / n;
     if (target < 1) target = 1;
     target *= chunks_per_wg;
+    if (target > max_chunks(n, m)) target = max_chunks(n, m);
     int64_t rows = (m + target - 1) / target;
     if (rows < 4) rows = 4;
     return {rows, (m + rows - 1) / rows};

@@ -77,7 +77,10 @@ def test_dense_gradient(gpu, oracle, n, d, m):
 # out of range; the last two take the two passes again
 @pytest.mark.parametrize("n,d,m", [(1, 4100, 1), (2, 4101, 9), (2, 8192, 13), (3, 8194, 7), (2, 12288, 31), (1, 12291, 5),
                                    (2, 16384, 6), (2, 16385, 6), (1, 20481, 10), (2, 24578, 5), (300, 4097, 3),
-                                   (1, 28672, 11), (1, 28673, 4), (2, 3, 5)])
+                                   (1, 28672, 11), (1, 28673, 4), (2, 3, 5),
+                                   # one block of rows per worker: more groups than between two folds of the sums,
+                                   # and no second chunk where there is room for one only
+                                   (300, 4100, 37), (257, 8196, 19), (257, 16388, 8)])
 def test_dense_gradient_wide_rows(gpu, oracle, n, d, m):
     torch, binding = gpu
     print(f"wide dense grad case n={n} d={d} m={m}", flush=True)
