@@ -128,6 +128,8 @@ struct ef21_ctx {
     // power iteration of ef21_theory_stepsize (allocated by the first call)
     float *power_v = nullptr;       // [n + 2][d]
     double *power_stats = nullptr;  // [n + 1][2]
+    void *gram_ws = nullptr;        // the same on Gram matrices: their tiles, the matrices, the vectors
+    size_t gram_bytes = 0;
     Timing timing;
 };
 
@@ -214,6 +216,7 @@ void free_ctx(ef21_ctx *c) {
     (void)hipFree(c->plus_bm);
     (void)hipFree(c->power_v);
     (void)hipFree(c->power_stats);
+    (void)hipFree(c->gram_ws);
     delete c;
 }
 
@@ -584,29 +587,46 @@ static int enqueue_gram_product(ef21_ctx *c, const float *v, int64_t v_stride, f
     return EF21_OK;
 }
 
+// Whether the power iteration runs on Gram matrices; the handle's workspace for them is then large enough.  It is
+// grown on demand; where there is no memory for it the iteration runs with A.
+static bool use_gram(ef21_ctx *c, int32_t iterations) {
+    if (c->kind != kDense) return false;
+    const size_t bytes = ef21::gram_power_bytes(c->n, c->m, c->d, iterations);
+    if (bytes == 0) return false;
+    if (bytes <= c->gram_bytes) return true;
+    (void)hipStreamSynchronize(c->stream);           // an error shows again at the call's own wait
+    (void)hipFree(c->gram_ws);
+    c->gram_ws = nullptr;
+    c->gram_bytes = 0;
+    if (hipMalloc(&c->gram_ws, bytes) != hipSuccess) {
+        (void)hipGetLastError();
+        c->gram_ws = nullptr;
+        return false;
+    }
+    c->gram_bytes = bytes;
+    return true;
+}
+
 int ef21_theory_stepsize(ef21_handle h, int32_t iterations, double *gamma, double *L, double *L_i) {
     if (int rc = check_handle(h)) return rc;
     if (h->kind == kNone) return fail(EF21_ESTATE, "no problem attached (ef21_set_problem_dense / _csr)");
     if (iterations < 1 || iterations > 1000000) return fail(EF21_EINVAL, "iterations must be in [1, 10^6]");
     const int32_t n = h->n;
     const int64_t d = h->d;
+    const bool gram = use_gram(h, iterations);
     // rows 0..n-1: the workers' vectors; row n: the vector of the whole problem; row n+1: its product
-    if (!h->power_v) {
-        if (hipMalloc((void **)&h->power_v, sizeof(float) * (size_t)(n + 2) * (size_t)d) != hipSuccess ||
-            hipMalloc((void **)&h->power_stats, sizeof(double) * 2 * (size_t)(n + 1)) != hipSuccess) {
-            (void)hipGetLastError();
-            (void)hipFree(h->power_v);
-            h->power_v = nullptr;
-            h->power_stats = nullptr;
-            return fail(EF21_ENOMEM, "hipMalloc of the power iteration's vectors failed");
-        }
+    if ((!h->power_stats && hipMalloc((void **)&h->power_stats, sizeof(double) * 2 * (size_t)(n + 1)) != hipSuccess) ||
+        (!gram && !h->power_v && hipMalloc((void **)&h->power_v, sizeof(float) * (size_t)(n + 2) * (size_t)d) != hipSuccess)) {
+        (void)hipGetLastError();
+        return fail(EF21_ENOMEM, "hipMalloc of the power iteration's vectors failed");
     }
     float *v = h->power_v;
     double *stats = h->power_stats;
-    float *v_all = v + (size_t)n * d, *w_all = v_all + d;
+    float *v_all = gram ? nullptr : v + (size_t)n * d, *w_all = gram ? nullptr : v_all + d;
     int rc = EF21_OK;
-    hipError_t st = ef21::launch_power_start(v, n + 1, d, h->stream);
-    for (int32_t it = 0; it < iterations && st == hipSuccess && rc == EF21_OK; ++it) {
+    hipError_t st = gram ? ef21::launch_gram_power(h->A, n, h->m, d, iterations, h->gram_ws, stats, h->stream)
+                         : ef21::launch_power_start(v, n + 1, d, h->stream);
+    for (int32_t it = 0; !gram && it < iterations && st == hipSuccess && rc == EF21_OK; ++it) {
         rc = enqueue_gram_product(h, v, d, h->grad);                         // w_i = (1/m) A_i^T A_i v_i
         if (rc != EF21_OK) break;
         st = ef21::launch_power_step(h->grad, v, n, d, stats, h->stream);

@@ -45,6 +45,16 @@ __device__ __forceinline__ float loss_derivative(float y, float z, int loss) {
     return loss == 1 /* kLossLeastSquares */ ? 2.0f * (z - y) : -y / (1.0f + expf(y * z));
 }
 
+// Entry j of the power iteration's fixed start vector number `row`: positive, in [0.5, 1.5) from an integer hash of the
+// position so that no two neighbours are alike, times scale = 1 / sqrt(d) (the vector's length is within [0.5, 1.5)).
+__device__ __forceinline__ float power_start_entry(int64_t row, int64_t j, float scale) {
+    uint32_t h = (uint32_t)j * 2654435761u + 0x9e3779b9u * (uint32_t)(row + 1);
+    h ^= h >> 15;
+    h *= 2246822519u;
+    h ^= h >> 13;
+    return (0.5f + (float)(h >> 8) * (1.0f / 16777216.0f)) * scale;
+}
+
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
     for (int o = kWave / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);

@@ -1,0 +1,479 @@
+// The power iteration of ef21_theory_stepsize on the workers' Gram matrices G_i = (1/m) A_i^T A_i (d x d), for dense
+// problems with few columns.  Iterating with A reads the whole problem twice per iteration (once for the workers'
+// vectors, once for the common one) in six launches; G_i is formed once per call on the matrix cores and an iteration
+// is then a d x d product.
+//
+//   gram_tile     G_i in tiles of 32 x 32 on and above the diagonal: v_mfma_f64_16x16x4, products of the fp32 entries
+//                 and their sums in fp64.  Rows are cut into chunks so that the chip is full; four wavefronts of a
+//                 workgroup share a chunk.
+//   gram_finish   the chunks added, divided by m, rounded to fp32 once and written to both halves; one more matrix is
+//                 the mean over the workers, G = (1/(nm)) sum_i A_i^T A_i.
+//   d <= 320:     ONE launch runs all iterations, a workgroup of 1024 threads per matrix.  G sits in registers (a
+//                 compute unit has 512 KB of them: 100 entries per thread at d = 320), the vector in LDS; a wavefront
+//                 multiplies its rows of G (columns, by symmetry) and the sixteen partial vectors are added in LDS.
+//   d <= 1024:    a launch per iteration; every workgroup normalises the previous vector for itself (d entries) and
+//                 multiplies 32 rows of G.
+// Vectors, products with G, sums and norms are in fp64; G is the only thing rounded to fp32, so the constants are
+// closer to the exact ones than through fp32 products with A.
+#include <utility>
+
+#include "device_utils.h"
+#include "kernels.h"
+
+namespace ef21 {
+namespace {
+
+typedef double v4d __attribute__((ext_vector_type(4)));
+
+constexpr int kTile = 32;                            // rows and columns of a tile of G
+constexpr int kTileThreads = 256, kTileWaves = kTileThreads / kWave;
+constexpr int kTileEntries = kTile * kTile;
+constexpr int kStepRows = 4;                         // rows of A per matrix instruction
+constexpr int64_t kXcds = 8;                         // workgroups go round them one by one
+constexpr int kAhead = 4;                            // instructions' rows whose loads are in flight
+
+constexpr int kResThreads = 1024, kResWaves = kResThreads / kWave;
+constexpr int64_t kResidentMax = 5 * kWave;          // columns (six would need 144 registers for G alone)
+constexpr int64_t kGramMax = 1024;
+constexpr int32_t kItersPerLaunch = 4096;            // of the resident kernel: bounds a launch to some ten milliseconds
+
+constexpr int kMvThreads = 256, kMvWaves = kMvThreads / kWave, kMvRowsPerWave = 8;
+constexpr int kMvRows = kMvWaves * kMvRowsPerWave;
+static_assert(kMvRows == kTile, "G is padded to whole tiles, so a workgroup's rows all exist");
+
+struct GramPlan {
+    int64_t nb, pairs;              // tiles per side, tiles on and above the diagonal
+    int64_t ld;                     // rows and row length of a padded G
+    int64_t rows_per_chunk, chunks;
+};
+
+// Enough workgroups to fill the chip four deep, at least 256 rows (16 matrix instructions per wavefront and
+// accumulator) each; up to three chunks more where that spreads the (worker, chunk) units evenly over the XCDs.
+GramPlan gram_plan(int32_t n, int64_t m, int64_t d) {
+    GramPlan p;
+    p.nb = (d + kTile - 1) / kTile;
+    p.pairs = p.nb * (p.nb + 1) / 2;
+    p.ld = p.nb * kTile;
+    int64_t chunks = 1024 / (n * p.pairs);
+    if (chunks > m / 256) chunks = m / 256;
+    if (chunks < 1) chunks = 1;
+    const int64_t least = chunks;
+    int64_t best = kXcds;
+    for (int64_t c = least; c < least + 4 && (c == least || c <= m / 256); ++c) {
+        const int64_t idle = (kXcds - n * c % kXcds) % kXcds;
+        if (idle < best) {
+            best = idle;
+            chunks = c;
+        }
+    }
+    p.rows_per_chunk = (m + chunks - 1) / chunks;
+    p.chunks = (m + p.rows_per_chunk - 1) / p.rows_per_chunk;
+    return p;
+}
+
+// tile number -> (I, J), I <= J: J (J + 1) / 2 + I
+__device__ __forceinline__ void tile_of(int32_t pair, int32_t *I, int32_t *J) {
+    int32_t j = (int32_t)((sqrtf(8.0f * (float)pair + 1.0f) - 1.0f) * 0.5f);
+    while (j * (j + 1) / 2 > pair) --j;
+    while ((j + 1) * (j + 2) / 2 <= pair) ++j;
+    *J = j;
+    *I = pair - j * (j + 1) / 2;
+}
+
+// part[worker][chunk][pair][32][32] = sum over the chunk's rows of a_l[I's columns] a_l[J's columns]^T.
+// Operand of v_mfma_f64_16x16x4: lane j holds row j / 16 of the four and column j % 16 of the sixteen; result
+// register v of lane j is entry (j / 16 + 4 v, j % 16).  Bound by the matrix cores: four instructions (256 clocks of a
+// SIMD) per four loads of 64-byte pieces, whose addresses are a scalar base and a constant offset per lane.  Columns
+// past d repeat column 0; what they add up to is dropped by gram_finish_kernel.
+__global__ __launch_bounds__(kTileThreads) void gram_tile_kernel(const float *__restrict__ A, int64_t m, int64_t d,
+                                                                 int64_t rows_per_chunk, int64_t chunks, int64_t units,
+                                                                 int64_t pairs, double *__restrict__ part) {
+    __shared__ double red[kTileWaves][kTileEntries];
+    // all tiles of a unit (a worker's chunk of rows) on one XCD: its L2 then fetches the rows once
+    const int64_t turn = blockIdx.x / kXcds, unit = turn / pairs * kXcds + blockIdx.x % kXcds;
+    if (unit >= units) return;                       // the whole workgroup
+    const int64_t pair = turn % pairs, chunk = unit % chunks, worker = unit / chunks;
+    const int wave = threadIdx.x / kWave, lane = lane_id();
+    int32_t I, J;
+    tile_of((int32_t)pair, &I, &J);
+    const int64_t l0 = chunk * rows_per_chunk;
+    const int64_t rows = l0 + rows_per_chunk < m ? rows_per_chunk : m - l0;
+    // matrix instruction s of a wavefront takes rows 16 s + 4 wave .. of the chunk
+    constexpr int kStride = kTileWaves * kStepRows;
+    const char *base = reinterpret_cast<const char *>(A + (worker * m + l0) * d);
+    const int32_t my_row = wave * kStepRows + lane / 16;
+    uint32_t off[4];                                 // bytes: two groups of sixteen columns of I, two of J
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        const int32_t c = (t < 2 ? I : J) * kTile + (t & 1) * 16 + (lane & 15);
+        off[t] = 4u * (uint32_t)(my_row * (int32_t)d + (c < d ? c : 0));
+    }
+    const int64_t step_bytes = 4 * kStride * d;
+    v4d acc[2][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[i][j] = (v4d){0.0, 0.0, 0.0, 0.0};
+    auto multiply = [&](const float (&v)[4]) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+                acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)v[i], (double)v[2 + j], acc[i][j], 0, 0, 0);
+    };
+    const int64_t groups = rows / (kAhead * kStride);           // of kAhead instructions, all rows inside the chunk
+    auto load_group = [&](int64_t g, float (&v)[kAhead][4]) {
+        const char *p = base + g * kAhead * step_bytes;
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) v[u][t] = *reinterpret_cast<const float *>(p + u * step_bytes + off[t]);
+    };
+    if (groups > 0) {
+        float v[kAhead][4], next[kAhead][4];
+        load_group(0, v);
+        for (int64_t g = 0; g < groups; ++g) {
+            load_group(g + 1 < groups ? g + 1 : g, next);
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) multiply(v[u]);
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u)
+#pragma unroll
+                for (int t = 0; t < 4; ++t) v[u][t] = next[u][t];
+        }
+    }
+    for (int64_t r0 = groups * kAhead * kStride; r0 < rows; r0 += kStride) {      // the rest; a row past the chunk is zero
+        const bool live = r0 + my_row < rows;
+        float v[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            v[t] = *reinterpret_cast<const float *>(base + (live ? r0 * d * 4 + off[t] : 0));
+            if (!live) v[t] = 0.f;
+        }
+        multiply(v);
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                red[wave][(i * 16 + lane / 16 + 4 * r) * kTile + j * 16 + (lane & 15)] = acc[i][j][r];
+    __syncthreads();
+    double *out = part + (unit * pairs + pair) * kTileEntries;
+    for (int e = threadIdx.x; e < kTileEntries; e += kTileThreads)
+        out[e] = ((red[0][e] + red[1][e]) + red[2][e]) + red[3][e];
+}
+
+// Matrix `which` of n + 1 (the last one: the mean over the workers): the partial sums in order, scaled, rounded once.
+__global__ __launch_bounds__(kTileThreads) void gram_finish_kernel(const double *__restrict__ part, int64_t chunks,
+                                                                   int64_t pairs, int64_t d, int64_t ld, double m,
+                                                                   float *__restrict__ G) {
+    constexpr int kPer = kTileEntries / kTileThreads, kInFlight = 4;
+    __shared__ float tile[kTile][kTile + 1];
+    const int64_t pair = blockIdx.x, which = blockIdx.y, n = gridDim.y - 1;
+    const bool mean = which == n;
+    const int64_t count = mean ? n * chunks : chunks;
+    const double *src = part + ((mean ? 0 : which * chunks) * pairs + pair) * kTileEntries;
+    double s[kPer] = {};
+    for (int64_t b = 0; b < count; b += kInFlight) {
+        double v[kInFlight][kPer];
+#pragma unroll
+        for (int u = 0; u < kInFlight; ++u) {
+            const int64_t at = b + u < count ? b + u : b;
+#pragma unroll
+            for (int q = 0; q < kPer; ++q) v[u][q] = src[at * pairs * kTileEntries + threadIdx.x + q * kTileThreads];
+        }
+#pragma unroll
+        for (int u = 0; u < kInFlight; ++u)
+#pragma unroll
+            for (int q = 0; q < kPer; ++q) s[q] += b + u < count ? v[u][q] : 0.0;
+    }
+    const double scale = mean ? m * (double)n : m;
+    int32_t I, J;
+    tile_of((int32_t)pair, &I, &J);
+    float *out = G + which * ld * ld;
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+        const int e = threadIdx.x + q * kTileThreads, r = e / kTile, c = e % kTile;
+        const float g = I * kTile + r < d && J * kTile + c < d ? (float)(s[q] / scale) : 0.f;
+        tile[r][c] = g;
+        out[((int64_t)I * kTile + r) * ld + (int64_t)J * kTile + c] = g;
+    }
+    if (I == J) return;                              // symmetric by itself (the products commute)
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+        const int e = threadIdx.x + q * kTileThreads, r = e / kTile, c = e % kTile;
+        out[((int64_t)J * kTile + r) * ld + (int64_t)I * kTile + c] = tile[c][r];
+    }
+}
+
+__device__ __forceinline__ double wave_sum_f64(double v) {
+#pragma unroll
+    for (int o = kWave / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
+    return v;
+}
+
+// v[row][0..ld): the start vectors (zero past d)
+__global__ __launch_bounds__(kTileThreads) void gram_start_kernel(double *__restrict__ v, int64_t d, int64_t ld) {
+    const int64_t row = blockIdx.y, j = (int64_t)blockIdx.x * kTileThreads + threadIdx.x;
+    if (j < ld) v[row * ld + j] = j < d ? (double)power_start_entry(row, j, rsqrtf((float)d)) : 0.0;
+}
+
+// 1 / |w|, or 0 for w = 0 (the vector then stays zero, as do the norms that follow)
+__device__ __forceinline__ double inverse_norm(double sum_sq) { return sum_sq == 0.0 ? 0.0 : 1.0 / sqrt(sum_sq); }
+
+// All iterations of one matrix.  NC: columns / 64.  w (one entry per thread) is the product of the iteration before,
+// w = G w' / |w'|, whose length is the estimate; the division happens after the product, so that an iteration holds two
+// barriers.  G is scaled by a power of two to a trace of about one (products of G with w are of the order of its
+// square).  fp32 products were measured too (1.8 us an iteration at d = 300 against 2.9): where the top eigenvalues nearly
+// coincide the constants then end up further from the exact ones than by iterating with A.
+// state [matrix][ld]: w between launches.
+template <int NC>
+__global__ __launch_bounds__(kResThreads) void gram_resident_kernel(const float *__restrict__ G, int64_t d, int64_t ld,
+                                                                    int32_t iterations, bool first,
+                                                                    double *__restrict__ state,
+                                                                    double2 *__restrict__ stats) {
+    constexpr int kCols = NC * kWave, NR = kCols / kResWaves;        // rows of G per wavefront
+    constexpr int kLds = NC == 5 ? 4 : 0, kReg = NR - kLds;          // five: four of the twenty rows in LDS, or registers spill
+    static_assert(kReg % 2 == 0 && (kLds == 0 || kLds == 4), "rows go in pairs, those in LDS as one float4 per column");
+    __shared__ double part[kResWaves][kCols], sums[kResWaves];
+    __shared__ __attribute__((aligned(16))) double vec[kCols];
+    __shared__ float4 g_lds[kLds ? kResWaves : 1][kLds ? kCols : 1];
+    const int tid = threadIdx.x, wave = tid / kWave, lane = lane_id();
+    const float *g = G + (int64_t)blockIdx.x * ld * ld;
+    // sum over the workgroup of the threads below kCols (whole wavefronts; the others pass zeros)
+    auto norm_part = [&](double x) {
+        if (tid < kCols) {
+            const double s = wave_sum_f64(x);
+            if (lane == 0) sums[wave] = s;
+        }
+    };
+    auto total = [&]() {
+        double s = 0.0;
+#pragma unroll
+        for (int q = 0; q < NC; ++q) s += sums[q];
+        return s;
+    };
+    norm_part(tid < ld ? (double)g[(int64_t)tid * ld + tid] : 0.0);
+    __syncthreads();
+    const double trace = total();
+    int exponent = 0;
+    if (trace > 0.0 && trace < 1e300) (void)frexp(trace, &exponent);
+    const float scale = ldexpf(1.0f, -exponent > 126 ? 126 : (-exponent < -126 ? -126 : -exponent));
+    float gr[kReg][NC];
+#pragma unroll
+    for (int i = 0; i < NR; ++i)
+#pragma unroll
+        for (int j = 0; j < NC; ++j) {
+            const int r = wave * NR + i, c = lane + j * kWave;
+            const float e = r < ld && c < ld ? g[(int64_t)r * ld + c] * scale : 0.f;
+            if (i < kReg) gr[i < kReg ? i : 0][j] = e;
+            else reinterpret_cast<float *>(&g_lds[kLds ? wave : 0][kLds ? c : 0])[i - kReg] = e;   // read by the same lane only
+        }
+    double *vr = state + (int64_t)blockIdx.x * ld;
+    double w = 0.0;
+    if (first) w = tid < d ? (double)power_start_entry(blockIdx.x, tid, rsqrtf((float)d)) : 0.0;
+    else if (tid < ld) w = vr[tid];
+    __syncthreads();                                 // the trace has been read
+    for (int32_t it = 0; it < iterations; ++it) {
+        norm_part(w * w);
+        if (tid < kCols) vec[tid] = w;
+        __syncthreads();
+        double acc[NC] = {};
+#pragma unroll
+        for (int i = 0; i < kReg; i += 2) {          // LDS reads cost as much as the products: two entries at a time
+            const double2 x = *reinterpret_cast<const double2 *>(vec + wave * NR + i);
+#pragma unroll
+            for (int j = 0; j < NC; ++j) {           // converted here: hoisted out of the loop, G would take twice the
+                asm("" : "+v"(gr[i][j]), "+v"(gr[i + 1][j]));                    // registers
+                acc[j] = fma((double)gr[i][j], x.x, acc[j]);
+                acc[j] = fma((double)gr[i + 1][j], x.y, acc[j]);
+            }
+            __builtin_amdgcn_sched_barrier(0);       // no more than two rows' operands at a time
+        }
+        if constexpr (kLds != 0) {
+            const double2 x0 = *reinterpret_cast<const double2 *>(vec + wave * NR + kReg);
+            const double2 x1 = *reinterpret_cast<const double2 *>(vec + wave * NR + kReg + 2);
+#pragma unroll
+            for (int j = 0; j < NC; ++j) {
+                const float4 e = g_lds[wave][lane + j * kWave];
+                acc[j] = fma((double)e.x, x0.x, acc[j]);
+                acc[j] = fma((double)e.y, x0.y, acc[j]);
+                acc[j] = fma((double)e.z, x1.x, acc[j]);
+                acc[j] = fma((double)e.w, x1.y, acc[j]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < NC; ++j) part[wave][lane + j * kWave] = acc[j];
+        double inv = 0.0;
+        if (tid < kCols) inv = inverse_norm(total());
+        __syncthreads();
+        if (tid < kCols) {
+            double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
+#pragma unroll
+            for (int q = 0; q < kResWaves; q += 4) {
+                s0 += part[q][tid];
+                s1 += part[q + 1][tid];
+                s2 += part[q + 2][tid];
+                s3 += part[q + 3][tid];
+            }
+            w = ((s0 + s1) + (s2 + s3)) * inv;
+        }
+    }
+    if (tid < ld) vr[tid] = w;
+    norm_part(w * w);                                // stats[matrix] = (0, the estimate)
+    __syncthreads();
+    if (tid == 0) stats[blockIdx.x] = make_double2(0.0, sqrt(total()) / (double)scale);
+}
+
+// One iteration: w = G v / |v|.  Grid (ld / 32, matrices).
+__global__ __launch_bounds__(kMvThreads) void gram_matvec_kernel(const float *__restrict__ G, int64_t ld,
+                                                                 const double *__restrict__ v, double *__restrict__ w) {
+    constexpr int kMaxPer = (int)kGramMax / kMvThreads, kQuads = (int)kGramMax / (4 * kWave), kTogether = 2;
+    __shared__ double vec[kGramMax], sums[kMvWaves];
+    const int64_t which = blockIdx.y;
+    const int tid = threadIdx.x, wave = tid / kWave, lane = lane_id();
+    const double *vr = v + which * ld;
+    double x[kMaxPer], sq = 0.0;
+#pragma unroll
+    for (int q = 0; q < kMaxPer; ++q) {
+        const int j = tid + q * kMvThreads;
+        x[q] = j < ld ? vr[j] : 0.0;
+        sq += x[q] * x[q];
+    }
+    sq = wave_sum_f64(sq);
+    if (lane == 0) sums[wave] = sq;
+    __syncthreads();
+    sq = 0.0;
+#pragma unroll
+    for (int q = 0; q < kMvWaves; ++q) sq += sums[q];
+    const double inv = inverse_norm(sq);
+#pragma unroll
+    for (int q = 0; q < kMaxPer; ++q) vec[tid + q * kMvThreads] = x[q] * inv;
+    __syncthreads();
+    const int64_t r0 = (int64_t)blockIdx.x * kMvRows + wave * kMvRowsPerWave;
+    const float *g = G + (which * ld + r0) * ld;
+#pragma unroll
+    for (int i0 = 0; i0 < kMvRowsPerWave; i0 += kTogether) {
+        float4 a[kTogether][kQuads];
+#pragma unroll
+        for (int i = 0; i < kTogether; ++i)
+#pragma unroll
+            for (int q = 0; q < kQuads; ++q) {
+                const int64_t c = 4 * (lane + q * kWave);            // ld is a multiple of 32
+                a[i][q] = c < ld ? *reinterpret_cast<const float4 *>(g + (i0 + i) * ld + c) : make_float4(0.f, 0.f, 0.f, 0.f);
+            }
+#pragma unroll
+        for (int i = 0; i < kTogether; ++i) {
+            double s = 0.0;
+#pragma unroll
+            for (int q = 0; q < kQuads; ++q) {
+                const int c = 4 * (lane + q * kWave);
+                s = fma((double)a[i][q].x, vec[c], s);
+                s = fma((double)a[i][q].y, vec[c + 1], s);
+                s = fma((double)a[i][q].z, vec[c + 2], s);
+                s = fma((double)a[i][q].w, vec[c + 3], s);
+            }
+            s = wave_sum_f64(s);
+            if (lane == 0) w[which * ld + r0 + i0 + i] = s;
+        }
+    }
+}
+
+// stats[row] = (0, |w|): what the last iteration multiplied was a unit vector.  One wavefront per row.
+__global__ __launch_bounds__(kWave) void gram_norm_kernel(const double *__restrict__ w, int64_t ld,
+                                                          double2 *__restrict__ stats) {
+    const double *r = w + (int64_t)blockIdx.x * ld;
+    double s = 0.0;
+    for (int64_t j = threadIdx.x; j < ld; j += kWave) s += r[j] * r[j];
+    s = wave_sum_f64(s);
+    if (threadIdx.x == 0) stats[blockIdx.x] = make_double2(0.0, sqrt(s));
+}
+
+struct GramWs {
+    double *part;                   // [n][chunks][pairs][32][32]
+    float *G;                       // [n + 1][ld][ld]
+    double *v, *w;                  // [n + 1][ld] each
+};
+
+size_t gram_layout(int32_t n, const GramPlan &p, char *base, GramWs *ws) {
+    size_t off = 0;
+    auto take = [&](size_t bytes) {
+        char *at = base ? base + off : nullptr;
+        off += (bytes + 255) / 256 * 256;
+        return at;
+    };
+    char *pt = take(sizeof(double) * (size_t)n * p.chunks * p.pairs * kTileEntries);
+    char *g = take(sizeof(float) * (size_t)(n + 1) * p.ld * p.ld);
+    char *v = take(sizeof(double) * (size_t)(n + 1) * p.ld);
+    char *w = take(sizeof(double) * (size_t)(n + 1) * p.ld);
+    if (ws) *ws = GramWs{(double *)pt, (float *)g, (double *)v, (double *)w};
+    return off;
+}
+
+constexpr size_t kGramWsMax = (size_t)1 << 30;
+
+template <int NC>
+void launch_resident(const GramWs &ws, int32_t n, int64_t d, int64_t ld, int32_t iterations, double *stats, hipStream_t stream) {
+    for (int32_t done = 0; done < iterations; done += kItersPerLaunch) {
+        const int32_t now = iterations - done < kItersPerLaunch ? iterations - done : kItersPerLaunch;
+        hipLaunchKernelGGL(gram_resident_kernel<NC>, dim3((unsigned)(n + 1)), dim3(kResThreads), 0, stream, ws.G, d, ld, now,
+                           done == 0, ws.v, (double2 *)stats);
+    }
+}
+
+}  // namespace
+
+size_t gram_power_bytes(int32_t n, int64_t m, int64_t d, int32_t iterations) {
+    if (d > kGramMax || n > 65534) return 0;
+    const GramPlan p = gram_plan(n, m, d);
+    const size_t bytes = gram_layout(n, p, nullptr, nullptr);
+    if (bytes > kGramWsMax) return 0;
+    // Microseconds: forming the matrices and one iteration on them, against one iteration with A (six launches).
+    // Measured: forming 134 (n = 20, m = 2487, d = 300), 332 (2, 7500, 1000), 415 (32, 468, 1000); an iteration by
+    // gram_matvec_kernel 7.5 (10, 3000, 500), 8.7 (2, 7500, 1000), 31 (32, 468, 1000); with A 27 (4, 250, 100),
+    // 45 (15, 1000, 1000), 62 (2, 7500, 1000), 93 (32, 8000, 50).
+    const double nn = n, ld = (double)p.ld;
+    const double form = 30.0 + nn * (double)m * ld * ld / 40e6;
+    const double with_g = d <= kResidentMax ? 2.5 : 6.5 + 4.0 * (nn + 1.0) * ld * ld / 4.4e6;
+    const double with_a = 26.0 + 8.0 * nn * (double)m * (double)d / 3.5e6;
+    return form + iterations * with_g < iterations * with_a ? bytes : 0;
+}
+
+hipError_t launch_gram_power(const float *A, int32_t n, int64_t m, int64_t d, int32_t iterations, void *workspace,
+                             double *stats, hipStream_t stream) {
+    const GramPlan p = gram_plan(n, m, d);
+    if (d > kGramMax || p.chunks > 65535 || n > 65534) return hipErrorInvalidValue;
+    GramWs ws;
+    gram_layout(n, p, (char *)workspace, &ws);
+    const int64_t units = n * p.chunks;
+    hipLaunchKernelGGL(gram_tile_kernel, dim3((unsigned)((units + kXcds - 1) / kXcds * kXcds * p.pairs)), dim3(kTileThreads),
+                       0, stream, A, m, d, p.rows_per_chunk, p.chunks, units, p.pairs, ws.part);
+    hipLaunchKernelGGL(gram_finish_kernel, dim3((unsigned)p.pairs, (unsigned)(n + 1)), dim3(kTileThreads), 0, stream, ws.part,
+                       p.chunks, p.pairs, d, p.ld, (double)m, ws.G);
+    if (d <= kResidentMax) {
+        switch ((d + kWave - 1) / kWave) {
+            case 1: launch_resident<1>(ws, n, d, p.ld, iterations, stats, stream); break;
+            case 2: launch_resident<2>(ws, n, d, p.ld, iterations, stats, stream); break;
+            case 3: launch_resident<3>(ws, n, d, p.ld, iterations, stats, stream); break;
+            case 4: launch_resident<4>(ws, n, d, p.ld, iterations, stats, stream); break;
+            default: launch_resident<5>(ws, n, d, p.ld, iterations, stats, stream); break;
+        }
+        return hipGetLastError();
+    }
+    hipLaunchKernelGGL(gram_start_kernel, dim3((unsigned)((p.ld + kTileThreads - 1) / kTileThreads), (unsigned)(n + 1)),
+                       dim3(kTileThreads), 0, stream, ws.v, d, p.ld);
+    double *from = ws.v, *to = ws.w;
+    for (int32_t it = 0; it < iterations; ++it) {
+        hipLaunchKernelGGL(gram_matvec_kernel, dim3((unsigned)(p.ld / kMvRows), (unsigned)(n + 1)), dim3(kMvThreads), 0, stream,
+                           ws.G, p.ld, from, to);
+        std::swap(from, to);
+    }
+    hipLaunchKernelGGL(gram_norm_kernel, dim3((unsigned)(n + 1)), dim3(kWave), 0, stream, from, p.ld, (double2 *)stats);
+    return hipGetLastError();
+}
+
+}  // namespace ef21

@@ -2,6 +2,7 @@
 // of f) that the stepsize of Theorem 1 is made of.  The products w = (1/m) A_i^T A_i v come from the gradient
 // kernels (per-row loss z^2 / 2); this file holds the start vector and the step v <- w / |w| with the two
 // numbers it yields, v^T w and |w| (both at most the largest eigenvalue for a unit v, |w| the closer one).
+// (Dense problems with few columns: gram_power.hip.)
 #include "device_utils.h"
 #include "kernels.h"
 
@@ -27,18 +28,12 @@ __device__ double block_sum_f64(double v, double *lds) {
     return t;
 }
 
-// A fixed start vector of unit length with every entry positive and no two neighbours alike: entries in
-// [0.5, 1.5) from an integer hash of the position, scaled by 1 / sqrt(d) (its length is then within [0.5, 1.5)).
 __global__ __launch_bounds__(kThreads) void power_start_kernel(float *__restrict__ v, int64_t d) {
     const int64_t row = blockIdx.y;
     const float scale = rsqrtf((float)d);
     const int64_t stride = (int64_t)gridDim.x * kThreads;
     for (int64_t j = (int64_t)blockIdx.x * kThreads + threadIdx.x; j < d; j += stride) {
-        uint32_t h = (uint32_t)j * 2654435761u + 0x9e3779b9u * (uint32_t)(row + 1);
-        h ^= h >> 15;
-        h *= 2246822519u;
-        h ^= h >> 13;
-        v[row * d + j] = (0.5f + (float)(h >> 8) * (1.0f / 16777216.0f)) * scale;
+        v[row * d + j] = power_start_entry(row, j, scale);
     }
 }
 

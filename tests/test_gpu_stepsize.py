@@ -125,3 +125,53 @@ def test_argument_errors(gpu):
             h.theory_stepsize(0)
         gamma, L, L_i = h.theory_stepsize(3)                      # rank one: lambda_max = |a|^2 = 16 exactly
         assert L_i == pytest.approx([4.0, 4.0], rel=1e-6) and L == pytest.approx(4.0, rel=1e-6)
+
+
+def power_values(A, steps):
+    """|w| / |v| after `steps` steps of the power iteration per worker and for the whole problem, in fp64 from the
+    library's start vectors (fp32 values)."""
+    n, m, d = A.shape
+    A = A.astype(np.float64)
+    G = [a.T @ a / m for a in A]
+    G.append(sum(G) / n)
+    out = []
+    for row, g in enumerate(G):
+        h = (np.arange(d, dtype=np.uint64) * 2654435761 + 0x9e3779b9 * (row + 1)) & 0xffffffff
+        h ^= h >> 15
+        h = (h * 2246822519) & 0xffffffff
+        h ^= h >> 13
+        v = (0.5 + (h >> 8).astype(np.float64) / 16777216.0) / np.sqrt(d)
+        for _ in range(steps):
+            w = g @ v
+            value = np.linalg.norm(w) / np.linalg.norm(v)
+            v = w / value if value > 0 else v
+        out.append(value)
+    return np.array(out)
+
+
+# both forms of the iteration on Gram matrices (one launch, up to 320 columns; a launch per step, up to 1024) at the
+# ends of their tiles, one row, ragged chunks of rows, several chunks, and the first size past them
+@pytest.mark.parametrize("n,d,m", [(1, 1, 1), (2, 31, 7), (3, 32, 300), (1, 33, 1), (2, 64, 1025), (2, 65, 515),
+                                   (2, 129, 33), (5, 192, 64), (2, 193, 2), (3, 256, 770), (2, 257, 9), (2, 319, 40),
+                                   (3, 320, 64), (2, 321, 31), (2, 352, 700), (1, 1023, 17), (2, 1024, 260), (1, 1025, 16)])
+def test_power_iteration_value(gpu, n, d, m):
+    """Non-negative features: every entry of the Gram matrix is a sum of positive terms, so rounding it to fp32 moves
+    |G v| by at most 2^-24 of itself; the start vector and the product with A (1025 columns) add roundings of that
+    size, which the iteration averages: 1e-6 after one to forty steps."""
+    torch, binding = gpu
+    print(f"power iteration n={n} d={d} m={m}", flush=True)
+    rng = np.random.default_rng(d * 7 + m)
+    A = rng.random((n, m, d)).astype(np.float32) * np.linspace(0.5, 2.0, n)[:, None, None].astype(np.float32)
+    t = np.zeros((n, m), dtype=np.float32)
+    with binding.EF21(n, d, 1, 0.1) as h:
+        h.set_problem_dense(to_gpu(torch, A), to_gpu(torch, t), 0.0)
+        for steps in (40, 7, 1):
+            _, L, L_i = h.theory_stepsize(steps)
+            got = 4.0 * np.array(list(L_i) + [L])
+            np.testing.assert_allclose(got, power_values(A, steps), rtol=1e-6, err_msg=f"{steps} steps")
+        h.set_problem_dense(to_gpu(torch, 3.0 * A), to_gpu(torch, t), 0.0)     # new data behind the same handle
+        _, L, L_i = h.theory_stepsize(40)
+        np.testing.assert_allclose(4.0 * np.array(list(L_i) + [L]), power_values(3.0 * A, 40), rtol=1e-6)
+        h.set_problem_dense(to_gpu(torch, 0.0 * A), to_gpu(torch, t), 0.0)
+        _, L, L_i = h.theory_stepsize(40)
+        assert L == 0.0 and not np.any(L_i)
