@@ -102,7 +102,7 @@ void plan(int32_t n, int64_t d, Ws *w) {
     const int64_t pieces = g * kBlkWaves;
     int64_t L = (d + pieces - 1) / pieces;
     L = (L + 2047) / 2048 * 2048;            // whole load groups (4 steps of 64 lanes x 4 entries), and whole
-                                             // blocks of the aggregation's message index (256 or 2048 coordinates)
+                                             // blocks of the aggregation's message index (256 or 512 coordinates)
     w->L = L;
     w->nslot = (d + L - 1) / L;
     w->G = (w->nslot + kBlkWaves - 1) / kBlkWaves;

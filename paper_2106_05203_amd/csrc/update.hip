@@ -78,7 +78,7 @@ __global__ __launch_bounds__(kThreads) void mean_rows_vec4_kernel(const float *_
 // adds the workers' runs one after the other into its LDS accumulator (positions inside a message are
 // distinct, so a plain read-add-write is enough, and a single wavefront needs no barrier between
 // workers): the sum runs in worker order, g is bitwise reproducible, and no global atomic is issued.
-constexpr int kAggSub = 2048;
+constexpr int kAggSub = 512;
 constexpr int kAggWaves = kThreads / kWave;
 
 __global__ __launch_bounds__(kThreads) void message_index_kernel(const int32_t *__restrict__ idx, int64_t k,
@@ -131,37 +131,55 @@ __device__ __forceinline__ void add_runs(const int32_t *__restrict__ idx, const 
     }
 }
 
-template <bool STEP, bool VEC4>
+// What bounds it: the bytes of g and x, provided the wavefront waits for memory once and not once per 256 columns, so
+// g and x are fetched whole into registers before the runs are added, by enough wavefronts: blocks of 512 columns fill
+// the chip from 10^5 columns on, and a worker's run fits the 64 lanes up to a tenth of the entries kept.  (Blocks of 2048
+// without the prefetch: 18.4 us against 8.5 at d = 1000003, n = 5, k = 50000; 45.9 against 45.4 at d = 11.2 million, where
+// the 180 MB of g and x at the rate of a plain copy take 39; blocks of 2048 with it: 50.)
+// vec: g and x 16-byte aligned (a block starts at a multiple of 512 columns whatever d is); the last, partial block
+// and unaligned vectors go column by column.
+template <bool STEP>
 __global__ __launch_bounds__(kThreads) void aggregate_kernel(const int32_t *__restrict__ idx,
                                                              const float *__restrict__ val,
                                                              const int32_t *__restrict__ start, int32_t n, int64_t k,
                                                              int64_t d, int64_t nblk, float *__restrict__ g,
-                                                             float *__restrict__ x, float inv_n, float neg_gamma) {
-    __shared__ float lds[kAggWaves][kAggSub];
+                                                             float *__restrict__ x, float inv_n, float neg_gamma,
+                                                             bool vec) {
+    constexpr int kPer = kAggSub / (4 * kWave);
+    __shared__ __attribute__((aligned(16))) float lds[kAggWaves][kAggSub];
     const int wave = threadIdx.x / kWave, lane = lane_id();
     const int64_t b = (int64_t)blockIdx.x * kAggWaves + wave;
     if (b >= nblk) return;
     float *acc = lds[wave];
     const int64_t c0 = b * kAggSub;
     const int64_t c1 = c0 + kAggSub < d ? c0 + kAggSub : d;
-    for (int j = lane; j < kAggSub; j += kWave) acc[j] = 0.f;
+    const bool whole = vec && c0 + kAggSub <= d;
+    float4 g4[kPer], x4[kPer];
+    if (whole) {
+#pragma unroll
+        for (int q = 0; q < kPer; ++q) {
+            g4[q] = *reinterpret_cast<const float4 *>(g + c0 + 4 * (q * kWave + lane));
+            if (STEP) x4[q] = *reinterpret_cast<const float4 *>(x + c0 + 4 * (q * kWave + lane));
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) *reinterpret_cast<float4 *>(acc + 4 * (q * kWave + lane)) = make_float4(0.f, 0.f, 0.f, 0.f);
     add_runs(idx, val, start, nblk, b, k, 0, n, acc, c0, lane);
-    if (VEC4) {
-        for (int64_t j = c0 + lane * 4; j < c1; j += kWave * 4) {
-            const float4 a4 = *reinterpret_cast<const float4 *>(acc + (j - c0));
-            float4 g4 = *reinterpret_cast<const float4 *>(g + j);
-            g4.x = fmaf(a4.x, inv_n, g4.x);
-            g4.y = fmaf(a4.y, inv_n, g4.y);
-            g4.z = fmaf(a4.z, inv_n, g4.z);
-            g4.w = fmaf(a4.w, inv_n, g4.w);
-            *reinterpret_cast<float4 *>(g + j) = g4;
+    if (whole) {
+#pragma unroll
+        for (int q = 0; q < kPer; ++q) {
+            const float4 a4 = *reinterpret_cast<const float4 *>(acc + 4 * (q * kWave + lane));
+            g4[q].x = fmaf(a4.x, inv_n, g4[q].x);
+            g4[q].y = fmaf(a4.y, inv_n, g4[q].y);
+            g4[q].z = fmaf(a4.z, inv_n, g4[q].z);
+            g4[q].w = fmaf(a4.w, inv_n, g4[q].w);
+            *reinterpret_cast<float4 *>(g + c0 + 4 * (q * kWave + lane)) = g4[q];
             if (STEP) {
-                float4 x4 = *reinterpret_cast<const float4 *>(x + j);
-                x4.x = fmaf(neg_gamma, g4.x, x4.x);
-                x4.y = fmaf(neg_gamma, g4.y, x4.y);
-                x4.z = fmaf(neg_gamma, g4.z, x4.z);
-                x4.w = fmaf(neg_gamma, g4.w, x4.w);
-                *reinterpret_cast<float4 *>(x + j) = x4;
+                x4[q].x = fmaf(neg_gamma, g4[q].x, x4[q].x);
+                x4[q].y = fmaf(neg_gamma, g4[q].y, x4[q].y);
+                x4[q].z = fmaf(neg_gamma, g4[q].z, x4[q].z);
+                x4[q].w = fmaf(neg_gamma, g4[q].w, x4[q].w);
+                *reinterpret_cast<float4 *>(x + c0 + 4 * (q * kWave + lane)) = x4[q];
             }
         }
     } else {
@@ -338,9 +356,9 @@ bool aggregate_is_small(int32_t n, int64_t k, int64_t d) {
 }  // namespace
 
 int aggregate_index_shift(int32_t n, int64_t k, int64_t d) {
-    static_assert(kManySub == 1 << 8 && kAggSub == 1 << 11, "block lengths as shifts");
+    static_assert(kManySub == 1 << 8 && kAggSub == 1 << 9, "block lengths as shifts");
     if (aggregate_is_small(n, k, d)) return -1;
-    return n >= kManyWorkers ? 8 : 11;
+    return n >= kManyWorkers ? 8 : 9;
 }
 
 hipError_t launch_aggregate(const int32_t *idx, const float *val, int32_t n, int64_t k, int64_t d, float *g, float *x,
@@ -374,19 +392,13 @@ hipError_t launch_aggregate(const int32_t *idx, const float *val, int32_t n, int
         hipLaunchKernelGGL(message_index_kernel, dim3((unsigned)((k + kThreads - 1) / kThreads), (unsigned)n),
                            dim3(kThreads), 0, stream, idx, k, nblk, kAggSub, start);
     const dim3 grid((unsigned)((nblk + kAggWaves - 1) / kAggWaves)), block(kThreads);
-    const bool vec4 = (d % 4 == 0) && (((uintptr_t)g | (uintptr_t)(x ? x : g)) % 16 == 0);
-    if (x && vec4)
-        hipLaunchKernelGGL((aggregate_kernel<true, true>), grid, block, 0, stream, idx, val, start, n, k, d, nblk, g, x,
-                           inv_n, -gamma);
-    else if (x)
-        hipLaunchKernelGGL((aggregate_kernel<true, false>), grid, block, 0, stream, idx, val, start, n, k, d, nblk, g, x,
-                           inv_n, -gamma);
-    else if (vec4)
-        hipLaunchKernelGGL((aggregate_kernel<false, true>), grid, block, 0, stream, idx, val, start, n, k, d, nblk, g, x,
-                           inv_n, -gamma);
+    const bool vec = ((uintptr_t)g | (uintptr_t)(x ? x : g)) % 16 == 0;
+    if (x)
+        hipLaunchKernelGGL(aggregate_kernel<true>, grid, block, 0, stream, idx, val, start, n, k, d, nblk, g, x, inv_n, -gamma,
+                           vec);
     else
-        hipLaunchKernelGGL((aggregate_kernel<false, false>), grid, block, 0, stream, idx, val, start, n, k, d, nblk, g,
-                           x, inv_n, -gamma);
+        hipLaunchKernelGGL(aggregate_kernel<false>, grid, block, 0, stream, idx, val, start, n, k, d, nblk, g, x, inv_n, -gamma,
+                           vec);
     return hipGetLastError();
 }
 
