@@ -726,17 +726,13 @@ static int enqueue_classic_ef(ef21_ctx *h, const float *grads, const ef21::Marke
     hipError_t st = ef21::launch_ef_accumulate(grads, h->g_i, h->n, h->d, h->gamma, h->stream);   // p_i over e_i
     mk(ef21::K_PLUS);
     if (st != hipSuccess) return fail_hip(st, "EF accumulation launch");
-    ef21::TopkArgs p{h->g_i, nullptr, h->n, h->d, h->k, h->msg_idx, h->msg_val, nullptr};            // w_i = C(p_i)
+    ef21::TopkArgs p{h->g_i, nullptr, h->n, h->d, h->k, h->msg_idx, h->msg_val, h->g_i};   // w_i = C(p_i), e_i = p_i - w_i
     p.warm = 1;
     bool index_ready = false;
     want_message_index(h, &p);
     if (int rc = enqueue_topk(p, h->topk_ws, h->stream, mk, &index_ready)) return rc;
-    st = ef21::launch_ef_clear_kept(h->msg_idx, h->n, h->k, h->g_i, h->d, h->stream);               // e_i = p_i - w_i
-    if (st == hipSuccess) st = ef21::launch_fill_zero(h->g, h->d, h->stream);
-    mk(ef21::K_PLUS);
-    if (st != hipSuccess) return fail_hip(st, "EF error update launch");
     st = ef21::launch_aggregate(h->msg_idx, h->msg_val, h->n, h->k, h->d, h->g, h->x, 1.0f, h->agg_index,
-                                h->stream, index_ready);                                            // x - mean w
+                                h->stream, index_ready, true);                                      // x - mean w
     mk(ef21::K_MODEL_STEP);
     if (st != hipSuccess) return fail_hip(st, "aggregation launch");
     return EF21_OK;

@@ -66,8 +66,9 @@ struct GradParts {
 // Arguments of one batched Top-k (Section 2.1) over n rows of length d.
 //   a, b      v = a - b if b != nullptr (the difference of Algorithm 2, line 5), else v = a
 //   out_idx, out_val   [n][k] ascending positions and signed values
-//   g_i       if != nullptr (then b must be the same array) the kept entries also update the workers'
-//             estimators in place (Algorithm 2, line 6): g_i[row][j] = b[row][j] + v
+//   g_i       if != nullptr the kept entries also update the workers' state in place:
+//             b != nullptr (then g_i is the same array): g_i[row][j] = b[row][j] + v (Algorithm 2, line 6)
+//             b == nullptr (then g_i is the same array as a): g_i[row][j] = 0 (Algorithm 4, e_i = p_i - w_i)
 struct TopkArgs {
     const float *a;
     const float *b;
@@ -132,8 +133,10 @@ hipError_t launch_model_step(float *x, const float *g, int64_t d, float gamma, h
 // index_ready: the caller has already written the index (launch_topk_split can); otherwise a kernel of the call does.
 size_t aggregate_index_bytes(int32_t n, int64_t d);
 int aggregate_index_shift(int32_t n, int64_t k, int64_t d);
+// from_zero: g is not read, (1/n) sum_i c_i is written.
 hipError_t launch_aggregate(const int32_t *idx, const float *val, int32_t n, int64_t k, int64_t d, float *g, float *x,
-                            float gamma, void *index, hipStream_t stream, bool index_ready = false);
+                            float gamma, void *index, hipStream_t stream, bool index_ready = false,
+                            bool from_zero = false);
 
 // g = (1/n) sum_i g_i (input line of Algorithm 2), summed in worker order.
 hipError_t launch_mean_rows(const float *g_i, float *g, int32_t n, int64_t d, hipStream_t stream);
@@ -211,10 +214,8 @@ size_t gram_power_bytes(int32_t n, int64_t m, int64_t d, int32_t iterations);
 hipError_t launch_gram_power(const float *A, int32_t n, int64_t m, int64_t d, int32_t iterations, void *workspace,
                              double *stats, hipStream_t stream);
 
-// Algorithm 4 (EF): e <- e + gamma s over all n * d entries; e <- 0 at the kept positions idx [n][k]; v <- 0.
+// Algorithm 4 (EF): e <- e + gamma s over all n * d entries.
 hipError_t launch_ef_accumulate(const float *s, float *e, int32_t n, int64_t d, float gamma, hipStream_t stream);
-hipError_t launch_ef_clear_kept(const int32_t *idx, int32_t n, int64_t k, float *e, int64_t d, hipStream_t stream);
-hipError_t launch_fill_zero(float *v, int64_t d, hipStream_t stream);
 
 // Plain streaming kernels for measuring what the HBM delivers: one read of `n16` 16-byte words (their sum goes
 // to sink[0]), and a copy.

@@ -78,7 +78,7 @@ __global__ __launch_bounds__(kRowThreads) void small_step_kernel(SmallArgs a) {
     {
         TopkArgs p{nullptr, a.g_i, a.n, a.d, a.k, a.msg_idx, a.msg_val, a.g_i,
                    GradParts{a.part, a.chunks, a.m, a.x, a.lambda}};
-        row_topk_parts<true>(s, cache, p, worker);
+        row_topk_parts<kAddUpdate>(s, cache, p, worker);
     }
     if (!draw_ticket(&a.tickets[a.n], (uint32_t)a.n, &last)) return;      // all messages, or done
 

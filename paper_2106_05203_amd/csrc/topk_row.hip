@@ -5,26 +5,26 @@
 // fix the key T of the k-th largest magnitude and the number q of entries equal to T that are
 // still needed; an ordered emission then writes every entry with key > T and the first q
 // entries with key == T, in ascending position order (ties go to the lower index).
-// With `g_i != nullptr` the emission also applies line 6 of Algorithm 2.
+// With `g_i != nullptr` the emission also updates the workers' state (TopkArgs::g_i).
 #include "topk_row_impl.h"
 
 namespace ef21 {
 namespace {
 
-template <bool DIFF, bool UPDATE>
+template <bool DIFF, int UPDATE>
 __global__ __launch_bounds__(kRowThreads) void topk_row_kernel(TopkArgs p) {
     __shared__ RowShared s;
     row_topk<DIFF, UPDATE>(s, p, blockIdx.x);
 }
 
-template <bool DIFF, bool UPDATE>
+template <bool DIFF, int UPDATE>
 __global__ __launch_bounds__(kRowThreads) void topk_row_cached_kernel(TopkArgs p) {
     __shared__ RowShared s;
     __shared__ float cache[kRowCache];
     row_topk_cached<DIFF, UPDATE>(s, cache, p, blockIdx.x);
 }
 
-template <bool UPDATE>
+template <int UPDATE>
 __global__ __launch_bounds__(kRowThreads) void topk_row_parts_kernel(TopkArgs p) {
     __shared__ RowShared s;
     __shared__ float cache[kRowCache];
@@ -36,21 +36,23 @@ __global__ __launch_bounds__(kRowThreads) void topk_row_parts_kernel(TopkArgs p)
 hipError_t launch_topk_row(const TopkArgs &p, hipStream_t stream) {
     const dim3 grid((unsigned)p.n), block(kRowThreads);
     const bool diff = p.b != nullptr, upd = p.g_i != nullptr;
-    if (upd && !diff) return hipErrorInvalidValue;   // line 6 needs the subtracted g_i
+    if (upd && p.g_i != (diff ? p.b : p.a)) return hipErrorInvalidValue;
     if (p.parts.part) {
         if (!diff || p.d > kRowCache) return hipErrorInvalidValue;
-        if (upd) hipLaunchKernelGGL((topk_row_parts_kernel<true>), grid, block, 0, stream, p);
-        else hipLaunchKernelGGL((topk_row_parts_kernel<false>), grid, block, 0, stream, p);
+        if (upd) hipLaunchKernelGGL((topk_row_parts_kernel<kAddUpdate>), grid, block, 0, stream, p);
+        else hipLaunchKernelGGL((topk_row_parts_kernel<kNoUpdate>), grid, block, 0, stream, p);
         return hipGetLastError();
     }
     if (p.d <= kRowCache) {
-        if (upd) hipLaunchKernelGGL((topk_row_cached_kernel<true, true>), grid, block, 0, stream, p);
-        else if (diff) hipLaunchKernelGGL((topk_row_cached_kernel<true, false>), grid, block, 0, stream, p);
-        else hipLaunchKernelGGL((topk_row_cached_kernel<false, false>), grid, block, 0, stream, p);
+        if (upd && diff) hipLaunchKernelGGL((topk_row_cached_kernel<true, kAddUpdate>), grid, block, 0, stream, p);
+        else if (upd) hipLaunchKernelGGL((topk_row_cached_kernel<false, kClearUpdate>), grid, block, 0, stream, p);
+        else if (diff) hipLaunchKernelGGL((topk_row_cached_kernel<true, kNoUpdate>), grid, block, 0, stream, p);
+        else hipLaunchKernelGGL((topk_row_cached_kernel<false, kNoUpdate>), grid, block, 0, stream, p);
     } else {
-        if (upd) hipLaunchKernelGGL((topk_row_kernel<true, true>), grid, block, 0, stream, p);
-        else if (diff) hipLaunchKernelGGL((topk_row_kernel<true, false>), grid, block, 0, stream, p);
-        else hipLaunchKernelGGL((topk_row_kernel<false, false>), grid, block, 0, stream, p);
+        if (upd && diff) hipLaunchKernelGGL((topk_row_kernel<true, kAddUpdate>), grid, block, 0, stream, p);
+        else if (upd) hipLaunchKernelGGL((topk_row_kernel<false, kClearUpdate>), grid, block, 0, stream, p);
+        else if (diff) hipLaunchKernelGGL((topk_row_kernel<true, kNoUpdate>), grid, block, 0, stream, p);
+        else hipLaunchKernelGGL((topk_row_kernel<false, kNoUpdate>), grid, block, 0, stream, p);
     }
     return hipGetLastError();
 }

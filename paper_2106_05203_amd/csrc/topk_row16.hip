@@ -67,6 +67,11 @@ constexpr int kChunks = (int)((kRow16Max / 8 + kRowThreads - 1) / kRowThreads); 
 constexpr int kListMax = 4096;                 // gathered entries (step 3) ...
 constexpr int kWordMax = 4096;                 // ... and 16-byte words that hold one
 
+__device__ void general_row(RowShared &s, const TopkArgs &p, int64_t row) {
+    if (p.g_i) row_topk<false, kClearUpdate>(s, p, row);
+    else row_topk<false, kNoUpdate>(s, p, row);
+}
+
 template <bool VEC4>
 __global__ __launch_bounds__(kRowThreads) void topk_row16_kernel(TopkArgs p) {
     __shared__ Shared16 sh;
@@ -203,7 +208,7 @@ __global__ __launch_bounds__(kRowThreads) void topk_row16_kernel(TopkArgs p) {
     __syncthreads();
     const uint32_t n_words = sh.n_words;
     if (n_words > (uint32_t)kWordMax) {                      // (n_list would overflow as well)
-        row_topk<false, false>(s, p, row);
+        general_row(s, p, row);
         return;
     }
     for (uint32_t i0 = 0; i0 < n_words; i0 += kRowThreads) {
@@ -231,7 +236,7 @@ __global__ __launch_bounds__(kRowThreads) void topk_row16_kernel(TopkArgs p) {
     __syncthreads();
     const uint32_t n_list = s.ncand;                         // >= k
     if (n_list > (uint32_t)kListMax) {                       // very many equal magnitudes: the general kernel
-        row_topk<false, false>(s, p, row);
+        general_row(s, p, row);
         return;
     }
 
@@ -272,7 +277,7 @@ __global__ __launch_bounds__(kRowThreads) void topk_row16_kernel(TopkArgs p) {
         __syncthreads();
     }
     if (in_bin > (uint32_t)kCandMax) {                       // still crowded: the general kernel re-reads the row
-        row_topk<false, false>(s, p, row);
+        general_row(s, p, row);
         return;
     }
 
@@ -364,6 +369,7 @@ __global__ __launch_bounds__(kRowThreads) void topk_row16_kernel(TopkArgs p) {
         const uint32_t at = prefix[e >> 5] + (uint32_t)__popc(bitmap[e >> 5] & ((1u << (e & 31u)) - 1u));
         out_idx[at] = (int32_t)e;
         out_val[at] = a[e];
+        if (p.g_i) p.g_i[row * p.d + e] = 0.f;               // Algorithm 4
     }
 }
 
@@ -384,7 +390,7 @@ hipError_t launch(const TopkArgs &p, hipStream_t stream) {
 }  // namespace
 
 hipError_t launch_topk_row16(const TopkArgs &p, hipStream_t stream) {
-    if (p.b || p.g_i || p.parts.part || p.d > kRow16Max || p.d < kRow16Min || p.k > kRow16MaxK)
+    if (p.b || (p.g_i && p.g_i != p.a) || p.parts.part || p.d > kRow16Max || p.d < kRow16Min || p.k > kRow16MaxK)
         return hipErrorInvalidValue;
     const bool vec4 = (p.d % 4 == 0) && ((uintptr_t)p.a % 16 == 0);
     return vec4 ? launch<true>(p, stream) : launch<false>(p, stream);

@@ -37,6 +37,9 @@ struct RowShared {
 };
 static_assert(kRankMax <= 0xffff, "two counts of at most kRankMax share one word");
 
+// What the emission does to TopkArgs::g_i at a kept position.
+enum UpdateMode { kNoUpdate = 0, kAddUpdate = 1 /* line 6 of Algorithm 2 */, kClearUpdate = 2 /* Algorithm 4 */ };
+
 template <bool DIFF>
 __device__ __forceinline__ float load_v(const float *a, const float *b, int64_t e) {
     float v = a[e];
@@ -121,9 +124,10 @@ __device__ void rank_gathered(RowShared &s, uint32_t need) {
 }
 
 // Whole Top-k of one row by the calling workgroup (all kRowThreads threads must call).
-// value(e) yields entry e of the row (the same bits every time it is asked); with UPDATE the emission
-// also applies line 6 of Algorithm 2, g_i[e] = base(e) + value(e), base(e) being the subtracted g_i[e].
-template <bool UPDATE, class ValueFn, class BaseFn>
+// value(e) yields entry e of the row (the same bits every time it is asked); with kAddUpdate the emission
+// also applies line 6 of Algorithm 2, g_i[e] = base(e) + value(e), base(e) being the subtracted g_i[e], with
+// kClearUpdate it sets g_i[e] to zero (value(e) of that position is not asked for afterwards).
+template <int UPDATE, class ValueFn, class BaseFn>
 __device__ void row_topk_on(RowShared &s, const TopkArgs &p, int64_t row, ValueFn value, BaseFn base_value) {
     const int64_t d = p.d;
 
@@ -200,7 +204,7 @@ __device__ void row_topk_on(RowShared &s, const TopkArgs &p, int64_t row, ValueF
 
     int32_t *out_idx = p.out_idx + row * p.k;
     float *out_val = p.out_val + row * p.k;
-    float *g_i = UPDATE ? p.g_i + row * d : nullptr;
+    float *g_i = UPDATE != kNoUpdate ? p.g_i + row * d : nullptr;
     for (int64_t base = lo; base < hi; base += kWave) {
         const int64_t e = base + lane;
         const bool in = e < hi;
@@ -216,7 +220,8 @@ __device__ void row_topk_on(RowShared &s, const TopkArgs &p, int64_t row, ValueF
             const uint32_t pos = out_run + lanes_below(m_gt) + ties_taken_before;
             out_idx[pos] = (int32_t)e;
             out_val[pos] = v;
-            if (UPDATE) g_i[e] = base_value(e) + v;    // Algorithm 2, line 6
+            if (UPDATE == kAddUpdate) g_i[e] = base_value(e) + v;    // Algorithm 2, line 6
+            if (UPDATE == kClearUpdate) g_i[e] = 0.f;
         }
         const uint32_t eq_next = eq_run + popc64(m_eq);
         out_run += popc64(m_gt) + ((eq_next < q ? eq_next : q) - (eq_run < q ? eq_run : q));
@@ -225,7 +230,7 @@ __device__ void row_topk_on(RowShared &s, const TopkArgs &p, int64_t row, ValueF
 }
 
 // The row read from global memory in every pass (any d).
-template <bool DIFF, bool UPDATE>
+template <bool DIFF, int UPDATE>
 __device__ void row_topk(RowShared &s, const TopkArgs &p, int64_t row) {
     const float *a = p.a + row * p.d;
     const float *b = DIFF ? p.b + row * p.d : nullptr;
@@ -236,7 +241,7 @@ __device__ void row_topk(RowShared &s, const TopkArgs &p, int64_t row) {
 // Rows of at most kRowCache entries: the row is formed once into LDS (`cache`), all passes read it there.
 constexpr int kRowCache = (int)kRowPartsMax;
 
-template <bool DIFF, bool UPDATE>
+template <bool DIFF, int UPDATE>
 __device__ void row_topk_cached(RowShared &s, float *cache, const TopkArgs &p, int64_t row) {
     const int64_t d = p.d;
     const float *a = p.a + row * d;
@@ -248,7 +253,7 @@ __device__ void row_topk_cached(RowShared &s, float *cache, const TopkArgs &p, i
 }
 
 // Same, the row being grad f_i - g_i with the gradient still in partial sums (p.parts).
-template <bool UPDATE>
+template <int UPDATE>
 __device__ void row_topk_parts(RowShared &s, float *cache, const TopkArgs &p, int64_t row) {
     const int64_t d = p.d;
     const float *part_w = p.parts.part + row * p.parts.chunks * d;

@@ -50,7 +50,16 @@ static_assert(kCandThreads == kRowThreads && kBlk == kRowThreads, "the rescue ru
 // 8.3 %) below the previous T and the window half an octave, so a threshold between 0.92 and 1.3 times the
 // previous one is found by the first pass: narrower bins, fewer entries to rank.  A candidate costs little (an
 // 8-byte store), a failed guess a second pass over the row, hence the generous margin.
-constexpr uint32_t kShiftCold = 11, kShiftWarm = 10;
+// That is where many entries are kept.  Where few are there is room in a bin, and the window is wider: T of a
+// heavy-tailed row lies up to an octave above the sample's bound, and a row that failed so once starts from a sample,
+// and can fail again, in every later call (n = 15, d = 5 million, k = 5000, Student-t gradients: up to 3.2 ms an
+// iteration against 0.15, all of it the exact algorithm on one row).  A bin then holds some two hundred entries at most;
+// wider bins everywhere cost the (n = 20, d = 10^6, k = 10^4) call 0.7 us of 33.8 in ranking.
+__device__ __forceinline__ uint32_t cold_shift(int64_t k, int64_t d) {
+    if (k <= 4096) return 13u;                                    // four octaves
+    return k <= 131072 && k * 200 < d ? 12u : 11u;                // two, or one
+}
+__device__ __forceinline__ uint32_t warm_shift(int64_t k, int64_t d) { return cold_shift(k, d) - 1u; }
 constexpr uint32_t kWarmBelow = 1u << 20;
 constexpr int kTieCap = 1024;                // entries of T's bin that are ranked directly (one per thread)
 constexpr int kWarmSlots = 1;                // remembered thresholds per row (TopkArgs::warm = 1 .. kWarmSlots)
@@ -292,12 +301,13 @@ __device__ __forceinline__ void drain_ring(const StageRing &ring, uint32_t flush
         ring_to_slot(ring, flushed, cnt - flushed < 64 ? cnt - flushed : 64, lane, slot, f);
 }
 
-// A wavefront walks its piece in steps of 64*VEC entries (VEC = 4 needs 16-byte aligned rows), U steps per
-// group (VEC = 1: four).  Whole groups are loaded without any bounds check so that all loads of a group
-// are in flight together; only the last piece of a row has a checked tail.
+// A wavefront walks its piece in steps of 256 entries, four per lane and load, U steps per group.  Rows may start at
+// any 4-byte address (rows of odd length: ef21_topk of 10 rows of 3000001, k = 30000, 52.5 us with 4-byte loads, 45 with 16-byte ones).
+// Whole groups are loaded without any bounds check so that all loads of a group are in flight together; only the last
+// piece of a row has a checked tail.
 // MODE: kColdPass key_lo from the sample; kWarmPass from the threshold remembered in slot p.warm if there is
 // one, else from the sample; kSecondPass: only rows whose warm start failed, from the sample, into hist_b.
-template <int VEC, bool DIFF, int MODE, int U>
+template <bool DIFF, int MODE, int U>
 __global__ __launch_bounds__(kBlk) void split_collect_kernel(TopkArgs p, Ws w) {
     __shared__ RowShared s;
     __shared__ StageRing rings[kBlkWaves];
@@ -307,7 +317,7 @@ __global__ __launch_bounds__(kBlk) void split_collect_kernel(TopkArgs p, Ws w) {
     const float *b = DIFF ? p.b + row * d : nullptr;
     RowInfo *info = w.info + row;
     CandFilter f;
-    f.shift = kShiftCold;
+    f.shift = cold_shift(p.k, d);
     f.hist = s.hist;
     uint32_t *merged = w.hist_a + row * kHistBins;
     uint32_t *row_total = &info->M;
@@ -331,7 +341,7 @@ __global__ __launch_bounds__(kBlk) void split_collect_kernel(TopkArgs p, Ws w) {
         if (warm) {
             const uint32_t T = info->warm_T[p.warm - 1];
             f.key_lo = T > kWarmBelow ? T - kWarmBelow : 0u;
-            f.shift = kShiftWarm;
+            f.shift = warm_shift(p.k, d);
         } else {
             f.key_lo = estimate_key_lo<DIFF>(s, a, b, d, p.k);
         }
@@ -358,69 +368,56 @@ __global__ __launch_bounds__(kBlk) void split_collect_kernel(TopkArgs p, Ws w) {
         const int64_t hi = lo + w.L < d ? lo + w.L : d;
         uint2 *slot = w.cand + (row * w.nslot + slot_no) * w.L;
         uint32_t cnt = 0, flushed = 0;
-        constexpr int kStep = kWave * VEC, kUnroll = VEC == 4 ? U : 4, kGroup = kStep * kUnroll;
+        constexpr int VEC = 4, kStep = kWave * VEC, kGroup = kStep * U;
         int64_t base = lo;
-        if constexpr (VEC == 4) {
-            // Groups of U steps, two register buffers: the next group's loads are issued before this group is
-            // filtered, so that a wavefront has loads in flight while it computes.  After the last group the
-            // "next" loads all read the piece's first 16 bytes (one cached line) instead of sitting behind a
-            // branch.  What is in flight per compute unit is 1024 lanes x workgroups per unit x arrays x 2 U x 16
-            // bytes; measured best at 64 to 128 KB (see launch_collect).
-            float4 va[kUnroll], vb[kUnroll];
-            if (base + kGroup <= hi) {
+        // Groups of U steps, two register buffers: the next group's loads are issued before this group is
+        // filtered, so that a wavefront has loads in flight while it computes.  After the last group the
+        // "next" loads all read the piece's first 16 bytes (one cached line) instead of sitting behind a
+        // branch.  What is in flight per compute unit is 1024 lanes x workgroups per unit x arrays x 2 U x 16
+        // bytes; measured best at 64 to 128 KB (see launch_collect).
+        float4 va[U], vb[U];
+        if (base + kGroup <= hi) {
 #pragma unroll
-                for (int u = 0; u < kUnroll; ++u) {
-                    va[u] = stream_load4(a + base + u * kStep + lane * 4);
-                    if constexpr (DIFF) vb[u] = stream_load4(b + base + u * kStep + lane * 4);
-                }
-            }
-            for (; base + kGroup <= hi; base += kGroup) {
-                const bool more = base + 2 * kGroup <= hi;
-                float4 na[kUnroll], nb[kUnroll];
-#pragma unroll
-                for (int u = 0; u < kUnroll; ++u) {
-                    const int64_t at = more ? base + kGroup + u * kStep + lane * 4 : lo;
-                    na[u] = stream_load4(a + at);
-                    if constexpr (DIFF) nb[u] = stream_load4(b + at);
-                }
-#pragma unroll
-                for (int u = 0; u < kUnroll; ++u) {
-                    float v[VEC] = {va[u].x, va[u].y, va[u].z, va[u].w};
-                    if constexpr (DIFF) {
-                        v[0] -= vb[u].x; v[1] -= vb[u].y; v[2] -= vb[u].z; v[3] -= vb[u].w;
-                    }
-                    append_candidates<VEC, true>(v, base + u * kStep + lane * VEC, hi, f, ring, lane, slot, cnt, flushed);
-                }
-#pragma unroll
-                for (int u = 0; u < kUnroll; ++u) {
-                    va[u] = na[u];
-                    if constexpr (DIFF) vb[u] = nb[u];
-                }
-            }
-        } else {
-            for (; base + kGroup <= hi; base += kGroup) {
-                float v[kUnroll][VEC];
-                float vb[kUnroll];
-#pragma unroll
-                for (int u = 0; u < kUnroll; ++u) {
-                    v[u][0] = stream_load(a + base + u * kStep + lane);
-                    if constexpr (DIFF) vb[u] = stream_load(b + base + u * kStep + lane);
-                }
-                if constexpr (DIFF) {
-#pragma unroll
-                    for (int u = 0; u < kUnroll; ++u) v[u][0] -= vb[u];
-                }
-#pragma unroll
-                for (int u = 0; u < kUnroll; ++u)
-                    append_candidates<VEC, true>(v[u], base + u * kStep + lane * VEC, hi, f, ring, lane, slot, cnt, flushed);
+            for (int u = 0; u < U; ++u) {
+                va[u] = stream_load4_any(a + base + u * kStep + lane * 4);
+                if constexpr (DIFF) vb[u] = stream_load4_any(b + base + u * kStep + lane * 4);
             }
         }
-        for (; base < hi; base += kStep) {           // checked tail, entry by entry
-            const int64_t e0 = base + lane * VEC;
-            float v[VEC];
+        for (; base + kGroup <= hi; base += kGroup) {
+            const bool more = base + 2 * kGroup <= hi;
+            float4 na[U], nb[U];
 #pragma unroll
-            for (int t = 0; t < VEC; ++t) v[t] = e0 + t < hi ? load_v<DIFF>(a, b, e0 + t) : 0.f;
-            append_candidates<VEC, false>(v, e0, hi, f, ring, lane, slot, cnt, flushed);
+            for (int u = 0; u < U; ++u) {
+                const int64_t at = more ? base + kGroup + u * kStep + lane * 4 : lo;
+                na[u] = stream_load4_any(a + at);
+                if constexpr (DIFF) nb[u] = stream_load4_any(b + at);
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                float v[VEC] = {va[u].x, va[u].y, va[u].z, va[u].w};
+                if constexpr (DIFF) {
+                    v[0] -= vb[u].x; v[1] -= vb[u].y; v[2] -= vb[u].z; v[3] -= vb[u].w;
+                }
+                append_candidates<VEC, true>(v, base + u * kStep + lane * VEC, hi, f, ring, lane, slot, cnt, flushed);
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                va[u] = na[u];
+                if constexpr (DIFF) vb[u] = nb[u];
+            }
+        }
+        if (base < hi) {                             // checked tail, less than a group, all loads issued first
+            float v[U][VEC];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int t = 0; t < VEC; ++t) {
+                    const int64_t e = base + u * kStep + lane * VEC + t;
+                    v[u][t] = e < hi ? load_v<DIFF>(a, b, e) : 0.f;
+                }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                append_candidates<VEC, false>(v[u], base + u * kStep + lane * VEC, hi, f, ring, lane, slot, cnt, flushed);
         }
         drain_ring(ring, flushed, cnt, lane, slot, f);
         if (lane == 0) {
@@ -449,7 +446,7 @@ __device__ __forceinline__ double wave_sum_f64(double v) {
     return v;
 }
 
-template <int VEC, bool WARM, int U>
+template <bool WARM, int U>
 __global__ __launch_bounds__(kBlk) void split_collect_pair_kernel(TopkArgs pm, Ws wm, int warm_p, Ws wp,
                                                                   double2 *__restrict__ norms) {
     __shared__ RowShared s;                      // its histogram serves the sampling, then the difference
@@ -466,18 +463,18 @@ __global__ __launch_bounds__(kBlk) void split_collect_pair_kernel(TopkArgs pm, W
     if (warm_m) {
         const uint32_t T = info_m->warm_T[pm.warm - 1];
         fm.key_lo = T > kWarmBelow ? T - kWarmBelow : 0u;
-        fm.shift = kShiftWarm;
+        fm.shift = warm_shift(pm.k, d);
     } else {
         fm.key_lo = estimate_key_lo<true>(s, a, b, d, pm.k);
-        fm.shift = kShiftCold;
+        fm.shift = cold_shift(pm.k, d);
     }
     if (warm_pl) {
         const uint32_t T = info_p->warm_T[warm_p - 1];
         fp.key_lo = T > kWarmBelow ? T - kWarmBelow : 0u;
-        fp.shift = kShiftWarm;
+        fp.shift = warm_shift(pm.k, d);
     } else {
         fp.key_lo = estimate_key_lo<false>(s, a, nullptr, d, pm.k);
-        fp.shift = kShiftCold;
+        fp.shift = cold_shift(pm.k, d);
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         info_m->key_lo = fm.key_lo; info_m->shift = fm.shift; info_m->use2 = 0u; info_m->ntie = 0u;
@@ -507,12 +504,12 @@ __global__ __launch_bounds__(kBlk) void split_collect_pair_kernel(TopkArgs pm, W
         uint2 *slot_p = wp.cand + (row * wp.nslot + slot_no) * wp.L;
         uint32_t cnt_m = 0, flushed_m = 0, cnt_p = 0, flushed_p = 0;
         double sq_s = 0.0, sq_v = 0.0;
-        constexpr int kStep = kWave * VEC, kUnroll = VEC == 4 ? U : 4, kGroup = kStep * kUnroll;
+        constexpr int VEC = 4, kStep = kWave * VEC, kGroup = kStep * U;
         int64_t base = lo;
         // one group: the squared norms of line 7, the difference of line 6, both filters
-        auto filter_group = [&](float (&vs)[kUnroll][VEC], float (&vd)[kUnroll][VEC]) {
+        auto filter_group = [&](float (&vs)[U][VEC], float (&vd)[U][VEC]) {
 #pragma unroll
-            for (int u = 0; u < kUnroll; ++u) {
+            for (int u = 0; u < U; ++u) {
 #pragma unroll
                 for (int t = 0; t < VEC; ++t) {
                     const double sv = (double)vs[u][t], dv = sv - (double)vd[u][t];      // exact
@@ -525,64 +522,60 @@ __global__ __launch_bounds__(kBlk) void split_collect_pair_kernel(TopkArgs pm, W
                 append_candidates<VEC, true>(vd[u], e0, hi, fm, ring_m, lane, slot_m, cnt_m, flushed_m);
             }
         };
-        if constexpr (VEC == 4) {
-            // two register buffers, as in split_collect_kernel: the next group's loads before this group's work
-            float4 va[kUnroll], vb[kUnroll];
-            if (base + kGroup <= hi) {
+        // two register buffers, as in split_collect_kernel: the next group's loads before this group's work
+        float4 va[U], vb[U];
+        if (base + kGroup <= hi) {
 #pragma unroll
-                for (int u = 0; u < kUnroll; ++u) {
-                    va[u] = stream_load4(a + base + u * kStep + lane * 4);
-                    vb[u] = stream_load4(b + base + u * kStep + lane * 4);
-                }
-            }
-            for (; base + kGroup <= hi; base += kGroup) {
-                const bool more = base + 2 * kGroup <= hi;
-                float4 na[kUnroll], nb[kUnroll];
-#pragma unroll
-                for (int u = 0; u < kUnroll; ++u) {
-                    const int64_t at = more ? base + kGroup + u * kStep + lane * 4 : lo;
-                    na[u] = stream_load4(a + at);
-                    nb[u] = stream_load4(b + at);
-                }
-                float vs[kUnroll][VEC], vd[kUnroll][VEC];
-#pragma unroll
-                for (int u = 0; u < kUnroll; ++u) {
-                    vs[u][0] = va[u].x; vs[u][1] = va[u].y; vs[u][2] = va[u].z; vs[u][3] = va[u].w;
-                    vd[u][0] = vb[u].x; vd[u][1] = vb[u].y; vd[u][2] = vb[u].z; vd[u][3] = vb[u].w;
-                }
-                filter_group(vs, vd);
-#pragma unroll
-                for (int u = 0; u < kUnroll; ++u) {
-                    va[u] = na[u];
-                    vb[u] = nb[u];
-                }
-            }
-        } else {
-            for (; base + kGroup <= hi; base += kGroup) {
-                float vs[kUnroll][VEC], vd[kUnroll][VEC];
-#pragma unroll
-                for (int u = 0; u < kUnroll; ++u) {
-                    vs[u][0] = stream_load(a + base + u * kStep + lane);
-                    vd[u][0] = stream_load(b + base + u * kStep + lane);
-                }
-                filter_group(vs, vd);
+            for (int u = 0; u < U; ++u) {
+                va[u] = stream_load4_any(a + base + u * kStep + lane * 4);
+                vb[u] = stream_load4_any(b + base + u * kStep + lane * 4);
             }
         }
-        for (; base < hi; base += kStep) {           // checked tail, entry by entry
-            const int64_t e0 = base + lane * VEC;
-            float vs[VEC], vd[VEC];
+        for (; base + kGroup <= hi; base += kGroup) {
+            const bool more = base + 2 * kGroup <= hi;
+            float4 na[U], nb[U];
 #pragma unroll
-            for (int t = 0; t < VEC; ++t) {
-                const bool in = e0 + t < hi;
-                const float sv = in ? a[e0 + t] : 0.f, bv = in ? b[e0 + t] : 0.f;
-                const double dv = (double)sv - (double)bv;
-                sq_s += (double)sv * (double)sv;
-                sq_v += dv * dv;
-                vs[t] = sv;
-                vd[t] = sv - bv;
+            for (int u = 0; u < U; ++u) {
+                const int64_t at = more ? base + kGroup + u * kStep + lane * 4 : lo;
+                na[u] = stream_load4_any(a + at);
+                nb[u] = stream_load4_any(b + at);
             }
-            append_candidates<VEC, false>(vs, e0, hi, fp, ring_p, lane, slot_p, cnt_p, flushed_p);
-            append_candidates<VEC, false>(vd, e0, hi, fm, ring_m, lane, slot_m, cnt_m, flushed_m);
+            float vs[U][VEC], vd[U][VEC];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                vs[u][0] = va[u].x; vs[u][1] = va[u].y; vs[u][2] = va[u].z; vs[u][3] = va[u].w;
+                vd[u][0] = vb[u].x; vd[u][1] = vb[u].y; vd[u][2] = vb[u].z; vd[u][3] = vb[u].w;
+            }
+            filter_group(vs, vd);
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                va[u] = na[u];
+                vb[u] = nb[u];
+            }
+        }
+        if (base < hi) {                             // checked tail, less than a group, all loads issued first
+            float vs[U][VEC], vd[U][VEC];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int t = 0; t < VEC; ++t) {
+                    const int64_t e = base + u * kStep + lane * VEC + t;
+                    vs[u][t] = e < hi ? a[e] : 0.f;
+                    vd[u][t] = e < hi ? b[e] : 0.f;
+                }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+#pragma unroll
+                for (int t = 0; t < VEC; ++t) {
+                    const double sv = (double)vs[u][t], dv = sv - (double)vd[u][t];      // exact
+                    sq_s += sv * sv;
+                    sq_v += dv * dv;
+                    vd[u][t] = vs[u][t] - vd[u][t];
+                }
+                const int64_t e0 = base + u * kStep + lane * VEC;
+                append_candidates<VEC, false>(vs[u], e0, hi, fp, ring_p, lane, slot_p, cnt_p, flushed_p);
+                append_candidates<VEC, false>(vd[u], e0, hi, fm, ring_m, lane, slot_m, cnt_m, flushed_m);
+            }
         }
         drain_ring(ring_p, flushed_p, cnt_p, lane, slot_p, fp);
         drain_ring(ring_m, flushed_m, cnt_m, lane, slot_m, fm);
@@ -612,7 +605,7 @@ __global__ __launch_bounds__(kBlk) void split_collect_pair_kernel(TopkArgs pm, W
 // ---------------------------------------------------------------- count
 // The exact one-workgroup algorithm on the original data for a row whose guess failed, and the message index of
 // the row if the caller asked for one.  All kCandThreads threads of the workgroup must call.
-template <bool DIFF, bool UPDATE>
+template <bool DIFF, int UPDATE>
 __device__ void rescue_row(RowShared &rs, const TopkArgs &p, int64_t row) {
     row_topk<DIFF, UPDATE>(rs, p, row);
     if (p.agg_start) {                  // from the pairs just written
@@ -640,7 +633,7 @@ constexpr int kPre = 4;
 // failed (see the head of the file).  The last workgroup of a row is the rescue: it selects a failed row by the
 // exact one-workgroup algorithm on the original data (DIFF and UPDATE matter here only).  The others: a slot's
 // candidates in bins above T's are counted, those in T's bin go to the tie list.
-template <bool DIFF, bool UPDATE, int kSPW>
+template <bool DIFF, int UPDATE, int kSPW>
 __global__ __launch_bounds__(kCandThreads) void cand_count_kernel(TopkArgs p, Ws w) {
     constexpr int kWgSlots = kCandWaves * kSPW;      // slots per workgroup
     __shared__ RowShared rs;
@@ -770,7 +763,7 @@ __global__ __launch_bounds__(kCandThreads) void cand_count_kernel(TopkArgs p, Ws
 // of index blocks, so every block begins inside exactly one wavefront's span, and that wavefront writes its start:
 // when it keeps the first entry at or beyond the block's first coordinate, or at the end of its span for the
 // blocks that follow its last kept entry (all of them if it kept nothing).
-template <bool DIFF, bool UPDATE>
+template <bool DIFF, int UPDATE>
 struct Emitter {
     const TopkArgs &p;
     int64_t row;
@@ -803,10 +796,9 @@ struct Emitter {
             const float v = __uint_as_float(rec.y);
             out_idx[pos] = (int32_t)rec.x;
             out_val[pos] = v;
-            if constexpr (UPDATE) {                      // Algorithm 2, line 6
-                const int64_t at = row * p.d + (int64_t)rec.x;
-                p.g_i[at] = (DIFF ? (have_b ? b_pre : p.b[at]) : 0.f) + v;
-            }
+            const int64_t at = row * p.d + (int64_t)rec.x;
+            if constexpr (UPDATE == kAddUpdate) p.g_i[at] = (have_b ? b_pre : p.b[at]) + v;      // Algorithm 2, line 6
+            if constexpr (UPDATE == kClearUpdate) p.g_i[at] = 0.f;                               // Algorithm 4
         }
         if (agg_start) {
             const uint64_t m_keep = __ballot(keep);
@@ -842,7 +834,7 @@ struct Emitter {
 // first position that are kept.  Grid (slot blocks + 1, n): the last workgroup of a row is a rescue, for a row
 // whose crowded bin (see RowInfo::tie_min) turned out to hold different keys.  A crowded bin of equal keys needs no
 // list: T is that key, and the ties before a slot are the earlier slots' entries of the bin (slot_inbin).
-template <bool DIFF, bool UPDATE, int kSPW>
+template <bool DIFF, int UPDATE, int kSPW>
 __global__ __launch_bounds__(kCandThreads) void cand_emit_kernel(TopkArgs p, Ws w) {
     constexpr int kWgSlots = kCandWaves * kSPW;      // slots per workgroup
     __shared__ RowShared rs;                     // the rescue's
@@ -889,7 +881,7 @@ __global__ __launch_bounds__(kCandThreads) void cand_emit_kernel(TopkArgs p, Ws 
     // candidates that can be kept (those in T's bin or above: T itself is not known yet) are issued here, with
     // everything else, instead of one step at a time between the stores of the emission.
     float bpre[kSPW][kPre];
-    if constexpr (DIFF && UPDATE) {
+    if constexpr (UPDATE == kAddUpdate) {
         const uint32_t key_lo = ri.use2 != 0u ? ri.key_lo2 : ri.key_lo, shift = ri.use2 != 0u ? ri.shift2 : ri.shift;
 #pragma unroll
         for (int s = 0; s < kSPW; ++s)
@@ -975,7 +967,7 @@ __global__ __launch_bounds__(kCandThreads) void cand_emit_kernel(TopkArgs p, Ws 
             }
 #pragma unroll
             for (int u = 0; u < kPre; ++u) {
-                if constexpr (DIFF && UPDATE) em.step(j0 + u * kWave + lane < cnt[s], c[s][u], j0 == 0, bpre[s][u]);
+                if constexpr (UPDATE == kAddUpdate) em.step(j0 + u * kWave + lane < cnt[s], c[s][u], j0 == 0, bpre[s][u]);
                 else em.step(j0 + u * kWave + lane < cnt[s], c[s][u]);
             }
         }
@@ -989,15 +981,14 @@ __global__ __launch_bounds__(kCandThreads) void zero_words_kernel(uint32_t *p, s
     for (size_t i = (size_t)blockIdx.x * kCandThreads + threadIdx.x; i < words; i += stride) p[i] = 0u;
 }
 
-template <int VEC, bool DIFF, int U>
+template <bool DIFF, int U>
 void launch_collect_u(const TopkArgs &p, const Ws &w, int mode, const dim3 &grid, hipStream_t stream) {
     const dim3 block(kBlk);
-    if (mode == kColdPass) hipLaunchKernelGGL((split_collect_kernel<VEC, DIFF, kColdPass, U>), grid, block, 0, stream, p, w);
-    else if (mode == kWarmPass) hipLaunchKernelGGL((split_collect_kernel<VEC, DIFF, kWarmPass, U>), grid, block, 0, stream, p, w);
-    else hipLaunchKernelGGL((split_collect_kernel<VEC, DIFF, kSecondPass, U>), grid, block, 0, stream, p, w);
+    if (mode == kColdPass) hipLaunchKernelGGL((split_collect_kernel<DIFF, kColdPass, U>), grid, block, 0, stream, p, w);
+    else if (mode == kWarmPass) hipLaunchKernelGGL((split_collect_kernel<DIFF, kWarmPass, U>), grid, block, 0, stream, p, w);
+    else hipLaunchKernelGGL((split_collect_kernel<DIFF, kSecondPass, U>), grid, block, 0, stream, p, w);
 }
 
-template <int VEC, bool DIFF>
 void launch_collect(const TopkArgs &p, const Ws &w, int mode, hipStream_t stream) {
     // the second pass has work only after a failed guess: about 64 workgroups, which loop over the slots
     int64_t g = w.G;
@@ -1006,22 +997,9 @@ void launch_collect(const TopkArgs &p, const Ws &w, int mode, hipStream_t stream
     // Steps per group.  Two arrays and two workgroups per compute unit: one step (128 KB in flight per unit; C4:
     // 138 us against 142 with two steps and 147 without the second buffer); otherwise two (one array, one workgroup
     // per unit, the C1 call: 31.7 us against 36 with one step and 33 with four).
-    if constexpr (VEC == 4 && DIFF) {
-        if (g * p.n > 256) {
-            launch_collect_u<VEC, DIFF, 1>(p, w, mode, grid, stream);
-            return;
-        }
-    }
-    launch_collect_u<VEC, DIFF, 2>(p, w, mode, grid, stream);
-}
-
-void launch_collect_any(const TopkArgs &p, const Ws &w, int mode, hipStream_t stream) {
-    const bool diff = p.b != nullptr;
-    const bool vec4 = (p.d % 4 == 0) && ((uintptr_t)p.a % 16 == 0) && (!diff || (uintptr_t)p.b % 16 == 0);
-    if (vec4 && diff) launch_collect<4, true>(p, w, mode, stream);
-    else if (vec4) launch_collect<4, false>(p, w, mode, stream);
-    else if (diff) launch_collect<1, true>(p, w, mode, stream);
-    else launch_collect<1, false>(p, w, mode, stream);
+    if (p.b != nullptr && g * p.n > 256) launch_collect_u<true, 1>(p, w, mode, grid, stream);
+    else if (p.b != nullptr) launch_collect_u<true, 2>(p, w, mode, grid, stream);
+    else launch_collect_u<false, 2>(p, w, mode, grid, stream);
 }
 
 // ---------------------------------------------------------------- k = 1: the entry of largest magnitude
@@ -1033,7 +1011,7 @@ void launch_collect_any(const TopkArgs &p, const Ws &w, int mode, hipStream_t st
 // the message, applies line 6 and clears the slot.
 constexpr int kArgThreads = 256, kArgWaves = kArgThreads / kWave;
 
-template <int VEC, bool DIFF>
+template <bool DIFF>
 __global__ __launch_bounds__(kArgThreads) void argmax_stream_kernel(TopkArgs p, Ws w, int64_t piece) {
     __shared__ unsigned long long best_of_wave[kArgWaves];
     const int64_t row = blockIdx.y, d = p.d;
@@ -1045,49 +1023,46 @@ __global__ __launch_bounds__(kArgThreads) void argmax_stream_kernel(TopkArgs p, 
         const unsigned long long word = ((unsigned long long)mag_key(v) << 32) | (0xffffffffu - (uint32_t)e);
         best = word > best ? word : best;
     };
-    if constexpr (VEC == 4) {
-        constexpr int kUnroll = DIFF ? 4 : 8;
-        constexpr int64_t kStep = (int64_t)kArgThreads * 4;
-        int64_t e = lo + (int64_t)threadIdx.x * 4;               // piece % 4 == 0: whole float4s inside [lo, hi)
-        for (; e + (kUnroll - 1) * kStep + 4 <= hi; e += kUnroll * kStep) {
-            float4 va[kUnroll], vb[kUnroll];
+    constexpr int kUnroll = DIFF ? 4 : 8;
+    constexpr int64_t kStep = (int64_t)kArgThreads * 4;
+    int64_t e = lo + (int64_t)threadIdx.x * 4;                   // rows may start at any 4-byte address
+    for (; e + (kUnroll - 1) * kStep + 4 <= hi; e += kUnroll * kStep) {
+        float4 va[kUnroll], vb[kUnroll];
 #pragma unroll
-            for (int u = 0; u < kUnroll; ++u) {
-                va[u] = stream_load4(a + e + u * kStep);
-                if constexpr (DIFF) vb[u] = stream_load4(b + e + u * kStep);
-            }
-#pragma unroll
-            for (int u = 0; u < kUnroll; ++u) {
-                if constexpr (DIFF) {
-                    va[u].x -= vb[u].x;
-                    va[u].y -= vb[u].y;
-                    va[u].z -= vb[u].z;
-                    va[u].w -= vb[u].w;
-                }
-                const int64_t e0 = e + u * kStep;
-                see(va[u].x, e0);
-                see(va[u].y, e0 + 1);
-                see(va[u].z, e0 + 2);
-                see(va[u].w, e0 + 3);
-            }
+        for (int u = 0; u < kUnroll; ++u) {
+            va[u] = stream_load4_any(a + e + u * kStep);
+            if constexpr (DIFF) vb[u] = stream_load4_any(b + e + u * kStep);
         }
-        for (; e + 4 <= hi; e += kStep) {
-            float4 va = stream_load4(a + e);
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u) {
             if constexpr (DIFF) {
-                const float4 vb = stream_load4(b + e);
-                va.x -= vb.x;
-                va.y -= vb.y;
-                va.z -= vb.z;
-                va.w -= vb.w;
+                va[u].x -= vb[u].x;
+                va[u].y -= vb[u].y;
+                va[u].z -= vb[u].z;
+                va[u].w -= vb[u].w;
             }
-            see(va.x, e);
-            see(va.y, e + 1);
-            see(va.z, e + 2);
-            see(va.w, e + 3);
+            const int64_t e0 = e + u * kStep;
+            see(va[u].x, e0);
+            see(va[u].y, e0 + 1);
+            see(va[u].z, e0 + 2);
+            see(va[u].w, e0 + 3);
         }
-    } else {
-        for (int64_t e = lo + threadIdx.x; e < hi; e += kArgThreads) see(load_v<DIFF>(a, b, e), e);
     }
+    for (; e + 4 <= hi; e += kStep) {
+        float4 va = stream_load4_any(a + e);
+        if constexpr (DIFF) {
+            const float4 vb = stream_load4_any(b + e);
+            va.x -= vb.x;
+            va.y -= vb.y;
+            va.z -= vb.z;
+            va.w -= vb.w;
+        }
+        see(va.x, e);
+        see(va.y, e + 1);
+        see(va.z, e + 2);
+        see(va.w, e + 3);
+    }
+    for (; e < hi; ++e) see(load_v<DIFF>(a, b, e), e);           // one thread: the last entries of a row of odd length
 #pragma unroll
     for (int o = kWave / 2; o > 0; o >>= 1) {
         const unsigned long long other = __shfl_xor(best, o, kWave);
@@ -1101,7 +1076,7 @@ __global__ __launch_bounds__(kArgThreads) void argmax_stream_kernel(TopkArgs p, 
     }
 }
 
-template <bool DIFF, bool UPDATE>
+template <bool DIFF, int UPDATE>
 __global__ __launch_bounds__(kArgThreads) void argmax_finish_kernel(TopkArgs p, Ws w) {
     const int64_t row = (int64_t)blockIdx.x * kArgThreads + threadIdx.x;
     if (row >= p.n) return;
@@ -1112,12 +1087,12 @@ __global__ __launch_bounds__(kArgThreads) void argmax_finish_kernel(TopkArgs p, 
     const float v = DIFF ? p.a[row * p.d + e] - bv : p.a[row * p.d + e];
     p.out_idx[row] = (int32_t)e;                                // k == 1: one pair per row
     p.out_val[row] = v;
-    if (UPDATE) p.g_i[row * p.d + e] = bv + v;                  // Algorithm 2, line 6
+    if (UPDATE == kAddUpdate) p.g_i[row * p.d + e] = bv + v;    // Algorithm 2, line 6
+    if (UPDATE == kClearUpdate) p.g_i[row * p.d + e] = 0.f;     // Algorithm 4
 }
 
 hipError_t launch_argmax(const TopkArgs &p, const Ws &w, hipStream_t stream, const Marker &mk) {
     const bool diff = p.b != nullptr, upd = p.g_i != nullptr;
-    const bool vec4 = (p.d % 4 == 0) && ((uintptr_t)p.a % 16 == 0) && (!diff || (uintptr_t)p.b % 16 == 0);
     int64_t G = 1024 / p.n;                                     // about four workgroups of 256 per compute unit
     if (G < 1) G = 1;
     int64_t piece = (p.d + G - 1) / G;
@@ -1125,15 +1100,14 @@ hipError_t launch_argmax(const TopkArgs &p, const Ws &w, hipStream_t stream, con
     if (piece < 4096) piece = 4096;
     G = (p.d + piece - 1) / piece;
     const dim3 grid((unsigned)G, (unsigned)p.n), block(kArgThreads);
-    if (vec4 && diff) hipLaunchKernelGGL((argmax_stream_kernel<4, true>), grid, block, 0, stream, p, w, piece);
-    else if (vec4) hipLaunchKernelGGL((argmax_stream_kernel<4, false>), grid, block, 0, stream, p, w, piece);
-    else if (diff) hipLaunchKernelGGL((argmax_stream_kernel<1, true>), grid, block, 0, stream, p, w, piece);
-    else hipLaunchKernelGGL((argmax_stream_kernel<1, false>), grid, block, 0, stream, p, w, piece);
+    if (diff) hipLaunchKernelGGL(argmax_stream_kernel<true>, grid, block, 0, stream, p, w, piece);
+    else hipLaunchKernelGGL(argmax_stream_kernel<false>, grid, block, 0, stream, p, w, piece);
     mk(K_TOPK_COLLECT);
     const dim3 fgrid((unsigned)((p.n + kArgThreads - 1) / kArgThreads));
-    if (upd) hipLaunchKernelGGL((argmax_finish_kernel<true, true>), fgrid, block, 0, stream, p, w);
-    else if (diff) hipLaunchKernelGGL((argmax_finish_kernel<true, false>), fgrid, block, 0, stream, p, w);
-    else hipLaunchKernelGGL((argmax_finish_kernel<false, false>), fgrid, block, 0, stream, p, w);
+    if (upd && diff) hipLaunchKernelGGL((argmax_finish_kernel<true, kAddUpdate>), fgrid, block, 0, stream, p, w);
+    else if (upd) hipLaunchKernelGGL((argmax_finish_kernel<false, kClearUpdate>), fgrid, block, 0, stream, p, w);
+    else if (diff) hipLaunchKernelGGL((argmax_finish_kernel<true, kNoUpdate>), fgrid, block, 0, stream, p, w);
+    else hipLaunchKernelGGL((argmax_finish_kernel<false, kNoUpdate>), fgrid, block, 0, stream, p, w);
     mk(K_TOPK_SELECT);
     return hipGetLastError();
 }
@@ -1159,7 +1133,7 @@ namespace {
 hipError_t launch_after_collect(const TopkArgs &p, const Ws &w, hipStream_t stream, const Marker &mk) {
     const bool diff = p.b != nullptr, upd = p.g_i != nullptr;
     if (p.warm > 0) {
-        launch_collect_any(p, w, kSecondPass, stream);
+        launch_collect(p, w, kSecondPass, stream);
         mk(K_TOPK_REFINE);
     }
     const int spw = (int64_t)p.n * ((w.nslot + kCandWaves - 1) / kCandWaves) > 256 ? 2 : 1;
@@ -1170,13 +1144,15 @@ hipError_t launch_after_collect(const TopkArgs &p, const Ws &w, hipStream_t stre
         if (spw == 2) hipLaunchKernelGGL((KERNEL<DIFF, UPD, 2>), GRID, block, 0, stream, p, w);          \
         else hipLaunchKernelGGL((KERNEL<DIFF, UPD, 1>), GRID, block, 0, stream, p, w);                   \
     } while (0)
-    if (upd) EF21_CAND(cand_count_kernel, cgrid, true, true);
-    else if (diff) EF21_CAND(cand_count_kernel, cgrid, true, false);
-    else EF21_CAND(cand_count_kernel, cgrid, false, false);
+    if (upd && diff) EF21_CAND(cand_count_kernel, cgrid, true, kAddUpdate);
+    else if (upd) EF21_CAND(cand_count_kernel, cgrid, false, kClearUpdate);
+    else if (diff) EF21_CAND(cand_count_kernel, cgrid, true, kNoUpdate);
+    else EF21_CAND(cand_count_kernel, cgrid, false, kNoUpdate);
     mk(K_TOPK_COUNT);
-    if (upd) EF21_CAND(cand_emit_kernel, cgrid, true, true);
-    else if (diff) EF21_CAND(cand_emit_kernel, cgrid, true, false);
-    else EF21_CAND(cand_emit_kernel, cgrid, false, false);
+    if (upd && diff) EF21_CAND(cand_emit_kernel, cgrid, true, kAddUpdate);
+    else if (upd) EF21_CAND(cand_emit_kernel, cgrid, false, kClearUpdate);
+    else if (diff) EF21_CAND(cand_emit_kernel, cgrid, true, kNoUpdate);
+    else EF21_CAND(cand_emit_kernel, cgrid, false, kNoUpdate);
 #undef EF21_CAND
     mk(K_TOPK_EMIT);
     return hipGetLastError();
@@ -1186,13 +1162,12 @@ hipError_t launch_after_collect(const TopkArgs &p, const Ws &w, hipStream_t stre
 hipError_t launch_topk_split(const TopkArgs &p, void *workspace, hipStream_t stream, const Marker &mk) {
     Ws w;
     layout(p.n, p.d, (char *)workspace, &w);
-    const bool diff = p.b != nullptr, upd = p.g_i != nullptr;
-    if (upd && !diff) return hipErrorInvalidValue;
+    if (p.g_i && p.g_i != (p.b ? p.b : p.a)) return hipErrorInvalidValue;
     if (p.warm < 0 || p.warm > kWarmSlots) return hipErrorInvalidValue;
     if (p.agg_start && (p.agg_shift < 0 || p.agg_shift > 11 || p.agg_nblk != ((p.d - 1) >> p.agg_shift) + 1 || p.k == 1))
         return hipErrorInvalidValue;
     if (p.k == 1) return launch_argmax(p, w, stream, mk);
-    launch_collect_any(p, w, p.warm > 0 ? kWarmPass : kColdPass, stream);
+    launch_collect(p, w, p.warm > 0 ? kWarmPass : kColdPass, stream);
     mk(K_TOPK_COLLECT);
     hipError_t st = hipGetLastError();
     if (st != hipSuccess) return st;
@@ -1215,19 +1190,16 @@ hipError_t launch_topk_split_pair(const TopkArgs &plain, const TopkArgs &markov,
     Ws wp, wm;
     layout(plain.n, plain.d, (char *)ws_plain, &wp);
     layout(markov.n, markov.d, (char *)ws_markov, &wm);
-    const bool vec4 = (markov.d % 4 == 0) && ((uintptr_t)markov.a % 16 == 0) && ((uintptr_t)markov.b % 16 == 0);
     const bool warm = markov.warm > 0;
     const dim3 grid((unsigned)wm.G, (unsigned)markov.n), block(kBlk);
     double2 *norms = (double2 *)norm_parts;
     const bool two_per_cu = wm.G * markov.n > 256;      // steps per group: see launch_collect
-#define EF21_PAIR(VEC, WARM, U) \
-    hipLaunchKernelGGL((split_collect_pair_kernel<VEC, WARM, U>), grid, block, 0, stream, markov, wm, plain.warm, wp, norms)
-    if (vec4 && warm && two_per_cu) EF21_PAIR(4, true, 1);
-    else if (vec4 && warm) EF21_PAIR(4, true, 2);
-    else if (vec4 && two_per_cu) EF21_PAIR(4, false, 1);
-    else if (vec4) EF21_PAIR(4, false, 2);
-    else if (warm) EF21_PAIR(1, true, 2);
-    else EF21_PAIR(1, false, 2);
+#define EF21_PAIR(WARM, U) \
+    hipLaunchKernelGGL((split_collect_pair_kernel<WARM, U>), grid, block, 0, stream, markov, wm, plain.warm, wp, norms)
+    if (warm && two_per_cu) EF21_PAIR(true, 1);
+    else if (warm) EF21_PAIR(true, 2);
+    else if (two_per_cu) EF21_PAIR(false, 1);
+    else EF21_PAIR(false, 2);
 #undef EF21_PAIR
     mk(K_TOPK_COLLECT);
     hipError_t st = hipGetLastError();

@@ -144,7 +144,7 @@ __global__ __launch_bounds__(kThreads) void aggregate_kernel(const int32_t *__re
                                                              const int32_t *__restrict__ start, int32_t n, int64_t k,
                                                              int64_t d, int64_t nblk, float *__restrict__ g,
                                                              float *__restrict__ x, float inv_n, float neg_gamma,
-                                                             bool vec) {
+                                                             bool vec, bool from_zero) {
     constexpr int kPer = kAggSub / (4 * kWave);
     __shared__ __attribute__((aligned(16))) float lds[kAggWaves][kAggSub];
     const int wave = threadIdx.x / kWave, lane = lane_id();
@@ -158,7 +158,8 @@ __global__ __launch_bounds__(kThreads) void aggregate_kernel(const int32_t *__re
     if (whole) {
 #pragma unroll
         for (int q = 0; q < kPer; ++q) {
-            g4[q] = *reinterpret_cast<const float4 *>(g + c0 + 4 * (q * kWave + lane));
+            g4[q] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (!from_zero) g4[q] = *reinterpret_cast<const float4 *>(g + c0 + 4 * (q * kWave + lane));
             if (STEP) x4[q] = *reinterpret_cast<const float4 *>(x + c0 + 4 * (q * kWave + lane));
         }
     }
@@ -184,7 +185,7 @@ __global__ __launch_bounds__(kThreads) void aggregate_kernel(const int32_t *__re
         }
     } else {
         for (int64_t j = c0 + lane; j < c1; j += kWave) {
-            const float gj = fmaf(acc[j - c0], inv_n, g[j]);
+            const float gj = fmaf(acc[j - c0], inv_n, from_zero ? 0.f : g[j]);
             g[j] = gj;
             if (STEP) x[j] = fmaf(neg_gamma, gj, x[j]);
         }
@@ -204,12 +205,12 @@ __global__ __launch_bounds__(kThreads) void aggregate_many_kernel(const int32_t 
                                                                   const int32_t *__restrict__ start, int32_t n,
                                                                   int64_t k, int64_t d, int64_t nblk,
                                                                   float *__restrict__ g, float *__restrict__ x,
-                                                                  float inv_n, float neg_gamma) {
+                                                                  float inv_n, float neg_gamma, bool from_zero) {
     __shared__ float lds[kAggWaves][kManySub];
     const int wave = threadIdx.x / kWave, lane = lane_id();
     const int64_t b = blockIdx.x, c0 = b * kManySub;
     const int64_t j = c0 + threadIdx.x;
-    const float gj = j < d ? g[j] : 0.f;                     // fetched while the runs are added
+    const float gj = !from_zero && j < d ? g[j] : 0.f;       // fetched while the runs are added
     const float xj = STEP && j < d ? x[j] : 0.f;
     float *acc = lds[wave];
     for (int t = lane; t < kManySub; t += kWave) acc[t] = 0.f;
@@ -240,7 +241,7 @@ __global__ __launch_bounds__(kSmallThreads) void aggregate_small_kernel(const in
                                                                         const float *__restrict__ val, int32_t n,
                                                                         int64_t k, int64_t d, float *__restrict__ g,
                                                                         float *__restrict__ x, float inv_n,
-                                                                        float neg_gamma) {
+                                                                        float neg_gamma, bool from_zero) {
     __shared__ float acc[kSmallD];
     __shared__ int32_t m_idx[kSmallEntries];
     __shared__ float m_val[kSmallEntries];
@@ -281,7 +282,7 @@ __global__ __launch_bounds__(kSmallThreads) void aggregate_small_kernel(const in
 #pragma unroll
         for (int u = 0; u < kSmallFetch; ++u) {
             const int64_t j = tid + (int64_t)u * kSmallThreads;
-            gj[u] = j < d ? g[j] : 0.f;
+            gj[u] = !from_zero && j < d ? g[j] : 0.f;
             xj[u] = STEP && j < d ? x[j] : 0.f;
         }
     }
@@ -298,7 +299,7 @@ __global__ __launch_bounds__(kSmallThreads) void aggregate_small_kernel(const in
         }
     } else {
         for (int64_t j = tid; j < d; j += kSmallThreads) {
-            const float gn = fmaf(acc[j], inv_n, g[j]);
+            const float gn = fmaf(acc[j], inv_n, from_zero ? 0.f : g[j]);
             g[j] = gn;
             if (STEP) x[j] = fmaf(neg_gamma, gn, x[j]);
         }
@@ -362,15 +363,15 @@ int aggregate_index_shift(int32_t n, int64_t k, int64_t d) {
 }
 
 hipError_t launch_aggregate(const int32_t *idx, const float *val, int32_t n, int64_t k, int64_t d, float *g, float *x,
-                            float gamma, void *index, hipStream_t stream, bool index_ready) {
+                            float gamma, void *index, hipStream_t stream, bool index_ready, bool from_zero) {
     const float inv_n = 1.0f / (float)n;
     if (aggregate_is_small(n, k, d)) {
         if (x)
             hipLaunchKernelGGL(aggregate_small_kernel<true>, dim3(1), dim3(kSmallThreads), 0, stream, idx, val, n, k, d,
-                               g, x, inv_n, -gamma);
+                               g, x, inv_n, -gamma, from_zero);
         else
             hipLaunchKernelGGL(aggregate_small_kernel<false>, dim3(1), dim3(kSmallThreads), 0, stream, idx, val, n, k,
-                               d, g, x, inv_n, -gamma);
+                               d, g, x, inv_n, -gamma, from_zero);
         return hipGetLastError();
     }
     int32_t *start = (int32_t *)index;
@@ -381,10 +382,10 @@ hipError_t launch_aggregate(const int32_t *idx, const float *val, int32_t n, int
                                dim3(kThreads), 0, stream, idx, k, nblk, kManySub, start);
         if (x)
             hipLaunchKernelGGL(aggregate_many_kernel<true>, dim3((unsigned)nblk), dim3(kThreads), 0, stream, idx, val,
-                               start, n, k, d, nblk, g, x, inv_n, -gamma);
+                               start, n, k, d, nblk, g, x, inv_n, -gamma, from_zero);
         else
             hipLaunchKernelGGL(aggregate_many_kernel<false>, dim3((unsigned)nblk), dim3(kThreads), 0, stream, idx, val,
-                               start, n, k, d, nblk, g, x, inv_n, -gamma);
+                               start, n, k, d, nblk, g, x, inv_n, -gamma, from_zero);
         return hipGetLastError();
     }
     const int64_t nblk = (d + kAggSub - 1) / kAggSub;
@@ -395,10 +396,10 @@ hipError_t launch_aggregate(const int32_t *idx, const float *val, int32_t n, int
     const bool vec = ((uintptr_t)g | (uintptr_t)(x ? x : g)) % 16 == 0;
     if (x)
         hipLaunchKernelGGL(aggregate_kernel<true>, grid, block, 0, stream, idx, val, start, n, k, d, nblk, g, x, inv_n, -gamma,
-                           vec);
+                           vec, from_zero);
     else
         hipLaunchKernelGGL(aggregate_kernel<false>, grid, block, 0, stream, idx, val, start, n, k, d, nblk, g, x, inv_n, -gamma,
-                           vec);
+                           vec, from_zero);
     return hipGetLastError();
 }
 
