@@ -105,12 +105,17 @@ void plan(int32_t n, int64_t d, Ws *w) {
     int64_t max_g = ((int64_t)n * d >= ((int64_t)1 << 26) ? 512 : 256) / n;
     if (max_g < 1) max_g = 1;
     if (max_g > kMaxSlots / kBlkWaves) max_g = kMaxSlots / kBlkWaves;
-    int64_t g = (d + kBlkWaves * 2048 - 1) / (kBlkWaves * 2048);   // at least 2048 entries per piece
+    // At least 2048 entries per piece; 1024 where that would leave most compute units idle (up to 2 million entries: n = 10,
+    // d = 10^5, k = 5000 21.6 us a call against 20.1; at 3 to 5 million 0.5 us are lost to the longer merge; many
+    // short rows have a workgroup each anyway).
+    const int64_t piece = n <= 64 && (int64_t)n * d <= 2000000 ? 1024 : 2048;
+    int64_t g = (d + kBlkWaves * piece - 1) / (kBlkWaves * piece);
     if (g > max_g) g = max_g;
     if (g < 1) g = 1;
     const int64_t pieces = g * kBlkWaves;
     int64_t L = (d + pieces - 1) / pieces;
-    L = (L + 2047) / 2048 * 2048;            // whole load groups (4 steps of 64 lanes x 4 entries), and whole
+    const int64_t unit = piece == 2048 ? 2048 : 512;
+    L = (L + unit - 1) / unit * unit;        // whole load groups (2 steps of 64 lanes x 4 entries), and whole
                                              // blocks of the aggregation's message index (256 or 512 coordinates)
     w->L = L;
     w->nslot = (d + L - 1) / L;
@@ -624,7 +629,7 @@ __device__ void rescue_row(RowShared &rs, const TopkArgs &p, int64_t row) {
 
 // A wavefront of the count and emit kernels takes kSPW consecutive slots (one, or two where one would put more
 // than a workgroup on every compute unit).  The first kPre steps of 64 candidates
-// of each (clamped to the slot's capacity, a multiple of 1024) are loaded at the very start of the kernel, together
+// of each (clamped to the slot's capacity, a multiple of 512) are loaded at the very start of the kernel, together
 // with everything else whose address does not depend on the prologue, so that a workgroup waits for memory once,
 // not once per step of its prologue.
 constexpr int kPre = 4;
