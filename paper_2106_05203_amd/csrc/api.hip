@@ -123,6 +123,7 @@ struct ef21_ctx {
     int32_t *plus_idx = nullptr;    // [2][n][k]: C(s), then C(s - g_i)
     float *plus_val = nullptr;
     void *plus_scratch = nullptr;
+    float *plus_resid = nullptr;    // long rows; nullptr: no memory was left for it
     int32_t *plus_branch = nullptr; // [n]
     double *plus_bm = nullptr;      // [n][2]
     // power iteration of ef21_theory_stepsize (allocated by the first call)
@@ -212,6 +213,7 @@ void free_ctx(ef21_ctx *c) {
     (void)hipFree(c->plus_idx);
     (void)hipFree(c->plus_val);
     (void)hipFree(c->plus_scratch);
+    (void)hipFree(c->plus_resid);
     (void)hipFree(c->plus_branch);
     (void)hipFree(c->plus_bm);
     (void)hipFree(c->power_v);
@@ -668,7 +670,8 @@ static int ensure_plus_buffers(ef21_ctx *c) {
     EF21_HIP(hipStreamSynchronize(c->stream));
     if (hipMalloc((void **)&c->plus_idx, sizeof(int32_t) * 2 * nk) != hipSuccess ||
         hipMalloc((void **)&c->plus_val, sizeof(float) * 2 * nk) != hipSuccess ||
-        hipMalloc(&c->plus_scratch, ef21::plus_scratch_bytes(c->n, c->d, c->k)) != hipSuccess ||
+        hipMalloc(&c->plus_scratch, c->topk_ws && c->k > 1 ? ef21::plus_long_layout(c->n, c->d, nullptr, nullptr)
+                                                           : ef21::plus_scratch_bytes(c->n, c->d, c->k)) != hipSuccess ||
         hipMalloc((void **)&c->plus_branch, sizeof(int32_t) * (size_t)c->n) != hipSuccess ||
         hipMalloc((void **)&c->plus_bm, sizeof(double) * 2 * (size_t)c->n) != hipSuccess ||
         (c->topk_ws && c->k > 1 &&
@@ -688,11 +691,16 @@ static int ensure_plus_buffers(ef21_ctx *c) {
         c->plus_bm = nullptr;
         return fail(EF21_ENOMEM, "hipMalloc of the EF21+ buffers failed");
     }
+    if (c->topk_ws2 && hipMalloc((void **)&c->plus_resid, sizeof(float) * (size_t)c->n *
+                                                              (size_t)ef21::topk_split_slot_entries(c->n, c->d)) != hipSuccess) {
+        (void)hipGetLastError();
+        c->plus_resid = nullptr;
+    }
     return EF21_OK;
 }
 
-// Lines 5 to 8 and 10 of Algorithm 3 for all workers (the model step is the caller's).
-static int enqueue_plus(ef21_ctx *h, const float *grads, const ef21::Marker &mk) {
+// Lines 5 to 8 and 10 of Algorithm 3 for all workers, and with take_step line 3.
+static int enqueue_plus(ef21_ctx *h, const float *grads, bool take_step, const ef21::Marker &mk) {
     const size_t nk = (size_t)h->n * (size_t)h->k;
     int32_t *idx_b = h->plus_idx, *idx_m = h->plus_idx + nk;
     float *val_b = h->plus_val, *val_m = h->plus_val + nk;
@@ -700,24 +708,50 @@ static int enqueue_plus(ef21_ctx *h, const float *grads, const ef21::Marker &mk)
     plain.warm = 2;
     ef21::TopkArgs markov{grads, h->g_i, h->n, h->d, h->k, idx_m, val_m, nullptr};        // line 6: C(s - g_i)
     markov.warm = 1;
-    int64_t norm_chunks = 0;
     hipError_t st;
     if (h->topk_ws2) {
         // long rows: both selections and the two squared norms of line 7 from ONE pass over s and g_i
         plain.warm = 1;           // each workspace keeps its own thresholds
-        st = ef21::launch_topk_split_pair(plain, markov, h->topk_ws2, h->topk_ws, h->plus_scratch, h->stream, mk);
+        ef21::PlusLong pl;
+        ef21::plus_long_layout(h->n, h->d, h->plus_scratch, &pl);
+        plain.agg_start = pl.start_plain;
+        markov.agg_start = pl.start_markov;
+        plain.agg_shift = markov.agg_shift = ef21::kPlusShift;
+        plain.agg_nblk = markov.agg_nblk = pl.nblk;
+        const ef21::PairSums sums{pl.norms, pl.kept_plain, pl.kept_markov, h->plus_resid};
+        st = ef21::launch_topk_split_pair(plain, markov, h->topk_ws2, h->topk_ws, sums, h->stream, mk);
         if (st != hipSuccess) return fail_hip(st, "Top-k kernel launch");
-        norm_chunks = ef21::topk_split_slots(h->n, h->d);
-    } else {
-        if (int rc = enqueue_topk(plain, h->topk_ws, h->stream, mk)) return rc;
-        if (int rc = enqueue_topk(markov, h->topk_ws, h->stream, mk)) return rc;
+        ef21::PlusLongArgs a{};
+        a.n = h->n;
+        a.d = h->d;
+        a.k = h->k;
+        a.idx_b = idx_b;
+        a.idx_m = idx_m;
+        a.val_b = val_b;
+        a.val_m = val_m;
+        a.g_i = h->g_i;
+        a.g = h->g;
+        a.x = take_step ? h->x : nullptr;
+        a.branch = h->plus_branch;
+        a.msg_idx = h->msg_idx;
+        a.msg_val = h->msg_val;
+        st = ef21::launch_plus_long(pl, a, h->plus_bm, h->gamma, h->stream);                   // lines 7, 8, 10, 3
+        mk(ef21::K_PLUS);
+        if (st != hipSuccess) return fail_hip(st, "EF21+ kernel launch");
+        return EF21_OK;
     }
+    if (int rc = enqueue_topk(plain, h->topk_ws, h->stream, mk)) return rc;
+    if (int rc = enqueue_topk(markov, h->topk_ws, h->stream, mk)) return rc;
     st = ef21::launch_plus_choose(grads, h->g_i, h->n, h->d, h->k, idx_b, val_b, idx_m, val_m, h->plus_scratch,
-                                  h->plus_branch, h->plus_bm, h->msg_idx, h->msg_val, h->stream,
-                                  norm_chunks);                                            // lines 7 and 8
+                                  h->plus_branch, h->plus_bm, h->msg_idx, h->msg_val, h->stream);   // lines 7 and 8
     if (st == hipSuccess) st = ef21::launch_mean_rows(h->g_i, h->g, h->n, h->d, h->stream);   // line 10
     mk(ef21::K_PLUS);
     if (st != hipSuccess) return fail_hip(st, "EF21+ kernel launch");
+    if (take_step) {
+        st = ef21::launch_model_step(h->x, h->g, h->d, h->gamma, h->stream);
+        mk(ef21::K_MODEL_STEP);
+        if (st != hipSuccess) return fail_hip(st, "model step launch");
+    }
     return EF21_OK;
 }
 
@@ -771,13 +805,7 @@ int ef21_step(ef21_handle h, const float *grads, uint32_t flags) {
             if (int rc = enqueue_local_grad(h, h->x, h->grad)) return rc;
             grads = h->grad;
         }
-        if (int rc = enqueue_plus(h, grads, mk)) return rc;
-        if (!step_first) {
-            hipError_t st = ef21::launch_model_step(h->x, h->g, h->d, h->gamma, h->stream);
-            mk(ef21::K_MODEL_STEP);
-            if (st != hipSuccess) return fail_hip(st, "model step launch");
-        }
-        return EF21_OK;
+        return enqueue_plus(h, grads, !step_first, mk);
     }
     if (!grads && h->kind == kDense && h->tickets && h->batch.tau == 0 && (flags & EF21_ONE_LAUNCH) &&
         ef21::small_step_applies(h->A, h->n, h->m, h->d, h->k)) {

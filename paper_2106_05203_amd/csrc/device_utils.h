@@ -33,6 +33,21 @@ __device__ __forceinline__ float4 stream_load4_any(const float *p) {
     const v4f t = __builtin_nontemporal_load(reinterpret_cast<const v4f *>(p));
     return make_float4(t.x, t.y, t.z, t.w);
 }
+// The same for data that is used again, and stores.
+__device__ __forceinline__ float4 load4_any(const float *p) {
+    typedef float v4f __attribute__((ext_vector_type(4), aligned(4)));
+    const v4f t = *reinterpret_cast<const v4f *>(p);
+    return make_float4(t.x, t.y, t.z, t.w);
+}
+__device__ __forceinline__ void store4_any(float *p, const float4 &v) {
+    typedef float v4f __attribute__((ext_vector_type(4), aligned(4)));
+    v4f t;
+    t.x = v.x;
+    t.y = v.y;
+    t.z = v.z;
+    t.w = v.w;
+    *reinterpret_cast<v4f *>(p) = t;
+}
 __device__ __forceinline__ float stream_load(const float *p) { return __builtin_nontemporal_load(p); }
 __device__ __forceinline__ int32_t stream_load(const int32_t *p) { return __builtin_nontemporal_load(p); }
 

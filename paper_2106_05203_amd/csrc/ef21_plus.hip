@@ -6,8 +6,8 @@
 //           up to the rounding of one fp32 addition), differences and sums in fp64, in a fixed order;
 //   line 8  g_i <- m if M <= B, else b: a sparse update, or a rewrite of the whole row;
 //   line 10 g = (1/n) sum_i g_i is then recomputed from the rows (launch_mean_rows).
-#include <algorithm>
-
+// Long rows (launch_plus_long): the norms and the kept sums come from the kernels of the two selections, and lines 8, 10
+// and the model step are one pass over the coordinates.
 #include "device_utils.h"
 #include "kernels.h"
 
@@ -196,30 +196,215 @@ __global__ __launch_bounds__(kThreads) void plus_apply_kernel(const int32_t *__r
     }
 }
 
+// ---- long rows
+// One workgroup per worker: B, M and the choice of line 8 from the sums per piece of the row.
+__global__ __launch_bounds__(kThreads) void plus_decide_long_kernel(const double2 *__restrict__ norms,
+                                                                    const double *__restrict__ kept_b,
+                                                                    const double *__restrict__ kept_m, int64_t slots,
+                                                                    int32_t *__restrict__ branch,
+                                                                    double *__restrict__ BM) {
+    __shared__ double lds[kWaves];
+    const int64_t row = blockIdx.x;
+    double ns = 0.0, nv = 0.0, kb = 0.0, km = 0.0;
+    for (int64_t c = threadIdx.x; c < slots; c += kThreads) {
+        const double2 p = norms[row * slots + c];
+        ns += p.x;
+        nv += p.y;
+        kb += kept_b[row * slots + c];
+        km += kept_m[row * slots + c];
+    }
+    ns = block_sum_f64(ns, lds);
+    nv = block_sum_f64(nv, lds);
+    kb = block_sum_f64(kb, lds);
+    km = block_sum_f64(km, lds);
+    if (threadIdx.x == 0) {
+        const double B = ns - kb, M = nv - km;
+        branch[row] = M > B ? 1 : 0;                // line 8: the Markov compressor unless it is strictly worse
+        BM[2 * row] = B;
+        BM[2 * row + 1] = M;
+    }
+}
+
+// Lines 8 and 10, and with STEP line 3, for a block of kApplyCols coordinates per wavefront: worker after worker, the
+// row's old values (Markov branch; zeros otherwise) go to LDS, the run of the chosen message inside the block is added
+// to them or written over them, and the new values are added to the sum in fp64.  A Markov row changes at the run's
+// positions only and is written there; a row that switches to the plain compressor is written whole.  The chosen pairs
+// are copied to the message buffers on the way.  What bounds it: the rows' bytes, read once and, where replaced,
+// written once (n = 5, d = 11.5 million, k = 575589, one row in five replaced: XX us; clearing, applying, averaging and
+// stepping in four kernels took 140).
+constexpr int kApplyCols = 512;
+static_assert(kApplyCols == 1 << kPlusShift, "the message index has this block length");
+
+template <bool STEP>
+__global__ __launch_bounds__(kThreads) void plus_apply_long_kernel(PlusLongArgs a, float neg_gamma) {
+    constexpr int kPer = kApplyCols / (4 * kWave), kInFlight = 4;
+    __shared__ __attribute__((aligned(16))) float lds[kWaves][kApplyCols];
+    const int wave = threadIdx.x / kWave, lane = lane_id();
+    const int64_t b = (int64_t)blockIdx.x * kWaves + wave;
+    if (b >= a.nblk) return;
+    float *acc = lds[wave];
+    const int64_t c0 = b * kApplyCols, d = a.d, k = a.k;
+    const bool whole = c0 + kApplyCols <= d;
+    double sum[kPer][4] = {};
+    float4 x4[kPer];
+    if (STEP && whole) {
+#pragma unroll
+        for (int q = 0; q < kPer; ++q) x4[q] = *reinterpret_cast<const float4 *>(a.x + c0 + 4 * (q * kWave + lane));
+    }
+    auto entry = [&](const float *row, int q, int t) {       // of the last, partial block
+        const int64_t c = c0 + 4 * (q * kWave + lane) + t;
+        return c < d ? row[c] : 0.f;
+    };
+    for (int32_t w0 = 0; w0 < a.n; w0 += kWave) {
+        const int32_t w = w0 + lane;
+        const bool plain_l = w < a.n && a.branch[w] != 0;
+        const int32_t *start = (plain_l ? a.start_b : a.start_m) + (int64_t)(w < a.n ? w : 0) * (a.nblk + 1) + b;
+        const int32_t s0 = w < a.n ? start[0] : 0, s1 = w < a.n ? start[1] : 0;
+        const int32_t tile = a.n - w0 < kWave ? a.n - w0 : kWave;
+        for (int32_t t0 = 0; t0 < tile; t0 += kInFlight) {
+            int32_t e[kInFlight], len[kInFlight];
+            int64_t base[kInFlight];
+            bool plain[kInFlight];
+            float v[kInFlight];
+            float4 old[kInFlight][kPer];
+#pragma unroll
+            for (int u = 0; u < kInFlight; ++u) {
+                const int src = t0 + u < tile ? t0 + u : 0;
+                const int32_t lo = __shfl(s0, src, kWave), hi = __shfl(s1, src, kWave);
+                plain[u] = __shfl((int)plain_l, src, kWave) != 0;
+                len[u] = t0 + u < tile ? hi - lo : 0;
+                base[u] = (int64_t)(w0 + src) * k + lo;
+                const int64_t at = lane < len[u] ? base[u] + lane : 0;     // unconditional loads, no branch
+                e[u] = plain[u] ? a.idx_b[at] : a.idx_m[at];
+                v[u] = plain[u] ? a.val_b[at] : a.val_m[at];
+                const float *row = a.g_i + (int64_t)(w0 + src) * d;
+#pragma unroll
+                for (int q = 0; q < kPer; ++q) {
+                    old[u][q] = make_float4(0.f, 0.f, 0.f, 0.f);
+                    if (!plain[u]) {
+                        if (whole) old[u][q] = load4_any(row + c0 + 4 * (q * kWave + lane));
+                        else old[u][q] = make_float4(entry(row, q, 0), entry(row, q, 1), entry(row, q, 2), entry(row, q, 3));
+                    }
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < kInFlight; ++u) {            // worker order
+                if (t0 + u >= tile) continue;
+                float *row = a.g_i + (int64_t)(w0 + t0 + u) * d;
+#pragma unroll
+                for (int q = 0; q < kPer; ++q) *reinterpret_cast<float4 *>(acc + 4 * (q * kWave + lane)) = old[u][q];
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                // line 8 at one position of the run (positions inside a message are distinct)
+                auto apply = [&](int32_t pos, float val, int64_t at) {
+                    const float now = plain[u] ? val : acc[pos - c0] + val;
+                    acc[pos - c0] = now;
+                    if (!plain[u]) row[pos] = now;
+                    a.msg_idx[at] = pos;
+                    a.msg_val[at] = val;
+                };
+                if (lane < len[u]) apply(e[u], v[u], base[u] + lane);
+                for (int32_t j = lane + kWave; j < len[u]; j += kWave) {
+                    const int64_t at = base[u] + j;
+                    apply(plain[u] ? a.idx_b[at] : a.idx_m[at], plain[u] ? a.val_b[at] : a.val_m[at], at);
+                }
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+#pragma unroll
+                for (int q = 0; q < kPer; ++q) {
+                    const float4 now = *reinterpret_cast<const float4 *>(acc + 4 * (q * kWave + lane));
+                    sum[q][0] += (double)now.x;
+                    sum[q][1] += (double)now.y;
+                    sum[q][2] += (double)now.z;
+                    sum[q][3] += (double)now.w;
+                    if (plain[u]) {
+                        const int64_t c = c0 + 4 * (q * kWave + lane);
+                        if (whole) {
+                            store4_any(row + c, now);
+                        } else {
+                            if (c < d) row[c] = now.x;
+                            if (c + 1 < d) row[c + 1] = now.y;
+                            if (c + 2 < d) row[c + 2] = now.z;
+                            if (c + 3 < d) row[c + 3] = now.w;
+                        }
+                    }
+                }
+            }
+        }
+    }
+    const double nn = (double)a.n;
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+        const int64_t c = c0 + 4 * (q * kWave + lane);
+        const float4 g4 = make_float4((float)(sum[q][0] / nn), (float)(sum[q][1] / nn), (float)(sum[q][2] / nn),
+                                      (float)(sum[q][3] / nn));
+        if (whole) {
+            *reinterpret_cast<float4 *>(a.g + c) = g4;
+            if (STEP) {
+                x4[q].x = fmaf(neg_gamma, g4.x, x4[q].x);
+                x4[q].y = fmaf(neg_gamma, g4.y, x4[q].y);
+                x4[q].z = fmaf(neg_gamma, g4.z, x4[q].z);
+                x4[q].w = fmaf(neg_gamma, g4.w, x4[q].w);
+                *reinterpret_cast<float4 *>(a.x + c) = x4[q];
+            }
+        } else {
+            const float gs[4] = {g4.x, g4.y, g4.z, g4.w};
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                if (c + t >= d) continue;
+                a.g[c + t] = gs[t];
+                if (STEP) a.x[c + t] = fmaf(neg_gamma, gs[t], a.x[c + t]);
+            }
+        }
+    }
+}
+
 int64_t chunks_of(int64_t d) { return (d + kNormChunk - 1) / kNormChunk; }
 int64_t kept_blocks_of(int64_t k) { return (k + kKeptBlock - 1) / kKeptBlock; }
 
 }  // namespace
 
-// room for the norm partials of either producer: the norm kernel's chunks, or one per piece of the long-row Top-k
-int64_t plus_norm_chunks_max(int32_t n, int64_t d) { return std::max<int64_t>(chunks_of(d), topk_split_slots(n, d)); }
-
 size_t plus_scratch_bytes(int32_t n, int64_t d, int64_t k) {
-    return sizeof(double2) * (size_t)n * (size_t)(plus_norm_chunks_max(n, d) + kept_blocks_of(k));
+    return sizeof(double2) * (size_t)n * (size_t)(chunks_of(d) + kept_blocks_of(k));
+}
+
+size_t plus_long_layout(int32_t n, int64_t d, void *scratch, PlusLong *out) {
+    char *base = (char *)scratch;
+    const size_t slots = (size_t)n * (size_t)topk_split_slots(n, d), nblk = (size_t)((d + kApplyCols - 1) / kApplyCols);
+    size_t off = 0;
+    auto take = [&](size_t bytes) {
+        char *p = base ? base + off : nullptr;
+        off += (bytes + 255) / 256 * 256;
+        return p;
+    };
+    char *norms = take(sizeof(double2) * slots);
+    char *kb = take(sizeof(double) * slots), *km = take(sizeof(double) * slots);
+    char *sb = take(sizeof(int32_t) * n * (nblk + 1)), *sm = take(sizeof(int32_t) * n * (nblk + 1));
+    if (out) *out = PlusLong{norms, (double *)kb, (double *)km, (int32_t *)sb, (int32_t *)sm, (int64_t)nblk};
+    return off;
+}
+
+hipError_t launch_plus_long(const PlusLong &pl, PlusLongArgs a, double *BM, float gamma, hipStream_t stream) {
+    if (((uintptr_t)a.g | (uintptr_t)(a.x ? a.x : a.g)) % 16 != 0) return hipErrorInvalidValue;
+    a.start_b = pl.start_plain;
+    a.start_m = pl.start_markov;
+    a.nblk = pl.nblk;
+    hipLaunchKernelGGL(plus_decide_long_kernel, dim3((unsigned)a.n), dim3(kThreads), 0, stream, (const double2 *)pl.norms,
+                       pl.kept_plain, pl.kept_markov, topk_split_slots(a.n, a.d), a.branch, BM);
+    const dim3 grid((unsigned)((a.nblk + kWaves - 1) / kWaves)), block(kThreads);
+    if (a.x) hipLaunchKernelGGL(plus_apply_long_kernel<true>, grid, block, 0, stream, a, -gamma);
+    else hipLaunchKernelGGL(plus_apply_long_kernel<false>, grid, block, 0, stream, a, -gamma);
+    return hipGetLastError();
 }
 
 hipError_t launch_plus_choose(const float *s, float *g_i, int32_t n, int64_t d, int64_t k, const int32_t *idx_b,
                               const float *val_b, const int32_t *idx_m, const float *val_m, void *scratch,
-                              int32_t *branch, double *BM, int32_t *msg_idx, float *msg_val, hipStream_t stream,
-                              int64_t norm_chunks) {
-    if (norm_chunks < 0 || norm_chunks > plus_norm_chunks_max(n, d)) return hipErrorInvalidValue;
-    const int64_t chunks = norm_chunks > 0 ? norm_chunks : chunks_of(d), grid_chunks = chunks_of(d);
+                              int32_t *branch, double *BM, int32_t *msg_idx, float *msg_val, hipStream_t stream) {
+    const int64_t chunks = chunks_of(d);
     double2 *part = (double2 *)scratch;
     // kNormChunk is a multiple of four, so with d % 4 == 0 every chunk is whole float4s
     const bool vec4 = (d % 4 == 0) && (((uintptr_t)s | (uintptr_t)g_i) % 16 == 0);
-    if (norm_chunks > 0) {
-        // the partial sums are already there
-    } else if (vec4) {
+    if (vec4) {
         hipLaunchKernelGGL(plus_sqnorms_kernel<4>, dim3((unsigned)chunks, (unsigned)n), dim3(kThreads), 0, stream, s,
                            g_i, d, part);
     } else {
@@ -227,17 +412,17 @@ hipError_t launch_plus_choose(const float *s, float *g_i, int32_t n, int64_t d, 
                            g_i, d, part);
     }
     const int64_t kblocks = k <= kKeptBlock ? 0 : kept_blocks_of(k);     // short messages: summed by the decide kernel
-    double2 *kept = part + (size_t)n * plus_norm_chunks_max(n, d);
+    double2 *kept = part + (size_t)n * chunks;
     if (kblocks > 0)
         hipLaunchKernelGGL(plus_kept_kernel, dim3((unsigned)kblocks, (unsigned)n), dim3(kThreads), 0, stream, s, g_i,
                            d, val_b, idx_m, k, kept);
     hipLaunchKernelGGL(plus_decide_kernel, dim3((unsigned)n), dim3(kThreads), 0, stream, part, chunks, kept, kblocks, s,
                        g_i, d, val_b, idx_m, k, branch, BM);
     if (vec4)
-        hipLaunchKernelGGL(plus_clear_kernel<4>, dim3((unsigned)grid_chunks, (unsigned)n), dim3(kThreads), 0, stream,
+        hipLaunchKernelGGL(plus_clear_kernel<4>, dim3((unsigned)chunks, (unsigned)n), dim3(kThreads), 0, stream,
                            branch, g_i, d);
     else
-        hipLaunchKernelGGL(plus_clear_kernel<1>, dim3((unsigned)grid_chunks, (unsigned)n), dim3(kThreads), 0, stream,
+        hipLaunchKernelGGL(plus_clear_kernel<1>, dim3((unsigned)chunks, (unsigned)n), dim3(kThreads), 0, stream,
                            branch, g_i, d);
     int64_t blocks = (k + kThreads - 1) / kThreads;
     if (blocks > 256) blocks = 256;

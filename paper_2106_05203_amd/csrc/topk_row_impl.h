@@ -25,7 +25,7 @@ static_assert(kBits1 + kBits2 + kBits3 == 31, "digits must cover the magnitude k
 constexpr int kRankMax = 256;   // a selected bin with at most this many entries is ranked directly
 
 struct RowShared {
-    uint32_t hist[1 << kBits1];
+    __attribute__((aligned(16))) uint32_t hist[1 << kBits1];
     uint32_t wave_a[kRowWaves];
     uint32_t wave_b[kRowWaves];
     uint32_t bin;     // selected digit

@@ -27,6 +27,7 @@
 // result never depends on the guess.  Slots have the capacity of their piece, so any input fits.
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 #include "topk_row_impl.h"
 
@@ -91,6 +92,9 @@ struct Ws {
     uint32_t *slot_inbin;                 // [n][nslot] those in T's bin (written for crowded bins only)
     uint2 *tie;                           // [n][kTieCap] (position, key) of the candidates in T's bin
     uint2 *cand;                          // [n][nslot][L] (position, value bits) of the candidates
+    // Algorithm 3 only (launch_topk_split_pair), the caller's:
+    float *resid;                         // [n][nslot][L] what the rounding of a difference took away (nullptr: not kept)
+    double *kept;                         // [n][nslot] sum of the squares of the kept entries, unrounded
     int64_t L;                            // entries per wavefront piece = slot capacity
     int64_t nslot;                        // pieces per row
     int64_t G;                            // collect workgroups per row
@@ -146,11 +150,19 @@ size_t layout(int32_t n, int64_t d, char *base, Ws *w) {
         w->slot_cnt = (uint32_t *)s0; w->slot_above = (uint32_t *)s1; w->slot_inbin = (uint32_t *)s2;
         w->tie = (uint2 *)tl;
         w->cand = (uint2 *)cd;
+        w->resid = nullptr;
+        w->kept = nullptr;
     }
     return off;
 }
 
 __device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v) {
+#pragma unroll
+    for (int o = kWave / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
+    return v;
+}
+
+__device__ __forceinline__ double wave_sum_f64(double v) {
 #pragma unroll
     for (int o = kWave / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
     return v;
@@ -229,8 +241,14 @@ __device__ uint32_t estimate_key_lo(RowShared &s, const float *a, const float *b
 // Per-wavefront staging ring in LDS: candidates (position, value bits) are appended here and leave for the slot
 // in global memory 64 at a time, as one full-width 8-byte store, instead of as many scattered stores.
 constexpr uint32_t kRing = 128;              // entries of a staging ring (power of two, >= 128)
+template <bool RESID>
 struct StageRing {
     uint2 e[kRing];
+    float r[RESID ? kRing : 1];
+};
+struct SlotOut {                             // a slot in global memory
+    uint2 *cand;
+    float *resid;
 };
 
 // What a wavefront needs to classify and count candidates.
@@ -241,23 +259,34 @@ struct CandFilter {
 
 // Writes the entries [flushed, flushed + count) of the ring (count <= 64) to the slot and counts them into the
 // histogram (here, with all lanes busy, rather than where they are found, a few lanes at a time).
-__device__ __forceinline__ void ring_to_slot(const StageRing &ring, uint32_t flushed, uint32_t count, int lane,
-                                             uint2 *slot, const CandFilter &f) {
+template <bool RESID, class Ring>
+__device__ __forceinline__ void ring_to_slot(const Ring &ring, uint32_t flushed, uint32_t count, int lane,
+                                             const SlotOut &slot, const CandFilter &f) {
     if ((uint32_t)lane < count) {
         const uint2 rec = ring.e[(flushed + lane) & (kRing - 1)];
-        slot[flushed + lane] = rec;
+        slot.cand[flushed + lane] = rec;
+        if constexpr (RESID) {
+            if (slot.resid) slot.resid[flushed + lane] = ring.r[(flushed + lane) & (kRing - 1)];
+        }
         atomicAdd(&f.hist[bin_of(rec.y & 0x7fffffffu, f.key_lo, f.shift)], 1u);
     }
 }
 
+// a - b = fl(a - b) + this, exactly (Knuth's two-sum; NaN where the difference is not finite)
+__device__ __forceinline__ float rounding_of_difference(float a, float b) {
+    const float x = a - b, b_seen = a - x, a_seen = x + b_seen;
+    return (a - a_seen) + (b_seen - b);
+}
+
 // Appends the candidates among one step's entries (VEC per lane, lane-major order) to the slot.
 // FULL: every entry of the step lies inside the piece, no bounds checks.
+// RESID: v = fl(va - vb), and what the rounding took away goes along.
 // cnt = candidates so far, flushed = how many of them are already in global memory (cnt - flushed < 64
 // between calls; both are uniform over the wavefront).
-template <int VEC, bool FULL>
-__device__ __forceinline__ void append_candidates(const float (&v)[VEC], int64_t e0, int64_t hi, const CandFilter &f,
-                                                  StageRing &ring, int lane, uint2 *slot, uint32_t &cnt,
-                                                  uint32_t &flushed) {
+template <int VEC, bool FULL, bool RESID, class Ring>
+__device__ __forceinline__ void append_candidates(const float (&v)[VEC], const float (&va)[VEC], const float (&vb)[VEC],
+                                                  int64_t e0, int64_t hi, const CandFilter &f, Ring &ring, int lane,
+                                                  const SlotOut &slot, uint32_t &cnt, uint32_t &flushed) {
     bool c[VEC];
     uint32_t below = 0, all = 0;
 #pragma unroll
@@ -270,11 +299,14 @@ __device__ __forceinline__ void append_candidates(const float (&v)[VEC], int64_t
     if (all == 0) return;
     uint32_t pos = cnt + below;
     if (all > 64) {        // a dense step would not fit the ring: drain it, then store directly
-        ring_to_slot(ring, flushed, cnt - flushed, lane, slot, f);
+        ring_to_slot<RESID>(ring, flushed, cnt - flushed, lane, slot, f);
 #pragma unroll
         for (int t = 0; t < VEC; ++t) {
             if (c[t]) {
-                slot[pos] = make_uint2((uint32_t)(e0 + t), __float_as_uint(v[t]));
+                slot.cand[pos] = make_uint2((uint32_t)(e0 + t), __float_as_uint(v[t]));
+                if constexpr (RESID) {
+                    if (slot.resid) slot.resid[pos] = rounding_of_difference(va[t], vb[t]);
+                }
                 atomicAdd(&f.hist[bin_of(mag_key(v[t]), f.key_lo, f.shift)], 1u);
                 ++pos;
             }
@@ -287,23 +319,25 @@ __device__ __forceinline__ void append_candidates(const float (&v)[VEC], int64_t
     for (int t = 0; t < VEC; ++t) {
         if (c[t]) {
             ring.e[pos & (kRing - 1)] = make_uint2((uint32_t)(e0 + t), __float_as_uint(v[t]));
+            if constexpr (RESID) ring.r[pos & (kRing - 1)] = rounding_of_difference(va[t], vb[t]);
             ++pos;
         }
     }
     cnt += all;
     if (cnt - flushed > kRing - 64) {        // keep room for the next step's candidates (at most 64)
         __builtin_amdgcn_wave_barrier();
-        ring_to_slot(ring, flushed, 64, lane, slot, f);
+        ring_to_slot<RESID>(ring, flushed, 64, lane, slot, f);
         flushed += 64;
     }
 }
 
 // Writes what is left in the ring at the end of a piece.
-__device__ __forceinline__ void drain_ring(const StageRing &ring, uint32_t flushed, uint32_t cnt, int lane,
-                                           uint2 *slot, const CandFilter &f) {
+template <bool RESID, class Ring>
+__device__ __forceinline__ void drain_ring(const Ring &ring, uint32_t flushed, uint32_t cnt, int lane,
+                                           const SlotOut &slot, const CandFilter &f) {
     __builtin_amdgcn_wave_barrier();
     for (; flushed < cnt; flushed += 64)
-        ring_to_slot(ring, flushed, cnt - flushed < 64 ? cnt - flushed : 64, lane, slot, f);
+        ring_to_slot<RESID>(ring, flushed, cnt - flushed < 64 ? cnt - flushed : 64, lane, slot, f);
 }
 
 // A wavefront walks its piece in steps of 256 entries, four per lane and load, U steps per group.  Rows may start at
@@ -312,11 +346,10 @@ __device__ __forceinline__ void drain_ring(const StageRing &ring, uint32_t flush
 // piece of a row has a checked tail.
 // MODE: kColdPass key_lo from the sample; kWarmPass from the threshold remembered in slot p.warm if there is
 // one, else from the sample; kSecondPass: only rows whose warm start failed, from the sample, into hist_b.
-template <bool DIFF, int MODE, int U>
-__global__ __launch_bounds__(kBlk) void split_collect_kernel(TopkArgs p, Ws w) {
-    __shared__ RowShared s;
-    __shared__ StageRing rings[kBlkWaves];
-    __shared__ uint32_t wg_total;
+// All kBlk threads of the workgroup must call; s, rings and wg_total are the workgroup's.
+template <bool DIFF, int MODE, int U, bool RESID, class Ring>
+__device__ __forceinline__ void collect_rows(const TopkArgs &p, const Ws &w, RowShared &s, Ring (&rings)[kBlkWaves],
+                                             uint32_t &wg_total) {
     const int64_t row = blockIdx.y, d = p.d;
     const float *a = p.a + row * d;
     const float *b = DIFF ? p.b + row * d : nullptr;
@@ -368,10 +401,11 @@ __global__ __launch_bounds__(kBlk) void split_collect_kernel(TopkArgs p, Ws w) {
     // the first pass has a wavefront per slot; the second pass, which seldom has work, runs on a small grid
     for (int64_t slot_no = (int64_t)blockIdx.x * kBlkWaves + wave; slot_no < w.nslot;
          slot_no += (int64_t)gridDim.x * kBlkWaves) {
-        StageRing &ring = rings[wave];
+        Ring &ring = rings[wave];
         const int64_t lo = slot_no * w.L;
         const int64_t hi = lo + w.L < d ? lo + w.L : d;
-        uint2 *slot = w.cand + (row * w.nslot + slot_no) * w.L;
+        const int64_t slot_at = (row * w.nslot + slot_no) * w.L;
+        const SlotOut slot{w.cand + slot_at, RESID && w.resid ? w.resid + slot_at : nullptr};
         uint32_t cnt = 0, flushed = 0;
         constexpr int VEC = 4, kStep = kWave * VEC, kGroup = kStep * U;
         int64_t base = lo;
@@ -399,11 +433,14 @@ __global__ __launch_bounds__(kBlk) void split_collect_kernel(TopkArgs p, Ws w) {
             }
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                float v[VEC] = {va[u].x, va[u].y, va[u].z, va[u].w};
+                const float ea[VEC] = {va[u].x, va[u].y, va[u].z, va[u].w};
+                float eb[VEC] = {}, v[VEC];
                 if constexpr (DIFF) {
-                    v[0] -= vb[u].x; v[1] -= vb[u].y; v[2] -= vb[u].z; v[3] -= vb[u].w;
+                    eb[0] = vb[u].x; eb[1] = vb[u].y; eb[2] = vb[u].z; eb[3] = vb[u].w;
                 }
-                append_candidates<VEC, true>(v, base + u * kStep + lane * VEC, hi, f, ring, lane, slot, cnt, flushed);
+#pragma unroll
+                for (int t = 0; t < VEC; ++t) v[t] = DIFF ? ea[t] - eb[t] : ea[t];
+                append_candidates<VEC, true, RESID>(v, ea, eb, base + u * kStep + lane * VEC, hi, f, ring, lane, slot, cnt, flushed);
             }
 #pragma unroll
             for (int u = 0; u < U; ++u) {
@@ -412,19 +449,24 @@ __global__ __launch_bounds__(kBlk) void split_collect_kernel(TopkArgs p, Ws w) {
             }
         }
         if (base < hi) {                             // checked tail, less than a group, all loads issued first
-            float v[U][VEC];
+            float ea[U][VEC], eb[U][VEC];
 #pragma unroll
             for (int u = 0; u < U; ++u)
 #pragma unroll
                 for (int t = 0; t < VEC; ++t) {
                     const int64_t e = base + u * kStep + lane * VEC + t;
-                    v[u][t] = e < hi ? load_v<DIFF>(a, b, e) : 0.f;
+                    ea[u][t] = e < hi ? a[e] : 0.f;
+                    eb[u][t] = DIFF && e < hi ? b[e] : 0.f;
                 }
 #pragma unroll
-            for (int u = 0; u < U; ++u)
-                append_candidates<VEC, false>(v[u], base + u * kStep + lane * VEC, hi, f, ring, lane, slot, cnt, flushed);
+            for (int u = 0; u < U; ++u) {
+                float v[VEC];
+#pragma unroll
+                for (int t = 0; t < VEC; ++t) v[t] = DIFF ? ea[u][t] - eb[u][t] : ea[u][t];
+                append_candidates<VEC, false, RESID>(v, ea[u], eb[u], base + u * kStep + lane * VEC, hi, f, ring, lane, slot, cnt, flushed);
+            }
         }
-        drain_ring(ring, flushed, cnt, lane, slot, f);
+        drain_ring<RESID>(ring, flushed, cnt, lane, slot, f);
         if (lane == 0) {
             w.slot_cnt[row * w.nslot + slot_no] = cnt;
             atomicAdd(&wg_total, cnt);
@@ -438,6 +480,23 @@ __global__ __launch_bounds__(kBlk) void split_collect_kernel(TopkArgs p, Ws w) {
     if (row_total && threadIdx.x == 0 && wg_total) atomicAdd(row_total, wg_total);
 }
 
+template <bool DIFF, int MODE, int U>
+__global__ __launch_bounds__(kBlk) void split_collect_kernel(TopkArgs p, Ws w) {
+    __shared__ RowShared s;
+    __shared__ StageRing<false> rings[kBlkWaves];
+    __shared__ uint32_t wg_total;
+    collect_rows<DIFF, MODE, U, false>(p, w, s, rings, wg_total);
+}
+
+// The second pass of the two selections of Algorithm 3 in one launch: grid (.., n, 2).
+__global__ __launch_bounds__(kBlk) void split_second_pair_kernel(TopkArgs pp, Ws wp, TopkArgs pm, Ws wm) {
+    __shared__ RowShared s;
+    __shared__ StageRing<true> rings[kBlkWaves];
+    __shared__ uint32_t wg_total;
+    if (blockIdx.z == 0) collect_rows<false, kSecondPass, 2, false>(pp, wp, s, rings, wg_total);
+    else collect_rows<true, kSecondPass, 2, true>(pm, wm, s, rings, wg_total);
+}
+
 // ---------------------------------------------------------------- collect, two selections in one pass
 // Algorithm 3 (EF21+) selects from two vectors built of the same arrays: the gradient s itself (line 5) and the
 // difference s - g_i (line 6), and needs the squared norms of both (line 7).  This kernel reads s and g_i once
@@ -445,18 +504,13 @@ __global__ __launch_bounds__(kBlk) void split_collect_kernel(TopkArgs p, Ws w) {
 // difference go to workspace `wm` (arguments pm: a = s, b = g_i), those of s to workspace `wp` (warm-start memory
 // warm_p), and every wavefront leaves (sum s^2, sum (s - g_i)^2) over its piece in norms[row][slot], the
 // differences of the stored values taken exactly in fp64 and the sums in a fixed order.
-__device__ __forceinline__ double wave_sum_f64(double v) {
-#pragma unroll
-    for (int o = kWave / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
-    return v;
-}
-
 template <bool WARM, int U>
 __global__ __launch_bounds__(kBlk) void split_collect_pair_kernel(TopkArgs pm, Ws wm, int warm_p, Ws wp,
                                                                   double2 *__restrict__ norms) {
     __shared__ RowShared s;                      // its histogram serves the sampling, then the difference
     __shared__ uint32_t hist_p[kHistBins];
-    __shared__ StageRing rings_m[kBlkWaves], rings_p[kBlkWaves];
+    __shared__ StageRing<true> rings_m[kBlkWaves];
+    __shared__ StageRing<false> rings_p[kBlkWaves];
     __shared__ uint32_t wg_total_m, wg_total_p;
     const int64_t row = blockIdx.y, d = pm.d;
     const float *a = pm.a + row * d, *b = pm.b + row * d;
@@ -502,30 +556,29 @@ __global__ __launch_bounds__(kBlk) void split_collect_pair_kernel(TopkArgs pm, W
     const int wave = threadIdx.x / kWave, lane = lane_id();
     const int64_t slot_no = (int64_t)blockIdx.x * kBlkWaves + wave;
     if (slot_no < wm.nslot) {
-        StageRing &ring_m = rings_m[wave], &ring_p = rings_p[wave];
+        StageRing<true> &ring_m = rings_m[wave];
+        StageRing<false> &ring_p = rings_p[wave];
         const int64_t lo = slot_no * wm.L;
         const int64_t hi = lo + wm.L < d ? lo + wm.L : d;
-        uint2 *slot_m = wm.cand + (row * wm.nslot + slot_no) * wm.L;
-        uint2 *slot_p = wp.cand + (row * wp.nslot + slot_no) * wp.L;
+        const int64_t slot_at = (row * wm.nslot + slot_no) * wm.L;           // the two layouts are the same
+        const SlotOut slot_m{wm.cand + slot_at, wm.resid ? wm.resid + slot_at : nullptr};
+        const SlotOut slot_p{wp.cand + slot_at, nullptr};
         uint32_t cnt_m = 0, flushed_m = 0, cnt_p = 0, flushed_p = 0;
         double sq_s = 0.0, sq_v = 0.0;
         constexpr int VEC = 4, kStep = kWave * VEC, kGroup = kStep * U;
         int64_t base = lo;
-        // one group: the squared norms of line 7, the difference of line 6, both filters
-        auto filter_group = [&](float (&vs)[U][VEC], float (&vd)[U][VEC]) {
+        // one step of the wavefront: the squared norms of line 7, the difference of line 6, both filters
+        auto filter_step = [&](const float (&vs)[VEC], const float (&vg)[VEC], int64_t e0, auto full) {
+            float vd[VEC];
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-#pragma unroll
-                for (int t = 0; t < VEC; ++t) {
-                    const double sv = (double)vs[u][t], dv = sv - (double)vd[u][t];      // exact
-                    sq_s += sv * sv;
-                    sq_v += dv * dv;
-                    vd[u][t] = vs[u][t] - vd[u][t];                                      // line 6: one fp32 subtraction
-                }
-                const int64_t e0 = base + u * kStep + lane * VEC;
-                append_candidates<VEC, true>(vs[u], e0, hi, fp, ring_p, lane, slot_p, cnt_p, flushed_p);
-                append_candidates<VEC, true>(vd[u], e0, hi, fm, ring_m, lane, slot_m, cnt_m, flushed_m);
+            for (int t = 0; t < VEC; ++t) {
+                const double sv = (double)vs[t], dv = sv - (double)vg[t];            // exact
+                sq_s += sv * sv;
+                sq_v += dv * dv;
+                vd[t] = vs[t] - vg[t];                                               // line 6: one fp32 subtraction
             }
+            append_candidates<VEC, decltype(full)::value, false>(vs, vs, vs, e0, hi, fp, ring_p, lane, slot_p, cnt_p, flushed_p);
+            append_candidates<VEC, decltype(full)::value, true>(vd, vs, vg, e0, hi, fm, ring_m, lane, slot_m, cnt_m, flushed_m);
         };
         // two register buffers, as in split_collect_kernel: the next group's loads before this group's work
         float4 va[U], vb[U];
@@ -545,13 +598,11 @@ __global__ __launch_bounds__(kBlk) void split_collect_pair_kernel(TopkArgs pm, W
                 na[u] = stream_load4_any(a + at);
                 nb[u] = stream_load4_any(b + at);
             }
-            float vs[U][VEC], vd[U][VEC];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                vs[u][0] = va[u].x; vs[u][1] = va[u].y; vs[u][2] = va[u].z; vs[u][3] = va[u].w;
-                vd[u][0] = vb[u].x; vd[u][1] = vb[u].y; vd[u][2] = vb[u].z; vd[u][3] = vb[u].w;
+                const float vs[VEC] = {va[u].x, va[u].y, va[u].z, va[u].w}, vg[VEC] = {vb[u].x, vb[u].y, vb[u].z, vb[u].w};
+                filter_step(vs, vg, base + u * kStep + lane * VEC, std::true_type());
             }
-            filter_group(vs, vd);
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 va[u] = na[u];
@@ -559,31 +610,20 @@ __global__ __launch_bounds__(kBlk) void split_collect_pair_kernel(TopkArgs pm, W
             }
         }
         if (base < hi) {                             // checked tail, less than a group, all loads issued first
-            float vs[U][VEC], vd[U][VEC];
+            float vs[U][VEC], vg[U][VEC];
 #pragma unroll
             for (int u = 0; u < U; ++u)
 #pragma unroll
                 for (int t = 0; t < VEC; ++t) {
                     const int64_t e = base + u * kStep + lane * VEC + t;
                     vs[u][t] = e < hi ? a[e] : 0.f;
-                    vd[u][t] = e < hi ? b[e] : 0.f;
+                    vg[u][t] = e < hi ? b[e] : 0.f;
                 }
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-#pragma unroll
-                for (int t = 0; t < VEC; ++t) {
-                    const double sv = (double)vs[u][t], dv = sv - (double)vd[u][t];      // exact
-                    sq_s += sv * sv;
-                    sq_v += dv * dv;
-                    vd[u][t] = vs[u][t] - vd[u][t];
-                }
-                const int64_t e0 = base + u * kStep + lane * VEC;
-                append_candidates<VEC, false>(vs[u], e0, hi, fp, ring_p, lane, slot_p, cnt_p, flushed_p);
-                append_candidates<VEC, false>(vd[u], e0, hi, fm, ring_m, lane, slot_m, cnt_m, flushed_m);
-            }
+            for (int u = 0; u < U; ++u) filter_step(vs[u], vg[u], base + u * kStep + lane * VEC, std::false_type());
         }
-        drain_ring(ring_p, flushed_p, cnt_p, lane, slot_p, fp);
-        drain_ring(ring_m, flushed_m, cnt_m, lane, slot_m, fm);
+        drain_ring<false>(ring_p, flushed_p, cnt_p, lane, slot_p, fp);
+        drain_ring<true>(ring_m, flushed_m, cnt_m, lane, slot_m, fm);
         sq_s = wave_sum_f64(sq_s);
         sq_v = wave_sum_f64(sq_v);
         if (lane == 0) {
@@ -610,9 +650,27 @@ __global__ __launch_bounds__(kBlk) void split_collect_pair_kernel(TopkArgs pm, W
 // ---------------------------------------------------------------- count
 // The exact one-workgroup algorithm on the original data for a row whose guess failed, and the message index of
 // the row if the caller asked for one.  All kCandThreads threads of the workgroup must call.
-template <bool DIFF, int UPDATE>
-__device__ void rescue_row(RowShared &rs, const TopkArgs &p, int64_t row) {
+// SUMS (Algorithm 3): the whole row's sum of kept squares goes to its first slot, the others' are zero.
+template <bool DIFF, int UPDATE, bool SUMS>
+__device__ void rescue_row(RowShared &rs, const TopkArgs &p, const Ws &w, int64_t row) {
     row_topk<DIFF, UPDATE>(rs, p, row);
+    if constexpr (SUMS) {
+        static_assert(UPDATE == kNoUpdate, "the vectors still hold what was selected from");
+        double *part = reinterpret_cast<double *>(rs.hist);
+        __syncthreads();                    // the pairs are written, the histogram is done with
+        double sq = 0.0;
+        for (int64_t at = threadIdx.x; at < p.k; at += kCandThreads) {
+            const int64_t e = row * p.d + p.out_idx[row * p.k + at];
+            const double v = (double)p.a[e] - (DIFF ? (double)p.b[e] : 0.0);
+            sq += v * v;
+        }
+        sq = wave_sum_f64(sq);
+        if (lane_id() == 0) part[threadIdx.x / kWave] = sq;
+        __syncthreads();
+        double all = 0.0;
+        for (int v = 0; v < kCandWaves; ++v) all += part[v];
+        for (int64_t t = threadIdx.x; t < w.nslot; t += kCandThreads) w.kept[row * w.nslot + t] = t == 0 ? all : 0.0;
+    }
     if (p.agg_start) {                  // from the pairs just written
         __syncthreads();
         const int32_t *out = p.out_idx + row * p.k;
@@ -638,11 +696,15 @@ constexpr int kPre = 4;
 // failed (see the head of the file).  The last workgroup of a row is the rescue: it selects a failed row by the
 // exact one-workgroup algorithm on the original data (DIFF and UPDATE matter here only).  The others: a slot's
 // candidates in bins above T's are counted, those in T's bin go to the tie list.
-template <bool DIFF, int UPDATE, int kSPW>
-__global__ __launch_bounds__(kCandThreads) void cand_count_kernel(TopkArgs p, Ws w) {
+struct CountShared {
+    RowShared rs;
+    uint32_t wave[kCandWaves], out[4];
+};
+template <bool DIFF, int UPDATE, int kSPW, bool SUMS>
+__device__ __forceinline__ void count_rows(const TopkArgs &p, const Ws &w, CountShared &sh) {
     constexpr int kWgSlots = kCandWaves * kSPW;      // slots per workgroup
-    __shared__ RowShared rs;
-    __shared__ uint32_t lds_wave[kCandWaves], lds_out[4];
+    RowShared &rs = sh.rs;
+    uint32_t (&lds_wave)[kCandWaves] = sh.wave, (&lds_out)[4] = sh.out;
     const int64_t row = blockIdx.y;
     const int tid = threadIdx.x, wave = tid / kWave, lane = lane_id();
     RowInfo *info = w.info + row;
@@ -702,7 +764,7 @@ __global__ __launch_bounds__(kCandThreads) void cand_count_kernel(TopkArgs p, Ws
         crowded = !failed && lds_out[2] > (uint32_t)kTieCap;           // too many to list: see RowInfo::tie_min
     }
     if (rescue) {
-        if (failed) rescue_row<DIFF, UPDATE>(rs, p, row);
+        if (failed) rescue_row<DIFF, UPDATE, SUMS>(rs, p, w, row);
         return;
     }
     if (blockIdx.x == 0 && tid == 0) {
@@ -762,13 +824,27 @@ __global__ __launch_bounds__(kCandThreads) void cand_count_kernel(TopkArgs p, Ws
     }
 }
 
+template <bool DIFF, int UPDATE, int kSPW>
+__global__ __launch_bounds__(kCandThreads) void cand_count_kernel(TopkArgs p, Ws w) {
+    __shared__ CountShared sh;
+    count_rows<DIFF, UPDATE, kSPW, false>(p, w, sh);
+}
+
+// The two selections of Algorithm 3 in one launch: grid (.., n, 2).  (Likewise cand_emit_pair_kernel.)
+template <int kSPW>
+__global__ __launch_bounds__(kCandThreads) void cand_count_pair_kernel(TopkArgs pp, Ws wp, TopkArgs pm, Ws wm) {
+    __shared__ CountShared sh;
+    if (blockIdx.z == 0) count_rows<false, kNoUpdate, kSPW, true>(pp, wp, sh);
+    else count_rows<true, kNoUpdate, kSPW, true>(pm, wm, sh);
+}
+
 // Ordered emission by one wavefront that walks candidates in position order, 64 at a time: the running output
 // offset, the ties seen so far, and (if asked for) the aggregation's message index, start[b] = output position of
 // the first kept entry at or beyond coordinate b << shift.  A wavefront's span [span_lo, span_end) is a whole number
 // of index blocks, so every block begins inside exactly one wavefront's span, and that wavefront writes its start:
 // when it keeps the first entry at or beyond the block's first coordinate, or at the end of its span for the
 // blocks that follow its last kept entry (all of them if it kept nothing).
-template <bool DIFF, int UPDATE>
+template <bool DIFF, int UPDATE, bool SUMS>
 struct Emitter {
     const TopkArgs &p;
     int64_t row;
@@ -779,6 +855,7 @@ struct Emitter {
     int32_t *agg_start;
     int64_t last_b;              // index blocks up to here have their start
     int lane;
+    double kept_sq = 0.0;        // SUMS: this lane's kept entries, unrounded and squared
 
     __device__ Emitter(const TopkArgs &p_, int64_t row_, uint32_t T_, uint32_t q_, uint32_t gt_before,
                        uint32_t eq_before, int64_t span_lo, int lane_)
@@ -788,8 +865,9 @@ struct Emitter {
           last_b((span_lo >> p_.agg_shift) - 1), lane(lane_) {}
 
     // one step: `in` marks the lanes that hold a candidate (position rec.x, value bits rec.y); all lanes call.
-    // have_b: b_pre is the value of b at the candidate's position, loaded by the caller beforehand.
-    __device__ __forceinline__ void step(bool in, uint2 rec, bool have_b = false, float b_pre = 0.f) {
+    // have_b: b_pre is the value of b at the candidate's position, loaded by the caller beforehand.  resid (SUMS of a
+    // difference): what its rounding took away; not finite: the difference is formed again.
+    __device__ __forceinline__ void step(bool in, uint2 rec, bool have_b = false, float b_pre = 0.f, float resid = 0.f) {
         const uint32_t key = rec.y & 0x7fffffffu;
         const bool gt = in && key > T, eq = in && key == T;
         const uint64_t m_gt = __ballot(gt), m_eq = __ballot(eq);
@@ -804,6 +882,12 @@ struct Emitter {
             const int64_t at = row * p.d + (int64_t)rec.x;
             if constexpr (UPDATE == kAddUpdate) p.g_i[at] = (have_b ? b_pre : p.b[at]) + v;      // Algorithm 2, line 6
             if constexpr (UPDATE == kClearUpdate) p.g_i[at] = 0.f;                               // Algorithm 4
+            if constexpr (SUMS) {
+                double exact = (double)v;
+                if constexpr (DIFF)
+                    exact = fabsf(resid) <= 3.0e38f ? exact + (double)resid : (double)p.a[at] - (double)p.b[at];
+                kept_sq += exact * exact;
+            }
         }
         if (agg_start) {
             const uint64_t m_keep = __ballot(keep);
@@ -839,13 +923,21 @@ struct Emitter {
 // first position that are kept.  Grid (slot blocks + 1, n): the last workgroup of a row is a rescue, for a row
 // whose crowded bin (see RowInfo::tie_min) turned out to hold different keys.  A crowded bin of equal keys needs no
 // list: T is that key, and the ties before a slot are the earlier slots' entries of the bin (slot_inbin).
-template <bool DIFF, int UPDATE, int kSPW>
-__global__ __launch_bounds__(kCandThreads) void cand_emit_kernel(TopkArgs p, Ws w) {
+// SUMS (Algorithm 3): the sum of the kept squares of every slot goes to w.kept.
+struct EmitShared {
+    RowShared rs;                                // the rescue's
+    uint32_t before_above[kCandWaves], own_above[kCandWaves], before_inbin[kCandWaves], own_inbin[kCandWaves];
+    uint32_t tie_key[kTieCap], tie_idx[kTieCap];
+    uint32_t T, q;
+};
+template <bool DIFF, int UPDATE, int kSPW, bool SUMS>
+__device__ __forceinline__ void emit_rows(const TopkArgs &p, const Ws &w, EmitShared &sh) {
     constexpr int kWgSlots = kCandWaves * kSPW;      // slots per workgroup
-    __shared__ RowShared rs;                     // the rescue's
-    __shared__ uint32_t before_above[kCandWaves], own_above[kCandWaves], before_inbin[kCandWaves], own_inbin[kCandWaves];
-    __shared__ uint32_t tie_key[kTieCap], tie_idx[kTieCap];
-    __shared__ uint32_t sh_T, sh_q;
+    RowShared &rs = sh.rs;
+    uint32_t (&before_above)[kCandWaves] = sh.before_above, (&own_above)[kCandWaves] = sh.own_above;
+    uint32_t (&before_inbin)[kCandWaves] = sh.before_inbin, (&own_inbin)[kCandWaves] = sh.own_inbin;
+    uint32_t (&tie_key)[kTieCap] = sh.tie_key, (&tie_idx)[kTieCap] = sh.tie_idx;
+    uint32_t &sh_T = sh.T, &sh_q = sh.q;
     static_assert(kTieCap <= kCandThreads, "one listed entry per thread");
     const int64_t row = blockIdx.y;
     const int tid = threadIdx.x, wave = tid / kWave, lane = lane_id();
@@ -856,7 +948,7 @@ __global__ __launch_bounds__(kCandThreads) void cand_emit_kernel(TopkArgs p, Ws 
     const RowInfo ri = *info;
     const bool crowded = ri.failed == kRowCrowded;
     if (rescue) {
-        if (crowded && ri.tie_min != ri.tie_max) rescue_row<DIFF, UPDATE>(rs, p, row);
+        if (crowded && ri.tie_min != ri.tie_max) rescue_row<DIFF, UPDATE, SUMS>(rs, p, w, row);
         return;
     }
     const uint2 listed = w.tie[row * kTieCap + (tid < kTieCap ? tid : 0)];
@@ -885,7 +977,14 @@ __global__ __launch_bounds__(kCandThreads) void cand_emit_kernel(TopkArgs p, Ws 
     // Line 6 needs g_i at the kept positions, scattered over the row: the loads for the wavefront's first
     // candidates that can be kept (those in T's bin or above: T itself is not known yet) are issued here, with
     // everything else, instead of one step at a time between the stores of the emission.
-    float bpre[kSPW][kPre];
+    float bpre[kSPW][kPre], resid[kSPW][kPre];
+    if constexpr (DIFF && SUMS) {
+#pragma unroll
+        for (int s = 0; s < kSPW; ++s)
+#pragma unroll
+            for (int q = 0; q < kPre; ++q)
+                resid[s][q] = w.resid ? w.resid[slot[s] - w.cand + q * kWave + lane] : INFINITY;
+    }
     if constexpr (UPDATE == kAddUpdate) {
         const uint32_t key_lo = ri.use2 != 0u ? ri.key_lo2 : ri.key_lo, shift = ri.use2 != 0u ? ri.shift2 : ri.shift;
 #pragma unroll
@@ -959,7 +1058,7 @@ __global__ __launch_bounds__(kCandThreads) void cand_emit_kernel(TopkArgs p, Ws 
         gt_run += before_above[v] + (v < wave ? own_above[v] : 0u);
         eq_run += before_inbin[v] + (v < wave ? own_inbin[v] : 0u);      // zero unless the bin is crowded
     }
-    Emitter<DIFF, UPDATE> em(p, row, T, q, gt_run, eq_run, sl_first * w.L, lane);
+    Emitter<DIFF, UPDATE, SUMS> em(p, row, T, q, gt_run, eq_run, sl_first * w.L, lane);
 #pragma unroll
     for (int s = 0; s < kSPW; ++s) {             // consecutive slots: the running offsets carry over
         for (uint32_t j0 = 0; j0 < cnt[s]; j0 += kWave * kPre) {
@@ -968,17 +1067,38 @@ __global__ __launch_bounds__(kCandThreads) void cand_emit_kernel(TopkArgs p, Ws 
                 for (int u = 0; u < kPre; ++u) {
                     const uint32_t j = j0 + u * kWave + lane;
                     c[s][u] = slot[s][j < cnt[s] ? j : 0u];      // clamped: no load behind a branch
+                    if constexpr (DIFF && SUMS)
+                        resid[s][u] = w.resid ? w.resid[slot[s] - w.cand + (j < cnt[s] ? j : 0u)] : INFINITY;
                 }
             }
 #pragma unroll
             for (int u = 0; u < kPre; ++u) {
-                if constexpr (UPDATE == kAddUpdate) em.step(j0 + u * kWave + lane < cnt[s], c[s][u], j0 == 0, bpre[s][u]);
+                if constexpr (DIFF && SUMS) em.step(j0 + u * kWave + lane < cnt[s], c[s][u], false, 0.f, resid[s][u]);
+                else if constexpr (UPDATE == kAddUpdate) em.step(j0 + u * kWave + lane < cnt[s], c[s][u], j0 == 0, bpre[s][u]);
                 else em.step(j0 + u * kWave + lane < cnt[s], c[s][u]);
             }
+        }
+        if constexpr (SUMS) {
+            const double sq = wave_sum_f64(em.kept_sq);
+            if (lane == 0 && sl_first + s < w.nslot) w.kept[row * w.nslot + sl_first + s] = sq;
+            em.kept_sq = 0.0;
         }
     }
     const int64_t span_end = (sl_first + kSPW) * w.L;
     em.finish(span_end < p.d ? span_end : p.d);
+}
+
+template <bool DIFF, int UPDATE, int kSPW>
+__global__ __launch_bounds__(kCandThreads) void cand_emit_kernel(TopkArgs p, Ws w) {
+    __shared__ EmitShared sh;
+    emit_rows<DIFF, UPDATE, kSPW, false>(p, w, sh);
+}
+
+template <int kSPW>
+__global__ __launch_bounds__(kCandThreads) void cand_emit_pair_kernel(TopkArgs pp, Ws wp, TopkArgs pm, Ws wm) {
+    __shared__ EmitShared sh;
+    if (blockIdx.z == 0) emit_rows<false, kNoUpdate, kSPW, true>(pp, wp, sh);
+    else emit_rows<true, kNoUpdate, kSPW, true>(pm, wm, sh);
 }
 
 __global__ __launch_bounds__(kCandThreads) void zero_words_kernel(uint32_t *p, size_t words) {
@@ -1134,6 +1254,14 @@ hipError_t launch_topk_split_reset(void *workspace, int32_t n, int64_t d, hipStr
 }
 
 namespace {
+int cand_slots_per_wave(int32_t n, const Ws &w) {
+    return (int64_t)n * ((w.nslot + kCandWaves - 1) / kCandWaves) > 256 ? 2 : 1;
+}
+dim3 cand_grid(int32_t n, const Ws &w, int spw, unsigned selections) {
+    const unsigned slot_blocks = (unsigned)((w.nslot + kCandWaves * spw - 1) / (kCandWaves * spw));
+    return dim3(slot_blocks + 1, (unsigned)n, selections);         // + 1: a row's rescue workgroup
+}
+
 // After the first collect pass: the second pass (after a warm start), count and emit.
 hipError_t launch_after_collect(const TopkArgs &p, const Ws &w, hipStream_t stream, const Marker &mk) {
     const bool diff = p.b != nullptr, upd = p.g_i != nullptr;
@@ -1141,9 +1269,8 @@ hipError_t launch_after_collect(const TopkArgs &p, const Ws &w, hipStream_t stre
         launch_collect(p, w, kSecondPass, stream);
         mk(K_TOPK_REFINE);
     }
-    const int spw = (int64_t)p.n * ((w.nslot + kCandWaves - 1) / kCandWaves) > 256 ? 2 : 1;
-    const unsigned slot_blocks = (unsigned)((w.nslot + kCandWaves * spw - 1) / (kCandWaves * spw));
-    const dim3 cgrid(slot_blocks + 1, (unsigned)p.n), block(kCandThreads);     // + 1: a row's rescue workgroup
+    const int spw = cand_slots_per_wave(p.n, w);
+    const dim3 cgrid = cand_grid(p.n, w, spw, 1), block(kCandThreads);
 #define EF21_CAND(KERNEL, GRID, DIFF, UPD)                                                               \
     do {                                                                                                 \
         if (spw == 2) hipLaunchKernelGGL((KERNEL<DIFF, UPD, 2>), GRID, block, 0, stream, p, w);          \
@@ -1185,19 +1312,31 @@ int64_t topk_split_slots(int32_t n, int64_t d) {
     return w.nslot;
 }
 
+int64_t topk_split_slot_entries(int32_t n, int64_t d) {
+    Ws w;
+    plan(n, d, &w);
+    return w.nslot * w.L;
+}
+
 hipError_t launch_topk_split_pair(const TopkArgs &plain, const TopkArgs &markov, void *ws_plain, void *ws_markov,
-                                  void *norm_parts, hipStream_t stream, const Marker &mk) {
+                                  const PairSums &sums, hipStream_t stream, const Marker &mk) {
     if (plain.b || !markov.b || plain.a != markov.a || plain.n != markov.n || plain.d != markov.d ||
-        plain.k != markov.k || plain.g_i || markov.g_i || plain.agg_start || markov.agg_start || plain.k < 2 ||
-        plain.warm < 0 || plain.warm > kWarmSlots || markov.warm < 0 || markov.warm > kWarmSlots ||
-        (plain.warm > 0) != (markov.warm > 0) || !norm_parts)
+        plain.k != markov.k || plain.g_i || markov.g_i || plain.k < 2 || plain.warm < 0 || plain.warm > kWarmSlots ||
+        markov.warm < 0 || markov.warm > kWarmSlots || (plain.warm > 0) != (markov.warm > 0) || !sums.norms ||
+        !sums.kept_plain || !sums.kept_markov)
         return hipErrorInvalidValue;
+    for (const TopkArgs *p : {&plain, &markov})
+        if (p->agg_start && (p->agg_shift < 0 || p->agg_shift > 9 || p->agg_nblk != ((p->d - 1) >> p->agg_shift) + 1))
+            return hipErrorInvalidValue;
     Ws wp, wm;
     layout(plain.n, plain.d, (char *)ws_plain, &wp);
     layout(markov.n, markov.d, (char *)ws_markov, &wm);
+    wp.kept = sums.kept_plain;
+    wm.kept = sums.kept_markov;
+    wm.resid = sums.resid;
     const bool warm = markov.warm > 0;
     const dim3 grid((unsigned)wm.G, (unsigned)markov.n), block(kBlk);
-    double2 *norms = (double2 *)norm_parts;
+    double2 *norms = (double2 *)sums.norms;
     const bool two_per_cu = wm.G * markov.n > 256;      // steps per group: see launch_collect
 #define EF21_PAIR(WARM, U) \
     hipLaunchKernelGGL((split_collect_pair_kernel<WARM, U>), grid, block, 0, stream, markov, wm, plain.warm, wp, norms)
@@ -1207,11 +1346,21 @@ hipError_t launch_topk_split_pair(const TopkArgs &plain, const TopkArgs &markov,
     else EF21_PAIR(false, 2);
 #undef EF21_PAIR
     mk(K_TOPK_COLLECT);
-    hipError_t st = hipGetLastError();
-    if (st != hipSuccess) return st;
-    st = launch_after_collect(plain, wp, stream, mk);
-    if (st != hipSuccess) return st;
-    return launch_after_collect(markov, wm, stream, mk);
+    if (warm) {
+        const int64_t g = std::max<int64_t>(1, std::min<int64_t>(wm.G, 64 / markov.n));      // as in launch_collect
+        hipLaunchKernelGGL(split_second_pair_kernel, dim3((unsigned)g, (unsigned)markov.n, 2), block, 0, stream, plain, wp,
+                           markov, wm);
+        mk(K_TOPK_REFINE);
+    }
+    const int spw = cand_slots_per_wave(markov.n, wm);
+    const dim3 cgrid = cand_grid(markov.n, wm, spw, 2);
+    if (spw == 2) hipLaunchKernelGGL(cand_count_pair_kernel<2>, cgrid, block, 0, stream, plain, wp, markov, wm);
+    else hipLaunchKernelGGL(cand_count_pair_kernel<1>, cgrid, block, 0, stream, plain, wp, markov, wm);
+    mk(K_TOPK_COUNT);
+    if (spw == 2) hipLaunchKernelGGL(cand_emit_pair_kernel<2>, cgrid, block, 0, stream, plain, wp, markov, wm);
+    else hipLaunchKernelGGL(cand_emit_pair_kernel<1>, cgrid, block, 0, stream, plain, wp, markov, wm);
+    mk(K_TOPK_EMIT);
+    return hipGetLastError();
 }
 
 }  // namespace ef21
