@@ -13,6 +13,9 @@ __device__ __forceinline__ uint32_t mag_key(float v) { return __float_as_uint(v)
 
 __device__ __forceinline__ int lane_id() { return (int)(threadIdx.x & (kWave - 1)); }
 
+// The wavefront's number in its workgroup, as a scalar: what is computed from it stays out of the vector registers.
+__device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave)); }
+
 // number of set bits of `mask` in lanes below the caller's
 __device__ __forceinline__ uint32_t lanes_below(uint64_t mask) {
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));

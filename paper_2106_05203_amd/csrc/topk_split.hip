@@ -38,6 +38,7 @@ constexpr int kBlk = kRowThreads;            // collect / rescue workgroups
 constexpr int kBlkWaves = kBlk / kWave;
 constexpr int kSample = 4096;                // sampled entries per row
 constexpr int kSamplePer = kSample / kBlk;
+constexpr int kSteps = 2;                    // steps of a collect group (loads in flight)
 constexpr int kPieceLen = 64, kPieces = kSample / kPieceLen;   // a wavefront's load is one piece
 constexpr int kMaxSlots = 4096;              // slots (wavefront pieces) per row
 constexpr int kCandThreads = 1024;           // count / emit workgroups: one wavefront per slot
@@ -58,9 +59,14 @@ static_assert(kCandThreads == kRowThreads && kBlk == kRowThreads, "the rescue ru
 // wider bins everywhere cost the (n = 20, d = 10^6, k = 10^4) call 0.7 us of 33.8 in ranking.
 __device__ __forceinline__ uint32_t cold_shift(int64_t k, int64_t d) {
     if (k <= 4096) return 13u;                                    // four octaves
-    return k <= 131072 && k * 200 < d ? 12u : 11u;                // two, or one
+    if (k <= 131072 && k * 200 < d) return 12u;                   // two
+    return k <= 400000 ? 11u : 10u;                               // one; half, where a wider bin would be crowded
 }
-__device__ __forceinline__ uint32_t warm_shift(int64_t k, int64_t d) { return cold_shift(k, d) - 1u; }
+__device__ __forceinline__ uint32_t warm_shift(int64_t k, int64_t d) {
+    if (k > 1500000) return 9u;
+    const uint32_t s = cold_shift(k, d);
+    return s > 10u ? s - 1u : 10u;
+}
 constexpr uint32_t kWarmBelow = 1u << 20;
 constexpr int kTieCap = 1024;                // entries of T's bin that are ranked directly (one per thread)
 constexpr int kWarmSlots = 1;                // remembered thresholds per row (TopkArgs::warm = 1 .. kWarmSlots)
@@ -103,10 +109,10 @@ struct Ws {
 size_t align256(size_t b) { return (b + 255) / 256 * 256; }
 
 void plan(int32_t n, int64_t d, Ws *w) {
-    // one 1024-thread workgroup per CU; two for inputs of 2^26 entries and more (the collect kernels need 44
-    // registers per lane and 36 KB of LDS, so two are resident).  Measured: short inputs lose with a second
-    // workgroup per CU (each repeats the sampling prologue), long ones with fewer or more than two.
-    int64_t max_g = ((int64_t)n * d >= ((int64_t)1 << 26) ? 512 : 256) / n;
+    // One 1024-thread workgroup per compute unit.  (Two, resident together or one after the other: n = 15,
+    // d = 5 million 155 and 149 us a step against 148; ef21_topk of 10 rows of 7 million 69 and 72 against 64; shorter
+    // inputs lose more, each workgroup repeats the sampling prologue.)
+    int64_t max_g = 256 / n;
     if (max_g < 1) max_g = 1;
     if (max_g > kMaxSlots / kBlkWaves) max_g = kMaxSlots / kBlkWaves;
     // At least 2048 entries per piece; 1024 where that would leave most compute units idle (up to 2 million entries: n = 10,
@@ -340,14 +346,14 @@ __device__ __forceinline__ void drain_ring(const Ring &ring, uint32_t flushed, u
         ring_to_slot<RESID>(ring, flushed, cnt - flushed < 64 ? cnt - flushed : 64, lane, slot, f);
 }
 
-// A wavefront walks its piece in steps of 256 entries, four per lane and load, U steps per group.  Rows may start at
+// A wavefront walks its piece in steps of 256 entries, four per lane and load, kSteps steps per group.  Rows may start at
 // any 4-byte address (rows of odd length: ef21_topk of 10 rows of 3000001, k = 30000, 52.5 us with 4-byte loads, 45 with 16-byte ones).
 // Whole groups are loaded without any bounds check so that all loads of a group are in flight together; only the last
 // piece of a row has a checked tail.
 // MODE: kColdPass key_lo from the sample; kWarmPass from the threshold remembered in slot p.warm if there is
 // one, else from the sample; kSecondPass: only rows whose warm start failed, from the sample, into hist_b.
 // All kBlk threads of the workgroup must call; s, rings and wg_total are the workgroup's.
-template <bool DIFF, int MODE, int U, bool RESID, class Ring>
+template <bool DIFF, int MODE, bool RESID, class Ring>
 __device__ __forceinline__ void collect_rows(const TopkArgs &p, const Ws &w, RowShared &s, Ring (&rings)[kBlkWaves],
                                              uint32_t &wg_total) {
     const int64_t row = blockIdx.y, d = p.d;
@@ -397,7 +403,7 @@ __device__ __forceinline__ void collect_rows(const TopkArgs &p, const Ws &w, Row
     if (threadIdx.x == 0) wg_total = 0u;
     __syncthreads();
 
-    const int wave = threadIdx.x / kWave, lane = lane_id();
+    const int wave = wave_id(), lane = lane_id();
     // the first pass has a wavefront per slot; the second pass, which seldom has work, runs on a small grid
     for (int64_t slot_no = (int64_t)blockIdx.x * kBlkWaves + wave; slot_no < w.nslot;
          slot_no += (int64_t)gridDim.x * kBlkWaves) {
@@ -407,32 +413,32 @@ __device__ __forceinline__ void collect_rows(const TopkArgs &p, const Ws &w, Row
         const int64_t slot_at = (row * w.nslot + slot_no) * w.L;
         const SlotOut slot{w.cand + slot_at, RESID && w.resid ? w.resid + slot_at : nullptr};
         uint32_t cnt = 0, flushed = 0;
-        constexpr int VEC = 4, kStep = kWave * VEC, kGroup = kStep * U;
+        constexpr int VEC = 4, kStep = kWave * VEC, kGroup = kStep * kSteps;
         int64_t base = lo;
-        // Groups of U steps, two register buffers: the next group's loads are issued before this group is
+        // Groups of kSteps steps, two register buffers: the next group's loads are issued before this group is
         // filtered, so that a wavefront has loads in flight while it computes.  After the last group the
         // "next" loads all read the piece's first 16 bytes (one cached line) instead of sitting behind a
-        // branch.  What is in flight per compute unit is 1024 lanes x workgroups per unit x arrays x 2 U x 16
-        // bytes; measured best at 64 to 128 KB (see launch_collect).
-        float4 va[U], vb[U];
+        // branch.  What is in flight per compute unit is 1024 lanes x arrays x 2 kSteps x 16 bytes; measured best
+        // at 64 to 128 KB (the C1 call, one array: 31.7 us with two steps, 36 with one, 33 with four).
+        float4 va[kSteps], vb[kSteps];
         if (base + kGroup <= hi) {
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
+            for (int u = 0; u < kSteps; ++u) {
                 va[u] = stream_load4_any(a + base + u * kStep + lane * 4);
                 if constexpr (DIFF) vb[u] = stream_load4_any(b + base + u * kStep + lane * 4);
             }
         }
         for (; base + kGroup <= hi; base += kGroup) {
             const bool more = base + 2 * kGroup <= hi;
-            float4 na[U], nb[U];
+            float4 na[kSteps], nb[kSteps];
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
+            for (int u = 0; u < kSteps; ++u) {
                 const int64_t at = more ? base + kGroup + u * kStep + lane * 4 : lo;
                 na[u] = stream_load4_any(a + at);
                 if constexpr (DIFF) nb[u] = stream_load4_any(b + at);
             }
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
+            for (int u = 0; u < kSteps; ++u) {
                 const float ea[VEC] = {va[u].x, va[u].y, va[u].z, va[u].w};
                 float eb[VEC] = {}, v[VEC];
                 if constexpr (DIFF) {
@@ -443,15 +449,15 @@ __device__ __forceinline__ void collect_rows(const TopkArgs &p, const Ws &w, Row
                 append_candidates<VEC, true, RESID>(v, ea, eb, base + u * kStep + lane * VEC, hi, f, ring, lane, slot, cnt, flushed);
             }
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
+            for (int u = 0; u < kSteps; ++u) {
                 va[u] = na[u];
                 if constexpr (DIFF) vb[u] = nb[u];
             }
         }
         if (base < hi) {                             // checked tail, less than a group, all loads issued first
-            float ea[U][VEC], eb[U][VEC];
+            float ea[kSteps][VEC], eb[kSteps][VEC];
 #pragma unroll
-            for (int u = 0; u < U; ++u)
+            for (int u = 0; u < kSteps; ++u)
 #pragma unroll
                 for (int t = 0; t < VEC; ++t) {
                     const int64_t e = base + u * kStep + lane * VEC + t;
@@ -459,7 +465,7 @@ __device__ __forceinline__ void collect_rows(const TopkArgs &p, const Ws &w, Row
                     eb[u][t] = DIFF && e < hi ? b[e] : 0.f;
                 }
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
+            for (int u = 0; u < kSteps; ++u) {
                 float v[VEC];
 #pragma unroll
                 for (int t = 0; t < VEC; ++t) v[t] = DIFF ? ea[u][t] - eb[u][t] : ea[u][t];
@@ -480,12 +486,12 @@ __device__ __forceinline__ void collect_rows(const TopkArgs &p, const Ws &w, Row
     if (row_total && threadIdx.x == 0 && wg_total) atomicAdd(row_total, wg_total);
 }
 
-template <bool DIFF, int MODE, int U>
+template <bool DIFF, int MODE>
 __global__ __launch_bounds__(kBlk) void split_collect_kernel(TopkArgs p, Ws w) {
     __shared__ RowShared s;
     __shared__ StageRing<false> rings[kBlkWaves];
     __shared__ uint32_t wg_total;
-    collect_rows<DIFF, MODE, U, false>(p, w, s, rings, wg_total);
+    collect_rows<DIFF, MODE, false>(p, w, s, rings, wg_total);
 }
 
 // The second pass of the two selections of Algorithm 3 in one launch: grid (.., n, 2).
@@ -493,8 +499,8 @@ __global__ __launch_bounds__(kBlk) void split_second_pair_kernel(TopkArgs pp, Ws
     __shared__ RowShared s;
     __shared__ StageRing<true> rings[kBlkWaves];
     __shared__ uint32_t wg_total;
-    if (blockIdx.z == 0) collect_rows<false, kSecondPass, 2, false>(pp, wp, s, rings, wg_total);
-    else collect_rows<true, kSecondPass, 2, true>(pm, wm, s, rings, wg_total);
+    if (blockIdx.z == 0) collect_rows<false, kSecondPass, false>(pp, wp, s, rings, wg_total);
+    else collect_rows<true, kSecondPass, true>(pm, wm, s, rings, wg_total);
 }
 
 // ---------------------------------------------------------------- collect, two selections in one pass
@@ -504,7 +510,7 @@ __global__ __launch_bounds__(kBlk) void split_second_pair_kernel(TopkArgs pp, Ws
 // difference go to workspace `wm` (arguments pm: a = s, b = g_i), those of s to workspace `wp` (warm-start memory
 // warm_p), and every wavefront leaves (sum s^2, sum (s - g_i)^2) over its piece in norms[row][slot], the
 // differences of the stored values taken exactly in fp64 and the sums in a fixed order.
-template <bool WARM, int U>
+template <bool WARM>
 __global__ __launch_bounds__(kBlk) void split_collect_pair_kernel(TopkArgs pm, Ws wm, int warm_p, Ws wp,
                                                                   double2 *__restrict__ norms) {
     __shared__ RowShared s;                      // its histogram serves the sampling, then the difference
@@ -553,7 +559,7 @@ __global__ __launch_bounds__(kBlk) void split_collect_pair_kernel(TopkArgs pm, W
     }
     __syncthreads();
 
-    const int wave = threadIdx.x / kWave, lane = lane_id();
+    const int wave = wave_id(), lane = lane_id();
     const int64_t slot_no = (int64_t)blockIdx.x * kBlkWaves + wave;
     if (slot_no < wm.nslot) {
         StageRing<true> &ring_m = rings_m[wave];
@@ -565,7 +571,7 @@ __global__ __launch_bounds__(kBlk) void split_collect_pair_kernel(TopkArgs pm, W
         const SlotOut slot_p{wp.cand + slot_at, nullptr};
         uint32_t cnt_m = 0, flushed_m = 0, cnt_p = 0, flushed_p = 0;
         double sq_s = 0.0, sq_v = 0.0;
-        constexpr int VEC = 4, kStep = kWave * VEC, kGroup = kStep * U;
+        constexpr int VEC = 4, kStep = kWave * VEC, kGroup = kStep * kSteps;
         int64_t base = lo;
         // one step of the wavefront: the squared norms of line 7, the difference of line 6, both filters
         auto filter_step = [&](const float (&vs)[VEC], const float (&vg)[VEC], int64_t e0, auto full) {
@@ -581,38 +587,38 @@ __global__ __launch_bounds__(kBlk) void split_collect_pair_kernel(TopkArgs pm, W
             append_candidates<VEC, decltype(full)::value, true>(vd, vs, vg, e0, hi, fm, ring_m, lane, slot_m, cnt_m, flushed_m);
         };
         // two register buffers, as in split_collect_kernel: the next group's loads before this group's work
-        float4 va[U], vb[U];
+        float4 va[kSteps], vb[kSteps];
         if (base + kGroup <= hi) {
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
+            for (int u = 0; u < kSteps; ++u) {
                 va[u] = stream_load4_any(a + base + u * kStep + lane * 4);
                 vb[u] = stream_load4_any(b + base + u * kStep + lane * 4);
             }
         }
         for (; base + kGroup <= hi; base += kGroup) {
             const bool more = base + 2 * kGroup <= hi;
-            float4 na[U], nb[U];
+            float4 na[kSteps], nb[kSteps];
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
+            for (int u = 0; u < kSteps; ++u) {
                 const int64_t at = more ? base + kGroup + u * kStep + lane * 4 : lo;
                 na[u] = stream_load4_any(a + at);
                 nb[u] = stream_load4_any(b + at);
             }
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
+            for (int u = 0; u < kSteps; ++u) {
                 const float vs[VEC] = {va[u].x, va[u].y, va[u].z, va[u].w}, vg[VEC] = {vb[u].x, vb[u].y, vb[u].z, vb[u].w};
                 filter_step(vs, vg, base + u * kStep + lane * VEC, std::true_type());
             }
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
+            for (int u = 0; u < kSteps; ++u) {
                 va[u] = na[u];
                 vb[u] = nb[u];
             }
         }
         if (base < hi) {                             // checked tail, less than a group, all loads issued first
-            float vs[U][VEC], vg[U][VEC];
+            float vs[kSteps][VEC], vg[kSteps][VEC];
 #pragma unroll
-            for (int u = 0; u < U; ++u)
+            for (int u = 0; u < kSteps; ++u)
 #pragma unroll
                 for (int t = 0; t < VEC; ++t) {
                     const int64_t e = base + u * kStep + lane * VEC + t;
@@ -620,7 +626,7 @@ __global__ __launch_bounds__(kBlk) void split_collect_pair_kernel(TopkArgs pm, W
                     vg[u][t] = e < hi ? b[e] : 0.f;
                 }
 #pragma unroll
-            for (int u = 0; u < U; ++u) filter_step(vs[u], vg[u], base + u * kStep + lane * VEC, std::false_type());
+            for (int u = 0; u < kSteps; ++u) filter_step(vs[u], vg[u], base + u * kStep + lane * VEC, std::false_type());
         }
         drain_ring<false>(ring_p, flushed_p, cnt_p, lane, slot_p, fp);
         drain_ring<true>(ring_m, flushed_m, cnt_m, lane, slot_m, fm);
@@ -650,14 +656,35 @@ __global__ __launch_bounds__(kBlk) void split_collect_pair_kernel(TopkArgs pm, W
 // ---------------------------------------------------------------- count
 // The exact one-workgroup algorithm on the original data for a row whose guess failed, and the message index of
 // the row if the caller asked for one.  All kCandThreads threads of the workgroup must call.
+// The threshold found is remembered as any other, so that the row's next call does not start from a sample again.
 // SUMS (Algorithm 3): the whole row's sum of kept squares goes to its first slot, the others' are zero.
 template <bool DIFF, int UPDATE, bool SUMS>
 __device__ void rescue_row(RowShared &rs, const TopkArgs &p, const Ws &w, int64_t row) {
     row_topk<DIFF, UPDATE>(rs, p, row);
+    if (p.warm > 0) {
+        uint32_t *part = rs.hist, T = 0xffffffffu;
+        __syncthreads();                    // the pairs are written, the histogram is done with
+        for (int64_t at = threadIdx.x; at < p.k; at += kCandThreads) {
+            const uint32_t key = mag_key(p.out_val[row * p.k + at]);
+            T = key < T ? key : T;
+        }
+#pragma unroll
+        for (int o = kWave / 2; o > 0; o >>= 1) {
+            const uint32_t other = __shfl_xor(T, o, kWave);
+            T = other < T ? other : T;
+        }
+        if (lane_id() == 0) part[threadIdx.x / kWave] = T;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            for (int v = 0; v < kCandWaves; ++v) T = part[v] < T ? part[v] : T;
+            w.info[row].warm_T[p.warm - 1] = T;
+            w.info[row].warm_ok[p.warm - 1] = 1u;
+        }
+    }
     if constexpr (SUMS) {
         static_assert(UPDATE == kNoUpdate, "the vectors still hold what was selected from");
         double *part = reinterpret_cast<double *>(rs.hist);
-        __syncthreads();                    // the pairs are written, the histogram is done with
+        __syncthreads();                    // the pairs are written, rs.hist is done with
         double sq = 0.0;
         for (int64_t at = threadIdx.x; at < p.k; at += kCandThreads) {
             const int64_t e = row * p.d + p.out_idx[row * p.k + at];
@@ -706,7 +733,7 @@ __device__ __forceinline__ void count_rows(const TopkArgs &p, const Ws &w, Count
     RowShared &rs = sh.rs;
     uint32_t (&lds_wave)[kCandWaves] = sh.wave, (&lds_out)[4] = sh.out;
     const int64_t row = blockIdx.y;
-    const int tid = threadIdx.x, wave = tid / kWave, lane = lane_id();
+    const int tid = threadIdx.x, wave = wave_id(), lane = lane_id();
     RowInfo *info = w.info + row;
     const bool rescue = blockIdx.x == gridDim.x - 1;
     const int64_t sl_first = rescue ? 0 : (int64_t)blockIdx.x * kWgSlots + wave * kSPW;
@@ -772,7 +799,6 @@ __device__ __forceinline__ void count_rows(const TopkArgs &p, const Ws &w, Count
         info->bin_a = bin_a;
         info->need_a = need_a;
         info->M = 0u;                        // consumed by the second collect pass: zero for the next call
-        if (failed && p.warm > 0) info->warm_ok[p.warm - 1] = 0u;
     }
     if (failed) return;
     uint2 *tie = w.tie + row * kTieCap;
@@ -940,7 +966,7 @@ __device__ __forceinline__ void emit_rows(const TopkArgs &p, const Ws &w, EmitSh
     uint32_t &sh_T = sh.T, &sh_q = sh.q;
     static_assert(kTieCap <= kCandThreads, "one listed entry per thread");
     const int64_t row = blockIdx.y;
-    const int tid = threadIdx.x, wave = tid / kWave, lane = lane_id();
+    const int tid = threadIdx.x, wave = wave_id(), lane = lane_id();
     RowInfo *info = w.info + row;
     const bool rescue = blockIdx.x == gridDim.x - 1;
     const int64_t sl0 = rescue ? 0 : (int64_t)blockIdx.x * kWgSlots, sl_first = sl0 + wave * kSPW;
@@ -1106,12 +1132,12 @@ __global__ __launch_bounds__(kCandThreads) void zero_words_kernel(uint32_t *p, s
     for (size_t i = (size_t)blockIdx.x * kCandThreads + threadIdx.x; i < words; i += stride) p[i] = 0u;
 }
 
-template <bool DIFF, int U>
-void launch_collect_u(const TopkArgs &p, const Ws &w, int mode, const dim3 &grid, hipStream_t stream) {
+template <bool DIFF>
+void launch_collect_mode(const TopkArgs &p, const Ws &w, int mode, const dim3 &grid, hipStream_t stream) {
     const dim3 block(kBlk);
-    if (mode == kColdPass) hipLaunchKernelGGL((split_collect_kernel<DIFF, kColdPass, U>), grid, block, 0, stream, p, w);
-    else if (mode == kWarmPass) hipLaunchKernelGGL((split_collect_kernel<DIFF, kWarmPass, U>), grid, block, 0, stream, p, w);
-    else hipLaunchKernelGGL((split_collect_kernel<DIFF, kSecondPass, U>), grid, block, 0, stream, p, w);
+    if (mode == kColdPass) hipLaunchKernelGGL((split_collect_kernel<DIFF, kColdPass>), grid, block, 0, stream, p, w);
+    else if (mode == kWarmPass) hipLaunchKernelGGL((split_collect_kernel<DIFF, kWarmPass>), grid, block, 0, stream, p, w);
+    else hipLaunchKernelGGL((split_collect_kernel<DIFF, kSecondPass>), grid, block, 0, stream, p, w);
 }
 
 void launch_collect(const TopkArgs &p, const Ws &w, int mode, hipStream_t stream) {
@@ -1119,12 +1145,8 @@ void launch_collect(const TopkArgs &p, const Ws &w, int mode, hipStream_t stream
     int64_t g = w.G;
     if (mode == kSecondPass) g = std::max<int64_t>(1, std::min<int64_t>(w.G, 64 / p.n));
     const dim3 grid((unsigned)g, (unsigned)p.n);
-    // Steps per group.  Two arrays and two workgroups per compute unit: one step (128 KB in flight per unit; C4:
-    // 138 us against 142 with two steps and 147 without the second buffer); otherwise two (one array, one workgroup
-    // per unit, the C1 call: 31.7 us against 36 with one step and 33 with four).
-    if (p.b != nullptr && g * p.n > 256) launch_collect_u<true, 1>(p, w, mode, grid, stream);
-    else if (p.b != nullptr) launch_collect_u<true, 2>(p, w, mode, grid, stream);
-    else launch_collect_u<false, 2>(p, w, mode, grid, stream);
+    if (p.b != nullptr) launch_collect_mode<true>(p, w, mode, grid, stream);
+    else launch_collect_mode<false>(p, w, mode, grid, stream);
 }
 
 // ---------------------------------------------------------------- k = 1: the entry of largest magnitude
@@ -1337,14 +1359,8 @@ hipError_t launch_topk_split_pair(const TopkArgs &plain, const TopkArgs &markov,
     const bool warm = markov.warm > 0;
     const dim3 grid((unsigned)wm.G, (unsigned)markov.n), block(kBlk);
     double2 *norms = (double2 *)sums.norms;
-    const bool two_per_cu = wm.G * markov.n > 256;      // steps per group: see launch_collect
-#define EF21_PAIR(WARM, U) \
-    hipLaunchKernelGGL((split_collect_pair_kernel<WARM, U>), grid, block, 0, stream, markov, wm, plain.warm, wp, norms)
-    if (warm && two_per_cu) EF21_PAIR(true, 1);
-    else if (warm) EF21_PAIR(true, 2);
-    else if (two_per_cu) EF21_PAIR(false, 1);
-    else EF21_PAIR(false, 2);
-#undef EF21_PAIR
+    if (warm) hipLaunchKernelGGL(split_collect_pair_kernel<true>, grid, block, 0, stream, markov, wm, plain.warm, wp, norms);
+    else hipLaunchKernelGGL(split_collect_pair_kernel<false>, grid, block, 0, stream, markov, wm, plain.warm, wp, norms);
     mk(K_TOPK_COLLECT);
     if (warm) {
         const int64_t g = std::max<int64_t>(1, std::min<int64_t>(wm.G, 64 / markov.n));      // as in launch_collect
