@@ -462,7 +462,7 @@ int ef21_set_problem_dense(ef21_handle h, const float *A, const float *y, int64_
     if (m < 1 || m >= ((int64_t)1 << 31)) return fail(EF21_EINVAL, "m must be in [1, 2^31)");
     if (!(lambda >= 0.f) || !std::isfinite(lambda)) return fail(EF21_EINVAL, "lambda must be finite and >= 0");
     if (int rc = ensure_problem_buffers(h, ef21::logreg_dense_scratch_bytes(h->n, m, h->d))) return rc;
-    if (!h->tickets && ef21::small_step_applies(A, h->n, m, h->d, h->k)) {
+    if (!h->tickets && ef21::small_step_applies(h->n, m, h->d, h->k)) {
         const size_t bytes = ef21::small_step_ticket_bytes(h->n);
         if (hipMalloc(&h->tickets, bytes) != hipSuccess) {
             (void)hipGetLastError();
@@ -808,7 +808,7 @@ int ef21_step(ef21_handle h, const float *grads, uint32_t flags) {
         return enqueue_plus(h, grads, !step_first, mk);
     }
     if (!grads && h->kind == kDense && h->tickets && h->batch.tau == 0 && (flags & EF21_ONE_LAUNCH) &&
-        ef21::small_step_applies(h->A, h->n, h->m, h->d, h->k)) {
+        ef21::small_step_applies(h->n, h->m, h->d, h->k)) {
         // lines 5, 6, 8 (and 3) in one launch
         hipError_t st = ef21::launch_small_step(h->A, h->y, h->x, h->g, h->g_i, h->n, h->m, h->d, h->k, h->lambda,
                                                 h->gamma, h->loss, !step_first, h->scratch, h->tickets, h->msg_idx,

@@ -230,7 +230,7 @@ __global__ __launch_bounds__(kThreads) void plus_decide_long_kernel(const double
 // to them or written over them, and the new values are added to the sum in fp64.  A Markov row changes at the run's
 // positions only and is written there; a row that switches to the plain compressor is written whole.  The chosen pairs
 // are copied to the message buffers on the way.  What bounds it: the rows' bytes, read once and, where replaced,
-// written once (n = 5, d = 11.5 million, k = 575589, one row in five replaced: XX us; clearing, applying, averaging and
+// written once (n = 5, d = 11.5 million, k = 575589, one or two rows in five replaced: 110 us; clearing, applying, averaging and
 // stepping in four kernels took 140).
 constexpr int kApplyCols = 512;
 static_assert(kApplyCols == 1 << kPlusShift, "the message index has this block length");

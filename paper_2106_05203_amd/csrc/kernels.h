@@ -188,7 +188,7 @@ hipError_t launch_logreg_grad_csr(const int64_t *rowptr, const int32_t *col, con
 // results are the same bits.  small_step_applies says whether the shape qualifies (d <= 1024, n * k <= 2048,
 // n * m * d <= 2^24, ...).  scratch: logreg_dense_scratch_bytes; tickets: small_step_ticket_bytes(n) bytes,
 // zero before the first launch (the kernel leaves them zero).
-bool small_step_applies(const float *A, int32_t n, int64_t m, int64_t d, int64_t k);
+bool small_step_applies(int32_t n, int64_t m, int64_t d, int64_t k);
 size_t small_step_ticket_bytes(int32_t n);
 hipError_t launch_small_step(const float *A, const float *y, float *x, float *g, float *g_i, int32_t n, int64_t m,
                              int64_t d, int64_t k, float lambda, float gamma, int loss, bool take_step, void *scratch,

@@ -4,12 +4,12 @@
 // These are GEMV-shaped (each matrix entry is used twice, about one flop per byte), far below
 // the matrix-core ridge, so they are written as coalesced streaming kernels, not MFMA tiles.
 //
-// Dense rows, d <= 4096: ONE pass over A.  A wavefront owns whole rows; a lane keeps its columns
-// of the row in registers between the dot product (wavefront reduction, no LDS) and the rank-one
+// Dense rows, d <= 4096: ONE pass over A.  A group of lanes owns whole rows; a lane keeps its columns
+// of the row in registers between the dot product (a sum over the group, no LDS) and the rank-one
 // accumulation r_l * a_l into per-lane accumulators.  Workgroups write partial sums that a small
 // second kernel adds in a fixed order (bitwise reproducible), together with the regulariser.
 // Dense rows, d up to 28672: the same with a workgroup per row (logreg_dense_wide_kernel).
-// Dense rows, larger d (and d < 4): z = A x, then A^T r, two passes.  (CSR rows: logreg_csr.hip.)
+// Dense rows, larger d: z = A x, then A^T r, two passes.  (CSR rows: logreg_csr.hip.)
 #include "device_utils.h"
 #include "kernels.h"
 #include "logreg_dense_block.h"
@@ -22,7 +22,7 @@ constexpr int kThreads = kDenseThreads;
 constexpr int kWaves = kDenseWaves;
 
 // ------------------------------------------------------------------ dense, one pass over A
-template <int VEC, int NQ, int ROWS, bool BATCH>
+template <int LANES, int NQ, bool DEEP, int SHAPE, bool BATCH>
 __global__ __launch_bounds__(kThreads) void logreg_dense_fused_kernel(const float *__restrict__ A,
                                                                       const float *__restrict__ y,
                                                                       const float *__restrict__ x,
@@ -30,11 +30,11 @@ __global__ __launch_bounds__(kThreads) void logreg_dense_fused_kernel(const floa
                                                                       int64_t d, int64_t rows_per_wg, int loss,
                                                                       const int32_t *__restrict__ batch,
                                                                       int64_t m_full, int64_t x_stride) {
-    __shared__ float red[NQ * kWave * VEC];
+    __shared__ __attribute__((aligned(16))) float red[NQ * LANES * 4];
     const int64_t worker = blockIdx.y;
-    dense_block<VEC, NQ, ROWS, BATCH>(A, y, x + worker * x_stride /* 0: one x for all workers */, part, m, d,
+    dense_block<LANES, NQ, dense_rows_in_flight<LANES, NQ, DEEP>(), SHAPE, BATCH>(A, y, x + worker * x_stride /* 0: one x for all workers */, part, m, d,
                                       rows_per_wg, loss, batch, m_full, worker, blockIdx.x, gridDim.x,
-                                      threadIdx.x / kWave, threadIdx.x, true, red);
+                                      wave_id(), threadIdx.x, true, red);
 }
 
 // ------------------------------------------------------------------ dense, wide rows, one pass over A
@@ -226,7 +226,7 @@ __global__ __launch_bounds__(kWideThreads) void logreg_dense_wide_kernel(const f
 
 // Rows of a worker are cut so that all workers together have about one workgroup per compute unit, at least four
 // rows each (a chunk's partial sums cost as much traffic as one of its rows, written and read again).  Never more
-// chunks per worker than the partial sums have room for (max_chunks: one from n = 257 on).
+// chunks per worker than the partial sums have room for (max_chunks).
 DensePlan wide_plan(int32_t n, int64_t m, int chunks_per_wg) {
     int64_t target = 256 / n;
     if (target < 1) target = 1;
@@ -311,18 +311,32 @@ struct DenseArgs {
     int loss;
     const int32_t *batch;
     int64_t m_full, x_stride;
+    bool deep;
 };
 
-template <int VEC, int NQ>
-void launch_fused(const DenseArgs &a, hipStream_t stream) {
-    constexpr int ROWS = dense_rows_in_flight<VEC, NQ>();
+template <int LANES, int NQ, bool DEEP, int SHAPE>
+void launch_fused_rows(const DenseArgs &a, hipStream_t stream) {
     const dim3 grid((unsigned)a.pl.chunks, (unsigned)a.n);
     if (a.batch)
-        hipLaunchKernelGGL((logreg_dense_fused_kernel<VEC, NQ, ROWS, true>), grid, dim3(kThreads), 0, stream, a.A, a.y,
-                           a.x, a.part, a.m, a.d, a.pl.rows_per_wg, a.loss, a.batch, a.m_full, a.x_stride);
+        hipLaunchKernelGGL((logreg_dense_fused_kernel<LANES, NQ, DEEP, SHAPE, true>), grid, dim3(kThreads), 0, stream, a.A,
+                           a.y, a.x, a.part, a.m, a.d, a.pl.rows_per_wg, a.loss, a.batch, a.m_full, a.x_stride);
     else
-        hipLaunchKernelGGL((logreg_dense_fused_kernel<VEC, NQ, ROWS, false>), grid, dim3(kThreads), 0, stream, a.A, a.y,
-                           a.x, a.part, a.m, a.d, a.pl.rows_per_wg, a.loss, a.batch, a.m_full, a.x_stride);
+        hipLaunchKernelGGL((logreg_dense_fused_kernel<LANES, NQ, DEEP, SHAPE, false>), grid, dim3(kThreads), 0, stream, a.A,
+                           a.y, a.x, a.part, a.m, a.d, a.pl.rows_per_wg, a.loss, a.batch, a.m_full, a.x_stride);
+}
+
+template <int LANES, int NQ>
+void launch_fused(const DenseArgs &a, hipStream_t stream) {
+    const bool quads = a.d % 4 == 0;
+    if constexpr (NQ < 8) {
+        if (a.deep) {
+            if (quads) launch_fused_rows<LANES, NQ, true, kQuadRows>(a, stream);
+            else launch_fused_rows<LANES, NQ, true, kRaggedRows>(a, stream);
+            return;
+        }
+    }
+    if (quads) launch_fused_rows<LANES, NQ, false, kQuadRows>(a, stream);
+    else launch_fused_rows<LANES, NQ, false, kRaggedRows>(a, stream);
 }
 
 template <int NQ, bool RAGGED>
@@ -355,24 +369,26 @@ hipError_t launch_logreg_grad_dense(const float *A, const float *y, const float 
     if (defer) *defer = GradParts();
     const int32_t *batch = rb.tau > 0 ? rb.rows : nullptr;
     const int64_t m = batch ? rb.tau : m_full;         // rows summed per worker (tau <= m_full, checked by the caller)
-    const bool vec4 = (d % 4 == 0) && ((uintptr_t)A % 16 == 0);
-    const DenseVariant dv = dense_variant(d, vec4);
-    const bool wide = dv.vec == 0 && d <= kWideMax && d >= 4;
+    const DenseVariant dv = dense_variant(d);
+    const bool deep = dense_deep(n, m_full, d) && d >= 4;
+    const bool wide = dv.lanes == 0 && d <= kWideMax && d >= 4;
     const DensePlan pl = wide ? wide_plan(n, m, d > 4 * 4 * kWideThreads ? wide_chunks<5>() : wide_chunks<4>())
-                              : dense_plan(n, m);
+                              : dense_plan(n, m, d, deep);
     float *part = (float *)scratch;
     float *resid = part + (size_t)n * max_chunks(n, m_full) * d;
-    const DenseArgs a{A, y, x, part, n, m, d, pl, loss, batch, m_full, x_stride};
-    const bool fused = dv.vec != 0 || wide;
-    switch (dv.vec * 100 + dv.nq) {
-        case 401: launch_fused<4, 1>(a, stream); break;
-        case 402: launch_fused<4, 2>(a, stream); break;
-        case 404: launch_fused<4, 4>(a, stream); break;
-        case 408: launch_fused<4, 8>(a, stream); break;
-        case 416: launch_fused<4, 16>(a, stream); break;
-        case 102: launch_fused<1, 2>(a, stream); break;
-        case 108: launch_fused<1, 8>(a, stream); break;
-        case 132: launch_fused<1, 32>(a, stream); break;
+    const DenseArgs a{A, y, x, part, n, m, d, pl, loss, batch, m_full, x_stride, deep};
+    const bool fused = dv.lanes != 0 || wide;
+    switch (dv.lanes * 100 + dv.nq) {
+        case 1601:
+            if (d < 4) launch_fused_rows<16, 1, false, kTinyRows>(a, stream);
+            else launch_fused<16, 1>(a, stream);
+            break;
+        case 3201: launch_fused<32, 1>(a, stream); break;
+        case 6401: launch_fused<64, 1>(a, stream); break;
+        case 6402: launch_fused<64, 2>(a, stream); break;
+        case 6404: launch_fused<64, 4>(a, stream); break;
+        case 6408: launch_fused<64, 8>(a, stream); break;
+        case 6416: launch_fused_rows<64, 16, false, kQuadRows>(a, stream); break;
         default: break;
     }
     if (wide) {

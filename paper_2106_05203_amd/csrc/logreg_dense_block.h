@@ -14,22 +14,9 @@ struct DensePlan {
     int64_t chunks;   // row blocks per worker
 };
 
-// About two workgroups per compute unit in all (512 on 256 CUs), each streaming one long block of rows:
-// fewer, longer blocks measured faster than several rounds of short ones, and they leave fewer partial
-// sums to add.  At least 8 rows each.
-inline DensePlan dense_plan(int32_t n, int64_t m) {
-    int64_t target = 512 / n;
-    if (target < 1) target = 1;
-    int64_t rows = (m + target - 1) / target;
-    if (rows < 8) rows = 8;
-    return {rows, (m + rows - 1) / rows};
-}
-
-// No batch of tau <= m rows gets more blocks per worker than this (the partial sums are sized by it).
+// Row blocks per worker that the partial sums have room for: about two workgroups per compute unit over all workers.
 inline int64_t max_chunks(int32_t n, int64_t m) {
-    int64_t target = 512 / n;
-    if (target < 1) target = 1;
-    const int64_t by_rows = (m + 3) / 4;
+    const int64_t target = (512 + n - 1) / n, by_rows = (m + 3) / 4;
     return by_rows < target ? by_rows : target;
 }
 
@@ -40,133 +27,193 @@ __device__ __forceinline__ int64_t batch_row(const int32_t *__restrict__ batch, 
     return b < (uint64_t)m_full ? (int64_t)b : -1;
 }
 
+// Which instantiation of dense_block serves rows of d columns (the kernels that must agree bit for bit choose through
+// this one function): LANES lanes of a wavefront per row, NQ quads of columns per lane.  {0, 0}: none (a workgroup per
+// row, or two passes).  Rows longer than 2048 whose length is no multiple of four go to the workgroup-per-row kernel.
+struct DenseVariant {
+    int lanes, nq;
+};
+enum RowShape { kQuadRows = 0 /* d % 4 == 0 */, kRaggedRows = 1, kTinyRows = 2 /* d < 4 */ };
+
+inline DenseVariant dense_variant(int64_t d) {
+    if (d <= 64) return {16, 1};
+    if (d <= 128) return {32, 1};
+    if (d <= 256) return {64, 1};
+    if (d <= 512) return {64, 2};
+    if (d <= 1024) return {64, 4};
+    if (d <= 2048) return {64, 8};
+    if (d <= 4096 && d % 4 == 0) return {64, 16};
+    return {0, 0};
+}
+
+// Rows in flight per group of LANES lanes: 32 row entries per lane for short rows of small problems (more does not fit
+// the registers of the 1024-thread kernel that shares this code), 64 otherwise (`deep`: n = 16, m = 8000, d = 60, 31 MB, the whole
+// gradient 11.6 us with 32 entries, 10.9 with 64); one row where a row alone fills the registers.
+constexpr int64_t kSmallProblem = (int64_t)1 << 24;                       // n * m * d
+template <int LANES, int NQ, bool DEEP>
+constexpr int dense_rows_in_flight() {
+    if (NQ >= 8) return NQ == 8 ? 2 : 1;
+    return (LANES == 16 ? 4 : 8 / NQ) * (DEEP ? 2 : 1);
+}
+inline bool dense_deep(int32_t n, int64_t m_full, int64_t d) { return (int64_t)n * m_full * d > kSmallProblem; }
+
+// Rows that a block of kDenseWaves wavefronts takes per trip, for rows of d columns.
+inline int64_t dense_trip_rows(int64_t d, bool deep) {
+    const DenseVariant v = dense_variant(d);
+    if (v.nq >= 8) return kDenseWaves * (v.nq == 8 ? 2 : 1);
+    return (v.lanes == 64 ? kDenseWaves * (8 / v.nq) : 64) * (deep ? 2 : 1);
+}
+
+// About two workgroups per compute unit in all (512 on 256 CUs), each streaming one long block of rows:
+// fewer, longer blocks measured faster than several rounds of short ones, and they leave fewer partial
+// sums to add.  At least 8 rows each, 32 short ones (12 KB): below that the sums cost more than the rows.  One block
+// more where that saves every block a trip.
+inline DensePlan dense_plan(int32_t n, int64_t m, int64_t d, bool deep) {
+    int64_t target = 512 / n;
+    if (target < 1) target = 1;
+    const int64_t trip = dense_trip_rows(d, deep), least = d <= 128 ? 32 : (d <= 256 ? 16 : 8);
+    int64_t rows = (m + target - 1) / target;
+    const int64_t fewer = (m + max_chunks(n, m) - 1) / max_chunks(n, m);
+    if ((fewer + trip - 1) / trip < (rows + trip - 1) / trip) rows = fewer;
+    // Small problems: at most 32 sums per worker, because one workgroup per worker adds them up in the Top-k kernel of
+    // ef21_step (n = 5, m = 700, d = 1001: 88 of them took 16 us there).
+    if ((int64_t)n * m * d <= ((int64_t)1 << 23) && rows < (m + 31) / 32) rows = (m + 31) / 32;
+    if (rows < least) rows = least;
+    return {rows, (m + rows - 1) / rows};
+}
+
 // One row block: rows [chunk * rows_per_wg, +rows_per_wg) of `worker`, by kDenseWaves wavefronts (`wave` = this
-// wavefront's number among them, `tid` = the thread's among their kDenseThreads).  A wavefront owns whole rows;
-// a lane keeps its columns of the row in registers between the dot product (wavefront reduction) and the
-// rank-one accumulation coef * a_l.  `red` (NQ * kWave * VEC floats of LDS, the block's own) adds the
-// wavefronts' accumulators in wavefront order; the result goes to part[worker][chunk][0..d).  Every thread of
-// the workgroup must call (it holds workgroup barriers); `active` = false does no work and writes nothing.
+// wavefront's number among them, `tid` = the thread's among their kDenseThreads).  A group of LANES lanes owns whole
+// rows; a lane keeps its columns of the row, NQ quads, in registers between the dot product (a sum over the group) and
+// the rank-one accumulation coef * a_l.  Rows need no alignment: in ragged rows (d no multiple of four) the quad that
+// straddles the end of the row is moved back onto its last four columns, those of them that belong to the quad before
+// it count as zero; rows of less than four columns are read one by one.  `red` (NQ * LANES * 4 floats of LDS, the block's own) adds the wavefronts' accumulators in
+// wavefront order; the result goes to part[worker][chunk][0..d).  Every thread of the workgroup must call (it holds
+// workgroup barriers); `active` = false does no work and writes nothing.
 // BATCH: the m rows of a worker are the entries of batch[worker][0..m) (row numbers inside its m_full rows), the
-// minibatch of Algorithm 5; otherwise m_full == m and row l is row l.
-template <int VEC, int NQ, int ROWS, bool BATCH>
+// minibatch of Algorithm 5, read one trip ahead; otherwise m_full == m and row l is row l.
+// n = 20, m = 1628, d = 123 (16 MB): 10.5 us with four-byte loads and a wavefront per row, 6.7 so; a minibatch of 625 of
+// 5000 rows of 2000 (100 MB): 25.1 -> 21.3 us.
+template <int LANES, int NQ, int ROWS, int SHAPE, bool BATCH>
 __device__ __forceinline__ void dense_block(const float *__restrict__ A, const float *__restrict__ y,
                                             const float *__restrict__ x, float *__restrict__ part, int64_t m,
                                             int64_t d, int64_t rows_per_wg, int loss,
                                             const int32_t *__restrict__ batch, int64_t m_full, int64_t worker,
                                             int64_t chunk, int64_t chunks, int wave, int tid, bool active,
                                             float *red) {
-    constexpr int kCols = NQ * kWave * VEC;   // columns covered by one wavefront
-    const int lane = lane_id();
+    constexpr int kCols = NQ * LANES * 4;     // columns covered by one group
+    constexpr int kGroups = kWave / LANES;    // rows side by side
+    const int lane = lane_id(), sub = lane % LANES, group = lane / LANES;
 
-    float xr[NQ][VEC], acc[NQ][VEC];
+    int32_t at[NQ];                           // where the quad is read
+    int dup[NQ];                              // its leading columns that are another quad's; 4: past the end of the row
+    float xr[NQ][4], acc[NQ][4];
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
-        const int64_t c0 = ((int64_t)q * kWave + lane) * VEC;
+        const int32_t c0 = (q * LANES + sub) * 4, last = (int32_t)d - 4;
+        at[q] = SHAPE == kTinyRows ? 0 : (c0 < last ? c0 : last);
+        dup[q] = c0 - at[q] < 4 ? c0 - at[q] : 4;
 #pragma unroll
-        for (int t = 0; t < VEC; ++t) {
-            xr[q][t] = (c0 + t < d) ? x[c0 + t] : 0.f;
+        for (int t = 0; t < 4; ++t) {
+            const float xv = SHAPE != kTinyRows || t < d ? x[at[q] + t] : 0.f;
+            xr[q][t] = t >= dup[q] ? xv : 0.f;
             acc[q][t] = 0.f;
         }
     }
 
-    // ROWS rows per wavefront and trip: their loads are all issued before the first dot product.  A row
-    // index past the block is clamped to the block's last row and its coefficient set to zero.
+    // ROWS rows per group and trip: their loads are all issued before the first dot product.  A row index past the
+    // block is clamped to the block's last row and its coefficient set to zero.
     const int64_t l0 = chunk * rows_per_wg;
     const int64_t l1 = !active ? l0 : (l0 + rows_per_wg < m ? l0 + rows_per_wg : m);
-    for (int64_t l = l0 + wave * ROWS; l < l1; l += kDenseWaves * ROWS) {
-        float av[ROWS][NQ][VEC], yl[ROWS], s[ROWS];
+    constexpr int64_t kTrip = (int64_t)kDenseWaves * ROWS * kGroups;
+    auto listed = [&](int64_t l, int64_t (&src)[ROWS]) {          // row numbers of a trip
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) {
+            const int64_t lr = l + r * kGroups + group < l1 ? l + r * kGroups + group : l1 - 1;
+            src[r] = BATCH ? batch_row(batch, worker * m + lr, m_full) : lr;
+        }
+    };
+    int64_t src[ROWS];
+    const int64_t first = l0 + wave * ROWS * kGroups;
+    if (first < l1) listed(first, src);
+    for (int64_t l = first; l < l1; l += kTrip) {
+        float av[ROWS][NQ][4], yl[ROWS], s[ROWS];
         bool live[ROWS];
 #pragma unroll
         for (int r = 0; r < ROWS; ++r) {
-            int64_t lr = l + r < l1 ? l + r : l1 - 1;
-            live[r] = l + r < l1;
-            if constexpr (BATCH) {
-                lr = batch_row(batch, worker * m + lr, m_full);
-                if (lr < 0) {
-                    lr = 0;
-                    live[r] = false;
-                }
-            }
+            live[r] = l + r * kGroups + group < l1 && (!BATCH || src[r] >= 0);
+            const int64_t lr = BATCH && src[r] < 0 ? 0 : src[r];
             const float *row = A + (worker * m_full + lr) * d;
             yl[r] = y[worker * m_full + lr];
 #pragma unroll
             for (int q = 0; q < NQ; ++q) {
-                const int64_t c0 = ((int64_t)q * kWave + lane) * VEC;
-                if constexpr (VEC == 4) {
-                    float4 t4 = make_float4(0.f, 0.f, 0.f, 0.f);
-                    if (c0 < d) t4 = stream_load4(row + c0);
-                    av[r][q][0] = t4.x;
-                    av[r][q][1] = t4.y;
-                    av[r][q][2] = t4.z;
-                    av[r][q][3] = t4.w;
+                if constexpr (SHAPE == kTinyRows) {
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) av[r][q][t] = t < d ? stream_load(row + t) : 0.f;
                 } else {
-                    av[r][q][0] = (c0 < d) ? stream_load(row + c0) : 0.f;
+                    const float4 t4 = stream_load4_any(row + at[q]);
+                    av[r][q][0] = SHAPE == kRaggedRows && dup[q] > 0 ? 0.f : t4.x;
+                    av[r][q][1] = SHAPE == kRaggedRows && dup[q] > 1 ? 0.f : t4.y;
+                    av[r][q][2] = SHAPE == kRaggedRows && dup[q] > 2 ? 0.f : t4.z;
+                    av[r][q][3] = t4.w;
                 }
             }
         }
+        if (l + kTrip < l1) listed(l + kTrip, src);
 #pragma unroll
         for (int r = 0; r < ROWS; ++r) {
             s[r] = 0.f;
 #pragma unroll
-            for (int q = 0; q < NQ; ++q)
+            for (int q = 0; q < NQ; ++q) {
+                float p = s[r];
 #pragma unroll
-                for (int t = 0; t < VEC; ++t) s[r] = fmaf(av[r][q][t], xr[q][t], s[r]);
+                for (int t = 0; t < 4; ++t) p = fmaf(av[r][q][t], xr[q][t], p);
+                s[r] = dup[q] < 4 ? p : s[r];                     // (an infinity of another column times zero)
+            }
         }
 #pragma unroll
-        for (int r = 0; r < ROWS; ++r) s[r] = wave_sum(s[r]);
+        for (int r = 0; r < ROWS; ++r) s[r] = group_sum<LANES>(s[r]);
 #pragma unroll
         for (int r = 0; r < ROWS; ++r) {
             const float coef = live[r] ? loss_derivative(yl[r], s[r], loss) : 0.f;
 #pragma unroll
             for (int q = 0; q < NQ; ++q)
 #pragma unroll
-                for (int t = 0; t < VEC; ++t) acc[q][t] = fmaf(coef, av[r][q][t], acc[q][t]);
+                for (int t = 0; t < 4; ++t) acc[q][t] = fmaf(coef, av[r][q][t], acc[q][t]);
         }
     }
 
-    // add the wavefronts' accumulators in wavefront order
+    // the groups of a wavefront, then the wavefronts in order
+#pragma unroll
+    for (int q = 0; q < NQ; ++q)
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int o = LANES; o < kWave; o <<= 1) acc[q][t] += __shfl_xor(acc[q][t], o, kWave);
     for (int w = 0; w < kDenseWaves; ++w) {
-        if (wave == w) {
+        if (wave == w && group == 0) {
 #pragma unroll
-            for (int q = 0; q < NQ; ++q)
-#pragma unroll
-                for (int t = 0; t < VEC; ++t) {
-                    const int c = (q * kWave + lane) * VEC + t;
-                    red[c] = (w == 0 ? 0.f : red[c]) + acc[q][t];
+            for (int q = 0; q < NQ; ++q) {
+                float4 *slot = reinterpret_cast<float4 *>(red) + q * LANES + sub;
+                float4 sum = make_float4(acc[q][0], acc[q][1], acc[q][2], acc[q][3]);
+                if (w > 0) {
+                    const float4 before = *slot;
+                    sum = make_float4(before.x + sum.x, before.y + sum.y, before.z + sum.z, before.w + sum.w);
                 }
+                *slot = sum;
+            }
         }
         __syncthreads();
     }
+    // entry e of `red` is entry e % 4 of quad e / 4, which was read at min(e / 4 * 4, d - 4): the straddling quad's
+    // leading columns are another's
     if (active) {
         float *out = part + (worker * chunks + chunk) * d;
-        for (int c = tid; c < kCols && c < d; c += kDenseThreads) out[c] = red[c];
+        for (int e = tid; e < kCols; e += kDenseThreads) {
+            const int32_t c0 = e & ~3, last = SHAPE == kTinyRows ? 0 : (int32_t)d - 4, c = (c0 < last ? c0 : last) + (e & 3);
+            if (c >= c0 && c < d) out[c] = red[e];
+        }
     }
-}
-
-// Which instantiation (VEC, NQ) of dense_block serves rows of d columns: the kernels that must agree bit for
-// bit choose through this one function.  vec4: d % 4 == 0 and A 16-byte aligned.  {0, 0}: none (two passes).
-struct DenseVariant {
-    int vec, nq;
-};
-inline DenseVariant dense_variant(int64_t d, bool vec4) {
-    if (vec4 && d <= 256) return {4, 1};
-    if (vec4 && d <= 512) return {4, 2};
-    if (vec4 && d <= 1024) return {4, 4};
-    if (vec4 && d <= 2048) return {4, 8};
-    if (vec4 && d <= 4096) return {4, 16};
-    if (d <= 128) return {1, 2};
-    if (d <= 512) return {1, 8};
-    if (d <= 2048) return {1, 32};
-    return {0, 0};
-}
-
-// Rows of a wavefront in flight: 32 row entries per lane for narrow rows (a wavefront would otherwise have only
-// a kilobyte or two of loads outstanding; more does not fit the registers of the 1024-thread kernel that shares
-// this code), at most eight rows; two rows of 32 entries per lane; one where a row alone fills the registers.
-template <int VEC, int NQ>
-constexpr int dense_rows_in_flight() {
-    constexpr int per_lane = NQ * VEC;
-    return per_lane > 32 ? 1 : (per_lane >= 16 ? 2 : (per_lane >= 8 ? 4 : 8));
 }
 
 }  // namespace ef21

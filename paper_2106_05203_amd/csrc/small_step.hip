@@ -22,7 +22,6 @@ constexpr int kBlocksPerWg = kRowThreads / kDenseThreads;   // 4 row blocks per 
 constexpr int kMaxCols = 1024;                              // d of the fused iteration
 constexpr int kMaxEntries = 2048;                           // n * k
 constexpr int kMaxAddSteps = 512;                           // n * ceil(k / 64), the adding wavefront's steps
-constexpr int64_t kMaxProblem = (int64_t)1 << 24;           // n * m * d
 
 struct SmallArgs {
     const float *A, *y;
@@ -53,10 +52,10 @@ __device__ __forceinline__ bool draw_ticket(uint32_t *counter, uint32_t tickets,
     return *flag != 0u;
 }
 
-template <int VEC, int NQ>
+template <int LANES, int NQ, int SHAPE>
 __global__ __launch_bounds__(kRowThreads) void small_step_kernel(SmallArgs a) {
     __shared__ RowShared s;
-    __shared__ float red[kBlocksPerWg][NQ * kWave * VEC];
+    __shared__ __attribute__((aligned(16))) float red[kBlocksPerWg][NQ * LANES * 4];
     __shared__ float cache[kMaxCols];
     __shared__ int32_t m_idx[kMaxEntries];
     __shared__ float m_val[kMaxEntries];
@@ -68,9 +67,9 @@ __global__ __launch_bounds__(kRowThreads) void small_step_kernel(SmallArgs a) {
     {
         const int vb = tid / kDenseThreads;
         const int64_t chunk = (int64_t)blockIdx.x * kBlocksPerWg + vb;
-        dense_block<VEC, NQ, dense_rows_in_flight<VEC, NQ>(), false>(
+        dense_block<LANES, NQ, dense_rows_in_flight<LANES, NQ, false>(), SHAPE, false>(
             a.A, a.y, a.x, a.part, a.m, a.d, a.rows_per_wg, a.loss, nullptr, a.m, worker, chunk, a.chunks,
-            (tid / kWave) % kDenseWaves, tid % kDenseThreads, chunk < a.chunks, red[vb]);
+            wave_id() % kDenseWaves, tid % kDenseThreads, chunk < a.chunks, red[vb]);
     }
     if (!draw_ticket(&a.tickets[worker], gridDim.x, &last)) return;     // the partial sums of the others, or done
 
@@ -112,19 +111,20 @@ __global__ __launch_bounds__(kRowThreads) void small_step_kernel(SmallArgs a) {
     }
 }
 
-template <int VEC, int NQ>
+template <int LANES, int NQ>
 void launch(const SmallArgs &a, hipStream_t stream) {
     const dim3 grid((unsigned)((a.chunks + kBlocksPerWg - 1) / kBlocksPerWg), (unsigned)a.n);
-    hipLaunchKernelGGL((small_step_kernel<VEC, NQ>), grid, dim3(kRowThreads), 0, stream, a);
+    const dim3 block(kRowThreads);
+    if (a.d % 4 == 0) hipLaunchKernelGGL((small_step_kernel<LANES, NQ, kQuadRows>), grid, block, 0, stream, a);
+    else if (a.d > 4) hipLaunchKernelGGL((small_step_kernel<LANES, NQ, kRaggedRows>), grid, block, 0, stream, a);
+    else if constexpr (LANES == 16) hipLaunchKernelGGL((small_step_kernel<LANES, NQ, kTinyRows>), grid, block, 0, stream, a);
 }
 
 }  // namespace
 
-bool small_step_applies(const float *A, int32_t n, int64_t m, int64_t d, int64_t k) {
-    const bool vec4 = (d % 4 == 0) && ((uintptr_t)A % 16 == 0);
-    const DenseVariant dv = dense_variant(d, vec4);
-    return d <= kMaxCols && dv.vec != 0 && dv.vec * dv.nq <= 16 && n < kRowThreads && (int64_t)n * k <= kMaxEntries &&
-           (int64_t)n * ((k + kWave - 1) / kWave) <= kMaxAddSteps && (int64_t)n * m * d <= kMaxProblem;
+bool small_step_applies(int32_t n, int64_t m, int64_t d, int64_t k) {
+    return d <= kMaxCols && dense_variant(d).lanes != 0 && n < kRowThreads && (int64_t)n * k <= kMaxEntries &&
+           (int64_t)n * ((k + kWave - 1) / kWave) <= kMaxAddSteps && (int64_t)n * m * d <= kSmallProblem;
 }
 
 size_t small_step_ticket_bytes(int32_t n) { return sizeof(uint32_t) * ((size_t)n + 1); }
@@ -132,18 +132,17 @@ size_t small_step_ticket_bytes(int32_t n) { return sizeof(uint32_t) * ((size_t)n
 hipError_t launch_small_step(const float *A, const float *y, float *x, float *g, float *g_i, int32_t n, int64_t m,
                              int64_t d, int64_t k, float lambda, float gamma, int loss, bool take_step, void *scratch,
                              void *tickets, int32_t *msg_idx, float *msg_val, hipStream_t stream) {
-    if (!small_step_applies(A, n, m, d, k)) return hipErrorInvalidValue;
-    const DensePlan pl = dense_plan(n, m);
+    if (!small_step_applies(n, m, d, k)) return hipErrorInvalidValue;
+    const DensePlan pl = dense_plan(n, m, d, false);
     const SmallArgs a{A, y, x, g, g_i, (float *)scratch, msg_idx, msg_val, (uint32_t *)tickets, n, m, d, k,
                       pl.rows_per_wg, pl.chunks, lambda, 1.0f / (float)n, -gamma, loss, take_step ? 1 : 0};
-    const bool vec4 = (d % 4 == 0) && ((uintptr_t)A % 16 == 0);
-    const DenseVariant dv = dense_variant(d, vec4);
-    switch (dv.vec * 100 + dv.nq) {
-        case 401: launch<4, 1>(a, stream); break;
-        case 402: launch<4, 2>(a, stream); break;
-        case 404: launch<4, 4>(a, stream); break;
-        case 102: launch<1, 2>(a, stream); break;
-        case 108: launch<1, 8>(a, stream); break;
+    const DenseVariant dv = dense_variant(d);
+    switch (dv.lanes * 100 + dv.nq) {
+        case 1601: launch<16, 1>(a, stream); break;
+        case 3201: launch<32, 1>(a, stream); break;
+        case 6401: launch<64, 1>(a, stream); break;
+        case 6402: launch<64, 2>(a, stream); break;
+        case 6404: launch<64, 4>(a, stream); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();

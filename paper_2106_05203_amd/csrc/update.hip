@@ -233,6 +233,7 @@ __global__ __launch_bounds__(kThreads) void aggregate_many_kernel(const int32_t 
 // program order, so no barrier is needed between workers) while the other wavefronts fetch g and x.
 constexpr int kSmallThreads = 1024, kSmallPer = 8;
 constexpr int kSmallD = 16384, kSmallEntries = kSmallThreads * kSmallPer;
+constexpr int kScanEntries = 128;    // messages in all that every coordinate can look through (n = 20, k = 4: 4.8 -> 2.8 us)
 constexpr int kSmallFetch = 4;      // coordinates per thread fetched ahead (d <= 4096)
 constexpr int kSmallSteps = 512;    // at most this many sequential steps of the adding wavefront
 
@@ -243,8 +244,8 @@ __global__ __launch_bounds__(kSmallThreads) void aggregate_small_kernel(const in
                                                                         float *__restrict__ x, float inv_n,
                                                                         float neg_gamma, bool from_zero) {
     __shared__ float acc[kSmallD];
-    __shared__ int32_t m_idx[kSmallEntries];
-    __shared__ float m_val[kSmallEntries];
+    __shared__ __attribute__((aligned(16))) int32_t m_idx[kSmallEntries];
+    __shared__ __attribute__((aligned(16))) float m_val[kSmallEntries];
     const int tid = threadIdx.x, lane = lane_id();
     const int64_t total = (int64_t)n * k;
     int32_t e[kSmallPer];
@@ -265,8 +266,31 @@ __global__ __launch_bounds__(kSmallThreads) void aggregate_small_kernel(const in
             m_val[t] = v[u];
         }
     }
+    if (total <= kScanEntries && tid < 8) m_idx[total + tid] = -1;      // the scan below takes eight at a time
     __syncthreads();
     const bool ahead = d <= (int64_t)kSmallFetch * kSmallThreads;
+    if (total <= kScanEntries && d <= kSmallThreads) {       // few messages: every coordinate looks through them all
+        if (tid < d) {
+            const float g0 = from_zero ? 0.f : g[tid], x0 = STEP ? x[tid] : 0.f;
+            float a = 0.f;
+            for (int t = 0; t < (int)total; t += 8) {        // eight at a time, in order: worker after worker
+                const int4 i0 = *reinterpret_cast<const int4 *>(m_idx + t), i1 = *reinterpret_cast<const int4 *>(m_idx + t + 4);
+                const float4 v0 = *reinterpret_cast<const float4 *>(m_val + t), v1 = *reinterpret_cast<const float4 *>(m_val + t + 4);
+                a = i0.x == tid ? a + v0.x : a;
+                a = i0.y == tid ? a + v0.y : a;
+                a = i0.z == tid ? a + v0.z : a;
+                a = i0.w == tid ? a + v0.w : a;
+                a = i1.x == tid ? a + v1.x : a;
+                a = i1.y == tid ? a + v1.y : a;
+                a = i1.z == tid ? a + v1.z : a;
+                a = i1.w == tid ? a + v1.w : a;
+            }
+            const float gn = fmaf(a, inv_n, g0);
+            g[tid] = gn;
+            if (STEP) x[tid] = fmaf(neg_gamma, gn, x0);
+        }
+        return;                                              // the whole workgroup
+    }
     float gj[kSmallFetch], xj[kSmallFetch];
     if (tid < kWave) {
         for (int32_t w = 0; w < n; ++w) {           // worker order
