@@ -30,8 +30,10 @@ constexpr int kAtrThreads = 1024;
 constexpr int kAtrWaves = kAtrThreads / kWave;
 constexpr int kCscThreads = 512;      // pass 2
 constexpr int kCscWaves = kCscThreads / kWave;
-constexpr int kCscGroups = 4;         // groups of 64 consecutive columns per wavefront
-constexpr int kCscCols = kCscWaves * kCscGroups * kWave;   // columns per workgroup
+// Groups of 64 consecutive segments (rows or columns) per wavefront: four, or one where four would leave most of the
+// chip without a workgroup (csr_groups).
+constexpr int kManyGroups = 4, kFewGroups = 1;
+constexpr int64_t group_segments(int groups) { return (int64_t)kCscWaves * groups * kWave; }   // per workgroup
 constexpr int kTile = 1024;           // staged products per wavefront: four loads of four entries per lane
 constexpr int64_t kCscPad = 2048;     // zeroed entries after the column-major copy (tiles are loaded whole)
 constexpr int64_t kIdx16Rows = 65536; // m up to this: 16-bit row indices in the column-major copy
@@ -233,31 +235,40 @@ __global__ __launch_bounds__(kAtrThreads) void csrr_build_kernel(const int64_t *
     }
 }
 
+// The value of one lane as a scalar.
+__device__ __forceinline__ int64_t lane_value(int64_t v, int lane) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, lane);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)v >> 32), lane);
+    return (int64_t)(((uint64_t)hi << 32) | lo);
+}
+
 // ---- both passes: sums over segments of a contiguous list of (index, value) pairs.
-// The calling wavefront owns 4 x 64 consecutive segments; lane j holds the entry ranges [b[g], e[g]) of
+// The calling wavefront owns GROUPS x 64 consecutive segments; lane j holds the entry ranges [b[g], e[g]) of
 // segments j, j + 64, ... (ascending and contiguous over (g, lane); an empty range where there is no
 // segment).  The span is walked in tiles of 1024 entries aligned to four entries: each lane loads four
 // times four consecutive pairs (the next tile's loads are issued before this tile is summed), multiplies the
 // values by vec(index) and stages the products in LDS; then every lane adds, for each of its segments, the piece
 // that lies in the tile, in storage order (a piece longer than kLongColumn entries by the whole
 // wavefront).  acc[g] receives the sums.  The lists must be readable up to three entries past the span.
-template <class Index, class VecFn>
-__device__ __forceinline__ void segment_sums(const int64_t (&b)[kCscGroups], const int64_t (&e)[kCscGroups],
+template <int GROUPS, class Index, class VecFn>
+__device__ __forceinline__ void segment_sums(const int64_t (&b)[GROUPS], const int64_t (&e)[GROUPS],
                                              const Index *__restrict__ index, const float *__restrict__ value,
-                                             VecFn vec, float *tile, int lane, float (&acc)[kCscGroups]) {
-    const int64_t span_b = __shfl(b[0], 0, kWave), span_e = __shfl(e[kCscGroups - 1], kWave - 1, kWave);
+                                             VecFn vec, float *tile, int lane, float (&acc)[GROUPS]) {
+    const int64_t span_b = lane_value(b[0], 0), span_e = lane_value(e[GROUPS - 1], kWave - 1);
     const int64_t origin = span_b & ~(int64_t)3;               // tiles are aligned to four entries
     // segment bounds and tile positions relative to the origin (a span has fewer than 2^31 entries)
-    int32_t rb[kCscGroups], re[kCscGroups];
+    int32_t rb[GROUPS], re[GROUPS];
 #pragma unroll
-    for (int g = 0; g < kCscGroups; ++g) {
+    for (int g = 0; g < GROUPS; ++g) {
         acc[g] = 0.f;
         rb[g] = (int32_t)(b[g] - origin);
         re[g] = (int32_t)(e[g] - origin);
     }
     const int32_t end = (int32_t)(span_e - origin);
     constexpr int kLoads = kTile / (4 * kWave);                // 4
-    const int64_t last4 = (span_e - 1) & ~(int64_t)3;          // last aligned quad that holds an entry of the span
+    const Index *const index0 = index + origin;                // scalar bases, 32-bit offsets per lane
+    const float *const value0 = value + origin;
+    const int32_t last4 = (end - 1) & ~3;                      // last aligned quad that holds an entry of the span
     typedef float v4f __attribute__((ext_vector_type(4)));
     typedef Index v4r __attribute__((ext_vector_type(4)));
     // the loads of a tile: addresses past the span are clamped (they re-read its last quad), so none sits behind
@@ -265,10 +276,10 @@ __device__ __forceinline__ void segment_sums(const int64_t (&b)[kCscGroups], con
     auto load_tile = [&](int32_t t0, v4r (&r)[kLoads], v4f (&v)[kLoads]) {
 #pragma unroll
         for (int u = 0; u < kLoads; ++u) {
-            int64_t at = origin + t0 + u * (4 * kWave) + 4 * lane;
-            at = at < last4 ? at : last4;
-            r[u] = __builtin_nontemporal_load(reinterpret_cast<const v4r *>(index + at));
-            v[u] = __builtin_nontemporal_load(reinterpret_cast<const v4f *>(value + at));
+            const int32_t want = t0 + u * (4 * kWave) + 4 * lane;
+            const uint32_t at = (uint32_t)(want < last4 ? want : last4);
+            r[u] = __builtin_nontemporal_load(reinterpret_cast<const v4r *>(index0 + at));
+            v[u] = __builtin_nontemporal_load(reinterpret_cast<const v4f *>(value0 + at));
         }
     };
     v4r r[kLoads], r_next[kLoads];
@@ -290,7 +301,7 @@ __device__ __forceinline__ void segment_sums(const int64_t (&b)[kCscGroups], con
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         const int32_t t1 = t0 + kTile < end ? t0 + kTile : end;
 #pragma unroll
-        for (int g = 0; g < kCscGroups; ++g) {
+        for (int g = 0; g < GROUPS; ++g) {
             const int32_t lo = (rb[g] > t0 ? rb[g] : t0) - t0, hi = (re[g] < t1 ? re[g] : t1) - t0;   // tile coordinates
             if (__ballot(lo < hi) == 0) continue;              // the group has nothing in this tile (uniform)
             const bool is_long = hi - lo > kLongColumn;
@@ -323,7 +334,8 @@ __device__ __forceinline__ void segment_sums(const int64_t (&b)[kCscGroups], con
 }
 
 // ---- pass 1: partial dot products from the range-major copy.  Dynamic LDS: Wc floats (the range of x).
-// Grid (R * row chunks, n); a workgroup takes kCscCols rows of one (range, worker), a wavefront 256 of them.
+// Grid (R * row chunks, n); a workgroup takes group_segments rows of one (range, worker).
+template <int GROUPS>
 __global__ __launch_bounds__(kCscThreads) void csrr_dot_kernel(const int64_t *__restrict__ bstart,
                                                                const int32_t *__restrict__ rptr,
                                                                const uint16_t *__restrict__ rcol,
@@ -335,26 +347,26 @@ __global__ __launch_bounds__(kCscThreads) void csrr_dot_kernel(const int64_t *__
     __shared__ __attribute__((aligned(16))) float tiles[kCscWaves][kTile];
     const int range = blockIdx.x % R;
     const int64_t chunk = blockIdx.x / R, worker = blockIdx.y, n = gridDim.y, rows = n * m;
-    const int wave = threadIdx.x / kWave, lane = lane_id();
+    const int wave = wave_id(), lane = lane_id();
     const int64_t c0 = (int64_t)range * Wc;
     const int64_t width = c0 + Wc < d ? Wc : d - c0;
     for (int64_t j = threadIdx.x; j < width; j += kCscThreads) x_lds[j] = x[worker * x_stride + c0 + j];
     __syncthreads();
-    const int64_t l_first = (chunk * kCscWaves + wave) * (kCscGroups * kWave);
+    const int64_t l_first = (chunk * kCscWaves + wave) * (GROUPS * kWave);
     if (l_first >= m) return;                                   // the whole wavefront; no barrier follows
     const int64_t base = bstart[(int64_t)range * n + worker];
     const int32_t *rp = rptr + ((int64_t)range * n + worker) * (m + 1);
-    int64_t b[kCscGroups], e[kCscGroups];
+    int64_t b[GROUPS], e[GROUPS];
 #pragma unroll
-    for (int g = 0; g < kCscGroups; ++g) {
+    for (int g = 0; g < GROUPS; ++g) {
         const int64_t l = l_first + g * kWave + lane;
         b[g] = base + rp[l < m ? l : m];                       // rows past m: an empty range at the end
         e[g] = base + rp[l < m ? l + 1 : m];
     }
-    float acc[kCscGroups];
-    segment_sums(b, e, rcol, rval, [&](uint16_t c) { return x_lds[c]; }, tiles[wave], lane, acc);
+    float acc[GROUPS];
+    segment_sums<GROUPS>(b, e, rcol, rval, [&](uint16_t c) { return x_lds[c]; }, tiles[wave], lane, acc);
 #pragma unroll
-    for (int g = 0; g < kCscGroups; ++g) {
+    for (int g = 0; g < GROUPS; ++g) {
         const int64_t l = l_first + g * kWave + lane;
         if (l < m) zpart[(int64_t)range * rows + worker * m + l] = acc[g];
     }
@@ -480,8 +492,8 @@ __global__ __launch_bounds__(kThreads) void csr_coef_kernel(const float *__restr
 }
 
 // ---- pass 2: gradient columns from the column-major copy.  Dynamic LDS: m floats if COEF_LDS.
-// A workgroup takes kCscCols columns of one worker, a wavefront 256 of them; vec = the worker's coef.
-template <bool COEF_LDS, class RowIndex>
+// A workgroup takes group_segments columns of one worker; vec = the worker's coef.
+template <int GROUPS, bool COEF_LDS, class RowIndex>
 __global__ __launch_bounds__(kCscThreads) void csc_grad_kernel(const int32_t *__restrict__ colptr,
                                                                const RowIndex *__restrict__ csc_row,
                                                                const float *__restrict__ csc_val,
@@ -492,28 +504,28 @@ __global__ __launch_bounds__(kCscThreads) void csc_grad_kernel(const int32_t *__
     extern __shared__ float coef_lds[];
     __shared__ __attribute__((aligned(16))) float tiles[kCscWaves][kTile];
     const int64_t worker = blockIdx.y;
-    const int wave = threadIdx.x / kWave, lane = lane_id();
+    const int wave = wave_id(), lane = lane_id();
     const float *cf = coef + worker * m;
     if constexpr (COEF_LDS) {
         for (int64_t l = threadIdx.x; l < m; l += kCscThreads) coef_lds[l] = cf[l];
         __syncthreads();
     }
-    const int64_t cb = ((int64_t)blockIdx.x * kCscWaves + wave) * (kCscGroups * kWave);
+    const int64_t cb = ((int64_t)blockIdx.x * kCscWaves + wave) * (GROUPS * kWave);
     if (cb >= d) return;                                        // the whole wavefront; no barrier follows
     const int64_t first = rowptr[worker * m];
     const int32_t *cp = colptr + worker * (d + 1);
-    int64_t b[kCscGroups], e[kCscGroups];                      // global entry ranges of this lane's columns
+    int64_t b[GROUPS], e[GROUPS];                      // global entry ranges of this lane's columns
 #pragma unroll
-    for (int g = 0; g < kCscGroups; ++g) {
+    for (int g = 0; g < GROUPS; ++g) {
         const int64_t c = cb + g * kWave + lane;
         b[g] = first + cp[c < d ? c : d];                      // columns past d: an empty range at the end
         e[g] = first + cp[c < d ? c + 1 : d];
     }
-    float acc[kCscGroups];
-    segment_sums(b, e, csc_row, csc_val, [&](RowIndex r) { return COEF_LDS ? coef_lds[r] : cf[r]; }, tiles[wave],
+    float acc[GROUPS];
+    segment_sums<GROUPS>(b, e, csc_row, csc_val, [&](RowIndex r) { return COEF_LDS ? coef_lds[r] : cf[r]; }, tiles[wave],
                     lane, acc);
 #pragma unroll
-    for (int g = 0; g < kCscGroups; ++g) {
+    for (int g = 0; g < GROUPS; ++g) {
         const int64_t c = cb + g * kWave + lane;
         if (c < d) grad[worker * d + c] = acc[g] + regulariser_grad(x[worker * x_stride + c], lambda);
     }
@@ -569,6 +581,41 @@ unsigned row_blocks(int64_t rows) {
     int64_t blocks = (rows + kWaves - 1) / kWaves;
     if (blocks > 16384) blocks = 16384;
     return (unsigned)blocks;
+}
+
+// Segments per list, lists (one per worker, or per worker and column range).  Four groups per wavefront are the faster
+// ones wherever they give most compute units a workgroup (500 workgroups in pass 1, 100 workers, 10^8 entries: 243 us
+// the gradient against 253 with one; 255 and 294, n = 3, m = 9000, d = 200000: 48.5 against 55); where they do not, one
+// group per wavefront (50 and 50, n = 10, m = 10000, d = 10000, 2 10^7 entries: 379 us with four, 112 with one; 50 and
+// 100, n = 50, m = 2000, d = 3000: 102 against 44).
+int csr_groups(int64_t segments, int64_t lists) {
+    const int64_t per = group_segments(kManyGroups);
+    return (segments + per - 1) / per * lists >= 192 ? kManyGroups : kFewGroups;
+}
+
+template <int GROUPS>
+void launch_dot(const IndexLayout &ix, const float *x, int32_t n, int64_t m, int64_t d, int64_t x_stride,
+                hipStream_t stream) {
+    const int64_t chunks = (m + group_segments(GROUPS) - 1) / group_segments(GROUPS);
+    hipLaunchKernelGGL(csrr_dot_kernel<GROUPS>, dim3((unsigned)(ix.R * chunks), (unsigned)n), dim3(kCscThreads),
+                       sizeof(float) * (size_t)ix.Wc, stream, ix.bstart, ix.rptr, ix.rcol, ix.rval, x, ix.zpart, m, d, ix.R,
+                       ix.Wc, x_stride);
+}
+
+template <int GROUPS>
+void launch_columns(const IndexLayout &ix, const int64_t *rowptr, const float *x, float *grad, int32_t n, int64_t m,
+                    int64_t d, float lambda, int64_t x_stride, hipStream_t stream) {
+    const dim3 grid((unsigned)((d + group_segments(GROUPS) - 1) / group_segments(GROUPS)), (unsigned)n), block(kCscThreads);
+    static_assert(kCoefLdsRows <= kIdx16Rows, "a coefficient vector that fits LDS has 16-bit row indices");
+    if (m <= kCoefLdsRows)
+        hipLaunchKernelGGL((csc_grad_kernel<GROUPS, true, uint16_t>), grid, block, sizeof(float) * (size_t)m, stream,
+                           ix.colptr, (const uint16_t *)ix.csc_row, ix.csc_val, rowptr, ix.coef, x, grad, m, d, lambda, x_stride);
+    else if (m <= kIdx16Rows)
+        hipLaunchKernelGGL((csc_grad_kernel<GROUPS, false, uint16_t>), grid, block, 0, stream, ix.colptr,
+                           (const uint16_t *)ix.csc_row, ix.csc_val, rowptr, ix.coef, x, grad, m, d, lambda, x_stride);
+    else
+        hipLaunchKernelGGL((csc_grad_kernel<GROUPS, false, int32_t>), grid, block, 0, stream, ix.colptr,
+                           (const int32_t *)ix.csc_row, ix.csc_val, rowptr, ix.coef, x, grad, m, d, lambda, x_stride);
 }
 
 }  // namespace
@@ -633,33 +680,32 @@ hipError_t launch_logreg_grad_csr(const int64_t *rowptr, const int32_t *col, con
         index_layout(n, m, d, nnz, (char *)const_cast<void *>(index), &ix);
         static PerDeviceOnce configured;
         const hipError_t cfg = configured([] {
-            hipError_t st = hipFuncSetAttribute(reinterpret_cast<const void *>(&csrr_dot_kernel),
-                                                hipFuncAttributeMaxDynamicSharedMemorySize, sizeof(float) * kRangeCols);
-            if (st == hipSuccess)
-                st = hipFuncSetAttribute(reinterpret_cast<const void *>(&csc_grad_kernel<true, uint16_t>),
-                                         hipFuncAttributeMaxDynamicSharedMemorySize, sizeof(float) * kCoefLdsRows);
+            const void *dots[] = {reinterpret_cast<const void *>(&csrr_dot_kernel<kManyGroups>),
+                                  reinterpret_cast<const void *>(&csrr_dot_kernel<kFewGroups>)};
+            const void *grads[] = {reinterpret_cast<const void *>(&csc_grad_kernel<kManyGroups, true, uint16_t>),
+                                   reinterpret_cast<const void *>(&csc_grad_kernel<kFewGroups, true, uint16_t>)};
+            hipError_t st = hipSuccess;
+            for (const void *f : dots)
+                if (st == hipSuccess)
+                    st = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, sizeof(float) * kRangeCols);
+            for (const void *f : grads)
+                if (st == hipSuccess)
+                    st = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, sizeof(float) * kCoefLdsRows);
             return st;
         });
         if (cfg != hipSuccess) return cfg;
-        const int64_t row_chunks = (m + kCscCols - 1) / kCscCols;
-        hipLaunchKernelGGL(csrr_dot_kernel, dim3((unsigned)(ix.R * row_chunks), (unsigned)n), dim3(kCscThreads),
-                           sizeof(float) * (size_t)ix.Wc, stream, ix.bstart, ix.rptr, ix.rcol, ix.rval, x, ix.zpart, m, d,
-                           ix.R, ix.Wc, x_stride);
+        if (csr_groups(m, (int64_t)n * ix.R) == kManyGroups)
+            launch_dot<kManyGroups>(ix, x, n, m, d, x_stride, stream);
+        else
+            launch_dot<kFewGroups>(ix, x, n, m, d, x_stride, stream);
         mk(K_GRAD_MAIN);
         hipLaunchKernelGGL(csr_coef_kernel, dim3((unsigned)((rows + kThreads - 1) / kThreads)), dim3(kThreads), 0,
                            stream, y, ix.zpart, ix.R, rows, 1.0f / (float)m, ix.coef, loss);
         mk(K_GRAD_AUX);
-        const dim3 grid((unsigned)((d + kCscCols - 1) / kCscCols), (unsigned)n);
-        static_assert(kCoefLdsRows <= kIdx16Rows, "a coefficient vector that fits LDS has 16-bit row indices");
-        if (m <= kCoefLdsRows)
-            hipLaunchKernelGGL((csc_grad_kernel<true, uint16_t>), grid, dim3(kCscThreads), sizeof(float) * (size_t)m, stream,
-                               ix.colptr, (const uint16_t *)ix.csc_row, ix.csc_val, rowptr, ix.coef, x, grad, m, d, lambda, x_stride);
-        else if (m <= kIdx16Rows)
-            hipLaunchKernelGGL((csc_grad_kernel<false, uint16_t>), grid, dim3(kCscThreads), 0, stream, ix.colptr,
-                               (const uint16_t *)ix.csc_row, ix.csc_val, rowptr, ix.coef, x, grad, m, d, lambda, x_stride);
+        if (csr_groups(d, n) == kManyGroups)
+            launch_columns<kManyGroups>(ix, rowptr, x, grad, n, m, d, lambda, x_stride, stream);
         else
-            hipLaunchKernelGGL((csc_grad_kernel<false, int32_t>), grid, dim3(kCscThreads), 0, stream, ix.colptr,
-                               (const int32_t *)ix.csc_row, ix.csc_val, rowptr, ix.coef, x, grad, m, d, lambda, x_stride);
+            launch_columns<kFewGroups>(ix, rowptr, x, grad, n, m, d, lambda, x_stride, stream);
         mk(K_GRAD_MAIN);
         return hipGetLastError();
     }
