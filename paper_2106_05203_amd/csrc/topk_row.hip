@@ -17,18 +17,28 @@ __global__ __launch_bounds__(kRowThreads) void topk_row_kernel(TopkArgs p) {
     row_topk<DIFF, UPDATE>(s, p, blockIdx.x);
 }
 
-template <bool DIFF, int UPDATE>
+template <int CACHE, bool DIFF, int UPDATE>
 __global__ __launch_bounds__(kRowThreads) void topk_row_cached_kernel(TopkArgs p) {
     __shared__ RowShared s;
-    __shared__ float cache[kRowCache];
+    __shared__ float cache[CACHE];
     row_topk_cached<DIFF, UPDATE>(s, cache, p, blockIdx.x);
 }
 
 template <int UPDATE>
 __global__ __launch_bounds__(kRowThreads) void topk_row_parts_kernel(TopkArgs p) {
     __shared__ RowShared s;
-    __shared__ float cache[kRowCache];
+    __shared__ float cache[kRowCacheShort];
     row_topk_parts<UPDATE>(s, cache, p, blockIdx.x);
+}
+
+template <int CACHE>
+void launch_cached(const TopkArgs &p, hipStream_t stream) {
+    const dim3 grid((unsigned)p.n), block(kRowThreads);
+    const bool diff = p.b != nullptr, upd = p.g_i != nullptr;
+    if (upd && diff) hipLaunchKernelGGL((topk_row_cached_kernel<CACHE, true, kAddUpdate>), grid, block, 0, stream, p);
+    else if (upd) hipLaunchKernelGGL((topk_row_cached_kernel<CACHE, false, kClearUpdate>), grid, block, 0, stream, p);
+    else if (diff) hipLaunchKernelGGL((topk_row_cached_kernel<CACHE, true, kNoUpdate>), grid, block, 0, stream, p);
+    else hipLaunchKernelGGL((topk_row_cached_kernel<CACHE, false, kNoUpdate>), grid, block, 0, stream, p);
 }
 
 }  // namespace
@@ -38,16 +48,15 @@ hipError_t launch_topk_row(const TopkArgs &p, hipStream_t stream) {
     const bool diff = p.b != nullptr, upd = p.g_i != nullptr;
     if (upd && p.g_i != (diff ? p.b : p.a)) return hipErrorInvalidValue;
     if (p.parts.part) {
-        if (!diff || p.d > kRowCache) return hipErrorInvalidValue;
+        if (!diff || p.d > kRowCacheShort) return hipErrorInvalidValue;
         if (upd) hipLaunchKernelGGL((topk_row_parts_kernel<kAddUpdate>), grid, block, 0, stream, p);
         else hipLaunchKernelGGL((topk_row_parts_kernel<kNoUpdate>), grid, block, 0, stream, p);
         return hipGetLastError();
     }
-    if (p.d <= kRowCache) {
-        if (upd && diff) hipLaunchKernelGGL((topk_row_cached_kernel<true, kAddUpdate>), grid, block, 0, stream, p);
-        else if (upd) hipLaunchKernelGGL((topk_row_cached_kernel<false, kClearUpdate>), grid, block, 0, stream, p);
-        else if (diff) hipLaunchKernelGGL((topk_row_cached_kernel<true, kNoUpdate>), grid, block, 0, stream, p);
-        else hipLaunchKernelGGL((topk_row_cached_kernel<false, kNoUpdate>), grid, block, 0, stream, p);
+    if (p.d <= kRowCacheShort) {
+        launch_cached<kRowCacheShort>(p, stream);
+    } else if (p.d <= kRowCache) {
+        launch_cached<kRowCache>(p, stream);
     } else {
         if (upd && diff) hipLaunchKernelGGL((topk_row_kernel<true, kAddUpdate>), grid, block, 0, stream, p);
         else if (upd) hipLaunchKernelGGL((topk_row_kernel<false, kClearUpdate>), grid, block, 0, stream, p);

@@ -238,15 +238,28 @@ __device__ void row_topk(RowShared &s, const TopkArgs &p, int64_t row) {
         s, p, row, [=](int64_t e) { return load_v<DIFF>(a, b, e); }, [=](int64_t e) { return DIFF ? b[e] : 0.f; });
 }
 
-// Rows of at most kRowCache entries: the row is formed once into LDS (`cache`), all passes read it there.
-constexpr int kRowCache = (int)kRowPartsMax;
+// Rows of at most kRowCache entries: the row is formed once into LDS (`cache`), all passes read it there.  (Rows from
+// 8193 entries on used to be read from L2 in every pass: ef21_topk of 20 rows of 12000, k = 1000, 15.9 us a call,
+// 14.7 so; 100 rows of 16383 17.6 and 15.7.)
+constexpr int kRowCache = 16384, kRowCacheShort = (int)kRowPartsMax;
 
 template <bool DIFF, int UPDATE>
 __device__ void row_topk_cached(RowShared &s, float *cache, const TopkArgs &p, int64_t row) {
     const int64_t d = p.d;
     const float *a = p.a + row * d;
     const float *b = DIFF ? p.b + row * d : nullptr;
-    for (int64_t e = threadIdx.x; e < d; e += kRowThreads) cache[e] = load_v<DIFF>(a, b, e);
+    constexpr int kInFlight = 8;
+    for (int64_t e0 = threadIdx.x; e0 < d; e0 += kInFlight * kRowThreads) {
+        float v[kInFlight];
+#pragma unroll
+        for (int u = 0; u < kInFlight; ++u) {         // past the end: the last entry, not kept
+            const int64_t e = e0 + u * kRowThreads;
+            v[u] = load_v<DIFF>(a, b, e < d ? e : d - 1);
+        }
+#pragma unroll
+        for (int u = 0; u < kInFlight; ++u)
+            if (e0 + u * kRowThreads < d) cache[e0 + u * kRowThreads] = v[u];
+    }
     __syncthreads();
     row_topk_on<UPDATE>(
         s, p, row, [=](int64_t e) { return cache[e]; }, [=](int64_t e) { return DIFF ? b[e] : 0.f; });
