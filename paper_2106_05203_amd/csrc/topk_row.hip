@@ -11,12 +11,6 @@
 namespace ef21 {
 namespace {
 
-template <bool DIFF, int UPDATE>
-__global__ __launch_bounds__(kRowThreads) void topk_row_kernel(TopkArgs p) {
-    __shared__ RowShared s;
-    row_topk<DIFF, UPDATE>(s, p, blockIdx.x);
-}
-
 template <int CACHE, bool DIFF, int UPDATE>
 __global__ __launch_bounds__(kRowThreads) void topk_row_cached_kernel(TopkArgs p) {
     __shared__ RowShared s;
@@ -58,10 +52,7 @@ hipError_t launch_topk_row(const TopkArgs &p, hipStream_t stream) {
     } else if (p.d <= kRowCache) {
         launch_cached<kRowCache>(p, stream);
     } else {
-        if (upd && diff) hipLaunchKernelGGL((topk_row_kernel<true, kAddUpdate>), grid, block, 0, stream, p);
-        else if (upd) hipLaunchKernelGGL((topk_row_kernel<false, kClearUpdate>), grid, block, 0, stream, p);
-        else if (diff) hipLaunchKernelGGL((topk_row_kernel<true, kNoUpdate>), grid, block, 0, stream, p);
-        else hipLaunchKernelGGL((topk_row_kernel<false, kNoUpdate>), grid, block, 0, stream, p);
+        return hipErrorInvalidValue;                  // longer rows: launch_topk_row16, launch_topk_split
     }
     return hipGetLastError();
 }

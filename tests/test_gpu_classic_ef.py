@@ -125,3 +125,35 @@ def test_flag_combinations_are_rejected(gpu):
         for flags in (binding.CLASSIC_EF | binding.PLUS, binding.CLASSIC_EF | binding.ORDER_STEP_FIRST, 16):
             with pytest.raises(binding.EF21Error):
                 h.step(to_gpu(torch, np.zeros((2, 10))), flags)
+
+
+# the errors are cleared by whatever kernel emits the message: the row kernel with its two LDS copies, rows kept as key
+# prefixes, the many-workgroup path with rows of odd length, Top-1 on long rows; n >= 16: the other aggregation pass;
+# n k of 128 and 136 with d at the 1024 columns of the small one
+@pytest.mark.parametrize("n,d,k", [(3, 9001, 90), (2, 16383, 33), (3, 20001, 200), (3, 20001, 1500), (3, 20001, 1),
+                                   (17, 16999, 170), (2, 65_537, 2000), (16, 1024, 8), (17, 1024, 8), (16, 1025, 8)])
+def test_errors_are_cleared_by_every_emission(gpu, oracle, n, d, k):
+    torch, binding = gpu
+    print(f"EF clearing case n={n} d={d} k={k}", flush=True)
+    rng = np.random.default_rng(d + k)
+    gamma = float(np.float32(0.3))
+    e0 = (0.2 * rng.standard_normal((n, d))).astype(np.float32)
+    st = oracle.EFState(np.zeros(d), e0.astype(np.float64))
+    with binding.EF21(n, d, k, gamma) as h:
+        h.set_state(to_gpu(torch, np.zeros(d)), to_gpu(torch, e0), to_gpu(torch, np.full(d, 7.0)))
+        for t in range(4):                                   # the last two: a threshold that jumps, then all equal
+            grads = (rng.standard_normal((n, d)) * (1.0, 1.0, 200.0, 1.0)[t]).astype(np.float32)
+            if t == 3:
+                grads = ((np.where(rng.random((n, d)) < 0.5, 1.0, -1.0) - st.e) / gamma).astype(np.float32)
+            oracle.ef_iteration(st, grads.astype(np.float64), k, gamma)
+            pad = torch.empty(n * d + 1, device="cuda")      # gradients at an odd 4-byte address
+            pad[1:].copy_(to_gpu(torch, grads).view(-1))
+            h.step(pad[1:].view(n, d), binding.CLASSIC_EF)
+            x, e, mean_w = (a.cpu().numpy() for a in h.get_state())
+            idx, val = (a.cpu().numpy() for a in h.get_messages())
+            assert np.array_equal(idx, st.msg_idx) and same_bits(val, st.msg_val.astype(np.float32)), f"round {t}: message"
+            assert same_bits(e, st.e.astype(np.float32)), f"round {t}: errors"
+            w = np.zeros((n, d))
+            np.put_along_axis(w, st.msg_idx.astype(np.int64), st.msg_val, axis=1)
+            # n fp32 additions and one rounding of 1/n, relative to the sum of the magnitudes
+            assert np.all(np.abs(mean_w - w.mean(axis=0)) <= (n + 2) * 2.0 ** -24 * np.abs(w).mean(axis=0)), f"round {t}: mean"

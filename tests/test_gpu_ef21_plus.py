@@ -172,3 +172,36 @@ def test_errors(gpu):
             h.step(to_gpu(torch, np.zeros((2, 10))), 16)      # unknown flag
         with pytest.raises(binding.EF21Error):
             h.step(None, binding.PLUS)            # no problem attached
+
+
+# long rows: one partial block of coordinates, whole blocks only, more than a wavefront's worth of workers, runs longer
+# than a wavefront, and thresholds that jump so that each of the two selections fails its guess (and goes through its
+# second pass, or, in the all-equal row, the crowded bin)
+@pytest.mark.parametrize("n,d,k", [(3, 16_384, 164), (2, 16_385, 9_000), (66, 16_901, 40), (4, 1_000_003, 2_000),
+                                   (3, 200_007, 30_000)])
+def test_long_rows_whose_thresholds_jump(gpu, oracle, n, d, k):
+    torch, binding = gpu
+    print(f"EF21+ jumping case n={n} d={d} k={k}", flush=True)
+    rng = np.random.default_rng(d + k)
+    gamma = 0.25
+    x0 = rng.standard_normal(d).astype(np.float32)
+    g_i0 = rng.standard_normal((n, d)).astype(np.float32)
+    g_i0[:, 1] = -0.0                                        # a negative zero that nothing touches stays one
+    g0 = g_i0.astype(np.float64).mean(axis=0).astype(np.float32)
+    st = oracle.EF21State(x0.astype(np.float64), g_i0.astype(np.float64), g0.astype(np.float64))
+    # up by 30: beyond the histograms' windows of at most two octaves; not more, because M leaves out the square of one
+    # fp32 rounding per kept entry, k (2^-24 |g_ij|)^2, which must stay below 1e-9 of M, some d
+    scales = [(1.0, 0.1), (1.0, 0.1), (30.0, 0.1), (1.0, 30.0), (1.0, 1.0)]
+    with binding.EF21(n, d, k, gamma) as h:
+        h.set_state(to_gpu(torch, x0), to_gpu(torch, g_i0), to_gpu(torch, g0))
+        for t, (plain, markov) in enumerate(scales):
+            grads = np.empty((n, d), np.float32)
+            grads[0::2] = st.g_i[0::2] + markov * rng.standard_normal(grads[0::2].shape)
+            grads[1::2] = plain * rng.standard_normal(grads[1::2].shape)
+            if t == 4:
+                grads[0] = np.where(rng.random(d) < 0.5, 0.5, -0.5)
+            x_before = st.x.copy()
+            choice = oracle.iteration_plus(st, grads.astype(np.float64), k, gamma, order="grad_first")
+            h.step(to_gpu(torch, grads), binding.PLUS)
+            compare_plus_step(torch, h, st, choice, x_before, gamma, f"step {t}")
+            h.set_state(to_gpu(torch, st.x), to_gpu(torch, st.g_i), to_gpu(torch, st.g))

@@ -268,3 +268,73 @@ def test_config3_full_size_gradient(gpu, oracle):
         assert np.median(bound) <= 2e-5 * np.max(np.abs(ref[i]))
     rel = np.linalg.norm(got - ref, axis=1) / np.linalg.norm(ref, axis=1)
     assert rel.max() <= 1e-6, f"relative error of the gradients in the 2-norm: {rel.max():.3e}"
+
+
+# groups of 16, 32 and 64 lanes per row at their ends, rows of 1 to 5 columns, with 32 entries per lane in flight and
+# (problems of more than 2^24 entries) with 64; A at an odd 4-byte address, a minibatch with an entry out of range
+@pytest.mark.parametrize("n,d,m", [(2, 1, 9), (3, 2, 70), (2, 3, 33), (2, 4, 65), (3, 5, 40), (2, 63, 129), (2, 64, 31),
+                                   (3, 65, 64), (2, 127, 200), (2, 129, 17), (2, 257, 90), (40, 515, 30), (2, 1023, 70),
+                                   (1, 1026, 19), (2, 2048, 12), (2, 61, 140_000), (2, 126, 70_000), (2, 251, 34_000),
+                                   (2, 509, 17_000), (2, 1021, 8_500)])
+def test_dense_gradient_short_rows(gpu, oracle, n, d, m):
+    torch, binding = gpu
+    print(f"short dense grad case n={n} d={d} m={m}", flush=True)
+    rng = np.random.default_rng(d + m)
+    A = rng.standard_normal((n, m, d), dtype=np.float32) / np.float32(np.sqrt(d))
+    y = np.where(rng.random((n, m)) < 0.5, 1.0, -1.0).astype(np.float32)
+    x = rng.standard_normal(d).astype(np.float32)
+    x64 = x.astype(np.float64)
+
+    def grads_of(rows):
+        out = []
+        for i in range(n):
+            Ai = A[i, rows].astype(np.float64)
+            r = -y[i, rows] / (1.0 + np.exp(y[i, rows] * (Ai @ x64)))
+            out.append(Ai.T @ r / rows.size + 0.2 * x64 / (1.0 + x64 * x64) ** 2)
+        return np.stack(out)
+
+    with binding.EF21(n, d, 1, 0.1) as h:
+        pad = torch.empty(A.size + 1, device="cuda")
+        Ag = pad[1:].view(n, m, d)
+        Ag.copy_(torch.from_numpy(A))
+        h.set_problem_dense(Ag, to_gpu(torch, y), 0.1)
+        got = h.local_grad(to_gpu(torch, x))
+        assert torch.equal(got, h.local_grad(to_gpu(torch, x)))
+        ref = grads_of(np.arange(m))
+        # additions behind a sum over rows: a group's trips and the two to eight levels that join the blocks
+        depth = d / 64 + 8
+        for i in range(n):
+            bound = 1e-5 * np.abs(ref[i]) + gradient_rounding_floor(A[i], y[i], x, depth, 16)
+            assert np.all(np.abs(got.cpu().numpy()[i] - ref[i]) <= bound)
+        if d <= 8192 and m < 10_000:                           # the same sums finished by the Top-k kernel
+            h.set_state(x=to_gpu(torch, x), g_i=torch.zeros((n, d), device="cuda"))
+            h.step()
+            idx, val = h.get_messages()
+            assert torch.equal(val, got.gather(1, idx.long()))
+        tau = max(1, m // 3)
+        batch = torch.from_numpy(np.stack([rng.permutation(m)[:tau] for _ in range(n)]).astype(np.int32)).cuda()
+        batch[:] = batch[0]
+        h.set_minibatch(batch)
+        ref = grads_of(batch[0].cpu().numpy())
+        got = h.local_grad(to_gpu(torch, x)).cpu().numpy()
+        rows = batch[0].cpu().numpy()
+        for i in range(n):
+            bound = 1e-5 * np.abs(ref[i]) + gradient_rounding_floor(A[i][rows], y[i][rows], x, depth, 16)
+            assert np.all(np.abs(got[i] - ref[i]) <= bound)
+        batch[:, 0] = -1
+        assert torch.isfinite(h.local_grad(to_gpu(torch, x))).all()
+
+
+# one segment group per wavefront and four (192 workgroups and more), rows and columns past the last group
+@pytest.mark.parametrize("n,d,m,nnz", [(191, 70, 66, 3), (192, 70, 66, 3), (192, 2049, 65, 4), (2, 600, 2050, 7)])
+def test_csr_gradient_groups(gpu, oracle, n, d, m, nnz):
+    torch, binding = gpu
+    print(f"csr groups case n={n} d={d} m={m} nnz/row={nnz}", flush=True)
+    W = workloads.logreg_csr(n, d, m, nnz, seed=d + n)
+    x = np.random.default_rng(5).standard_normal(d).astype(np.float32)
+    P = oracle.LogRegCSR(W.rowptr, W.col, W.val, W.y, n, m, d, 0.1)
+    with binding.EF21(n, d, 1, 0.1) as h:
+        h.set_problem_csr(to_gpu(torch, W.rowptr, np.int64), to_gpu(torch, W.col, np.int32), to_gpu(torch, W.val),
+                          to_gpu(torch, W.y), m, 0.1)
+        got = h.local_grad(to_gpu(torch, x))
+        assert_grads_close(got.cpu().numpy(), P.grads(x.astype(np.float64)), densify(W), W.y, x, nnz / 64 + 8, 32, "groups")

@@ -259,3 +259,31 @@ def test_crowded_threshold_bin_on_long_rows(gpu, oracle, kind):
             V[i, pos] = bits.view(np.float32) * np.where(rng.random(6000) < 0.5, 1.0, -1.0).astype(np.float32)
     for k in (3000, 5999, 6001):
         check(gpu, oracle, V, k)
+
+
+# rows at an odd 4-byte address and of lengths that leave one, two and three entries after the last whole load, on both
+# sides of every limit that chooses piece length (two million entries in all) and bin width (k = 4096, k = 131072 with
+# less than one entry in 200 kept, k = 400000), and the LDS copies of the row kernel (8192, 16384)
+@pytest.mark.parametrize("n,d,k", [(2, 8193, 82), (3, 16383, 1025), (3, 16386, 4096), (3, 16387, 4097), (2, 999_999, 4097),
+                                   (2, 1_000_001, 4096), (1, 1_000_003, 400_000), (1, 1_000_003, 400_001), (3, 70_002, 1),
+                                   (1, 2_000_517, 9_000), (1, 30_000_001, 131_073)])
+def test_rows_at_any_address(gpu, oracle, n, d, k):
+    torch, binding = gpu
+    print(f"unaligned topk case n={n} d={d} k={k}", flush=True)
+    rng = np.random.default_rng(d + k)
+    V = rng.standard_t(3, size=(n, d)).astype(np.float32) if d < 10_000_000 else rng.standard_normal((n, d), dtype=np.float32)
+    V[:, ::7] = np.round(V[:, ::7] * 8) / 8                                  # ties
+    pad = torch.empty(n * d + 1, device="cuda")
+    rows = pad[1:].view(n, d)
+    rows.copy_(torch.from_numpy(V))
+    idx, val = (t.cpu().numpy() for t in binding.ef21_topk(rows, k))
+    for i in range(n):
+        key = np.abs(V[i])
+        order = np.argsort(-key, kind="stable")[:k] if d < 10_000_000 else None
+        if order is None:                                                    # the same selection without a full sort
+            T = np.partition(key, d - k)[d - k]
+            above = np.nonzero(key > T)[0]
+            order = np.concatenate([above, np.nonzero(key == T)[0][:k - above.size]])
+        want = np.sort(order)
+        assert np.array_equal(idx[i], want), f"row {i}: positions differ"
+        assert same_bits(val[i], V[i][want])
