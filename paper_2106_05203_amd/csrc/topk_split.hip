@@ -712,12 +712,10 @@ __device__ void rescue_row(RowShared &rs, const TopkArgs &p, const Ws &w, int64_
     }
 }
 
-// A wavefront of the count and emit kernels takes kSPW consecutive slots (one, or two where one would put more
-// than a workgroup on every compute unit).  The first kPre steps of 64 candidates
-// of each (clamped to the slot's capacity, a multiple of 512) are loaded at the very start of the kernel, together
+// A wavefront of the count and emit kernels takes one slot.  The first kPre steps of 64 candidates (clamped to the
+// slot's capacity, a multiple of 512) are loaded at the very start of the kernel, together
 // with everything else whose address does not depend on the prologue, so that a workgroup waits for memory once,
-// not once per step of its prologue.
-constexpr int kPre = 4;
+// not once per step of its prologue.  See cand_steps for kPre.
 
 // Grid (slot blocks + 1, n).  Prologue of every workgroup: T's bin from the row's histogram, and whether the row
 // failed (see the head of the file).  The last workgroup of a row is the rescue: it selects a failed row by the
@@ -727,9 +725,9 @@ struct CountShared {
     RowShared rs;
     uint32_t wave[kCandWaves], out[4];
 };
-template <bool DIFF, int UPDATE, int kSPW, bool SUMS>
+template <bool DIFF, int UPDATE, int kPre, bool SUMS>
 __device__ __forceinline__ void count_rows(const TopkArgs &p, const Ws &w, CountShared &sh) {
-    constexpr int kWgSlots = kCandWaves * kSPW;      // slots per workgroup
+    constexpr int kSPW = 1, kWgSlots = kCandWaves;   // slots per wavefront and workgroup
     RowShared &rs = sh.rs;
     uint32_t (&lds_wave)[kCandWaves] = sh.wave, (&lds_out)[4] = sh.out;
     const int64_t row = blockIdx.y;
@@ -850,18 +848,18 @@ __device__ __forceinline__ void count_rows(const TopkArgs &p, const Ws &w, Count
     }
 }
 
-template <bool DIFF, int UPDATE, int kSPW>
+template <bool DIFF, int UPDATE, int kPre>
 __global__ __launch_bounds__(kCandThreads) void cand_count_kernel(TopkArgs p, Ws w) {
     __shared__ CountShared sh;
-    count_rows<DIFF, UPDATE, kSPW, false>(p, w, sh);
+    count_rows<DIFF, UPDATE, kPre, false>(p, w, sh);
 }
 
 // The two selections of Algorithm 3 in one launch: grid (.., n, 2).  (Likewise cand_emit_pair_kernel.)
-template <int kSPW>
+template <int kPre>
 __global__ __launch_bounds__(kCandThreads) void cand_count_pair_kernel(TopkArgs pp, Ws wp, TopkArgs pm, Ws wm) {
     __shared__ CountShared sh;
-    if (blockIdx.z == 0) count_rows<false, kNoUpdate, kSPW, true>(pp, wp, sh);
-    else count_rows<true, kNoUpdate, kSPW, true>(pm, wm, sh);
+    if (blockIdx.z == 0) count_rows<false, kNoUpdate, kPre, true>(pp, wp, sh);
+    else count_rows<true, kNoUpdate, kPre, true>(pm, wm, sh);
 }
 
 // Ordered emission by one wavefront that walks candidates in position order, 64 at a time: the running output
@@ -956,9 +954,9 @@ struct EmitShared {
     uint32_t tie_key[kTieCap], tie_idx[kTieCap];
     uint32_t T, q;
 };
-template <bool DIFF, int UPDATE, int kSPW, bool SUMS>
+template <bool DIFF, int UPDATE, int kPre, bool SUMS>
 __device__ __forceinline__ void emit_rows(const TopkArgs &p, const Ws &w, EmitShared &sh) {
-    constexpr int kWgSlots = kCandWaves * kSPW;      // slots per workgroup
+    constexpr int kSPW = 1, kWgSlots = kCandWaves;   // slots per wavefront and workgroup
     RowShared &rs = sh.rs;
     uint32_t (&before_above)[kCandWaves] = sh.before_above, (&own_above)[kCandWaves] = sh.own_above;
     uint32_t (&before_inbin)[kCandWaves] = sh.before_inbin, (&own_inbin)[kCandWaves] = sh.own_inbin;
@@ -1114,17 +1112,17 @@ __device__ __forceinline__ void emit_rows(const TopkArgs &p, const Ws &w, EmitSh
     em.finish(span_end < p.d ? span_end : p.d);
 }
 
-template <bool DIFF, int UPDATE, int kSPW>
+template <bool DIFF, int UPDATE, int kPre>
 __global__ __launch_bounds__(kCandThreads) void cand_emit_kernel(TopkArgs p, Ws w) {
     __shared__ EmitShared sh;
-    emit_rows<DIFF, UPDATE, kSPW, false>(p, w, sh);
+    emit_rows<DIFF, UPDATE, kPre, false>(p, w, sh);
 }
 
-template <int kSPW>
+template <int kPre>
 __global__ __launch_bounds__(kCandThreads) void cand_emit_pair_kernel(TopkArgs pp, Ws wp, TopkArgs pm, Ws wm) {
     __shared__ EmitShared sh;
-    if (blockIdx.z == 0) emit_rows<false, kNoUpdate, kSPW, true>(pp, wp, sh);
-    else emit_rows<true, kNoUpdate, kSPW, true>(pm, wm, sh);
+    if (blockIdx.z == 0) emit_rows<false, kNoUpdate, kPre, true>(pp, wp, sh);
+    else emit_rows<true, kNoUpdate, kPre, true>(pm, wm, sh);
 }
 
 __global__ __launch_bounds__(kCandThreads) void zero_words_kernel(uint32_t *p, size_t words) {
@@ -1276,12 +1274,19 @@ hipError_t launch_topk_split_reset(void *workspace, int32_t n, int64_t d, hipStr
 }
 
 namespace {
-int cand_slots_per_wave(int32_t n, const Ws &w) {
-    return (int64_t)n * ((w.nslot + kCandWaves - 1) / kCandWaves) > 256 ? 2 : 1;
+dim3 cand_grid(int32_t n, const Ws &w, unsigned selections) {
+    return dim3((unsigned)((w.nslot + kCandWaves - 1) / kCandWaves) + 1, (unsigned)n, selections);   // + 1: a row's rescue
 }
-dim3 cand_grid(int32_t n, const Ws &w, int spw, unsigned selections) {
-    const unsigned slot_blocks = (unsigned)((w.nslot + kCandWaves * spw - 1) / (kCandWaves * spw));
-    return dim3(slot_blocks + 1, (unsigned)n, selections);         // + 1: a row's rescue workgroup
+
+// Steps loaded ahead, from the candidates to be expected in a slot (1.3 k per row after a warm start, some 1.6 k from a
+// sample): enough for all of them where that is few, and no more, since every wavefront loads them.  Measured: ef21_topk
+// n = 10, d = 10^5, k = 5000 20.1 us with four, 19.2 with two; n = 20, d = 10^6, k = 1000 31.2 and 30.1; k = 10^4
+// 34.0 with two and four, 33.8 with three; step n = 8, d = 11.2 million, k = 112000 251.7 with four, 249.5 with six.
+int cand_steps(const TopkArgs &p, const Ws &w) {
+    const double expected = (p.warm > 0 ? 1.3 : 1.6) * (double)p.k * (double)w.L / (double)p.d;
+    if (expected <= 90.0) return 2;
+    if (expected <= 170.0) return 3;
+    return expected > 240.0 && expected <= 360.0 ? 6 : 4;
 }
 
 // After the first collect pass: the second pass (after a warm start), count and emit.
@@ -1291,12 +1296,14 @@ hipError_t launch_after_collect(const TopkArgs &p, const Ws &w, hipStream_t stre
         launch_collect(p, w, kSecondPass, stream);
         mk(K_TOPK_REFINE);
     }
-    const int spw = cand_slots_per_wave(p.n, w);
-    const dim3 cgrid = cand_grid(p.n, w, spw, 1), block(kCandThreads);
+    const int steps = cand_steps(p, w);
+    const dim3 cgrid = cand_grid(p.n, w, 1), block(kCandThreads);
 #define EF21_CAND(KERNEL, GRID, DIFF, UPD)                                                               \
     do {                                                                                                 \
-        if (spw == 2) hipLaunchKernelGGL((KERNEL<DIFF, UPD, 2>), GRID, block, 0, stream, p, w);          \
-        else hipLaunchKernelGGL((KERNEL<DIFF, UPD, 1>), GRID, block, 0, stream, p, w);                   \
+        if (steps == 2) hipLaunchKernelGGL((KERNEL<DIFF, UPD, 2>), GRID, block, 0, stream, p, w);        \
+        else if (steps == 3) hipLaunchKernelGGL((KERNEL<DIFF, UPD, 3>), GRID, block, 0, stream, p, w);   \
+        else if (steps == 4) hipLaunchKernelGGL((KERNEL<DIFF, UPD, 4>), GRID, block, 0, stream, p, w);   \
+        else hipLaunchKernelGGL((KERNEL<DIFF, UPD, 6>), GRID, block, 0, stream, p, w);                   \
     } while (0)
     if (upd && diff) EF21_CAND(cand_count_kernel, cgrid, true, kAddUpdate);
     else if (upd) EF21_CAND(cand_count_kernel, cgrid, false, kClearUpdate);
@@ -1368,13 +1375,18 @@ hipError_t launch_topk_split_pair(const TopkArgs &plain, const TopkArgs &markov,
                            markov, wm);
         mk(K_TOPK_REFINE);
     }
-    const int spw = cand_slots_per_wave(markov.n, wm);
-    const dim3 cgrid = cand_grid(markov.n, wm, spw, 2);
-    if (spw == 2) hipLaunchKernelGGL(cand_count_pair_kernel<2>, cgrid, block, 0, stream, plain, wp, markov, wm);
-    else hipLaunchKernelGGL(cand_count_pair_kernel<1>, cgrid, block, 0, stream, plain, wp, markov, wm);
+    const int steps = cand_steps(markov, wm);
+    const dim3 cgrid = cand_grid(markov.n, wm, 2);
+#define EF21_CAND(KERNEL)                                                                                \
+    do {                                                                                                 \
+        if (steps == 2) hipLaunchKernelGGL(KERNEL<2>, cgrid, block, 0, stream, plain, wp, markov, wm);   \
+        else if (steps == 3) hipLaunchKernelGGL(KERNEL<3>, cgrid, block, 0, stream, plain, wp, markov, wm); \
+        else hipLaunchKernelGGL(KERNEL<4>, cgrid, block, 0, stream, plain, wp, markov, wm);              \
+    } while (0)
+    EF21_CAND(cand_count_pair_kernel);
     mk(K_TOPK_COUNT);
-    if (spw == 2) hipLaunchKernelGGL(cand_emit_pair_kernel<2>, cgrid, block, 0, stream, plain, wp, markov, wm);
-    else hipLaunchKernelGGL(cand_emit_pair_kernel<1>, cgrid, block, 0, stream, plain, wp, markov, wm);
+    EF21_CAND(cand_emit_pair_kernel);
+#undef EF21_CAND
     mk(K_TOPK_EMIT);
     return hipGetLastError();
 }
