@@ -109,7 +109,8 @@ __global__ __launch_bounds__(kWideThreads) void logreg_dense_wide_kernel(const f
     int64_t chunk = (int64_t)blockIdx.x * kChunks;
     const int64_t l0 = chunk * rows_per_chunk;
     const int64_t l1 = l0 + kChunks * rows_per_chunk < m ? l0 + kChunks * rows_per_chunk : m;
-    // the loads of rows l .. l + R - 1; a row past the block reads the first 16 bytes of A (one cached line)
+    // the loads of rows l .. l + R - 1; a row past the block, or an entry of the batch that names no row, reads the first
+    // 16 bytes of A (one cached line) and is cleared before it is used
     auto load = [&](int64_t l, float4 (&v)[R][NQ], float (&yl)[R], bool (&live)[R]) {
 #pragma unroll
         for (int r = 0; r < R; ++r) {
@@ -137,6 +138,10 @@ __global__ __launch_bounds__(kWideThreads) void logreg_dense_wide_kernel(const f
         load(l + R, next, y_next, live_next);
 #pragma unroll
         for (int r = 0; r < R; ++r) {
+            if (!live[r]) {                                    // uniform; an infinity there times a zero coefficient is NaN
+#pragma unroll
+                for (int q = 0; q < NQ; ++q) av[r][q] = make_float4(0.f, 0.f, 0.f, 0.f);
+            }
             float s = 0.f;
 #pragma unroll
             for (int q = 0; q < NQ; ++q) {

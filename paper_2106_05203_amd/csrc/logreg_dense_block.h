@@ -122,7 +122,8 @@ __device__ __forceinline__ void dense_block(const float *__restrict__ A, const f
     }
 
     // ROWS rows per group and trip: their loads are all issued before the first dot product.  A row index past the
-    // block is clamped to the block's last row and its coefficient set to zero.
+    // block is clamped to the block's last row, an entry of the batch that names no row to row 0; what they load is
+    // cleared and their coefficient set to zero (an infinity times that zero would be NaN).
     const int64_t l0 = chunk * rows_per_wg;
     const int64_t l1 = !active ? l0 : (l0 + rows_per_wg < m ? l0 + rows_per_wg : m);
     constexpr int64_t kTrip = (int64_t)kDenseWaves * ROWS * kGroups;
@@ -160,6 +161,17 @@ __device__ __forceinline__ void dense_block(const float *__restrict__ A, const f
             }
         }
         if (l + kTrip < l1) listed(l + kTrip, src);
+        bool whole = true;
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) whole = whole && live[r];
+        if (!__all(whole)) {                                      // a block's last trip, or a batch entry out of range
+#pragma unroll
+            for (int r = 0; r < ROWS; ++r)
+#pragma unroll
+                for (int q = 0; q < NQ; ++q)
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) av[r][q][t] = live[r] ? av[r][q][t] : 0.f;
+        }
 #pragma unroll
         for (int r = 0; r < ROWS; ++r) {
             s[r] = 0.f;

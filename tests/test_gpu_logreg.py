@@ -338,3 +338,50 @@ def test_csr_gradient_groups(gpu, oracle, n, d, m, nnz):
                           to_gpu(torch, W.y), m, 0.1)
         got = h.local_grad(to_gpu(torch, x))
         assert_grads_close(got.cpu().numpy(), P.grads(x.astype(np.float64)), densify(W), W.y, x, nnz / 64 + 8, 32, "groups")
+
+
+# an infinity in a row that a group of rows only carries along: worker 0's first row (loaded by every worker of the
+# workgroup-per-row kernel in place of rows it does not have), a worker's last row (in place of rows past the block), and
+# row 0 outside the minibatch beside an entry out of range
+@pytest.mark.parametrize("n,d,m", [(3, 4097, 7), (2, 8192, 9), (3, 9000, 15), (2, 16384, 63), (2, 20001, 5), (3, 1, 9),
+                                   (3, 4, 33), (2, 60, 37), (2, 61, 70), (2, 120, 41), (3, 200, 19), (2, 500, 13),
+                                   (2, 1000, 11), (2, 2000, 21), (2, 2047, 21), (2, 3000, 9), (2, 29000, 5),
+                                   (2, 60, 150_000)])
+def test_an_infinite_entry_stays_in_its_row(gpu, n, d, m):
+    torch, binding = gpu
+    print(f"infinite entry case n={n} d={d} m={m}", flush=True)
+    rng = np.random.default_rng(d + m)
+    A = rng.standard_normal((n, m, d), dtype=np.float32) / np.float32(np.sqrt(d))
+    y = np.ones((n, m), np.float32)
+    x = -np.abs(rng.standard_normal(d)).astype(np.float32) - np.float32(0.1)    # every product with +inf is -inf
+    x64 = x.astype(np.float64)
+    A[0, 0, rng.integers(min(4, d))] = np.inf         # z = -inf: the coefficient is -1, the gradient's entry -inf
+    A[n - 1, m - 1, rng.integers(d)] = np.inf
+
+    def grads_of(rows, tau):
+        """rows [n][..]: valid row numbers; the sum is divided by tau."""
+        out = np.empty((n, d))
+        for i in range(n):
+            Ai, yi = A[i, rows[i]].astype(np.float64), y[i, rows[i]].astype(np.float64)
+            with np.errstate(over="ignore"):
+                r = -yi / (1.0 + np.exp(yi * (Ai @ x64)))
+            out[i] = r @ Ai / tau + 0.2 * x64 / (1.0 + x64 * x64) ** 2
+        return out
+
+    def check(got, ref, what):
+        assert np.array_equal(np.isfinite(got), np.isfinite(ref)), f"{what}: {np.argwhere(np.isfinite(got) != np.isfinite(ref))[:4]}"
+        fin = np.isfinite(ref)
+        assert np.array_equal(got[~fin], ref[~fin]), what
+        assert np.all(np.abs(got[fin] - ref[fin]) <= 1e-4 * np.abs(ref[fin]).max()), what    # the values: the tests above
+
+    with binding.EF21(n, d, 1, 0.1) as h:
+        h.set_problem_dense(to_gpu(torch, A), to_gpu(torch, y), 0.1)
+        check(h.local_grad(to_gpu(torch, x)).cpu().numpy(), grads_of([np.arange(m)] * n, m), "all rows")
+        if m > 2:
+            batch = np.stack([1 + rng.permutation(m - 2) for _ in range(n)]).astype(np.int32)   # neither infinite row
+            tau = batch.shape[1]
+            h.set_minibatch(to_gpu(torch, batch, np.int32))
+            check(h.local_grad(to_gpu(torch, x)).cpu().numpy(), grads_of(batch, tau), "batch")
+            batch[:, tau // 2] = m
+            h.set_minibatch(to_gpu(torch, batch, np.int32))
+            check(h.local_grad(to_gpu(torch, x)).cpu().numpy(), grads_of(np.delete(batch, tau // 2, axis=1), tau), "entry out of range")
