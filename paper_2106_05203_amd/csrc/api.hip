@@ -705,7 +705,6 @@ static int enqueue_plus(ef21_ctx *h, const float *grads, bool take_step, const e
     int32_t *idx_b = h->plus_idx, *idx_m = h->plus_idx + nk;
     float *val_b = h->plus_val, *val_m = h->plus_val + nk;
     ef21::TopkArgs plain{grads, nullptr, h->n, h->d, h->k, idx_b, val_b, nullptr};        // line 5: C(s)
-    plain.warm = 2;
     ef21::TopkArgs markov{grads, h->g_i, h->n, h->d, h->k, idx_m, val_m, nullptr};        // line 6: C(s - g_i)
     markov.warm = 1;
     hipError_t st;

@@ -80,9 +80,9 @@ struct TopkArgs {
     float *g_i;
     GradParts parts;   // if parts.part != nullptr the rows of `a` are these unreduced gradients (`a` is not read);
                        // launch_topk_row only, d <= kRowPartsMax, b != nullptr
-    int32_t warm;      // launch_topk_split only: 0, or 1 .. 2 = the row thresholds of the last call that named the
-                       // same number on this workspace serve as the first guess of this call's (the result never
-                       // depends on it; meant for consecutive iterations of one algorithm on one state)
+    int32_t warm;      // launch_topk_split only, k >= 2: 0, or 1 = the row thresholds of the last such call on this
+                       // workspace serve as the first guess of this call's (the result never depends on it; meant
+                       // for consecutive iterations of one algorithm on one state)
     // launch_topk_split with k > 1 only: if agg_start != nullptr the emission also writes the index that
     // launch_aggregate needs of the messages (aggregate_index_shift), so that its own indexing kernel can be skipped
     int32_t *agg_start;

@@ -205,3 +205,32 @@ def test_long_rows_whose_thresholds_jump(gpu, oracle, n, d, k):
             h.step(to_gpu(torch, grads), binding.PLUS)
             compare_plus_step(torch, h, st, choice, x_before, gamma, f"step {t}")
             h.set_state(to_gpu(torch, st.x), to_gpu(torch, st.g_i), to_gpu(torch, st.g))
+
+
+# Top-1: rows for the row kernel, for the many-workgroup path's argmax (more than 61440 entries; a Top-1 of s - g_i alone
+# from 16384 on), odd lengths, both loop orders
+@pytest.mark.parametrize("order", ["grad_first", "step_first"])
+@pytest.mark.parametrize("n,d", [(3, 9_001), (2, 20_001), (2, 61_440), (3, 70_001), (2, 1_000_004)])
+def test_top_1(gpu, oracle, n, d, order):
+    torch, binding = gpu
+    print(f"EF21+ Top-1 case n={n} d={d} {order}", flush=True)
+    rng = np.random.default_rng(d)
+    gamma = 0.25
+    x0 = rng.standard_normal(d).astype(np.float32)
+    g_i0 = (0.1 * rng.standard_normal((n, d))).astype(np.float32)
+    g0 = g_i0.astype(np.float64).mean(axis=0).astype(np.float32)
+    st = oracle.EF21State(x0.astype(np.float64), g_i0.astype(np.float64), g0.astype(np.float64))
+    flags = binding.PLUS | (binding.ORDER_STEP_FIRST if order == "step_first" else binding.ORDER_GRAD_FIRST)
+    with binding.EF21(n, d, 1, gamma) as h:
+        h.set_state(to_gpu(torch, x0), to_gpu(torch, g_i0), to_gpu(torch, g0))
+        for t in range(3):
+            grads = (st.g_i + 0.1 * rng.standard_normal((n, d))).astype(np.float32)
+            grads[:, 7 + t] = -3.0                            # the entry that both compressors keep
+            if t == 2:
+                grads[0] = 0.0
+                grads[0, -1] = 5.0                            # b = s exactly: the plain compressor
+            x_before = st.x.copy()
+            choice = oracle.iteration_plus(st, grads.astype(np.float64), 1, gamma, order=order)
+            h.step(to_gpu(torch, grads), flags)
+            compare_plus_step(torch, h, st, choice, x_before, gamma, f"step {t}")
+            h.set_state(to_gpu(torch, st.x), to_gpu(torch, st.g_i), to_gpu(torch, st.g))
