@@ -52,20 +52,31 @@ static_assert(kCandThreads == kRowThreads && kBlk == kRowThreads, "the rescue ru
 // 8.3 %) below the previous T and the window half an octave, so a threshold between 0.92 and 1.3 times the
 // previous one is found by the first pass: narrower bins, fewer entries to rank.  A candidate costs little (an
 // 8-byte store), a failed guess a second pass over the row, hence the generous margin.
-// That is where many entries are kept.  Where few are there is room in a bin, and the window is wider: T of a
-// heavy-tailed row lies up to an octave above the sample's bound, and a row that failed so once starts from a sample,
-// and can fail again, in every later call (n = 15, d = 5 million, k = 5000, Student-t gradients: up to 3.2 ms an
-// iteration against 0.15, all of it the exact algorithm on one row).  A bin then holds some two hundred entries at most;
-// wider bins everywhere cost the (n = 20, d = 10^6, k = 10^4) call 0.7 us of 33.8 in ranking.
-__device__ __forceinline__ uint32_t cold_shift(int64_t k, int64_t d) {
+// That is where many entries are kept.  Where few are, T of a heavy-tailed row lies up to an octave above the sample's
+// bound, and a row that failed so once starts from a sample, and can fail again, in every later call (n = 15, d = 5
+// million, k = 5000, Student-t gradients: 13 ms an iteration against 0.14, all of it the exact algorithm on one row), so
+// the window may be wider there: widest_cold and widest_warm.  It is so only where T's bin then holds no more than
+// kBinEntries entries, by the sample's density around T or, after a warm start, by what T's bin held in the call before:
+// heavy and Gaussian tails always, but the largest of 3 million uniform entries share a few bins, and a bin of more than
+// kTieCap different keys costs the exact algorithm (n = 1, d = 3 million, k = 1000, U(0, 1): 5.4 ms in the widest window,
+// 37 us in one of an octave).  The limit leaves a factor of 16 for a density that is uneven inside 1/16 octave.
+constexpr uint32_t kBinEntries = 64;
+__host__ __device__ inline uint32_t widest_cold(int64_t k, int64_t d) {
     if (k <= 4096) return 13u;                                    // four octaves
     if (k <= 131072 && k * 200 < d) return 12u;                   // two
     return k <= 400000 ? 11u : 10u;                               // one; half, where a wider bin would be crowded
 }
-__device__ __forceinline__ uint32_t warm_shift(int64_t k, int64_t d) {
+__host__ __device__ inline uint32_t widest_warm(int64_t k, int64_t d) {
     if (k > 1500000) return 9u;
-    const uint32_t s = cold_shift(k, d);
+    const uint32_t s = widest_cold(k, d);
     return s > 10u ? s - 1u : 10u;
+}
+// in_bin: entries of T's bin, 2^used keys wide, in this call (at most kTieCap, or kCrowdedBin)
+constexpr uint32_t kCrowdedBin = 1u << 16;
+__device__ __forceinline__ uint32_t warm_shift(int64_t k, int64_t d, uint32_t in_bin, uint32_t used) {
+    uint32_t s = widest_warm(k, d);
+    while (s > 10u && (in_bin << s) >> used > kBinEntries) --s;
+    return s;
 }
 constexpr uint32_t kWarmBelow = 1u << 20;
 constexpr int kTieCap = 1024;                // entries of T's bin that are ranked directly (one per thread)
@@ -83,13 +94,36 @@ struct __attribute__((aligned(64))) RowInfo {     // one cache line per row
     uint32_t ntie;                // length of the tie list
     uint32_t M;                   // candidates of the first pass (zero between calls)
     uint32_t q;                   // number of entries equal to the threshold key T that are kept
-    uint32_t warm_T[kWarmSlots], warm_ok[kWarmSlots];   // thresholds T of earlier calls (the last call's: warm_T[0] if warm == 0)
+    uint32_t warm_T[kWarmSlots];  // threshold T of the last call (also with warm == 0)
+    uint32_t warm_s[kWarmSlots];  // bin width for the next warm start from it; 0: there is none to start from
     uint32_t tie_min, tie_max;    // crowded bin: smallest and largest key in it.  Equal: T is that key (many equal
                                   // magnitudes at the threshold, e.g. zeros), no ranking needed.  Different: the
                                   // exact one-workgroup algorithm, in the emit kernel.
 };
 enum { kRowFine = 0, kRowFailed = 1, kRowCrowded = 2 };
 static_assert(sizeof(RowInfo) == 64, "one cache line");
+
+// How a sample is read, from k and d alone (set on the host: double precision in every wavefront cost half a microsecond).
+struct SampleRule {
+    uint32_t r;          // the r-th largest sampled key is, except with negligible probability, not above the k-th largest
+                         // key of the row; above kSample: no bound
+    uint32_t mid;        // where T is expected among the sampled keys
+    uint32_t widest;     // widest_cold
+    uint32_t most, most_next;   // samples in T's 2^19 keys up to which the bins are that wide, and half as wide
+};
+SampleRule sample_rule(int64_t k, int64_t d) {
+    SampleRule q{};
+    const double ns = (double)std::min<int64_t>(d, kSample), mu = (double)k * ns / (double)d;
+    // mean + 5 standard deviations + 8 of the number of sampled entries among the row's top k (a binomial with mean mu)
+    q.r = d <= kSample ? (uint32_t)k : (uint32_t)std::ceil(mu + 5.0 * std::sqrt(mu) + 8.0);
+    q.mid = std::max<uint32_t>(1u, std::min<uint32_t>(q.r, (uint32_t)(mu + 0.5)));
+    q.widest = widest_cold(k, d);
+    // a sample in 2^19 keys stands for d / ns / 2^19 entries per key; never narrower than 2^11 keys
+    auto most = [&](uint32_t s) { return (uint32_t)(s <= 11u ? (double)kSample : (double)kBinEntries * 524288.0 / (double)(1u << s) * ns / (double)d); };
+    q.most = most(q.widest);
+    q.most_next = most(q.widest - 1u);
+    return q;
+}
 
 struct Ws {
     uint32_t *hist_a, *hist_b;            // [n][kHistBins] each, kept zero between calls
@@ -104,6 +138,7 @@ struct Ws {
     int64_t L;                            // entries per wavefront piece = slot capacity
     int64_t nslot;                        // pieces per row
     int64_t G;                            // collect workgroups per row
+    SampleRule rule;                      // of the call's k and d
 };
 
 size_t align256(size_t b) { return (b + 255) / 256 * 256; }
@@ -158,6 +193,7 @@ size_t layout(int32_t n, int64_t d, char *base, Ws *w) {
         w->cand = (uint2 *)cd;
         w->resid = nullptr;
         w->kept = nullptr;
+        w->rule = SampleRule{};
     }
     return off;
 }
@@ -203,24 +239,44 @@ __device__ void zero_global_hist(uint32_t *hist, int bins) {
 }
 
 // ---------------------------------------------------------------- collect
-// Sample rank r such that the r-th largest sampled key is, except with negligible probability,
-// not above the k-th largest key of the row: mean + 5 standard deviations + 8 of the number of
-// sampled entries among the row's top k (a binomial with mean mu = k * sample / d).
-__device__ __forceinline__ uint32_t sample_rank(int64_t k, int64_t ns, int64_t d) {
-    if (ns >= d) return (uint32_t)k;      // the sample is the row
-    const double mu = (double)k * (double)ns / (double)d;
-    return (uint32_t)ceil(mu + 5.0 * sqrt(mu) + 8.0);
+// Where the sample's keys lie, by their 12 leading bits (s.hist): s.bin = the bin of the r-th largest, s.need = the number
+// of samples in the bin of the mid-th largest.  1 <= mid <= r <= the number of samples.
+__device__ void select_sample_bins(RowShared &s, uint32_t r, uint32_t mid) {
+    constexpr int kPer = kBins1 / kBlk;                               // bins per thread, from the top
+    uint32_t h[kPer], mine = 0u;
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+        h[j] = s.hist[kBins1 - 1 - ((int)threadIdx.x * kPer + j)];
+        mine += h[j];
+    }
+    const uint32_t incl = wave_inclusive_scan(mine);
+    const int wave = threadIdx.x / kWave;
+    if (lane_id() == kWave - 1) s.wave_a[wave] = incl;
+    __syncthreads();
+    uint32_t run = incl - mine;
+    for (int w = 0; w < wave; ++w) run += s.wave_a[w];
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {                                  // each holds for one bin
+        if (run < r && r <= run + h[j]) s.bin = (uint32_t)(kBins1 - 1 - ((int)threadIdx.x * kPer + j));
+        if (run < mid && mid <= run + h[j]) s.need = h[j];
+        run += h[j];
+    }
+    __syncthreads();
 }
 
-// Lower bound of the candidate keys from the sample, identical in every workgroup of a row (it depends on
-// the data only): the lower edge of the bin, in a histogram of the keys' 12 leading bits (1/16 octave), that holds
+// Lower bound of the candidate keys and bin width from the sample, identical in every workgroup of a row (they depend on
+// the data only).  key_lo: the lower edge of the bin, in a histogram of the keys' 12 leading bits (1/16 octave), that holds
 // the sample's r-th largest key.  A finer bound would save a few per cent of the candidates, which cost little,
 // for a second histogram pass, which costs a microsecond in every workgroup.  0 means "every entry is a candidate".
+// shift: see widest_cold.
+struct Guess {
+    uint32_t key_lo, shift;
+};
 template <bool DIFF>
-__device__ uint32_t estimate_key_lo(RowShared &s, const float *a, const float *b, int64_t d, int64_t k) {
+__device__ Guess guess_from_sample(RowShared &s, const float *a, const float *b, int64_t d, const SampleRule &rule) {
+    static_assert(kBits2 + kBits3 == 19, "sample_rule counts samples in 2^19 keys");
     const int64_t ns = d < kSample ? d : kSample;
-    const uint32_t r = sample_rank(k, ns, d);
-    if (r > ns) return 0u;
+    if (rule.r > ns) return {0u, rule.widest};
     uint32_t skey[kSamplePer];
 #pragma unroll
     for (int j = 0; j < kSamplePer; ++j) {
@@ -238,10 +294,11 @@ __device__ uint32_t estimate_key_lo(RowShared &s, const float *a, const float *b
     for (int j = 0; j < kSamplePer; ++j)
         if (skey[j] != 0xffffffffu) atomicAdd(&s.hist[skey[j] >> (kBits2 + kBits3)], 1u);
     __syncthreads();
-    select_bin(s, kBins1, r);
-    const uint32_t key_lo = s.bin << (kBits2 + kBits3);
+    select_sample_bins(s, rule.r, rule.mid);
+    const uint32_t near_t = s.need;
+    const Guess g{s.bin << (kBits2 + kBits3), rule.widest - (near_t <= rule.most ? 0u : (near_t <= rule.most_next ? 1u : 2u))};
     __syncthreads();
-    return key_lo;
+    return g;
 }
 
 // Per-wavefront staging ring in LDS: candidates (position, value bits) are appended here and leave for the slot
@@ -361,7 +418,6 @@ __device__ __forceinline__ void collect_rows(const TopkArgs &p, const Ws &w, Row
     const float *b = DIFF ? p.b + row * d : nullptr;
     RowInfo *info = w.info + row;
     CandFilter f;
-    f.shift = cold_shift(p.k, d);
     f.hist = s.hist;
     uint32_t *merged = w.hist_a + row * kHistBins;
     uint32_t *row_total = &info->M;
@@ -371,7 +427,9 @@ __device__ __forceinline__ void collect_rows(const TopkArgs &p, const Ws &w, Row
         const uint32_t warm_used = info->warm_used, M = info->M, beyond = merged[kHistBins - 1];
         if (!warm_used) return;                      // a cold first pass: what fails goes to the exact algorithm
         if (M >= (uint32_t)p.k && beyond < (uint32_t)p.k) return;
-        f.key_lo = estimate_key_lo<DIFF>(s, a, b, d, p.k);
+        const Guess g = guess_from_sample<DIFF>(s, a, b, d, w.rule);
+        f.key_lo = g.key_lo;
+        f.shift = g.shift;
         merged = w.hist_b + row * kHistBins;
         row_total = nullptr;
         if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -380,14 +438,16 @@ __device__ __forceinline__ void collect_rows(const TopkArgs &p, const Ws &w, Row
             info->use2 = 1u;
         }
     } else {
-        bool warm = false;
-        if constexpr (MODE == kWarmPass) warm = info->warm_ok[p.warm - 1] != 0u;
+        uint32_t warm = 0u;                          // the remembered threshold's bin width
+        if constexpr (MODE == kWarmPass) warm = info->warm_s[p.warm - 1];
         if (warm) {
             const uint32_t T = info->warm_T[p.warm - 1];
             f.key_lo = T > kWarmBelow ? T - kWarmBelow : 0u;
-            f.shift = warm_shift(p.k, d);
+            f.shift = warm;
         } else {
-            f.key_lo = estimate_key_lo<DIFF>(s, a, b, d, p.k);
+            const Guess g = guess_from_sample<DIFF>(s, a, b, d, w.rule);
+            f.key_lo = g.key_lo;
+            f.shift = g.shift;
         }
         if (blockIdx.x == 0 && threadIdx.x == 0) {
             info->key_lo = f.key_lo;
@@ -524,22 +584,24 @@ __global__ __launch_bounds__(kBlk) void split_collect_pair_kernel(TopkArgs pm, W
     CandFilter fm, fp;
     fm.hist = s.hist;
     fp.hist = hist_p;
-    const bool warm_m = WARM && info_m->warm_ok[pm.warm - 1] != 0u, warm_pl = WARM && info_p->warm_ok[warm_p - 1] != 0u;
+    const uint32_t warm_m = WARM ? info_m->warm_s[pm.warm - 1] : 0u, warm_pl = WARM ? info_p->warm_s[warm_p - 1] : 0u;
     if (warm_m) {
         const uint32_t T = info_m->warm_T[pm.warm - 1];
         fm.key_lo = T > kWarmBelow ? T - kWarmBelow : 0u;
-        fm.shift = warm_shift(pm.k, d);
+        fm.shift = warm_m;
     } else {
-        fm.key_lo = estimate_key_lo<true>(s, a, b, d, pm.k);
-        fm.shift = cold_shift(pm.k, d);
+        const Guess g = guess_from_sample<true>(s, a, b, d, wm.rule);
+        fm.key_lo = g.key_lo;
+        fm.shift = g.shift;
     }
     if (warm_pl) {
         const uint32_t T = info_p->warm_T[warm_p - 1];
         fp.key_lo = T > kWarmBelow ? T - kWarmBelow : 0u;
-        fp.shift = warm_shift(pm.k, d);
+        fp.shift = warm_pl;
     } else {
-        fp.key_lo = estimate_key_lo<false>(s, a, nullptr, d, pm.k);
-        fp.shift = cold_shift(pm.k, d);
+        const Guess g = guess_from_sample<false>(s, a, nullptr, d, wm.rule);
+        fp.key_lo = g.key_lo;
+        fp.shift = g.shift;
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         info_m->key_lo = fm.key_lo; info_m->shift = fm.shift; info_m->use2 = 0u; info_m->ntie = 0u;
@@ -656,10 +718,11 @@ __global__ __launch_bounds__(kBlk) void split_collect_pair_kernel(TopkArgs pm, W
 // ---------------------------------------------------------------- count
 // The exact one-workgroup algorithm on the original data for a row whose guess failed, and the message index of
 // the row if the caller asked for one.  All kCandThreads threads of the workgroup must call.
-// The threshold found is remembered as any other, so that the row's next call does not start from a sample again.
+// The threshold found is remembered as any other, so that the row's next call does not start from a sample again, with
+// next_shift as the bin width.
 // SUMS (Algorithm 3): the whole row's sum of kept squares goes to its first slot, the others' are zero.
 template <bool DIFF, int UPDATE, bool SUMS>
-__device__ void rescue_row(RowShared &rs, const TopkArgs &p, const Ws &w, int64_t row) {
+__device__ void rescue_row(RowShared &rs, const TopkArgs &p, const Ws &w, int64_t row, uint32_t next_shift) {
     row_topk<DIFF, UPDATE>(rs, p, row);
     if (p.warm > 0) {
         uint32_t *part = rs.hist, T = 0xffffffffu;
@@ -678,7 +741,7 @@ __device__ void rescue_row(RowShared &rs, const TopkArgs &p, const Ws &w, int64_
         if (threadIdx.x == 0) {
             for (int v = 0; v < kCandWaves; ++v) T = part[v] < T ? part[v] : T;
             w.info[row].warm_T[p.warm - 1] = T;
-            w.info[row].warm_ok[p.warm - 1] = 1u;
+            w.info[row].warm_s[p.warm - 1] = next_shift;
         }
     }
     if constexpr (SUMS) {
@@ -789,7 +852,7 @@ __device__ __forceinline__ void count_rows(const TopkArgs &p, const Ws &w, Count
         crowded = !failed && lds_out[2] > (uint32_t)kTieCap;           // too many to list: see RowInfo::tie_min
     }
     if (rescue) {
-        if (failed) rescue_row<DIFF, UPDATE, SUMS>(rs, p, w, row);
+        if (failed) rescue_row<DIFF, UPDATE, SUMS>(rs, p, w, row, widest_warm(p.k, p.d));
         return;
     }
     if (blockIdx.x == 0 && tid == 0) {
@@ -972,7 +1035,8 @@ __device__ __forceinline__ void emit_rows(const TopkArgs &p, const Ws &w, EmitSh
     const RowInfo ri = *info;
     const bool crowded = ri.failed == kRowCrowded;
     if (rescue) {
-        if (crowded && ri.tie_min != ri.tie_max) rescue_row<DIFF, UPDATE, SUMS>(rs, p, w, row);
+        if (crowded && ri.tie_min != ri.tie_max)
+            rescue_row<DIFF, UPDATE, SUMS>(rs, p, w, row, warm_shift(p.k, p.d, kCrowdedBin, 0u));
         return;
     }
     const uint2 listed = w.tie[row * kTieCap + (tid < kTieCap ? tid : 0)];
@@ -1052,7 +1116,8 @@ __device__ __forceinline__ void emit_rows(const TopkArgs &p, const Ws &w, EmitSh
         info->q = q;
         const int mem = p.warm > 0 ? p.warm - 1 : 0;
         info->warm_T[mem] = T;
-        info->warm_ok[mem] = p.warm > 0 ? 1u : 0u;
+        // a crowded bin of equal keys: no wider the next time (narrower would not help)
+        info->warm_s[mem] = p.warm > 0 ? warm_shift(p.k, p.d, crowded ? kBinEntries : ntie, ri.use2 != 0u ? ri.shift2 : ri.shift) : 0u;
     }
 
     part = wave_sum_u32(part);
@@ -1323,6 +1388,7 @@ hipError_t launch_after_collect(const TopkArgs &p, const Ws &w, hipStream_t stre
 hipError_t launch_topk_split(const TopkArgs &p, void *workspace, hipStream_t stream, const Marker &mk) {
     Ws w;
     layout(p.n, p.d, (char *)workspace, &w);
+    w.rule = sample_rule(p.k, p.d);
     if (p.g_i && p.g_i != (p.b ? p.b : p.a)) return hipErrorInvalidValue;
     if (p.warm < 0 || p.warm > kWarmSlots) return hipErrorInvalidValue;
     if (p.agg_start && (p.agg_shift < 0 || p.agg_shift > 11 || p.agg_nblk != ((p.d - 1) >> p.agg_shift) + 1 || p.k == 1))
@@ -1360,6 +1426,7 @@ hipError_t launch_topk_split_pair(const TopkArgs &plain, const TopkArgs &markov,
     Ws wp, wm;
     layout(plain.n, plain.d, (char *)ws_plain, &wp);
     layout(markov.n, markov.d, (char *)ws_markov, &wm);
+    wp.rule = wm.rule = sample_rule(plain.k, plain.d);
     wp.kept = sums.kept_plain;
     wm.kept = sums.kept_markov;
     wm.resid = sums.resid;

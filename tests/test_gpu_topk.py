@@ -287,3 +287,100 @@ def test_rows_at_any_address(gpu, oracle, n, d, k):
         want = np.sort(order)
         assert np.array_equal(idx[i], want), f"row {i}: positions differ"
         assert same_bits(val[i], V[i][want])
+
+
+def to_gpu(torch, a):
+    return torch.from_numpy(np.ascontiguousarray(a, dtype=np.float32)).cuda()
+
+
+def largest(V, k):
+    """Positions (ascending) of the k largest magnitudes of one row, ties to the lower position, without a full sort."""
+    key = np.abs(V)
+    T = np.partition(key, key.size - k)[key.size - k]
+    above = np.nonzero(key > T)[0]
+    return np.sort(np.concatenate([above, np.nonzero(key == T)[0][:k - above.size]]))
+
+
+def best_time(torch, call, repeats=6):
+    """Shortest of a few calls, in microseconds."""
+    best = np.inf
+    for _ in range(repeats):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        call()
+        b.record()
+        torch.cuda.synchronize()
+        best = min(best, 1e3 * a.elapsed_time(b))
+    return best
+
+
+def rows_like(kind, rng, n, d):
+    if kind == "uniform":
+        return rng.random((n, d), dtype=np.float32)
+    if kind == "offset":
+        return np.float32(10) + np.float32(0.02) * rng.standard_normal((n, d), dtype=np.float32)
+    if kind == "student":
+        return rng.standard_t(3, size=(n, d)).astype(np.float32)
+    return rng.standard_normal((n, d), dtype=np.float32)
+
+
+# rows whose largest entries lie close together (many of them in one wide bin of the candidates' histogram), rows with a
+# heavy tail (the threshold far above the sample's bound) and Gaussian ones, k on both sides of the limits that choose
+# the widest bin: right, and no row by the one-workgroup algorithm, which takes milliseconds for rows this long
+@pytest.mark.parametrize("n,d,k", [(1, 3_000_000, 1000), (2, 3_000_000, 4096), (1, 7_000_000, 12_000), (2, 1_000_000, 1000),
+                                   (1, 5_000_000, 100)])
+def test_flat_and_heavy_rows_take_the_fast_path(gpu, n, d, k):
+    torch, binding = gpu
+    print(f"flat rows n={n} d={d} k={k}", flush=True)
+    rng = np.random.default_rng(d + k)
+    V = rows_like("normal", rng, n, d)
+    rows = to_gpu(torch, V)
+    binding.ef21_topk(rows, k)
+    usual = best_time(torch, lambda: binding.ef21_topk(rows, k))
+    for kind in ("uniform", "offset", "student"):
+        if kind == "offset" and k > 1000:
+            continue                                  # more than kTieCap entries at the threshold however narrow the bin
+        V = rows_like(kind, rng, n, d)
+        rows = to_gpu(torch, V)
+        idx, val = (t.cpu().numpy() for t in binding.ef21_topk(rows, k))
+        for i in range(n):
+            want = largest(V[i], k)
+            assert np.array_equal(idx[i], want), f"{kind}, row {i}"
+            assert same_bits(val[i], V[i][want]), f"{kind}, row {i}"
+        took = best_time(torch, lambda: binding.ef21_topk(rows, k))
+        print(f"  {kind}: {took:.0f} us, normal {usual:.0f} us", flush=True)
+        assert took <= 12 * usual + 200, f"{kind}: {took:.0f} us against {usual:.0f} us"
+
+
+@pytest.mark.parametrize("kind", ["uniform", "student"])
+@pytest.mark.parametrize("n,d,k", [(2, 5_000_000, 1000), (3, 3_000_000, 9000)])
+def test_flat_and_heavy_gradients_take_the_fast_path(gpu, n, d, k, kind):
+    """The same inside ef21_step, whose thresholds and bin widths carry over from step to step."""
+    torch, binding = gpu
+    print(f"flat gradients {kind} n={n} d={d} k={k}", flush=True)
+    rng = np.random.default_rng(d + k)
+    g_i = np.zeros((n, d), np.float32)
+    times = {}
+    with binding.EF21(n, d, k, 0.01) as h:
+        for what in (kind, "normal"):
+            g_i[:] = 0.0
+            h.set_state(torch.zeros(d, device="cuda"), to_gpu(torch, g_i))
+            pool = [rows_like(what, rng, n, d) for _ in range(2)]
+            dev = [to_gpu(torch, v) for v in pool]
+            for t in range(4):
+                diff = pool[t % 2] - g_i
+                h.step(dev[t % 2])
+                idx, val = (a.cpu().numpy() for a in h.get_messages())
+                for i in range(n):
+                    want = largest(diff[i], k)
+                    assert np.array_equal(idx[i], want), f"{what}, step {t}, row {i}"
+                    assert same_bits(val[i], diff[i][want]), f"{what}, step {t}, row {i}"
+                    g_i[i, want] += diff[i][want]
+            turn = [0]
+
+            def one():
+                turn[0] ^= 1
+                h.step(dev[turn[0]])
+            times[what] = best_time(torch, one)
+    print(f"  {times}", flush=True)
+    assert times[kind] <= 12 * times["normal"] + 200, times
