@@ -420,7 +420,13 @@ hipError_t launch_logreg_grad_dense(const float *A, const float *y, const float 
     mk(K_GRAD_MAIN);
     hipError_t st = hipGetLastError();
     if (st != hipSuccess) return st;
-    if (defer && fused && x_stride == 0 && d <= kRowPartsMax) {      // the consumer finishes the sums itself (dense_grad_entry)
+    // The consumer finishes the sums itself (dense_grad_entry) where that is less work for its one workgroup per row than
+    // another kernel of 4 to 5 us: 1 us per 40 KB of sums and per 1000 columns (the regulariser's divisions).  step, us,
+    // with the sums left and finished: n = 2, m = 50000, d = 300 (256 blocks) 37.9 and 39.4; n = 4, m = 2000, d = 1000 (64)
+    // 20.9 and 22.1; n = 20, m = 5000, d = 2000 (25) 137.3 and 137.0; n = 10, m = 4000, d = 2000 (51) 69.1 and 67.0; n = 1, m = 8000,
+    // d = 1000 (250) 29.6 and 26.1; n = 32, m = 200, d = 8000 (8) 75 and 65; n = 1, m = 1000, d = 8000 (250) 116 and 39.
+    constexpr int64_t kPartsWork = 120000, kColumnWork = 25;
+    if (defer && fused && x_stride == 0 && d <= kRowPartsMax && (pl.chunks + kColumnWork) * d <= kPartsWork) {
         *defer = GradParts{part, pl.chunks, m, x, lambda};
         return hipSuccess;
     }

@@ -161,10 +161,14 @@ __device__ __forceinline__ void dense_block(const float *__restrict__ A, const f
             }
         }
         if (l + kTrip < l1) listed(l + kTrip, src);
-        bool whole = true;
+        bool clear = l + ROWS * kGroups > l1;                     // a block's last trip
+        if constexpr (BATCH) {
+            bool named = true;
 #pragma unroll
-        for (int r = 0; r < ROWS; ++r) whole = whole && live[r];
-        if (!__all(whole)) {                                      // a block's last trip, or a batch entry out of range
+            for (int r = 0; r < ROWS; ++r) named = named && live[r];
+            clear = !__all(named);
+        }
+        if (clear) {
 #pragma unroll
             for (int r = 0; r < ROWS; ++r)
 #pragma unroll

@@ -385,3 +385,44 @@ def test_an_infinite_entry_stays_in_its_row(gpu, n, d, m):
             batch[:, tau // 2] = m
             h.set_minibatch(to_gpu(torch, batch, np.int32))
             check(h.local_grad(to_gpu(torch, x)).cpu().numpy(), grads_of(np.delete(batch, tau // 2, axis=1), tau), "entry out of range")
+
+
+def best_time(torch, call, repeats=8):
+    """Shortest of a few calls, in microseconds."""
+    best = np.inf
+    for _ in range(repeats):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        call()
+        b.record()
+        torch.cuda.synchronize()
+        best = min(best, 1e3 * a.elapsed_time(b))
+    return best
+
+
+# step finishes the gradient's sums in the Top-k kernel or before it, by their number and the row's length: the same bits
+# as local_grad on both sides, and not one workgroup per worker where there are many (long rows, few workers)
+@pytest.mark.parametrize("n,d,m", [(1, 8000, 1000), (2, 8192, 500), (1, 4097, 3000), (2, 4096, 60), (32, 8000, 9),
+                                   (2, 2000, 2000), (4, 1000, 2000), (10, 2000, 40), (2, 300, 5000)])
+def test_step_finishes_the_gradient_either_way(gpu, n, d, m):
+    torch, binding = gpu
+    print(f"finish case n={n} d={d} m={m}", flush=True)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(d + m)
+    A = torch.randn((n, m, d), device="cuda", generator=g) / d ** 0.5
+    y = torch.where(torch.rand((n, m), device="cuda", generator=g) < 0.5, 1.0, -1.0)
+    x = torch.randn(d, device="cuda", generator=g)
+    with binding.EF21(n, d, 5, 1e-30) as h:
+        h.set_problem_dense(A, y, 0.1)
+        want = h.local_grad(x)
+        h.set_state(x=x, g_i=torch.zeros((n, d), device="cuda"))
+        h.step()
+        idx, val = h.get_messages()
+        assert torch.equal(val, want.gather(1, idx.long()))
+        kept = val.abs().min(1).values
+        rest = want.scatter(1, idx.long(), 0.0).abs().max(1).values
+        assert (rest <= kept).all()
+        out = torch.empty((n, d), device="cuda")
+        grad, step = best_time(torch, lambda: h.local_grad(x, out=out)), best_time(torch, h.step)
+    print(f"  local_grad {grad:.0f} us, step {step:.0f} us", flush=True)
+    assert step <= grad + 45.0, (grad, step)
