@@ -75,9 +75,16 @@ inline DensePlan dense_plan(int32_t n, int64_t m, int64_t d, bool deep) {
     int64_t rows = (m + target - 1) / target;
     const int64_t fewer = (m + max_chunks(n, m) - 1) / max_chunks(n, m);
     if ((fewer + trip - 1) / trip < (rows + trip - 1) / trip) rows = fewer;
-    // Small problems: at most 32 sums per worker, because one workgroup per worker adds them up in the Top-k kernel of
-    // ef21_step (n = 5, m = 700, d = 1001: 88 of them took 16 us there).
-    if ((int64_t)n * m * d <= ((int64_t)1 << 23) && rows < (m + 31) / 32) rows = (m + 31) / 32;
+    // Small problems: half as many blocks, one per compute unit, of about 100 KB of rows or more, but 32 per worker in any
+    // case: each block's sums are read again.  The gradient of n = 1, m = 8000, d = 1000: 34 us with 500 blocks, 31 with 32,
+    // 16.3 so; n = 1, m = 100000, d = 80: 42, 95, 23; n = 8, m = 1000, d = 1000: 14.4, 11.1, 11.1.  step of n = 5, m = 700,
+    // d = 1001: 17.9 us with 32 blocks per worker, 19.2 with 42.  Above 2^23 entries: m = 20000, d = 1000 30 us with 512 blocks
+    // and 25 with 256, but m = 200000, d = 80 31 and 35, n = 8, m = 8000, d = 300 19.6 and 25.9.
+    if ((int64_t)n * m * d <= ((int64_t)1 << 23)) {
+        int64_t most = m * d / 24576 < 256 / n ? m * d / 24576 : 256 / n;
+        if (most < 48) most = 32;                              // (a few more gain nothing)
+        if (rows < (m + most - 1) / most) rows = (m + most - 1) / most;
+    }
     if (rows < least) rows = least;
     return {rows, (m + rows - 1) / rows};
 }

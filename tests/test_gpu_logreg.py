@@ -426,3 +426,26 @@ def test_step_finishes_the_gradient_either_way(gpu, n, d, m):
         grad, step = best_time(torch, lambda: h.local_grad(x, out=out)), best_time(torch, h.step)
     print(f"  local_grad {grad:.0f} us, step {step:.0f} us", flush=True)
     assert step <= grad + 45.0, (grad, step)
+
+
+# the same rows with one or two workers and with sixteen: few workers fill the chip by cutting their rows into more blocks
+@pytest.mark.parametrize("n,d,m", [(1, 80, 100_000), (2, 100, 40_000), (1, 1000, 8000)])
+def test_few_workers_fill_the_chip(gpu, n, d, m):
+    torch, binding = gpu
+    print(f"few workers case n={n} d={d} m={m}", flush=True)
+    times = {}
+    for workers in (n, 16):
+        rows = n * m // workers
+        A = torch.randn((workers, rows, d), device="cuda")
+        y = torch.ones((workers, rows), device="cuda")
+        x = torch.zeros(d, device="cuda")
+        out = torch.empty((workers, d), device="cuda")
+        with binding.EF21(workers, d, 1, 0.1) as h:
+            h.set_problem_dense(A, y, 0.1)
+            h.local_grad(x, out=out)
+            # at x = 0 every coefficient is -1/2: the gradient is the rows' mean times that
+            want = -0.5 * A.double().mean(1)
+            assert (out.double() - want).abs().max() <= 1e-5 * want.abs().max() + 1e-7
+            times[workers] = best_time(torch, lambda: h.local_grad(x, out=out))
+    print(f"  {times}", flush=True)
+    assert times[n] <= 2.0 * times[16] + 10.0, times
