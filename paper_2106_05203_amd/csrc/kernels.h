@@ -93,8 +93,8 @@ struct TopkArgs {
 // Rows this long can be handed to launch_topk_row as unreduced gradients (TopkArgs::parts).
 constexpr int64_t kRowPartsMax = 8192;
 
-// One workgroup per row, four radix passes over the row plus an ordered emission.  Needs no workspace; rows of at most
-// 16384 entries, which are held in LDS.
+// One workgroup per row: a histogram pass over the row and a ranking of the threshold's bin (three histogram passes where
+// the bin is crowded), then an ordered emission.  Needs no workspace; rows of at most 16384 entries.
 hipError_t launch_topk_row(const TopkArgs &p, hipStream_t stream);
 
 // One workgroup per row that reads the row once and keeps 16 bits of every key in LDS: rows of kRow16Min to

@@ -11,6 +11,13 @@
 namespace ef21 {
 namespace {
 
+// The row read from L2 in every pass: 16 KB of LDS, two workgroups per compute unit.
+template <bool DIFF, int UPDATE>
+__global__ __launch_bounds__(kRowThreads) void topk_row_kernel(TopkArgs p) {
+    __shared__ RowShared s;
+    row_topk<DIFF, UPDATE>(s, p, blockIdx.x);
+}
+
 template <int CACHE, bool DIFF, int UPDATE>
 __global__ __launch_bounds__(kRowThreads) void topk_row_cached_kernel(TopkArgs p) {
     __shared__ RowShared s;
@@ -35,6 +42,15 @@ void launch_cached(const TopkArgs &p, hipStream_t stream) {
     else hipLaunchKernelGGL((topk_row_cached_kernel<CACHE, false, kNoUpdate>), grid, block, 0, stream, p);
 }
 
+void launch_uncached(const TopkArgs &p, hipStream_t stream) {
+    const dim3 grid((unsigned)p.n), block(kRowThreads);
+    const bool diff = p.b != nullptr, upd = p.g_i != nullptr;
+    if (upd && diff) hipLaunchKernelGGL((topk_row_kernel<true, kAddUpdate>), grid, block, 0, stream, p);
+    else if (upd) hipLaunchKernelGGL((topk_row_kernel<false, kClearUpdate>), grid, block, 0, stream, p);
+    else if (diff) hipLaunchKernelGGL((topk_row_kernel<true, kNoUpdate>), grid, block, 0, stream, p);
+    else hipLaunchKernelGGL((topk_row_kernel<false, kNoUpdate>), grid, block, 0, stream, p);
+}
+
 }  // namespace
 
 hipError_t launch_topk_row(const TopkArgs &p, hipStream_t stream) {
@@ -49,8 +65,10 @@ hipError_t launch_topk_row(const TopkArgs &p, hipStream_t stream) {
     }
     if (p.d <= kRowCacheShort) {
         launch_cached<kRowCacheShort>(p, stream);
-    } else if (p.d <= kRowCache) {
+    } else if (p.d <= kRowCache && p.n <= 256) {
         launch_cached<kRowCache>(p, stream);
+    } else if (p.d <= kRowCache) {                    // more rows than compute units: see kRowCache
+        launch_uncached(p, stream);
     } else {
         return hipErrorInvalidValue;                  // longer rows: launch_topk_row16, launch_topk_split
     }

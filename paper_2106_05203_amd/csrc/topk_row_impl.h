@@ -238,9 +238,10 @@ __device__ void row_topk(RowShared &s, const TopkArgs &p, int64_t row) {
         s, p, row, [=](int64_t e) { return load_v<DIFF>(a, b, e); }, [=](int64_t e) { return DIFF ? b[e] : 0.f; });
 }
 
-// Rows of at most kRowCache entries: the row is formed once into LDS (`cache`), all passes read it there.  (Rows from
-// 8193 entries on used to be read from L2 in every pass: ef21_topk of 20 rows of 12000, k = 1000, 15.9 us a call,
-// 14.7 so; 100 rows of 16383 17.6 and 15.7.)
+// Rows of at most kRowCache entries: the row is formed once into LDS (`cache`), all passes read it there.  From 8193 entries
+// on the copy leaves room for one workgroup per compute unit instead of two, so more than 256 rows are read from L2 in
+// every pass (row_topk).  ef21_topk, us, from L2 and from LDS: 20 rows of 12000, k = 1000 15.9 and 14.7; 100 of 16383 17.6 and
+// 15.7; 300 of 9000 15.7 and 20.7; 1000 of 9000 31.9 and 43.6.
 constexpr int kRowCache = 16384, kRowCacheShort = (int)kRowPartsMax;
 
 template <bool DIFF, int UPDATE>

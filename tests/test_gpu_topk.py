@@ -384,3 +384,53 @@ def test_flat_and_heavy_gradients_take_the_fast_path(gpu, n, d, k, kind):
             times[what] = best_time(torch, one)
     print(f"  {times}", flush=True)
     assert times[kind] <= 12 * times["normal"] + 200, times
+
+
+# rows just too long for the short LDS copy, as many as there are compute units (the long copy) and more (none)
+@pytest.mark.parametrize("n,d,k", [(256, 8193, 80), (257, 8193, 80), (300, 16_383, 1), (513, 9001, 9001), (300, 12_001, 1200)])
+def test_many_rows_of_moderate_length(gpu, n, d, k):
+    torch, binding = gpu
+    print(f"many rows n={n} d={d} k={k}", flush=True)
+    rng = np.random.default_rng(d + k)
+    V = np.round(rng.standard_normal((n, d), dtype=np.float32) * 64) / 64          # ties
+    g_i = np.round(rng.standard_normal((n, d), dtype=np.float32) * 64) / 64
+    idx, val = (t.cpu().numpy() for t in binding.ef21_topk(to_gpu(torch, V), k))
+    diff = V - g_i
+    with binding.EF21(n, d, k, 1.0) as h:
+        h.set_state(torch.zeros(d, device="cuda"), to_gpu(torch, g_i))
+        h.step(to_gpu(torch, V))
+        m_idx, m_val = (t.cpu().numpy() for t in h.get_messages())
+        g_new = h.get_state()[1].cpu().numpy()
+        h.set_state(torch.zeros(d, device="cuda"), to_gpu(torch, g_i))
+        h.step(to_gpu(torch, V), binding.CLASSIC_EF)
+        e_idx, e_val = (t.cpu().numpy() for t in h.get_messages())
+        e_new = h.get_state()[1].cpu().numpy()
+    for i in range(n):
+        want = largest(V[i], k)
+        assert np.array_equal(idx[i], want) and same_bits(val[i], V[i][want]), f"row {i}"
+        want = largest(diff[i], k)
+        assert np.array_equal(m_idx[i], want) and same_bits(m_val[i], diff[i][want]), f"row {i}: message"
+        row = g_i[i].copy()
+        row[want] += diff[i][want]
+        assert same_bits(g_new[i], row), f"row {i}: g_i"
+        p = g_i[i] + V[i]                                     # exact: multiples of 1/64
+        want = largest(p, k)
+        assert np.array_equal(e_idx[i], want) and same_bits(e_val[i], p[want]), f"row {i}: EF message"
+        p[want] = 0.0
+        assert same_bits(e_new[i], p), f"row {i}: error"
+
+
+def test_rows_just_too_long_for_the_short_copy(gpu):
+    """1000 rows of 8193 and of 8192 entries: a workgroup of either takes as much room, so they take as long (with the
+    long LDS copy 41 us against 28, so 31)."""
+    torch, binding = gpu
+    times = {}
+    for d in (8192, 8193):
+        rows = torch.randn((1000, d), device="cuda")
+
+        def twenty():
+            for _ in range(20):
+                binding.ef21_topk(rows, 81)
+        times[d] = best_time(torch, twenty) / 20
+    print(times, flush=True)
+    assert times[8193] <= 1.27 * times[8192], times
