@@ -23,7 +23,7 @@
 // The guess can be wrong: fewer than k candidates, T beyond the histogram's window, or a crowded bin (more
 // than kTieCap entries, i.e. very many equal magnitudes at the threshold).  After a warm start a second collect
 // pass (normally a launch that ends at once) redoes such a row from the sample; a row that still fails is selected
-// by the exact one-workgroup algorithm on the original data (an extra workgroup of the count kernel), so the
+// by the exact one-workgroup algorithm on the original data (its first workgroup of the count kernel), so the
 // result never depends on the guess.  Slots have the capacity of their piece, so any input fits.
 #include <algorithm>
 #include <cmath>
@@ -780,10 +780,12 @@ __device__ void rescue_row(RowShared &rs, const TopkArgs &p, const Ws &w, int64_
 // with everything else whose address does not depend on the prologue, so that a workgroup waits for memory once,
 // not once per step of its prologue.  See cand_steps for kPre.
 
-// Grid (slot blocks + 1, n).  Prologue of every workgroup: T's bin from the row's histogram, and whether the row
-// failed (see the head of the file).  The last workgroup of a row is the rescue: it selects a failed row by the
-// exact one-workgroup algorithm on the original data (DIFF and UPDATE matter here only).  The others: a slot's
-// candidates in bins above T's are counted, those in T's bin go to the tie list.
+// Grid (slot blocks, n).  Prologue of every workgroup: T's bin from the row's histogram, and whether the row failed (see
+// the head of the file); the row's first workgroup then selects it by the exact one-workgroup algorithm on the original
+// data (DIFF and UPDATE matter here only).  Otherwise a slot's candidates in bins above T's are counted, those in T's bin
+// go to the tie list.  (An extra workgroup per row for the exact algorithm, as there used to be, keeps a compute unit from
+// the last of 255 others for a few microseconds, here and in the emit kernel, since a unit holds one of them: step of
+// n = 15, d = 5 million, k = 50000 10.1 and 40.6 us in the two kernels, 6.7 and 31.7 without.)
 struct CountShared {
     RowShared rs;
     uint32_t wave[kCandWaves], out[4];
@@ -796,8 +798,7 @@ __device__ __forceinline__ void count_rows(const TopkArgs &p, const Ws &w, Count
     const int64_t row = blockIdx.y;
     const int tid = threadIdx.x, wave = wave_id(), lane = lane_id();
     RowInfo *info = w.info + row;
-    const bool rescue = blockIdx.x == gridDim.x - 1;
-    const int64_t sl_first = rescue ? 0 : (int64_t)blockIdx.x * kWgSlots + wave * kSPW;
+    const int64_t sl_first = (int64_t)blockIdx.x * kWgSlots + wave * kSPW;
     // everything whose address is known now
     const RowInfo ri = *info;
     constexpr int PER = kHistBins / kCandThreads;
@@ -809,7 +810,7 @@ __device__ __forceinline__ void count_rows(const TopkArgs &p, const Ws &w, Count
     uint2 c[kSPW][kPre];
 #pragma unroll
     for (int s = 0; s < kSPW; ++s) {
-        const bool active = !rescue && sl_first + s < w.nslot;
+        const bool active = sl_first + s < w.nslot;
         const int64_t slc = active ? sl_first + s : 0;
         cnt[s] = w.slot_cnt[row * w.nslot + slc];
         slot[s] = w.cand + (row * w.nslot + slc) * w.L;
@@ -851,17 +852,16 @@ __device__ __forceinline__ void count_rows(const TopkArgs &p, const Ws &w, Count
         failed = bin_a == (uint32_t)kHistBins - 1u;                    // beyond the window
         crowded = !failed && lds_out[2] > (uint32_t)kTieCap;           // too many to list: see RowInfo::tie_min
     }
-    if (rescue) {
-        if (failed) rescue_row<DIFF, UPDATE, SUMS>(rs, p, w, row, widest_warm(p.k, p.d));
-        return;
-    }
     if (blockIdx.x == 0 && tid == 0) {
         info->failed = failed ? kRowFailed : (crowded ? kRowCrowded : kRowFine);
         info->bin_a = bin_a;
         info->need_a = need_a;
         info->M = 0u;                        // consumed by the second collect pass: zero for the next call
     }
-    if (failed) return;
+    if (failed) {
+        if (blockIdx.x == 0) rescue_row<DIFF, UPDATE, SUMS>(rs, p, w, row, widest_warm(p.k, p.d));
+        return;
+    }
     uint2 *tie = w.tie + row * kTieCap;
     uint32_t key_min = 0xffffffffu, key_max = 0u;
 #pragma unroll
@@ -1007,8 +1007,8 @@ struct Emitter {
 // among equal keys): the entry that need_a - 1 others precede is the last one kept, its key is T, and q counts it
 // and the equal keys before it.  The output offset of a slot is the number of kept entries in all earlier slots:
 // their candidates above T's bin (slot_above, summed by the workgroup) plus the listed entries before the slot's
-// first position that are kept.  Grid (slot blocks + 1, n): the last workgroup of a row is a rescue, for a row
-// whose crowded bin (see RowInfo::tie_min) turned out to hold different keys.  A crowded bin of equal keys needs no
+// first position that are kept.  Grid (slot blocks, n); a row whose crowded bin (see RowInfo::tie_min) turned out to hold
+// different keys is selected by its first workgroup, by the exact algorithm.  A crowded bin of equal keys needs no
 // list: T is that key, and the ties before a slot are the earlier slots' entries of the bin (slot_inbin).
 // SUMS (Algorithm 3): the sum of the kept squares of every slot goes to w.kept.
 struct EmitShared {
@@ -1029,16 +1029,10 @@ __device__ __forceinline__ void emit_rows(const TopkArgs &p, const Ws &w, EmitSh
     const int64_t row = blockIdx.y;
     const int tid = threadIdx.x, wave = wave_id(), lane = lane_id();
     RowInfo *info = w.info + row;
-    const bool rescue = blockIdx.x == gridDim.x - 1;
-    const int64_t sl0 = rescue ? 0 : (int64_t)blockIdx.x * kWgSlots, sl_first = sl0 + wave * kSPW;
+    const int64_t sl0 = (int64_t)blockIdx.x * kWgSlots, sl_first = sl0 + wave * kSPW;
     // everything whose address is known now
     const RowInfo ri = *info;
     const bool crowded = ri.failed == kRowCrowded;
-    if (rescue) {
-        if (crowded && ri.tie_min != ri.tie_max)
-            rescue_row<DIFF, UPDATE, SUMS>(rs, p, w, row, warm_shift(p.k, p.d, kCrowdedBin, 0u));
-        return;
-    }
     const uint2 listed = w.tie[row * kTieCap + (tid < kTieCap ? tid : 0)];
     const uint32_t *slot_above = w.slot_above + row * w.nslot;
     const uint32_t *slot_inbin = w.slot_inbin + row * w.nslot;
@@ -1090,7 +1084,11 @@ __device__ __forceinline__ void emit_rows(const TopkArgs &p, const Ws &w, EmitSh
         zero_global_hist(w.hist_a + row * kHistBins, kHistBins);
         if (ri.use2 != 0u) zero_global_hist(w.hist_b + row * kHistBins, kHistBins);
     }
-    if (ri.failed == kRowFailed || (crowded && ri.tie_min != ri.tie_max)) return;     // the whole workgroup
+    if (ri.failed == kRowFailed) return;         // the whole workgroup
+    if (crowded && ri.tie_min != ri.tie_max) {
+        if (blockIdx.x == 0) rescue_row<DIFF, UPDATE, SUMS>(rs, p, w, row, warm_shift(p.k, p.d, kCrowdedBin, 0u));
+        return;
+    }
     const uint32_t ntie = crowded ? 0u : (ri.ntie < (uint32_t)kTieCap ? ri.ntie : (uint32_t)kTieCap);
     const uint32_t my_idx = listed.x, my_key = listed.y;
     if ((uint32_t)tid < ntie) {
@@ -1340,7 +1338,7 @@ hipError_t launch_topk_split_reset(void *workspace, int32_t n, int64_t d, hipStr
 
 namespace {
 dim3 cand_grid(int32_t n, const Ws &w, unsigned selections) {
-    return dim3((unsigned)((w.nslot + kCandWaves - 1) / kCandWaves) + 1, (unsigned)n, selections);   // + 1: a row's rescue
+    return dim3((unsigned)((w.nslot + kCandWaves - 1) / kCandWaves), (unsigned)n, selections);
 }
 
 // Steps loaded ahead, from the candidates to be expected in a slot (1.3 k per row after a warm start, some 1.6 k from a
