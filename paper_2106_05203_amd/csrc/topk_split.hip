@@ -1342,14 +1342,19 @@ dim3 cand_grid(int32_t n, const Ws &w, unsigned selections) {
 }
 
 // Steps loaded ahead, from the candidates to be expected in a slot (1.3 k per row after a warm start, some 1.6 k from a
-// sample): enough for all of them where that is few, and no more, since every wavefront loads them.  Measured: ef21_topk
-// n = 10, d = 10^5, k = 5000 20.1 us with four, 19.2 with two; n = 20, d = 10^6, k = 1000 31.2 and 30.1; k = 10^4
-// 34.0 with two and four, 33.8 with three; step n = 8, d = 11.2 million, k = 112000 251.7 with four, 249.5 with six.
-int cand_steps(const TopkArgs &p, const Ws &w) {
+// sample): enough for all of them where that is few, and no more, since every wavefront loads them; `most` is what the
+// kernel is compiled for.  Where a slot holds several times as many, the first load counts for less and the longer one
+// only delays it.  Measured, us: ef21_topk n = 20, d = 10^6, k = 5000 (expects 68): 31.7 with two, 31.8 three, 32.4 four, 33.8
+// six; step n = 8, d = 11.2 million, k = 60000 (157) 203, 202 and 198 with three, four and six; k = 92000 (240) 218, 217, 216;
+// Student-t 212, 210, 208; k = 138000 (361) 234, 233, 232 and 230, 229, 224; k = 160000 (419) 236, 235, 234; k = 200000 (524)
+// 250 with four, 250 with six; k = 300000 (785) 287 and 289, 280 and 283.
+int cand_steps(const TopkArgs &p, const Ws &w, int most) {
     const double expected = (p.warm > 0 ? 1.3 : 1.6) * (double)p.k * (double)w.L / (double)p.d;
-    if (expected <= 90.0) return 2;
-    if (expected <= 170.0) return 3;
-    return expected > 240.0 && expected <= 360.0 ? 6 : 4;
+    int steps = 4;
+    if (expected <= 90.0) steps = 2;
+    else if (expected <= 150.0) steps = 3;
+    else if (expected <= 450.0) steps = 6;
+    return steps < most ? steps : most;
 }
 
 // After the first collect pass: the second pass (after a warm start), count and emit.
@@ -1359,7 +1364,7 @@ hipError_t launch_after_collect(const TopkArgs &p, const Ws &w, hipStream_t stre
         launch_collect(p, w, kSecondPass, stream);
         mk(K_TOPK_REFINE);
     }
-    const int steps = cand_steps(p, w);
+    const int steps = cand_steps(p, w, 6);
     const dim3 cgrid = cand_grid(p.n, w, 1), block(kCandThreads);
 #define EF21_CAND(KERNEL, GRID, DIFF, UPD)                                                               \
     do {                                                                                                 \
@@ -1440,7 +1445,7 @@ hipError_t launch_topk_split_pair(const TopkArgs &plain, const TopkArgs &markov,
                            markov, wm);
         mk(K_TOPK_REFINE);
     }
-    const int steps = cand_steps(markov, wm);
+    const int steps = cand_steps(markov, wm, 4);
     const dim3 cgrid = cand_grid(markov.n, wm, 2);
 #define EF21_CAND(KERNEL)                                                                                \
     do {                                                                                                 \
