@@ -78,7 +78,7 @@ __global__ __launch_bounds__(kThreads) void mean_rows_vec4_kernel(const float *_
 // adds the workers' runs one after the other into its LDS accumulator (positions inside a message are
 // distinct, so a plain read-add-write is enough, and a single wavefront needs no barrier between
 // workers): the sum runs in worker order, g is bitwise reproducible, and no global atomic is issued.
-constexpr int kAggSub = 512;
+constexpr int kAggSub = 512, kAggLong = 2048;      // columns of a sub-block; see aggregate_kernel
 constexpr int kAggWaves = kThreads / kWave;
 
 __global__ __launch_bounds__(kThreads) void message_index_kernel(const int32_t *__restrict__ idx, int64_t k,
@@ -136,31 +136,41 @@ __device__ __forceinline__ void add_runs(const int32_t *__restrict__ idx, const 
 // the chip from 10^5 columns on, and a worker's run fits the 64 lanes up to a tenth of the entries kept.  (Blocks of 2048
 // without the prefetch: 18.4 us against 8.5 at d = 1000003, n = 5, k = 50000; 45.9 against 45.4 at d = 11.2 million, where
 // the 180 MB of g and x at the rate of a plain copy take 39; blocks of 2048 with it: 50.)
+// Where blocks of 2048 fill the chip as well and a run is a handful of entries, the longer blocks are the better ones: a
+// quarter as many run bounds to read here and to write in the emission.  step, us, with 512 and 2048 columns: n = 15, d = 5
+// million, k = 50000 178 and 174; n = 9, d = 4 million, k = 40000 101 and 97.5; n = 12, d = 6 million, k = 6000 138.5 and
+// 134; n = 9, d = 8 million, k = 80000 181 and 175; but n = 15, d = 2 million, k = 20000 81 and 83.4; n = 15, d = 4.2 million,
+// k = 210000 214 and 222; n = 8, d = 11.2 million, k = 112000 248 and 251 (with the copy of x that follows); n = 2, d = 40
+// million, k = 400000 330 and 338.
 // vec: g and x 16-byte aligned (a block starts at a multiple of 512 columns whatever d is); the last, partial block
 // and unaligned vectors go column by column.
-template <bool STEP>
+template <bool STEP, int SUB>
 __global__ __launch_bounds__(kThreads) void aggregate_kernel(const int32_t *__restrict__ idx,
                                                              const float *__restrict__ val,
                                                              const int32_t *__restrict__ start, int32_t n, int64_t k,
                                                              int64_t d, int64_t nblk, float *__restrict__ g,
                                                              float *__restrict__ x, float inv_n, float neg_gamma,
                                                              bool vec, bool from_zero) {
-    constexpr int kPer = kAggSub / (4 * kWave);
-    __shared__ __attribute__((aligned(16))) float lds[kAggWaves][kAggSub];
+    constexpr int kPer = SUB / (4 * kWave);
+    constexpr bool kAhead = SUB == kAggSub;
+    __shared__ __attribute__((aligned(16))) float lds[kAggWaves][SUB];
     const int wave = threadIdx.x / kWave, lane = lane_id();
     const int64_t b = (int64_t)blockIdx.x * kAggWaves + wave;
     if (b >= nblk) return;
     float *acc = lds[wave];
-    const int64_t c0 = b * kAggSub;
-    const int64_t c1 = c0 + kAggSub < d ? c0 + kAggSub : d;
-    const bool whole = vec && c0 + kAggSub <= d;
-    float4 g4[kPer], x4[kPer];
-    if (whole) {
+    const int64_t c0 = b * SUB;
+    const int64_t c1 = c0 + SUB < d ? c0 + SUB : d;
+    const bool whole = vec && c0 + SUB <= d;
+    float4 g4[kAhead ? kPer : 1], x4[kAhead ? kPer : 1];
+    auto fetch = [&](int q, float4 &gq, float4 &xq) {
+        gq = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (!from_zero) gq = *reinterpret_cast<const float4 *>(g + c0 + 4 * (q * kWave + lane));
+        if (STEP) xq = *reinterpret_cast<const float4 *>(x + c0 + 4 * (q * kWave + lane));
+    };
+    if constexpr (kAhead) {
+        if (whole) {
 #pragma unroll
-        for (int q = 0; q < kPer; ++q) {
-            g4[q] = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (!from_zero) g4[q] = *reinterpret_cast<const float4 *>(g + c0 + 4 * (q * kWave + lane));
-            if (STEP) x4[q] = *reinterpret_cast<const float4 *>(x + c0 + 4 * (q * kWave + lane));
+            for (int q = 0; q < kPer; ++q) fetch(q, g4[q], x4[q]);
         }
     }
 #pragma unroll
@@ -169,18 +179,20 @@ __global__ __launch_bounds__(kThreads) void aggregate_kernel(const int32_t *__re
     if (whole) {
 #pragma unroll
         for (int q = 0; q < kPer; ++q) {
+            float4 &gq = g4[kAhead ? q : 0], &xq = x4[kAhead ? q : 0];
+            if constexpr (!kAhead) fetch(q, gq, xq);
             const float4 a4 = *reinterpret_cast<const float4 *>(acc + 4 * (q * kWave + lane));
-            g4[q].x = fmaf(a4.x, inv_n, g4[q].x);
-            g4[q].y = fmaf(a4.y, inv_n, g4[q].y);
-            g4[q].z = fmaf(a4.z, inv_n, g4[q].z);
-            g4[q].w = fmaf(a4.w, inv_n, g4[q].w);
-            *reinterpret_cast<float4 *>(g + c0 + 4 * (q * kWave + lane)) = g4[q];
+            gq.x = fmaf(a4.x, inv_n, gq.x);
+            gq.y = fmaf(a4.y, inv_n, gq.y);
+            gq.z = fmaf(a4.z, inv_n, gq.z);
+            gq.w = fmaf(a4.w, inv_n, gq.w);
+            *reinterpret_cast<float4 *>(g + c0 + 4 * (q * kWave + lane)) = gq;
             if (STEP) {
-                x4[q].x = fmaf(neg_gamma, g4[q].x, x4[q].x);
-                x4[q].y = fmaf(neg_gamma, g4[q].y, x4[q].y);
-                x4[q].z = fmaf(neg_gamma, g4[q].z, x4[q].z);
-                x4[q].w = fmaf(neg_gamma, g4[q].w, x4[q].w);
-                *reinterpret_cast<float4 *>(x + c0 + 4 * (q * kWave + lane)) = x4[q];
+                xq.x = fmaf(neg_gamma, gq.x, xq.x);
+                xq.y = fmaf(neg_gamma, gq.y, xq.y);
+                xq.z = fmaf(neg_gamma, gq.z, xq.z);
+                xq.w = fmaf(neg_gamma, gq.w, xq.w);
+                *reinterpret_cast<float4 *>(x + c0 + 4 * (q * kWave + lane)) = xq;
             }
         }
     } else {
@@ -381,9 +393,10 @@ bool aggregate_is_small(int32_t n, int64_t k, int64_t d) {
 }  // namespace
 
 int aggregate_index_shift(int32_t n, int64_t k, int64_t d) {
-    static_assert(kManySub == 1 << 8 && kAggSub == 1 << 9, "block lengths as shifts");
+    static_assert(kManySub == 1 << 8 && kAggSub == 1 << 9 && kAggLong == 1 << 11, "block lengths as shifts");
     if (aggregate_is_small(n, k, d)) return -1;
-    return n >= kManyWorkers ? 8 : 9;
+    if (n >= kManyWorkers) return 8;
+    return d >= 4000000 && d <= 8000000 && k * 100 <= d ? 11 : 9;
 }
 
 hipError_t launch_aggregate(const int32_t *idx, const float *val, int32_t n, int64_t k, int64_t d, float *g, float *x,
@@ -412,18 +425,21 @@ hipError_t launch_aggregate(const int32_t *idx, const float *val, int32_t n, int
                                start, n, k, d, nblk, g, x, inv_n, -gamma, from_zero);
         return hipGetLastError();
     }
-    const int64_t nblk = (d + kAggSub - 1) / kAggSub;
+    const int shift = aggregate_index_shift(n, k, d);
+    const int64_t nblk = ((d - 1) >> shift) + 1;
     if (!index_ready)
         hipLaunchKernelGGL(message_index_kernel, dim3((unsigned)((k + kThreads - 1) / kThreads), (unsigned)n),
-                           dim3(kThreads), 0, stream, idx, k, nblk, kAggSub, start);
+                           dim3(kThreads), 0, stream, idx, k, nblk, 1 << shift, start);
     const dim3 grid((unsigned)((nblk + kAggWaves - 1) / kAggWaves)), block(kThreads);
     const bool vec = ((uintptr_t)g | (uintptr_t)(x ? x : g)) % 16 == 0;
-    if (x)
-        hipLaunchKernelGGL(aggregate_kernel<true>, grid, block, 0, stream, idx, val, start, n, k, d, nblk, g, x, inv_n, -gamma,
-                           vec, from_zero);
-    else
-        hipLaunchKernelGGL(aggregate_kernel<false>, grid, block, 0, stream, idx, val, start, n, k, d, nblk, g, x, inv_n, -gamma,
-                           vec, from_zero);
+#define EF21_AGG(STEP, SUB)                                                                                              \
+    hipLaunchKernelGGL((aggregate_kernel<STEP, SUB>), grid, block, 0, stream, idx, val, start, n, k, d, nblk, g, x, inv_n, \
+                       -gamma, vec, from_zero)
+    if (shift == 11 && x) EF21_AGG(true, kAggLong);
+    else if (shift == 11) EF21_AGG(false, kAggLong);
+    else if (x) EF21_AGG(true, kAggSub);
+    else EF21_AGG(false, kAggSub);
+#undef EF21_AGG
     return hipGetLastError();
 }
 

@@ -651,3 +651,35 @@ def test_step_replayed_from_a_hip_graph(gpu, case):
             torch.cuda.synchronize()
             for a, b, name in zip(got, ref, ("x", "g_i", "g", "message positions", "message values")):
                 assert torch.equal(a, b), f"replay {r}: {name} differ from the eager handle"
+
+
+# blocks of 512 and of 2048 coordinates in the aggregation pass: both sides of the limits on d and on k / d, a last block of
+# one coordinate and of all but one, both loop orders and Algorithm 4 (which writes g without reading it)
+@pytest.mark.parametrize("n,d,k", [(3, 3_999_999, 900), (3, 4_000_000, 900), (2, 4_000_769, 40_007), (2, 4_000_769, 40_009),
+                                   (9, 4_098_047, 300), (1, 8_000_000, 700), (1, 8_000_001, 700)])
+def test_aggregation_block_lengths(gpu, n, d, k):
+    torch, binding = gpu
+    print(f"aggregation blocks case n={n} d={d} k={k}", flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(d)
+    x0 = torch.randn(d, device="cuda", generator=gen)
+    g0 = torch.randn(d, device="cuda", generator=gen)
+    g_i = 0.1 * torch.randn((n, d), device="cuda", generator=gen)
+    grads = torch.randn((n, d), device="cuda", generator=gen)
+    gamma = 0.25                                                   # exact in fp32
+    for flags in (binding.ORDER_GRAD_FIRST, binding.ORDER_STEP_FIRST, binding.CLASSIC_EF):
+        with binding.EF21(n, d, k, gamma) as h:
+            h.set_state(x0, g_i, g0)
+            h.step(grads, flags)
+            x, _, g = h.get_state()
+            idx, val = h.get_messages()
+        ef = flags == binding.CLASSIC_EF
+        total = torch.zeros(d, device="cuda")
+        for i in range(n):                                         # worker order, fp32
+            total[idx[i].long()] += val[i]
+        want_g = (0.0 if ef else g0.double()) + total.double() * float(np.float32(1.0 / n))
+        # one rounding each: g is a fused multiply-add, x another one from the g that was written
+        assert ((g.double() - want_g).abs() <= 2.0 ** -24 * want_g.abs() + 1e-40).all(), flags
+        step = g0 if flags == binding.ORDER_STEP_FIRST else g
+        want_x = x0.double() - (1.0 if ef else gamma) * step.double()
+        assert ((x.double() - want_x).abs() <= 2.0 ** -24 * want_x.abs() + 1e-40).all(), flags
