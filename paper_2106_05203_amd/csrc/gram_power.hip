@@ -432,14 +432,16 @@ size_t gram_power_bytes(int32_t n, int64_t m, int64_t d, int32_t iterations) {
     const GramPlan p = gram_plan(n, m, d);
     const size_t bytes = gram_layout(n, p, nullptr, nullptr);
     if (bytes > kGramWsMax) return 0;
-    // Microseconds: forming the matrices and one iteration on them, against one iteration with A (six launches).
-    // Measured: forming 134 (n = 20, m = 2487, d = 300), 332 (2, 7500, 1000), 415 (32, 468, 1000); an iteration by
-    // gram_matvec_kernel 7.5 (10, 3000, 500), 8.7 (2, 7500, 1000), 31 (32, 468, 1000); with A 27 (4, 250, 100),
-    // 45 (15, 1000, 1000), 62 (2, 7500, 1000), 93 (32, 8000, 50).
-    const double nn = n, ld = (double)p.ld;
-    const double form = 30.0 + nn * (double)m * ld * ld / 40e6;
-    const double with_g = d <= kResidentMax ? 2.5 : 6.5 + 4.0 * (nn + 1.0) * ld * ld / 4.4e6;
-    const double with_a = 26.0 + 8.0 * nn * (double)m * (double)d / 3.5e6;
+    // Microseconds, a handle's first call: forming the matrices (with the allocation of their workspace) and one iteration
+    // on them, against one iteration with A (six launches).  Measured, forming | iteration on G | with A: n = 4, m = 250,
+    // d = 100 1 | 0.9 | 22; 20, 2487, 300 172 | 2.5 | 44; 10, 3000, 500 223 | 7.3 | 40; 2, 7500, 1000 354 | 8.7 | 50;
+    // 15, 1000, 1000 424 | 15 | 41; 32, 468, 1000 482 | 32 | 40; 32, 100, 1000 253 | 32 | 30; 1000, 20, 100 286 | 2.4 | 137.
+    const double nn = n, mm = (double)m, dd = (double)d, ld = (double)p.ld, rows = nn * mm;
+    const double form = 10.0 + 0.055 * dd + rows * ld * ld / 55e6 + 0.3e-6 * (double)bytes;
+    const double matrices = (nn + 1.0) * ld * ld * 0.92e-6;                     // read in every iteration
+    const double with_g = d <= kResidentMax ? 2.6 * (double)((n + 256) / 256) : (matrices > 8.5 ? matrices : 8.5);
+    const double sums = 512.0 / nn < mm / 8.0 ? 512.0 / nn : mm / 8.0;           // of the gradient, per worker
+    const double with_a = 22.0 + 1.1e-6 * rows * dd + 0.08 * nn + 3.5e-5 * sums * dd;
     return form + iterations * with_g < iterations * with_a ? bytes : 0;
 }
 

@@ -1,6 +1,8 @@
 """GPU parity of ef21_theory_stepsize against the oracle's exact eigenvalues: the power iteration approaches
 every smoothness constant from below, to 1e-4 where the matrix has a dominant direction and to two per cent
 on matrices without one (the gap of a random matrix's top eigenvalues is small), and the stepsize follows."""
+import time
+
 import numpy as np
 import pytest
 
@@ -175,3 +177,27 @@ def test_power_iteration_value(gpu, n, d, m):
         h.set_problem_dense(to_gpu(torch, 0.0 * A), to_gpu(torch, t), 0.0)
         _, L, L_i = h.theory_stepsize(40)
         assert L == 0.0 and not np.any(L_i)
+
+
+def test_few_iterations_on_large_matrices(gpu):
+    """32 workers, 1000 columns: forming 33 matrices of a million entries takes as long as a dozen iterations with the
+    468 rows per worker, and an iteration on them 32 us against 40, so twenty iterations run with A: 3.4 times as long as
+    five, where forming the matrices made it 4.5."""
+    torch, binding = gpu
+    n, d, m = 32, 1000, 468
+    A = torch.randn((n, m, d), device="cuda") / d ** 0.5
+    y = torch.ones((n, m), device="cuda")
+    times = {}
+    with binding.EF21(n, d, 10, 0.1) as h:
+        h.set_problem_dense(A, y, 0.1)
+        for iterations in (5, 20):
+            h.theory_stepsize(iterations)
+            best = np.inf
+            for _ in range(5):
+                torch.cuda.synchronize()
+                t0 = time.perf_counter()
+                h.theory_stepsize(iterations)
+                best = min(best, time.perf_counter() - t0)
+            times[iterations] = 1e6 * best
+    print(times, flush=True)
+    assert times[20] <= 3.9 * times[5], times
