@@ -792,32 +792,26 @@ struct CountShared {
 };
 template <bool DIFF, int UPDATE, int kPre, bool SUMS>
 __device__ __forceinline__ void count_rows(const TopkArgs &p, const Ws &w, CountShared &sh) {
-    constexpr int kSPW = 1, kWgSlots = kCandWaves;   // slots per wavefront and workgroup
     RowShared &rs = sh.rs;
     uint32_t (&lds_wave)[kCandWaves] = sh.wave, (&lds_out)[4] = sh.out;
     const int64_t row = blockIdx.y;
     const int tid = threadIdx.x, wave = wave_id(), lane = lane_id();
     RowInfo *info = w.info + row;
-    const int64_t sl_first = (int64_t)blockIdx.x * kWgSlots + wave * kSPW;
+    const int64_t slot_no = (int64_t)blockIdx.x * kCandWaves + wave;
     // everything whose address is known now
     const RowInfo ri = *info;
     constexpr int PER = kHistBins / kCandThreads;
     uint32_t h[PER];
 #pragma unroll
     for (int j = 0; j < PER; ++j) h[j] = w.hist_a[row * kHistBins + kHistBins - 1 - (tid * PER + j)];
-    uint32_t cnt[kSPW];
-    const uint2 *slot[kSPW];
-    uint2 c[kSPW][kPre];
+    uint2 c[kPre];
+    const bool active = slot_no < w.nslot;
+    const int64_t slc = active ? slot_no : 0;
+    uint32_t cnt = w.slot_cnt[row * w.nslot + slc];
+    const uint2 *slot = w.cand + (row * w.nslot + slc) * w.L;
 #pragma unroll
-    for (int s = 0; s < kSPW; ++s) {
-        const bool active = sl_first + s < w.nslot;
-        const int64_t slc = active ? sl_first + s : 0;
-        cnt[s] = w.slot_cnt[row * w.nslot + slc];
-        slot[s] = w.cand + (row * w.nslot + slc) * w.L;
-#pragma unroll
-        for (int q = 0; q < kPre; ++q) c[s][q] = slot[s][q * kWave + lane];
-        if (!active) cnt[s] = 0u;
-    }
+    for (int q = 0; q < kPre; ++q) c[q] = slot[q * kWave + lane];
+    if (!active) cnt = 0u;
 
     const bool second = ri.use2 != 0u;
     const uint32_t key_lo = second ? ri.key_lo2 : ri.key_lo, shift = second ? ri.shift2 : ri.shift;
@@ -864,38 +858,35 @@ __device__ __forceinline__ void count_rows(const TopkArgs &p, const Ws &w, Count
     }
     uint2 *tie = w.tie + row * kTieCap;
     uint32_t key_min = 0xffffffffu, key_max = 0u;
-#pragma unroll
-    for (int s = 0; s < kSPW; ++s) {
-        uint32_t above = 0, inbin = 0;
-        for (uint32_t j0 = 0; j0 < cnt[s]; j0 += kWave * kPre) {
-            if (j0 > 0) {
-#pragma unroll
-                for (int q = 0; q < kPre; ++q) {
-                    const uint32_t j = j0 + q * kWave + lane;
-                    c[s][q] = slot[s][j < cnt[s] ? j : 0u];       // clamped: no load behind a branch
-                }
-            }
+    uint32_t above = 0, inbin = 0;
+    for (uint32_t j0 = 0; j0 < cnt; j0 += kWave * kPre) {
+        if (j0 > 0) {
 #pragma unroll
             for (int q = 0; q < kPre; ++q) {
                 const uint32_t j = j0 + q * kWave + lane;
-                const uint32_t key = c[s][q].y & 0x7fffffffu;
-                const uint32_t bin = bin_of(key < key_lo ? key_lo : key, key_lo, shift);
-                above += popc64(__ballot(j < cnt[s] && bin > bin_a));
-                const bool in_bin = j < cnt[s] && bin == bin_a;
-                if (!crowded) {
-                    const uint32_t at = wave_append(in_bin, &info->ntie);
-                    if (in_bin && at < (uint32_t)kTieCap) tie[at] = make_uint2(c[s][q].x, key);
-                } else {
-                    inbin += popc64(__ballot(in_bin));
-                    key_min = in_bin && key < key_min ? key : key_min;
-                    key_max = in_bin && key > key_max ? key : key_max;
-                }
+                c[q] = slot[j < cnt ? j : 0u];           // clamped: no load behind a branch
             }
         }
-        if (lane == 0 && sl_first + s < w.nslot) {
-            w.slot_above[row * w.nslot + sl_first + s] = above;
-            if (crowded) w.slot_inbin[row * w.nslot + sl_first + s] = inbin;
+#pragma unroll
+        for (int q = 0; q < kPre; ++q) {
+            const uint32_t j = j0 + q * kWave + lane;
+            const uint32_t key = c[q].y & 0x7fffffffu;
+            const uint32_t bin = bin_of(key < key_lo ? key_lo : key, key_lo, shift);
+            above += popc64(__ballot(j < cnt && bin > bin_a));
+            const bool in_bin = j < cnt && bin == bin_a;
+            if (!crowded) {
+                const uint32_t at = wave_append(in_bin, &info->ntie);
+                if (in_bin && at < (uint32_t)kTieCap) tie[at] = make_uint2(c[q].x, key);
+            } else {
+                inbin += popc64(__ballot(in_bin));
+                key_min = in_bin && key < key_min ? key : key_min;
+                key_max = in_bin && key > key_max ? key : key_max;
+            }
         }
+    }
+    if (lane == 0 && slot_no < w.nslot) {
+        w.slot_above[row * w.nslot + slot_no] = above;
+        if (crowded) w.slot_inbin[row * w.nslot + slot_no] = inbin;
     }
     if (crowded) {
 #pragma unroll
@@ -1019,7 +1010,6 @@ struct EmitShared {
 };
 template <bool DIFF, int UPDATE, int kPre, bool SUMS>
 __device__ __forceinline__ void emit_rows(const TopkArgs &p, const Ws &w, EmitShared &sh) {
-    constexpr int kSPW = 1, kWgSlots = kCandWaves;   // slots per wavefront and workgroup
     RowShared &rs = sh.rs;
     uint32_t (&before_above)[kCandWaves] = sh.before_above, (&own_above)[kCandWaves] = sh.own_above;
     uint32_t (&before_inbin)[kCandWaves] = sh.before_inbin, (&own_inbin)[kCandWaves] = sh.own_inbin;
@@ -1029,7 +1019,7 @@ __device__ __forceinline__ void emit_rows(const TopkArgs &p, const Ws &w, EmitSh
     const int64_t row = blockIdx.y;
     const int tid = threadIdx.x, wave = wave_id(), lane = lane_id();
     RowInfo *info = w.info + row;
-    const int64_t sl0 = (int64_t)blockIdx.x * kWgSlots, sl_first = sl0 + wave * kSPW;
+    const int64_t sl0 = (int64_t)blockIdx.x * kCandWaves, slot_no = sl0 + wave;
     // everything whose address is known now
     const RowInfo ri = *info;
     const bool crowded = ri.failed == kRowCrowded;
@@ -1041,43 +1031,34 @@ __device__ __forceinline__ void emit_rows(const TopkArgs &p, const Ws &w, EmitSh
         part += slot_above[t];
         if (crowded) part_in += slot_inbin[t];
     }
-    uint32_t mine = 0, mine_in = 0, cnt[kSPW];
-    const uint2 *slot[kSPW];
-    uint2 c[kSPW][kPre];
+    uint2 c[kPre];
+    const bool active = slot_no < w.nslot;
+    const int64_t slc = active ? slot_no : 0;
+    const uint32_t mine = active ? slot_above[slc] : 0u;
+    const uint32_t mine_in = active && crowded ? slot_inbin[slc] : 0u;
+    uint32_t cnt = w.slot_cnt[row * w.nslot + slc];
+    const uint2 *slot = w.cand + (row * w.nslot + slc) * w.L;
 #pragma unroll
-    for (int s = 0; s < kSPW; ++s) {
-        const bool active = sl_first + s < w.nslot;
-        const int64_t slc = active ? sl_first + s : 0;
-        mine += active ? slot_above[slc] : 0u;
-        mine_in += active && crowded ? slot_inbin[slc] : 0u;
-        cnt[s] = w.slot_cnt[row * w.nslot + slc];
-        slot[s] = w.cand + (row * w.nslot + slc) * w.L;
-#pragma unroll
-        for (int q = 0; q < kPre; ++q) c[s][q] = slot[s][q * kWave + lane];
-        if (!active) cnt[s] = 0u;
-    }
+    for (int q = 0; q < kPre; ++q) c[q] = slot[q * kWave + lane];
+    if (!active) cnt = 0u;
     // Line 6 needs g_i at the kept positions, scattered over the row: the loads for the wavefront's first
     // candidates that can be kept (those in T's bin or above: T itself is not known yet) are issued here, with
     // everything else, instead of one step at a time between the stores of the emission.
-    float bpre[kSPW][kPre], resid[kSPW][kPre];
+    float bpre[kPre], resid[kPre];
     if constexpr (DIFF && SUMS) {
 #pragma unroll
-        for (int s = 0; s < kSPW; ++s)
-#pragma unroll
-            for (int q = 0; q < kPre; ++q)
-                resid[s][q] = w.resid ? w.resid[slot[s] - w.cand + q * kWave + lane] : INFINITY;
+        for (int q = 0; q < kPre; ++q)
+            resid[q] = w.resid ? w.resid[slot - w.cand + q * kWave + lane] : INFINITY;
     }
     if constexpr (UPDATE == kAddUpdate) {
         const uint32_t key_lo = ri.use2 != 0u ? ri.key_lo2 : ri.key_lo, shift = ri.use2 != 0u ? ri.shift2 : ri.shift;
 #pragma unroll
-        for (int s = 0; s < kSPW; ++s)
-#pragma unroll
-            for (int q = 0; q < kPre; ++q) {
-                const uint32_t key = c[s][q].y & 0x7fffffffu;
-                const bool have = (uint32_t)(q * kWave + lane) < cnt[s] &&
-                                  bin_of(key < key_lo ? key_lo : key, key_lo, shift) >= ri.bin_a;
-                bpre[s][q] = p.b[row * p.d + (have ? (int64_t)c[s][q].x : 0)];
-            }
+        for (int q = 0; q < kPre; ++q) {
+            const uint32_t key = c[q].y & 0x7fffffffu;
+            const bool have = (uint32_t)(q * kWave + lane) < cnt &&
+                              bin_of(key < key_lo ? key_lo : key, key_lo, shift) >= ri.bin_a;
+            bpre[q] = p.b[row * p.d + (have ? (int64_t)c[q].x : 0)];
+        }
     }
 
     if (blockIdx.x == 0) {                       // the histograms are consumed: zero for the next call
@@ -1121,7 +1102,7 @@ __device__ __forceinline__ void emit_rows(const TopkArgs &p, const Ws &w, EmitSh
     part = wave_sum_u32(part);
     part_in = wave_sum_u32(part_in);
     // listed entries before this wavefront's first position: kept ones above T, and ties
-    const uint32_t my_lo = (uint32_t)(sl_first * w.L);
+    const uint32_t my_lo = (uint32_t)(slot_no * w.L);
     uint32_t list_gt = 0, list_eq = 0;
     for (uint32_t j = lane; j < ntie; j += kWave) {
         const uint32_t kj = tie_key[j];
@@ -1139,39 +1120,35 @@ __device__ __forceinline__ void emit_rows(const TopkArgs &p, const Ws &w, EmitSh
         own_inbin[wave] = mine_in;
     }
     __syncthreads();
-    if (sl_first >= w.nslot) return;
+    if (slot_no >= w.nslot) return;
     uint32_t gt_run = list_gt, eq_run = list_eq;
     for (int v = 0; v < kCandWaves; ++v) {
         gt_run += before_above[v] + (v < wave ? own_above[v] : 0u);
         eq_run += before_inbin[v] + (v < wave ? own_inbin[v] : 0u);      // zero unless the bin is crowded
     }
-    Emitter<DIFF, UPDATE, SUMS> em(p, row, T, q, gt_run, eq_run, sl_first * w.L, lane);
-#pragma unroll
-    for (int s = 0; s < kSPW; ++s) {             // consecutive slots: the running offsets carry over
-        for (uint32_t j0 = 0; j0 < cnt[s]; j0 += kWave * kPre) {
-            if (j0 > 0) {
-#pragma unroll
-                for (int u = 0; u < kPre; ++u) {
-                    const uint32_t j = j0 + u * kWave + lane;
-                    c[s][u] = slot[s][j < cnt[s] ? j : 0u];      // clamped: no load behind a branch
-                    if constexpr (DIFF && SUMS)
-                        resid[s][u] = w.resid ? w.resid[slot[s] - w.cand + (j < cnt[s] ? j : 0u)] : INFINITY;
-                }
-            }
+    Emitter<DIFF, UPDATE, SUMS> em(p, row, T, q, gt_run, eq_run, slot_no * w.L, lane);
+    for (uint32_t j0 = 0; j0 < cnt; j0 += kWave * kPre) {
+        if (j0 > 0) {
 #pragma unroll
             for (int u = 0; u < kPre; ++u) {
-                if constexpr (DIFF && SUMS) em.step(j0 + u * kWave + lane < cnt[s], c[s][u], false, 0.f, resid[s][u]);
-                else if constexpr (UPDATE == kAddUpdate) em.step(j0 + u * kWave + lane < cnt[s], c[s][u], j0 == 0, bpre[s][u]);
-                else em.step(j0 + u * kWave + lane < cnt[s], c[s][u]);
+                const uint32_t j = j0 + u * kWave + lane;
+                c[u] = slot[j < cnt ? j : 0u];           // clamped: no load behind a branch
+                if constexpr (DIFF && SUMS)
+                    resid[u] = w.resid ? w.resid[slot - w.cand + (j < cnt ? j : 0u)] : INFINITY;
             }
         }
-        if constexpr (SUMS) {
-            const double sq = wave_sum_f64(em.kept_sq);
-            if (lane == 0 && sl_first + s < w.nslot) w.kept[row * w.nslot + sl_first + s] = sq;
-            em.kept_sq = 0.0;
+#pragma unroll
+        for (int u = 0; u < kPre; ++u) {
+            if constexpr (DIFF && SUMS) em.step(j0 + u * kWave + lane < cnt, c[u], false, 0.f, resid[u]);
+            else if constexpr (UPDATE == kAddUpdate) em.step(j0 + u * kWave + lane < cnt, c[u], j0 == 0, bpre[u]);
+            else em.step(j0 + u * kWave + lane < cnt, c[u]);
         }
     }
-    const int64_t span_end = (sl_first + kSPW) * w.L;
+    if constexpr (SUMS) {
+        const double sq = wave_sum_f64(em.kept_sq);
+        if (lane == 0 && slot_no < w.nslot) w.kept[row * w.nslot + slot_no] = sq;
+    }
+    const int64_t span_end = (slot_no + 1) * w.L;
     em.finish(span_end < p.d ? span_end : p.d);
 }
 
@@ -1341,6 +1318,12 @@ dim3 cand_grid(int32_t n, const Ws &w, unsigned selections) {
     return dim3((unsigned)((w.nslot + kCandWaves - 1) / kCandWaves), (unsigned)n, selections);
 }
 
+// The message index asked for, if any: a slot has to be a whole number of its blocks (see Emitter).
+bool index_fits(const TopkArgs &p, const Ws &w) {
+    return !p.agg_start || (p.agg_shift >= 0 && p.agg_shift < 31 && w.L % ((int64_t)1 << p.agg_shift) == 0 &&
+                            p.agg_nblk == ((p.d - 1) >> p.agg_shift) + 1);
+}
+
 // Steps loaded ahead, from the candidates to be expected in a slot (1.3 k per row after a warm start, some 1.6 k from a
 // sample): enough for all of them where that is few, and no more, since every wavefront loads them; `most` is what the
 // kernel is compiled for.  Where a slot holds several times as many, the first load counts for less and the longer one
@@ -1394,8 +1377,7 @@ hipError_t launch_topk_split(const TopkArgs &p, void *workspace, hipStream_t str
     w.rule = sample_rule(p.k, p.d);
     if (p.g_i && p.g_i != (p.b ? p.b : p.a)) return hipErrorInvalidValue;
     if (p.warm < 0 || p.warm > kWarmSlots) return hipErrorInvalidValue;
-    if (p.agg_start && (p.agg_shift < 0 || p.agg_shift > 11 || p.agg_nblk != ((p.d - 1) >> p.agg_shift) + 1 || p.k == 1))
-        return hipErrorInvalidValue;
+    if (!index_fits(p, w) || (p.agg_start && p.k == 1)) return hipErrorInvalidValue;
     if (p.k == 1) return launch_argmax(p, w, stream, mk);
     launch_collect(p, w, p.warm > 0 ? kWarmPass : kColdPass, stream);
     mk(K_TOPK_COLLECT);
@@ -1423,12 +1405,10 @@ hipError_t launch_topk_split_pair(const TopkArgs &plain, const TopkArgs &markov,
         markov.warm < 0 || markov.warm > kWarmSlots || (plain.warm > 0) != (markov.warm > 0) || !sums.norms ||
         !sums.kept_plain || !sums.kept_markov)
         return hipErrorInvalidValue;
-    for (const TopkArgs *p : {&plain, &markov})
-        if (p->agg_start && (p->agg_shift < 0 || p->agg_shift > 9 || p->agg_nblk != ((p->d - 1) >> p->agg_shift) + 1))
-            return hipErrorInvalidValue;
     Ws wp, wm;
     layout(plain.n, plain.d, (char *)ws_plain, &wp);
     layout(markov.n, markov.d, (char *)ws_markov, &wm);
+    if (!index_fits(plain, wp) || !index_fits(markov, wm)) return hipErrorInvalidValue;
     wp.rule = wm.rule = sample_rule(plain.k, plain.d);
     wp.kept = sums.kept_plain;
     wm.kept = sums.kept_markov;
