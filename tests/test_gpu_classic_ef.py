@@ -128,10 +128,10 @@ def test_flag_combinations_are_rejected(gpu):
 
 
 # the errors are cleared by whatever kernel emits the message: the row kernel with its two LDS copies, rows kept as key
-# prefixes, the many-workgroup path with rows of odd length, Top-1 on long rows; n >= 16: the other aggregation pass;
+# prefixes, the many-workgroup path with rows of odd length, Top-1 on long rows (more than 61440 entries); n >= 16: the other aggregation pass;
 # n k of 128 and 136 with d at the 1024 columns of the small one
 @pytest.mark.parametrize("n,d,k", [(3, 9001, 90), (2, 16383, 33), (3, 20001, 200), (3, 20001, 1500), (3, 20001, 1),
-                                   (17, 16999, 170), (2, 65_537, 2000), (16, 1024, 8), (17, 1024, 8), (16, 1025, 8)])
+                                   (3, 70_001, 1), (2, 1_000_003, 1), (17, 16999, 170), (2, 65_537, 2000), (16, 1024, 8), (17, 1024, 8), (16, 1025, 8)])
 def test_errors_are_cleared_by_every_emission(gpu, oracle, n, d, k):
     torch, binding = gpu
     print(f"EF clearing case n={n} d={d} k={k}", flush=True)

@@ -108,11 +108,15 @@ def test_dense_gradient_wide_rows(gpu, oracle, n, d, m):
         h.set_minibatch(rows)
         assert torch.equal(got, h.local_grad(to_gpu(torch, x))), "all rows in order"
         if m > 1:
-            rows[:, 0] = m                                           # contributes nothing
+            batch = np.stack([rng.permutation(m) for _ in range(n)])   # another order, and another row left out, per worker
+            left_out = batch[:, 0].copy()
+            batch[:, 0] = m                                          # contributes nothing
+            rows.copy_(torch.from_numpy(batch.astype(np.int32)))
             part = h.local_grad(to_gpu(torch, x)).cpu().numpy()
-            z = A[:, 0].astype(np.float64) @ x.astype(np.float64)
-            one = (-y[:, 0] / (1 + np.exp(y[:, 0] * z)))[:, None] * A[:, 0].astype(np.float64) / m
-            assert np.all(np.abs(part - (ref - one)) <= 1e-5 * np.abs(ref).max() + 1e-6)
+            for i in range(n):
+                a, yi = A[i, left_out[i]].astype(np.float64), float(y[i, left_out[i]])
+                one = -yi / (1 + np.exp(yi * (a @ x.astype(np.float64)))) * a / m
+                assert np.all(np.abs(part[i] - (ref[i] - one)) <= 1e-5 * np.abs(ref).max() + 1e-6), f"worker {i}"
 
 
 @pytest.mark.parametrize("n,d,m,nnz", [(3, 64, 30, 7), (4, 5000, 200, 50), (2, 50_000, 100, 500), (2, 1000, 40, 130)])
@@ -285,12 +289,13 @@ def test_dense_gradient_short_rows(gpu, oracle, n, d, m):
     x = rng.standard_normal(d).astype(np.float32)
     x64 = x.astype(np.float64)
 
-    def grads_of(rows):
+    def grads_of(rows, tau):
+        """rows: the row numbers of each worker; the sums are divided by tau."""
         out = []
         for i in range(n):
-            Ai = A[i, rows].astype(np.float64)
-            r = -y[i, rows] / (1.0 + np.exp(y[i, rows] * (Ai @ x64)))
-            out.append(Ai.T @ r / rows.size + 0.2 * x64 / (1.0 + x64 * x64) ** 2)
+            Ai = A[i, rows[i]].astype(np.float64)
+            r = -y[i, rows[i]] / (1.0 + np.exp(y[i, rows[i]] * (Ai @ x64)))
+            out.append(Ai.T @ r / tau + 0.2 * x64 / (1.0 + x64 * x64) ** 2)
         return np.stack(out)
 
     with binding.EF21(n, d, 1, 0.1) as h:
@@ -300,7 +305,7 @@ def test_dense_gradient_short_rows(gpu, oracle, n, d, m):
         h.set_problem_dense(Ag, to_gpu(torch, y), 0.1)
         got = h.local_grad(to_gpu(torch, x))
         assert torch.equal(got, h.local_grad(to_gpu(torch, x)))
-        ref = grads_of(np.arange(m))
+        ref = grads_of([np.arange(m)] * n, m)
         # additions behind a sum over rows: a group's trips and the two to eight levels that join the blocks
         depth = d / 64 + 8
         for i in range(n):
@@ -312,17 +317,20 @@ def test_dense_gradient_short_rows(gpu, oracle, n, d, m):
             idx, val = h.get_messages()
             assert torch.equal(val, got.gather(1, idx.long()))
         tau = max(1, m // 3)
-        batch = torch.from_numpy(np.stack([rng.permutation(m)[:tau] for _ in range(n)]).astype(np.int32)).cuda()
-        batch[:] = batch[0]
-        h.set_minibatch(batch)
-        ref = grads_of(batch[0].cpu().numpy())
-        got = h.local_grad(to_gpu(torch, x)).cpu().numpy()
-        rows = batch[0].cpu().numpy()
-        for i in range(n):
-            bound = 1e-5 * np.abs(ref[i]) + gradient_rounding_floor(A[i][rows], y[i][rows], x, depth, 16)
-            assert np.all(np.abs(got[i] - ref[i]) <= bound)
-        batch[:, 0] = -1
-        assert torch.isfinite(h.local_grad(to_gpu(torch, x))).all()
+        batch = np.stack([rng.permutation(m)[:tau] for _ in range(n)]).astype(np.int32)
+        out_of_range = (np.arange(n), rng.integers(tau, size=n))          # one place per worker
+        for wrong in (None, -1, m, 2 ** 31 - 1):
+            rows = [batch[i] for i in range(n)]
+            if wrong is not None:
+                given = batch.copy()
+                given[out_of_range] = wrong
+                rows = [np.delete(batch[i], out_of_range[1][i]) for i in range(n)]
+            h.set_minibatch(to_gpu(torch, batch if wrong is None else given, np.int32))
+            ref = grads_of(rows, tau)
+            got = h.local_grad(to_gpu(torch, x)).cpu().numpy()
+            for i in range(n):
+                bound = 1e-5 * np.abs(ref[i]) + gradient_rounding_floor(A[i][batch[i]], y[i][batch[i]], x, depth, 16)
+                assert np.all(np.abs(got[i] - ref[i]) <= bound), f"worker {i}, entry {wrong}"
 
 
 # one segment group per wavefront and four (192 workgroups and more), rows and columns past the last group

@@ -179,6 +179,28 @@ def test_power_iteration_value(gpu, n, d, m):
         assert L == 0.0 and not np.any(L_i)
 
 
+# more iterations than one launch of the resident kernel runs (4096): it goes on from the vectors the launch before left.
+# Two close eigenvalues, so that the last thousand iterations still move the value
+@pytest.mark.parametrize("d", [40, 300])
+def test_power_iteration_goes_on_over_launches(gpu, d):
+    torch, binding = gpu
+    n, m = 2, d
+    A = np.zeros((n, m, d), np.float32)
+    for i in range(n):                                    # A_i^T A_i / m diagonal, eigenvalues 1, 0.9998, and small ones
+        scale = np.full(d, 0.05, np.float32)
+        scale[1 + i], scale[7 + i] = 1.0, 0.9999
+        A[i][np.arange(d), np.arange(d)] = np.sqrt(np.float32(m)) * scale
+    y = np.zeros((n, m), np.float32)
+    with binding.EF21(n, d, 1, 0.1) as h:
+        h.set_problem_dense(to_gpu(torch, A), to_gpu(torch, y), 0.0)
+        for steps in (4096, 4097, 5000, 8300):
+            _, L, L_i = h.theory_stepsize(steps)
+            got = 4.0 * np.array(list(L_i) + [L])
+            want = power_values(A, steps)
+            # fp32 entries of G, fp64 everywhere else: as in test_power_iteration_value
+            np.testing.assert_allclose(got, want, rtol=1e-6, err_msg=f"{steps} steps")
+
+
 def test_few_iterations_on_large_matrices(gpu):
     """32 workers, 1000 columns: forming 33 matrices of a million entries takes as long as a dozen iterations with the
     468 rows per worker, and an iteration on them 32 us against 40, so twenty iterations run with A: 3.4 times as long as
