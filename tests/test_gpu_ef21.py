@@ -683,3 +683,53 @@ def test_aggregation_block_lengths(gpu, n, d, k):
         step = g0 if flags == binding.ORDER_STEP_FIRST else g
         want_x = x0.double() - (1.0 if ef else gamma) * step.double()
         assert ((x.double() - want_x).abs() <= 2.0 ** -24 * want_x.abs() + 1e-40).all(), flags
+
+
+# messages of one or a few entries on rows of many blocks, whose index is built by the aggregation: entries in the first
+# and the last coordinate, on block boundaries, all in one block; as many workers as take either pass; and Top-1 of a long
+# row takes no longer than Top-2, whose index comes out of the Top-k
+@pytest.mark.parametrize("n,d,k,where", [(2, 10_000_000, 1, [0]), (2, 10_000_001, 1, [10_000_000]), (17, 700_001, 1, [255]),
+                                         (3, 20_481, 1, [511]), (3, 16_000, 3, [512, 1024, 15_999]), (40, 16_000, 2, [0, 256]),
+                                         (2, 61_000, 15, list(range(1024, 1039)))])
+def test_few_entries_on_many_blocks(gpu, n, d, k, where):
+    torch, binding = gpu
+    print(f"few entries case n={n} d={d} k={k}", flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(d)
+    x0 = torch.randn(d, device="cuda", generator=gen)
+    g0 = torch.randn(d, device="cuda", generator=gen)
+    for flags in (binding.ORDER_GRAD_FIRST, binding.CLASSIC_EF):
+        grads = torch.randn((n, d), device="cuda", generator=gen)  # below 6 in magnitude
+        for i in range(n):                                         # every worker its own places: a block apart
+            at = (torch.tensor(where, device="cuda") + 512 * i * (i % 3)) % d
+            grads[i, at] = 8.0 + torch.arange(k, device="cuda") + i
+        ef = flags == binding.CLASSIC_EF
+        with binding.EF21(n, d, k, 1.0) as h:
+            h.set_state(x0, torch.zeros((n, d), device="cuda"), g0)
+            h.step(grads, flags)
+            x, _, g = h.get_state()
+            idx, val = h.get_messages()
+            assert (val >= 8.0).all()
+            total = torch.zeros(d, device="cuda")
+            for i in range(n):
+                total[idx[i].long()] += val[i]
+            want_g = (0.0 if ef else g0.double()) + total.double() * float(np.float32(1.0 / n))
+            assert ((g.double() - want_g).abs() <= 2.0 ** -24 * want_g.abs() + 1e-40).all(), flags
+            want_x = x0.double() - g.double()
+            assert ((x.double() - want_x).abs() <= 2.0 ** -24 * want_x.abs() + 1e-40).all(), flags
+    if k == 1 and d > 1_000_000:
+        times = {}
+        for kept in (1, 2):
+            with binding.EF21(n, d, kept, 1.0) as h:
+                h.step(grads)
+                best = np.inf
+                for _ in range(6):
+                    a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+                    a.record()
+                    h.step(grads)
+                    b.record()
+                    torch.cuda.synchronize()
+                    best = min(best, 1e3 * a.elapsed_time(b))
+                times[kept] = best
+        print(f"  {times}", flush=True)
+        assert times[1] <= 1.5 * times[2] + 20.0, times
