@@ -384,6 +384,27 @@ size_t plus_long_layout(int32_t n, int64_t d, void *scratch, PlusLong *out) {
     return off;
 }
 
+namespace {
+// Line 8 in two kernels: rows whose worker chose the plain compressor are cleared, the chosen pairs applied.
+void launch_apply_rows(const int32_t *branch, float *g_i, int32_t n, int64_t d, int64_t k, const int32_t *idx_b,
+                       const float *val_b, const int32_t *idx_m, const float *val_m, int32_t *msg_idx, float *msg_val,
+                       hipStream_t stream) {
+    const dim3 grid((unsigned)chunks_of(d), (unsigned)n);
+    if (d % 4 == 0 && (uintptr_t)g_i % 16 == 0)      // kNormChunk is a multiple of four: every chunk is whole float4s
+        hipLaunchKernelGGL(plus_clear_kernel<4>, grid, dim3(kThreads), 0, stream, branch, g_i, d);
+    else
+        hipLaunchKernelGGL(plus_clear_kernel<1>, grid, dim3(kThreads), 0, stream, branch, g_i, d);
+    int64_t blocks = (k + kThreads - 1) / kThreads;
+    if (blocks > 256) blocks = 256;
+    hipLaunchKernelGGL(plus_apply_kernel, dim3((unsigned)blocks, (unsigned)n), dim3(kThreads), 0, stream, branch,
+                       idx_b, val_b, idx_m, val_m, k, msg_idx, msg_val, g_i, d);
+}
+}  // namespace
+
+// Many workers and few blocks of coordinates: plus_apply_long_kernel takes a wavefront per block and worker after worker,
+// so line 8 goes over the rows instead, and lines 10 and 3 are kernels of their own.  step, us, by coordinates and by rows:
+// 20 x 60000 41 and 43; 32 x 60000 48 and 46; 32 x 250000 66 and 69; 64 x 100000 81 and 67; 100 x 250000 126 and 130;
+// 200 x 60000 149 and 92; 1000 x 17000 598 and 285.
 hipError_t launch_plus_long(const PlusLong &pl, PlusLongArgs a, double *BM, float gamma, hipStream_t stream) {
     if (((uintptr_t)a.g | (uintptr_t)(a.x ? a.x : a.g)) % 16 != 0) return hipErrorInvalidValue;
     a.start_b = pl.start_plain;
@@ -391,6 +412,12 @@ hipError_t launch_plus_long(const PlusLong &pl, PlusLongArgs a, double *BM, floa
     a.nblk = pl.nblk;
     hipLaunchKernelGGL(plus_decide_long_kernel, dim3((unsigned)a.n), dim3(kThreads), 0, stream, (const double2 *)pl.norms,
                        pl.kept_plain, pl.kept_markov, topk_split_slots(a.n, a.d), a.branch, BM);
+    if (a.n >= 32 && a.d <= 200000) {
+        launch_apply_rows(a.branch, a.g_i, a.n, a.d, a.k, a.idx_b, a.val_b, a.idx_m, a.val_m, a.msg_idx, a.msg_val, stream);
+        hipError_t st = launch_mean_rows(a.g_i, a.g, a.n, a.d, stream);
+        if (st == hipSuccess && a.x) st = launch_model_step(a.x, a.g, a.d, gamma, stream);
+        return st;
+    }
     const dim3 grid((unsigned)((a.nblk + kWaves - 1) / kWaves)), block(kThreads);
     if (a.x) hipLaunchKernelGGL(plus_apply_long_kernel<true>, grid, block, 0, stream, a, -gamma);
     else hipLaunchKernelGGL(plus_apply_long_kernel<false>, grid, block, 0, stream, a, -gamma);
@@ -418,16 +445,7 @@ hipError_t launch_plus_choose(const float *s, float *g_i, int32_t n, int64_t d, 
                            d, val_b, idx_m, k, kept);
     hipLaunchKernelGGL(plus_decide_kernel, dim3((unsigned)n), dim3(kThreads), 0, stream, part, chunks, kept, kblocks, s,
                        g_i, d, val_b, idx_m, k, branch, BM);
-    if (vec4)
-        hipLaunchKernelGGL(plus_clear_kernel<4>, dim3((unsigned)chunks, (unsigned)n), dim3(kThreads), 0, stream,
-                           branch, g_i, d);
-    else
-        hipLaunchKernelGGL(plus_clear_kernel<1>, dim3((unsigned)chunks, (unsigned)n), dim3(kThreads), 0, stream,
-                           branch, g_i, d);
-    int64_t blocks = (k + kThreads - 1) / kThreads;
-    if (blocks > 256) blocks = 256;
-    hipLaunchKernelGGL(plus_apply_kernel, dim3((unsigned)blocks, (unsigned)n), dim3(kThreads), 0, stream, branch,
-                       idx_b, val_b, idx_m, val_m, k, msg_idx, msg_val, g_i, d);
+    launch_apply_rows(branch, g_i, n, d, k, idx_b, val_b, idx_m, val_m, msg_idx, msg_val, stream);
     return hipGetLastError();
 }
 

@@ -234,3 +234,31 @@ def test_top_1(gpu, oracle, n, d, order):
             h.step(to_gpu(torch, grads), flags)
             compare_plus_step(torch, h, st, choice, x_before, gamma, f"step {t}")
             h.set_state(to_gpu(torch, st.x), to_gpu(torch, st.g_i), to_gpu(torch, st.g))
+
+
+# long rows of many workers: lines 8, 10 and 3 over the rows (32 workers and more, up to 200000 columns) and over the
+# coordinates, in both loop orders; every third worker's gradient is one that the plain compressor keeps better
+@pytest.mark.parametrize("order", ["grad_first", "step_first"])
+@pytest.mark.parametrize("n,d,k", [(31, 16_401, 150), (32, 16_401, 150), (32, 16_404, 2), (70, 17_000, 170), (32, 200_000, 700),
+                                   (66, 200_001, 300)])
+def test_many_workers_on_long_rows(gpu, oracle, n, d, k, order):
+    torch, binding = gpu
+    print(f"EF21+ many workers case n={n} d={d} k={k} {order}", flush=True)
+    rng = np.random.default_rng(d + n)
+    gamma = 0.25
+    x0 = rng.standard_normal(d).astype(np.float32)
+    g_i0 = rng.standard_normal((n, d)).astype(np.float32)
+    g0 = g_i0.astype(np.float64).mean(axis=0).astype(np.float32)
+    st = oracle.EF21State(x0.astype(np.float64), g_i0.astype(np.float64), g0.astype(np.float64))
+    flags = binding.PLUS | (binding.ORDER_STEP_FIRST if order == "step_first" else binding.ORDER_GRAD_FIRST)
+    with binding.EF21(n, d, k, gamma) as h:
+        h.set_state(to_gpu(torch, x0), to_gpu(torch, g_i0), to_gpu(torch, g0))
+        for t in range(2):
+            grads = (st.g_i + 0.1 * rng.standard_normal((n, d))).astype(np.float32)
+            grads[t::3] = 0.01 * rng.standard_normal(grads[t::3].shape)
+            x_before = st.x.copy()
+            choice = oracle.iteration_plus(st, grads.astype(np.float64), k, gamma, order=order)
+            assert 0 < np.count_nonzero(choice[0]) < n
+            h.step(to_gpu(torch, grads), flags)
+            compare_plus_step(torch, h, st, choice, x_before, gamma, f"step {t}")
+            h.set_state(to_gpu(torch, st.x), to_gpu(torch, st.g_i), to_gpu(torch, st.g))
