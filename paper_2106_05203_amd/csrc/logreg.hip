@@ -136,12 +136,16 @@ __global__ __launch_bounds__(kWideThreads) void logreg_dense_wide_kernel(const f
     int buf = 0, unfolded = 0;
     for (int64_t l = l0; l < l1; l += R, buf ^= 1) {
         load(l + R, next, y_next, live_next);
+        if (BATCH || l + R > l1) {                             // (an infinity there times a zero coefficient would be NaN)
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-            if (!live[r]) {                                    // uniform; an infinity there times a zero coefficient is NaN
+            for (int r = 0; r < R; ++r) {
+                if (live[r]) continue;                         // uniform
 #pragma unroll
                 for (int q = 0; q < NQ; ++q) av[r][q] = make_float4(0.f, 0.f, 0.f, 0.f);
             }
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
             float s = 0.f;
 #pragma unroll
             for (int q = 0; q < NQ; ++q) {
