@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace ef21 {
 
 // The row blocks are added in fp64 in eight interleaved chains (block b into chain b mod 8, ascending), so that several
@@ -34,17 +36,21 @@ __device__ __forceinline__ float dense_grad_entry(const float *__restrict__ part
 #pragma unroll
         for (int u = 0; u < 16; ++u) s[u % 8] += (double)p[u];
     }
-    if (b < chunks) {                                   // up to fifteen left; past the end: the last block, not added
-        float p[16];
+    auto rest = [&](auto count) {                       // up to `count` left; past the end: the last block, not added
+        constexpr int kCount = decltype(count)::value;
+        float p[kCount];
 #pragma unroll
-        for (int u = 0; u < 16; ++u) {
+        for (int u = 0; u < kCount; ++u) {
             const float *block = part_w + (b + u < chunks ? b + u : chunks - 1) * d;
             p[u] = block[(uint32_t)c];
         }
 #pragma unroll
-        for (int u = 0; u < 16; ++u)
+        for (int u = 0; u < kCount; ++u)
             if (b + u < chunks) s[u % 8] += (double)p[u];
-    }
+    };
+    if (b + 4 < chunks) rest(std::integral_constant<int, 16>());
+    else if (b + 1 < chunks) rest(std::integral_constant<int, 4>());
+    else if (b < chunks) rest(std::integral_constant<int, 1>());
     return dense_grad_of_sum(dense_chains(s), x_c, m, lambda);
 }
 

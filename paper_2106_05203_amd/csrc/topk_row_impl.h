@@ -11,6 +11,8 @@
 // emission then writes every entry with key > T and the first q entries with key == T, in
 // ascending position order (ties go to the lower index).
 #pragma once
+#include <type_traits>
+
 #include "device_utils.h"
 #include "kernels.h"
 #include "logreg_finish.h"
@@ -249,18 +251,25 @@ __device__ void row_topk_cached(RowShared &s, float *cache, const TopkArgs &p, i
     const int64_t d = p.d;
     const float *a = p.a + row * d;
     const float *b = DIFF ? p.b + row * d : nullptr;
-    constexpr int kInFlight = 8;
-    for (int64_t e0 = threadIdx.x; e0 < d; e0 += kInFlight * kRowThreads) {
-        float v[kInFlight];
+    // loads in flight per thread: no more than the row has
+    auto fill = [&](auto in_flight) {
+        constexpr int kInFlight = decltype(in_flight)::value;
+        for (int64_t e0 = threadIdx.x; e0 < d; e0 += kInFlight * kRowThreads) {
+            float v[kInFlight];
 #pragma unroll
-        for (int u = 0; u < kInFlight; ++u) {         // past the end: the last entry, not kept
-            const int64_t e = e0 + u * kRowThreads;
-            v[u] = load_v<DIFF>(a, b, e < d ? e : d - 1);
+            for (int u = 0; u < kInFlight; ++u) {         // past the end: the last entry, not kept
+                const int64_t e = e0 + u * kRowThreads;
+                v[u] = load_v<DIFF>(a, b, e < d ? e : d - 1);
+            }
+#pragma unroll
+            for (int u = 0; u < kInFlight; ++u)
+                if (e0 + u * kRowThreads < d) cache[e0 + u * kRowThreads] = v[u];
         }
-#pragma unroll
-        for (int u = 0; u < kInFlight; ++u)
-            if (e0 + u * kRowThreads < d) cache[e0 + u * kRowThreads] = v[u];
-    }
+    };
+    if (d <= kRowThreads) fill(std::integral_constant<int, 1>());
+    else if (d <= 2 * kRowThreads) fill(std::integral_constant<int, 2>());
+    else if (d <= 4 * kRowThreads) fill(std::integral_constant<int, 4>());
+    else fill(std::integral_constant<int, 8>());
     __syncthreads();
     row_topk_on<UPDATE>(
         s, p, row, [=](int64_t e) { return cache[e]; }, [=](int64_t e) { return DIFF ? b[e] : 0.f; });
@@ -275,7 +284,11 @@ __device__ void row_topk_parts(RowShared &s, float *cache, const TopkArgs &p, in
     // short rows: several threads per column (the sums of 32 blocks by one thread each took 2 us of the kernel's 5.6)
     auto put = [&](int c, float g) { cache[c] = g - b[c]; };
     double *lds = reinterpret_cast<double *>(s.hist);               // 16 KB, not yet in use
-    if (d <= 128) {
+    if (p.parts.chunks <= 4) {                            // few sums: a barrier costs more than it saves
+        for (int64_t e = threadIdx.x; e < d; e += kRowThreads)
+            put((int)e, dense_grad_entry(part_w, p.parts.chunks, d, e, p.parts.x[e], p.parts.m, p.parts.lambda));
+        __syncthreads();
+    } else if (d <= 128) {
         dense_grad_shared<kRowThreads, 128>(part_w, p.parts.chunks, d, p.parts.x, p.parts.m, p.parts.lambda, lds, put);
     } else if (d <= 256) {
         dense_grad_shared<kRowThreads, 256>(part_w, p.parts.chunks, d, p.parts.x, p.parts.m, p.parts.lambda, lds, put);
