@@ -164,9 +164,13 @@ int ef21_set_minibatch(ef21_handle h, const int32_t *rows, int64_t tau);
  * unit vector v of the last step approaches lambda_max from below, so few iterations give a stepsize that is
  * too large by the same factor: 100 to 300 steps bring problems without a dominant direction within about one
  * per cent.  gamma, L, L_i [n]: host memory, each may be NULL.  Uses the handle's loss, lambda and k, and all
- * rows whatever ef21_set_minibatch says; the handle's stepsize is not changed.  The first call on a handle
- * allocates (n + 2) d floats that the handle keeps; every call overwrites the handle's gradient buffer and
- * returns after the stream has drained.
+ * rows whatever ef21_set_minibatch says; the handle's stepsize is not changed.  Returns after the stream has drained.
+ * A dense problem with d <= 1024 columns is iterated on the workers' Gram matrices where that is the faster way (it is from
+ * some ten iterations on, usually); a call that needs more than the handle has allocates a workspace of
+ * 4 (n + 1) d'^2 + 4 n c d' (d' + 32) bytes (d' = d rounded up to 32, c pieces of a worker's rows, one or as many as make
+ * a thousand tiles in all), never more than 1 GiB, which the handle keeps until ef21_destroy.
+ * Where that much is not to be had, and for all other problems, a call iterates with the problem itself: the first one
+ * on a handle allocates (n + 2) d floats that the handle keeps, and every one overwrites the handle's gradient buffer.
  * EF21_ESTATE without a problem; EF21_EINVAL: iterations outside [1, 10^6]; EF21_ENOMEM.
  */
 int ef21_theory_stepsize(ef21_handle h, int32_t iterations, double *gamma, double *L, double *L_i);
@@ -205,9 +209,10 @@ int ef21_local_grad(ef21_handle h, const float *x, float *out_grad);
  * With EF21_ONE_LAUNCH in flags, a small dense problem (grads NULL, d <= 1024, n * k <= 2048,
  * n * m * d <= 2^24, no minibatch, no EF21_PLUS) runs the whole pass as ONE kernel: the same arithmetic in the
  * same order as the separate gradient, Top-k and aggregation kernels, so the results are the same bits.  It
- * saves two launches and pays for them in device-scope fences: measured on par with the separate kernels for
- * a handful of workers and slower for twenty, hence not the default.  Where the problem does not qualify the
- * flag changes nothing.
+ * saves two launches and pays for them in device-scope fences: measured within ten per cent of the separate kernels
+ * either way for two to four workers with a few hundred rows of 100 columns (n = 4, m = 250, d = 100: 12.0 us against 11 to
+ * 15, the more the slower the host launches) and slower for larger problems and more workers (n = 20, m = 1628,
+ * d = 123: 21.7 against 15), hence not the default.  Where the problem does not qualify the flag changes nothing.
  * EF21_EINVAL: unknown flag bits, or EF21_CLASSIC_EF together with an order or EF21_PLUS.
  */
 int ef21_step(ef21_handle h, const float *grads, uint32_t flags);
@@ -219,7 +224,9 @@ int ef21_step(ef21_handle h, const float *grads, uint32_t flags);
  * M = ||m - s||^2 (line 7) are computed in fp64 as ||s||^2 and ||s - g_i||^2 minus the sums of the kept
  * squares, every sum in a fixed order; g_i <- m if M <= B, else b (line 8); g <- (1/n) sum_i g_i, the
  * rows added in worker order in fp64 and the mean rounded once (line 10).  ef21_get_messages then returns, per worker, the k pairs
- * of the compressor it chose.  The first such call on a handle allocates (and waits for the stream).
+ * of the compressor it chose.  The first such call on a handle allocates (and waits for the stream): 16 n k bytes for
+ * the two selections, and for rows of 16384 entries or more with k > 1 a second Top-k workspace (about 8 d + 90 000 bytes
+ * per row, as the handle's first) and, where there is room for it, 4 n d bytes more (without them the step is slower).
  *
  * ef21_get_choices copies out what the last EF21_PLUS step decided: branch [n] int32 (1 = the plain
  * compressor b was chosen, 0 = the Markov compressor m) and distortions [n][2] fp64 (B_i, M_i); either

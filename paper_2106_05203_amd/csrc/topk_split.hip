@@ -144,9 +144,9 @@ struct Ws {
 size_t align256(size_t b) { return (b + 255) / 256 * 256; }
 
 void plan(int32_t n, int64_t d, Ws *w) {
-    // One 1024-thread workgroup per compute unit.  (Two, resident together or one after the other: n = 15,
-    // d = 5 million 155 and 149 us a step against 148; ef21_topk of 10 rows of 7 million 69 and 72 against 64; shorter
-    // inputs lose more, each workgroup repeats the sampling prologue.)
+    // One 1024-thread workgroup per compute unit.  (Two, one step of loads ahead each or two, us a step: n = 15, d = 5
+    // million, k = 5000 147 and 145 against 136; n = 8, d = 11.2 million, k = 112000 225 and 222 against 212; ef21_topk of 10 rows
+    // of 7 million 69 and 72 against 64; shorter inputs lose more, each workgroup repeats the sampling prologue.)
     int64_t max_g = 256 / n;
     if (max_g < 1) max_g = 1;
     if (max_g > kMaxSlots / kBlkWaves) max_g = kMaxSlots / kBlkWaves;
