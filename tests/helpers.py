@@ -21,6 +21,21 @@ def sampled_positions(d):
     return np.concatenate([(p * (d - 64)) // 63 + np.arange(64) for p in range(64)])
 
 
+def best_time(torch, call, calls=10, repeats=6):
+    """Microseconds of one call: the shortest of a few runs of `calls` calls back to back (so that the host, which
+    launches ahead, does not count unless it is the slower one)."""
+    best = np.inf
+    for _ in range(repeats):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        for _ in range(calls):
+            call()
+        b.record()
+        torch.cuda.synchronize()
+        best = min(best, 1e3 * a.elapsed_time(b) / calls)
+    return best
+
+
 def same_bits(a, b):
     """Bitwise equality of two float32 arrays (so -0.0 != +0.0 and equal NaNs compare equal)."""
     a = np.ascontiguousarray(a, dtype=np.float32)

@@ -7,7 +7,7 @@ in fp32 in worker order, the oracle in fp64); f(x^t) within 1e-4 relative over a
 import numpy as np
 import pytest
 
-from helpers import RoundingBudget, close_per_coordinate, same_bits, sampled_positions
+from helpers import RoundingBudget, best_time, close_per_coordinate, same_bits, sampled_positions
 from paper_2106_05203_amd import workloads
 
 pytestmark = pytest.mark.gpu
@@ -722,14 +722,6 @@ def test_few_entries_on_many_blocks(gpu, n, d, k, where):
         for kept in (1, 2):
             with binding.EF21(n, d, kept, 1.0) as h:
                 h.step(grads)
-                best = np.inf
-                for _ in range(6):
-                    a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-                    a.record()
-                    h.step(grads)
-                    b.record()
-                    torch.cuda.synchronize()
-                    best = min(best, 1e3 * a.elapsed_time(b))
-                times[kept] = best
+                times[kept] = best_time(torch, lambda: h.step(grads))
         print(f"  {times}", flush=True)
         assert times[1] <= 1.5 * times[2] + 20.0, times
