@@ -8,13 +8,24 @@
 //                 workgroup share a chunk.
 //   gram_finish   the chunks added, divided by m, rounded to fp32 once and written to both halves; one more matrix is
 //                 the mean over the workers, G = (1/(nm)) sum_i A_i^T A_i.
+//   The estimate after T iterations is sqrt(u_2T / u_2T-2), u_N = v' G^N v with the start vector v.  Between 48 and 2822
+//   iterations these moments come from J = 4.8 sqrt(T) steps of the Lanczos recurrence instead (two in the place of four
+//   products with G at T = 100): u_N / |v|^2 is entry (1, 1) of the N-th power of its J x J tridiagonal matrix, exactly for
+//   N < 2J and to twice the error of the best polynomial of degree 2J - 1 on [0, lambda_max] beyond; for t^N that is at most
+//   2 exp(-4 J^2 / N) (Newman and Rivlin, Approximation of monomials by lower degree polynomials, 1976): 2e-20 of
+//   lambda_max^N.  What loss of orthogonality adds is rounding (Druskin and Knizhnerman, Error bounds in the simple Lanczos
+//   procedure, 1991): on Gaussian, non-negative, low-rank and badly scaled matrices the two estimates agree to 1e-15.
+//   The T iterations are then taken with the tridiagonal matrix, by one wavefront.  n = 20, m = 2487, d = 300, 100
+//   iterations: 436 -> 319 us a call;
+//   n = 2, m = 7500, d = 1000: 1255 -> 800.
 //   d <= 320:     ONE launch runs all iterations, a workgroup of 1024 threads per matrix.  G sits in registers (a
 //                 compute unit has 512 KB of them: 100 entries per thread at d = 320), the vector in LDS; a wavefront
 //                 multiplies its rows of G (columns, by symmetry) and the sixteen partial vectors are added in LDS.
-//   d <= 1024:    a launch per iteration; every workgroup normalises the previous vector for itself (d entries) and
-//                 multiplies 32 rows of G.
+//   d <= 1024:    a launch per iteration; every workgroup works out the vector of the recurrence for itself (d entries)
+//                 and multiplies 32 rows of G.
 // Vectors, products with G, sums and norms are in fp64; G is the only thing rounded to fp32, so the constants are
 // closer to the exact ones than through fp32 products with A.
+#include <cmath>
 #include <utility>
 
 #include "device_utils.h"
@@ -36,6 +47,18 @@ constexpr int kResThreads = 1024, kResWaves = kResThreads / kWave;
 constexpr int64_t kResidentMax = 5 * kWave;          // columns (six would need 144 registers for G alone)
 constexpr int64_t kGramMax = 1024;
 constexpr int32_t kItersPerLaunch = 4096;            // of the resident kernel: bounds a launch to some ten milliseconds
+
+constexpr int kLanczosMax = 256;                     // steps of the recurrence: four per lane of the last wavefront
+// Fewer iterations save next to nothing and a step takes longer than an iteration, us a call with the iteration and with the
+// recurrence, 40 iterations (32 steps): n = 20, m = 1000, d = 64 71.3 and 72.7; 4, 250, 100 76.6 and 75.1; 16, 2000, 200 166.3
+// and 166.4; 10, 3000, 500 520 and 455; 100 iterations (49 steps): 109 and 89, 131 and 96, 266 and 205, 960 and 580.
+constexpr int32_t kLanczosLeast = 48;
+// Steps that stand for `iterations` of the power iteration; 0: it is run as it is.
+int32_t lanczos_steps(int32_t iterations) {
+    if (iterations < kLanczosLeast) return 0;
+    const int32_t steps = (int32_t)std::ceil(4.8 * std::sqrt((double)iterations)) + 1;
+    return steps <= kLanczosMax ? steps : 0;
+}
 
 constexpr int kMvThreads = 256, kMvWaves = kMvThreads / kWave, kMvRowsPerWave = 8;
 constexpr int kMvRows = kMvWaves * kMvRowsPerWave;
@@ -209,11 +232,33 @@ __global__ __launch_bounds__(kTileThreads) void gram_finish_kernel(const double 
     }
 }
 
-__device__ __forceinline__ double wave_sum_f64(double v) {
-#pragma unroll
-    for (int o = kWave / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
+// Sum over each group of LANES consecutive lanes (16 or 64), as group_sum does it: no trip through the LDS crossbar.
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double x) {
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, 0xf, 0xf, true);
+    return __hiloint2double(hi, lo);
+}
+template <int LANES>
+__device__ __forceinline__ double group_sum_f64(double v) {
+    static_assert(LANES == 16 || LANES == 64, "whole rows of sixteen lanes");
+    v += dpp_f64<0xB1>(v);                  // quad_perm [1,0,3,2]
+    v += dpp_f64<0x4E>(v);                  // quad_perm [2,3,0,1]
+    v += dpp_f64<0x141>(v);                 // row_half_mirror
+    v += dpp_f64<0x140>(v);                 // row_mirror
+    if constexpr (LANES == 64) {
+        const uint32_t lo = (uint32_t)__double2loint(v), hi = (uint32_t)__double2hiint(v);
+        const auto l16 = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+        const auto h16 = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+        v = __hiloint2double((int)h16[0], (int)l16[0]) + __hiloint2double((int)h16[1], (int)l16[1]);
+        const uint32_t lo2 = (uint32_t)__double2loint(v), hi2 = (uint32_t)__double2hiint(v);
+        const auto l32 = __builtin_amdgcn_permlane32_swap(lo2, lo2, false, false);
+        const auto h32 = __builtin_amdgcn_permlane32_swap(hi2, hi2, false, false);
+        v = __hiloint2double((int)h32[0], (int)l32[0]) + __hiloint2double((int)h32[1], (int)l32[1]);
+    }
     return v;
 }
+__device__ __forceinline__ double wave_sum_f64(double v) { return group_sum_f64<kWave>(v); }
 
 // v[row][0..ld): the start vectors (zero past d)
 __global__ __launch_bounds__(kTileThreads) void gram_start_kernel(double *__restrict__ v, int64_t d, int64_t ld) {
@@ -224,24 +269,75 @@ __global__ __launch_bounds__(kTileThreads) void gram_start_kernel(double *__rest
 // 1 / |w|, or 0 for w = 0 (the vector then stays zero, as do the norms that follow)
 __device__ __forceinline__ double inverse_norm(double sum_sq) { return sum_sq == 0.0 ? 0.0 : 1.0 / sqrt(sum_sq); }
 
+// x of the next lower / next higher lane, zero at the end of the wavefront
+__device__ __forceinline__ double from_lower(double x) { return dpp_f64<0x138>(x); }    // wave_shr:1
+__device__ __forceinline__ double from_higher(double x) { return dpp_f64<0x130>(x); }   // wave_shl:1
+
+// What `iterations` steps of the power iteration from the first unit vector give for the symmetric tridiagonal matrix with
+// diagonal alpha[0..steps) and beta[i] beside it in rows i - 1 and i; by one wavefront, PER rows per lane.  The vector is
+// scaled every 32 steps (the matrix has a trace of about one, so its largest eigenvalue is at least 1 / (2 d)).
+template <int PER>
+__device__ double tridiagonal_power(const double *alpha, const double *beta, int32_t steps, int32_t iterations) {
+    const int lane = lane_id();
+    double a[PER], b[PER + 1], y[PER];
+#pragma unroll
+    for (int q = 0; q <= PER; ++q) {
+        const int i = lane * PER + q;
+        if (q < PER) {
+            a[q < PER ? q : 0] = i < steps ? alpha[i] : 0.0;
+            y[q < PER ? q : 0] = i == 0 ? 1.0 : 0.0;
+        }
+        b[q] = i > 0 && i < steps ? beta[i] : 0.0;
+    }
+    auto length_sq = [&]() {
+        double s = 0.0;
+#pragma unroll
+        for (int q = 0; q < PER; ++q) s += y[q] * y[q];
+        return wave_sum_f64(s);
+    };
+    auto multiply = [&]() {
+        const double below = from_lower(y[PER - 1]), above = from_higher(y[0]);
+        double z[PER];
+#pragma unroll
+        for (int q = 0; q < PER; ++q)
+            z[q] = fma(b[q], q > 0 ? y[q > 0 ? q - 1 : 0] : below, fma(b[q + 1], q + 1 < PER ? y[q + 1 < PER ? q + 1 : 0] : above, a[q] * y[q]));
+#pragma unroll
+        for (int q = 0; q < PER; ++q) y[q] = z[q];
+    };
+    for (int32_t it = 1; it < iterations; ++it) {
+        multiply();
+        if (it % 32 == 0 || it + 1 == iterations) {
+            const double inv = inverse_norm(length_sq());
+#pragma unroll
+            for (int q = 0; q < PER; ++q) y[q] *= inv;
+        }
+    }
+    multiply();                                      // of a unit vector, or zero
+    return sqrt(length_sq());
+}
+
 // All iterations of one matrix.  NC: columns / 64.  w (one entry per thread) is the product of the iteration before,
 // w = G w' / |w'|, whose length is the estimate; the division happens after the product, so that an iteration holds two
 // barriers.  G is scaled by a power of two to a trace of about one (products of G with w are of the order of its
 // square).  fp32 products were measured too (1.8 us an iteration at d = 300 against 2.9): where the top eigenvalues nearly
 // coincide the constants then end up further from the exact ones than by iterating with A.
 // state [matrix][ld]: w between launches.
-template <int NC>
+// LANCZOS: `steps` steps of the recurrence w = G v_j - alpha_j v_j - beta_j v_{j-1}, v_{j+1} = w / |w| instead (one launch,
+// first), the division put off in the same way; alpha_j = v_j' G v_j is summed from the wavefronts' products beside them.
+template <int NC, bool LANCZOS>
 __global__ __launch_bounds__(kResThreads) void gram_resident_kernel(const float *__restrict__ G, int64_t d, int64_t ld,
-                                                                    int32_t iterations, bool first,
+                                                                    int32_t iterations, int32_t steps, bool first,
                                                                     double *__restrict__ state,
                                                                     double2 *__restrict__ stats) {
     constexpr int kCols = NC * kWave, NR = kCols / kResWaves;        // rows of G per wavefront
-    constexpr int kLds = NC == 5 ? 4 : 0, kReg = NR - kLds;          // five: four of the twenty rows in LDS, or registers spill
+    constexpr int kLds = NC >= 4 ? 4 : 0, kReg = NR - kLds;          // four of the rows in LDS, or registers spill
     static_assert(kReg % 2 == 0 && (kLds == 0 || kLds == 4), "rows go in pairs, those in LDS as one float4 per column");
     __shared__ double part[kResWaves][kCols], sums[kResWaves];
     __shared__ __attribute__((aligned(16))) double vec[kCols];
     __shared__ float4 g_lds[kLds ? kResWaves : 1][kLds ? kCols : 1];
-    const int tid = threadIdx.x, wave = tid / kWave, lane = lane_id();
+    __shared__ double prev[LANCZOS ? kCols : 1], dots[LANCZOS ? kResWaves : 1];
+    __shared__ double alpha[LANCZOS ? kLanczosMax : 1], beta[LANCZOS ? kLanczosMax : 1];
+    const int tid = threadIdx.x, wave = wave_id(), lane = lane_id();
     const float *g = G + (int64_t)blockIdx.x * ld * ld;
     // sum over the workgroup of the threads below kCols (whole wavefronts; the others pass zeros)
     auto norm_part = [&](double x) {
@@ -276,8 +372,10 @@ __global__ __launch_bounds__(kResThreads) void gram_resident_kernel(const float 
     double w = 0.0;
     if (first) w = tid < d ? (double)power_start_entry(blockIdx.x, tid, rsqrtf((float)d)) : 0.0;
     else if (tid < ld) w = vr[tid];
+    if (LANCZOS && tid < kCols) prev[LANCZOS ? tid : 0] = 0.0;
     __syncthreads();                                 // the trace has been read
-    for (int32_t it = 0; it < iterations; ++it) {
+    const int32_t rounds = LANCZOS ? steps : iterations;
+    for (int32_t it = 0; it < rounds; ++it) {
         norm_part(w * w);
         if (tid < kCols) vec[tid] = w;
         __syncthreads();
@@ -308,20 +406,51 @@ __global__ __launch_bounds__(kResThreads) void gram_resident_kernel(const float 
         }
 #pragma unroll
         for (int j = 0; j < NC; ++j) part[wave][lane + j * kWave] = acc[j];
-        double inv = 0.0;
-        if (tid < kCols) inv = inverse_norm(total());
+        if constexpr (LANCZOS) {                     // this wavefront's rows' share of w' G w
+            double s = 0.0;
+#pragma unroll
+            for (int j = 0; j < NC; ++j) {
+                __builtin_amdgcn_sched_barrier(0);
+                s = fma(acc[j], vec[lane + j * kWave], s);
+            }
+            s = wave_sum_f64(s);
+            if (lane == 0) dots[wave] = s;
+        }
+        double inv = 0.0, length_sq = 0.0;
+        if (tid < kCols) {
+            length_sq = total();
+            inv = inverse_norm(length_sq);
+        }
         __syncthreads();
         if (tid < kCols) {
             double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
 #pragma unroll
             for (int q = 0; q < kResWaves; q += 4) {
+                if (LANCZOS && q == kResWaves / 2) __builtin_amdgcn_sched_barrier(0);
                 s0 += part[q][tid];
                 s1 += part[q + 1][tid];
                 s2 += part[q + 2][tid];
                 s3 += part[q + 3][tid];
             }
             w = ((s0 + s1) + (s2 + s3)) * inv;
+            if constexpr (LANCZOS) {                 // w = G v_j so far, v_j = vec * inv
+                __builtin_amdgcn_sched_barrier(0);   // the sixteen shares after the sixteen partial products, not beside them
+                static_assert(kResWaves == 16, "one row of lanes");
+                const double al = group_sum_f64<kResWaves>(dots[lane % kResWaves]) * inv * inv, be = sqrt(length_sq), v = vec[tid] * inv;
+                w = fma(-be, prev[tid], fma(-al, v, w));     // prev = 0 the first time, when be is the start vector's length
+                prev[tid] = v;
+                alpha[it] = al;                      // the same from every thread: behind a branch the loop's registers spill
+                beta[it] = be;
+            }
         }
+    }
+    if constexpr (LANCZOS) {
+        __syncthreads();
+        if (wave > 0) return;
+        const double value = steps <= kWave ? tridiagonal_power<1>(alpha, beta, steps, iterations)
+                                            : tridiagonal_power<kLanczosMax / kWave>(alpha, beta, steps, iterations);
+        if (lane == 0) stats[blockIdx.x] = make_double2(0.0, value / (double)scale);
+        return;
     }
     if (tid < ld) vr[tid] = w;
     norm_part(w * w);                                // stats[matrix] = (0, the estimate)
@@ -330,29 +459,64 @@ __global__ __launch_bounds__(kResThreads) void gram_resident_kernel(const float 
 }
 
 // One iteration: w = G v / |v|.  Grid (ld / 32, matrices).
+// Recurrence number `step` of the Lanczos path (step >= 0): v is the product G v_j (step 0: the start vector), r.vj and
+// r.vprev are v_j and the one before; every workgroup forms v_{j+1} for itself and multiplies its rows, and the first one of
+// a matrix leaves alpha_j, beta_{j+1} and v_{j+1} for the launches that follow.
+struct Recurrence {
+    int32_t step;                                    // -1: the power iteration
+    const double *vj, *vprev;                        // [matrix][ld]
+    double *vnext;
+    double *alpha, *beta;                            // [matrix][kLanczosMax]
+};
 __global__ __launch_bounds__(kMvThreads) void gram_matvec_kernel(const float *__restrict__ G, int64_t ld,
-                                                                 const double *__restrict__ v, double *__restrict__ w) {
+                                                                 const double *__restrict__ v, double *__restrict__ w,
+                                                                 Recurrence r) {
     constexpr int kMaxPer = (int)kGramMax / kMvThreads, kQuads = (int)kGramMax / (4 * kWave), kTogether = 2;
-    __shared__ double vec[kGramMax], sums[kMvWaves];
+    __shared__ double vec[kGramMax], sums[2][kMvWaves];
     const int64_t which = blockIdx.y;
     const int tid = threadIdx.x, wave = tid / kWave, lane = lane_id();
     const double *vr = v + which * ld;
+    auto block_sum = [&](double s, int slot) {
+        s = wave_sum_f64(s);
+        if (lane == 0) sums[slot][wave] = s;
+        __syncthreads();
+        s = 0.0;
+#pragma unroll
+        for (int q = 0; q < kMvWaves; ++q) s += sums[slot][q];
+        return s;
+    };
     double x[kMaxPer], sq = 0.0;
 #pragma unroll
     for (int q = 0; q < kMaxPer; ++q) {
         const int j = tid + q * kMvThreads;
         x[q] = j < ld ? vr[j] : 0.0;
-        sq += x[q] * x[q];
     }
-    sq = wave_sum_f64(sq);
-    if (lane == 0) sums[wave] = sq;
-    __syncthreads();
-    sq = 0.0;
+    if (r.step > 0) {
+        double vj[kMaxPer], vp[kMaxPer], dot = 0.0;
+        const double be = r.beta[which * kLanczosMax + r.step - 1];
 #pragma unroll
-    for (int q = 0; q < kMvWaves; ++q) sq += sums[q];
+        for (int q = 0; q < kMaxPer; ++q) {
+            const int j = tid + q * kMvThreads;
+            vj[q] = j < ld ? r.vj[which * ld + j] : 0.0;
+            vp[q] = r.step > 1 && j < ld ? r.vprev[which * ld + j] : 0.0;
+            dot = fma(x[q], vj[q], dot);
+        }
+        dot = block_sum(dot, 0);
+#pragma unroll
+        for (int q = 0; q < kMaxPer; ++q) x[q] = fma(-be, vp[q], fma(-dot, vj[q], x[q]));
+        if (blockIdx.x == 0 && tid == 0) r.alpha[which * kLanczosMax + r.step - 1] = dot;
+    }
+#pragma unroll
+    for (int q = 0; q < kMaxPer; ++q) sq += x[q] * x[q];
+    sq = block_sum(sq, 1);
     const double inv = inverse_norm(sq);
 #pragma unroll
-    for (int q = 0; q < kMaxPer; ++q) vec[tid + q * kMvThreads] = x[q] * inv;
+    for (int q = 0; q < kMaxPer; ++q) {
+        const int j = tid + q * kMvThreads;
+        vec[j] = x[q] * inv;
+        if (r.step >= 0 && blockIdx.x == 0 && j < ld) r.vnext[which * ld + j] = x[q] * inv;
+    }
+    if (r.step >= 0 && blockIdx.x == 0 && tid == 0) r.beta[which * kLanczosMax + r.step] = r.step > 0 ? sqrt(sq) : 0.0;
     __syncthreads();
     const int64_t r0 = (int64_t)blockIdx.x * kMvRows + wave * kMvRowsPerWave;
     const float *g = G + (which * ld + r0) * ld;
@@ -393,10 +557,40 @@ __global__ __launch_bounds__(kWave) void gram_norm_kernel(const double *__restri
     if (threadIdx.x == 0) stats[blockIdx.x] = make_double2(0.0, sqrt(s));
 }
 
+// The end of the Lanczos path: the last alpha, then the power iteration with the tridiagonal matrix.  y = G v_J.
+__global__ __launch_bounds__(kWave) void gram_tridiagonal_kernel(const double *__restrict__ y, const double *__restrict__ v,
+                                                                 int64_t ld, const double *__restrict__ alpha,
+                                                                 const double *__restrict__ beta, int32_t steps,
+                                                                 int32_t iterations, double2 *__restrict__ stats) {
+    __shared__ double a[kLanczosMax], b[kLanczosMax];
+    const int64_t which = blockIdx.x;
+    const int lane = lane_id();
+    double dot = 0.0, trace = 0.0;
+    for (int64_t j = lane; j < ld; j += kWave) dot = fma(y[which * ld + j], v[which * ld + j], dot);
+    dot = wave_sum_f64(dot);
+    for (int32_t i = lane; i < steps; i += kWave) {
+        a[i] = i + 1 < steps ? alpha[which * kLanczosMax + i] : dot;
+        b[i] = beta[which * kLanczosMax + i];
+        trace += a[i];
+    }
+    trace = wave_sum_f64(trace);
+    int exponent = 0;                                // scaled as in gram_resident_kernel; every eigenvalue is in [0, trace]
+    if (trace > 0.0 && trace < 1e300) (void)frexp(trace, &exponent);
+    for (int32_t i = lane; i < steps; i += kWave) {
+        a[i] = ldexp(a[i], -exponent);
+        b[i] = ldexp(b[i], -exponent);
+    }
+    __syncthreads();
+    const double value = steps <= kWave ? tridiagonal_power<1>(a, b, steps, iterations)
+                                        : tridiagonal_power<kLanczosMax / kWave>(a, b, steps, iterations);
+    if (lane == 0) stats[which] = make_double2(0.0, ldexp(value, exponent));
+}
+
 struct GramWs {
     double *part;                   // [n][chunks][pairs][32][32]
     float *G;                       // [n + 1][ld][ld]
     double *v, *w;                  // [n + 1][ld] each
+    double *lanczos;                // three more vectors of that size, and alpha and beta [n + 1][kLanczosMax]
 };
 
 size_t gram_layout(int32_t n, const GramPlan &p, char *base, GramWs *ws) {
@@ -410,7 +604,8 @@ size_t gram_layout(int32_t n, const GramPlan &p, char *base, GramWs *ws) {
     char *g = take(sizeof(float) * (size_t)(n + 1) * p.ld * p.ld);
     char *v = take(sizeof(double) * (size_t)(n + 1) * p.ld);
     char *w = take(sizeof(double) * (size_t)(n + 1) * p.ld);
-    if (ws) *ws = GramWs{(double *)pt, (float *)g, (double *)v, (double *)w};
+    char *l = take(sizeof(double) * (size_t)(n + 1) * (3 * p.ld + 2 * kLanczosMax));
+    if (ws) *ws = GramWs{(double *)pt, (float *)g, (double *)v, (double *)w, (double *)l};
     return off;
 }
 
@@ -418,10 +613,15 @@ constexpr size_t kGramWsMax = (size_t)1 << 30;
 
 template <int NC>
 void launch_resident(const GramWs &ws, int32_t n, int64_t d, int64_t ld, int32_t iterations, double *stats, hipStream_t stream) {
+    if (const int32_t steps = lanczos_steps(iterations)) {
+        hipLaunchKernelGGL((gram_resident_kernel<NC, true>), dim3((unsigned)(n + 1)), dim3(kResThreads), 0, stream, ws.G, d, ld,
+                           iterations, steps, true, ws.v, (double2 *)stats);
+        return;
+    }
     for (int32_t done = 0; done < iterations; done += kItersPerLaunch) {
         const int32_t now = iterations - done < kItersPerLaunch ? iterations - done : kItersPerLaunch;
-        hipLaunchKernelGGL(gram_resident_kernel<NC>, dim3((unsigned)(n + 1)), dim3(kResThreads), 0, stream, ws.G, d, ld, now,
-                           done == 0, ws.v, (double2 *)stats);
+        hipLaunchKernelGGL((gram_resident_kernel<NC, false>), dim3((unsigned)(n + 1)), dim3(kResThreads), 0, stream, ws.G, d, ld,
+                           now, 0, done == 0, ws.v, (double2 *)stats);
     }
 }
 
@@ -433,7 +633,7 @@ size_t gram_power_bytes(int32_t n, int64_t m, int64_t d, int32_t iterations) {
     const size_t bytes = gram_layout(n, p, nullptr, nullptr);
     if (bytes > kGramWsMax) return 0;
     // Microseconds, a handle's first call: forming the matrices (with the allocation of their workspace) and one iteration
-    // on them, against one iteration with A (six launches).  Measured, forming | iteration on G | with A: n = 4, m = 250,
+    // on them (or one step of the recurrence), against one iteration with A (six launches).  Measured, forming | iteration on G | with A: n = 4, m = 250,
     // d = 100 1 | 0.9 | 22; 20, 2487, 300 172 | 2.5 | 44; 10, 3000, 500 223 | 7.3 | 40; 2, 7500, 1000 354 | 8.7 | 50;
     // 15, 1000, 1000 424 | 15 | 41; 32, 468, 1000 482 | 32 | 40; 32, 100, 1000 253 | 32 | 30; 1000, 20, 100 286 | 2.4 | 137.
     const double nn = n, mm = (double)m, dd = (double)d, ld = (double)p.ld, rows = nn * mm;
@@ -442,7 +642,8 @@ size_t gram_power_bytes(int32_t n, int64_t m, int64_t d, int32_t iterations) {
     const double with_g = d <= kResidentMax ? 2.6 * (double)((n + 256) / 256) : (matrices > 8.5 ? matrices : 8.5);
     const double sums = 512.0 / nn < mm / 8.0 ? 512.0 / nn : mm / 8.0;           // of the gradient, per worker
     const double with_a = 22.0 + 1.1e-6 * rows * dd + 0.08 * nn + 3.5e-5 * sums * dd;
-    return form + iterations * with_g < iterations * with_a ? bytes : 0;
+    const int32_t steps = lanczos_steps(iterations);
+    return form + (steps ? steps : iterations) * with_g < iterations * with_a ? bytes : 0;
 }
 
 hipError_t launch_gram_power(const float *A, int32_t n, int64_t m, int64_t d, int32_t iterations, void *workspace,
@@ -469,9 +670,23 @@ hipError_t launch_gram_power(const float *A, int32_t n, int64_t m, int64_t d, in
     hipLaunchKernelGGL(gram_start_kernel, dim3((unsigned)((p.ld + kTileThreads - 1) / kTileThreads), (unsigned)(n + 1)),
                        dim3(kTileThreads), 0, stream, ws.v, d, p.ld);
     double *from = ws.v, *to = ws.w;
+    const dim3 grid((unsigned)(p.ld / kMvRows), (unsigned)(n + 1));
+    if (const int32_t steps = lanczos_steps(iterations)) {
+        const size_t vector = (size_t)(n + 1) * p.ld;
+        double *v3[3] = {ws.lanczos, ws.lanczos + vector, ws.lanczos + 2 * vector};
+        double *alpha = ws.lanczos + 3 * vector, *beta = alpha + (size_t)(n + 1) * kLanczosMax;
+        for (int32_t j = 0; j < steps; ++j) {       // launch j: v_{j+1}, in v3[(j + 1) % 3], and its product
+            const Recurrence r{j, v3[j % 3], v3[(j + 2) % 3], v3[(j + 1) % 3], alpha, beta};
+            hipLaunchKernelGGL(gram_matvec_kernel, grid, dim3(kMvThreads), 0, stream, ws.G, p.ld, from, to, r);
+            std::swap(from, to);
+        }
+        hipLaunchKernelGGL(gram_tridiagonal_kernel, dim3((unsigned)(n + 1)), dim3(kWave), 0, stream, from, v3[steps % 3], p.ld,
+                           alpha, beta, steps, iterations, (double2 *)stats);
+        return hipGetLastError();
+    }
     for (int32_t it = 0; it < iterations; ++it) {
-        hipLaunchKernelGGL(gram_matvec_kernel, dim3((unsigned)(p.ld / kMvRows), (unsigned)(n + 1)), dim3(kMvThreads), 0, stream,
-                           ws.G, p.ld, from, to);
+        hipLaunchKernelGGL(gram_matvec_kernel, grid, dim3(kMvThreads), 0, stream, ws.G, p.ld, from, to,
+                           Recurrence{-1, nullptr, nullptr, nullptr, nullptr, nullptr});
         std::swap(from, to);
     }
     hipLaunchKernelGGL(gram_norm_kernel, dim3((unsigned)(n + 1)), dim3(kWave), 0, stream, from, p.ld, (double2 *)stats);

@@ -201,6 +201,51 @@ def test_power_iteration_goes_on_over_launches(gpu, d):
             np.testing.assert_allclose(got, want, rtol=1e-6, err_msg=f"{steps} steps")
 
 
+# the first and last numbers of iterations that run as a Lanczos recurrence and those beside them (47, 2823: the power
+# iteration), one row and four rows of the tridiagonal matrix per lane (177 and 178 iterations: 65 and 66 steps), in each
+# form of the product
+@pytest.mark.parametrize("d", [2, 64, 65, 192, 256, 320, 321, 700])
+def test_recurrence_gives_the_power_iterations_value(gpu, d):
+    torch, binding = gpu
+    print(f"recurrence d={d}", flush=True)
+    n, m = 2, d
+    rng = np.random.default_rng(d)
+    A = np.zeros((n, m, d), np.float32)                   # A_i^T A_i / m diagonal: one product per entry, exact in fp64
+    for i in range(n):
+        scale = rng.random(d).astype(np.float32)          # many eigenvalues, the largest ones close to one another
+        scale[0], scale[d - 1] = 1.0, 0.9995
+        A[i][np.arange(d), np.arange(d)] = np.sqrt(np.float32(m)) * scale * np.float32(1 + i)
+    y = np.zeros((n, m), np.float32)
+    diagonals = np.array([np.diagonal(a).astype(np.float64) ** 2 / m for a in A])
+    rounded = np.vstack([diagonals, diagonals.mean(0)]).astype(np.float32).astype(np.float64)
+    with binding.EF21(n, d, 1, 0.1) as h:
+        h.set_problem_dense(to_gpu(torch, A), to_gpu(torch, y), 0.0)
+        for steps in (47, 48, 100, 177, 178, 2822, 2823):
+            _, L, L_i = h.theory_stepsize(steps)
+            got = 4.0 * np.array(list(L_i) + [L])
+            # fp64 on both sides from the same fp32 matrix.  The start vectors' fp32 entries may differ by a rounding (the
+            # device's 1 / sqrt(d)), 2^-23: each weight in the two moments by 2^-22, and the estimate by half that times
+            # the spread of the eigenvalues that still count, those above 0.9 (0.9^94 = 5e-5): 2^-23 * 0.2 = 2.4e-8.
+            # Half the steps would be 1e-5 off.
+            np.testing.assert_allclose(got, diagonal_power(rounded, steps), rtol=2.4e-8, err_msg=f"{steps} iterations")
+
+
+def diagonal_power(eigenvalues, steps):
+    out = []
+    for row, e in enumerate(eigenvalues):
+        d = e.size
+        h = (np.arange(d, dtype=np.uint64) * 2654435761 + 0x9e3779b9 * (row + 1)) & 0xffffffff
+        h ^= h >> 15
+        h = (h * 2246822519) & 0xffffffff
+        h ^= h >> 13
+        v = ((0.5 + (h >> 8).astype(np.float32) * np.float32(1 / 16777216)) / np.sqrt(np.float32(d))).astype(np.float64)
+        for _ in range(steps - 1):
+            v = e * v
+            v /= np.linalg.norm(v)
+        out.append(np.linalg.norm(e * v) / np.linalg.norm(v))
+    return np.array(out)
+
+
 def test_few_iterations_on_large_matrices(gpu):
     """32 workers, 1000 columns: forming 33 matrices of a million entries takes as long as a dozen iterations with the
     468 rows per worker, and an iteration on them 32 us against 40, so twenty iterations run with A: 3.4 times as long as
