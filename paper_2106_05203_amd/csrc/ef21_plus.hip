@@ -249,7 +249,7 @@ __global__ __launch_bounds__(kThreads) void plus_apply_long_kernel(PlusLongArgs 
     float4 x4[kPer];
     if (STEP && whole) {
 #pragma unroll
-        for (int q = 0; q < kPer; ++q) x4[q] = stream_load4(a.x + c0 + 4 * (q * kWave + lane));
+        for (int q = 0; q < kPer; ++q) x4[q] = *reinterpret_cast<const float4 *>(a.x + c0 + 4 * (q * kWave + lane));
     }
     auto entry = [&](const float *row, int q, int t) {       // of the last, partial block
         const int64_t c = c0 + 4 * (q * kWave + lane) + t;
@@ -282,7 +282,7 @@ __global__ __launch_bounds__(kThreads) void plus_apply_long_kernel(PlusLongArgs 
                 for (int q = 0; q < kPer; ++q) {
                     old[u][q] = make_float4(0.f, 0.f, 0.f, 0.f);
                     if (!plain[u]) {
-                        if (whole) old[u][q] = stream_load4_any(row + c0 + 4 * (q * kWave + lane));
+                        if (whole) old[u][q] = load4_any(row + c0 + 4 * (q * kWave + lane));
                         else old[u][q] = make_float4(entry(row, q, 0), entry(row, q, 1), entry(row, q, 2), entry(row, q, 3));
                     }
                 }
