@@ -99,8 +99,14 @@ def _opt(t, dtype, shape=None):
     return None if t is None else _dev(t, dtype, shape)
 
 
+# torch.cuda.current_stream() builds a Stream object (2.8 us); the handle alone takes 0.3.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _current_stream_ptr() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def ef21_topk(rows: torch.Tensor, k: int, out_idx: torch.Tensor | None = None,
@@ -112,9 +118,9 @@ def ef21_topk(rows: torch.Tensor, k: int, out_idx: torch.Tensor | None = None,
         raise ValueError("rows must be [n][d]")
     n, d = rows.shape
     if out_idx is None:
-        out_idx = torch.empty((n, max(k, 0)), dtype=torch.int32, device=rows.device)
+        out_idx = torch.empty(n, max(k, 0), dtype=torch.int32, device=rows.device)
     if out_val is None:
-        out_val = torch.empty((n, max(k, 0)), dtype=torch.float32, device=rows.device)
+        out_val = torch.empty(n, max(k, 0), dtype=torch.float32, device=rows.device)
     call = lib.ef21_topk_static if static else lib.ef21_topk
     _check(call(_dev(rows, torch.float32), n, d, k, _dev(out_idx, torch.int32), _dev(out_val, torch.float32),
                 _current_stream_ptr()))
@@ -151,6 +157,15 @@ class EF21:
         self.use_current_stream()
 
     # -- plumbing
+    def _call(self, function, *args) -> None:
+        """function(handle, *args) with the handle's device current; switching there and back costs as much as a small
+        call's own host work, so it is left out where that device is the current one already."""
+        if self.device.index is None or torch.cuda.current_device() == self.device.index:
+            _check(function(self._h, *args))
+            return
+        with torch.cuda.device(self.device):
+            _check(function(self._h, *args))
+
     def use_current_stream(self) -> None:
         with torch.cuda.device(self.device):
             _check(self._lib.ef21_set_stream(self._h, _current_stream_ptr()))
@@ -179,9 +194,8 @@ class EF21:
         n, m, d = A.shape
         if (n, d) != (self.n, self.d):
             raise ValueError("A must be [n][m][d]")
-        with torch.cuda.device(self.device):
-            _check(self._lib.ef21_set_problem_dense(self._h, _dev(A, torch.float32), _dev(y, torch.float32, (n, m)), m,
-                                                    float(lam)))
+        self._call(self._lib.ef21_set_problem_dense, _dev(A, torch.float32), _dev(y, torch.float32, (n, m)), m,
+                   float(lam))
         self._keep = [A, y]
         self._batch = None
 
@@ -189,44 +203,38 @@ class EF21:
                         lam: float) -> None:
         if rowptr.numel() != self.n * m + 1 or col.numel() != val.numel():
             raise ValueError("rowptr must have n*m+1 entries and col, val equal lengths")
-        with torch.cuda.device(self.device):
-            _check(self._lib.ef21_set_problem_csr(self._h, _dev(rowptr, torch.int64), _dev(col, torch.int32),
-                                                  _dev(val, torch.float32), _dev(y, torch.float32, (self.n, m)), m,
-                                                  float(lam)))
+        self._call(self._lib.ef21_set_problem_csr, _dev(rowptr, torch.int64), _dev(col, torch.int32),
+                   _dev(val, torch.float32), _dev(y, torch.float32, (self.n, m)), m,
+                   float(lam))
         self._keep = [rowptr, col, val, y]
         self._batch = None
 
     # -- state
     def set_state(self, x=None, g_i=None, g=None) -> None:
-        with torch.cuda.device(self.device):
-            _check(self._lib.ef21_set_state(self._h, _opt(x, torch.float32, (self.d,)),
-                                            _opt(g_i, torch.float32, (self.n, self.d)),
-                                            _opt(g, torch.float32, (self.d,))))
+        self._call(self._lib.ef21_set_state, _opt(x, torch.float32, (self.d,)),
+                   _opt(g_i, torch.float32, (self.n, self.d)),
+                   _opt(g, torch.float32, (self.d,)))
 
     def get_state(self):
         x = torch.empty(self.d, dtype=torch.float32, device=self.device)
         g_i = torch.empty((self.n, self.d), dtype=torch.float32, device=self.device)
         g = torch.empty(self.d, dtype=torch.float32, device=self.device)
-        with torch.cuda.device(self.device):
-            _check(self._lib.ef21_get_state(self._h, x.data_ptr(), g_i.data_ptr(), g.data_ptr()))
+        self._call(self._lib.ef21_get_state, x.data_ptr(), g_i.data_ptr(), g.data_ptr())
         return x, g_i, g
 
     def get_x(self) -> torch.Tensor:
         x = torch.empty(self.d, dtype=torch.float32, device=self.device)
-        with torch.cuda.device(self.device):
-            _check(self._lib.ef21_get_state(self._h, x.data_ptr(), None, None))
+        self._call(self._lib.ef21_get_state, x.data_ptr(), None, None)
         return x
 
     def get_messages(self):
         idx = torch.empty((self.n, self.k), dtype=torch.int32, device=self.device)
         val = torch.empty((self.n, self.k), dtype=torch.float32, device=self.device)
-        with torch.cuda.device(self.device):
-            _check(self._lib.ef21_get_messages(self._h, idx.data_ptr(), val.data_ptr()))
+        self._call(self._lib.ef21_get_messages, idx.data_ptr(), val.data_ptr())
         return idx, val
 
     def set_loss(self, loss: int) -> None:
-        with torch.cuda.device(self.device):
-            _check(self._lib.ef21_set_loss(self._h, int(loss)))
+        self._call(self._lib.ef21_set_loss, int(loss))
 
     def set_minibatch(self, rows: "torch.Tensor | None") -> None:
         """rows: int32 [n][tau] on the device (kept alive by the handle and read at every gradient), or None
@@ -245,8 +253,7 @@ class EF21:
         """(gamma, L, L_i [n]) of Theorem 1 for the attached problem, eigenvalues by power iteration on the GPU."""
         gamma, L = C.c_double(), C.c_double()
         L_i = (C.c_double * self.n)()
-        with torch.cuda.device(self.device):
-            _check(self._lib.ef21_theory_stepsize(self._h, int(iterations), C.byref(gamma), C.byref(L), L_i))
+        self._call(self._lib.ef21_theory_stepsize, int(iterations), C.byref(gamma), C.byref(L), L_i)
         return gamma.value, L.value, list(L_i)
 
     def get_choices(self):
@@ -254,32 +261,27 @@ class EF21:
         step taken with PLUS."""
         branch = torch.empty(self.n, dtype=torch.int32, device=self.device)
         bm = torch.empty((self.n, 2), dtype=torch.float64, device=self.device)
-        with torch.cuda.device(self.device):
-            _check(self._lib.ef21_get_choices(self._h, branch.data_ptr(), bm.data_ptr()))
+        self._call(self._lib.ef21_get_choices, branch.data_ptr(), bm.data_ptr())
         return branch, bm
 
     # -- measurement
     def set_timing(self, enabled: bool) -> None:
-        with torch.cuda.device(self.device):
-            _check(self._lib.ef21_set_timing(self._h, int(bool(enabled))))
+        self._call(self._lib.ef21_set_timing, int(bool(enabled)))
 
     def get_timing(self, reset: bool = True) -> dict:
         """{kernel class: (milliseconds, launches)} accumulated while timing was enabled."""
         ms = (C.c_double * K_COUNT)()
         cnt = (C.c_int64 * K_COUNT)()
-        with torch.cuda.device(self.device):
-            _check(self._lib.ef21_get_timing(self._h, C.addressof(ms), C.addressof(cnt), int(reset)))
+        self._call(self._lib.ef21_get_timing, C.addressof(ms), C.addressof(cnt), int(reset))
         return {self._lib.ef21_kernel_name(i).decode(): (ms[i], cnt[i]) for i in range(K_COUNT) if cnt[i]}
 
     # -- the hot path
     def local_grad(self, x: torch.Tensor | None = None, out: torch.Tensor | None = None) -> torch.Tensor:
         if out is None:
             out = torch.empty((self.n, self.d), dtype=torch.float32, device=self.device)
-        with torch.cuda.device(self.device):
-            _check(self._lib.ef21_local_grad(self._h, _opt(x, torch.float32, (self.d,)),
-                                             _dev(out, torch.float32, (self.n, self.d))))
+        self._call(self._lib.ef21_local_grad, _opt(x, torch.float32, (self.d,)),
+                   _dev(out, torch.float32, (self.n, self.d)))
         return out
 
     def step(self, grads: torch.Tensor | None = None, order: int = ORDER_GRAD_FIRST) -> None:
-        with torch.cuda.device(self.device):
-            _check(self._lib.ef21_step(self._h, _opt(grads, torch.float32, (self.n, self.d)), int(order)))
+        self._call(self._lib.ef21_step, _opt(grads, torch.float32, (self.n, self.d)), int(order))
