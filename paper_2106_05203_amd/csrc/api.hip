@@ -816,6 +816,19 @@ int ef21_step(ef21_handle h, const float *grads, uint32_t flags) {
         if (st != hipSuccess) return fail_hip(st, "iteration kernel launch");
         return EF21_OK;
     }
+    if (!grads && h->kind == kDense &&
+        ef21::solo_applies(h->n, h->batch.tau > 0 ? h->batch.tau : h->m, h->m, h->d)) {
+        // lines 5 and 6 in one launch, lines 8 and 3 in another
+        hipError_t st = ef21::launch_solo_select(h->A, h->y, h->x, h->g_i, h->n, h->m, h->d, h->k, h->lambda, h->loss,
+                                                 h->batch, h->msg_idx, h->msg_val, h->stream);
+        mk(ef21::K_GRAD_MAIN);
+        if (st != hipSuccess) return fail_hip(st, "gradient and Top-k kernel launch");
+        st = ef21::launch_aggregate(h->msg_idx, h->msg_val, h->n, h->k, h->d, h->g, step_first ? nullptr : h->x, h->gamma,
+                                    h->agg_index, h->stream);
+        mk(ef21::K_MODEL_STEP);
+        if (st != hipSuccess) return fail_hip(st, "aggregation launch");
+        return EF21_OK;
+    }
     ef21::GradParts parts;
     if (!grads) {
         const bool row_kernel = !(use_split(h->d) && h->topk_ws);

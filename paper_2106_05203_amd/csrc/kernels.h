@@ -182,6 +182,16 @@ hipError_t launch_logreg_grad_csr(const int64_t *rowptr, const int32_t *col, con
                                   float lambda, const void *index, hipStream_t stream, const Marker &mk = Marker(),
                                   int loss = kLossLogistic, RowBatch batch = RowBatch(), int64_t x_stride = 0);
 
+// Dense problems with few rows per worker (m of m_full, d columns), a workgroup per worker: the gradient, or lines 5 and 6 of
+// Algorithm 2 (the messages, and g_i updated in place).  The gradient's bits are the same either way.  launch_logreg_grad_dense
+// takes the first by itself.
+bool solo_applies(int32_t n, int64_t m, int64_t m_full, int64_t d);
+hipError_t launch_solo_grad(const float *A, const float *y, const float *x, float *grad, int32_t n, int64_t m_full,
+                            int64_t d, float lambda, int loss, RowBatch batch, int64_t x_stride, hipStream_t stream);
+hipError_t launch_solo_select(const float *A, const float *y, const float *x, float *g_i, int32_t n, int64_t m_full,
+                              int64_t d, int64_t k, float lambda, int loss, RowBatch batch, int32_t *msg_idx,
+                              float *msg_val, hipStream_t stream);
+
 // Small dense problems: lines 5, 6, 8 (and 3 if take_step) of Algorithm 2 in ONE launch, from the problem and the
 // state, with the arithmetic of the separate kernels (gradient, row Top-k with update, aggregation), so the
 // results are the same bits.  small_step_applies says whether the shape qualifies (d <= 1024, n * k <= 2048,

@@ -378,6 +378,11 @@ hipError_t launch_logreg_grad_dense(const float *A, const float *y, const float 
     if (defer) *defer = GradParts();
     const int32_t *batch = rb.tau > 0 ? rb.rows : nullptr;
     const int64_t m = batch ? rb.tau : m_full;         // rows summed per worker (tau <= m_full, checked by the caller)
+    if (solo_applies(n, m, m_full, d)) {
+        const hipError_t st = launch_solo_grad(A, y, x, grad, n, m_full, d, lambda, loss, rb, x_stride, stream);
+        mk(K_GRAD_MAIN);
+        return st;
+    }
     const DenseVariant dv = dense_variant(d);
     const bool deep = dense_deep(n, m_full, d) && d >= 4;
     const bool wide = dv.lanes == 0 && d <= kWideMax && d >= 4;

@@ -66,6 +66,55 @@ def test_same_bits_as_the_separate_kernels(gpu, n, d, m, k, order):
         assert "small_step" in classes and "topk_row" not in classes and "grad_main" not in classes
 
 
+# a workgroup per worker: every form of its rows (tiny, quads, ragged; 16, 32 and 64 lanes, two quads per lane) with the most rows
+# it takes, one row more (the separate kernels), a row or two, and trips that end inside a wavefront's rows
+@pytest.mark.parametrize("d", [1, 3, 4, 5, 63, 64, 65, 126, 128, 129, 255, 256, 258, 511, 512, 513])
+@pytest.mark.parametrize("loss", ["logistic", "squares"])
+def test_workgroup_per_worker(gpu, oracle, d, loss):
+    torch, binding = gpu
+    most = 512 if d <= 128 else 256 if d <= 256 else 128            # rows: two trips of sixteen wavefronts
+    for m in sorted({1, 2, 17, most // 4 - 1, most - 1, most, most + 1}):
+        print(f"workgroup per worker d={d} m={m} {loss}", flush=True)
+        n, k = 3, max(1, d // 3)
+        A, y, rng = problem(n, d, m, d + m)
+        if loss == "squares":
+            y = rng.standard_normal((n, m)).astype(np.float32)
+        x = (0.3 * rng.standard_normal(d)).astype(np.float32)
+        batch = rng.integers(0, m, (n, m)).astype(np.int32)
+        batch[0, 0], batch[1, m - 1] = -1, m                      # entries that name no row
+        P = (oracle.LeastSquaresDense if loss == "squares" else oracle.LogRegDense)(A, y, 0.1)
+        with binding.EF21(n, d, k, 0.3) as h, binding.EF21(n, d, k, 0.3) as given:
+            for e in (h, given):
+                e.set_problem_dense(to_gpu(torch, A), to_gpu(torch, y), 0.1)
+                if loss == "squares":
+                    e.set_loss(binding.LOSS_LEAST_SQUARES)
+                e.set_state(to_gpu(torch, x), to_gpu(torch, 0.1 * rng.standard_normal((n, d)) if e is h else h.get_state()[1].cpu()),
+                            None)
+            got = h.local_grad().cpu().numpy().astype(np.float64)
+            ref = P.grads(x.astype(np.float64))
+            # per row: the margin's rounding, (d / 64 + 8) u sum |a x| (d / 64 additions per lane, six levels over the lanes), moves
+            # the coefficient by at most its curvature (1/4, or 2); sums of at most sixteen levels; helpers.gradient_rounding_floor
+            # is the same for the logistic loss
+            u = 2.0 ** -24
+            a64, z = A.astype(np.float64), np.einsum("imd,d->im", A.astype(np.float64), x.astype(np.float64))
+            coef = np.abs(2.0 * (z - y)) if loss == "squares" else 1.0 / (1.0 + np.exp(y * z))
+            dz = (d / 64 + 8) * u * np.einsum("imd,d->im", np.abs(a64), np.abs(x.astype(np.float64)))
+            dcoef = (2.0 if loss == "squares" else 0.25) * dz + 16 * u * (coef + (2.0 * np.abs(z) if loss == "squares" else 0.0))
+            bound = 1e-6 * np.abs(ref) + np.einsum("imd,im->id", np.abs(a64), dcoef) / m + u
+            assert np.all(np.abs(got - ref) <= bound), (m, np.max(np.abs(got - ref) / bound))
+            for rows in (None, to_gpu(torch, batch, np.int32)):
+                h.set_minibatch(rows)
+                given.set_minibatch(rows)
+                for _ in range(2):                                # its lines 5 and 6 against the Top-k of the reported gradient
+                    s = given.local_grad()
+                    h.step()
+                    given.step(s)
+                    for name, a, b in zip(("x", "g_i", "g"), h.get_state(), given.get_state()):
+                        assert torch.equal(a, b), f"m = {m}: {name} differs"
+                    for a, b in zip(h.get_messages(), given.get_messages()):
+                        assert torch.equal(a, b), f"m = {m}: messages differ"
+
+
 def test_least_squares_same_bits(gpu):
     torch, binding = gpu
     n, d, m, k = 3, 200, 90, 7
