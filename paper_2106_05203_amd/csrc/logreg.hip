@@ -311,6 +311,23 @@ __global__ __launch_bounds__(kThreads) void logreg_dense_finish_kernel(const flo
             dense_grad_entry(part + worker * chunks * d, chunks, d, c, x[worker * x_stride + c], m, lambda);
 }
 
+// The same where a column has many sums: eight threads per column, a chain of dense_grad_entry's each, and all of a chain's
+// entries in flight up to AHEAD of them (in memory order a thread alone waits for every sixteen: 12.8 us of a gradient's 26 at n = 1,
+// m = 200000, d = 80 with 512 blocks).
+constexpr int kSharedCols = 64, kSharedThreads = 8 * kSharedCols;
+template <int AHEAD>
+__global__ __launch_bounds__(kSharedThreads) void logreg_dense_finish_shared_kernel(const float *__restrict__ part,
+                                                                                   const float *__restrict__ x,
+                                                                                   float *__restrict__ grad,
+                                                                                   int64_t chunks, int64_t m, int64_t d,
+                                                                                   float lambda, int64_t x_stride) {
+    __shared__ double lds[8 * kSharedCols];
+    const int64_t worker = blockIdx.y;
+    dense_grad_shared<kSharedThreads, kSharedCols, AHEAD>(part + worker * chunks * d, chunks, d,
+                                                          (int64_t)blockIdx.x * kSharedCols, x + worker * x_stride, m, lambda,
+                                                          lds, [&](int c, float g) { grad[worker * d + c] = g; });
+}
+
 struct DenseArgs {
     const float *A, *y, *x;
     float *part;
@@ -430,17 +447,33 @@ hipError_t launch_logreg_grad_dense(const float *A, const float *y, const float 
     hipError_t st = hipGetLastError();
     if (st != hipSuccess) return st;
     // The consumer finishes the sums itself (dense_grad_entry) where that is less work for its one workgroup per row than
-    // another kernel of 4 to 5 us: 1 us per 40 KB of sums and per 1000 columns (the regulariser's divisions).  step, us,
-    // with the sums left and finished: n = 2, m = 50000, d = 300 (256 blocks) 37.9 and 39.4; n = 4, m = 2000, d = 1000 (64)
-    // 20.9 and 22.1; n = 20, m = 5000, d = 2000 (25) 137.3 and 137.0; n = 10, m = 4000, d = 2000 (51) 69.1 and 67.0; n = 1, m = 8000,
-    // d = 1000 (250) 29.6 and 26.1; n = 32, m = 200, d = 8000 (8) 75 and 65; n = 1, m = 1000, d = 8000 (250) 116 and 39.
-    constexpr int64_t kPartsWork = 120000, kColumnWork = 25;
-    if (defer && fused && x_stride == 0 && d <= kRowPartsMax && (pl.chunks + kColumnWork) * d <= kPartsWork) {
+    // another kernel of 3 to 5 us: 1 us per 40 KB of sums and per 1000 columns (the regulariser's divisions); many sums per column
+    // go better by the threads of the kernel that shares them out.  step, us, with the sums left and finished: n = 2, m = 40000,
+    // d = 250 (256 blocks) 31.3 and 27.2; n = 2, m = 50000, d = 300 (256) 34.6 and 31.5; n = 4, m = 2000, d = 1000 (64) 20.7 and 19.7;
+    // n = 1, m = 200000, d = 80 (512) 26.8 and 25.5; n = 2, m = 700, d = 1500 (32) 19.0 and 20.4; n = 8, m = 1000, d = 1000 (32) 19.4
+    // and 20.4; n = 20, m = 5000, d = 2000 (25) 136.8 and 135.6; n = 32, m = 200, d = 8000 (8) 75 and 65; n = 1, m = 1000, d = 8000
+    // (250) 116 and 39.
+    constexpr int64_t kColumnWork = 25, kManyBlocks = 32;
+    const int64_t parts_work = pl.chunks > kManyBlocks ? 60000 : 90000;
+    if (defer && fused && x_stride == 0 && d <= kRowPartsMax && pl.chunks <= 256 && (pl.chunks + kColumnWork) * d <= parts_work) {
         *defer = GradParts{part, pl.chunks, m, x, lambda};
         return hipSuccess;
     }
-    hipLaunchKernelGGL(logreg_dense_finish_kernel, dim3((unsigned)((d + kThreads - 1) / kThreads), (unsigned)n),
-                       dim3(kThreads), 0, stream, part, x, grad, pl.chunks, m, d, lambda, x_stride);
+    const dim3 shared_grid((unsigned)((d + kSharedCols - 1) / kSharedCols), (unsigned)n);
+    // Up to sixteen sums are one round trip of a thread alone, a chain of up to eight is one of a shared column's.  Enough columns
+    // fill the chip by themselves (n = 8, m = 2000, d = 12000, 32 sums: 124.0 us the gradient by a thread per column, 125.0 shared;
+    // n = 10, m = 5000, d = 1000, 51 sums: 35.3 and 34.3).
+    constexpr int64_t kAloneMost = 16, kFewMost = 64, kFewColumns = 32768;
+    const bool alone = pl.chunks <= kAloneMost || (pl.chunks <= kFewMost && (int64_t)n * d > kFewColumns);
+    if (!alone && pl.chunks <= kFewMost)
+        hipLaunchKernelGGL(logreg_dense_finish_shared_kernel<8>, shared_grid, dim3(kSharedThreads), 0, stream, part, x, grad,
+                           pl.chunks, m, d, lambda, x_stride);
+    else if (!alone)
+        hipLaunchKernelGGL(logreg_dense_finish_shared_kernel<16>, shared_grid, dim3(kSharedThreads), 0, stream, part, x, grad,
+                           pl.chunks, m, d, lambda, x_stride);
+    else
+        hipLaunchKernelGGL(logreg_dense_finish_kernel, dim3((unsigned)((d + kThreads - 1) / kThreads), (unsigned)n),
+                           dim3(kThreads), 0, stream, part, x, grad, pl.chunks, m, d, lambda, x_stride);
     mk(K_GRAD_AUX);
     return hipGetLastError();
 }

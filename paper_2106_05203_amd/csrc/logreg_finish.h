@@ -54,16 +54,18 @@ __device__ __forceinline__ float dense_grad_entry(const float *__restrict__ part
     return dense_grad_of_sum(dense_chains(s), x_c, m, lambda);
 }
 
-// The same by THREADS / COLS threads per column (THREADS: the workgroup's; COLS >= d), each with its share of the
-// chains; `lds`: 8 * COLS doubles.  Calls put(c, entry) for every column c < d by thread c, and holds barriers.
-template <int THREADS, int COLS, class PutFn>
-__device__ __forceinline__ void dense_grad_shared(const float *__restrict__ part_w, int64_t chunks, int64_t d,
+// The same for COLS columns from c0 on by THREADS / COLS threads per column (THREADS: the workgroup's), each with its share of
+// the chains, AHEAD entries of each in flight; `lds`: 8 * COLS doubles.  Calls put(c, entry) for every column c < d by
+// thread c - c0, and holds barriers.
+template <int THREADS, int COLS, int AHEAD, class PutFn>
+__device__ __forceinline__ void dense_grad_shared(const float *__restrict__ part_w, int64_t chunks, int64_t d, int64_t c0,
                                                   const float *__restrict__ x, int64_t m, float lambda, double *lds,
                                                   PutFn put) {
-    constexpr int kShare = THREADS / COLS, kOwn = 8 / kShare, kAhead = 4;
+    constexpr int kShare = THREADS / COLS, kOwn = 8 / kShare, kAhead = AHEAD;
     static_assert(kShare * kOwn == 8, "every chain has one owner");
     static_assert(COLS % 64 == 0, "a wavefront's columns are one thread's share each");
-    const int c = threadIdx.x % COLS, share = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / COLS));
+    const int local = threadIdx.x % COLS, share = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / COLS));
+    const int64_t c = c0 + local;
     const float x_c = share == 0 && c < d ? x[c] : 0.f;
     if (c < d) {
         double s[kOwn] = {};
@@ -83,14 +85,14 @@ __device__ __forceinline__ void dense_grad_shared(const float *__restrict__ part
                 for (int u = 0; u < kOwn; ++u) s[u] += b + 8 * a + u < chunks ? (double)p[a][u] : 0.0;
         }
 #pragma unroll
-        for (int u = 0; u < kOwn; ++u) lds[(share * kOwn + u) * COLS + c] = s[u];
+        for (int u = 0; u < kOwn; ++u) lds[(share * kOwn + u) * COLS + local] = s[u];
     }
     __syncthreads();
     if (share == 0 && c < d) {
         double s[8];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) s[u] = lds[u * COLS + c];
-        put(c, dense_grad_of_sum(dense_chains(s), x_c, m, lambda));
+        for (int u = 0; u < 8; ++u) s[u] = lds[u * COLS + local];
+        put((int)c, dense_grad_of_sum(dense_chains(s), x_c, m, lambda));
     }
     __syncthreads();
 }

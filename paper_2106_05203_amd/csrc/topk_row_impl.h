@@ -289,9 +289,9 @@ __device__ void row_topk_parts(RowShared &s, float *cache, const TopkArgs &p, in
             put((int)e, dense_grad_entry(part_w, p.parts.chunks, d, e, p.parts.x[e], p.parts.m, p.parts.lambda));
         __syncthreads();
     } else if (d <= 128) {
-        dense_grad_shared<kRowThreads, 128>(part_w, p.parts.chunks, d, p.parts.x, p.parts.m, p.parts.lambda, lds, put);
+        dense_grad_shared<kRowThreads, 128, 4>(part_w, p.parts.chunks, d, 0, p.parts.x, p.parts.m, p.parts.lambda, lds, put);
     } else if (d <= 256) {
-        dense_grad_shared<kRowThreads, 256>(part_w, p.parts.chunks, d, p.parts.x, p.parts.m, p.parts.lambda, lds, put);
+        dense_grad_shared<kRowThreads, 256, 4>(part_w, p.parts.chunks, d, 0, p.parts.x, p.parts.m, p.parts.lambda, lds, put);
     } else {
         for (int64_t e = threadIdx.x; e < d; e += kRowThreads)
             cache[e] = dense_grad_entry(part_w, p.parts.chunks, d, e, p.parts.x[e], p.parts.m, p.parts.lambda) - b[e];

@@ -444,3 +444,41 @@ def test_few_workers_fill_the_chip(gpu, n, d, m):
             times[workers] = best_time(torch, lambda: h.local_grad(x, out=out))
     print(f"  {times}", flush=True)
     assert times[n] <= 2.0 * times[16] + 10.0, times
+
+
+# the kernels that add a column's partial sums: a thread per column (up to 16 blocks, or many columns), eight threads with up to
+# 8 and up to 16 entries of a chain in flight, each with a last, partial group of 64 columns, and the sums left to the Top-k kernel: an
+# iteration from the reported gradient and one that forms its own agree bit for bit (both add the chains in the same order)
+@pytest.mark.parametrize("n,d,m", [(2, 100, 700), (30, 70, 1600), (3, 130, 5000), (1, 65, 9000), (1, 1, 20000), (2, 300, 60000),
+                                   (1, 1001, 3000), (12, 3000, 400), (8, 5000, 300)])
+def test_partial_sums_of_many_blocks(gpu, n, d, m):
+    torch, binding = gpu
+    print(f"partial sums n={n} d={d} m={m}", flush=True)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(d + m)
+    A = torch.randn((n, m, d), device="cuda", generator=g) / d ** 0.5
+    y = torch.where(torch.rand((n, m), device="cuda", generator=g) < 0.5, 1.0, -1.0)
+    x = 0.3 * torch.randn(d, device="cuda", generator=g)
+    k = max(1, d // 20)
+    with binding.EF21(n, d, k, 0.3) as own, binding.EF21(n, d, k, 0.3) as given:
+        for h in (own, given):
+            h.set_problem_dense(A, y, 0.1)
+            h.set_state(x, torch.zeros((n, d), device="cuda"), None)
+        s = given.local_grad()
+        # fp64 on the GPU; per entry the first-order rounding of helpers.gradient_rounding_floor: margins summed in d / 64 + 8
+        # levels with curvature 1/4, sums of a block's rows in fp32, 16 levels and a chain of up to 64 rows per lane
+        z = torch.stack([torch.mv(A[i].double(), x.double()) for i in range(n)])
+        coef = -y * torch.sigmoid(-y.double() * z)
+        ref = torch.stack([torch.mv(A[i].double().t(), coef[i]) / m for i in range(n)]) + 0.2 * x.double() / (1 + x.double() ** 2) ** 2
+        u = 2.0 ** -24
+        dz = torch.stack([(d / 64 + 8) * u * torch.mv(A[i].abs().double(), x.abs().double()) for i in range(n)])
+        dcoef = 0.25 * dz + 32 * u * coef.abs()
+        bound = 1e-6 * ref.abs() + torch.stack([torch.mv(A[i].abs().double().t(), dcoef[i]) / m for i in range(n)]) + u
+        assert bool(((s.double() - ref).abs() <= bound).all())
+        for _ in range(3):
+            own.step()
+            given.step(given.local_grad())
+            for a, b in zip(own.get_state(), given.get_state()):
+                assert torch.equal(a, b)
+            for a, b in zip(own.get_messages(), given.get_messages()):
+                assert torch.equal(a, b)
