@@ -43,6 +43,14 @@ constexpr int64_t kSplitMinRow = 1 << 14;
 
 bool use_split(int64_t d) { return d >= kSplitMinRow; }
 
+// Rows that fit the registers of one workgroup, of which few entries are kept, are selected there: longer ones than the kernels
+// with an LDS copy take, and shorter ones from where that is quicker.  Kernel, us, 20 rows, from LDS and from registers:
+// d = 500 5.4 and 5.6; 2000 6.5 and 5.7; 8000 10.6 and 6.1.  Beyond one entry in eight the bound that the kernel takes from
+// its quads' largest entries is poor.
+bool use_row_reg(int64_t d, int64_t k) {
+    return d >= ef21::kRowRegMin && d <= ef21::kRowRegMax && k <= ef21::kRowRegMaxK && 8 * k <= d;
+}
+
 // Workspaces of the stateless ef21_topk: one per (device, stream), so that calls on different streams never share
 // one (calls on one stream run one after the other).  They live until the process ends; if a device collects more
 // than kMaxTopkStreams of them, all of that device's are freed after a device-wide wait and the list starts over.
@@ -70,7 +78,7 @@ StaticScratch g_static_ws;
 
 // Rows that the long-row path selects with a workspace (the others are selected by one workgroup each, without).
 bool topk_needs_workspace(int64_t d, int64_t k) {
-    return use_split(d) && !(d <= ef21::kRow16Max && k <= ef21::kRow16MaxK);
+    return use_split(d) && !use_row_reg(d, k);
 }
 
 }  // namespace
@@ -259,13 +267,14 @@ int enqueue_local_grad(ef21_ctx *c, const float *x, float *out, ef21::GradParts 
 int enqueue_topk(ef21::TopkArgs p, void *workspace, hipStream_t stream, const ef21::Marker &mk,
                  bool *index_ready = nullptr) {
     hipError_t st;
-    const bool split = use_split(p.d) && workspace && !(p.d <= ef21::kRow16Max && p.k <= ef21::kRow16MaxK && !p.b && !p.parts.part);
+    const bool reg = use_row_reg(p.d, p.k) && !p.parts.part;
+    const bool split = use_split(p.d) && workspace && !reg;
     if (!(split && p.k > 1)) p.agg_start = nullptr;
     if (index_ready) *index_ready = p.agg_start != nullptr;
-    if (use_split(p.d) && p.d <= ef21::kRow16Max && p.k <= ef21::kRow16MaxK && !p.b && !p.parts.part) {
-        st = ef21::launch_topk_row16(p, stream);
+    if (reg) {
+        st = ef21::launch_topk_row_reg(p, stream);
         mk(ef21::K_TOPK_ROW);
-    } else if (use_split(p.d) && workspace) {
+    } else if (split) {
         st = ef21::launch_topk_split(p, workspace, stream, mk);
     } else {
         st = ef21::launch_topk_row(p, stream);

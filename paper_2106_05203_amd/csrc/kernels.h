@@ -90,19 +90,20 @@ struct TopkArgs {
     int64_t agg_nblk;
 };
 
-// Rows this long can be handed to launch_topk_row as unreduced gradients (TopkArgs::parts).
-constexpr int64_t kRowPartsMax = 8192;
+// Rows this long can be handed to launch_topk_row as unreduced gradients (TopkArgs::parts).  Longer ones are finished by a
+// kernel that the whole chip shares, and launch_topk_row_reg selects from the differences.  step, us, unreduced and
+// finished: n = 4, m = 500, d = 700 14.0 and 15.6; n = 10, m = 1000, d = 800 18.5 and 19.4; n = 20, m = 2000, d = 1000 42.4 and 40.3;
+// n = 4, m = 250, d = 2000 17.8 and 16.6.
+constexpr int64_t kRowPartsMax = 900;
 
 // One workgroup per row: a histogram pass over the row and a ranking of the threshold's bin (three histogram passes where
 // the bin is crowded), then an ordered emission.  Needs no workspace; rows of at most 16384 entries.
 hipError_t launch_topk_row(const TopkArgs &p, hipStream_t stream);
 
-// One workgroup per row that reads the row once and keeps 16 bits of every key in LDS: rows of kRow16Min to
-// kRow16Max entries given as they are (p.b == nullptr), k <= kRow16MaxK (meant for rows too long for
-// launch_topk_row's LDS copy; the lower limit keeps the kernel's later use of the row copy's LDS, 15 KB of bitmap
-// and prefix words, inside the 2 d bytes of the copy).  No workspace.  Other shapes: hipErrorInvalidValue.
-constexpr int64_t kRow16Min = 16384, kRow16Max = 61440, kRow16MaxK = 1024;
-hipError_t launch_topk_row16(const TopkArgs &p, hipStream_t stream);
+// One workgroup per row that keeps the row in registers: rows of kRowRegMin to kRowRegMax entries, given as they are or as
+// a difference, k <= kRowRegMaxK.  No workspace.  Other shapes: hipErrorInvalidValue.
+constexpr int64_t kRowRegMin = 512, kRowRegMax = 61440, kRowRegMaxK = 1024;
+hipError_t launch_topk_row_reg(const TopkArgs &p, hipStream_t stream);
 
 // Many workgroups per row for long rows.  Workspace layout and size: topk_split_workspace_bytes.
 size_t topk_split_workspace_bytes(int32_t n, int64_t d, int64_t k);

@@ -70,7 +70,7 @@ hipError_t launch_topk_row(const TopkArgs &p, hipStream_t stream) {
     } else if (p.d <= kRowCache) {                    // more rows than compute units: see kRowCache
         launch_uncached(p, stream);
     } else {
-        return hipErrorInvalidValue;                  // longer rows: launch_topk_row16, launch_topk_split
+        return hipErrorInvalidValue;                  // longer rows: launch_topk_row_reg, launch_topk_split
     }
     return hipGetLastError();
 }

@@ -244,7 +244,7 @@ __device__ void row_topk(RowShared &s, const TopkArgs &p, int64_t row) {
 // on the copy leaves room for one workgroup per compute unit instead of two, so more than 256 rows are read from L2 in
 // every pass (row_topk).  ef21_topk, us, from L2 and from LDS: 20 rows of 12000, k = 1000 15.9 and 14.7; 100 of 16383 17.6 and
 // 15.7; 300 of 9000 15.7 and 20.7; 1000 of 9000 31.9 and 43.6.
-constexpr int kRowCache = 16384, kRowCacheShort = (int)kRowPartsMax;
+constexpr int kRowCache = 16384, kRowCacheShort = 8192;
 
 template <bool DIFF, int UPDATE>
 __device__ void row_topk_cached(RowShared &s, float *cache, const TopkArgs &p, int64_t row) {

@@ -105,6 +105,67 @@ def test_rows_held_in_lds_as_key_prefixes(gpu, oracle, d, k):
     check(gpu, oracle, V, k)
 
 
+def rows_for_registers(d, k, seed):
+    """One row per way through the kernel that holds the row in registers: an ordinary one, ties everywhere, fewer than k
+    non-zeros, magnitudes all alike (the list or the threshold's bin overflows), large entries side by side, a threshold far
+    above the bound (beyond the window), NaN and infinities, large entries at the row's very end."""
+    rng = np.random.default_rng(seed)
+    V = rng.standard_normal((8, d)).astype(np.float32)
+    V[1] = np.round(V[1] * 2) / 2
+    V[2] = np.where(rng.random(d) < 0.5 * k / d, V[2], np.where(V[2] > 0, 0.0, -0.0))
+    V[3] = 10 + 0.01 * V[3]
+    V[4, d // 3:d // 3 + min(2 * k, d // 4)] *= 100
+    V[5, ::7] *= np.exp(20 * rng.random(V[5, ::7].size)).astype(np.float32)
+    V[6, ::d // 5] = np.nan
+    V[6, 1::d // 3] = np.inf
+    V[7, -3:] = [1e30, -1e30, 1e30]
+    return V.astype(np.float32)
+
+
+def first_by_magnitude(V, k):
+    """Ascending positions of the k largest magnitude keys, ties to the lower position (NaN above infinity, as the
+    kernels order the bits)."""
+    key = (V.view(np.int32) & 0x7fffffff).astype(np.int64)
+    return np.sort(np.argsort(-key, axis=1, kind="stable")[:, :k], axis=1)
+
+
+@pytest.mark.parametrize("d", [512, 513, 1025, 4095, 4096, 4097, 8192, 8195, 12289, 16385, 24577, 36865, 53249, 61439, 61440])
+def test_rows_held_in_registers(gpu, d):
+    """The edges of every length of the register array (4096 entries a quad), k up to its limits."""
+    for k in sorted({1, max(1, d // 100), min(d // 8, 1024)}):
+        V = rows_for_registers(d, k, d + k)
+        idx, val = run_gpu(gpu, V, k)
+        ref = first_by_magnitude(V, k)
+        assert np.array_equal(idx, ref), (d, k)
+        assert same_bits(val, np.take_along_axis(V, ref, axis=1)), (d, k)
+
+
+@pytest.mark.parametrize("d", [513, 4097, 12289, 24577, 50001, 61440])
+def test_differences_held_in_registers(gpu, d):
+    """The same for grad - g_i inside a step: message, and g_i updated at the kept positions only."""
+    torch, binding = gpu
+    k = min(d // 8, 500)
+    S = rows_for_registers(d, k, d)
+    S[6] = S[0]                                        # (a step keeps NaN in its state: not compared here)
+    G = np.random.default_rng(d + 1).standard_normal(S.shape).astype(np.float32)
+    G[1:3] = 0.0                                       # ties and zeros stay what they are
+    n = S.shape[0]
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    with binding.EF21(n, d, k, 0.1) as h:
+        h.set_state(x=torch.zeros(d, device="cuda"), g_i=dev(G))
+        h.step(dev(S))
+        idx, val = (t.cpu().numpy() for t in h.get_messages())
+        _, g_i, _ = (t.cpu().numpy() for t in h.get_state())
+    diff = S - G
+    ref = first_by_magnitude(diff, k)
+    assert np.array_equal(idx, ref)
+    kept = np.take_along_axis(diff, ref, axis=1)
+    assert same_bits(val, kept)
+    want = G.copy()
+    np.put_along_axis(want, ref, np.take_along_axis(G, ref, axis=1) + kept, axis=1)
+    assert same_bits(g_i, want)
+
+
 @pytest.mark.parametrize("d,k", [(70001, 700), (262144, 5), (300007, 3000), (1_000_003, 999), (70001, 1), (1_000_003, 1),
                                  (262144, 1)])
 def test_long_rows_ragged(gpu, oracle, d, k):
