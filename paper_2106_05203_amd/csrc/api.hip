@@ -127,6 +127,7 @@ struct ef21_ctx {
     void *csr_index = nullptr;      // column-range index of the attached CSR problem
     bool csr_indexed = false;
     int64_t nnz = 0;                // entries of the attached CSR problem
+    bool ef_started = false;        // a round of Algorithm 4 has left thresholds in topk_ws
     // Algorithm 3 (allocated by the first EF21_PLUS step)
     int32_t *plus_idx = nullptr;    // [2][n][k]: C(s), then C(s - g_i)
     float *plus_val = nullptr;
@@ -765,11 +766,22 @@ static int enqueue_plus(ef21_ctx *h, const float *grads, bool take_step, const e
 
 // One round of Algorithm 4 (EF) on the handle: the errors e_i live in g_i, g receives (1/n) sum_i w_i.
 static int enqueue_classic_ef(ef21_ctx *h, const float *grads, const ef21::Marker &mk) {
-    hipError_t st = ef21::launch_ef_accumulate(grads, h->g_i, h->n, h->d, h->gamma, h->stream);   // p_i over e_i
-    mk(ef21::K_PLUS);
-    if (st != hipSuccess) return fail_hip(st, "EF accumulation launch");
+    hipError_t st;
     ef21::TopkArgs p{h->g_i, nullptr, h->n, h->d, h->k, h->msg_idx, h->msg_val, h->g_i};   // w_i = C(p_i), e_i = p_i - w_i
     p.warm = 1;
+    // p_i over e_i: by the pass of the long-row Top-k that reads the rows, once there are thresholds to start from, else by a
+    // kernel of its own.  A round, us, in two passes and in one: n = 5, d = 1 000 003, k = 50 000 46.4 and 42.2; n = 20, d = 1.5
+    // million, k = 60 000 141 and 119; n = 8, d = 11.2 million, k = 112 000 381 and 322.
+    const bool split = use_split(h->d) && h->topk_ws && !use_row_reg(h->d, h->k) && h->k > 1;
+    if (split && h->ef_started) {
+        p.add = grads;
+        p.add_scale = h->gamma;
+    } else {
+        st = ef21::launch_ef_accumulate(grads, h->g_i, h->n, h->d, h->gamma, h->stream);
+        mk(ef21::K_PLUS);
+        if (st != hipSuccess) return fail_hip(st, "EF accumulation launch");
+    }
+    h->ef_started = true;
     bool index_ready = false;
     want_message_index(h, &p);
     if (int rc = enqueue_topk(p, h->topk_ws, h->stream, mk, &index_ready)) return rc;

@@ -1,7 +1,8 @@
 // EF, the original error feedback (Algorithm 4 of the EF21 paper), kept beside EF21 as the method it is
 // compared with.  One round at the current x, with the errors e_i in the place of EF21's g_i:
 //   p_i = e_i + gamma grad f_i(x)   written over e_i (one fused multiply-add per entry; every entry changes,
-//                                   unlike EF21's state, which changes in k places);
+//                                   unlike EF21's state, which changes in k places); on long rows, from the second
+//                                   round on, by the Top-k's own pass over them (TopkArgs::add);
 //   w_i = C(p_i)                    the library's Top-k on the rows of e;
 //   e_i = p_i - w_i                 zero at the kept positions, written by the Top-k's emission;
 //   x   = x - (1/n) sum_i w_i       the aggregation pass of Algorithm 2's line 8 from a zero vector, step 1.

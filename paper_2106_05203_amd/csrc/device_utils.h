@@ -51,6 +51,15 @@ __device__ __forceinline__ void store4_any(float *p, const float4 &v) {
     t.w = v.w;
     *reinterpret_cast<v4f *>(p) = t;
 }
+__device__ __forceinline__ void stream_store4_any(float *p, const float4 &v) {
+    typedef float v4f __attribute__((ext_vector_type(4), aligned(4)));
+    v4f t;
+    t.x = v.x;
+    t.y = v.y;
+    t.z = v.z;
+    t.w = v.w;
+    __builtin_nontemporal_store(t, reinterpret_cast<v4f *>(p));
+}
 __device__ __forceinline__ float stream_load(const float *p) { return __builtin_nontemporal_load(p); }
 __device__ __forceinline__ int32_t stream_load(const int32_t *p) { return __builtin_nontemporal_load(p); }
 

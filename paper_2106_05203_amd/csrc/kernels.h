@@ -88,6 +88,10 @@ struct TopkArgs {
     int32_t *agg_start;
     int32_t agg_shift;
     int64_t agg_nblk;
+    // launch_topk_split with warm = 1, k >= 2, b == nullptr and g_i == a only: if add != nullptr the rows are
+    // a + add_scale * add (one fused multiply-add per entry), written over a by the pass that reads them
+    const float *add;
+    float add_scale;
 };
 
 // Rows this long can be handed to launch_topk_row as unreduced gradients (TopkArgs::parts).  Longer ones are finished by a

@@ -82,6 +82,8 @@ constexpr uint32_t kWarmBelow = 1u << 20;
 constexpr int kTieCap = 1024;                // entries of T's bin that are ranked directly (one per thread)
 constexpr int kWarmSlots = 1;                // remembered thresholds per row (TopkArgs::warm = 1 .. kWarmSlots)
 enum CollectMode { kColdPass = 0, kWarmPass = 1, kSecondPass = 2 };
+// TopkArgs::add, and how the sums are stored: as lines that stay in the caches for the next round, or past them.
+enum AddMode { kNoAdd = 0, kAddKept = 1, kAddStreamed = 2 };
 
 struct __attribute__((aligned(64))) RowInfo {     // one cache line per row
     uint32_t key_lo, shift;       // lower bound of the candidate keys and bin width (first collect pass)
@@ -409,13 +411,18 @@ __device__ __forceinline__ void drain_ring(const Ring &ring, uint32_t flushed, u
 // piece of a row has a checked tail.
 // MODE: kColdPass key_lo from the sample; kWarmPass from the threshold remembered in slot p.warm if there is
 // one, else from the sample; kSecondPass: only rows whose warm start failed, from the sample, into hist_b.
+// ADD != kNoAdd (kWarmPass): the rows are a + add_scale * add, written over a on the way.  A sample would find some entries of the row
+// old and some new, so a row without a remembered threshold collects nothing here and is left to the second pass.
 // All kBlk threads of the workgroup must call; s, rings and wg_total are the workgroup's.
-template <bool DIFF, int MODE, bool RESID, class Ring>
+template <bool DIFF, int MODE, bool RESID, int ADD, class Ring>
 __device__ __forceinline__ void collect_rows(const TopkArgs &p, const Ws &w, RowShared &s, Ring (&rings)[kBlkWaves],
                                              uint32_t &wg_total) {
     const int64_t row = blockIdx.y, d = p.d;
     const float *a = p.a + row * d;
-    const float *b = DIFF ? p.b + row * d : nullptr;
+    static_assert(ADD == kNoAdd || (!DIFF && !RESID && MODE == kWarmPass), "see above");
+    constexpr bool TWO = DIFF || ADD != kNoAdd;      // two arrays are read
+    const float *b = DIFF ? p.b + row * d : (ADD ? p.add + row * d : nullptr);
+    float *const out = ADD ? p.g_i + row * d : nullptr;
     RowInfo *info = w.info + row;
     CandFilter f;
     f.hist = s.hist;
@@ -444,6 +451,9 @@ __device__ __forceinline__ void collect_rows(const TopkArgs &p, const Ws &w, Row
             const uint32_t T = info->warm_T[p.warm - 1];
             f.key_lo = T > kWarmBelow ? T - kWarmBelow : 0u;
             f.shift = warm;
+        } else if constexpr (ADD) {
+            f.key_lo = 0x80000000u;                  // above every key
+            f.shift = w.rule.widest;
         } else {
             const Guess g = guess_from_sample<DIFF>(s, a, b, d, w.rule);
             f.key_lo = g.key_lo;
@@ -456,7 +466,7 @@ __device__ __forceinline__ void collect_rows(const TopkArgs &p, const Ws &w, Row
             info->ntie = 0u;                 // the count kernel appends to the list
             info->tie_min = 0xffffffffu;
             info->tie_max = 0u;
-            info->warm_used = warm ? 1u : 0u;
+            info->warm_used = warm || ADD ? 1u : 0u;
         }
     }
     for (int i = threadIdx.x; i < kHistBins; i += kBlk) s.hist[i] = 0u;
@@ -485,7 +495,7 @@ __device__ __forceinline__ void collect_rows(const TopkArgs &p, const Ws &w, Row
 #pragma unroll
             for (int u = 0; u < kSteps; ++u) {
                 va[u] = stream_load4_any(a + base + u * kStep + lane * 4);
-                if constexpr (DIFF) vb[u] = stream_load4_any(b + base + u * kStep + lane * 4);
+                if constexpr (TWO) vb[u] = stream_load4_any(b + base + u * kStep + lane * 4);
             }
         }
         for (; base + kGroup <= hi; base += kGroup) {
@@ -495,23 +505,25 @@ __device__ __forceinline__ void collect_rows(const TopkArgs &p, const Ws &w, Row
             for (int u = 0; u < kSteps; ++u) {
                 const int64_t at = more ? base + kGroup + u * kStep + lane * 4 : lo;
                 na[u] = stream_load4_any(a + at);
-                if constexpr (DIFF) nb[u] = stream_load4_any(b + at);
+                if constexpr (TWO) nb[u] = stream_load4_any(b + at);
             }
 #pragma unroll
             for (int u = 0; u < kSteps; ++u) {
                 const float ea[VEC] = {va[u].x, va[u].y, va[u].z, va[u].w};
                 float eb[VEC] = {}, v[VEC];
-                if constexpr (DIFF) {
+                if constexpr (TWO) {
                     eb[0] = vb[u].x; eb[1] = vb[u].y; eb[2] = vb[u].z; eb[3] = vb[u].w;
                 }
 #pragma unroll
-                for (int t = 0; t < VEC; ++t) v[t] = DIFF ? ea[t] - eb[t] : ea[t];
+                for (int t = 0; t < VEC; ++t) v[t] = DIFF ? ea[t] - eb[t] : (ADD ? fmaf(p.add_scale, eb[t], ea[t]) : ea[t]);
+                if constexpr (ADD == kAddKept) store4_any(out + base + u * kStep + lane * 4, make_float4(v[0], v[1], v[2], v[3]));
+                if constexpr (ADD == kAddStreamed) stream_store4_any(out + base + u * kStep + lane * 4, make_float4(v[0], v[1], v[2], v[3]));
                 append_candidates<VEC, true, RESID>(v, ea, eb, base + u * kStep + lane * VEC, hi, f, ring, lane, slot, cnt, flushed);
             }
 #pragma unroll
             for (int u = 0; u < kSteps; ++u) {
                 va[u] = na[u];
-                if constexpr (DIFF) vb[u] = nb[u];
+                if constexpr (TWO) vb[u] = nb[u];
             }
         }
         if (base < hi) {                             // checked tail, less than a group, all loads issued first
@@ -522,13 +534,17 @@ __device__ __forceinline__ void collect_rows(const TopkArgs &p, const Ws &w, Row
                 for (int t = 0; t < VEC; ++t) {
                     const int64_t e = base + u * kStep + lane * VEC + t;
                     ea[u][t] = e < hi ? a[e] : 0.f;
-                    eb[u][t] = DIFF && e < hi ? b[e] : 0.f;
+                    eb[u][t] = TWO && e < hi ? b[e] : 0.f;
                 }
 #pragma unroll
             for (int u = 0; u < kSteps; ++u) {
                 float v[VEC];
 #pragma unroll
-                for (int t = 0; t < VEC; ++t) v[t] = DIFF ? ea[u][t] - eb[u][t] : ea[u][t];
+                for (int t = 0; t < VEC; ++t) {
+                    v[t] = DIFF ? ea[u][t] - eb[u][t] : (ADD ? fmaf(p.add_scale, eb[u][t], ea[u][t]) : ea[u][t]);
+                    const int64_t e = base + u * kStep + lane * VEC + t;
+                    if (ADD && e < hi) out[e] = v[t];
+                }
                 append_candidates<VEC, false, RESID>(v, ea[u], eb[u], base + u * kStep + lane * VEC, hi, f, ring, lane, slot, cnt, flushed);
             }
         }
@@ -546,12 +562,12 @@ __device__ __forceinline__ void collect_rows(const TopkArgs &p, const Ws &w, Row
     if (row_total && threadIdx.x == 0 && wg_total) atomicAdd(row_total, wg_total);
 }
 
-template <bool DIFF, int MODE>
+template <bool DIFF, int MODE, int ADD = kNoAdd>
 __global__ __launch_bounds__(kBlk) void split_collect_kernel(TopkArgs p, Ws w) {
     __shared__ RowShared s;
     __shared__ StageRing<false> rings[kBlkWaves];
     __shared__ uint32_t wg_total;
-    collect_rows<DIFF, MODE, false>(p, w, s, rings, wg_total);
+    collect_rows<DIFF, MODE, false, ADD>(p, w, s, rings, wg_total);
 }
 
 // The second pass of the two selections of Algorithm 3 in one launch: grid (.., n, 2).
@@ -559,8 +575,8 @@ __global__ __launch_bounds__(kBlk) void split_second_pair_kernel(TopkArgs pp, Ws
     __shared__ RowShared s;
     __shared__ StageRing<true> rings[kBlkWaves];
     __shared__ uint32_t wg_total;
-    if (blockIdx.z == 0) collect_rows<false, kSecondPass, false>(pp, wp, s, rings, wg_total);
-    else collect_rows<true, kSecondPass, true>(pm, wm, s, rings, wg_total);
+    if (blockIdx.z == 0) collect_rows<false, kSecondPass, false, kNoAdd>(pp, wp, s, rings, wg_total);
+    else collect_rows<true, kSecondPass, true, kNoAdd>(pm, wm, s, rings, wg_total);
 }
 
 // ---------------------------------------------------------------- collect, two selections in one pass
@@ -1371,6 +1387,11 @@ hipError_t launch_after_collect(const TopkArgs &p, const Ws &w, hipStream_t stre
 }
 }  // namespace
 
+// Rows of up to this size in all are found in the 256 MB of the last cache by the next round.  A round of EF, us, stored to stay
+// there and streamed past: n = 8, d = 4 million (128 MB) 108 and 119; 6 million (192) 156 and 179; 7 million (224) 207 and
+// 205; 9 million (288) 304 and 264.
+constexpr int64_t kKeptBytes = (int64_t)200 << 20;
+
 hipError_t launch_topk_split(const TopkArgs &p, void *workspace, hipStream_t stream, const Marker &mk) {
     Ws w;
     layout(p.n, p.d, (char *)workspace, &w);
@@ -1378,8 +1399,15 @@ hipError_t launch_topk_split(const TopkArgs &p, void *workspace, hipStream_t str
     if (p.g_i && p.g_i != (p.b ? p.b : p.a)) return hipErrorInvalidValue;
     if (p.warm < 0 || p.warm > kWarmSlots) return hipErrorInvalidValue;
     if (!index_fits(p, w) || (p.agg_start && p.k == 1)) return hipErrorInvalidValue;
+    if (p.add && (p.b || p.g_i != p.a || p.warm == 0 || p.k == 1)) return hipErrorInvalidValue;
     if (p.k == 1) return launch_argmax(p, w, stream, mk);
-    launch_collect(p, w, p.warm > 0 ? kWarmPass : kColdPass, stream);
+    const dim3 add_grid((unsigned)w.G, (unsigned)p.n), block(kBlk);
+    if (p.add && (int64_t)p.n * p.d * 4 <= kKeptBytes)
+        hipLaunchKernelGGL((split_collect_kernel<false, kWarmPass, kAddKept>), add_grid, block, 0, stream, p, w);
+    else if (p.add)
+        hipLaunchKernelGGL((split_collect_kernel<false, kWarmPass, kAddStreamed>), add_grid, block, 0, stream, p, w);
+    else
+        launch_collect(p, w, p.warm > 0 ? kWarmPass : kColdPass, stream);
     mk(K_TOPK_COLLECT);
     hipError_t st = hipGetLastError();
     if (st != hipSuccess) return st;

@@ -157,3 +157,31 @@ def test_errors_are_cleared_by_every_emission(gpu, oracle, n, d, k):
             np.put_along_axis(w, st.msg_idx.astype(np.int64), st.msg_val, axis=1)
             # n fp32 additions and one rounding of 1/n, relative to the sum of the magnitudes
             assert np.all(np.abs(mean_w - w.mean(axis=0)) <= (n + 2) * 2.0 ** -24 * np.abs(w).mean(axis=0)), f"round {t}: mean"
+
+
+@pytest.mark.parametrize("n,d,k", [(3, 61_441, 700), (2, 100_003, 5001), (5, 300_002, 2), (9, 6_000_001, 3000)])
+def test_accumulation_inside_the_selection(gpu, n, d, k):
+    """Long rows: from the second round on p = e + gamma s is formed by the pass that selects (the last case: rows beyond what
+    the caches keep).  Rounds whose remembered threshold holds, is far too high (the gradients shrink a thousandfold, the errors are
+    spent) and far too low, a round without gradients, and a tail shorter than a group of loads."""
+    torch, binding = gpu
+    gamma = 0.25
+    g = torch.Generator(device="cuda")
+    g.manual_seed(d)
+    e = torch.zeros((n, d), device="cuda")
+    x = torch.zeros(d, device="cuda")
+    with binding.EF21(n, d, k, gamma) as h:
+        h.set_state(x=x, g_i=e)
+        for scale in (1.0, 1.0, 1e-3, 1e3, 0.0, 1.0):
+            s = torch.randn((n, d), device="cuda", generator=g) * scale
+            h.step(s, binding.CLASSIC_EF)
+            # a power of two times s is exact, so the sum has the one rounding of the fused multiply-add
+            p = e + gamma * s
+            key = (p.view(torch.int32) & 0x7fffffff).long() * 2**31 + (2**31 - 1 - torch.arange(d, device="cuda"))
+            at = torch.stack([row.topk(k).indices.sort().values for row in key])
+            idx, val = h.get_messages()
+            assert torch.equal(idx.long(), at), (n, d, k, scale)
+            assert torch.equal(val, p.gather(1, at)), (n, d, k, scale)
+            e = p.scatter(1, at, 0.0)
+            _, state, _ = h.get_state()
+            assert torch.equal(state, e), (n, d, k, scale)
