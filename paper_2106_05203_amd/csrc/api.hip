@@ -270,7 +270,7 @@ int enqueue_topk(ef21::TopkArgs p, void *workspace, hipStream_t stream, const ef
     hipError_t st;
     const bool reg = use_row_reg(p.d, p.k) && !p.parts.part;
     const bool split = use_split(p.d) && workspace && !reg;
-    if (!(split && p.k > 1)) p.agg_start = nullptr;
+    if (!reg && !(split && p.k > 1)) p.agg_start = nullptr;
     if (index_ready) *index_ready = p.agg_start != nullptr;
     if (reg) {
         st = ef21::launch_topk_row_reg(p, stream);
@@ -285,7 +285,7 @@ int enqueue_topk(ef21::TopkArgs p, void *workspace, hipStream_t stream, const ef
     return EF21_OK;
 }
 
-// Asks the Top-k (long rows only) to write the index of the messages that launch_aggregate would otherwise build.
+// Asks the Top-k (where its kernel can) to write the index of the messages that launch_aggregate would otherwise build.
 void want_message_index(const ef21_ctx *c, ef21::TopkArgs *p) {
     const int shift = ef21::aggregate_index_shift(c->n, c->k, c->d);
     if (shift < 0) return;

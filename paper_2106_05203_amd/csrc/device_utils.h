@@ -125,6 +125,12 @@ __device__ __forceinline__ uint32_t wave_append(bool has, uint32_t *counter) {
     return __shfl(base, first, kWave) + lanes_below(m);
 }
 
+// *p += v in LDS without the round trip of reading it first.  The LDS executes one wavefront's accesses in order, so where
+// only that wavefront adds, and its lanes to different places at a time, the order of the additions is that of the code.
+__device__ __forceinline__ void lds_add(float *p, float v) {
+    __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
 __device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t v) {
     const int lane = lane_id();
 #pragma unroll

@@ -83,7 +83,7 @@ struct TopkArgs {
     int32_t warm;      // launch_topk_split only, k >= 2: 0, or 1 = the row thresholds of the last such call on this
                        // workspace serve as the first guess of this call's (the result never depends on it; meant
                        // for consecutive iterations of one algorithm on one state)
-    // launch_topk_split with k > 1 only: if agg_start != nullptr the emission also writes the index that
+    // launch_topk_split with k > 1 and launch_topk_row_reg only: if agg_start != nullptr the emission also writes the index that
     // launch_aggregate needs of the messages (aggregate_index_shift), so that its own indexing kernel can be skipped
     int32_t *agg_start;
     int32_t agg_shift;

@@ -150,6 +150,16 @@ __device__ __forceinline__ void count_bitmap(RegShared<R> &sh) {
     __syncthreads();
 }
 
+// The index of the row's message that launch_aggregate needs (TopkArgs::agg_start), after count_bitmap: a block of
+// coordinates is a whole number of the bitmap's words.
+template <int R>
+__device__ __forceinline__ void write_index(const RegShared<R> &sh, const TopkArgs &p, int64_t row) {
+    if (!p.agg_start) return;
+    int32_t *start = p.agg_start + row * (p.agg_nblk + 1);
+    for (int b = threadIdx.x; b <= (int)p.agg_nblk; b += kRowThreads)
+        start[b] = b < (int)p.agg_nblk ? (int32_t)sh.prefix[b << (p.agg_shift - 5)] : (int32_t)p.k;
+}
+
 // `bits` without all but its `n` lowest set bits.
 __device__ __forceinline__ uint32_t lowest_bits(uint32_t bits, uint32_t n) {
     uint32_t rest = bits;
@@ -248,6 +258,7 @@ __device__ void select_by_bisection(RegShared<R> &sh, const TopkArgs &p, const f
     }
     __syncthreads();
     count_bitmap(sh);
+    write_index(sh, p, blockIdx.x);
     if ((uint32_t)tid < k) {                                 // one kept entry per thread
         int word = 0;                                        // the last word with prefix <= tid
         for (int step = 1024; step; step >>= 1)              // kMapWords <= 2048
@@ -471,6 +482,7 @@ __global__ __launch_bounds__(kRowThreads) void topk_row_reg_kernel(TopkArgs p) {
 
     // ---- 4: the places of the kept entries
     count_bitmap(sh);
+    write_index(sh, p, row);
     int32_t *out_idx = p.out_idx + row * p.k;
     float *out_val = p.out_val + row * p.k;
     for (uint32_t i = tid; i < n_flat; i += kRowThreads) {
@@ -499,6 +511,7 @@ void launch(const TopkArgs &p, hipStream_t stream) {
 hipError_t launch_topk_row_reg(const TopkArgs &p, hipStream_t stream) {
     if ((p.g_i && p.g_i != (p.b ? p.b : p.a)) || p.parts.part || p.d < kRowRegMin || p.d > kRowRegMax || p.k > kRowRegMaxK)
         return hipErrorInvalidValue;
+    if (p.agg_start && (p.agg_shift < 5 || p.agg_nblk != ((p.d - 1) >> p.agg_shift) + 1)) return hipErrorInvalidValue;
     if (p.d <= kQuadStep) launch<1>(p, stream);
     else if (p.d <= 2 * kQuadStep) launch<2>(p, stream);
     else if (p.d <= 3 * kQuadStep) launch<3>(p, stream);

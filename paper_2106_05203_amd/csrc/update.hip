@@ -268,7 +268,7 @@ __global__ __launch_bounds__(kThreads) void aggregate_many_kernel(const int32_t 
     }
 }
 
-// Small problems (d <= kSmallD, n * k <= kSmallEntries, n * ceil(k / 64) <= kSmallSteps): one workgroup, one launch.  All threads stage the
+// Small problems (aggregate_is_small): one workgroup, one launch.  All threads stage the
 // messages in LDS; then ONE wavefront adds them to the LDS accumulator worker by worker, 64 entries of a
 // worker per step (positions inside a message are distinct, and a wavefront's LDS accesses execute in
 // program order, so no barrier is needed between workers) while the other wavefronts fetch g and x.
@@ -276,6 +276,9 @@ constexpr int kSmallThreads = 1024, kSmallPer = 8;
 constexpr int kSmallD = 16384, kSmallEntries = kSmallThreads * kSmallPer;
 constexpr int kScanEntries = 128;    // messages in all that every coordinate can look through (n = 20, k = 4: 4.8 -> 2.8 us)
 constexpr int kSmallFetch = 4;      // coordinates per thread fetched ahead (d <= 4096)
+constexpr int kSmallAhead = 8;      // steps whose pairs are in registers (kernel, us: n = 20, d = 2000, k = 20 5.3 -> 4.9)
+constexpr int kSmallLanes = 32;     // pairs of a worker up to which an LDS atomic is the quicker addition (n = 20, d = 300, k = 8
+                                    // 4.5 -> 4.0 us; n = 16, d = 12000, k = 400 16.6 -> 19.2)
 constexpr int kSmallSteps = 512;    // at most this many sequential steps of the adding wavefront
 
 template <bool STEP>
@@ -293,10 +296,14 @@ __global__ __launch_bounds__(kSmallThreads) void aggregate_small_kernel(const in
     float v[kSmallPer];
 #pragma unroll
     for (int u = 0; u < kSmallPer; ++u) {
-        const int64_t t = tid + (int64_t)u * kSmallThreads;
-        const int64_t at = t < total ? t : 0;
-        e[u] = idx[at];
-        v[u] = val[at];
+        e[u] = 0;
+        v[u] = 0.f;
+        if ((int64_t)u * kSmallThreads < total) {                // uniform
+            const int64_t t = tid + (int64_t)u * kSmallThreads;
+            const int64_t at = t < total ? t : 0;
+            e[u] = idx[at];
+            v[u] = val[at];
+        }
     }
     for (int64_t j = tid; j < d; j += kSmallThreads) acc[j] = 0.f;
 #pragma unroll
@@ -334,10 +341,31 @@ __global__ __launch_bounds__(kSmallThreads) void aggregate_small_kernel(const in
     }
     float gj[kSmallFetch], xj[kSmallFetch];
     if (tid < kWave) {
-        for (int32_t w = 0; w < n; ++w) {           // worker order
-            for (int64_t i0 = 0; i0 < k; i0 += kWave) {
-                const int64_t i = i0 + lane;
-                if (i < k) acc[m_idx[w * k + i]] += m_val[w * k + i];
+        // worker order; the pairs of eight steps (a worker's next 64 pairs each) are read before the first of them is added
+        const int per = (int)((k + kWave - 1) / kWave), steps = n * per;
+        int at = 0, i0 = 0;                         // of the next step: the worker's first pair, and how far into the message
+        for (int s0 = 0; s0 < steps; s0 += kSmallAhead) {
+            int32_t e8[kSmallAhead];
+            float v8[kSmallAhead];
+            bool in[kSmallAhead];
+#pragma unroll
+            for (int u = 0; u < kSmallAhead; ++u) {
+                in[u] = s0 + u < steps && i0 + lane < k;
+                const int from = in[u] ? at + i0 + lane : 0;
+                e8[u] = m_idx[from];
+                v8[u] = m_val[from];
+                i0 += kWave;
+                if (i0 >= k) {
+                    i0 = 0;
+                    at += (int)k;
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < kSmallAhead; ++u) {
+                if (in[u]) {
+                    if (k <= kSmallLanes) lds_add(acc + e8[u], v8[u]);
+                    else acc[e8[u]] += v8[u];
+                }
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
                 __builtin_amdgcn_wave_barrier();
             }
@@ -416,8 +444,17 @@ size_t aggregate_index_bytes(int32_t n, int64_t d) {      // for the shorter of 
 }
 
 namespace {
+// One workgroup adds one step after the other, 0.12 us each, and walks all coordinates; the kernels with a wavefront or
+// four per block of coordinates take a message index, which launch_topk_row_reg and launch_topk_split write with the message.
+// step with supplied gradients, us, small and not: 8 x 1000, k = 100 (16 steps) 10.5 and 11.0; 15 x 1000, k = 20 10.5 and 12.2;
+// 10 x 5000, k = 50 11.3 and 12.1; 8 x 2000, k = 200 (32) 12.7 and 11.3; 8 x 12000, k = 60 12.3 and 11.1; 20 x 2000, k = 20 11.5 and
+// 10.1; 32 x 2000, k = 200 (128) 25.1 and 10.5; 16 x 12000, k = 400 (112) 26.6 and 11.8.  Up to 1024 coordinates and 2048 pairs
+// the sums are those of the iteration in one launch (small_step.hip) to the bit, in worker order, so they stay here.
+constexpr int64_t kSmallReach = 24, kSmallStep1 = 1024, kSmallPairs1 = 2048;
 bool aggregate_is_small(int32_t n, int64_t k, int64_t d) {
-    return d <= kSmallD && (int64_t)n * k <= kSmallEntries && (int64_t)n * ((k + kWave - 1) / kWave) <= kSmallSteps;
+    const int64_t pairs = (int64_t)n * k, steps = (int64_t)n * ((k + kWave - 1) / kWave);
+    if (d > kSmallD || pairs > kSmallEntries || steps > kSmallSteps) return false;
+    return (d <= kSmallStep1 && pairs <= kSmallPairs1) || (n < kManyWorkers && steps + d / 512 <= kSmallReach);
 }
 }  // namespace
 

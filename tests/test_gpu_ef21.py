@@ -725,3 +725,34 @@ def test_few_entries_on_many_blocks(gpu, n, d, k, where):
                 times[kept] = best_time(torch, lambda: h.step(grads))
         print(f"  {times}", flush=True)
         assert times[1] <= 1.5 * times[2] + 20.0, times
+
+
+@pytest.mark.parametrize("n,d,k", [(2, 512, 64), (15, 1000, 125), (16, 1024, 128), (16, 1025, 1), (17, 1024, 33), (8, 4000, 65), (3, 8191, 1024),
+                                   (20, 2000, 20), (33, 4097, 64), (5, 12289, 64), (16, 16383, 300), (7, 61440, 1)])
+def test_aggregation_of_messages_of_rows_in_registers(gpu, n, d, k):
+    """Either side of the rule for the one-workgroup aggregation, and the index of the messages as the kernel that holds a row
+    in registers writes it, for messages spread out, all in the first block and all in the last: g within the rounding of a
+    sum of n terms, x one fused multiply-add on."""
+    torch, binding = gpu
+    rng = np.random.default_rng(n * d + k)
+    for where in ("spread", "first", "last"):
+        S = rng.standard_normal((n, d)).astype(np.float32)
+        if where == "first":
+            S[:, :k] *= 1e4
+        if where == "last":
+            S[:, d - k:] *= 1e4
+        with binding.EF21(n, d, k, 0.5) as h:
+            h.set_state(x=torch.zeros(d, device="cuda"), g_i=torch.zeros((n, d), device="cuda"))
+            h.step(torch.from_numpy(S).cuda())
+            idx, val = (t.cpu().numpy() for t in h.get_messages())
+            x, _, g = (t.cpu().numpy() for t in h.get_state())
+        total, size = np.zeros(d), np.zeros(d)
+        for i in range(n):
+            key = np.abs(S[i])
+            assert np.array_equal(idx[i], np.sort(np.argsort(-key, kind="stable")[:k]))
+            assert np.array_equal(val[i], S[i, idx[i]])
+            total[idx[i]] += val[i]
+            size[idx[i]] += np.abs(val[i])
+        # n - 1 additions, the rounding of 1 / n and the fused multiply-add
+        assert np.all(np.abs(g - total / n) <= (n + 2) * 2.0**-24 * size / n), (n, d, k, where)
+        assert np.array_equal(x, np.float32(-0.5) * g)
