@@ -19,11 +19,11 @@
 //   2  The quads that hold an entry of at least `low` (about one in twenty at k / d = 1 %) go to LDS with their
 //      position: one atomic per wavefront, a bit mask per quad.
 //   3  A histogram of the listed entries, (key - low) >> 14 (bins of 1/512 octave, a window of eight octaves), gives the
-//      bin of the k-th largest magnitude.  Its entries (a handful) are ranked against one another, larger key first,
-//      lower position first.
+//      bin of the k-th largest magnitude; a crowded bin gets a histogram of its own.  The bin's entries (a handful) are
+//      ranked against one another, larger key first, lower position first.
 //   4  The kept entries set their bits in a bitmap of the row; a prefix sum over the bitmap gives each its place in
 //      the ascending output.
-// A list that overflows, a threshold beyond the window or a bin of more than 1024 entries (rows with very many magnitudes
+// A list that overflows, a threshold beyond the window or more than 256 entries within four keys of it (rows with very many magnitudes
 // alike, fewer than k non-zeros among them) leaves the threshold to a bisection of the keys over the registers.
 #include "topk_row_impl.h"
 
@@ -37,7 +37,7 @@ constexpr int kBins = 4096;
 constexpr int kListMost = 4096;                 // listed quads
 constexpr int kTieMax = 256;                    // entries of the threshold's bin that are ranked
 constexpr uint32_t kKeyEnd = 0x80000000u;       // beyond every key
-constexpr int kWindowShift = 14;
+constexpr int kWindowShift = 14, kFineShift = 2;
 constexpr int kCrowded = 768;                   // maxima in a bin from which four more bits are worth two barriers
 static_assert(kRowRegMax <= 65536, "positions in 16 bits");
 
@@ -435,21 +435,40 @@ __global__ __launch_bounds__(kRowThreads) void topk_row_reg_kernel(TopkArgs p) {
     }
     __syncthreads();
     select_and_clear(sh, k);
-    const uint32_t tie_bin = sh.bin, need = sh.need, c = sh.count;
-    if (c > (uint32_t)kTieMax || tie_bin == (uint32_t)kBins - 1u) {
-        const uint32_t from = low + (tie_bin << kWindowShift);
-        const bool last = tie_bin == (uint32_t)kBins - 1u;                // open above; below 2^31 (low + 4095 * 2^14 may not be)
-        if (last) select_by_bisection<R, DIFF>(sh, p, v, low, kKeyEnd, 0u, max_of_thread);
-        else select_by_bisection<R, DIFF>(sh, p, v, from, from + (1u << kWindowShift), k - need, max_of_thread);
+    uint32_t need = sh.need, c = sh.count, width = kWindowShift;          // T's bin: keys [tie_lo, tie_lo + 2^width)
+    uint32_t tie_lo = low + (sh.bin << kWindowShift);
+    if (sh.bin == (uint32_t)kBins - 1u) {                                 // beyond the window
+        select_by_bisection<R, DIFF>(sh, p, v, low, kKeyEnd, 0u, max_of_thread);
         return;
+    }
+    if (c > (uint32_t)kTieMax) {
+        // Many entries just below what earlier iterations have sent, as EF21 leaves them: the bin's own histogram, four keys a bin
+        // (100 x 50000, iterations of a sparse problem, us in this kernel: 22.2 and up to 44 with a bisection of the bin, 20.5 and up to
+        // 27 so).
+        static_assert(kWindowShift - kFineShift == 12 && kBins == 1 << 12, "the bin's keys fill the histogram");
+        __syncthreads();                                                  // sh.bin, sh.need and sh.count have been read
+        for (uint32_t i0 = 0; i0 < n_flat; i0 += kRowThreads) {
+            const uint32_t i = i0 + tid, off = (i < n_flat ? mag_key(flat[i]) : 0u) - tie_lo;
+            vote(sh.hist, off >> kFineShift, off < (1u << kWindowShift));
+        }
+        __syncthreads();
+        select_and_clear(sh, need);
+        need = sh.need;
+        c = sh.count;
+        width = kFineShift;
+        tie_lo += sh.bin << kFineShift;
+        if (c > (uint32_t)kTieMax) {
+            select_by_bisection<R, DIFF>(sh, p, v, tie_lo, tie_lo + (1u << width), k - need, max_of_thread);
+            return;
+        }
     }
     for (uint32_t i = tid; i < n_flat; i += kRowThreads) {
         const uint32_t key = mag_key(flat[i]);
-        if (key >= low) {
-            const uint32_t e = 4u * sh.quad_at[i >> 2] + (i & 3u), bin = (key - low) >> kWindowShift;
-            if (bin > tie_bin) {
+        if (key >= tie_lo) {
+            const uint32_t e = 4u * sh.quad_at[i >> 2] + (i & 3u);
+            if (key - tie_lo >= (1u << width)) {
                 atomicOr(&sh.bitmap[e >> 5], 1u << (e & 31u));
-            } else if (bin == tie_bin) {
+            } else {
                 const uint32_t at = atomicAdd(&sh.n_tie, 1u);
                 sh.tie_key[at] = key;
                 sh.tie_at[at] = e;

@@ -108,9 +108,9 @@ def test_rows_held_in_lds_as_key_prefixes(gpu, oracle, d, k):
 def rows_for_registers(d, k, seed):
     """One row per way through the kernel that holds the row in registers: an ordinary one, ties everywhere, fewer than k
     non-zeros, magnitudes all alike (the list or the threshold's bin overflows), large entries side by side, a threshold far
-    above the bound (beyond the window), NaN and infinities, large entries at the row's very end."""
+    above the bound (beyond the window), NaN and infinities, large entries at the row's very end, entries piled up."""
     rng = np.random.default_rng(seed)
-    V = rng.standard_normal((8, d)).astype(np.float32)
+    V = rng.standard_normal((9, d)).astype(np.float32)
     V[1] = np.round(V[1] * 2) / 2
     V[2] = np.where(rng.random(d) < 0.5 * k / d, V[2], np.where(V[2] > 0, 0.0, -0.0))
     V[3] = 10 + 0.01 * V[3]
@@ -119,6 +119,7 @@ def rows_for_registers(d, k, seed):
     V[6, ::d // 5] = np.nan
     V[6, 1::d // 3] = np.inf
     V[7, -3:] = [1e30, -1e30, 1e30]
+    V[8] = np.sign(V[8]) * (1 - 5e-4 * rng.random(d))          # piled up: more than 256 entries in T's bin, few within four keys
     return V.astype(np.float32)
 
 
