@@ -26,41 +26,18 @@
 // A list that overflows, a threshold beyond the window or more than 256 entries within four keys of it (rows with very many magnitudes
 // alike, fewer than k non-zeros among them) leaves the threshold to a bisection of the keys over the registers.
 #include "topk_row_impl.h"
+#include "topk_row_reg_shared.h"
 
 namespace ef21 {
 namespace {
 
-constexpr int kQuadStep = kRowThreads * 4;      // entries between a thread's neighbouring quads
 constexpr int kMaxQuads = 15;                   // per thread: 60 of 128 registers
 static_assert((int64_t)kMaxQuads * kQuadStep == kRowRegMax, "the longest row fills the registers");
-constexpr int kBins = 4096;
-constexpr int kListMost = 4096;                 // listed quads
-constexpr int kTieMax = 256;                    // entries of the threshold's bin that are ranked
 constexpr uint32_t kKeyEnd = 0x80000000u;       // beyond every key
 constexpr int kWindowShift = 14, kFineShift = 2;
 constexpr int kCrowded = 768;                   // maxima in a bin from which four more bits are worth two barriers
+static_assert(kRegThreads == kRowThreads && kRegWaves == kRowWaves, "RegShared is the workgroup's");
 static_assert(kRowRegMax <= 65536, "positions in 16 bits");
-
-// R quads per thread.  Rows of up to 16384 entries leave room for two workgroups per compute unit (1000 x 8193, k = 81:
-// 25 us with one, 15 with two).
-template <int R>
-struct RegShared {
-    static constexpr int kListMax = R <= 2 ? R * kRowThreads : R <= 4 ? 2560 : kListMost;
-    static constexpr int kMapWords = R * kQuadStep / 32;
-    static_assert(kMapWords % 2 == 0 && kMapWords <= 2 * kRowThreads, "two bitmap words per thread");
-    static_assert(kMapWords <= kBins, "the bisection's map of ties lies over the histogram");
-    static constexpr bool kHoldsRow = kListMax == R * kRowThreads;       // the list has room for every quad
-    __attribute__((aligned(16))) uint32_t hist[kBins];
-    __attribute__((aligned(16))) float quads[kListMax][4];
-    uint32_t waves[kRowWaves];
-    uint16_t quad_at[kListMax];                 // position / 4
-    uint32_t tie_key[kTieMax], tie_at[kTieMax], tie_rank[kTieMax];
-    uint32_t bitmap[kMapWords], prefix[kMapWords];
-    uint32_t sub[16];
-    uint32_t bin, need, count;                  // of the last selection
-    uint32_t n_list, n_tie;
-    uint32_t probe[3];
-};
 
 // Inclusive prefix sum over the wavefront, in vector instructions alone.
 __device__ __forceinline__ uint32_t dpp_inclusive_scan(uint32_t v) {
@@ -326,15 +303,7 @@ __global__ __launch_bounds__(kRowThreads) void topk_row_reg_kernel(TopkArgs p) {
         }
     }
     // cleared while the loads are in flight
-    reinterpret_cast<uint4 *>(sh.hist)[tid] = make_uint4(0u, 0u, 0u, 0u);
-    for (int i = tid; i < kMapWords; i += kRowThreads) sh.bitmap[i] = 0u;
-    sh.tie_rank[tid] = 0u;
-    if (tid < 16) sh.sub[tid] = 0u;
-    if (tid == 0) {
-        sh.n_list = 0u;
-        sh.n_tie = 0u;
-        sh.bin = sh.count = 0u;                 // stand if fewer than k of the largest are no zeros
-    }
+    clear_shared(sh, tid);
     // Entries past the end become zeros at positions past the end: as the last of all ties they are never kept.
 #pragma unroll
     for (int u = 0; u < R; ++u) {
