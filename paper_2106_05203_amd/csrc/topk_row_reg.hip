@@ -255,7 +255,7 @@ __device__ void select_by_bisection(RegShared<R> &sh, const TopkArgs &p, const f
 template <int R, bool DIFF>
 __global__ __launch_bounds__(kRowThreads) void topk_row_reg_kernel(TopkArgs p) {
     __shared__ RegShared<R> sh;
-    constexpr int kListMax = RegShared<R>::kListMax, kMapWords = RegShared<R>::kMapWords;
+    constexpr int kListMax = RegShared<R>::kListMax;
     const int64_t row = blockIdx.x;
     const int d = (int)p.d, tid = threadIdx.x, lane = lane_id();
     const uint32_t k = (uint32_t)p.k;
