@@ -272,14 +272,19 @@ __global__ __launch_bounds__(kThreads) void aggregate_many_kernel(const int32_t 
 // messages in LDS; then ONE wavefront adds them to the LDS accumulator worker by worker, 64 entries of a
 // worker per step (positions inside a message are distinct, and a wavefront's LDS accesses execute in
 // program order, so no barrier is needed between workers) while the other wavefronts fetch g and x.
-constexpr int kSmallThreads = 1024, kSmallPer = 8;
-constexpr int kSmallD = 16384, kSmallEntries = kSmallThreads * kSmallPer;
+// Two pairs a thread and 12 288 columns are what the rule admits; with room for 8192 pairs and 16 384 columns a step of 4 x 1000,
+// k = 100 took 8.6 us, of 1 x 622, k = 622 8.5 and of 64 x 70, k = 20 14.5: 8.1, 8.0 and 12.3 so.
+constexpr int kSmallThreads = 1024, kSmallPer = 2;
+constexpr int kSmallD = 12288, kSmallEntries = kSmallThreads * kSmallPer;
+constexpr int kSmallSteps = 512;     // at most this many sequential steps of the adding wavefront
 constexpr int kScanEntries = 128;    // messages in all that every coordinate can look through (n = 20, k = 4: 4.8 -> 2.8 us)
-constexpr int kSmallFetch = 4;      // coordinates per thread fetched ahead (d <= 4096)
-constexpr int kSmallAhead = 8;      // steps whose pairs are in registers (kernel, us: n = 20, d = 2000, k = 20 5.3 -> 4.9)
-constexpr int kSmallLanes = 32;     // pairs of a worker up to which an LDS atomic is the quicker addition (n = 20, d = 300, k = 8
-                                    // 4.5 -> 4.0 us; n = 16, d = 12000, k = 400 16.6 -> 19.2)
-constexpr int kSmallSteps = 512;    // at most this many sequential steps of the adding wavefront
+constexpr int kSmallFetch = 4;       // coordinates per thread fetched ahead (d <= 4096)
+// Steps whose pairs are in registers.  step with supplied gradients, us, one step ahead and eight: 20 x 1000, k = 100 13.1 and 12.2;
+// 64 x 300, k = 30 14.8 and 13.7; 200 x 200, k = 10 32.6 and 27.3.
+constexpr int kSmallAhead = 8;
+// Pairs of a worker up to which an LDS atomic is the quicker addition.  The same, us, read-add-write and atomic: 500 x 256, k = 4
+// 70.5 and 59.3; 64 x 300, k = 30 14.5 and 13.7; 8 x 1000, k = 64 8.1 and 8.4; 20 x 1000, k = 100 12.2 and 12.7.
+constexpr int kSmallLanes = 32;
 
 template <bool STEP>
 __global__ __launch_bounds__(kSmallThreads) void aggregate_small_kernel(const int32_t *__restrict__ idx,
@@ -445,22 +450,26 @@ size_t aggregate_index_bytes(int32_t n, int64_t d) {      // for the shorter of 
 
 namespace {
 // One workgroup adds one step after the other, 0.12 us each, and walks all coordinates; the kernels with a wavefront or
-// four per block of coordinates take a message index, which launch_topk_row_reg and launch_topk_split write with the message.
-// step with supplied gradients, us, small and not: 8 x 1000, k = 100 (16 steps) 10.5 and 11.0; 15 x 1000, k = 20 10.5 and 12.2;
-// 10 x 5000, k = 50 11.3 and 12.1; 8 x 2000, k = 200 (32) 12.7 and 11.3; 8 x 12000, k = 60 12.3 and 11.1; 20 x 2000, k = 20 11.5 and
-// 10.1; 32 x 2000, k = 200 (128) 25.1 and 10.5; 16 x 12000, k = 400 (112) 26.6 and 11.8.  Up to 1024 coordinates and 2048 pairs
+// four per block of coordinates take a message index, which launch_topk_row_reg and launch_topk_split write with the message
+// (kReachIndexed) and a kernel of its own where neither selects, on short rows and where more than an eighth is kept
+// (kReachNot).  step with supplied gradients, us, small and not, workers x columns, k (steps + columns / 512):
+// with the index at hand: 5 x 10000, 30 (24) 10.4 and 10.4; 8 x 10000, 30 (27) 10.6 and 10.3; 10 x 5000, 130 (39) 12.4 and 11.6;
+// 8 x 2000, 200 (35) 11.6 and 10.4; without: 1 x 1500, 1500 (26) 10.0 and 12.5; 8 x 1500, 250 (34) 11.9 and 13.6; 4 x 2468,
+// 493 (36) 13.0 and 14.0; 3 x 4000, 640 (37) 14.3 and 14.6; 6 x 2600, 330 (41) 14.2 and 13.0; 2 x 6000, 1000 (43) 17.0 and 16.3;
+// 1 x 12000, 1900 (53) 23.7 and 22.0.  Up to 1024 coordinates and 2048 pairs
 // the sums are those of the iteration in one launch (small_step.hip) to the bit, in worker order, so they stay here.
-constexpr int64_t kSmallReach = 24, kSmallStep1 = 1024, kSmallPairs1 = 2048;
-bool aggregate_is_small(int32_t n, int64_t k, int64_t d) {
-    const int64_t pairs = (int64_t)n * k, steps = (int64_t)n * ((k + kWave - 1) / kWave);
-    if (d > kSmallD || pairs > kSmallEntries || steps > kSmallSteps) return false;
-    return (d <= kSmallStep1 && pairs <= kSmallPairs1) || (n < kManyWorkers && steps + d / 512 <= kSmallReach);
+constexpr int64_t kSmallStep1 = 1024, kReachIndexed = 24, kReachNot = 38;
+static_assert(kReachIndexed <= kReachNot, "with an index there is one more reason against the one workgroup");
+bool aggregate_is_small(int32_t n, int64_t k, int64_t d, int64_t reach) {
+    const int64_t steps = (int64_t)n * ((k + kWave - 1) / kWave);
+    if (d > kSmallD || (int64_t)n * k > kSmallEntries || steps > kSmallSteps) return false;
+    return d <= kSmallStep1 || (n < kManyWorkers && steps + d / 512 <= reach);
 }
 }  // namespace
 
 int aggregate_index_shift(int32_t n, int64_t k, int64_t d) {
     static_assert(kManySub == 1 << 8 && kAggSub == 1 << 9 && kAggLong == 1 << 11, "block lengths as shifts");
-    if (aggregate_is_small(n, k, d)) return -1;
+    if (aggregate_is_small(n, k, d, kReachIndexed)) return -1;
     if (n >= kManyWorkers) return 8;
     return d >= 4000000 && d <= 8000000 && k * 100 <= d ? 11 : 9;
 }
@@ -468,7 +477,7 @@ int aggregate_index_shift(int32_t n, int64_t k, int64_t d) {
 hipError_t launch_aggregate(const int32_t *idx, const float *val, int32_t n, int64_t k, int64_t d, float *g, float *x,
                             float gamma, void *index, hipStream_t stream, bool index_ready, bool from_zero) {
     const float inv_n = 1.0f / (float)n;
-    if (aggregate_is_small(n, k, d)) {
+    if (!index_ready && aggregate_is_small(n, k, d, kReachNot)) {
         if (x)
             hipLaunchKernelGGL(aggregate_small_kernel<true>, dim3(1), dim3(kSmallThreads), 0, stream, idx, val, n, k, d,
                                g, x, inv_n, -gamma, from_zero);

@@ -756,3 +756,12 @@ def test_aggregation_of_messages_of_rows_in_registers(gpu, n, d, k):
         # n - 1 additions, the rounding of 1 / n and the fused multiply-add
         assert np.all(np.abs(g - total / n) <= (n + 2) * 2.0**-24 * size / n), (n, d, k, where)
         assert np.array_equal(x, np.float32(-0.5) * g)
+
+
+@pytest.mark.parametrize("n,d,k", [(1, 3072, 2048), (1, 3584, 2048), (2, 1100, 1024), (2, 1100, 1025), (4, 2468, 493), (15, 511, 136),
+                                   (15, 511, 137), (16, 1024, 128), (16, 1024, 129), (3, 10239, 1), (1, 1025, 1025), (512, 300, 4),
+                                   (513, 300, 1)])
+def test_aggregation_of_messages_without_an_index(gpu, n, d, k):
+    """Either side of the one-workgroup aggregation's limits (38 steps and blocks of 512 columns, 2048 pairs, 512 steps) where
+    the Top-k does not write the index: short rows, and messages of more than an eighth of a row."""
+    test_aggregation_of_messages_of_rows_in_registers(gpu, n, d, k)
