@@ -43,13 +43,20 @@ constexpr int64_t kSplitMinRow = 1 << 14;
 
 bool use_split(int64_t d) { return d >= kSplitMinRow; }
 
-// Rows that fit the registers of one workgroup, of which few entries are kept, are selected there: longer ones than the kernels
-// with an LDS copy take, and shorter ones from where that is quicker.  Kernel, us, 20 rows, from LDS and from registers:
-// d = 500 5.4 and 5.6; 2000 6.5 and 5.7; 8000 10.6 and 6.1.  Beyond one entry in eight the bound that the kernel takes from
-// its quads' largest entries is poor.
+// Rows that fit the registers of one workgroup, of which few entries are kept, are selected there.  Beyond one entry in eight
+// the bound that the kernel takes from its quads' largest entries is poor.
 bool use_row_reg(int64_t d, int64_t k) {
     return d >= ef21::kRowRegMin && d <= ef21::kRowRegMax && k <= ef21::kRowRegMaxK && 8 * k <= d;
 }
+
+// From this length on, with one number of rows above the compute units' 256 and one up to it.  ef21_topk, us, from LDS and
+// from registers: 20 x 512, k = 25 4.9 and 5.0; 20 x 900, k = 108 5.1 and 5.3; 20 x 1023, k = 51 5.3 and 5.2; 20 x 2000, k = 100 6.0
+// and 5.5; 100 x 2000 6.2 and 5.6; 300 x 512, k = 61 6.2 and 6.2; 300 x 800, k = 40 6.6 and 6.2; 1000 x 700, k = 84 11.1 and 11.4;
+// 1000 x 900, k = 45 11.8 and 11.3; 1000 x 2000 14.5 and 11.9.  (Rows all of one magnitude, which end in the bisection: 20 x 1200 9.4
+// and 11.0; 20 x 2000 11.8 and 11.5; 300 x 1200 14.3 and 12.9; 256 x 12311 44.7 and 10.9.)  The message index, which only this
+// kernel writes with the message, is a launch less for the aggregation: step of 100 x 512, k = 51 15.7 and 14.0; 300 x 600, k = 60
+// 28.0 and 26.1.
+int64_t row_reg_from(int32_t n, bool indexed) { return indexed ? ef21::kRowRegMin : (n > 256 ? 800 : 1024); }
 
 // Workspaces of the stateless ef21_topk: one per (device, stream), so that calls on different streams never share
 // one (calls on one stream run one after the other).  They live until the process ends; if a device collects more
@@ -268,7 +275,7 @@ int enqueue_local_grad(ef21_ctx *c, const float *x, float *out, ef21::GradParts 
 int enqueue_topk(ef21::TopkArgs p, void *workspace, hipStream_t stream, const ef21::Marker &mk,
                  bool *index_ready = nullptr) {
     hipError_t st;
-    const bool reg = use_row_reg(p.d, p.k) && !p.parts.part;
+    const bool reg = use_row_reg(p.d, p.k) && p.d >= row_reg_from(p.n, p.agg_start != nullptr) && !p.parts.part;
     const bool split = use_split(p.d) && workspace && !reg;
     if (!reg && !(split && p.k > 1)) p.agg_start = nullptr;
     if (index_ready) *index_ready = p.agg_start != nullptr;

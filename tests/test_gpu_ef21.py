@@ -728,7 +728,8 @@ def test_few_entries_on_many_blocks(gpu, n, d, k, where):
 
 
 @pytest.mark.parametrize("n,d,k", [(2, 512, 64), (15, 1000, 125), (16, 1024, 128), (16, 1025, 1), (17, 1024, 33), (8, 4000, 65), (3, 8191, 1024),
-                                   (20, 2000, 20), (33, 4097, 64), (5, 12289, 64), (16, 16383, 300), (7, 61440, 1)])
+                                   (20, 2000, 20), (33, 4097, 64), (5, 12289, 64), (16, 16383, 300), (7, 61440, 1),
+                                   (33, 511, 63), (33, 512, 64), (41, 1023, 50)])
 def test_aggregation_of_messages_of_rows_in_registers(gpu, n, d, k):
     """Either side of the rule for the one-workgroup aggregation, and the index of the messages as the kernel that holds a row
     in registers writes it, for messages spread out, all in the first block and all in the last: g within the rounding of a

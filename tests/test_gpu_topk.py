@@ -141,6 +141,18 @@ def test_rows_held_in_registers(gpu, d):
         assert same_bits(val, np.take_along_axis(V, ref, axis=1)), (d, k)
 
 
+@pytest.mark.parametrize("n", [9, 261])
+@pytest.mark.parametrize("d", [511, 512, 799, 800, 1023, 1024])
+def test_either_side_of_the_shortest_rows_in_registers(gpu, n, d):
+    """The shortest rows that go there depend on whether there are more of them than compute units."""
+    for k in (1, d // 20, d // 8):
+        V = np.tile(rows_for_registers(d, k, d + k), (n // 9, 1))
+        idx, val = run_gpu(gpu, V, k)
+        ref = first_by_magnitude(V, k)
+        assert np.array_equal(idx, ref), (n, d, k)
+        assert same_bits(val, np.take_along_axis(V, ref, axis=1)), (n, d, k)
+
+
 @pytest.mark.parametrize("d", [513, 4097, 12289, 24577, 50001, 61440])
 def test_differences_held_in_registers(gpu, d):
     """The same for grad - g_i inside a step: message, and g_i updated at the kept positions only."""
