@@ -26,13 +26,14 @@ constexpr int kBlocksPerWg = kRowThreads / kDenseThreads;   // 4 row blocks per 
 constexpr int kMaxCols = 1024;                              // d of the fused iteration
 constexpr int kMaxEntries = 2048;                           // n * k
 // A workgroup per worker where its sixteen wavefronts have the rows in two trips (128 KB and more in flight each); with more, the
-// separate kernels are ahead.  step and gradient, us, by the separate kernels and so: n = 4, m = 250, d = 100 11.0 and 8.6, 8.6
-// and 4.7; 4, 500, 100 11.0 and 10.1, 8.6 and 5.4; 2, 256, 256 14.8 and 12.9, 8.4 and 5.2; 30, 128, 500 17.1 and 15.5, 8.4 and 5.3; but
-// 4, 1000, 60 10.2 and 10.3, 8.4 and 5.9; 4, 1000, 100 12.0 and 13.0; 20, 1300, 100 13.3 and 15.5.  Many workers, which fill the
-// chip anyway, save no more than a launch and have fewer workgroups side by side: 300, 300, 100 62.5 and 59.0; 500, 100, 300 93.5 and
-// 93.9; 1000, 20, 50 65.7 and 68.8.
+// separate kernels are ahead.  step and gradient, us, calls back to back, by the separate kernels and so: n = 4, m = 250,
+// d = 100 11.9 and 8.6, 8.6 and 4.6; 4, 500, 100 11.8 and 10.4, 8.8 and 5.3; 2, 256, 256 14.1 and 13.1, 9.1 and 5.1; 30, 128, 500
+// 17.9 and 17.0, 9.0 and 5.1; but step of 4, 1000, 60 10.2 and 10.3; 4, 1000, 100 12.0 and 13.0; 20, 1300, 100 13.3 and 15.5.
+// And up to as many workers as there are compute units: the sums and the staged messages take most of a unit's LDS, so
+// more workers take turns, where the separate kernels' workgroups lie side by side.  step, us: 256, 100, 300 33.3 and 28.3; 257, 100,
+// 300 35.2 and 37.5; 257, 20, 500 33.9 and 36.0; 300, 1, 96 29.3 and 30.9; 400, 128, 500 54.6 and 54.6.
 constexpr int kSoloCols = 512, kSoloTrips = 2;
-constexpr int32_t kSoloWorkers = 512;
+constexpr int32_t kSoloWorkers = 256;
 constexpr int kMaxAddSteps = 512;                           // n * ceil(k / 64), the adding wavefront's steps
 
 struct SmallArgs {
@@ -137,8 +138,8 @@ __global__ __launch_bounds__(kRowThreads) void small_step_kernel(SmallArgs a) {
 }
 
 // One workgroup per worker.  The gradient's sums stay in LDS, in fp64.  What bounds it is a chain: the worker's rows through
-// one compute unit (a trip of 128 KB takes about 1.5 us), the sums over sixteen wavefronts, the selection.  n = 4, m = 250, d = 100:
-// an iteration 12.6 -> 9.1 us, a gradient 9.7 -> 5.4.
+// one compute unit (a trip of 128 KB takes about 1.5 us), the sums over sixteen wavefronts, the selection.  Against the
+// separate kernels see kSoloTrips.
 enum SoloMode { kSoloGrad = 0, kSoloSelect = 1 /* lines 5 and 6 */, kSoloWhole = 2 /* lines 5, 6, 8, 3 */ };
 template <int LANES, int NQ, int SHAPE, bool BATCH, int MODE>
 __global__ __launch_bounds__(kRowThreads) void solo_kernel(SmallArgs a) {

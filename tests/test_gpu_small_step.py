@@ -115,6 +115,41 @@ def test_workgroup_per_worker(gpu, oracle, d, loss):
                         assert torch.equal(a, b), f"m = {m}: messages differ"
 
 
+@pytest.mark.parametrize("n", [256, 257])
+def test_workgroup_per_worker_up_to_the_compute_units(gpu, oracle, n):
+    """One workgroup per worker where each has a compute unit to itself; with more workers they take turns and an iteration is
+    slower than by the separate kernels (n = 257, m = 20, d = 500: 36.0 and 33.9 us).  One launch, the separate kernels
+    and an iteration from the reported gradient agree bit for bit on either side."""
+    torch, binding = gpu
+    d, m, k = 60, 20, 2
+    A, y, rng = problem(n, d, m, n)
+    x, g_i = (0.3 * rng.standard_normal(d)).astype(np.float32), 0.1 * rng.standard_normal((n, d))
+    P = oracle.LogRegDense(A, y, 0.1)
+    with binding.EF21(n, d, k, 0.3) as own, binding.EF21(n, d, k, 0.3) as given, binding.EF21(n, d, k, 0.3) as one:
+        for h in (own, given, one):
+            h.set_problem_dense(to_gpu(torch, A), to_gpu(torch, y), 0.1)
+            h.set_state(to_gpu(torch, x), to_gpu(torch, g_i), None)
+        s = own.local_grad()
+        # as in test_workgroup_per_worker
+        u = 2.0 ** -24
+        a64, x64 = A.astype(np.float64), x.astype(np.float64)
+        coef = 1.0 / (1.0 + np.exp(y * np.einsum("imd,d->im", a64, x64)))
+        dcoef = 0.25 * (d / 64 + 8) * u * np.einsum("imd,d->im", np.abs(a64), np.abs(x64)) + 16 * u * coef
+        ref = P.grads(x64)
+        bound = 1e-6 * np.abs(ref) + np.einsum("imd,im->id", np.abs(a64), dcoef) / m + u
+        assert np.all(np.abs(s.cpu().numpy() - ref) <= bound)
+        for t in range(3):
+            given.step(given.local_grad())
+            one.step(None, binding.ONE_LAUNCH)
+            if t == 2:
+                own.set_timing(True)
+            own.step()
+            for h in (given, one):
+                for a, b in zip(own.get_state() + own.get_messages(), h.get_state() + h.get_messages()):
+                    assert torch.equal(a, b), f"step {t}"
+        assert ("topk_row" in own.get_timing()) == (n > 256)       # beyond, a Top-k kernel of its own
+
+
 def test_least_squares_same_bits(gpu):
     torch, binding = gpu
     n, d, m, k = 3, 200, 90, 7
