@@ -203,8 +203,11 @@ int ef21_local_grad(ef21_handle h, const float *x, float *out_grad);
  *   flags: EF21_ORDER_GRAD_FIRST or EF21_ORDER_STEP_FIRST.  With supplied gradients and
  *   STEP_FIRST the caller must have evaluated them at x - gamma*g.
  * The difference in line 5 is one fp32 subtraction; line 6 is one fp32 addition per kept
- * entry; line 8 adds the messages per coordinate in worker order in fp32 and applies
+ * entry; line 8 adds the messages per coordinate in fp32 and applies
  * g + sum * (1/n) as one fused multiply-add; line 3 is one fused multiply-add per coordinate.
+ * The sum of line 8 takes the workers in order where n < 16, and where d <= 1024, n k <= 2048 and n ceil(k / 64) <= 512.
+ * In all other calls it is ((r0 + r1) + r2) + r3 of the sums r0 .. r3, each in worker order, over four runs of
+ * ceil(n / 4) consecutive workers (the last may hold fewer): the order depends on n, d and k alone.
  * With supplied gradients every result (messages, g_i, g, x) is bitwise reproducible.
  * With EF21_ONE_LAUNCH in flags, a small dense problem (grads NULL, d <= 1024, n * k <= 2048,
  * n * m * d <= 2^24, no minibatch, no EF21_PLUS) runs the whole pass as ONE kernel: the same arithmetic in the
@@ -240,7 +243,7 @@ int ef21_get_choices(ef21_handle h, int32_t *branch, double *distortions);
  * ef21_set_state / ef21_get_state (start from e_i = 0): at the handle's x, with s = grad f_i(x) or the
  * supplied row,  p_i = e_i + gamma s  (one fused multiply-add per entry, written over e_i),
  * w_i = C(p_i)  (Top-k as in ef21_topk; returned by ef21_get_messages),  e_i = p_i - w_i  (zero at the kept
- * positions),  x <- x - (1/n) sum_i w_i  (the sum per coordinate in worker order in fp32).  Started from
+ * positions),  x <- x - (1/n) sum_i w_i  (the sum per coordinate in fp32, in the order of line 8 of ef21_step).  Started from
  * e_i = 0 this produces the iterates x^0, x^1, ... of Algorithm 4.  The g of ef21_get_state holds
  * (1/n) sum_i w_i of the last round.  Do not mix rounds of different algorithms on one state.
  */

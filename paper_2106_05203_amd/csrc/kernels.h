@@ -134,8 +134,9 @@ hipError_t launch_topk_split_reset(void *workspace, int32_t n, int64_t d, hipStr
 hipError_t launch_model_step(float *x, const float *g, int64_t d, float gamma, hipStream_t stream);
 
 // Algorithm 2, line 8: g <- g + (1/n) sum_i c_i from the messages (idx, val) [n][k] (positions ascending
-// and distinct inside a row), summed in worker order, without atomics; if x != nullptr followed, in the
-// same pass over the coordinates, by line 3 with the new g.
+// and distinct inside a row), summed without global atomics in an order that n, d and k alone fix: the workers' own, except
+// with many workers (kManyWorkers in update.hip) on more than small messages, where four runs of consecutive workers are
+// summed side by side; if x != nullptr followed, in the same pass over the coordinates, by line 3 with the new g.
 // `index`: aggregate_index_bytes(n, d) bytes of scratch, overwritten by every call.
 // The index: start[w][b] = first pair of worker w's message at or beyond coordinate b << shift, for the blocks
 // b = 0 .. nblk of 2^shift coordinates (start[w][nblk] = k), int32 [n][nblk + 1].  aggregate_index_shift gives the

@@ -48,7 +48,7 @@ class RoundingBudget:
     oracle's (which computes lines 8 and 3 of Algorithm 2 in fp64 and rounds once), to first order in the unit
     roundoff u = 2^-24.
 
-    Line 8 on the GPU: the messages that hit coordinate j are added in fp32 in worker order (c_j of them: c_j - 1
+    Line 8 on the GPU: the messages that hit coordinate j are added in fp32 in a fixed order (c_j of them: c_j - 1
     additions, each off by at most u times the partial sum, so at most (c_j - 1) u sum_i |c_ij| in all), then
     g_j + sum * (1/n) as one fused multiply-add with 1/n rounded to fp32 (u |sum| / n) and one rounding of the
     result (u |g_j^new|); the oracle rounds its fp64 result once more (u |g_j^new|).  With

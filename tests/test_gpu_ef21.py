@@ -2,7 +2,7 @@
 
 Bars: messages (positions, values) and g_i bit-exact when both sides start from the same state and
 see the same gradients; g and x within 1e-5 relative per coordinate (the library sums the messages
-in fp32 in worker order, the oracle in fp64); f(x^t) within 1e-4 relative over a whole run with GPU-computed gradients.
+in fp32 in a fixed order, the oracle in fp64); f(x^t) within 1e-4 relative over a whole run with GPU-computed gradients.
 """
 import numpy as np
 import pytest
@@ -766,3 +766,36 @@ def test_aggregation_of_messages_without_an_index(gpu, n, d, k):
     """Either side of the one-workgroup aggregation's limits (38 steps and blocks of 512 columns, 2048 pairs, 512 steps) where
     the Top-k does not write the index: short rows, and messages of more than an eighth of a row."""
     test_aggregation_of_messages_of_rows_in_registers(gpu, n, d, k)
+
+
+def line8_sum(n, d, k, idx, val):
+    """The messages added per coordinate in fp32 in the order that include/ef21.h states for ef21_step."""
+    def in_order(workers):
+        s = np.zeros(d, np.float32)
+        for i in workers:
+            s[idx[i]] += val[i]
+        return s
+    if n < 16 or (d <= 1024 and n * k <= 2048 and n * -(-k // 64) <= 512):
+        return in_order(range(n))
+    run = -(-n // 4)
+    r = [in_order(range(j * run, min(n, (j + 1) * run))) for j in range(4)]
+    return ((r[0] + r[1]) + r[2]) + r[3]
+
+
+@pytest.mark.parametrize("n,d,k", [(15, 3000, 700), (15, 700, 300), (16, 1024, 128), (16, 1024, 129), (16, 1025, 64), (17, 40, 20), (20, 2000, 20),
+                                   (21, 2000, 900), (512, 64, 4), (513, 64, 1), (33, 300, 200), (15, 20000, 900), (18, 20000, 1500),
+                                   (30, 16383, 300), (9, 70001, 7000), (25, 70001, 7000)])
+def test_order_of_the_sum_of_messages(gpu, n, d, k):
+    """g after one step from g = 0 is the sum times 1/n rounded once, so its bits are those of the documented order and of no
+    other (magnitudes spread over many octaves: another order would differ somewhere); Algorithm 4 sums the same way."""
+    torch, binding = gpu
+    rng = np.random.default_rng(n + d + k)
+    S = (rng.standard_normal((n, d)) * np.exp(3 * rng.standard_normal((n, d)))).astype(np.float32)
+    S[:, : d // 20 + 1] *= 1e3                           # coordinates that many messages hit
+    for flags in (0, binding.CLASSIC_EF):
+        with binding.EF21(n, d, k, 0.5) as h:
+            h.set_state(x=torch.zeros(d, device="cuda"), g_i=torch.zeros((n, d), device="cuda"))
+            h.step(torch.from_numpy(S).cuda(), flags)
+            idx, val = (t.cpu().numpy() for t in h.get_messages())
+            g = h.get_state()[2].cpu().numpy()
+        assert np.array_equal(g, line8_sum(n, d, k, idx, val) * (np.float32(1) / np.float32(n))), (n, d, k, flags)
