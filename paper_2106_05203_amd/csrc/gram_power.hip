@@ -9,12 +9,14 @@
 //   gram_finish   the chunks added, divided by m, rounded to fp32 once and written to both halves; one more matrix is
 //                 the mean over the workers, G = (1/(nm)) sum_i A_i^T A_i.
 //   The estimate after T iterations is sqrt(u_2T / u_2T-2), u_N = v' G^N v with the start vector v.  Between 48 and 2822
-//   iterations these moments come from J = 4.8 sqrt(T) steps of the Lanczos recurrence instead (two in the place of four
-//   products with G at T = 100): u_N / |v|^2 is entry (1, 1) of the N-th power of its J x J tridiagonal matrix, exactly for
+//   iterations these moments come from J = ceil(4.8 sqrt(T)) + 1 steps of the Lanczos recurrence instead (49 products
+//   with G in the place of 100 at T = 100): u_N / |v|^2 is entry (1, 1) of the N-th power of its J x J tridiagonal matrix, exactly for
 //   N < 2J and to twice the error of the best polynomial of degree 2J - 1 on [0, lambda_max] beyond; for t^N that is at most
 //   2 exp(-4 J^2 / N) (Newman and Rivlin, Approximation of monomials by lower degree polynomials, 1976): 2e-20 of
 //   lambda_max^N.  What loss of orthogonality adds is rounding (Druskin and Knizhnerman, Error bounds in the simple Lanczos
-//   procedure, 1991): on Gaussian, non-negative, low-rank and badly scaled matrices the two estimates agree to 1e-15.
+//   procedure, 1991): the tests hold the estimates against the power iteration in fp64 from the same
+//   start vector on Gaussian, non-negative, rank-three, rank-one, badly scaled and diagonal matrices, where what is
+//   left is the start vector's rounding to fp32 (2^-23).
 //   The T iterations are then taken with the tridiagonal matrix, by one wavefront.  n = 20, m = 2487, d = 300, 100
 //   iterations: 436 -> 319 us a call;
 //   n = 2, m = 7500, d = 1000: 1255 -> 800.

@@ -230,15 +230,66 @@ def test_recurrence_gives_the_power_iterations_value(gpu, d):
             np.testing.assert_allclose(got, diagonal_power(rounded, steps), rtol=2.4e-8, err_msg=f"{steps} iterations")
 
 
+def matrices_of_a_kind(kind, n, m, d, rng):
+    A = rng.standard_normal((n, m, d))
+    if kind == "non-negative":                            # one dominant eigenvalue
+        A = rng.random((n, m, d))
+    if kind == "rank 3":                                  # the recurrence ends after three steps, in exact arithmetic
+        A = rng.standard_normal((n, m, 3)) @ rng.standard_normal((n, 3, d))
+    if kind == "badly scaled":                            # eigenvalues over twelve orders of magnitude
+        A = A * 10.0 ** -np.linspace(0, 6, d)
+    if kind == "one entry":                               # rank one, in a direction the start vector hardly has
+        A = np.zeros((n, m, d))
+        A[:, 0, d // 2] = 3.0
+    if kind == "zero":
+        A = np.zeros((n, m, d))
+    return A.astype(np.float32)
+
+
+@pytest.mark.parametrize("kind", ["Gaussian", "non-negative", "rank 3", "badly scaled", "one entry", "zero"])
+@pytest.mark.parametrize("d", [5, 40, 300, 320, 700])         # fewer columns than steps, and each form of the product
+def test_recurrence_on_kinds_of_matrices(gpu, kind, d):
+    torch, binding = gpu
+    print(f"recurrence on {kind} matrices, d={d}", flush=True)
+    n, m, lam = 2, 500, 0.0 if kind != "zero" else 0.125
+    A = matrices_of_a_kind(kind, n, m, d, np.random.default_rng(d))
+    G = np.array([a.astype(np.float64).T @ a.astype(np.float64) / m for a in A])
+    G = np.concatenate([G, G.mean(0)[None]]).astype(np.float32).astype(np.float64)
+    with binding.EF21(n, d, 1, 0.1) as h:
+        h.set_problem_dense(to_gpu(torch, A), to_gpu(torch, np.zeros((n, m), np.float32)), lam)
+        for steps in (48, 100, 400, 2822):
+            _, L, L_i = h.theory_stepsize(steps)
+            got = 4.0 * (np.array(list(L_i) + [L]) - 2.0 * lam)
+            want = np.array([power_estimate(G[row], row, steps) for row in range(n + 1)])
+            # The start vectors' entries may differ by 2^-23 (see above): each weight in the two moments by 2^-22, the estimate by
+            # at most half of that.  The matrices are rounded to fp32 on both sides from sums in fp64 that differ in their
+            # last bits: an entry may fall to the other side, 2^-24 of it, a vanishing part of the whole.
+            np.testing.assert_allclose(got, want, rtol=2.0 ** -23, err_msg=f"{steps} iterations")
+
+
+def power_estimate(G, row, steps):
+    v = start_vector(G.shape[0], row)
+    for _ in range(steps - 1):
+        v = G @ v
+        size = np.linalg.norm(v)
+        if size == 0.0:
+            return 0.0
+        v /= size
+    return np.linalg.norm(G @ v) / np.linalg.norm(v)
+
+
+def start_vector(d, row):
+    h = (np.arange(d, dtype=np.uint64) * 2654435761 + 0x9e3779b9 * (row + 1)) & 0xffffffff
+    h ^= h >> 15
+    h = (h * 2246822519) & 0xffffffff
+    h ^= h >> 13
+    return ((0.5 + (h >> 8).astype(np.float32) * np.float32(1 / 16777216)) / np.sqrt(np.float32(d))).astype(np.float64)
+
+
 def diagonal_power(eigenvalues, steps):
     out = []
     for row, e in enumerate(eigenvalues):
-        d = e.size
-        h = (np.arange(d, dtype=np.uint64) * 2654435761 + 0x9e3779b9 * (row + 1)) & 0xffffffff
-        h ^= h >> 15
-        h = (h * 2246822519) & 0xffffffff
-        h ^= h >> 13
-        v = ((0.5 + (h >> 8).astype(np.float32) * np.float32(1 / 16777216)) / np.sqrt(np.float32(d))).astype(np.float64)
+        v = start_vector(e.size, row)
         for _ in range(steps - 1):
             v = e * v
             v /= np.linalg.norm(v)
