@@ -159,17 +159,20 @@ int ef21_set_minibatch(ef21_handle h, const int32_t *rows, int64_t tau);
  *   L_i = c lambda_max((1/m) A_i^T A_i) + 2 lambda
  * (c = 1/4 for the logistic loss, 2 for least squares: the largest curvature of the per-row loss; 2 is the
  * largest curvature of t^2 / (1 + t^2)), and L = c lambda_max((1/(n m)) sum_i A_i^T A_i) + 2 lambda for f itself.
- * The eigenvalues come from `iterations` steps of the power iteration on the GPU (each step two passes of
- * the gradient kernels over the problem), started from a fixed positive vector; the estimate |M v| for the
+ * The eigenvalues are the estimates that `iterations` steps of the power iteration give on the GPU, started from a fixed
+ * positive vector: the estimate |M v| for the
  * unit vector v of the last step approaches lambda_max from below, so few iterations give a stepsize that is
  * too large by the same factor: 100 to 300 steps bring problems without a dominant direction within about one
  * per cent.  gamma, L, L_i [n]: host memory, each may be NULL.  Uses the handle's loss, lambda and k, and all
  * rows whatever ef21_set_minibatch says; the handle's stepsize is not changed.  Returns after the stream has drained.
  * A dense problem with d <= 1024 columns is iterated on the workers' Gram matrices where that is the faster way (it is from
- * some ten iterations on, usually); a call that needs more than the handle has allocates a workspace of
- * 4 (n + 1) d'^2 + 4 n c d' (d' + 32) bytes (d' = d rounded up to 32, c pieces of a worker's rows, one or as many as make
- * a thousand tiles in all), never more than 1 GiB, which the handle keeps until ef21_destroy.
- * Where that much is not to be had, and for all other problems, a call iterates with the problem itself: the first one
+ * some ten iterations on, usually); 48 to 2822 iterations are then not run one by one, but their estimate is taken from
+ * ceil(4.8 sqrt(iterations)) + 1 steps of the Lanczos recurrence on the same start vector, which give it to fp64 rounding.
+ * A call that needs more than the handle has allocates a workspace of
+ * 4 (n + 1) d'^2 + 4 n c d' (d' + 32) + 8 (n + 1) (5 d' + 512) bytes (d' = d rounded up to 32, c pieces of a worker's rows, one
+ * or as many as make a thousand tiles in all) and some hundred for alignment, never more than 1 GiB, which the handle keeps until ef21_destroy.
+ * Where that much is not to be had, and for all other problems, a call iterates with the problem itself, a step two passes
+ * of the gradient kernels over it: the first one
  * on a handle allocates (n + 2) d floats that the handle keeps, and every one overwrites the handle's gradient buffer.
  * EF21_ESTATE without a problem; EF21_EINVAL: iterations outside [1, 10^6]; EF21_ENOMEM.
  */
@@ -211,11 +214,11 @@ int ef21_local_grad(ef21_handle h, const float *x, float *out_grad);
  * With supplied gradients every result (messages, g_i, g, x) is bitwise reproducible.
  * With EF21_ONE_LAUNCH in flags, a small dense problem (grads NULL, d <= 1024, n * k <= 2048,
  * n * m * d <= 2^24, no minibatch, no EF21_PLUS) runs the whole pass as ONE kernel: the same arithmetic in the
- * same order as the separate gradient, Top-k and aggregation kernels, so the results are the same bits.  It
- * saves two launches and pays for them in device-scope fences: measured within ten per cent of the separate kernels
- * either way for two to four workers with a few hundred rows of 100 columns (n = 4, m = 250, d = 100: 12.0 us against 11 to
- * 15, the more the slower the host launches) and slower for larger problems and more workers (n = 20, m = 1628,
- * d = 123: 21.7 against 15), hence not the default.  Where the problem does not qualify the flag changes nothing.
+ * same order as without the flag, so the results are the same bits.  It saves one launch (two where a worker's rows are
+ * too many for one workgroup) and pays for it in device-scope fences: measured within five per cent of the
+ * default for a few workers with a few hundred rows of 100 columns (calls back to back: n = 4, m = 250, d = 100 8.7 us against
+ * 8.6, m = 500 10.2 against 10.4) and slower for larger problems and more workers (n = 20, m = 1628,
+ * d = 123: 20.3 against 13.3), hence not the default.  Where the problem does not qualify the flag changes nothing.
  * EF21_EINVAL: unknown flag bits, or EF21_CLASSIC_EF together with an order or EF21_PLUS.
  */
 int ef21_step(ef21_handle h, const float *grads, uint32_t flags);
