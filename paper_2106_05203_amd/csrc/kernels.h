@@ -96,8 +96,10 @@ struct TopkArgs {
 
 // Rows this long can be handed to launch_topk_row as unreduced gradients (TopkArgs::parts).  Longer ones are finished by a
 // kernel that the whole chip shares, and launch_topk_row_reg selects from the differences.  step, us, unreduced and
-// finished: n = 4, m = 500, d = 700 14.0 and 15.6; n = 10, m = 1000, d = 800 18.5 and 19.4; n = 20, m = 2000, d = 1000 42.4 and 40.3;
-// n = 4, m = 250, d = 2000 17.8 and 16.6.
+// finished, k = d / 20: d = 700: n = 10, m = 8 16.1 and 16.7, n = 32, m = 500 23.5 and 24.2, n = 10, m = 2000 24.0 and 23.7; d = 900:
+// n = 4, m = 8 15.7 and 16.2, n = 4, m = 500 18.3 and 17.8, n = 10, m = 2000 28.0 and 26.9; d = 1000: 15.8 and 16.4, 18.0 and 17.7, 29.7
+// and 28.3; d = 1200: 17.7 and 17.8, 21.6 and 19.7, 35.0 and 32.4; d = 2000: 21.0 and 18.5, 26.0 and 20.8, 48.5 and 43.7.  Around
+// 900 the few-row problems still gain what the many-row ones lose.
 constexpr int64_t kRowPartsMax = 900;
 
 // One workgroup per row: a histogram pass over the row and a ranking of the threshold's bin (three histogram passes where

@@ -447,15 +447,14 @@ hipError_t launch_logreg_grad_dense(const float *A, const float *y, const float 
     hipError_t st = hipGetLastError();
     if (st != hipSuccess) return st;
     // The consumer finishes the sums itself (dense_grad_entry) where that is less work for its one workgroup per row than
-    // another kernel of 3 to 5 us: 1 us per 40 KB of sums and per 1000 columns (the regulariser's divisions); many sums per column
+    // another kernel of 3 to 5 us: on short rows (kRowPartsMax) with few sums per column, or with more of them 1 us per 40 KB of
+    // sums and per 1000 columns (the regulariser's divisions); many sums per column
     // go better by the threads of the kernel that shares them out.  step, us, with the sums left and finished: n = 2, m = 40000,
-    // d = 250 (256 blocks) 31.3 and 27.2; n = 2, m = 50000, d = 300 (256) 34.6 and 31.5; n = 4, m = 2000, d = 1000 (64) 20.7 and 19.7;
-    // n = 1, m = 200000, d = 80 (512) 26.8 and 25.5; n = 2, m = 700, d = 1500 (32) 19.0 and 20.4; n = 8, m = 1000, d = 1000 (32) 19.4
-    // and 20.4; n = 20, m = 5000, d = 2000 (25) 136.8 and 135.6; n = 32, m = 200, d = 8000 (8) 75 and 65; n = 1, m = 1000, d = 8000
-    // (250) 116 and 39.
-    constexpr int64_t kColumnWork = 25, kManyBlocks = 32;
-    const int64_t parts_work = pl.chunks > kManyBlocks ? 60000 : 90000;
-    if (defer && fused && x_stride == 0 && d <= kRowPartsMax && pl.chunks <= 256 && (pl.chunks + kColumnWork) * d <= parts_work) {
+    // d = 250 (256 blocks) 31.3 and 27.2; n = 2, m = 50000, d = 300 (256) 34.6 and 31.5; n = 1, m = 200000, d = 80 (512) 26.8 and
+    // 25.5.
+    constexpr int64_t kColumnWork = 25, kFewBlocks = 32, kPartsWork = 60000, kPartsBlocks = 256;
+    const bool little = pl.chunks <= kFewBlocks || (pl.chunks <= kPartsBlocks && (pl.chunks + kColumnWork) * d <= kPartsWork);
+    if (defer && fused && x_stride == 0 && d <= kRowPartsMax && little) {
         *defer = GradParts{part, pl.chunks, m, x, lambda};
         return hipSuccess;
     }

@@ -28,7 +28,7 @@ __global__ __launch_bounds__(kRowThreads) void topk_row_cached_kernel(TopkArgs p
 template <int UPDATE>
 __global__ __launch_bounds__(kRowThreads) void topk_row_parts_kernel(TopkArgs p) {
     __shared__ RowShared s;
-    __shared__ float cache[kRowCacheShort];
+    __shared__ float cache[kRowPartsMax];
     row_topk_parts<UPDATE>(s, cache, p, blockIdx.x);
 }
 
@@ -58,7 +58,7 @@ hipError_t launch_topk_row(const TopkArgs &p, hipStream_t stream) {
     const bool diff = p.b != nullptr, upd = p.g_i != nullptr;
     if (upd && p.g_i != (diff ? p.b : p.a)) return hipErrorInvalidValue;
     if (p.parts.part) {
-        if (!diff || p.d > kRowCacheShort) return hipErrorInvalidValue;
+        if (!diff || p.d > kRowPartsMax) return hipErrorInvalidValue;
         if (upd) hipLaunchKernelGGL((topk_row_parts_kernel<kAddUpdate>), grid, block, 0, stream, p);
         else hipLaunchKernelGGL((topk_row_parts_kernel<kNoUpdate>), grid, block, 0, stream, p);
         return hipGetLastError();

@@ -450,7 +450,7 @@ def test_few_workers_fill_the_chip(gpu, n, d, m):
 # 8 and up to 16 entries of a chain in flight, each with a last, partial group of 64 columns, and the sums left to the Top-k kernel: an
 # iteration from the reported gradient and one that forms its own agree bit for bit (both add the chains in the same order)
 @pytest.mark.parametrize("n,d,m", [(2, 100, 700), (30, 70, 1600), (3, 130, 5000), (1, 65, 9000), (1, 1, 20000), (2, 300, 60000),
-                                   (1, 1001, 3000), (12, 3000, 400), (8, 5000, 300)])
+                                   (1, 1001, 3000), (12, 3000, 400), (8, 5000, 300), (3, 900, 640), (3, 901, 640), (14, 600, 4000), (1, 224, 40000)])
 def test_partial_sums_of_many_blocks(gpu, n, d, m):
     torch, binding = gpu
     print(f"partial sums n={n} d={d} m={m}", flush=True)
