@@ -232,7 +232,8 @@ int ef21_step(ef21_handle h, const float *grads, uint32_t flags);
  * rows added in worker order in fp64 and the mean rounded once (line 10).  ef21_get_messages then returns, per worker, the k pairs
  * of the compressor it chose.  The first such call on a handle allocates (and waits for the stream): 16 n k bytes for
  * the two selections, and for rows of 16384 entries or more with k > 1 a second Top-k workspace (about 8 d + 90 000 bytes
- * per row, as the handle's first) and, where there is room for it, 4 n d bytes more (without them the step is slower).
+ * per row, as the first, which a handle has from the start if d > 61440 or k > 1024 and else gets here) and, where there is
+ * room for it, 4 n d bytes more (without them the step is slower).
  *
  * ef21_get_choices copies out what the last EF21_PLUS step decided: branch [n] int32 (1 = the plain
  * compressor b was chosen, 0 = the Markov compressor m) and distortions [n][2] fp64 (B_i, M_i); either

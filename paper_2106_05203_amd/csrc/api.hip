@@ -127,7 +127,7 @@ struct ef21_ctx {
     float *grad = nullptr;
     void *scratch = nullptr;
     size_t scratch_bytes = 0;
-    void *topk_ws = nullptr;
+    void *topk_ws = nullptr;        // where the rows need one (topk_needs_workspace), and for Algorithm 3 on all long rows
     void *topk_ws2 = nullptr;       // second long-row workspace: the plain compressor of Algorithm 3
     void *agg_index = nullptr;      // runs of the messages per coordinate sub-block (scratch of line 8)
     void *tickets = nullptr;        // counters of the one-launch iteration (zero between launches)
@@ -347,7 +347,7 @@ ef21_handle ef21_create(int32_t n, int64_t d, int64_t k, float gamma) {
               hipMalloc((void **)&c->msg_idx, sizeof(int32_t) * nk) == hipSuccess &&
               hipMalloc((void **)&c->msg_val, sizeof(float) * nk) == hipSuccess;
     if (ok) ok = hipMalloc(&c->agg_index, ef21::aggregate_index_bytes(n, d)) == hipSuccess;
-    if (ok && use_split(d))
+    if (ok && topk_needs_workspace(d, k))
         ok = alloc_split_workspace(&c->topk_ws, ef21::topk_split_workspace_bytes(n, d, k), n, d) == hipSuccess;
     if (ok)
         ok = hipMemset(c->x, 0, sizeof(float) * d) == hipSuccess && hipMemset(c->g, 0, sizeof(float) * d) == hipSuccess &&
@@ -685,14 +685,17 @@ static int ensure_plus_buffers(ef21_ctx *c) {
     if (c->plus_bm) return EF21_OK;
     const size_t nk = (size_t)c->n * (size_t)c->k;
     EF21_HIP(hipStreamSynchronize(c->stream));
+    const bool split = use_split(c->d) && c->k > 1;       // both selections by many workgroups per row, a workspace each
+    const bool first = split && !c->topk_ws;
+    const size_t ws_bytes = split ? ef21::topk_split_workspace_bytes(c->n, c->d, c->k) : 0;
     if (hipMalloc((void **)&c->plus_idx, sizeof(int32_t) * 2 * nk) != hipSuccess ||
         hipMalloc((void **)&c->plus_val, sizeof(float) * 2 * nk) != hipSuccess ||
-        hipMalloc(&c->plus_scratch, c->topk_ws && c->k > 1 ? ef21::plus_long_layout(c->n, c->d, nullptr, nullptr)
-                                                           : ef21::plus_scratch_bytes(c->n, c->d, c->k)) != hipSuccess ||
+        hipMalloc(&c->plus_scratch, split ? ef21::plus_long_layout(c->n, c->d, nullptr, nullptr)
+                                          : ef21::plus_scratch_bytes(c->n, c->d, c->k)) != hipSuccess ||
         hipMalloc((void **)&c->plus_branch, sizeof(int32_t) * (size_t)c->n) != hipSuccess ||
         hipMalloc((void **)&c->plus_bm, sizeof(double) * 2 * (size_t)c->n) != hipSuccess ||
-        (c->topk_ws && c->k > 1 &&
-         alloc_split_workspace(&c->topk_ws2, ef21::topk_split_workspace_bytes(c->n, c->d, c->k), c->n, c->d) != hipSuccess)) {
+        (first && alloc_split_workspace(&c->topk_ws, ws_bytes, c->n, c->d) != hipSuccess) ||
+        (split && alloc_split_workspace(&c->topk_ws2, ws_bytes, c->n, c->d) != hipSuccess)) {
         (void)hipGetLastError();
         (void)hipFree(c->plus_idx);
         (void)hipFree(c->plus_val);
@@ -701,6 +704,10 @@ static int ensure_plus_buffers(ef21_ctx *c) {
         (void)hipFree(c->plus_bm);
         (void)hipFree(c->topk_ws2);
         c->topk_ws2 = nullptr;
+        if (first) {
+            (void)hipFree(c->topk_ws);
+            c->topk_ws = nullptr;
+        }
         c->plus_idx = nullptr;
         c->plus_val = nullptr;
         c->plus_scratch = nullptr;
@@ -779,7 +786,7 @@ static int enqueue_classic_ef(ef21_ctx *h, const float *grads, const ef21::Marke
     // p_i over e_i: by the pass of the long-row Top-k that reads the rows, once there are thresholds to start from, else by a
     // kernel of its own.  A round, us, in two passes and in one: n = 5, d = 1 000 003, k = 50 000 46.4 and 42.2; n = 20, d = 1.5
     // million, k = 60 000 141 and 119; n = 8, d = 11.2 million, k = 112 000 381 and 322.
-    const bool split = use_split(h->d) && h->topk_ws && !use_row_reg(h->d, h->k) && h->k > 1;
+    const bool split = topk_needs_workspace(h->d, h->k) && h->k > 1;
     if (split && h->ef_started) {
         p.add = grads;
         p.add_scale = h->gamma;
@@ -859,7 +866,7 @@ int ef21_step(ef21_handle h, const float *grads, uint32_t flags) {
     }
     ef21::GradParts parts;
     if (!grads) {
-        const bool row_kernel = !(use_split(h->d) && h->topk_ws);
+        const bool row_kernel = !use_split(h->d);
         if (int rc = enqueue_local_grad(h, h->x, h->grad, row_kernel ? &parts : nullptr)) return rc;
         grads = h->grad;
     }

@@ -262,3 +262,34 @@ def test_many_workers_on_long_rows(gpu, oracle, n, d, k, order):
             h.step(to_gpu(torch, grads), flags)
             compare_plus_step(torch, h, st, choice, x_before, gamma, f"step {t}")
             h.set_state(to_gpu(torch, st.x), to_gpu(torch, st.g_i), to_gpu(torch, st.g))
+
+
+def test_workspace_of_rows_held_in_registers(gpu):
+    """Rows of 16 384 to 61 440 entries of which up to 1024 are kept are selected without a workspace, so a handle holds none
+    until its first EF21+ step, which selects with many workgroups per row; and that step's result is that of a handle which
+    took no other step before."""
+    torch, binding = gpu
+    n, d, k = 1000, 50_000, 10
+    state = 4 * n * d + 8 * n * k + 4 * n * (d // 256 + 2)         # g_i, messages, message index
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    h = binding.EF21(n, d, k, 0.1)
+    held = before - torch.cuda.mem_get_info()[0]
+    print(f"  held {held / 2**20:.0f} MiB, of which state {state / 2**20:.0f}", flush=True)
+    assert held < state + (64 << 20), "a workspace of 8 d + 90 000 bytes per row would be 490 MB more"
+    h.close()
+
+    n, d, k = 3, 20_001, 200
+    g = torch.Generator(device="cuda")
+    g.manual_seed(5)
+    s = [torch.randn((n, d), device="cuda", generator=g) for _ in range(3)]
+    with binding.EF21(n, d, k, 0.1) as h, binding.EF21(n, d, k, 0.1) as fresh:
+        h.set_state(x=torch.zeros(d, device="cuda"), g_i=torch.zeros((n, d), device="cuda"))
+        h.step(s[0])
+        x, g_i, g0 = h.get_state()
+        fresh.set_state(x, g_i, g0)
+        for e in (h, fresh):
+            e.step(s[1], binding.PLUS)
+            e.step(s[2])
+        for a, b in zip(h.get_state() + h.get_messages(), fresh.get_state() + fresh.get_messages()):
+            assert torch.equal(a, b)

@@ -66,7 +66,7 @@ def test_two_calls_in_a_row_second_smaller(gpu, oracle):
 def test_shapes_without_workspace_and_ties(gpu):
     rng = np.random.default_rng(5)
     agree(gpu, rng.standard_normal((6, 5000)).astype(np.float32), 50)          # one workgroup per row
-    agree(gpu, rng.standard_normal((3, 40_000)).astype(np.float32), 400)       # 16-bit prefixes in LDS
+    agree(gpu, rng.standard_normal((3, 40_000)).astype(np.float32), 400)       # the row in registers
     V = np.round(rng.standard_normal((2, 100_000)) * 4).astype(np.float32) / 4  # heavy ties, long rows
     agree(gpu, V, 5000)
     agree(gpu, np.zeros((2, 66_000), dtype=np.float32), 3000)                  # all equal: the slots fill up
