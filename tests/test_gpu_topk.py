@@ -153,22 +153,25 @@ def test_either_side_of_the_shortest_rows_in_registers(gpu, n, d):
         assert same_bits(val, np.take_along_axis(V, ref, axis=1)), (n, d, k)
 
 
+@pytest.mark.parametrize("copies", [1, 2])
 @pytest.mark.parametrize("d", [513, 4097, 12289, 24577, 50001, 61440])
-def test_differences_held_in_registers(gpu, d):
-    """The same for grad - g_i inside a step: message, and g_i updated at the kept positions only."""
+def test_differences_held_in_registers(gpu, d, copies):
+    """The same for grad - g_i inside a step: message, g_i updated at the kept positions only, and g and x, which are added
+    up by the index that the kernel writes on each of its ways (9 workers: blocks of 512 columns, 18: of 256)."""
     torch, binding = gpu
     k = min(d // 8, 500)
     S = rows_for_registers(d, k, d)
     S[6] = S[0]                                        # (a step keeps NaN in its state: not compared here)
     G = np.random.default_rng(d + 1).standard_normal(S.shape).astype(np.float32)
     G[1:3] = 0.0                                       # ties and zeros stay what they are
+    S, G = np.tile(S, (copies, 1)), np.tile(G, (copies, 1))
     n = S.shape[0]
     dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
     with binding.EF21(n, d, k, 0.1) as h:
-        h.set_state(x=torch.zeros(d, device="cuda"), g_i=dev(G))
+        h.set_state(x=torch.zeros(d, device="cuda"), g_i=dev(G), g=torch.zeros(d, device="cuda"))
         h.step(dev(S))
         idx, val = (t.cpu().numpy() for t in h.get_messages())
-        _, g_i, _ = (t.cpu().numpy() for t in h.get_state())
+        x, g_i, g = (t.cpu().numpy() for t in h.get_state())
     diff = S - G
     ref = first_by_magnitude(diff, k)
     assert np.array_equal(idx, ref)
@@ -177,6 +180,11 @@ def test_differences_held_in_registers(gpu, d):
     want = G.copy()
     np.put_along_axis(want, ref, np.take_along_axis(G, ref, axis=1) + kept, axis=1)
     assert same_bits(g_i, want)
+    c = np.zeros((n, d))
+    np.put_along_axis(c, ref, kept.astype(np.float64), axis=1)
+    # n - 1 additions, the rounding of 1 / n and the fused multiply-add
+    assert np.all(np.abs(g - c.mean(axis=0)) <= (n + 2) * 2.0**-24 * np.abs(c).mean(axis=0))
+    assert np.array_equal(x, np.float32(-0.1) * g)
 
 
 @pytest.mark.parametrize("d,k", [(70001, 700), (262144, 5), (300007, 3000), (1_000_003, 999), (70001, 1), (1_000_003, 1),
