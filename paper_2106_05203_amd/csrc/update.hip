@@ -272,10 +272,11 @@ __global__ __launch_bounds__(kThreads) void aggregate_many_kernel(const int32_t 
 // messages in LDS; then ONE wavefront adds them to the LDS accumulator worker by worker, 64 entries of a
 // worker per step (positions inside a message are distinct, and a wavefront's LDS accesses execute in
 // program order, so no barrier is needed between workers) while the other wavefronts fetch g and x.
-// Two pairs a thread and 12 288 columns are what the rule admits; with room for 8192 pairs and 16 384 columns a step of 4 x 1000,
-// k = 100 took 8.6 us, of 1 x 622, k = 622 8.5 and of 64 x 70, k = 20 14.5: 8.1, 8.0 and 12.3 so.
-constexpr int kSmallThreads = 1024, kSmallPer = 2;
-constexpr int kSmallD = 12288, kSmallEntries = kSmallThreads * kSmallPer;
+// Room for what the rule admits, in two sizes: up to two pairs a thread and 12 288 columns, or up to eight pairs and 3072 columns.
+// With eight and 16 384 for all calls a step of 4 x 1000, k = 100 took 8.6 us, of 1 x 622, k = 622 8.5 and of 64 x 70, k = 20 14.5: 8.1,
+// 8.0 and 12.3 so.
+constexpr int kSmallThreads = 1024;
+constexpr int kFewPer = 2, kFewCols = 12288, kManyPer = 8, kManyCols = 3072;
 constexpr int kSmallSteps = 512;     // at most this many sequential steps of the adding wavefront
 constexpr int kScanEntries = 128;    // messages in all that every coordinate can look through (n = 20, k = 4: 4.8 -> 2.8 us)
 constexpr int kSmallFetch = 4;       // coordinates per thread fetched ahead (d <= 4096)
@@ -286,33 +287,29 @@ constexpr int kSmallAhead = 8;
 // 70.5 and 59.3; 64 x 300, k = 30 14.5 and 13.7; 8 x 1000, k = 64 8.1 and 8.4; 20 x 1000, k = 100 12.2 and 12.7.
 constexpr int kSmallLanes = 32;
 
-template <bool STEP>
+template <bool STEP, int PER, int COLS>
 __global__ __launch_bounds__(kSmallThreads) void aggregate_small_kernel(const int32_t *__restrict__ idx,
                                                                         const float *__restrict__ val, int32_t n,
                                                                         int64_t k, int64_t d, float *__restrict__ g,
                                                                         float *__restrict__ x, float inv_n,
                                                                         float neg_gamma, bool from_zero) {
-    __shared__ float acc[kSmallD];
-    __shared__ __attribute__((aligned(16))) int32_t m_idx[kSmallEntries];
-    __shared__ __attribute__((aligned(16))) float m_val[kSmallEntries];
+    __shared__ float acc[COLS];
+    __shared__ __attribute__((aligned(16))) int32_t m_idx[PER * kSmallThreads];
+    __shared__ __attribute__((aligned(16))) float m_val[PER * kSmallThreads];
     const int tid = threadIdx.x, lane = lane_id();
     const int64_t total = (int64_t)n * k;
-    int32_t e[kSmallPer];
-    float v[kSmallPer];
+    int32_t e[PER];
+    float v[PER];
 #pragma unroll
-    for (int u = 0; u < kSmallPer; ++u) {
-        e[u] = 0;
-        v[u] = 0.f;
-        if ((int64_t)u * kSmallThreads < total) {                // uniform
-            const int64_t t = tid + (int64_t)u * kSmallThreads;
-            const int64_t at = t < total ? t : 0;
-            e[u] = idx[at];
-            v[u] = val[at];
-        }
+    for (int u = 0; u < PER; ++u) {
+        const int64_t t = tid + (int64_t)u * kSmallThreads;
+        const int64_t at = t < total ? t : 0;
+        e[u] = idx[at];
+        v[u] = val[at];
     }
     for (int64_t j = tid; j < d; j += kSmallThreads) acc[j] = 0.f;
 #pragma unroll
-    for (int u = 0; u < kSmallPer; ++u) {
+    for (int u = 0; u < PER; ++u) {
         const int64_t t = tid + (int64_t)u * kSmallThreads;
         if (t < total) {
             m_idx[t] = e[u];
@@ -449,27 +446,33 @@ size_t aggregate_index_bytes(int32_t n, int64_t d) {      // for the shorter of 
 }
 
 namespace {
-// One workgroup adds one step after the other, 0.12 us each, and walks all coordinates; the kernels with a wavefront or
-// four per block of coordinates take a message index, which launch_topk_row_reg and launch_topk_split write with the message
-// (kReachIndexed) and a kernel of its own where neither selects, on short rows and where more than an eighth is kept
-// (kReachNot).  step with supplied gradients, us, small and not, workers x columns, k (steps + columns / 512):
-// with the index at hand: 5 x 10000, 30 (24) 10.4 and 10.4; 8 x 10000, 30 (27) 10.6 and 10.3; 10 x 5000, 130 (39) 12.4 and 11.6;
-// 8 x 2000, 200 (35) 11.6 and 10.4; without: 1 x 1500, 1500 (26) 10.0 and 12.5; 8 x 1500, 250 (34) 11.9 and 13.6; 4 x 2468,
-// 493 (36) 13.0 and 14.0; 3 x 4000, 640 (37) 14.3 and 14.6; 6 x 2600, 330 (41) 14.2 and 13.0; 2 x 6000, 1000 (43) 17.0 and 16.3;
-// 1 x 12000, 1900 (53) 23.7 and 22.0.  Up to 1024 coordinates and 2048 pairs
+// One workgroup adds one step (64 pairs of a worker) after the other, 0.12 us each, and walks all coordinates; the kernels with a
+// wavefront or four per block of coordinates take a message index, which launch_topk_row_reg and launch_topk_split write with the
+// message, and a kernel of its own (2.5 us) where neither selects, on short rows and where more than an eighth of a row is kept:
+// there a block's runs are long, and their pairs are read in turn.  step with supplied gradients, us, small and not, workers x
+// columns, k (steps + columns / 512).  With the index at hand: 5 x 10000, 30 (24) 10.4 and 10.4; 8 x 10000, 30 (27) 10.6 and 10.3;
+// 10 x 5000, 130 (39) 12.4 and 11.6; 8 x 2000, 200 (35) 11.6 and 10.4.  Without: 8 x 300, 300 (40) 12.1 and 18.5; 12 x 500, 500 (96)
+// 18.5 and 35.0; 4 x 1000, 1000 (65) 15.5 and 18.1; 2 x 1500, 1500 (50) 13.6 and 15.1; 15 x 1500, 195 (62) 16.2 and 14.7; 3 x 1500,
+// 1500 (74) 17.1 and 16.8; 4 x 2468, 493 (36) 13.0 and 14.0; 6 x 2500, 325 (40) 14.5 and 13.6; 1 x 2500, 2500 (44) 13.4 and 14.6;
+// 3 x 4000, 520 (34) 14.7 and 14.6; 1 x 8000, 2000 (47) 19.1 and 17.8; 16 workers and more: 16 x 300, 300 17.0 and 13.9; 32 x 500, 65
+// 15.2 and 10.9.  Up to 1024 coordinates and 2048 pairs
 // the sums are those of the iteration in one launch (small_step.hip) to the bit, in worker order, so they stay here.
-constexpr int64_t kSmallStep1 = 1024, kReachIndexed = 24, kReachNot = 38;
+constexpr int64_t kSmallStep1 = 1024, kReachIndexed = 24, kReachNot = 38, kReachNot1 = 44, kReachNot3 = 52, kSmallCols3 = 1536;
 static_assert(kReachIndexed <= kReachNot, "with an index there is one more reason against the one workgroup");
-bool aggregate_is_small(int32_t n, int64_t k, int64_t d, int64_t reach) {
-    const int64_t steps = (int64_t)n * ((k + kWave - 1) / kWave);
-    if (d > kSmallD || (int64_t)n * k > kSmallEntries || steps > kSmallSteps) return false;
-    return d <= kSmallStep1 || (n < kManyWorkers && steps + d / 512 <= reach);
+bool aggregate_is_small(int32_t n, int64_t k, int64_t d, bool indexed) {
+    const int64_t pairs = (int64_t)n * k, steps = (int64_t)n * ((k + kWave - 1) / kWave), reach = steps + d / 512;
+    if (pairs > (int64_t)kManyPer * kSmallThreads || steps > kSmallSteps || d > kFewCols) return false;
+    const bool few = pairs <= (int64_t)kFewPer * kSmallThreads;
+    if (few && d <= kSmallStep1) return true;
+    if (n >= kManyWorkers || !(few || d <= kManyCols)) return false;
+    if (indexed) return reach <= kReachIndexed;
+    return d <= kSmallStep1 || reach <= (d <= kSmallCols3 ? kReachNot3 : n == 1 ? kReachNot1 : kReachNot);
 }
 }  // namespace
 
 int aggregate_index_shift(int32_t n, int64_t k, int64_t d) {
     static_assert(kManySub == 1 << 8 && kAggSub == 1 << 9 && kAggLong == 1 << 11, "block lengths as shifts");
-    if (aggregate_is_small(n, k, d, kReachIndexed)) return -1;
+    if (aggregate_is_small(n, k, d, true)) return -1;
     if (n >= kManyWorkers) return 8;
     return d >= 4000000 && d <= 8000000 && k * 100 <= d ? 11 : 9;
 }
@@ -477,13 +480,18 @@ int aggregate_index_shift(int32_t n, int64_t k, int64_t d) {
 hipError_t launch_aggregate(const int32_t *idx, const float *val, int32_t n, int64_t k, int64_t d, float *g, float *x,
                             float gamma, void *index, hipStream_t stream, bool index_ready, bool from_zero) {
     const float inv_n = 1.0f / (float)n;
-    if (!index_ready && aggregate_is_small(n, k, d, kReachNot)) {
-        if (x)
-            hipLaunchKernelGGL(aggregate_small_kernel<true>, dim3(1), dim3(kSmallThreads), 0, stream, idx, val, n, k, d,
-                               g, x, inv_n, -gamma, from_zero);
-        else
-            hipLaunchKernelGGL(aggregate_small_kernel<false>, dim3(1), dim3(kSmallThreads), 0, stream, idx, val, n, k,
-                               d, g, x, inv_n, -gamma, from_zero);
+    if (!index_ready && aggregate_is_small(n, k, d, false)) {
+#define EF21_SMALL(STEP, PER, COLS)                                                                                     \
+    hipLaunchKernelGGL((aggregate_small_kernel<STEP, PER, COLS>), dim3(1), dim3(kSmallThreads), 0, stream, idx, val, n, k, \
+                       d, g, x, inv_n, -gamma, from_zero)
+        if ((int64_t)n * k <= (int64_t)kFewPer * kSmallThreads) {
+            if (x) EF21_SMALL(true, kFewPer, kFewCols);
+            else EF21_SMALL(false, kFewPer, kFewCols);
+        } else {
+            if (x) EF21_SMALL(true, kManyPer, kManyCols);
+            else EF21_SMALL(false, kManyPer, kManyCols);
+        }
+#undef EF21_SMALL
         return hipGetLastError();
     }
     int32_t *start = (int32_t *)index;

@@ -759,12 +759,13 @@ def test_aggregation_of_messages_of_rows_in_registers(gpu, n, d, k):
         assert np.array_equal(x, np.float32(-0.5) * g)
 
 
-@pytest.mark.parametrize("n,d,k", [(1, 3072, 2048), (1, 3584, 2048), (2, 1100, 1024), (2, 1100, 1025), (4, 2468, 493), (15, 511, 136),
-                                   (15, 511, 137), (16, 1024, 128), (16, 1024, 129), (3, 10239, 1), (1, 1025, 1025), (512, 300, 4),
+@pytest.mark.parametrize("n,d,k", [(1, 3072, 2048), (1, 3584, 2048), (1, 2500, 2500), (1, 3071, 2432), (2, 1100, 1024), (2, 1100, 1025),
+                                   (4, 2468, 493), (4, 1536, 768), (15, 511, 136), (15, 511, 137), (8, 1024, 1024), (8, 1025, 1024),
+                                   (15, 547, 546), (15, 547, 547), (16, 1024, 128), (16, 1024, 129), (3, 10239, 1), (1, 1025, 1025), (512, 300, 4),
                                    (513, 300, 1)])
 def test_aggregation_of_messages_without_an_index(gpu, n, d, k):
-    """Either side of the one-workgroup aggregation's limits (38 steps and blocks of 512 columns, 2048 pairs, 512 steps) where
-    the Top-k does not write the index: short rows, and messages of more than an eighth of a row."""
+    """Either side of the one-workgroup aggregation's limits (steps and blocks of 512 columns, 2048 and 8192 pairs, 512 steps)
+    where the Top-k does not write the index: short rows, and messages of more than an eighth of a row."""
     test_aggregation_of_messages_of_rows_in_registers(gpu, n, d, k)
 
 
@@ -782,7 +783,7 @@ def line8_sum(n, d, k, idx, val):
     return ((r[0] + r[1]) + r[2]) + r[3]
 
 
-@pytest.mark.parametrize("n,d,k", [(15, 3000, 700), (15, 700, 300), (16, 1024, 128), (16, 1024, 129), (16, 1025, 64), (17, 40, 20), (20, 2000, 20),
+@pytest.mark.parametrize("n,d,k", [(15, 3000, 700), (15, 700, 300), (16, 1024, 128), (16, 1024, 129), (16, 1025, 64), (17, 40, 20), (15, 500, 500), (20, 2000, 20),
                                    (21, 2000, 900), (512, 64, 4), (513, 64, 1), (33, 300, 200), (15, 20000, 900), (18, 20000, 1500),
                                    (30, 16383, 300), (9, 70001, 7000), (25, 70001, 7000)])
 def test_order_of_the_sum_of_messages(gpu, n, d, k):
