@@ -262,7 +262,8 @@ int enqueue_local_grad(ef21_ctx *c, const float *x, float *out, ef21::GradParts 
     if (defer) *defer = ef21::GradParts();
     if (c->kind == kDense)
         st = ef21::launch_logreg_grad_dense(c->A, c->y, x, out, c->n, c->m, c->d, c->lambda, c->scratch, c->stream,
-                                            mk, defer, c->loss, c->batch);
+                                            mk, defer, c->loss, c->batch, 0,
+                                            use_row_reg(c->d, c->k) ? ef21::kRowPartsFewCols : ef21::kRowPartsMax);
     else
         st = ef21::launch_logreg_grad_csr(c->rowptr, c->col, c->val, c->y, x, out, c->n, c->m, c->d, c->nnz,
                                           c->lambda, c->csr_indexed ? c->csr_index : nullptr, c->stream, mk, c->loss,

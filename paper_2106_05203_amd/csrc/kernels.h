@@ -94,13 +94,19 @@ struct TopkArgs {
     float add_scale;
 };
 
-// Rows this long can be handed to launch_topk_row as unreduced gradients (TopkArgs::parts).  Longer ones are finished by a
-// kernel that the whole chip shares, and launch_topk_row_reg selects from the differences.  step, us, unreduced and
-// finished, k = d / 20: d = 700: n = 10, m = 8 16.1 and 16.7, n = 32, m = 500 23.5 and 24.2, n = 10, m = 2000 24.0 and 23.7; d = 900:
-// n = 4, m = 8 15.7 and 16.2, n = 4, m = 500 18.3 and 17.8, n = 10, m = 2000 28.0 and 26.9; d = 1000: 15.8 and 16.4, 18.0 and 17.7, 29.7
-// and 28.3; d = 1200: 17.7 and 17.8, 21.6 and 19.7, 35.0 and 32.4; d = 2000: 21.0 and 18.5, 26.0 and 20.8, 48.5 and 43.7.  Around
-// 900 the few-row problems still gain what the many-row ones lose.
-constexpr int64_t kRowPartsMax = 900;
+// Rows this long can be handed to launch_topk_row as unreduced gradients (TopkArgs::parts).
+constexpr int64_t kRowPartsMax = 4096;
+// Up to this length they are (launch_logreg_grad_dense).  Longer ones are finished by a kernel that the whole chip shares, and
+// launch_topk_row_reg selects from the differences.  step, us, unreduced and finished, k = d / 20: d = 700: n = 10, m = 8 16.1
+// and 16.7, n = 32, m = 500 23.5 and 24.2, n = 10, m = 2000 24.0 and 23.7; d = 900: n = 4, m = 500 18.3 and 17.8, n = 10, m = 2000 28.0
+// and 26.9; d = 1200: 21.6 and 19.7, 35.0 and 32.4; d = 2000: 26.0 and 20.8, 48.5 and 43.7.
+constexpr int64_t kRowPartsCols = 900;
+// With up to kRowPartsFew sums per column, unreduced costs the Top-k kernel next to nothing and saves a launch: up to this length
+// against the selection from registers (m = 8, the same way: n = 4, d = 900 15.7 and 16.2; d = 1000 15.8 and 16.4; n = 10 17.3 and 17.4;
+// n = 4, d = 1200 17.7 and 17.8; d = 1500 19.1 and 18.5), and up to kRowPartsMax where too many entries are kept for that one and
+// both select from LDS (k = d / 5: n = 1, m = 8, d = 950 15.2 and 17.0; n = 4, m = 32, d = 1507 21.5 and 22.7; n = 32, m = 16, d = 2500 26.5
+// and 27.6; n = 1, m = 2, d = 4000 24.6 and 25.0; eight sums: n = 1, m = 64, d = 1507 21.3 and 20.9, d = 2500 26.2 and 24.4).
+constexpr int64_t kRowPartsFew = 4, kRowPartsFewCols = 1200;
 
 // One workgroup per row: a histogram pass over the row and a ranking of the threshold's bin (three histogram passes where
 // the bin is crowded), then an ordered emission.  Needs no workspace; rows of at most 16384 entries.
@@ -168,12 +174,14 @@ struct RowBatch {
 
 // Gradient of eq. (9) for all workers, dense rows.  scratch: logreg_dense_scratch_bytes.  With defer != nullptr
 // the last reduction may be left to the consumer: then *defer describes the partial sums (they live in
-// scratch until the next call) and grad is not written; defer->part == nullptr means grad was written.
+// scratch until the next call) and grad is not written; defer->part == nullptr means grad was written.  few_cols: the most columns
+// of which it leaves a few sums (kRowPartsFewCols or kRowPartsMax).
 size_t logreg_dense_scratch_bytes(int32_t n, int64_t m, int64_t d);
 hipError_t launch_logreg_grad_dense(const float *A, const float *y, const float *x, float *grad, int32_t n,
                                     int64_t m, int64_t d, float lambda, void *scratch, hipStream_t stream,
                                     const Marker &mk = Marker(), GradParts *defer = nullptr,
-                                    int loss = kLossLogistic, RowBatch batch = RowBatch(), int64_t x_stride = 0);
+                                    int loss = kLossLogistic, RowBatch batch = RowBatch(), int64_t x_stride = 0,
+                                    int64_t few_cols = kRowPartsFewCols);
 
 // Gradient of eq. (9) for all workers, CSR rows with nnz entries in all.  `index`
 // (logreg_csr_index_bytes bytes, owned by the caller) is built once per problem by logreg_csr_build_index

@@ -391,7 +391,8 @@ size_t logreg_dense_scratch_bytes(int32_t n, int64_t m, int64_t d) {
 
 hipError_t launch_logreg_grad_dense(const float *A, const float *y, const float *x, float *grad, int32_t n,
                                     int64_t m_full, int64_t d, float lambda, void *scratch, hipStream_t stream,
-                                    const Marker &mk, GradParts *defer, int loss, RowBatch rb, int64_t x_stride) {
+                                    const Marker &mk, GradParts *defer, int loss, RowBatch rb, int64_t x_stride,
+                                    int64_t few_cols) {
     if (defer) *defer = GradParts();
     const int32_t *batch = rb.tau > 0 ? rb.rows : nullptr;
     const int64_t m = batch ? rb.tau : m_full;         // rows summed per worker (tau <= m_full, checked by the caller)
@@ -447,14 +448,15 @@ hipError_t launch_logreg_grad_dense(const float *A, const float *y, const float 
     hipError_t st = hipGetLastError();
     if (st != hipSuccess) return st;
     // The consumer finishes the sums itself (dense_grad_entry) where that is less work for its one workgroup per row than
-    // another kernel of 3 to 5 us: on short rows (kRowPartsMax) with few sums per column, or with more of them 1 us per 40 KB of
+    // another kernel of 3 to 5 us: on short rows (kRowPartsCols, kRowPartsFew) with few sums per column, or with more of them 1 us per 40 KB of
     // sums and per 1000 columns (the regulariser's divisions); many sums per column
     // go better by the threads of the kernel that shares them out.  step, us, with the sums left and finished: n = 2, m = 40000,
     // d = 250 (256 blocks) 31.3 and 27.2; n = 2, m = 50000, d = 300 (256) 34.6 and 31.5; n = 1, m = 200000, d = 80 (512) 26.8 and
     // 25.5.
     constexpr int64_t kColumnWork = 25, kFewBlocks = 32, kPartsWork = 60000, kPartsBlocks = 256;
     const bool little = pl.chunks <= kFewBlocks || (pl.chunks <= kPartsBlocks && (pl.chunks + kColumnWork) * d <= kPartsWork);
-    if (defer && fused && x_stride == 0 && d <= kRowPartsMax && little) {
+    const bool left = d <= kRowPartsCols ? little : pl.chunks <= kRowPartsFew && d <= few_cols && d <= kRowPartsMax;
+    if (defer && fused && x_stride == 0 && left) {
         *defer = GradParts{part, pl.chunks, m, x, lambda};
         return hipSuccess;
     }

@@ -451,7 +451,7 @@ def test_few_workers_fill_the_chip(gpu, n, d, m):
 # iteration from the reported gradient and one that forms its own agree bit for bit (both add the chains in the same order)
 @pytest.mark.parametrize("n,d,m", [(2, 100, 700), (30, 70, 1600), (3, 130, 5000), (1, 65, 9000), (1, 1, 20000), (2, 300, 60000),
                                    (1, 1001, 3000), (12, 3000, 400), (8, 5000, 300), (3, 900, 640), (3, 901, 640), (14, 600, 4000), (1, 224, 40000)])
-def test_partial_sums_of_many_blocks(gpu, n, d, m):
+def test_partial_sums_of_many_blocks(gpu, n, d, m, kept=None):
     torch, binding = gpu
     print(f"partial sums n={n} d={d} m={m}", flush=True)
     g = torch.Generator(device="cuda")
@@ -459,7 +459,7 @@ def test_partial_sums_of_many_blocks(gpu, n, d, m):
     A = torch.randn((n, m, d), device="cuda", generator=g) / d ** 0.5
     y = torch.where(torch.rand((n, m), device="cuda", generator=g) < 0.5, 1.0, -1.0)
     x = 0.3 * torch.randn(d, device="cuda", generator=g)
-    k = max(1, d // 20)
+    k = kept or max(1, d // 20)
     with binding.EF21(n, d, k, 0.3) as own, binding.EF21(n, d, k, 0.3) as given:
         for h in (own, given):
             h.set_problem_dense(A, y, 0.1)
@@ -482,3 +482,11 @@ def test_partial_sums_of_many_blocks(gpu, n, d, m):
                 assert torch.equal(a, b)
             for a, b in zip(own.get_messages(), given.get_messages()):
                 assert torch.equal(a, b)
+
+
+# few rows: up to four sums per column are left to the Top-k kernel up to 1200 columns, and up to 4096 where more than an eighth of
+# the row (or more than 1024 entries) is kept
+@pytest.mark.parametrize("n,d,m,k", [(3, 901, 8, 40), (3, 1200, 32, 150), (3, 1201, 32, 150), (3, 1200, 33, 150), (2, 1200, 3, 151),
+                                     (2, 4096, 32, 513), (2, 4096, 7, 1025), (2, 4097, 7, 1025), (1, 4096, 40, 2000)])
+def test_few_sums_left_to_the_selection(gpu, n, d, m, k):
+    test_partial_sums_of_many_blocks(gpu, n, d, m, k)
