@@ -145,9 +145,10 @@ def bench_dense(torch, binding, workloads, name: str, steps: int, warmup: int):
     out = {"value": round(1e3 / wall, 2), "unit": "EF21 iterations/s", **t.fields(),
            "ms_per_step_events": round(t.ev, 5), "kernel_ms": {k_: round(v, 5) for k_, v in per_kernel.items()},
            "iteration_algorithmic_bytes": 4 * n * m * d + 4 * n * m + 12 * n * d + 24 * n * k + 12 * d}
-    if "grad_main" in per_kernel:
+    if "grad_main" in per_kernel:      # few rows per worker: gradient, selection and update are one kernel
         out["roofline"] = roofline(4.0 * n * m * d + 4.0 * n * m + 4.0 * d, per_kernel["grad_main"],
-                                   "logreg_dense_fused_kernel (grad_main)", measured_traffic(f"{name}/grad_main"))
+                                   ("logreg_dense_fused_kernel" if "topk_row" in per_kernel else "solo_kernel") + " (grad_main)",
+                                   measured_traffic(f"{name}/grad_main"))
     else:                 # (a run that measures the one-launch iteration only)
         out["roofline"] = roofline(out["iteration_algorithmic_bytes"], per_kernel["small_step"],
                                    "small_step_kernel (the whole iteration)", None)

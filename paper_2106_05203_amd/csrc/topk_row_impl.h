@@ -242,8 +242,8 @@ __device__ void row_topk(RowShared &s, const TopkArgs &p, int64_t row) {
 
 // Rows of at most kRowCache entries: the row is formed once into LDS (`cache`), all passes read it there.  From 8193 entries
 // on the copy leaves room for one workgroup per compute unit instead of two, so more than 256 rows are read from L2 in
-// every pass (row_topk).  ef21_topk, us, from L2 and from LDS: 20 rows of 12000, k = 1000 15.9 and 14.7; 100 of 16383 17.6 and
-// 15.7; 300 of 9000 15.7 and 20.7; 1000 of 9000 31.9 and 43.6.
+// every pass (row_topk).  ef21_topk, us, from L2 and from LDS: 20 rows of 12000, k = 2000 17.9 and 16.9; 100 of 16383, k = 3000 22.9 and
+// 18.5; 256 of 16000, k = 4000 26.9 and 20.6; 300 of 16000 32.0 and 36.9; 300 of 9000, k = 1200 20.1 and 26.4; 1000 of 9000 38.4 and 52.0.
 constexpr int kRowCache = 16384, kRowCacheShort = 8192;
 
 template <bool DIFF, int UPDATE>

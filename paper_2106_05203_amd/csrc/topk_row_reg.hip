@@ -7,9 +7,9 @@
 // passes over the registers all work is done on a list of candidates in LDS.
 //
 // Against rows held in LDS as 16-bit prefixes of their keys, of which kept entries and the threshold's bin were read again
-// (us a call): 100 x 50000, k = 500 21.6 -> 12.6; 20 x 20000, k = 200 15.4 -> 7.7; against full rows in LDS: 20 x 12000, k = 1000
-// 14.8 -> 8.7; 600 x 16000, k = 80 49.7 -> 13.7; against many workgroups per row for differences (a step): 100 x 50000, k = 500
-// 40.2 -> 27.5; 2 x 50000 25.4 -> 17.6.  What bounds it: 100 x 50000 takes 11 us in the kernel, of which the loads some 4, the two
+// (us a call, back to back): 100 x 50000, k = 500 19.8 -> 11.9; 20 x 20000, k = 200 15.0 -> 7.5; against full rows in LDS: 20 x 12000,
+// k = 1000 14.9 -> 8.5; 600 x 16000, k = 80 46.2 -> 13.2; against many workgroups per row for differences (a step): 100 x 50000,
+// k = 500 34.6 -> 26.0; 2 x 50000 23.2 -> 18.2.  What bounds it: 100 x 50000 takes 11 us in the kernel, of which the loads some 4, the two
 // passes over the registers 1.5, and the rest a chain of fourteen barriers.
 //
 //   1  Every thread takes the largest magnitude key of each half of its registers: 2048 distinct entries (all entries of

@@ -86,10 +86,10 @@ def test_threshold_inside_a_bin_of_near_equal_magnitudes(gpu, oracle, d, crowd):
 @pytest.mark.parametrize("d", [16384, 20001, 50000, 61440, 61441])
 @pytest.mark.parametrize("k", [1, 37, 1000, 1024, 1025])
 def test_rows_held_in_lds_as_key_prefixes(gpu, oracle, d, k):
-    """Rows of 16 384 to 61 440 entries with k <= 1024 are selected by one workgroup that keeps 16 bits of every key
-    in LDS (the sizes around those limits take the other kernels).  Rows: Gaussian; heavy exact ties (the list
-    of entries above the bound overflows); a crowded bin of near-equal magnitudes with ties (narrowed by four
-    bits, or given up); fewer non-zeros than k (the threshold is zero); infinities and a row of one value."""
+    """Rows of 16 384 to 61 440 entries with k <= 1024 are selected by one workgroup (by its registers; a kernel with 16 bits
+    of every key in LDS before; the sizes around those limits take the other kernels).  Rows: Gaussian; heavy exact ties (the list
+    of entries above the bound overflows); a crowded bin of near-equal magnitudes with ties (a second histogram, or
+    the bisection); fewer non-zeros than k (the threshold is zero); infinities and a row of one value."""
     rng = np.random.default_rng(d + k)
     V = rng.standard_normal((7, d)).astype(np.float32)
     V[1] = np.round(V[1] * 2) / 2
