@@ -160,8 +160,8 @@ int ef21_set_minibatch(ef21_handle h, const int32_t *rows, int64_t tau);
  * (c = 1/4 for the logistic loss, 2 for least squares: the largest curvature of the per-row loss; 2 is the
  * largest curvature of t^2 / (1 + t^2)), and L = c lambda_max((1/(n m)) sum_i A_i^T A_i) + 2 lambda for f itself.
  * The eigenvalues are the estimates that `iterations` steps of the power iteration give on the GPU, started from a fixed
- * positive vector: the estimate |M v| for the
- * unit vector v of the last step approaches lambda_max from below, so few iterations give a stepsize that is
+ * positive vector: the estimate |M v| for the unit vector v of the last step approaches lambda_max from below, so few
+ * iterations give a stepsize that is
  * too large by the same factor: 100 to 300 steps bring problems without a dominant direction within about one
  * per cent.  gamma, L, L_i [n]: host memory, each may be NULL.  Uses the handle's loss, lambda and k, and all
  * rows whatever ef21_set_minibatch says; the handle's stepsize is not changed.  Returns after the stream has drained.
@@ -170,7 +170,8 @@ int ef21_set_minibatch(ef21_handle h, const int32_t *rows, int64_t tau);
  * ceil(4.8 sqrt(iterations)) + 1 steps of the Lanczos recurrence on the same start vector, which give it to fp64 rounding.
  * A call that needs more than the handle has allocates a workspace of
  * 4 (n + 1) d'^2 + 4 n c d' (d' + 32) + 8 (n + 1) (5 d' + 512) bytes (d' = d rounded up to 32, c pieces of a worker's rows, one
- * or as many as make a thousand tiles in all) and some hundred for alignment, never more than 1 GiB, which the handle keeps until ef21_destroy.
+ * or as many as make a thousand tiles in all) and a few hundred for alignment, never more than 1 GiB, which the handle
+ * keeps until ef21_destroy.
  * Where that much is not to be had, and for all other problems, a call iterates with the problem itself, a step two passes
  * of the gradient kernels over it: the first one
  * on a handle allocates (n + 2) d floats that the handle keeps, and every one overwrites the handle's gradient buffer.
