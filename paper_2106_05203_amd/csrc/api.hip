@@ -553,9 +553,43 @@ int ef21_set_minibatch(ef21_handle h, const int32_t *rows, int64_t tau) {
     return EF21_OK;
 }
 
+// A caller's array that the library's own copy kernels can go over: 4-byte aligned memory of this device, all of it inside one
+// allocation.  Anything else (pinned host memory, another device's, an array that is too short) is left to hipMemcpyAsync, which
+// copies it or refuses it.  The two queries take 0.1 us.
+static bool copies_by_kernel(const ef21_ctx *c, const float *p, int64_t count) {
+    if (!p) return true;
+    hipPointerAttribute_t at{};
+    hipDeviceptr_t base = nullptr;
+    size_t bytes = 0;
+    if ((uintptr_t)p % 4 != 0 || hipPointerGetAttributes(&at, p) != hipSuccess || at.type != hipMemoryTypeDevice ||
+        at.device != c->device || hipMemGetAddressRange(&base, &bytes, (hipDeviceptr_t)p) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return (size_t)((const char *)p - (const char *)base) + sizeof(float) * (size_t)count <= bytes;
+}
+
+// hipMemcpyAsync takes a launch for each array, and the mean another that reads the rows again: the set_state and get_state of
+// n = 20, d = 123 10.5 and 13.7 us, in one launch each 5.8 and 9.0 (the three torch.empty of the binding included); n = 8, d =
+// 11.2 million 208 and 171, 172 and 137.
 int ef21_set_state(ef21_handle h, const float *x, const float *g_i, const float *g) {
     if (int rc = check_handle(h)) return rc;
-    const size_t db = sizeof(float) * (size_t)h->d;
+    const int64_t d = h->d, nd = (int64_t)h->n * d;
+    const size_t db = sizeof(float) * (size_t)d;
+    const ef21::CopyList list{{x, g_i, g}, {h->x, h->g_i, h->g}, {x ? d : 0, g_i ? nd : 0, g ? d : 0}};
+    const bool with_mean = g_i && !g;
+    if ((with_mean || ef21::copy_arrays_applies(list)) && copies_by_kernel(h, x, d) && copies_by_kernel(h, g_i, nd) &&
+        copies_by_kernel(h, g, d)) {
+        hipError_t st;
+        if (with_mean) {
+            st = ef21::launch_mean_rows(g_i, h->g, h->n, d, h->stream, h->g_i, x, x ? h->x : nullptr);
+        } else {
+            st = ef21::launch_copy_arrays(list, h->stream);
+            if (st == hipSuccess && !g) st = ef21::launch_mean_rows(h->g_i, h->g, h->n, d, h->stream);
+        }
+        if (st != hipSuccess) return fail_hip(st, "state kernel launch");
+        return EF21_OK;
+    }
     if (x) EF21_HIP(hipMemcpyAsync(h->x, x, db, hipMemcpyDeviceToDevice, h->stream));
     if (g_i) EF21_HIP(hipMemcpyAsync(h->g_i, g_i, db * h->n, hipMemcpyDeviceToDevice, h->stream));
     if (g) {
@@ -569,7 +603,14 @@ int ef21_set_state(ef21_handle h, const float *x, const float *g_i, const float 
 
 int ef21_get_state(ef21_handle h, float *x, float *g_i, float *g) {
     if (int rc = check_handle(h)) return rc;
-    const size_t db = sizeof(float) * (size_t)h->d;
+    const int64_t d = h->d, nd = (int64_t)h->n * d;
+    const size_t db = sizeof(float) * (size_t)d;
+    const ef21::CopyList list{{h->x, h->g_i, h->g}, {x, g_i, g}, {x ? d : 0, g_i ? nd : 0, g ? d : 0}};
+    if (ef21::copy_arrays_applies(list) && copies_by_kernel(h, x, d) && copies_by_kernel(h, g_i, nd) && copies_by_kernel(h, g, d)) {
+        hipError_t st = ef21::launch_copy_arrays(list, h->stream);
+        if (st != hipSuccess) return fail_hip(st, "state kernel launch");
+        return EF21_OK;
+    }
     if (x) EF21_HIP(hipMemcpyAsync(x, h->x, db, hipMemcpyDeviceToDevice, h->stream));
     if (g_i) EF21_HIP(hipMemcpyAsync(g_i, h->g_i, db * h->n, hipMemcpyDeviceToDevice, h->stream));
     if (g) EF21_HIP(hipMemcpyAsync(g, h->g, db, hipMemcpyDeviceToDevice, h->stream));

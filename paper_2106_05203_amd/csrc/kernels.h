@@ -157,8 +157,19 @@ hipError_t launch_aggregate(const int32_t *idx, const float *val, int32_t n, int
                             float gamma, void *index, hipStream_t stream, bool index_ready = false,
                             bool from_zero = false);
 
-// g = (1/n) sum_i g_i (input line of Algorithm 2), summed in worker order.
-hipError_t launch_mean_rows(const float *g_i, float *g, int32_t n, int64_t d, hipStream_t stream);
+// g = (1/n) sum_i g_i (input line of Algorithm 2), summed in worker order; in the same launch, if rows_out != nullptr, rows_out <-
+// g_i and, if x_out != nullptr as well, x_out [d] <- x.
+hipError_t launch_mean_rows(const float *g_i, float *g, int32_t n, int64_t d, hipStream_t stream, float *rows_out = nullptr,
+                            const float *x = nullptr, float *x_out = nullptr);
+
+// dst[a][0 .. count[a]) <- src[a] for up to three arrays (count 0: none) in one launch.
+struct CopyList {
+    const float *src[3];
+    float *dst[3];
+    int64_t count[3];
+};
+bool copy_arrays_applies(const CopyList &c);       // false: hipMemcpyAsync is the faster way
+hipError_t launch_copy_arrays(const CopyList &c, hipStream_t stream);
 
 // `loss` below: the per-row loss of the linear model (LossKind in device_utils.h): logistic (eq. (9)) or squared.
 // kLossHalfSquare (z^2 / 2, no target) is internal: its gradient is (1/m) A_i^T A_i x, the product the power

@@ -1,5 +1,8 @@
 // Vector kernels of Algorithm 2: the model step (line 3), the master's aggregation of the messages
 // (line 8), and the mean of the workers' estimators (input line, g^0 = (1/n) sum_i g_i^0).
+#include <algorithm>
+#include <type_traits>
+
 #include "device_utils.h"
 #include "kernels.h"
 
@@ -7,6 +10,17 @@ namespace ef21 {
 namespace {
 
 constexpr int kThreads = 256;
+// A column per thread up to this length of a row, beyond it four.  The mean with a copy of the rows, us, one and four: 20 x 123
+// 5.8 and 9.1; 100 x 2000 8.0 and 12.5; 100 x 50000 11.1 and 29.2; 8 x 65536 5.7 and 5.6; 8 x 200000 6.7 and 5.6, and without the
+// copy 5.6 and 4.3; 8 x 1000003 17.7 and 17.3, without 13.6 and 5.7.
+constexpr int64_t kMeanFewCols = 65536;
+// Arrays of this many entries in all and more are copied past the caches, a block per 2048 entries; shorter ones through them, by
+// one block per compute unit, and one short array alone is left to hipMemcpyAsync (copy_arrays_applies).  A step and the copy of x,
+// us, by hipMemcpyAsync, through the caches and past them: n = 8, d = 10^6 38.3, 39.0 and 39.8; n = 4, d = 6 million 82.8, 83.4 and
+// 86.3; d = 9 million 113.2, 114.5 and 114.0; n = 8, d = 11.2 million 229.5, 230.0 and 225.0; EF21+ on n = 5, d = 11.5 million 287,
+// 282 and 270.
+constexpr int kCopyThreads = 512, kCopyBlocks = 256;
+constexpr int64_t kCopyStream = (int64_t)10 << 20;
 
 // x_j <- x_j - gamma g_j as one fused multiply-add per coordinate (a single rounding).
 __global__ __launch_bounds__(kThreads) void model_step_kernel(float *__restrict__ x, const float *__restrict__ g,
@@ -32,42 +46,88 @@ __global__ __launch_bounds__(kThreads) void model_step_vec4_kernel(float4 *__res
     }
 }
 
+// The rows' mean, and on the way a copy of the rows (rows_out) and of one more vector (x_out <- x) for ef21_set_state, which
+// took a launch each and read the rows twice.  Per coordinate the workers in order, in fp64, rounded once.  Eight workers' loads
+// in flight where a thread has four columns, 32 where it has one: short rows have few threads, and there the waits for memory
+// are all there is (20 x 123, the three things in 4 launches 9.4 us, in this one 3.3).  Rows may start at any 4-byte address.
+struct RowsOut {
+    float *rows;                 // nullptr: the mean alone
+    const float *x;              // with x_out, or nullptr
+    float *x_out;
+};
+template <int VEC, bool COPY>
 __global__ __launch_bounds__(kThreads) void mean_rows_kernel(const float *__restrict__ g_i, float *__restrict__ g,
-                                                             int32_t n, int64_t d) {
-    const int64_t stride = (int64_t)gridDim.x * kThreads;
-    for (int64_t j = (int64_t)blockIdx.x * kThreads + threadIdx.x; j < d; j += stride) {
-        double s = 0.0;
-        for (int32_t i = 0; i < n; ++i) s += (double)g_i[(int64_t)i * d + j];
-        g[j] = (float)(s / (double)n);
-    }
-}
-
-// Same sums (per coordinate, the workers in order, in fp64), four coordinates per thread and eight workers'
-// loads in flight; needs d % 4 == 0 and 16-byte aligned pointers.
-__global__ __launch_bounds__(kThreads) void mean_rows_vec4_kernel(const float *__restrict__ g_i,
-                                                                  float *__restrict__ g, int32_t n, int64_t d) {
-    const int64_t stride = (int64_t)gridDim.x * kThreads * 4;
-    constexpr int kInFlight = 8;
-    for (int64_t j = ((int64_t)blockIdx.x * kThreads + threadIdx.x) * 4; j < d; j += stride) {
-        double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
+                                                             int32_t n, int64_t d, RowsOut out) {
+    const int64_t stride = (int64_t)gridDim.x * kThreads * VEC;
+    constexpr int kInFlight = VEC == 4 ? 8 : 32;
+    auto columns = [&](auto width, int64_t j) {
+        constexpr int W = decltype(width)::value;
+        double s[W] = {};
         for (int32_t i0 = 0; i0 < n; i0 += kInFlight) {
-            float4 v[kInFlight];
+            float v[kInFlight][W];
 #pragma unroll
-            for (int u = 0; u < kInFlight; ++u)        // a worker past the end re-reads the last one, unused
-                v[u] = stream_load4(g_i + (int64_t)(i0 + u < n ? i0 + u : n - 1) * d + j);
+            for (int u = 0; u < kInFlight; ++u) {      // a worker past the end re-reads the last one, unused
+                const float *at = g_i + (int64_t)(i0 + u < n ? i0 + u : n - 1) * d + j;
+                if constexpr (W == 4) {
+                    const float4 t = stream_load4_any(at);
+                    v[u][0] = t.x, v[u][1] = t.y, v[u][2] = t.z, v[u][3] = t.w;
+                } else {
+                    v[u][0] = *at;
+                }
+            }
 #pragma unroll
             for (int u = 0; u < kInFlight; ++u) {
                 if (i0 + u < n) {
-                    s0 += (double)v[u].x;
-                    s1 += (double)v[u].y;
-                    s2 += (double)v[u].z;
-                    s3 += (double)v[u].w;
+#pragma unroll
+                    for (int t = 0; t < W; ++t) s[t] += (double)v[u][t];
+                    if constexpr (COPY) {
+                        float *to = out.rows + (int64_t)(i0 + u) * d + j;
+                        if constexpr (W == 4) store4_any(to, make_float4(v[u][0], v[u][1], v[u][2], v[u][3]));
+                        else *to = v[u][0];
+                    }
                 }
             }
         }
-        const double nn = (double)n;
-        *reinterpret_cast<float4 *>(g + j) =
-            make_float4((float)(s0 / nn), (float)(s1 / nn), (float)(s2 / nn), (float)(s3 / nn));
+#pragma unroll
+        for (int t = 0; t < W; ++t) {
+            g[j + t] = (float)(s[t] / (double)n);
+            if (COPY && out.x_out) out.x_out[j + t] = out.x[j + t];
+        }
+    };
+    for (int64_t j = ((int64_t)blockIdx.x * kThreads + threadIdx.x) * VEC; j < d; j += stride) {
+        if (j + VEC <= d) columns(std::integral_constant<int, VEC>(), j);
+        else
+            for (int64_t c = j; c < d; ++c) columns(std::integral_constant<int, 1>(), c);
+    }
+}
+
+// Up to three arrays copied by one launch, 16 bytes a thread and access, at any 4-byte address.  STREAM: past the caches.
+template <bool STREAM>
+__global__ __launch_bounds__(kCopyThreads) void copy_arrays_kernel(CopyList c) {
+    constexpr int kInFlight = 4;
+    const int64_t stride = (int64_t)gridDim.x * kCopyThreads * 4;
+    auto load = [](const float *p) { return STREAM ? stream_load4_any(p) : load4_any(p); };
+    auto store = [](float *p, const float4 &v) {
+        if constexpr (STREAM) stream_store4_any(p, v);
+        else store4_any(p, v);
+    };
+    for (int a = 0; a < 3; ++a) {
+        const float *src = c.src[a];
+        float *dst = c.dst[a];
+        const int64_t count = c.count[a];
+        int64_t e = ((int64_t)blockIdx.x * kCopyThreads + threadIdx.x) * 4;
+        for (; e + (kInFlight - 1) * stride + 4 <= count; e += kInFlight * stride) {
+            float4 v[kInFlight];
+#pragma unroll
+            for (int u = 0; u < kInFlight; ++u) v[u] = load(src + e + u * stride);
+#pragma unroll
+            for (int u = 0; u < kInFlight; ++u) store(dst + e + u * stride, v[u]);
+        }
+        for (; e < count; e += stride) {
+            if (e + 4 <= count) store(dst + e, load(src + e));
+            else
+                for (int64_t t = e; t < count; ++t) dst[t] = src[t];
+        }
     }
 }
 
@@ -534,11 +594,36 @@ hipError_t launch_hbm_copy(void *dst, const void *src, int64_t n16, hipStream_t 
     return hipGetLastError();
 }
 
-hipError_t launch_mean_rows(const float *g_i, float *g, int32_t n, int64_t d, hipStream_t stream) {
-    if ((d % 4 == 0) && (((uintptr_t)g_i | (uintptr_t)g) % 16 == 0))
-        hipLaunchKernelGGL(mean_rows_vec4_kernel, dim3(grid_for(d / 4, 8192)), dim3(kThreads), 0, stream, g_i, g, n, d);
-    else
-        hipLaunchKernelGGL(mean_rows_kernel, dim3(grid_for(d, 8192)), dim3(kThreads), 0, stream, g_i, g, n, d);
+hipError_t launch_mean_rows(const float *g_i, float *g, int32_t n, int64_t d, hipStream_t stream, float *rows_out,
+                            const float *x, float *x_out) {
+    const RowsOut out{rows_out, x, x_out};
+    // a column per thread as long as that leaves compute units idle
+#define EF21_MEAN(VEC, COPY)                                                                                            \
+    hipLaunchKernelGGL((mean_rows_kernel<VEC, COPY>), dim3(grid_for((d + VEC - 1) / VEC, 8192)), dim3(kThreads), 0, stream, \
+                       g_i, g, n, d, out)
+    const bool few = d <= kMeanFewCols;
+    if (rows_out && few) EF21_MEAN(1, true);
+    else if (rows_out) EF21_MEAN(4, true);
+    else if (few) EF21_MEAN(1, false);
+    else EF21_MEAN(4, false);
+#undef EF21_MEAN
+    return hipGetLastError();
+}
+
+bool copy_arrays_applies(const CopyList &c) {
+    const int64_t entries = c.count[0] + c.count[1] + c.count[2];
+    const bool one = entries == std::max(c.count[0], std::max(c.count[1], c.count[2]));
+    return !one || entries >= kCopyStream;
+}
+
+hipError_t launch_copy_arrays(const CopyList &c, hipStream_t stream) {
+    const int64_t entries = c.count[0] + c.count[1] + c.count[2], per = kCopyThreads * 4;
+    if (entries == 0) return hipSuccess;
+    const int64_t blocks = (entries + per - 1) / per;
+    const bool streamed = entries >= kCopyStream;
+    const dim3 grid((unsigned)std::min<int64_t>(blocks, streamed ? 1 << 20 : kCopyBlocks)), block(kCopyThreads);
+    if (streamed) hipLaunchKernelGGL(copy_arrays_kernel<true>, grid, block, 0, stream, c);
+    else hipLaunchKernelGGL(copy_arrays_kernel<false>, grid, block, 0, stream, c);
     return hipGetLastError();
 }
 

@@ -800,3 +800,45 @@ def test_order_of_the_sum_of_messages(gpu, n, d, k):
             idx, val = (t.cpu().numpy() for t in h.get_messages())
             g = h.get_state()[2].cpu().numpy()
         assert np.array_equal(g, line8_sum(n, d, k, idx, val) * (np.float32(1) / np.float32(n))), (n, d, k, flags)
+
+
+@pytest.mark.parametrize("n,d,offset", [(1, 1, 0), (4, 3, 1), (3, 1023, 0), (33, 1025, 3), (65, 257, 2), (2, 4096, 0), (7, 65537, 1),
+                                        (151, 70001, 0), (151, 70001, 1), (9, 65536, 1)])
+def test_state_in_and_out(gpu, n, d, offset):
+    """set_state and get_state move every entry, from and to any 4-byte address, on both sides of the lengths from which the mean's
+    threads have four columns and the copies go past the caches; g is the fp64 mean in worker order, rounded once."""
+    torch, binding = gpu
+    rng = np.random.default_rng(n + d)
+    sizes = {"x": d, "g_i": n * d, "g": d}
+    host = {key: rng.standard_normal(size).astype(np.float32) for key, size in sizes.items()}
+
+    def at(values):                                     # starts `offset` entries into its storage
+        buf = torch.zeros(values.size + offset + 4, device="cuda")
+        buf[offset:offset + values.size] = torch.from_numpy(values).cuda()
+        return buf[offset:offset + values.size]
+    dev = {key: at(values) for key, values in host.items()}
+    mean = np.zeros(d)
+    for row in host["g_i"].reshape(n, d):
+        mean += row
+    mean = (mean / n).astype(np.float32)
+    with binding.EF21(n, d, 1, 0.5) as h:
+        def check(**expected):
+            lib = binding.load_library()
+            out = {key: at(np.full(size, np.float32(7.0))) for key, size in sizes.items()}
+            binding._check(lib.ef21_get_state(h._h, *(out[key].data_ptr() for key in ("x", "g_i", "g"))))
+            for (key, got), plain in zip(out.items(), h.get_state()):
+                assert same_bits(got.cpu().numpy(), expected[key]), key
+                assert same_bits(plain.cpu().numpy().reshape(-1), expected[key]), key
+                assert got._base is None or got._base[offset + got.numel():].eq(0).all(), f"{key}: written past the end"
+            assert same_bits(h.get_x().cpu().numpy(), expected["x"])
+        g_i = dev["g_i"].view(n, d)
+        h.set_state(x=dev["x"], g_i=g_i)                # g: the mean
+        check(x=host["x"], g_i=host["g_i"], g=mean)
+        h.set_state(g_i=g_i * 2, g=dev["g"])            # x stays
+        check(x=host["x"], g_i=host["g_i"] * 2, g=host["g"])
+        h.set_state(x=dev["x"] + 1)                     # the mean of the rows that are there
+        check(x=host["x"] + 1, g_i=host["g_i"] * 2, g=mean * 2)
+        pinned = torch.from_numpy(host["x"]).pin_memory()
+        binding._check(binding.load_library().ef21_set_state(h._h, pinned.data_ptr(), g_i.data_ptr(), None))
+        check(x=host["x"], g_i=host["g_i"], g=mean)     # an array that is not in this device's memory
+        torch.cuda.synchronize()
