@@ -166,11 +166,13 @@ int ef21_set_minibatch(ef21_handle h, const int32_t *rows, int64_t tau);
  * per cent.  gamma, L, L_i [n]: host memory, each may be NULL.  Uses the handle's loss, lambda and k, and all
  * rows whatever ef21_set_minibatch says; the handle's stepsize is not changed.  Returns after the stream has drained.
  * A dense problem with d <= 1024 columns is iterated on the workers' Gram matrices where that is the faster way (it is from
- * some ten iterations on, usually); 48 to 2822 iterations are then not run one by one, but their estimate is taken from
- * ceil(4.8 sqrt(iterations)) + 1 steps of the Lanczos recurrence on the same start vector, which give it to fp64 rounding.
+ * some ten iterations on, usually); many iterations are then not run one by one, but their estimate is taken, to fp64 rounding,
+ * from powers of the matrices by repeated squaring, or (48 to 2822 iterations) from
+ * ceil(4.8 sqrt(iterations)) + 1 steps of the Lanczos recurrence on the same start vector, whichever is estimated to be faster.
  * A call that needs more than the handle has allocates a workspace of
  * 4 (n + 1) d'^2 + 4 n c d' (d' + 32) + 8 (n + 1) (5 d' + 512) bytes (d' = d rounded up to 32, c pieces of a worker's rows, one
- * or as many as make a thousand tiles in all) and a few hundred for alignment, never more than 1 GiB, which the handle
+ * or as many as make a thousand tiles in all; by squaring 24 (n + 1) d'^2, or 16 (n + 1) d'^2 + 4 n c d' (d' + 32) where that is more,
+ * and 16 (n + 1) (d' + 96)) and some ten thousand for alignment, never more than 1 GiB, which the handle
  * keeps until ef21_destroy.
  * Where that much is not to be had, and for all other problems, a call iterates with the problem itself, a step two passes
  * of the gradient kernels over it: the first one

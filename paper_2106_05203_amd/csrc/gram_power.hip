@@ -20,6 +20,11 @@
 //   The T iterations are then taken with the tridiagonal matrix, by one wavefront.  n = 20, m = 2487, d = 300, 100
 //   iterations: 436 -> 319 us a call;
 //   n = 2, m = 7500, d = 1000: 1255 -> 800.
+//   Where that is the faster way the start vector is taken to y = G^(T-1) v by squarings instead, G^2, G^4, .., G^(2^s) in fp64 (gram_square;
+//   two products a step have to wait for each other, the 21 x 300^3 of a square have the whole chip), and applications of those powers,
+//   and the estimate is |G y| / |y|.  A relative error e of a power becomes 2 e in its square, some 2^s of a rounding in all, in y alone: the
+//   last product is taken with G itself.  n = 20, m = 2487, d = 300: 317 -> 289 us a call of 100 iterations, 660 -> 363 of 1000; 32, 1400, 330
+//   563 -> 373; 3, 2000, 700 528 -> 325; 2, 7500, 1000 796 -> 656.
 //   d <= 320:     ONE launch runs all iterations, a workgroup of 1024 threads per matrix.  G sits in registers (a
 //                 compute unit has 512 KB of them: 100 entries per thread at d = 320), the vector in LDS; a wavefront
 //                 multiplies its rows of G (columns, by symmetry) and the sixteen partial vectors are added in LDS.
@@ -27,6 +32,7 @@
 //                 and multiplies 32 rows of G.
 // Vectors, products with G, sums and norms are in fp64; G is the only thing rounded to fp32, so the constants are
 // closer to the exact ones than through fp32 products with A.
+#include <algorithm>
 #include <cmath>
 #include <utility>
 
@@ -190,12 +196,15 @@ __global__ __launch_bounds__(kTileThreads) void gram_tile_kernel(const float *__
         out[e] = ((red[0][e] + red[1][e]) + red[2][e]) + red[3][e];
 }
 
-// Matrix `which` of n + 1 (the last one: the mean over the workers): the partial sums in order, scaled, rounded once.
+// Matrix `which` of n + 1 (the last one: the mean over the workers): the partial sums in order, scaled, rounded to fp32 once.
+// Where the entries are kept in fp64 the tiles on the diagonal leave their sum of diagonal entries in traces[matrix][tile].
+constexpr int kTraces = kWave;
+template <class T>
 __global__ __launch_bounds__(kTileThreads) void gram_finish_kernel(const double *__restrict__ part, int64_t chunks,
                                                                    int64_t pairs, int64_t d, int64_t ld, double m,
-                                                                   float *__restrict__ G) {
+                                                                   T *__restrict__ G, double *__restrict__ traces) {
     constexpr int kPer = kTileEntries / kTileThreads, kInFlight = 4;
-    __shared__ float tile[kTile][kTile + 1];
+    __shared__ T tile[kTile][kTile + 1];
     const int64_t pair = blockIdx.x, which = blockIdx.y, n = gridDim.y - 1;
     const bool mean = which == n;
     const int64_t count = mean ? n * chunks : chunks;
@@ -217,16 +226,24 @@ __global__ __launch_bounds__(kTileThreads) void gram_finish_kernel(const double 
     const double scale = mean ? m * (double)n : m;
     int32_t I, J;
     tile_of((int32_t)pair, &I, &J);
-    float *out = G + which * ld * ld;
+    T *out = G + which * ld * ld;
 #pragma unroll
     for (int q = 0; q < kPer; ++q) {
         const int e = threadIdx.x + q * kTileThreads, r = e / kTile, c = e % kTile;
         const float g = I * kTile + r < d && J * kTile + c < d ? (float)(s[q] / scale) : 0.f;
-        tile[r][c] = g;
-        out[((int64_t)I * kTile + r) * ld + (int64_t)J * kTile + c] = g;
+        tile[r][c] = (T)g;
+        out[((int64_t)I * kTile + r) * ld + (int64_t)J * kTile + c] = (T)g;
     }
-    if (I == J) return;                              // symmetric by itself (the products commute)
+    if (I == J && sizeof(T) == 4) return;            // symmetric by itself (the products commute)
     __syncthreads();
+    if (I == J) {
+        if (threadIdx.x == 0) {
+            double sum = 0.0;
+            for (int i = 0; i < kTile; ++i) sum += (double)tile[i][i];
+            traces[which * kTraces + I] = sum;
+        }
+        return;
+    }
 #pragma unroll
     for (int q = 0; q < kPer; ++q) {
         const int e = threadIdx.x + q * kTileThreads, r = e / kTile, c = e % kTile;
@@ -588,26 +605,282 @@ __global__ __launch_bounds__(kWave) void gram_tridiagonal_kernel(const double *_
     if (lane == 0) stats[which] = make_double2(0.0, ldexp(value, exponent));
 }
 
+// ---- powers of G by squaring
+// M, in fp64 and symmetric, [n + 1][ld][ld], stands for its multiple with a trace in [1/2, 1): every kernel that reads it
+// multiplies by that power of two, which is exact.  Its trace is the sum of the first `parts` entries of traces[matrix].
+struct Power {
+    const double *M, *traces;
+    int32_t parts;
+};
+// 2^-e, the trace being in [2^(e-1), 2^e); the same in all lanes
+__device__ __forceinline__ double unit_scale(double part_of_trace) {
+    const double trace = wave_sum_f64(part_of_trace);
+    int exponent = 0;
+    if (trace > 0.0 && trace < 1e300) (void)frexp(trace, &exponent);
+    return ldexp(1.0, -exponent);
+}
+__device__ __forceinline__ double trace_part(const Power &a, int64_t which) {
+    return lane_id() < a.parts ? a.traces[which * kTraces + lane_id()] : 0.0;
+}
+
+// z = M y for rows [r0, r0 + 32) of matrix `which`, of whose columns `cols` are used (the squares leave those beyond unwritten);
+// y == nullptr: the start vector.  vec: LDS.  A wavefront's eight rows, TOGETHER of them in flight, PAIRS x 128 columns at most.
+template <int PAIRS, int TOGETHER>
+__device__ __forceinline__ void power_rows(const Power &a, int64_t which, int64_t r0, int64_t d, int64_t cols, int64_t ld,
+                                           const double *__restrict__ y, double *__restrict__ z, double *vec) {
+    const int tid = threadIdx.x, wave = tid / kWave, lane = lane_id();
+    const double part = trace_part(a, which);
+    const double *g = a.M + (which * ld + r0 + wave * kMvRowsPerWave) * ld;
+    double2 m[TOGETHER][PAIRS];
+    auto load = [&](int i0) {
+#pragma unroll
+        for (int i = 0; i < TOGETHER; ++i)
+#pragma unroll
+            for (int q = 0; q < PAIRS; ++q) {
+                const int64_t c = 2 * (lane + q * kWave);
+                m[i][q] = c < cols ? *reinterpret_cast<const double2 *>(g + (i0 + i) * ld + c) : make_double2(0.0, 0.0);
+            }
+    };
+    load(0);
+    for (int64_t j = tid; j < PAIRS * 2 * kWave; j += kMvThreads)
+        vec[j] = j >= cols ? 0.0 : y ? y[which * ld + j] : j < d ? (double)power_start_entry(which, j, rsqrtf((float)d)) : 0.0;
+    __syncthreads();
+    const double scale = unit_scale(part);
+#pragma unroll
+    for (int i0 = 0; i0 < kMvRowsPerWave; i0 += TOGETHER) {
+        if (i0 > 0) load(i0);
+#pragma unroll
+        for (int i = 0; i < TOGETHER; ++i) {
+            double s = 0.0;
+#pragma unroll
+            for (int q = 0; q < PAIRS; ++q) {
+                const int c = 2 * (lane + q * kWave);
+                s = fma(m[i][q].x, vec[c], fma(m[i][q].y, vec[c + 1], s));
+            }
+            s = wave_sum_f64(s);
+            const int64_t row = r0 + wave * kMvRowsPerWave + i0 + i;
+            if (lane == 0) z[which * ld + row] = row < cols ? s * scale : 0.0;
+        }
+    }
+}
+__device__ __forceinline__ void power_rows(const Power &a, int64_t which, int64_t r0, int64_t d, int64_t cols, int64_t ld,
+                                           const double *__restrict__ y, double *__restrict__ z, double *vec) {
+    if (cols <= 2 * kWave) power_rows<1, 8>(a, which, r0, d, cols, ld, y, z, vec);
+    else if (cols <= 6 * kWave) power_rows<3, 8>(a, which, r0, d, cols, ld, y, z, vec);
+    else power_rows<8, 4>(a, which, r0, d, cols, ld, y, z, vec);
+}
+
+// A square in blocks of 16 x 16 on and above the diagonal, which go in strips: the groups of columns 2 p and 2 p + 1 against four groups
+// from 2 p + 4 q on (fewer at the end; the block below the diagonal in the first strip of a row is left out).
+constexpr int kGroup = 16, kBlock = kGroup * kGroup, kWide = 4, kTurns = 4;
+static_assert(kBlock == kTileThreads, "an entry per thread");
+int64_t strip_count(int64_t groups) {
+    int64_t strips = 0;
+    for (int64_t p = 0; 2 * p < groups; ++p) strips += (groups - 2 * p + kWide - 1) / kWide;
+    return strips;
+}
+
+// v_mfma_f64_4x4x4 forms four 4 x 4 products side by side: lane l gives row l / 16 of four and column l % 16 of a
+// group, and quad b of the columns of the one operand meets quad b of the other.  So the one is also taken turned by one, two and three
+// quads, and sum r of lane l is entry (4 ((l / 4 + r) % 4) + l % 4, 4 (l / 4 % 4) + l / 16) of the 16 x 16 product.  v_mfma_f64_16x16x4
+// needs no turns, but takes 100 to 140 clocks for the work of four of these at 16: 45 TFLOP/s on the whole chip against 73.
+// Vector instructions and these do not overlap, so what is turned serves four groups: with two 58 TFLOP/s are left, with four 67.
+template <int CTRL>
+__device__ __forceinline__ double turned(double x) {
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, 0xf, 0xf, true);
+    return __hiloint2double(hi, lo);
+}
+
+// The strip whose first columns are ci and cj of M^T M, M [rows][ld] with rows a multiple of 16, by a workgroup, its four wavefronts four
+// rows each of every sixteen: put(i, j, row, column, sum) for the entries of its blocks.  red: LDS.
+template <int HIGH, int WIDE, bool DIAGONAL, class Put>
+__device__ __forceinline__ void square_strip(const double *__restrict__ M, int32_t rows, int64_t ld, int32_t ci, int32_t cj,
+                                             double (*red)[kWide][kBlock], Put put) {
+    constexpr int kInFlight = 2;                     // steps per buffer
+    const int wave = threadIdx.x / kWave, lane = lane_id();
+    const int64_t step = (int64_t)kTileWaves * kStepRows * ld;
+    const double *from_i = M + (wave * kStepRows + lane / 16) * ld + ci + (lane & 15), *from_j = from_i + (cj - ci);
+    double e[HIGH][WIDE][kTurns] = {};
+    struct Step {
+        double i[HIGH], j[WIDE];
+    };
+    auto load = [&](int32_t at, Step &v) {
+#pragma unroll
+        for (int t = 0; t < HIGH; ++t) v.i[t] = from_i[at * step + t * kGroup];
+#pragma unroll
+        for (int t = 0; t < WIDE; ++t) v.j[t] = from_j[at * step + t * kGroup];
+    };
+    auto multiply = [&](const Step &v) {
+#pragma unroll
+        for (int i = 0; i < HIGH; ++i) {
+            const double a[kTurns] = {v.i[i], turned<0x12c>(v.i[i]), turned<0x128>(v.i[i]), turned<0x124>(v.i[i])};   // row_ror by 12, 8, 4
+#pragma unroll
+            for (int r = 0; r < kTurns; ++r)
+#pragma unroll
+                for (int j = DIAGONAL ? i : 0; j < WIDE; ++j) e[i][j][r] = __builtin_amdgcn_mfma_f64_4x4x4f64(v.j[j], a[r], e[i][j][r], 0, 0, 0);
+        }
+    };
+    // two buffers in turn: the one's loads are in flight while the other is multiplied; a step past the end loads the last one
+    const int32_t steps = rows / (kTileWaves * kStepRows), last = steps - 1;
+    Step v[kInFlight], w[kInFlight];
+#pragma unroll
+    for (int u = 0; u < kInFlight; ++u) load(u < last ? u : last, v[u]);
+    for (int32_t at = 0; at < steps; at += 2 * kInFlight) {
+#pragma unroll
+        for (int u = 0; u < kInFlight; ++u) load(at + kInFlight + u < last ? at + kInFlight + u : last, w[u]);
+#pragma unroll
+        for (int u = 0; u < kInFlight; ++u)
+            if (at + u < steps) multiply(v[u]);
+#pragma unroll
+        for (int u = 0; u < kInFlight; ++u) load(at + 2 * kInFlight + u < last ? at + 2 * kInFlight + u : last, v[u]);
+#pragma unroll
+        for (int u = 0; u < kInFlight; ++u)
+            if (at + kInFlight + u < steps) multiply(w[u]);
+    }
+    const int t = threadIdx.x, quad = (lane >> 2) & 3, row = 4 * ((quad + wave) & 3) + (lane & 3), col = 4 * quad + (lane >> 4);
+#pragma unroll
+    for (int i = 0; i < HIGH; ++i) {
+        const int j0 = DIAGONAL ? i : 0;
+        if (i > 0) __syncthreads();                  // what was there before has been read
+#pragma unroll
+        for (int j = j0; j < WIDE; ++j)
+#pragma unroll
+            for (int r = 0; r < kTurns; ++r) red[wave][j][r * kWave + lane] = e[i][j][r];
+        __syncthreads();
+        for (int j = j0; j < WIDE; ++j)              // this wavefront's entries are those of turn `wave`
+            put(i, j, row, col, ((red[0][j][t] + red[1][j][t]) + red[2][j][t]) + red[3][j][t]);
+    }
+}
+static_assert(kTurns == kTileWaves, "see square_strip");
+
+// to = M M (both scaled as above; to's traces in an entry per row of strips), a workgroup per strip, consecutive ones
+// on one XCD; and, by the workgroups beyond, z = M y where z is given: M stands for G^(2^j), and the exponent asked for has that bit.
+// Bound by the matrix cores, three workgroups to a compute unit, and by there being two or three of them: 21 matrices of d = 300 are
+// 630 strips for 256 units, 24.5 us where the products take 11.
+__global__ __launch_bounds__(kTileThreads, 3) void gram_square_kernel(Power a, int64_t d, int64_t ld, int32_t groups, int32_t strips,
+                                                                      int32_t matrices, double *__restrict__ to,
+                                                                      double *__restrict__ to_traces, const double *__restrict__ y,
+                                                                      double *__restrict__ z) {
+    __shared__ double red[kTileWaves][kWide][kBlock];
+    const int32_t cols = groups * kGroup, units = matrices * strips, per = (units + (int32_t)kXcds - 1) / (int32_t)kXcds;
+    if ((int32_t)blockIdx.x >= per * (int32_t)kXcds) {               // rows of M y
+        const int32_t at = (int32_t)blockIdx.x - per * (int32_t)kXcds, blocks = (int32_t)ld / kMvRows;
+        power_rows(a, at / blocks, at % blocks * kMvRows, d, cols, ld, y, z, &red[0][0][0]);
+        return;
+    }
+    const int32_t unit = (int32_t)blockIdx.x % (int32_t)kXcds * per + (int32_t)blockIdx.x / (int32_t)kXcds;
+    if (unit >= units) return;
+    const int32_t which = unit / strips;
+    const double part = trace_part(a, which);
+    int32_t p = 0, q = unit % strips;
+    for (int32_t here; q >= (here = (groups - 2 * p + kWide - 1) / kWide); ++p) q -= here;
+    double *out = to + which * ld * ld, diagonal = 0.0, scale = 0.0;
+    auto put = [&](int i, int j, int r, int c, double sum) {
+        if (scale == 0.0) {
+            scale = unit_scale(part);
+            scale *= scale;
+        }
+        const int32_t gi = 2 * p + i, gj = 2 * p + kWide * q + j;
+        const int64_t row = gi * kGroup + r, col = gj * kGroup + c;
+        sum *= scale;
+        out[row * ld + col] = sum;
+        if (gi != gj) out[col * ld + row] = sum;
+        else if (r == c) diagonal += sum;
+    };
+    const double *M = a.M + which * ld * ld;
+    const int32_t ci = 2 * p * kGroup, cj = ci + kWide * q * kGroup, left = groups - 2 * p - kWide * q;
+    if (q == 0) {
+        if (left == 1) square_strip<1, 1, true>(M, cols, ld, ci, cj, red, put);
+        else if (left == 2) square_strip<2, 2, true>(M, cols, ld, ci, cj, red, put);
+        else if (left == 3) square_strip<2, 3, true>(M, cols, ld, ci, cj, red, put);
+        else square_strip<2, 4, true>(M, cols, ld, ci, cj, red, put);
+    } else {
+        if (left == 1) square_strip<2, 1, false>(M, cols, ld, ci, cj, red, put);
+        else if (left == 2) square_strip<2, 2, false>(M, cols, ld, ci, cj, red, put);
+        else if (left == 3) square_strip<2, 3, false>(M, cols, ld, ci, cj, red, put);
+        else square_strip<2, 4, false>(M, cols, ld, ci, cj, red, put);
+    }
+    if (q > 0) return;
+    diagonal = wave_sum_f64(diagonal);
+    __syncthreads();
+    if (lane_id() == 0) red[0][0][threadIdx.x / kWave] = diagonal;
+    __syncthreads();
+    if (threadIdx.x == 0) to_traces[which * kTraces + p] = (red[0][0][0] + red[0][0][1]) + (red[0][0][2] + red[0][0][3]);
+}
+
+__global__ __launch_bounds__(kMvThreads) void gram_apply_kernel(Power a, int64_t d, int64_t cols, int64_t ld, const double *__restrict__ y,
+                                                                double *__restrict__ z) {
+    __shared__ double vec[kGramMax];
+    power_rows(a, blockIdx.y, (int64_t)blockIdx.x * kMvRows, d, cols, ld, y, z, vec);
+}
+
+// stats[row] = (0, |z| / |y|), z the product of y and G scaled as above.
+__global__ __launch_bounds__(kMvThreads) void gram_ratio_kernel(Power a, const double *__restrict__ y, const double *__restrict__ z,
+                                                                int64_t ld, double2 *__restrict__ stats) {
+    __shared__ double sums[2][kMvWaves];
+    constexpr int kPer = (int)kGramMax / kMvThreads;
+    const int64_t which = blockIdx.x;
+    const double part = trace_part(a, which);
+    double vy[kPer], vz[kPer], sy = 0.0, sz = 0.0;
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+        const int64_t j = threadIdx.x + q * kMvThreads;
+        vy[q] = j < ld ? y[which * ld + j] : 0.0;
+        vz[q] = j < ld ? z[which * ld + j] : 0.0;
+    }
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+        sy += vy[q] * vy[q];
+        sz += vz[q] * vz[q];
+    }
+    sy = wave_sum_f64(sy);
+    sz = wave_sum_f64(sz);
+    if (lane_id() == 0) {
+        sums[0][threadIdx.x / kWave] = sy;
+        sums[1][threadIdx.x / kWave] = sz;
+    }
+    const double scale = unit_scale(part);
+    __syncthreads();
+    if (threadIdx.x > 0) return;
+    sy = (sums[0][0] + sums[0][1]) + (sums[0][2] + sums[0][3]);
+    sz = (sums[1][0] + sums[1][1]) + (sums[1][2] + sums[1][3]);
+    static_assert(kMvWaves == 4, "four sums");
+    stats[which] = make_double2(0.0, sqrt(sz) * inverse_norm(sy) / scale);
+}
+
 struct GramWs {
     double *part;                   // [n][chunks][pairs][32][32]
     float *G;                       // [n + 1][ld][ld]
     double *v, *w;                  // [n + 1][ld] each
     double *lanczos;                // three more vectors of that size, and alpha and beta [n + 1][kLanczosMax]
+    double *power[3];               // by squaring: G, and two matrices in turn, the first of them in part's place
+    double *traces[3];              // [n + 1][kTraces] each
 };
 
-size_t gram_layout(int32_t n, const GramPlan &p, char *base, GramWs *ws) {
+size_t gram_layout(int32_t n, const GramPlan &p, bool squaring, char *base, GramWs *ws) {
     size_t off = 0;
+    // at whole 4096 bytes: the matrices' rows of d = 1000 otherwise straddle two channels' shares of memory (a product 13.4 us instead of 8.6)
     auto take = [&](size_t bytes) {
         char *at = base ? base + off : nullptr;
-        off += (bytes + 255) / 256 * 256;
+        off += (bytes + 4095) / 4096 * 4096;
         return at;
     };
-    char *pt = take(sizeof(double) * (size_t)n * p.chunks * p.pairs * kTileEntries);
-    char *g = take(sizeof(float) * (size_t)(n + 1) * p.ld * p.ld);
-    char *v = take(sizeof(double) * (size_t)(n + 1) * p.ld);
-    char *w = take(sizeof(double) * (size_t)(n + 1) * p.ld);
-    char *l = take(sizeof(double) * (size_t)(n + 1) * (3 * p.ld + 2 * kLanczosMax));
-    if (ws) *ws = GramWs{(double *)pt, (float *)g, (double *)v, (double *)w, (double *)l};
+    const size_t entries = (size_t)(n + 1) * p.ld * p.ld, part = sizeof(double) * (size_t)n * p.chunks * p.pairs * kTileEntries;
+    GramWs out{};
+    out.part = (double *)take(squaring ? std::max(part, sizeof(double) * entries) : part);
+    if (squaring) {
+        out.power[0] = (double *)take(sizeof(double) * entries);
+        out.power[1] = out.part;
+        out.power[2] = (double *)take(sizeof(double) * entries);
+        for (auto &t : out.traces) t = (double *)take(sizeof(double) * (size_t)(n + 1) * kTraces);
+    } else {
+        out.G = (float *)take(sizeof(float) * entries);
+        out.lanczos = (double *)take(sizeof(double) * (size_t)(n + 1) * (3 * p.ld + 2 * kLanczosMax));
+    }
+    out.v = (double *)take(sizeof(double) * (size_t)(n + 1) * p.ld);
+    out.w = (double *)take(sizeof(double) * (size_t)(n + 1) * p.ld);
+    if (ws) *ws = out;
     return off;
 }
 
@@ -629,10 +902,47 @@ void launch_resident(const GramWs &ws, int32_t n, int64_t d, int64_t ld, int32_t
 
 }  // namespace
 
+namespace {
+// Squarings after which the rest of the iterations is taken with the power reached: G^(2^s) applied (iterations - 1) >> s times, the other
+// bits' powers beside the squarings.  us: of it all.  Measured, us, a squaring and a product with a power: n = 4, d = 100 6.1 and 2.4; 20, 300
+// 24.5 and 4.8; 32, 330 39.5 and 5.5; 2, 1000 79 and 5.8; 15, 1000 320 and 21.
+int32_t squarings(int32_t n, const GramPlan &p, int32_t iterations, double *us) {
+    const double groups = (double)(p.ld / kGroup), square = 8.0 + 8.6e-5 * (n + 1.0) * groups * groups * groups;
+    const double apply = 4.0 + 1.1e-6 * (double)(n + 1) * (double)p.ld * (double)p.ld;
+    int32_t least = 0;
+    *us = 1e30;
+    for (int32_t s = 0; s <= 20; ++s) {
+        const double with = s * square + (double)(((iterations - 1) >> s) + 2) * apply;
+        if (with < *us) {
+            *us = with;
+            least = s;
+        }
+    }
+    return least;
+}
+// How launch_gram_power goes about it: so many squarings, or -1 for the iteration or recurrence with G in fp32.  A call of 100 iterations,
+// us, by the recurrence and by squaring: n = 16, m = 2000, d = 200 204 and 179; 25, 800, 250 204 and 212; 20, 2487, 300 317 and 289; 32, 1400, 330
+// 563 and 373; 10, 3000, 500 581 and 419; 3, 2000, 700 528 and 325; 2, 7500, 1000 796 and 656; 15, 1000, 1000 1154 and 1560; 1000 iterations of
+// 20, 2487, 300 660 and 363; 20 of them 225 and 236.  Up to 128 columns the host's dozen launches are what counts: 4, 250, 100 95 and 101.
+int32_t power_way(int32_t n, const GramPlan &p, int64_t d, int32_t iterations, double *us) {
+    const int32_t lanczos = lanczos_steps(iterations);
+    const double matrices = (n + 1.0) * (double)p.ld * (double)p.ld * 0.92e-6;                     // read in every iteration
+    const double wide = (double)((d + kWave - 1) / kWave), resident = (0.9 + 0.095 * wide * wide) * (double)((n + 256) / 256);
+    const double step = d <= kResidentMax ? resident : (matrices > 8.5 ? matrices : 8.5);
+    const double plain = (lanczos ? lanczos : iterations) * step;
+    const int32_t s = squarings(n, p, iterations, us);
+    if (d > 2 * kWave && iterations > 1 && *us < 0.95 * plain && gram_layout(n, p, true, nullptr, nullptr) <= kGramWsMax) return s;
+    *us = plain;
+    return -1;
+}
+}  // namespace
+
 size_t gram_power_bytes(int32_t n, int64_t m, int64_t d, int32_t iterations) {
     if (d > kGramMax || n > 65534) return 0;
     const GramPlan p = gram_plan(n, m, d);
-    const size_t bytes = gram_layout(n, p, nullptr, nullptr);
+    double with_g;
+    const int32_t way = power_way(n, p, d, iterations, &with_g);
+    const size_t bytes = gram_layout(n, p, way >= 0, nullptr, nullptr);
     if (bytes > kGramWsMax) return 0;
     // Microseconds, a handle's first call: forming the matrices (with the allocation of their workspace) and one iteration
     // on them (or one step of the recurrence), against one iteration with A (six launches).  Measured, forming | iteration on G | with A: n = 4, m = 250,
@@ -640,25 +950,56 @@ size_t gram_power_bytes(int32_t n, int64_t m, int64_t d, int32_t iterations) {
     // 15, 1000, 1000 424 | 15 | 41; 32, 468, 1000 482 | 32 | 40; 32, 100, 1000 253 | 32 | 30; 1000, 20, 100 286 | 2.4 | 137.
     const double nn = n, mm = (double)m, dd = (double)d, ld = (double)p.ld, rows = nn * mm;
     const double form = 10.0 + 0.055 * dd + rows * ld * ld / 55e6 + 0.3e-6 * (double)bytes;
-    const double matrices = (nn + 1.0) * ld * ld * 0.92e-6;                     // read in every iteration
-    const double with_g = d <= kResidentMax ? 2.6 * (double)((n + 256) / 256) : (matrices > 8.5 ? matrices : 8.5);
     const double sums = 512.0 / nn < mm / 8.0 ? 512.0 / nn : mm / 8.0;           // of the gradient, per worker
     const double with_a = 22.0 + 1.1e-6 * rows * dd + 0.08 * nn + 3.5e-5 * sums * dd;
-    const int32_t steps = lanczos_steps(iterations);
-    return form + (steps ? steps : iterations) * with_g < iterations * with_a ? bytes : 0;
+    return form + with_g < iterations * with_a ? bytes : 0;
 }
 
 hipError_t launch_gram_power(const float *A, int32_t n, int64_t m, int64_t d, int32_t iterations, void *workspace,
                              double *stats, hipStream_t stream) {
     const GramPlan p = gram_plan(n, m, d);
     if (d > kGramMax || p.chunks > 65535 || n > 65534) return hipErrorInvalidValue;
+    double us;
+    const int32_t way = power_way(n, p, d, iterations, &us);
     GramWs ws;
-    gram_layout(n, p, (char *)workspace, &ws);
+    gram_layout(n, p, way >= 0, (char *)workspace, &ws);
     const int64_t units = n * p.chunks;
     hipLaunchKernelGGL(gram_tile_kernel, dim3((unsigned)((units + kXcds - 1) / kXcds * kXcds * p.pairs)), dim3(kTileThreads),
                        0, stream, A, m, d, p.rows_per_chunk, p.chunks, units, p.pairs, ws.part);
-    hipLaunchKernelGGL(gram_finish_kernel, dim3((unsigned)p.pairs, (unsigned)(n + 1)), dim3(kTileThreads), 0, stream, ws.part,
-                       p.chunks, p.pairs, d, p.ld, (double)m, ws.G);
+    const dim3 finish_grid((unsigned)p.pairs, (unsigned)(n + 1));
+    if (way >= 0) {
+        hipLaunchKernelGGL(gram_finish_kernel<double>, finish_grid, dim3(kTileThreads), 0, stream, ws.part, p.chunks, p.pairs,
+                           d, p.ld, (double)m, ws.power[0], ws.traces[0]);
+        const Power G{ws.power[0], ws.traces[0], (int32_t)p.nb};
+        Power now = G;
+        const double *y = nullptr;                   // the start vector
+        double *z = ws.v, *other = ws.w;
+        auto applied = [&]() {
+            y = z;
+            std::swap(z, other);
+        };
+        const int64_t groups = (d + kGroup - 1) / kGroup, strips = strip_count(groups), row_blocks = p.ld / kMvRows;
+        const int32_t rest = iterations - 1;
+        for (int32_t j = 0; j < way; ++j) {
+            const int to = 1 + j % 2;
+            const bool apply = (rest >> j) & 1;
+            const int64_t grid = ((n + 1) * strips + kXcds - 1) / kXcds * kXcds + (apply ? (n + 1) * row_blocks : 0);
+            hipLaunchKernelGGL(gram_square_kernel, dim3((unsigned)grid), dim3(kTileThreads), 0, stream, now, d, p.ld, (int32_t)groups,
+                               (int32_t)strips, n + 1, ws.power[to], ws.traces[to], y, z);
+            if (apply) applied();
+            now = Power{ws.power[to], ws.traces[to], (int32_t)((groups + 1) / 2)};
+        }
+        const dim3 apply_grid((unsigned)row_blocks, (unsigned)(n + 1));
+        for (int32_t i = 0; i < rest >> way; ++i) {
+            hipLaunchKernelGGL(gram_apply_kernel, apply_grid, dim3(kMvThreads), 0, stream, now, d, groups * kGroup, p.ld, y, z);
+            applied();
+        }
+        hipLaunchKernelGGL(gram_apply_kernel, apply_grid, dim3(kMvThreads), 0, stream, G, d, groups * kGroup, p.ld, y, z);
+        hipLaunchKernelGGL(gram_ratio_kernel, dim3((unsigned)(n + 1)), dim3(kMvThreads), 0, stream, G, y, z, p.ld, (double2 *)stats);
+        return hipGetLastError();
+    }
+    hipLaunchKernelGGL(gram_finish_kernel<float>, finish_grid, dim3(kTileThreads), 0, stream, ws.part, p.chunks, p.pairs, d,
+                       p.ld, (double)m, ws.G, (double *)nullptr);
     if (d <= kResidentMax) {
         switch ((d + kWave - 1) / kWave) {
             case 1: launch_resident<1>(ws, n, d, p.ld, iterations, stats, stream); break;

@@ -319,3 +319,24 @@ def test_few_iterations_on_large_matrices(gpu):
             times[iterations] = 1e6 * best
     print(times, flush=True)
     assert times[20] <= 3.9 * times[5], times
+
+
+# powers by squaring (more than 128 columns): the ends of the groups of sixteen columns and of the strips of four groups, one row of A and
+# several chunks, and iterations whose exponents have few and many bits
+@pytest.mark.parametrize("n,d,m", [(1, 129, 40), (3, 143, 1), (2, 145, 600), (4, 176, 33), (2, 209, 80), (2, 305, 64), (2, 320, 30),
+                                   (3, 337, 50), (2, 500, 17), (1, 1009, 40), (2, 1024, 12)])
+def test_powers_by_squaring_give_the_power_iterations_value(gpu, n, d, m):
+    """Against the power iteration in fp64.  Non-negative features: 1e-6, as in test_power_iteration_value.  One worker's rows are zero, one's
+    of the order of 1e-12, the first one's of 1e12 (the mean over the workers then is the first one's share to fp32)."""
+    torch, binding = gpu
+    print(f"squaring n={n} d={d} m={m}", flush=True)
+    rng = np.random.default_rng(d + m)
+    scale = np.array([1e12, 1e-12, 0.0, 1.0][:n], np.float32)
+    A = rng.random((n, m, d)).astype(np.float32) * scale[:, None, None]
+    with binding.EF21(n, d, 1, 0.1) as h:
+        h.set_problem_dense(to_gpu(torch, A), torch.zeros((n, m), device="cuda"), 0.0)
+        for steps in (2, 65, 48, 100, 128, 1001, 100000, 64):
+            _, L, L_i = h.theory_stepsize(steps)
+            got = 4.0 * np.array(list(L_i) + [L])
+            # the product with a rank-one dominated matrix settles within a few steps: 200 stand for more
+            np.testing.assert_allclose(got, power_values(A, min(steps, 200)), rtol=1e-6, err_msg=f"{steps} iterations")
