@@ -21,9 +21,9 @@
 //             wavefront per slot: ordered emission of the k kept entries (+ line 6 of Algorithm 2 on request).
 //
 // The guess can be wrong: fewer than k candidates, T beyond the histogram's window, or a crowded bin (more
-// than kTieCap entries, i.e. very many equal magnitudes at the threshold).  After a warm start a second collect
-// pass (normally a launch that ends at once) redoes such a row from the sample; a row that still fails is selected
-// by the exact one-workgroup algorithm on the original data (its first workgroup of the count kernel), so the
+// than kTieCap entries, i.e. very many equal magnitudes at the threshold).  After a warm start the count kernel's workgroups
+// collect such a row again from the sample, and the last one of them counts it; a row that still fails is selected
+// by the exact one-workgroup algorithm on the original data (one workgroup of the count or the emit kernel), so the
 // result never depends on the guess.  Slots have the capacity of their piece, so any input fits.
 #include <algorithm>
 #include <cmath>
@@ -79,6 +79,33 @@ __device__ __forceinline__ uint32_t warm_shift(int64_t k, int64_t d, uint32_t in
     return s;
 }
 constexpr uint32_t kWarmBelow = 1u << 20;
+// A threshold that has just moved by more than a sixteenth of an octave, or that is the first one, may well move again by more than that
+// allows.  The steps of EF21 from a fresh state on gradients that stay alike keep k entries more each: at k = 5 per
+// cent of a Gaussian row T falls by 16 per cent, then 12, 11, 10 ..; the errors of EF grow from zero by 100 per cent, 50, 33 ..; and a
+// failed guess costs twice the call.  After a fall, half an octave of margin brings two to seven times the candidates
+// instead; after either, a window of two octaves (bins of 2^12 keys) or one, unless T's bin would be crowded, costs next to nothing.  The first
+// ten steps, us each, before and now: EF21 on n = 8, d = 10^6, k = 10^4 52 and 47; n = 5, d = 10^6, k = 50 000 67 and 51; n = 8, d = 11.2 million,
+// k = 112 000 347 and 279.  (Where every row's guess fails at every step, scales a thousand apart in turn: n = 8, d = 10^5, k = 3000 37 and 43;
+// n = 8, d = 10^6, k = 10^4 78 and 96; n = 4, d = 3 million, k = 200 000 131 and 243, most of it the count by one workgroup per row.)
+constexpr uint32_t kMoved = 1u << 19, kWarmBelowWide = 1u << 22, kWideEntries = 256u;
+constexpr uint32_t kWideStart = 0x100u;      // flag in RowInfo::warm_s: the wide margin, which takes a window of an octave
+__device__ __forceinline__ uint32_t warm_start(int64_t k, int64_t d, uint32_t in_bin, uint32_t used, bool before, uint32_t T_before, uint32_t T, bool errors) {
+    uint32_t s = warm_shift(k, d, in_bin, used);
+    const bool fell = !before || T + kMoved < T_before, rose = !before || T > T_before + kMoved;
+    if (fell || rose) {
+        // (EF21's falling threshold comes to where the entries are closer together: two octaves took a third more time in a run that had kept
+        // all entries; the errors of EF fall when a run starts again, and grow then)
+        for (uint32_t wide = before && fell && !errors ? 11u : 12u; wide > s && wide > 10u; --wide)
+            if ((in_bin << wide) >> used <= kWideEntries) s = wide;
+    }
+    return fell && s >= 11u ? s | kWideStart : s;
+}
+// lower bound of the candidates' keys and bin width of a start from threshold T, noted as `start`
+__device__ __forceinline__ void start_from(uint32_t T, uint32_t start, uint32_t *key_lo, uint32_t *shift) {
+    const uint32_t below = start & kWideStart ? kWarmBelowWide : kWarmBelow;
+    *key_lo = T > below ? T - below : 0u;
+    *shift = start & ~kWideStart;
+}
 constexpr int kTieCap = 1024;                // entries of T's bin that are ranked directly (one per thread)
 constexpr int kWarmSlots = 1;                // remembered thresholds per row (TopkArgs::warm = 1 .. kWarmSlots)
 enum CollectMode { kColdPass = 0, kWarmPass = 1, kSecondPass = 2 };
@@ -86,18 +113,17 @@ enum CollectMode { kColdPass = 0, kWarmPass = 1, kSecondPass = 2 };
 enum AddMode { kNoAdd = 0, kAddKept = 1, kAddStreamed = 2 };
 
 struct __attribute__((aligned(64))) RowInfo {     // one cache line per row
-    uint32_t key_lo, shift;       // lower bound of the candidate keys and bin width (first collect pass)
-    uint32_t key_lo2, shift2;     // ... of the second pass, valid if use2
-    uint32_t use2;                // the second pass redid this row: its histogram is hist_b
+    uint32_t key_lo, shift;       // lower bound of the candidate keys and bin width
+    uint32_t key_lo2, shift2;     // ... of the row collected again, valid if use2
+    uint32_t use2;                // the count kernel collected this row again: its histogram is hist_b
     uint32_t warm_used;           // the first pass started from a remembered threshold
     uint32_t failed;              // kRowFailed: the row went to the exact one-workgroup algorithm in the count kernel;
                                   // kRowCrowded: T's bin holds more than kTieCap candidates (see tie_min, tie_max)
     uint32_t bin_a, need_a;       // bin of T; entries still needed from that bin
     uint32_t ntie;                // length of the tie list
-    uint32_t M;                   // candidates of the first pass (zero between calls)
-    uint32_t q;                   // number of entries equal to the threshold key T that are kept
+    uint32_t arrived;             // workgroups of the count kernel that have collected the row again (zero between calls)
     uint32_t warm_T[kWarmSlots];  // threshold T of the last call (also with warm == 0)
-    uint32_t warm_s[kWarmSlots];  // bin width for the next warm start from it; 0: there is none to start from
+    uint32_t warm_s[kWarmSlots];  // bin width for the next warm start from it, with kWideStart; 0: there is none to start from
     uint32_t tie_min, tie_max;    // crowded bin: smallest and largest key in it.  Equal: T is that key (many equal
                                   // magnitudes at the threshold, e.g. zeros), no ranking needed.  Different: the
                                   // exact one-workgroup algorithm, in the emit kernel.
@@ -410,13 +436,12 @@ __device__ __forceinline__ void drain_ring(const Ring &ring, uint32_t flushed, u
 // Whole groups are loaded without any bounds check so that all loads of a group are in flight together; only the last
 // piece of a row has a checked tail.
 // MODE: kColdPass key_lo from the sample; kWarmPass from the threshold remembered in slot p.warm if there is
-// one, else from the sample; kSecondPass: only rows whose warm start failed, from the sample, into hist_b.
+// one, else from the sample; kSecondPass: a row whose warm start failed, from the sample, into hist_b (in the count kernel).
 // ADD != kNoAdd (kWarmPass): the rows are a + add_scale * add, written over a on the way.  A sample would find some entries of the row
-// old and some new, so a row without a remembered threshold collects nothing here and is left to the second pass.
+// old and some new, so a row without a remembered threshold collects nothing here and is left to the count kernel.
 // All kBlk threads of the workgroup must call; s, rings and wg_total are the workgroup's.
 template <bool DIFF, int MODE, bool RESID, int ADD, class Ring>
-__device__ __forceinline__ void collect_rows(const TopkArgs &p, const Ws &w, RowShared &s, Ring (&rings)[kBlkWaves],
-                                             uint32_t &wg_total) {
+__device__ __forceinline__ void collect_rows(const TopkArgs &p, const Ws &w, RowShared &s, Ring (&rings)[kBlkWaves]) {
     const int64_t row = blockIdx.y, d = p.d;
     const float *a = p.a + row * d;
     static_assert(ADD == kNoAdd || (!DIFF && !RESID && MODE == kWarmPass), "see above");
@@ -427,18 +452,11 @@ __device__ __forceinline__ void collect_rows(const TopkArgs &p, const Ws &w, Row
     CandFilter f;
     f.hist = s.hist;
     uint32_t *merged = w.hist_a + row * kHistBins;
-    uint32_t *row_total = &info->M;
     if constexpr (MODE == kSecondPass) {
-        // The guess of the first pass held if it kept at least k candidates and the k-th largest of them lies
-        // inside the histogram's window, i.e. fewer than k fell into the last bin: then this pass ends here.
-        const uint32_t warm_used = info->warm_used, M = info->M, beyond = merged[kHistBins - 1];
-        if (!warm_used) return;                      // a cold first pass: what fails goes to the exact algorithm
-        if (M >= (uint32_t)p.k && beyond < (uint32_t)p.k) return;
         const Guess g = guess_from_sample<DIFF>(s, a, b, d, w.rule);
         f.key_lo = g.key_lo;
         f.shift = g.shift;
         merged = w.hist_b + row * kHistBins;
-        row_total = nullptr;
         if (blockIdx.x == 0 && threadIdx.x == 0) {
             info->key_lo2 = f.key_lo;
             info->shift2 = f.shift;
@@ -448,9 +466,7 @@ __device__ __forceinline__ void collect_rows(const TopkArgs &p, const Ws &w, Row
         uint32_t warm = 0u;                          // the remembered threshold's bin width
         if constexpr (MODE == kWarmPass) warm = info->warm_s[p.warm - 1];
         if (warm) {
-            const uint32_t T = info->warm_T[p.warm - 1];
-            f.key_lo = T > kWarmBelow ? T - kWarmBelow : 0u;
-            f.shift = warm;
+            start_from(info->warm_T[p.warm - 1], warm, &f.key_lo, &f.shift);
         } else if constexpr (ADD) {
             f.key_lo = 0x80000000u;                  // above every key
             f.shift = w.rule.widest;
@@ -470,13 +486,11 @@ __device__ __forceinline__ void collect_rows(const TopkArgs &p, const Ws &w, Row
         }
     }
     for (int i = threadIdx.x; i < kHistBins; i += kBlk) s.hist[i] = 0u;
-    if (threadIdx.x == 0) wg_total = 0u;
     __syncthreads();
 
     const int wave = wave_id(), lane = lane_id();
-    // the first pass has a wavefront per slot; the second pass, which seldom has work, runs on a small grid
-    for (int64_t slot_no = (int64_t)blockIdx.x * kBlkWaves + wave; slot_no < w.nslot;
-         slot_no += (int64_t)gridDim.x * kBlkWaves) {
+    const int64_t slot_no = (int64_t)blockIdx.x * kBlkWaves + wave;
+    if (slot_no < w.nslot) {
         Ring &ring = rings[wave];
         const int64_t lo = slot_no * w.L;
         const int64_t hi = lo + w.L < d ? lo + w.L : d;
@@ -549,34 +563,20 @@ __device__ __forceinline__ void collect_rows(const TopkArgs &p, const Ws &w, Row
             }
         }
         drain_ring<RESID>(ring, flushed, cnt, lane, slot, f);
-        if (lane == 0) {
-            w.slot_cnt[row * w.nslot + slot_no] = cnt;
-            atomicAdd(&wg_total, cnt);
-        }
+        if (lane == 0) w.slot_cnt[row * w.nslot + slot_no] = cnt;
     }
     __syncthreads();
     for (int i = threadIdx.x; i < kHistBins; i += kBlk) {
         const uint32_t c = s.hist[i];
         if (c) atomicAdd(merged + i, c);
     }
-    if (row_total && threadIdx.x == 0 && wg_total) atomicAdd(row_total, wg_total);
 }
 
 template <bool DIFF, int MODE, int ADD = kNoAdd>
 __global__ __launch_bounds__(kBlk) void split_collect_kernel(TopkArgs p, Ws w) {
     __shared__ RowShared s;
     __shared__ StageRing<false> rings[kBlkWaves];
-    __shared__ uint32_t wg_total;
-    collect_rows<DIFF, MODE, false, ADD>(p, w, s, rings, wg_total);
-}
-
-// The second pass of the two selections of Algorithm 3 in one launch: grid (.., n, 2).
-__global__ __launch_bounds__(kBlk) void split_second_pair_kernel(TopkArgs pp, Ws wp, TopkArgs pm, Ws wm) {
-    __shared__ RowShared s;
-    __shared__ StageRing<true> rings[kBlkWaves];
-    __shared__ uint32_t wg_total;
-    if (blockIdx.z == 0) collect_rows<false, kSecondPass, false, kNoAdd>(pp, wp, s, rings, wg_total);
-    else collect_rows<true, kSecondPass, true, kNoAdd>(pm, wm, s, rings, wg_total);
+    collect_rows<DIFF, MODE, false, ADD>(p, w, s, rings);
 }
 
 // ---------------------------------------------------------------- collect, two selections in one pass
@@ -593,7 +593,6 @@ __global__ __launch_bounds__(kBlk) void split_collect_pair_kernel(TopkArgs pm, W
     __shared__ uint32_t hist_p[kHistBins];
     __shared__ StageRing<true> rings_m[kBlkWaves];
     __shared__ StageRing<false> rings_p[kBlkWaves];
-    __shared__ uint32_t wg_total_m, wg_total_p;
     const int64_t row = blockIdx.y, d = pm.d;
     const float *a = pm.a + row * d, *b = pm.b + row * d;
     RowInfo *info_m = wm.info + row, *info_p = wp.info + row;
@@ -602,18 +601,14 @@ __global__ __launch_bounds__(kBlk) void split_collect_pair_kernel(TopkArgs pm, W
     fp.hist = hist_p;
     const uint32_t warm_m = WARM ? info_m->warm_s[pm.warm - 1] : 0u, warm_pl = WARM ? info_p->warm_s[warm_p - 1] : 0u;
     if (warm_m) {
-        const uint32_t T = info_m->warm_T[pm.warm - 1];
-        fm.key_lo = T > kWarmBelow ? T - kWarmBelow : 0u;
-        fm.shift = warm_m;
+        start_from(info_m->warm_T[pm.warm - 1], warm_m, &fm.key_lo, &fm.shift);
     } else {
         const Guess g = guess_from_sample<true>(s, a, b, d, wm.rule);
         fm.key_lo = g.key_lo;
         fm.shift = g.shift;
     }
     if (warm_pl) {
-        const uint32_t T = info_p->warm_T[warm_p - 1];
-        fp.key_lo = T > kWarmBelow ? T - kWarmBelow : 0u;
-        fp.shift = warm_pl;
+        start_from(info_p->warm_T[warm_p - 1], warm_pl, &fp.key_lo, &fp.shift);
     } else {
         const Guess g = guess_from_sample<false>(s, a, nullptr, d, wm.rule);
         fp.key_lo = g.key_lo;
@@ -630,10 +625,6 @@ __global__ __launch_bounds__(kBlk) void split_collect_pair_kernel(TopkArgs pm, W
     for (int i = threadIdx.x; i < kHistBins; i += kBlk) {
         s.hist[i] = 0u;
         hist_p[i] = 0u;
-    }
-    if (threadIdx.x == 0) {
-        wg_total_m = 0u;
-        wg_total_p = 0u;
     }
     __syncthreads();
 
@@ -713,8 +704,6 @@ __global__ __launch_bounds__(kBlk) void split_collect_pair_kernel(TopkArgs pm, W
         if (lane == 0) {
             wm.slot_cnt[row * wm.nslot + slot_no] = cnt_m;
             wp.slot_cnt[row * wp.nslot + slot_no] = cnt_p;
-            atomicAdd(&wg_total_m, cnt_m);
-            atomicAdd(&wg_total_p, cnt_p);
             norms[row * wm.nslot + slot_no] = make_double2(sq_s, sq_v);
         }
     }
@@ -724,10 +713,6 @@ __global__ __launch_bounds__(kBlk) void split_collect_pair_kernel(TopkArgs pm, W
         const uint32_t cm = s.hist[i], cp = hist_p[i];
         if (cm) atomicAdd(merged_m + i, cm);
         if (cp) atomicAdd(merged_p + i, cp);
-    }
-    if (threadIdx.x == 0) {
-        if (wg_total_m) atomicAdd(&info_m->M, wg_total_m);
-        if (wg_total_p) atomicAdd(&info_p->M, wg_total_p);
     }
 }
 
@@ -802,12 +787,42 @@ __device__ void rescue_row(RowShared &rs, const TopkArgs &p, const Ws &w, int64_
 // go to the tie list.  (An extra workgroup per row for the exact algorithm, as there used to be, keeps a compute unit from
 // the last of 255 others for a few microseconds, here and in the emit kernel, since a unit holds one of them: step of
 // n = 15, d = 5 million, k = 50000 10.1 and 40.6 us in the two kernels, 6.7 and 31.7 without.)
+//
+// A row whose warm start failed is collected again from the sample instead, by all its workgroups, into hist_b; the one that is done
+// last counts all of its slots.  Nobody waits.  (As a launch of its own, which nearly always ended at once, the second pass took 3.8 to 4.6 us of
+// every warm call: n = 8, d = 10^5, k = 3000 26.6 us a step with it, 24.5 so; n = 8, d = 10^6, k = 10^4 38.7 and 36.2; EF on n = 5, d = 10^6, k =
+// 50 000 44.4 and 42.1; EF21+ on n = 5, d = 10^6 55.2 and 53.0.)
 struct CountShared {
     RowShared rs;
-    uint32_t wave[kCandWaves], out[4];
+    uint32_t wave[kCandWaves], out[4], last;
 };
+// The bin of the row's histogram that holds the need-th largest key: the largest bin b with count(bins > b) < need <= count(bins >= b),
+// from the thread's bins h, the highest first.  out[0] = b, out[1] = need - count(bins > b), out[2] = the bin's entries; false if there
+// are fewer than `need`.  All threads of the workgroup must call.
+constexpr int kPerThread = kHistBins / kCandThreads;
+__device__ __forceinline__ bool threshold_bin(const uint32_t (&h)[kPerThread], uint32_t need, uint32_t (&lds_wave)[kCandWaves],
+                                              uint32_t (&out)[4]) {
+    uint32_t mine = 0, total;
+#pragma unroll
+    for (int j = 0; j < kPerThread; ++j) mine += h[j];
+    const uint32_t higher = cand_block_scan<kCandThreads>(mine, lds_wave, &total);
+    if (higher < need && need <= higher + mine) {         // exactly one thread, if total >= need
+        uint32_t run = higher;
+#pragma unroll
+        for (int j = 0; j < kPerThread; ++j) {
+            if (need > run && need <= run + h[j]) {
+                out[0] = (uint32_t)(kHistBins - 1 - ((int)threadIdx.x * kPerThread + j));
+                out[1] = need - run;
+                out[2] = h[j];
+            }
+            run += h[j];
+        }
+    }
+    __syncthreads();
+    return total >= need;
+}
 template <bool DIFF, int UPDATE, int kPre, bool SUMS>
-__device__ __forceinline__ void count_rows(const TopkArgs &p, const Ws &w, CountShared &sh) {
+__device__ __forceinline__ void count_rows(const TopkArgs &p, const Ws &w, CountShared &sh, StageRing<DIFF && SUMS> (&rings)[kBlkWaves]) {
     RowShared &rs = sh.rs;
     uint32_t (&lds_wave)[kCandWaves] = sh.wave, (&lds_out)[4] = sh.out;
     const int64_t row = blockIdx.y;
@@ -816,10 +831,9 @@ __device__ __forceinline__ void count_rows(const TopkArgs &p, const Ws &w, Count
     const int64_t slot_no = (int64_t)blockIdx.x * kCandWaves + wave;
     // everything whose address is known now
     const RowInfo ri = *info;
-    constexpr int PER = kHistBins / kCandThreads;
-    uint32_t h[PER];
+    uint32_t h[kPerThread];
 #pragma unroll
-    for (int j = 0; j < PER; ++j) h[j] = w.hist_a[row * kHistBins + kHistBins - 1 - (tid * PER + j)];
+    for (int j = 0; j < kPerThread; ++j) h[j] = w.hist_a[row * kHistBins + kHistBins - 1 - (tid * kPerThread + j)];
     uint2 c[kPre];
     const bool active = slot_no < w.nslot;
     const int64_t slc = active ? slot_no : 0;
@@ -829,80 +843,96 @@ __device__ __forceinline__ void count_rows(const TopkArgs &p, const Ws &w, Count
     for (int q = 0; q < kPre; ++q) c[q] = slot[q * kWave + lane];
     if (!active) cnt = 0u;
 
-    const bool second = ri.use2 != 0u;
-    const uint32_t key_lo = second ? ri.key_lo2 : ri.key_lo, shift = second ? ri.shift2 : ri.shift;
-    if (second) {
-#pragma unroll
-        for (int j = 0; j < PER; ++j) h[j] = w.hist_b[row * kHistBins + kHistBins - 1 - (tid * PER + j)];
-    }
-    // T's bin: the largest bin b with count(bins > b) < k <= count(bins >= b)
-    uint32_t mine = 0, total;
-#pragma unroll
-    for (int j = 0; j < PER; ++j) mine += h[j];
-    const uint32_t higher = cand_block_scan<kCandThreads>(mine, lds_wave, &total);
-    const uint32_t need = (uint32_t)p.k;
-    if (higher < need && need <= higher + mine) {         // exactly one thread, if total >= k
-        uint32_t run = higher;
-#pragma unroll
-        for (int j = 0; j < PER; ++j) {
-            if (need > run && need <= run + h[j]) {
-                lds_out[0] = (uint32_t)(kHistBins - 1 - (tid * PER + j));
-                lds_out[1] = need - run;
-                lds_out[2] = h[j];
-            }
-            run += h[j];
-        }
-    }
-    __syncthreads();
-    bool failed = total < need, crowded = false;                       // fewer than k candidates
-    uint32_t bin_a = 0, need_a = 0;
-    if (!failed) {
-        bin_a = lds_out[0];
-        need_a = lds_out[1];
-        failed = bin_a == (uint32_t)kHistBins - 1u;                    // beyond the window
-        crowded = !failed && lds_out[2] > (uint32_t)kTieCap;           // too many to list: see RowInfo::tie_min
-    }
-    if (blockIdx.x == 0 && tid == 0) {
+    uint32_t key_lo = ri.key_lo, shift = ri.shift, bin_a = 0, need_a = 0;
+    bool crowded = false;
+    auto find_bin = [&]() {                      // false: fewer than k candidates, or T beyond the window
+        const bool enough = threshold_bin(h, (uint32_t)p.k, lds_wave, lds_out);
+        bin_a = enough ? lds_out[0] : 0u;
+        need_a = enough ? lds_out[1] : 0u;
+        const bool found = enough && bin_a != (uint32_t)kHistBins - 1u;
+        crowded = found && lds_out[2] > (uint32_t)kTieCap;             // too many to list: see RowInfo::tie_min
+        return found;
+    };
+    auto record = [&](bool failed) {
         info->failed = failed ? kRowFailed : (crowded ? kRowCrowded : kRowFine);
         info->bin_a = bin_a;
         info->need_a = need_a;
-        info->M = 0u;                        // consumed by the second collect pass: zero for the next call
+    };
+    const bool failed = !find_bin();
+    if (failed && ri.warm_used) {
+        __syncthreads();                         // lds_out has been read
+        collect_rows<DIFF, kSecondPass, DIFF && SUMS, kNoAdd>(p, w, rs, rings);
+        __syncthreads();                         // all of this workgroup's candidates and counts are stored
+        if (tid == 0) {                          // one thread releases and acquires for its workgroup
+            __threadfence();
+            sh.last = atomicAdd(&info->arrived, 1u) + 1u == gridDim.x ? 1u : 0u;
+            if (sh.last) {
+                __threadfence();
+                info->arrived = 0u;
+            }
+        }
+        __syncthreads();
+        if (!sh.last) return;
+        key_lo = info->key_lo2;
+        shift = info->shift2;
+#pragma unroll
+        for (int j = 0; j < kPerThread; ++j) {
+            uint32_t *bin = w.hist_b + row * kHistBins + kHistBins - 1 - (tid * kPerThread + j);
+            h[j] = *bin;
+            *bin = 0u;                           // consumed: zero for the next time
+        }
+        const bool found = find_bin();
+        if (tid == 0) record(!found);
+        if (!found) {
+            rescue_row<DIFF, UPDATE, SUMS>(rs, p, w, row, widest_warm(p.k, p.d));
+            return;
+        }
+    } else {
+        if (blockIdx.x == 0 && tid == 0) record(failed);
+        if (failed) {
+            if (blockIdx.x == 0) rescue_row<DIFF, UPDATE, SUMS>(rs, p, w, row, widest_warm(p.k, p.d));
+            return;
+        }
     }
-    if (failed) {
-        if (blockIdx.x == 0) rescue_row<DIFF, UPDATE, SUMS>(rs, p, w, row, widest_warm(p.k, p.d));
-        return;
-    }
+    const bool again = failed;
     uint2 *tie = w.tie + row * kTieCap;
     uint32_t key_min = 0xffffffffu, key_max = 0u;
-    uint32_t above = 0, inbin = 0;
-    for (uint32_t j0 = 0; j0 < cnt; j0 += kWave * kPre) {
-        if (j0 > 0) {
+    // this wavefront's slot, or every sixteenth one of the row
+    for (int64_t s = again ? wave : slot_no; s < w.nslot; s += again ? kCandWaves : w.nslot) {
+        if (again) {
+            cnt = w.slot_cnt[row * w.nslot + s];
+            slot = w.cand + (row * w.nslot + s) * w.L;
+        }
+        uint32_t above = 0, inbin = 0;
+        for (uint32_t j0 = 0; j0 < cnt; j0 += kWave * kPre) {
+            if (j0 > 0 || again) {
+#pragma unroll
+                for (int q = 0; q < kPre; ++q) {
+                    const uint32_t j = j0 + q * kWave + lane;
+                    c[q] = slot[j < cnt ? j : 0u];           // clamped: no load behind a branch
+                }
+            }
 #pragma unroll
             for (int q = 0; q < kPre; ++q) {
                 const uint32_t j = j0 + q * kWave + lane;
-                c[q] = slot[j < cnt ? j : 0u];           // clamped: no load behind a branch
+                const uint32_t key = c[q].y & 0x7fffffffu;
+                const uint32_t bin = bin_of(key < key_lo ? key_lo : key, key_lo, shift);
+                above += popc64(__ballot(j < cnt && bin > bin_a));
+                const bool in_bin = j < cnt && bin == bin_a;
+                if (!crowded) {
+                    const uint32_t at = wave_append(in_bin, &info->ntie);
+                    if (in_bin && at < (uint32_t)kTieCap) tie[at] = make_uint2(c[q].x, key);
+                } else {
+                    inbin += popc64(__ballot(in_bin));
+                    key_min = in_bin && key < key_min ? key : key_min;
+                    key_max = in_bin && key > key_max ? key : key_max;
+                }
             }
         }
-#pragma unroll
-        for (int q = 0; q < kPre; ++q) {
-            const uint32_t j = j0 + q * kWave + lane;
-            const uint32_t key = c[q].y & 0x7fffffffu;
-            const uint32_t bin = bin_of(key < key_lo ? key_lo : key, key_lo, shift);
-            above += popc64(__ballot(j < cnt && bin > bin_a));
-            const bool in_bin = j < cnt && bin == bin_a;
-            if (!crowded) {
-                const uint32_t at = wave_append(in_bin, &info->ntie);
-                if (in_bin && at < (uint32_t)kTieCap) tie[at] = make_uint2(c[q].x, key);
-            } else {
-                inbin += popc64(__ballot(in_bin));
-                key_min = in_bin && key < key_min ? key : key_min;
-                key_max = in_bin && key > key_max ? key : key_max;
-            }
+        if (lane == 0) {
+            w.slot_above[row * w.nslot + s] = above;
+            if (crowded) w.slot_inbin[row * w.nslot + s] = inbin;
         }
-    }
-    if (lane == 0 && slot_no < w.nslot) {
-        w.slot_above[row * w.nslot + slot_no] = above;
-        if (crowded) w.slot_inbin[row * w.nslot + slot_no] = inbin;
     }
     if (crowded) {
 #pragma unroll
@@ -921,15 +951,20 @@ __device__ __forceinline__ void count_rows(const TopkArgs &p, const Ws &w, Count
 template <bool DIFF, int UPDATE, int kPre>
 __global__ __launch_bounds__(kCandThreads) void cand_count_kernel(TopkArgs p, Ws w) {
     __shared__ CountShared sh;
-    count_rows<DIFF, UPDATE, kPre, false>(p, w, sh);
+    __shared__ StageRing<false> rings[kBlkWaves];
+    count_rows<DIFF, UPDATE, kPre, false>(p, w, sh, rings);
 }
 
 // The two selections of Algorithm 3 in one launch: grid (.., n, 2).  (Likewise cand_emit_pair_kernel.)
 template <int kPre>
 __global__ __launch_bounds__(kCandThreads) void cand_count_pair_kernel(TopkArgs pp, Ws wp, TopkArgs pm, Ws wm) {
     __shared__ CountShared sh;
-    if (blockIdx.z == 0) count_rows<false, kNoUpdate, kPre, true>(pp, wp, sh);
-    else count_rows<true, kNoUpdate, kPre, true>(pm, wm, sh);
+    __shared__ union {
+        StageRing<false> plain[kBlkWaves];
+        StageRing<true> markov[kBlkWaves];
+    } rings;
+    if (blockIdx.z == 0) count_rows<false, kNoUpdate, kPre, true>(pp, wp, sh, rings.plain);
+    else count_rows<true, kNoUpdate, kPre, true>(pm, wm, sh, rings.markov);
 }
 
 // Ordered emission by one wavefront that walks candidates in position order, 64 at a time: the running output
@@ -1077,10 +1112,7 @@ __device__ __forceinline__ void emit_rows(const TopkArgs &p, const Ws &w, EmitSh
         }
     }
 
-    if (blockIdx.x == 0) {                       // the histograms are consumed: zero for the next call
-        zero_global_hist(w.hist_a + row * kHistBins, kHistBins);
-        if (ri.use2 != 0u) zero_global_hist(w.hist_b + row * kHistBins, kHistBins);
-    }
+    if (blockIdx.x == 0) zero_global_hist(w.hist_a + row * kHistBins, kHistBins);        // consumed: zero for the next call
     if (ri.failed == kRowFailed) return;         // the whole workgroup
     if (crowded && ri.tie_min != ri.tie_max) {
         if (blockIdx.x == 0) rescue_row<DIFF, UPDATE, SUMS>(rs, p, w, row, warm_shift(p.k, p.d, kCrowdedBin, 0u));
@@ -1108,11 +1140,12 @@ __device__ __forceinline__ void emit_rows(const TopkArgs &p, const Ws &w, EmitSh
     __syncthreads();
     const uint32_t T = crowded ? ri.tie_min : sh_T, q = crowded ? ri.need_a : sh_q;
     if (blockIdx.x == 0 && tid == 0) {
-        info->q = q;
         const int mem = p.warm > 0 ? p.warm - 1 : 0;
+        static_assert(kWarmSlots == 1, "mem is zero; as an index it would put ri into scratch memory");
         info->warm_T[mem] = T;
         // a crowded bin of equal keys: no wider the next time (narrower would not help)
-        info->warm_s[mem] = p.warm > 0 ? warm_shift(p.k, p.d, crowded ? kBinEntries : ntie, ri.use2 != 0u ? ri.shift2 : ri.shift) : 0u;
+        info->warm_s[mem] = p.warm > 0 ? warm_start(p.k, p.d, crowded ? kBinEntries : ntie, ri.use2 != 0u ? ri.shift2 : ri.shift,
+                                                    ri.warm_s[0] != 0u, ri.warm_T[0], T, UPDATE == kClearUpdate) : 0u;
     }
 
     part = wave_sum_u32(part);
@@ -1186,21 +1219,13 @@ __global__ __launch_bounds__(kCandThreads) void zero_words_kernel(uint32_t *p, s
     for (size_t i = (size_t)blockIdx.x * kCandThreads + threadIdx.x; i < words; i += stride) p[i] = 0u;
 }
 
-template <bool DIFF>
-void launch_collect_mode(const TopkArgs &p, const Ws &w, int mode, const dim3 &grid, hipStream_t stream) {
-    const dim3 block(kBlk);
-    if (mode == kColdPass) hipLaunchKernelGGL((split_collect_kernel<DIFF, kColdPass>), grid, block, 0, stream, p, w);
-    else if (mode == kWarmPass) hipLaunchKernelGGL((split_collect_kernel<DIFF, kWarmPass>), grid, block, 0, stream, p, w);
-    else hipLaunchKernelGGL((split_collect_kernel<DIFF, kSecondPass>), grid, block, 0, stream, p, w);
-}
-
-void launch_collect(const TopkArgs &p, const Ws &w, int mode, hipStream_t stream) {
-    // the second pass has work only after a failed guess: about 64 workgroups, which loop over the slots
-    int64_t g = w.G;
-    if (mode == kSecondPass) g = std::max<int64_t>(1, std::min<int64_t>(w.G, 64 / p.n));
-    const dim3 grid((unsigned)g, (unsigned)p.n);
-    if (p.b != nullptr) launch_collect_mode<true>(p, w, mode, grid, stream);
-    else launch_collect_mode<false>(p, w, mode, grid, stream);
+void launch_collect(const TopkArgs &p, const Ws &w, hipStream_t stream) {
+    const dim3 grid((unsigned)w.G, (unsigned)p.n), block(kBlk);
+    const bool diff = p.b != nullptr, warm = p.warm > 0;
+    if (diff && warm) hipLaunchKernelGGL((split_collect_kernel<true, kWarmPass>), grid, block, 0, stream, p, w);
+    else if (diff) hipLaunchKernelGGL((split_collect_kernel<true, kColdPass>), grid, block, 0, stream, p, w);
+    else if (warm) hipLaunchKernelGGL((split_collect_kernel<false, kWarmPass>), grid, block, 0, stream, p, w);
+    else hipLaunchKernelGGL((split_collect_kernel<false, kColdPass>), grid, block, 0, stream, p, w);
 }
 
 // ---------------------------------------------------------------- k = 1: the entry of largest magnitude
@@ -1356,13 +1381,9 @@ int cand_steps(const TopkArgs &p, const Ws &w, int most) {
     return steps < most ? steps : most;
 }
 
-// After the first collect pass: the second pass (after a warm start), count and emit.
+// After the collect pass: count (or, for a row whose warm start failed, collect again) and emit.
 hipError_t launch_after_collect(const TopkArgs &p, const Ws &w, hipStream_t stream, const Marker &mk) {
     const bool diff = p.b != nullptr, upd = p.g_i != nullptr;
-    if (p.warm > 0) {
-        launch_collect(p, w, kSecondPass, stream);
-        mk(K_TOPK_REFINE);
-    }
     const int steps = cand_steps(p, w, 6);
     const dim3 cgrid = cand_grid(p.n, w, 1), block(kCandThreads);
 #define EF21_CAND(KERNEL, GRID, DIFF, UPD)                                                               \
@@ -1407,7 +1428,7 @@ hipError_t launch_topk_split(const TopkArgs &p, void *workspace, hipStream_t str
     else if (p.add)
         hipLaunchKernelGGL((split_collect_kernel<false, kWarmPass, kAddStreamed>), add_grid, block, 0, stream, p, w);
     else
-        launch_collect(p, w, p.warm > 0 ? kWarmPass : kColdPass, stream);
+        launch_collect(p, w, stream);
     mk(K_TOPK_COLLECT);
     hipError_t st = hipGetLastError();
     if (st != hipSuccess) return st;
@@ -1447,12 +1468,6 @@ hipError_t launch_topk_split_pair(const TopkArgs &plain, const TopkArgs &markov,
     if (warm) hipLaunchKernelGGL(split_collect_pair_kernel<true>, grid, block, 0, stream, markov, wm, plain.warm, wp, norms);
     else hipLaunchKernelGGL(split_collect_pair_kernel<false>, grid, block, 0, stream, markov, wm, plain.warm, wp, norms);
     mk(K_TOPK_COLLECT);
-    if (warm) {
-        const int64_t g = std::max<int64_t>(1, std::min<int64_t>(wm.G, 64 / markov.n));      // as in launch_collect
-        hipLaunchKernelGGL(split_second_pair_kernel, dim3((unsigned)g, (unsigned)markov.n, 2), block, 0, stream, plain, wp,
-                           markov, wm);
-        mk(K_TOPK_REFINE);
-    }
     const int steps = cand_steps(markov, wm, 4);
     const dim3 cgrid = cand_grid(markov.n, wm, 2);
 #define EF21_CAND(KERNEL)                                                                                \

@@ -842,3 +842,53 @@ def test_state_in_and_out(gpu, n, d, offset):
         binding._check(binding.load_library().ef21_set_state(h._h, pinned.data_ptr(), g_i.data_ptr(), None))
         check(x=host["x"], g_i=host["g_i"], g=mean)     # an array that is not in this device's memory
         torch.cuda.synchronize()
+
+
+# rows that are collected again because the remembered threshold was wrong, and what can go wrong with them then: one slot of candidates
+# and many, few and many candidates per slot, a row of odd length
+@pytest.mark.parametrize("n,d,k", [(1, 61_441, 1_025), (3, 300_001, 40_000), (2, 1_000_003, 2_000)])
+def test_rows_collected_again(gpu, oracle, n, d, k):
+    """The first row's differences change by a factor of a thousand at every step, so that its warm start always fails, into: Gaussian
+    ones; a crowd of different keys at the threshold (the exact algorithm); large entries on the sampled pieces (too few candidates: the
+    exact algorithm); equal magnitudes; zeros but for fewer than k entries.  The other rows stay as they are.  Messages bit for bit."""
+    torch, binding = gpu
+    print(f"collected again n={n} d={d} k={k}", flush=True)
+    rng = np.random.default_rng(d + k)
+    g_i = np.zeros((n, d), np.float32)
+
+    def crowd(size):
+        v = 0.1 * size * rng.standard_normal(d)
+        pos = rng.choice(d, size=min(d, k + 5000), replace=False)
+        bits = np.float32(size).view(np.uint32) + rng.permutation(pos.size).astype(np.uint32) % 2000
+        v[pos] = bits.view(np.float32) * np.where(rng.random(pos.size) < 0.5, 1, -1)
+        return v
+
+    def misleading(size):
+        v = 1e-3 * size * rng.standard_normal(d)
+        pos = sampled_positions(d)
+        v[pos] = size * (1.0 + rng.random(pos.size))
+        return v
+
+    def sparse(size):
+        v = np.zeros(d)
+        v[rng.choice(d, size=k // 2, replace=False)] = size
+        return v
+    normal = lambda size: size * rng.standard_normal(d)
+    equal = lambda size: np.where(rng.random(d) < 0.5, size, -size)
+    with binding.EF21(n, d, k, 0.25) as h:
+        h.set_state(torch.zeros(d, device="cuda"), to_gpu(torch, g_i))
+        for t, kind in enumerate((normal, normal, crowd, normal, misleading, equal, normal, sparse, normal, normal)):
+            diff = rng.standard_normal((n, d))
+            diff[0] = kind(1e3 if t % 2 else 1.0)
+            s = diff.astype(np.float32)              # the state is zero: the differences are these values
+            h.step(to_gpu(torch, s))
+            idx, val = (a.cpu().numpy() for a in h.get_messages())
+            state = h.get_state()[1].cpu().numpy()
+            for i in range(n):
+                ref_idx, ref_val = oracle.topk(s[i].astype(np.float64), k)
+                assert np.array_equal(idx[i], ref_idx), (t, i)
+                assert same_bits(val[i], ref_val.astype(np.float32)), (t, i)
+                kept = np.zeros(d, np.float32)
+                kept[ref_idx] = s[i][ref_idx]
+                assert np.array_equal(state[i], kept), (t, i)
+            h.set_state(None, to_gpu(torch, g_i))
