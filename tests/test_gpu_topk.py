@@ -65,6 +65,19 @@ def test_random_small_rows(gpu, oracle, d):
         check(gpu, oracle, V, k)
 
 
+@pytest.mark.parametrize("d", [3, 64, 65, 128, 129, 171, 205, 255, 256])
+def test_rows_ranked_whole(gpu, oracle, d):
+    """Rows of at most 256 entries, where the comparisons are shared among 1024 // d threads an entry: ties across the
+    threads' and the wavefronts' shares, infinities, and every fifth k."""
+    rng = np.random.default_rng(d)
+    V = rng.integers(-3, 4, size=(3, d)).astype(np.float32)
+    V[1] = rng.standard_normal(d).astype(np.float32)
+    V[1, rng.integers(0, d, size=d // 8 + 1)] = np.inf
+    V[2] = np.where(rng.random(d) < 0.5, -0.25, 0.25).astype(np.float32)
+    for k in sorted({1, 2, d - 1, d} | set(range(1, d, 5))):
+        check(gpu, oracle, V, k)
+
+
 @pytest.mark.parametrize("d", [200, 256, 257, 5000, 9000, 300_000])
 @pytest.mark.parametrize("crowd", [3, 255, 256, 257, 600])
 def test_threshold_inside_a_bin_of_near_equal_magnitudes(gpu, oracle, d, crowd):
