@@ -175,12 +175,16 @@ __device__ void short_row_topk(RowShared &s, const TopkArgs &p, int64_t row, Val
 // value(e) yields entry e of the row (the same bits every time it is asked); with kAddUpdate the emission
 // also applies line 6 of Algorithm 2, g_i[e] = base(e) + value(e), base(e) being the subtracted g_i[e], with
 // kClearUpdate it sets g_i[e] to zero (value(e) of that position is not asked for afterwards).
-template <int UPDATE, class ValueFn, class BaseFn>
+// SHORT: rows of at most kRankMax entries may come (code that the kernels of the long rows do without: with it their rescue was
+// no longer inlined, which put their arguments into scratch memory).
+template <int UPDATE, bool SHORT = true, class ValueFn, class BaseFn>
 __device__ void row_topk_on(RowShared &s, const TopkArgs &p, int64_t row, ValueFn value, BaseFn base_value) {
     const int64_t d = p.d;
-    if (d <= kRankMax) {
-        short_row_topk<UPDATE>(s, p, row, value, base_value);
-        return;
+    if constexpr (SHORT) {
+        if (d <= kRankMax) {
+            short_row_topk<UPDATE>(s, p, row, value, base_value);
+            return;
+        }
     }
 
     // ---- threshold key T and tie quota q ------------------------------------------------
@@ -275,12 +279,12 @@ __device__ void row_topk_on(RowShared &s, const TopkArgs &p, int64_t row, ValueF
     }
 }
 
-// The row read from global memory in every pass (any d).
+// The row read from global memory in every pass (any d; what calls it has rows of more than kRowCacheShort entries).
 template <bool DIFF, int UPDATE>
 __device__ void row_topk(RowShared &s, const TopkArgs &p, int64_t row) {
     const float *a = p.a + row * p.d;
     const float *b = DIFF ? p.b + row * p.d : nullptr;
-    row_topk_on<UPDATE>(
+    row_topk_on<UPDATE, false>(
         s, p, row, [=](int64_t e) { return load_v<DIFF>(a, b, e); }, [=](int64_t e) { return DIFF ? b[e] : 0.f; });
 }
 
