@@ -578,7 +578,7 @@ int ef21_set_state(ef21_handle h, const float *x, const float *g_i, const float 
     const size_t db = sizeof(float) * (size_t)d;
     const ef21::CopyList list{{x, g_i, g}, {h->x, h->g_i, h->g}, {x ? d : 0, g_i ? nd : 0, g ? d : 0}};
     const bool with_mean = g_i && !g;
-    if ((with_mean || ef21::copy_arrays_applies(list)) && copies_by_kernel(h, x, d) && copies_by_kernel(h, g_i, nd) &&
+    if ((with_mean ? ef21::mean_rows_copies(h->n, d) : ef21::copy_arrays_applies(list)) && copies_by_kernel(h, x, d) && copies_by_kernel(h, g_i, nd) &&
         copies_by_kernel(h, g, d)) {
         hipError_t st;
         if (with_mean) {

@@ -21,6 +21,7 @@ constexpr int64_t kMeanFewCols = 65536;
 // 282 and 270.
 constexpr int kCopyThreads = 512, kCopyBlocks = 256;
 constexpr int64_t kCopyStream = (int64_t)10 << 20;
+constexpr int64_t kMeanStream = (int64_t)64 << 20;   // entries of the 256 MB cache
 
 // x_j <- x_j - gamma g_j as one fused multiply-add per coordinate (a single rounding).
 __global__ __launch_bounds__(kThreads) void model_step_kernel(float *__restrict__ x, const float *__restrict__ g,
@@ -47,26 +48,27 @@ __global__ __launch_bounds__(kThreads) void model_step_vec4_kernel(float4 *__res
 }
 
 // The rows' mean, and on the way a copy of the rows (rows_out) and of one more vector (x_out <- x) for ef21_set_state, which
-// took a launch each and read the rows twice.  Per coordinate the workers in order, in fp64, rounded once.  Eight workers' loads
-// in flight where a thread has four columns, 32 where it has one: short rows have few threads, and there the waits for memory
+// took a launch each and read the rows twice.  Per coordinate the workers in order, in fp64, rounded once.  FLIGHT workers' loads
+// in flight: up to eight where a thread has four columns (with eight for two workers, six of them the second one's again, 2 x 28 million
+// took 269 us, see launch_mean_rows), 32 where it has one: short rows have few threads, and there the waits for memory
 // are all there is (20 x 123, the three things in 4 launches 9.4 us, in this one 3.3).  Rows may start at any 4-byte address.
 struct RowsOut {
     float *rows;                 // nullptr: the mean alone
     const float *x;              // with x_out, or nullptr
     float *x_out;
 };
-template <int VEC, bool COPY>
+enum RowsCopy { kNoCopy = 0, kCopy = 1, kCopyStreamed = 2 /* past the caches, see launch_mean_rows */ };
+template <int VEC, int COPY, int FLIGHT>
 __global__ __launch_bounds__(kThreads) void mean_rows_kernel(const float *__restrict__ g_i, float *__restrict__ g,
                                                              int32_t n, int64_t d, RowsOut out) {
     const int64_t stride = (int64_t)gridDim.x * kThreads * VEC;
-    constexpr int kInFlight = VEC == 4 ? 8 : 32;
     auto columns = [&](auto width, int64_t j) {
         constexpr int W = decltype(width)::value;
         double s[W] = {};
-        for (int32_t i0 = 0; i0 < n; i0 += kInFlight) {
-            float v[kInFlight][W];
+        for (int32_t i0 = 0; i0 < n; i0 += FLIGHT) {
+            float v[FLIGHT][W];
 #pragma unroll
-            for (int u = 0; u < kInFlight; ++u) {      // a worker past the end re-reads the last one, unused
+            for (int u = 0; u < FLIGHT; ++u) {      // a worker past the end re-reads the last one, unused
                 const float *at = g_i + (int64_t)(i0 + u < n ? i0 + u : n - 1) * d + j;
                 if constexpr (W == 4) {
                     const float4 t = stream_load4_any(at);
@@ -76,14 +78,15 @@ __global__ __launch_bounds__(kThreads) void mean_rows_kernel(const float *__rest
                 }
             }
 #pragma unroll
-            for (int u = 0; u < kInFlight; ++u) {
+            for (int u = 0; u < FLIGHT; ++u) {
                 if (i0 + u < n) {
 #pragma unroll
                     for (int t = 0; t < W; ++t) s[t] += (double)v[u][t];
-                    if constexpr (COPY) {
+                    if constexpr (COPY != kNoCopy) {
                         float *to = out.rows + (int64_t)(i0 + u) * d + j;
-                        if constexpr (W == 4) store4_any(to, make_float4(v[u][0], v[u][1], v[u][2], v[u][3]));
-                        else *to = v[u][0];
+                        if constexpr (W != 4) *to = v[u][0];
+                        else if constexpr (COPY == kCopyStreamed) stream_store4_any(to, make_float4(v[u][0], v[u][1], v[u][2], v[u][3]));
+                        else store4_any(to, make_float4(v[u][0], v[u][1], v[u][2], v[u][3]));
                     }
                 }
             }
@@ -91,7 +94,7 @@ __global__ __launch_bounds__(kThreads) void mean_rows_kernel(const float *__rest
 #pragma unroll
         for (int t = 0; t < W; ++t) {
             g[j + t] = (float)(s[t] / (double)n);
-            if (COPY && out.x_out) out.x_out[j + t] = out.x[j + t];
+            if (COPY != kNoCopy && out.x_out) out.x_out[j + t] = out.x[j + t];
         }
     };
     for (int64_t j = ((int64_t)blockIdx.x * kThreads + threadIdx.x) * VEC; j < d; j += stride) {
@@ -594,18 +597,33 @@ hipError_t launch_hbm_copy(void *dst, const void *src, int64_t n16, hipStream_t 
     return hipGetLastError();
 }
 
+// set_state and a step of one worker, us, by hipMemcpyAsync and a mean, and in one launch: d = 300 000 49 and 40, 2 million 58 and 53,
+// 20 million 232 and 235, 80 million 849 and 860.
+bool mean_rows_copies(int32_t n, int64_t d) { return n > 1 || d < kCopyStream; }
+
 hipError_t launch_mean_rows(const float *g_i, float *g, int32_t n, int64_t d, hipStream_t stream, float *rows_out,
                             const float *x, float *x_out) {
     const RowsOut out{rows_out, x, x_out};
-    // a column per thread as long as that leaves compute units idle
-#define EF21_MEAN(VEC, COPY)                                                                                            \
-    hipLaunchKernelGGL((mean_rows_kernel<VEC, COPY>), dim3(grid_for((d + VEC - 1) / VEC, 8192)), dim3(kThreads), 0, stream, \
+    // A column per thread as long as that leaves compute units idle.  Rows that the last cache cannot hold are copied past it: what it
+    // kept of them would have to be written back while the first step reads.  set_state and a step, us, kept and past the caches: 20 x
+    // 1.5 million 141 and 150; 8 x 5 million 172 and 180; 8 x 7 million 240 and 236; 2 x 28 million 394 and 378; 3 x 20 million 353 and 342;
+    // 8 x 11.2 million 413 and 374 (452 by hipMemcpyAsync and a mean).
+    const bool few = d <= kMeanFewCols, streamed = ((int64_t)n + 2) * d > kMeanStream;       // with x and g
+#define EF21_MEAN(VEC, COPY, FLIGHT)                                                                                    \
+    hipLaunchKernelGGL((mean_rows_kernel<VEC, COPY, FLIGHT>), dim3(grid_for((d + VEC - 1) / VEC, 8192)), dim3(kThreads), 0, stream, \
                        g_i, g, n, d, out)
-    const bool few = d <= kMeanFewCols;
-    if (rows_out && few) EF21_MEAN(1, true);
-    else if (rows_out) EF21_MEAN(4, true);
-    else if (few) EF21_MEAN(1, false);
-    else EF21_MEAN(4, false);
+#define EF21_MEAN4(COPY)                   \
+    do {                                   \
+        if (n <= 2) EF21_MEAN(4, COPY, 2); \
+        else if (n <= 4) EF21_MEAN(4, COPY, 4); \
+        else EF21_MEAN(4, COPY, 8);        \
+    } while (0)
+    if (rows_out && few) EF21_MEAN(1, kCopy, 32);
+    else if (rows_out && streamed) EF21_MEAN4(kCopyStreamed);
+    else if (rows_out) EF21_MEAN4(kCopy);
+    else if (few) EF21_MEAN(1, kNoCopy, 32);
+    else EF21_MEAN4(kNoCopy);
+#undef EF21_MEAN4
 #undef EF21_MEAN
     return hipGetLastError();
 }

@@ -803,10 +803,11 @@ def test_order_of_the_sum_of_messages(gpu, n, d, k):
 
 
 @pytest.mark.parametrize("n,d,offset", [(1, 1, 0), (4, 3, 1), (3, 1023, 0), (33, 1025, 3), (65, 257, 2), (2, 4096, 0), (7, 65537, 1),
-                                        (151, 70001, 0), (151, 70001, 1), (9, 65536, 1)])
+                                        (151, 70001, 0), (151, 70001, 1), (9, 65536, 1),
+                                        (2, 65539, 1), (3, 70001, 0), (1, 65537, 3), (2, 16_777_219, 1)])
 def test_state_in_and_out(gpu, n, d, offset):
     """set_state and get_state move every entry, from and to any 4-byte address, on both sides of the lengths from which the mean's
-    threads have four columns and the copies go past the caches; g is the fp64 mean in worker order, rounded once."""
+    threads have four columns (of two, four or eight workers at once) and the copies go past the caches; g is the fp64 mean in worker order, rounded once."""
     torch, binding = gpu
     rng = np.random.default_rng(n + d)
     sizes = {"x": d, "g_i": n * d, "g": d}
