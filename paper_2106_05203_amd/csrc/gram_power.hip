@@ -608,9 +608,14 @@ __global__ __launch_bounds__(kWave) void gram_tridiagonal_kernel(const double *_
 // ---- powers of G by squaring
 // M, in fp64 and symmetric, [n + 1][ld][ld], stands for its multiple with a trace in [1/2, 1): every kernel that reads it
 // multiplies by that power of two, which is exact.  Its trace is the sum of the first `parts` entries of traces[matrix].
+// Of that multiple the largest eigenvalue lies between 1 / (2 d) (all d alike: columns that are orthogonal and of one length) and 1, and
+// nothing rescales the vector, so its products are taken with `lift` times the multiple, the power of two next above sqrt(d): they grow or
+// shrink by at most 2^6 each.  There are sixty of them at most (a call that needs c applications beyond the squarings has c at most twice
+// the ratio of the two times, 40, and twenty bits), so that the squares of the entries stay within 2^(+-800).
 struct Power {
     const double *M, *traces;
     int32_t parts;
+    double lift;
 };
 // 2^-e, the trace being in [2^(e-1), 2^e); the same in all lanes
 __device__ __forceinline__ double unit_scale(double part_of_trace) {
@@ -645,7 +650,7 @@ __device__ __forceinline__ void power_rows(const Power &a, int64_t which, int64_
     for (int64_t j = tid; j < PAIRS * 2 * kWave; j += kMvThreads)
         vec[j] = j >= cols ? 0.0 : y ? y[which * ld + j] : j < d ? (double)power_start_entry(which, j, rsqrtf((float)d)) : 0.0;
     __syncthreads();
-    const double scale = unit_scale(part);
+    const double scale = a.lift * unit_scale(part);
 #pragma unroll
     for (int i0 = 0; i0 < kMvRowsPerWave; i0 += TOGETHER) {
         if (i0 > 0) load(i0);
@@ -815,7 +820,7 @@ __global__ __launch_bounds__(kMvThreads) void gram_apply_kernel(Power a, int64_t
     power_rows(a, blockIdx.y, (int64_t)blockIdx.x * kMvRows, d, cols, ld, y, z, vec);
 }
 
-// stats[row] = (0, |z| / |y|), z the product of y and G scaled as above.
+// stats[row] = (0, |z| / |y|), z the product of y and G scaled and lifted as above.
 __global__ __launch_bounds__(kMvThreads) void gram_ratio_kernel(Power a, const double *__restrict__ y, const double *__restrict__ z,
                                                                 int64_t ld, double2 *__restrict__ stats) {
     __shared__ double sums[2][kMvWaves];
@@ -840,7 +845,7 @@ __global__ __launch_bounds__(kMvThreads) void gram_ratio_kernel(Power a, const d
         sums[0][threadIdx.x / kWave] = sy;
         sums[1][threadIdx.x / kWave] = sz;
     }
-    const double scale = unit_scale(part);
+    const double scale = a.lift * unit_scale(part);
     __syncthreads();
     if (threadIdx.x > 0) return;
     sy = (sums[0][0] + sums[0][1]) + (sums[0][2] + sums[0][3]);
@@ -970,7 +975,8 @@ hipError_t launch_gram_power(const float *A, int32_t n, int64_t m, int64_t d, in
     if (way >= 0) {
         hipLaunchKernelGGL(gram_finish_kernel<double>, finish_grid, dim3(kTileThreads), 0, stream, ws.part, p.chunks, p.pairs,
                            d, p.ld, (double)m, ws.power[0], ws.traces[0]);
-        const Power G{ws.power[0], ws.traces[0], (int32_t)p.nb};
+        const double lift = std::exp2(std::ceil(0.5 * std::log2((double)d)));
+        const Power G{ws.power[0], ws.traces[0], (int32_t)p.nb, lift};
         Power now = G;
         const double *y = nullptr;                   // the start vector
         double *z = ws.v, *other = ws.w;
@@ -987,7 +993,7 @@ hipError_t launch_gram_power(const float *A, int32_t n, int64_t m, int64_t d, in
             hipLaunchKernelGGL(gram_square_kernel, dim3((unsigned)grid), dim3(kTileThreads), 0, stream, now, d, p.ld, (int32_t)groups,
                                (int32_t)strips, n + 1, ws.power[to], ws.traces[to], y, z);
             if (apply) applied();
-            now = Power{ws.power[to], ws.traces[to], (int32_t)((groups + 1) / 2)};
+            now = Power{ws.power[to], ws.traces[to], (int32_t)((groups + 1) / 2), lift};
         }
         const dim3 apply_grid((unsigned)row_blocks, (unsigned)(n + 1));
         for (int32_t i = 0; i < rest >> way; ++i) {

@@ -340,3 +340,23 @@ def test_powers_by_squaring_give_the_power_iterations_value(gpu, n, d, m):
             got = 4.0 * np.array(list(L_i) + [L])
             # the product with a rank-one dominated matrix settles within a few steps: 200 stand for more
             np.testing.assert_allclose(got, power_values(A, min(steps, 200)), rtol=1e-6, err_msg=f"{steps} iterations")
+
+
+# what the vector can come to when it is multiplied some fifty times by a power that is scaled by its trace: d times smaller at each product where all
+# eigenvalues are alike, and as large as it was where there is one
+@pytest.mark.parametrize("n,iterations", [(20, 573440), (40, 606208)])
+def test_flat_spectrum_and_one_eigenvalue_under_many_products(gpu, n, iterations):
+    torch, binding = gpu
+    print(f"many products n={n} iterations={iterations}", flush=True)
+    d = m = 1024
+    y = torch.zeros((n, m), device="cuda")
+    with binding.EF21(n, d, 1, 0.1) as h:
+        A = 32.0 * torch.eye(d, device="cuda").expand(n, m, d).contiguous()         # G = I, and powers of two all the way
+        h.set_problem_dense(A, y, 0.0)
+        gamma, L, L_i = h.theory_stepsize(iterations)
+        np.testing.assert_allclose(list(L_i) + [L], 0.25, rtol=1e-13)
+        assert np.isfinite(gamma)
+        A.fill_(0.999)                                                              # rank one, its eigenvalue just below 1024
+        _, L, L_i = h.theory_stepsize(iterations)
+        # fp32 entries of G
+        np.testing.assert_allclose(list(L_i) + [L], 0.25 * d * float(np.float32(0.999)) ** 2, rtol=2.0 ** -23)
