@@ -13,7 +13,7 @@
 //
 // Nobody waits: a workgroup that is not the last to draw its ticket simply ends, so the kernel cannot hang.
 // The tickets are device-scope atomics between device-scope fences (release before the ticket, acquire after
-// it), which is what makes one workgroup's stores visible to another on a different compute die.
+// it), which is what makes one workgroup's stores visible to another on a different compute die (draw_ticket).
 #include "device_utils.h"
 #include "kernels.h"
 #include "logreg_dense_block.h"
@@ -50,23 +50,6 @@ struct SmallArgs {
     const int32_t *batch;     // solo_kernel: Algorithm 5 (m rows of m_full each)
     int64_t m_full, x_stride;
 };
-
-// All threads of the workgroup call.  Publishes what the workgroup has stored, draws a ticket of `counter`, and
-// returns true in the workgroup that drew the last of `tickets` (it may then read what the others published).
-// One thread fences for the workgroup: the barriers order the other threads' accesses against its fences (the
-// release and acquire are cumulative), and the device-scope fences write back and invalidate caches that the
-// whole workgroup shares, so one of each is enough and sixteen wavefronts' worth would only queue up.
-__device__ __forceinline__ bool draw_ticket(uint32_t *counter, uint32_t tickets, uint32_t *flag) {
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        __threadfence();                                     // release
-        const uint32_t drawn = atomicAdd(counter, 1u);
-        __threadfence();                                     // acquire
-        *flag = drawn == tickets - 1u ? 1u : 0u;
-    }
-    __syncthreads();
-    return *flag != 0u;
-}
 
 // Line 8, then line 3, by the workgroup that drew the last ticket of all: the messages staged in LDS, ONE wavefront adds them
 // worker by worker (positions inside a message are distinct, a wavefront's LDS accesses execute in program order).

@@ -862,17 +862,8 @@ __device__ __forceinline__ void count_rows(const TopkArgs &p, const Ws &w, Count
     if (failed && ri.warm_used) {
         __syncthreads();                         // lds_out has been read
         collect_rows<DIFF, kSecondPass, DIFF && SUMS, kNoAdd>(p, w, rs, rings);
-        __syncthreads();                         // all of this workgroup's candidates and counts are stored
-        if (tid == 0) {                          // one thread releases and acquires for its workgroup
-            __threadfence();
-            sh.last = atomicAdd(&info->arrived, 1u) + 1u == gridDim.x ? 1u : 0u;
-            if (sh.last) {
-                __threadfence();
-                info->arrived = 0u;
-            }
-        }
-        __syncthreads();
-        if (!sh.last) return;
+        if (!draw_ticket(&info->arrived, gridDim.x, &sh.last)) return;
+        if (tid == 0) info->arrived = 0u;
         key_lo = info->key_lo2;
         shift = info->shift2;
 #pragma unroll
