@@ -50,8 +50,9 @@ __global__ __launch_bounds__(kThreads) void model_step_vec4_kernel(float4 *__res
 // The rows' mean, and on the way a copy of the rows (rows_out) and of one more vector (x_out <- x) for ef21_set_state, which
 // took a launch each and read the rows twice.  Per coordinate the workers in order, in fp64, rounded once.  FLIGHT workers' loads
 // in flight: up to eight where a thread has four columns (with eight for two workers, six of them the second one's again, 2 x 28 million
-// took 269 us, see launch_mean_rows), 32 where it has one: short rows have few threads, and there the waits for memory
-// are all there is (20 x 123, the three things in 4 launches 9.4 us, in this one 3.3).  Rows may start at any 4-byte address.
+// took 269 us, see launch_mean_rows), up to 32 where it has one: short rows have few threads, and there the waits for memory
+// are all there is (20 x 123, the three things in 4 launches 9.4 us, in this one 3.0; with 32 for any number of workers, the last one's read again,
+// 2 x 2000 took 2.9 against 2.0 and the mean alone 0.9 more than the kernel before).  Rows may start at any 4-byte address.
 struct RowsOut {
     float *rows;                 // nullptr: the mean alone
     const float *x;              // with x_out, or nullptr
@@ -618,11 +619,20 @@ hipError_t launch_mean_rows(const float *g_i, float *g, int32_t n, int64_t d, hi
         else if (n <= 4) EF21_MEAN(4, COPY, 4); \
         else EF21_MEAN(4, COPY, 8);        \
     } while (0)
-    if (rows_out && few) EF21_MEAN(1, kCopy, 32);
+#define EF21_MEAN1(COPY) \
+    do { \
+        if (n <= 2) EF21_MEAN(1, COPY, 2); \
+        else if (n <= 4) EF21_MEAN(1, COPY, 4); \
+        else if (n <= 8) EF21_MEAN(1, COPY, 8); \
+        else if (n <= 16) EF21_MEAN(1, COPY, 16); \
+        else EF21_MEAN(1, COPY, 32); \
+    } while (0)
+    if (rows_out && few) EF21_MEAN1(kCopy);
     else if (rows_out && streamed) EF21_MEAN4(kCopyStreamed);
     else if (rows_out) EF21_MEAN4(kCopy);
-    else if (few) EF21_MEAN(1, kNoCopy, 32);
+    else if (few) EF21_MEAN1(kNoCopy);
     else EF21_MEAN4(kNoCopy);
+#undef EF21_MEAN1
 #undef EF21_MEAN4
 #undef EF21_MEAN
     return hipGetLastError();

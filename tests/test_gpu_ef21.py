@@ -893,3 +893,52 @@ def test_rows_collected_again(gpu, oracle, n, d, k):
                 kept[ref_idx] = s[i][ref_idx]
                 assert np.array_equal(state[i], kept), (t, i)
             h.set_state(None, to_gpu(torch, g_i))
+
+
+@pytest.mark.parametrize("n", [1, 2, 3, 4, 5, 8, 9, 16, 17, 33])
+def test_mean_of_short_rows_at_each_number_of_loads(gpu, n):
+    """set_state where a thread has one column: two, four, eight, sixteen or thirty-two workers' loads at once, g and the copy."""
+    torch, binding = gpu
+    d = 131
+    rng = np.random.default_rng(n)
+    rows = rng.standard_normal((n, d)).astype(np.float32)
+    mean = np.zeros(d)
+    for row in rows:
+        mean += row
+    with binding.EF21(n, d, 1, 0.5) as h:
+        h.set_state(torch.zeros(d, device="cuda"), to_gpu(torch, rows))
+        x, g_i, g = (a.cpu().numpy() for a in h.get_state())
+        assert same_bits(g_i, rows) and not x.any()
+        assert same_bits(g, (mean / n).astype(np.float32))
+        h.set_state(torch.ones(d, device="cuda"))       # the mean alone, of the rows that are there
+        assert same_bits(h.get_state()[2].cpu().numpy(), (mean / n).astype(np.float32))
+
+
+def test_mean_of_few_rows_reads_each_once(gpu):
+    """A thread with 32 loads in flight for two rows reads the second one 31 times: as long as for 20 rows (4.4 us with the copy of x, d = 2000).
+    With as many as there are rows 3.5 and 4.5."""
+    torch, binding = gpu
+    times = {}
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        for n in (2, 20):
+            with binding.EF21(n, 2000, 1, 0.1) as h:
+                x = torch.rand(2000, device="cuda")
+                h.set_state(x)
+                side.synchronize()
+                graph = torch.cuda.CUDAGraph()
+                with torch.cuda.graph(graph, stream=side):
+                    for _ in range(40):
+                        h.set_state(x)
+                best = np.inf
+                for _ in range(10):
+                    start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+                    start.record()
+                    graph.replay()
+                    graph.replay()
+                    end.record()
+                    end.synchronize()
+                    best = min(best, start.elapsed_time(end) * 1000 / 80)
+                times[n] = best
+    print(times, flush=True)
+    assert times[2] <= 0.9 * times[20], times
