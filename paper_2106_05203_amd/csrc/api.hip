@@ -7,6 +7,7 @@
 #include <vector>
 
 #include "../../include/ef21.h"
+#include "gram_way.h"
 #include "kernels.h"
 
 // Workspace of ef21_topk_static: device memory that exists from the moment the library is loaded, so that call
@@ -650,10 +651,12 @@ static int enqueue_gram_product(ef21_ctx *c, const float *v, int64_t v_stride, f
 
 // Whether the power iteration runs on Gram matrices; the handle's workspace for them is then large enough.  It is
 // grown on demand; where there is no memory for it the iteration runs with A.
-static bool use_gram(ef21_ctx *c, int32_t iterations) {
+static bool use_gram(ef21_ctx *c, int32_t iterations, int32_t *squarings) {
     if (c->kind != kDense) return false;
-    const size_t bytes = ef21::gram_power_bytes(c->n, c->m, c->d, iterations);
+    const ef21::GramWay way = ef21::gram_way(c->n, c->m, c->d, iterations);
+    const size_t bytes = way.bytes;
     if (bytes == 0) return false;
+    *squarings = way.squarings;
     if (bytes <= c->gram_bytes) return true;
     (void)hipStreamSynchronize(c->stream);           // an error shows again at the call's own wait
     (void)hipFree(c->gram_ws);
@@ -674,7 +677,8 @@ int ef21_theory_stepsize(ef21_handle h, int32_t iterations, double *gamma, doubl
     if (iterations < 1 || iterations > 1000000) return fail(EF21_EINVAL, "iterations must be in [1, 10^6]");
     const int32_t n = h->n;
     const int64_t d = h->d;
-    const bool gram = use_gram(h, iterations);
+    int32_t squarings = -1;
+    const bool gram = use_gram(h, iterations, &squarings);
     // rows 0..n-1: the workers' vectors; row n: the vector of the whole problem; row n+1: its product
     if ((!h->power_stats && hipMalloc((void **)&h->power_stats, sizeof(double) * 2 * (size_t)(n + 1)) != hipSuccess) ||
         (!gram && !h->power_v && hipMalloc((void **)&h->power_v, sizeof(float) * (size_t)(n + 2) * (size_t)d) != hipSuccess)) {
@@ -685,7 +689,7 @@ int ef21_theory_stepsize(ef21_handle h, int32_t iterations, double *gamma, doubl
     double *stats = h->power_stats;
     float *v_all = gram ? nullptr : v + (size_t)n * d, *w_all = gram ? nullptr : v_all + d;
     int rc = EF21_OK;
-    hipError_t st = gram ? ef21::launch_gram_power(h->A, n, h->m, d, iterations, h->gram_ws, stats, h->stream)
+    hipError_t st = gram ? ef21::launch_gram_power(h->A, n, h->m, d, iterations, squarings, h->gram_ws, stats, h->stream)
                          : ef21::launch_power_start(v, n + 1, d, h->stream);
     for (int32_t it = 0; !gram && it < iterations && st == hipSuccess && rc == EF21_OK; ++it) {
         rc = enqueue_gram_product(h, v, d, h->grad);                         // w_i = (1/m) A_i^T A_i v_i

@@ -37,6 +37,7 @@
 #include <utility>
 
 #include "device_utils.h"
+#include "gram_way.h"
 #include "kernels.h"
 
 namespace ef21 {
@@ -44,63 +45,16 @@ namespace {
 
 typedef double v4d __attribute__((ext_vector_type(4)));
 
-constexpr int kTile = 32;                            // rows and columns of a tile of G
 constexpr int kTileThreads = 256, kTileWaves = kTileThreads / kWave;
-constexpr int kTileEntries = kTile * kTile;
 constexpr int kStepRows = 4;                         // rows of A per matrix instruction
-constexpr int64_t kXcds = 8;                         // workgroups go round them one by one
 constexpr int kAhead = 4;                            // instructions' rows whose loads are in flight
 
 constexpr int kResThreads = 1024, kResWaves = kResThreads / kWave;
-constexpr int64_t kResidentMax = 5 * kWave;          // columns (six would need 144 registers for G alone)
-constexpr int64_t kGramMax = 1024;
 constexpr int32_t kItersPerLaunch = 4096;            // of the resident kernel: bounds a launch to some ten milliseconds
-
-constexpr int kLanczosMax = 256;                     // steps of the recurrence: four per lane of the last wavefront
-// Fewer iterations save next to nothing and a step takes longer than an iteration, us a call with the iteration and with the
-// recurrence, 40 iterations (32 steps): n = 20, m = 1000, d = 64 71.3 and 72.7; 4, 250, 100 76.6 and 75.1; 16, 2000, 200 166.3
-// and 166.4; 10, 3000, 500 520 and 455; 100 iterations (49 steps): 109 and 89, 131 and 96, 266 and 205, 960 and 580.
-constexpr int32_t kLanczosLeast = 48;
-// Steps that stand for `iterations` of the power iteration; 0: it is run as it is.
-int32_t lanczos_steps(int32_t iterations) {
-    if (iterations < kLanczosLeast) return 0;
-    const int32_t steps = (int32_t)std::ceil(4.8 * std::sqrt((double)iterations)) + 1;
-    return steps <= kLanczosMax ? steps : 0;
-}
 
 constexpr int kMvThreads = 256, kMvWaves = kMvThreads / kWave, kMvRowsPerWave = 8;
 constexpr int kMvRows = kMvWaves * kMvRowsPerWave;
 static_assert(kMvRows == kTile, "G is padded to whole tiles, so a workgroup's rows all exist");
-
-struct GramPlan {
-    int64_t nb, pairs;              // tiles per side, tiles on and above the diagonal
-    int64_t ld;                     // rows and row length of a padded G
-    int64_t rows_per_chunk, chunks;
-};
-
-// Enough workgroups to fill the chip four deep, at least 256 rows (16 matrix instructions per wavefront and
-// accumulator) each; up to three chunks more where that spreads the (worker, chunk) units evenly over the XCDs.
-GramPlan gram_plan(int32_t n, int64_t m, int64_t d) {
-    GramPlan p;
-    p.nb = (d + kTile - 1) / kTile;
-    p.pairs = p.nb * (p.nb + 1) / 2;
-    p.ld = p.nb * kTile;
-    int64_t chunks = 1024 / (n * p.pairs);
-    if (chunks > m / 256) chunks = m / 256;
-    if (chunks < 1) chunks = 1;
-    const int64_t least = chunks;
-    int64_t best = kXcds;
-    for (int64_t c = least; c < least + 4 && (c == least || c <= m / 256); ++c) {
-        const int64_t idle = (kXcds - n * c % kXcds) % kXcds;
-        if (idle < best) {
-            best = idle;
-            chunks = c;
-        }
-    }
-    p.rows_per_chunk = (m + chunks - 1) / chunks;
-    p.chunks = (m + p.rows_per_chunk - 1) / p.rows_per_chunk;
-    return p;
-}
 
 // tile number -> (I, J), I <= J: J (J + 1) / 2 + I
 __device__ __forceinline__ void tile_of(int32_t pair, int32_t *I, int32_t *J) {
@@ -198,7 +152,6 @@ __global__ __launch_bounds__(kTileThreads) void gram_tile_kernel(const float *__
 
 // Matrix `which` of n + 1 (the last one: the mean over the workers): the partial sums in order, scaled, rounded to fp32 once.
 // Where the entries are kept in fp64 the tiles on the diagonal leave their sum of diagonal entries in traces[matrix][tile].
-constexpr int kTraces = kWave;
 template <class T>
 __global__ __launch_bounds__(kTileThreads) void gram_finish_kernel(const double *__restrict__ part, int64_t chunks,
                                                                    int64_t pairs, int64_t d, int64_t ld, double m,
@@ -670,21 +623,15 @@ __device__ __forceinline__ void power_rows(const Power &a, int64_t which, int64_
 }
 __device__ __forceinline__ void power_rows(const Power &a, int64_t which, int64_t r0, int64_t d, int64_t cols, int64_t ld,
                                            const double *__restrict__ y, double *__restrict__ z, double *vec) {
-    if (cols <= 2 * kWave) power_rows<1, 8>(a, which, r0, d, cols, ld, y, z, vec);
-    else if (cols <= 6 * kWave) power_rows<3, 8>(a, which, r0, d, cols, ld, y, z, vec);
+    static_assert(kSquareLeast > 2 * kWave, "fewer columns are not squared");
+    if (cols <= 6 * kWave) power_rows<3, 8>(a, which, r0, d, cols, ld, y, z, vec);
     else power_rows<8, 4>(a, which, r0, d, cols, ld, y, z, vec);
 }
 
 // A square in blocks of 16 x 16 on and above the diagonal, which go in strips: the groups of columns 2 p and 2 p + 1 against four groups
 // from 2 p + 4 q on (fewer at the end; the block below the diagonal in the first strip of a row is left out).
-constexpr int kGroup = 16, kBlock = kGroup * kGroup, kWide = 4, kTurns = 4;
+constexpr int kBlock = kGroup * kGroup, kTurns = 4;
 static_assert(kBlock == kTileThreads, "an entry per thread");
-int64_t strip_count(int64_t groups) {
-    int64_t strips = 0;
-    for (int64_t p = 0; 2 * p < groups; ++p) strips += (groups - 2 * p + kWide - 1) / kWide;
-    return strips;
-}
-
 // v_mfma_f64_4x4x4 forms four 4 x 4 products side by side: lane l gives row l / 16 of four and column l % 16 of a
 // group, and quad b of the columns of the one operand meets quad b of the other.  So the one is also taken turned by one, two and three
 // quads, and sum r of lane l is entry (4 ((l / 4 + r) % 4) + l % 4, 4 (l / 4 % 4) + l / 16) of the 16 x 16 product.  v_mfma_f64_16x16x4
@@ -854,43 +801,6 @@ __global__ __launch_bounds__(kMvThreads) void gram_ratio_kernel(Power a, const d
     stats[which] = make_double2(0.0, sqrt(sz) * inverse_norm(sy) / scale);
 }
 
-struct GramWs {
-    double *part;                   // [n][chunks][pairs][32][32]
-    float *G;                       // [n + 1][ld][ld]
-    double *v, *w;                  // [n + 1][ld] each
-    double *lanczos;                // three more vectors of that size, and alpha and beta [n + 1][kLanczosMax]
-    double *power[3];               // by squaring: G, and two matrices in turn, the first of them in part's place
-    double *traces[3];              // [n + 1][kTraces] each
-};
-
-size_t gram_layout(int32_t n, const GramPlan &p, bool squaring, char *base, GramWs *ws) {
-    size_t off = 0;
-    // at whole 4096 bytes: the matrices' rows of d = 1000 otherwise straddle two channels' shares of memory (a product 13.4 us instead of 8.6)
-    auto take = [&](size_t bytes) {
-        char *at = base ? base + off : nullptr;
-        off += (bytes + 4095) / 4096 * 4096;
-        return at;
-    };
-    const size_t entries = (size_t)(n + 1) * p.ld * p.ld, part = sizeof(double) * (size_t)n * p.chunks * p.pairs * kTileEntries;
-    GramWs out{};
-    out.part = (double *)take(squaring ? std::max(part, sizeof(double) * entries) : part);
-    if (squaring) {
-        out.power[0] = (double *)take(sizeof(double) * entries);
-        out.power[1] = out.part;
-        out.power[2] = (double *)take(sizeof(double) * entries);
-        for (auto &t : out.traces) t = (double *)take(sizeof(double) * (size_t)(n + 1) * kTraces);
-    } else {
-        out.G = (float *)take(sizeof(float) * entries);
-        out.lanczos = (double *)take(sizeof(double) * (size_t)(n + 1) * (3 * p.ld + 2 * kLanczosMax));
-    }
-    out.v = (double *)take(sizeof(double) * (size_t)(n + 1) * p.ld);
-    out.w = (double *)take(sizeof(double) * (size_t)(n + 1) * p.ld);
-    if (ws) *ws = out;
-    return off;
-}
-
-constexpr size_t kGramWsMax = (size_t)1 << 30;
-
 template <int NC>
 void launch_resident(const GramWs &ws, int32_t n, int64_t d, int64_t ld, int32_t iterations, double *stats, hipStream_t stream) {
     if (const int32_t steps = lanczos_steps(iterations)) {
@@ -907,72 +817,17 @@ void launch_resident(const GramWs &ws, int32_t n, int64_t d, int64_t ld, int32_t
 
 }  // namespace
 
-namespace {
-// Squarings after which the rest of the iterations is taken with the power reached: G^(2^s) applied (iterations - 1) >> s times, the other
-// bits' powers beside the squarings.  us: of it all.  Measured, us, a squaring and a product with a power: n = 4, d = 100 6.1 and 2.4; 20, 300
-// 24.5 and 4.8; 32, 330 39.5 and 5.5; 2, 1000 79 and 5.8; 15, 1000 320 and 21.
-int32_t squarings(int32_t n, const GramPlan &p, int32_t iterations, double *us) {
-    const double groups = (double)(p.ld / kGroup), square = 8.0 + 8.6e-5 * (n + 1.0) * groups * groups * groups;
-    const double apply = 4.0 + 1.1e-6 * (double)(n + 1) * (double)p.ld * (double)p.ld;
-    int32_t least = 0;
-    *us = 1e30;
-    for (int32_t s = 0; s <= 20; ++s) {
-        const double with = s * square + (double)(((iterations - 1) >> s) + 2) * apply;
-        if (with < *us) {
-            *us = with;
-            least = s;
-        }
-    }
-    return least;
-}
-// How launch_gram_power goes about it: so many squarings, or -1 for the iteration or recurrence with G in fp32.  A call of 100 iterations,
-// us, by the recurrence and by squaring: n = 16, m = 2000, d = 200 204 and 179; 25, 800, 250 204 and 212; 20, 2487, 300 317 and 289; 32, 1400, 330
-// 563 and 373; 10, 3000, 500 581 and 419; 3, 2000, 700 528 and 325; 2, 7500, 1000 796 and 656; 15, 1000, 1000 1154 and 1560; 1000 iterations of
-// 20, 2487, 300 660 and 363; 20 of them 225 and 236.  Up to 128 columns the host's dozen launches are what counts: 4, 250, 100 95 and 101.
-int32_t power_way(int32_t n, const GramPlan &p, int64_t d, int32_t iterations, double *us) {
-    const int32_t lanczos = lanczos_steps(iterations);
-    const double matrices = (n + 1.0) * (double)p.ld * (double)p.ld * 0.92e-6;                     // read in every iteration
-    const double wide = (double)((d + kWave - 1) / kWave), resident = (0.9 + 0.095 * wide * wide) * (double)((n + 256) / 256);
-    const double step = d <= kResidentMax ? resident : (matrices > 8.5 ? matrices : 8.5);
-    const double plain = (lanczos ? lanczos : iterations) * step;
-    const int32_t s = squarings(n, p, iterations, us);
-    if (d > 2 * kWave && iterations > 1 && *us < 0.95 * plain && gram_layout(n, p, true, nullptr, nullptr) <= kGramWsMax) return s;
-    *us = plain;
-    return -1;
-}
-}  // namespace
-
-size_t gram_power_bytes(int32_t n, int64_t m, int64_t d, int32_t iterations) {
-    if (d > kGramMax || n > 65534) return 0;
-    const GramPlan p = gram_plan(n, m, d);
-    double with_g;
-    const int32_t way = power_way(n, p, d, iterations, &with_g);
-    const size_t bytes = gram_layout(n, p, way >= 0, nullptr, nullptr);
-    if (bytes > kGramWsMax) return 0;
-    // Microseconds, a handle's first call: forming the matrices (with the allocation of their workspace) and one iteration
-    // on them (or one step of the recurrence), against one iteration with A (six launches).  Measured, forming | iteration on G | with A: n = 4, m = 250,
-    // d = 100 1 | 0.9 | 22; 20, 2487, 300 172 | 2.5 | 44; 10, 3000, 500 223 | 7.3 | 40; 2, 7500, 1000 354 | 8.7 | 50;
-    // 15, 1000, 1000 424 | 15 | 41; 32, 468, 1000 482 | 32 | 40; 32, 100, 1000 253 | 32 | 30; 1000, 20, 100 286 | 2.4 | 137.
-    const double nn = n, mm = (double)m, dd = (double)d, ld = (double)p.ld, rows = nn * mm;
-    const double form = 10.0 + 0.055 * dd + rows * ld * ld / 55e6 + 0.3e-6 * (double)bytes;
-    const double sums = 512.0 / nn < mm / 8.0 ? 512.0 / nn : mm / 8.0;           // of the gradient, per worker
-    const double with_a = 22.0 + 1.1e-6 * rows * dd + 0.08 * nn + 3.5e-5 * sums * dd;
-    return form + with_g < iterations * with_a ? bytes : 0;
-}
-
-hipError_t launch_gram_power(const float *A, int32_t n, int64_t m, int64_t d, int32_t iterations, void *workspace,
+hipError_t launch_gram_power(const float *A, int32_t n, int64_t m, int64_t d, int32_t iterations, int32_t squarings, void *workspace,
                              double *stats, hipStream_t stream) {
     const GramPlan p = gram_plan(n, m, d);
-    if (d > kGramMax || p.chunks > 65535 || n > 65534) return hipErrorInvalidValue;
-    double us;
-    const int32_t way = power_way(n, p, d, iterations, &us);
+    if (d > kGramMax || p.chunks > 65535 || n > 65534 || (squarings >= 0 && d < kSquareLeast)) return hipErrorInvalidValue;
     GramWs ws;
-    gram_layout(n, p, way >= 0, (char *)workspace, &ws);
+    gram_layout(n, p, squarings >= 0, (char *)workspace, &ws);
     const int64_t units = n * p.chunks;
     hipLaunchKernelGGL(gram_tile_kernel, dim3((unsigned)((units + kXcds - 1) / kXcds * kXcds * p.pairs)), dim3(kTileThreads),
                        0, stream, A, m, d, p.rows_per_chunk, p.chunks, units, p.pairs, ws.part);
     const dim3 finish_grid((unsigned)p.pairs, (unsigned)(n + 1));
-    if (way >= 0) {
+    if (squarings >= 0) {
         hipLaunchKernelGGL(gram_finish_kernel<double>, finish_grid, dim3(kTileThreads), 0, stream, ws.part, p.chunks, p.pairs,
                            d, p.ld, (double)m, ws.power[0], ws.traces[0]);
         const double lift = std::exp2(std::ceil(0.5 * std::log2((double)d)));
@@ -986,7 +841,7 @@ hipError_t launch_gram_power(const float *A, int32_t n, int64_t m, int64_t d, in
         };
         const int64_t groups = (d + kGroup - 1) / kGroup, strips = strip_count(groups), row_blocks = p.ld / kMvRows;
         const int32_t rest = iterations - 1;
-        for (int32_t j = 0; j < way; ++j) {
+        for (int32_t j = 0; j < squarings; ++j) {
             const int to = 1 + j % 2;
             const bool apply = (rest >> j) & 1;
             const int64_t grid = ((n + 1) * strips + kXcds - 1) / kXcds * kXcds + (apply ? (n + 1) * row_blocks : 0);
@@ -996,7 +851,7 @@ hipError_t launch_gram_power(const float *A, int32_t n, int64_t m, int64_t d, in
             now = Power{ws.power[to], ws.traces[to], (int32_t)((groups + 1) / 2), lift};
         }
         const dim3 apply_grid((unsigned)row_blocks, (unsigned)(n + 1));
-        for (int32_t i = 0; i < rest >> way; ++i) {
+        for (int32_t i = 0; i < rest >> squarings; ++i) {
             hipLaunchKernelGGL(gram_apply_kernel, apply_grid, dim3(kMvThreads), 0, stream, now, d, groups * kGroup, p.ld, y, z);
             applied();
         }

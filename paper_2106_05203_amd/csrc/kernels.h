@@ -270,11 +270,9 @@ hipError_t launch_plus_long(const PlusLong &pl, PlusLongArgs a, double *BM, floa
 hipError_t launch_power_start(float *v, int32_t rows, int64_t d, hipStream_t stream);
 hipError_t launch_power_step(const float *w, float *v, int32_t rows, int64_t d, double *stats, hipStream_t stream);
 
-// The same on the Gram matrices of a dense problem (d <= 1024): gram_power_bytes says how much workspace `iterations`
-// steps take this way, or 0 where iterating with A is the faster one or the matrices would take more than a gigabyte.
+// The same on the Gram matrices of a dense problem (d <= 1024), a workspace of gram_way's bytes and its squarings (gram_way.h).
 // stats [n + 1] pairs as above, the last one of the whole problem; the first number of a pair is not formed (0).
-size_t gram_power_bytes(int32_t n, int64_t m, int64_t d, int32_t iterations);
-hipError_t launch_gram_power(const float *A, int32_t n, int64_t m, int64_t d, int32_t iterations, void *workspace,
+hipError_t launch_gram_power(const float *A, int32_t n, int64_t m, int64_t d, int32_t iterations, int32_t squarings, void *workspace,
                              double *stats, hipStream_t stream);
 
 // Algorithm 4 (EF): e <- e + gamma s over all n * d entries.
