@@ -151,8 +151,9 @@ def power_values(A, steps):
     return np.array(out)
 
 
-# both forms of the iteration on Gram matrices (one launch, up to 320 columns; a launch per step, up to 1024) at the
-# ends of their tiles, one row, ragged chunks of rows, several chunks, and the first size past them
+# the iteration on Gram matrices (one launch, up to 320 columns; a launch per step, up to 1024; products with a power) at the
+# ends of its tiles, one row, ragged chunks of rows, several chunks, and the first size past them.  Which way a call goes
+# is gram_way's matter (csrc/gram_way.h): REACHED below has shapes for each of them, which tests/test_stepsize_ways.py holds to it
 @pytest.mark.parametrize("n,d,m", [(1, 1, 1), (2, 31, 7), (3, 32, 300), (1, 33, 1), (2, 64, 1025), (2, 65, 515),
                                    (2, 129, 33), (5, 192, 64), (2, 193, 2), (3, 256, 770), (2, 257, 9), (2, 319, 40),
                                    (3, 320, 64), (2, 321, 31), (2, 352, 700), (1, 1023, 17), (2, 1024, 260), (1, 1025, 16)])
@@ -179,8 +180,8 @@ def test_power_iteration_value(gpu, n, d, m):
         assert L == 0.0 and not np.any(L_i)
 
 
-# more iterations than one launch of the resident kernel runs (4096): it goes on from the vectors the launch before left.
-# Two close eigenvalues, so that the last thousand iterations still move the value
+# more iterations than one launch of the resident kernel runs (4096): it goes on from the vectors the launch before left (up to 128
+# columns; 300 are squared, and see REACHED).  Two close eigenvalues, so that the last thousand iterations still move the value
 @pytest.mark.parametrize("d", [40, 300])
 def test_power_iteration_goes_on_over_launches(gpu, d):
     torch, binding = gpu
@@ -202,8 +203,8 @@ def test_power_iteration_goes_on_over_launches(gpu, d):
 
 
 # the first and last numbers of iterations that run as a Lanczos recurrence and those beside them (47, 2823: the power
-# iteration), one row and four rows of the tridiagonal matrix per lane (177 and 178 iterations: 65 and 66 steps), in each
-# form of the product
+# iteration), one row and four rows of the tridiagonal matrix per lane (177 and 178 iterations: 65 and 66 steps).  Of two workers' matrices
+# this is so up to 128 columns; more columns are squared for most of these numbers, see REACHED for the recurrence's other forms
 @pytest.mark.parametrize("d", [2, 64, 65, 192, 256, 320, 321, 700])
 def test_recurrence_gives_the_power_iterations_value(gpu, d):
     torch, binding = gpu
@@ -247,7 +248,7 @@ def matrices_of_a_kind(kind, n, m, d, rng):
 
 
 @pytest.mark.parametrize("kind", ["Gaussian", "non-negative", "rank 3", "badly scaled", "one entry", "zero"])
-@pytest.mark.parametrize("d", [5, 40, 300, 320, 700])         # fewer columns than steps, and each form of the product
+@pytest.mark.parametrize("d", [5, 40, 300, 320, 700])         # fewer columns than steps; from 300 on by squaring
 def test_recurrence_on_kinds_of_matrices(gpu, kind, d):
     torch, binding = gpu
     print(f"recurrence on {kind} matrices, d={d}", flush=True)
@@ -322,7 +323,7 @@ def test_few_iterations_on_large_matrices(gpu):
 
 
 # powers by squaring (more than 128 columns): the ends of the groups of sixteen columns and of the strips of four groups, one row of A and
-# several chunks, and iterations whose exponents have few and many bits
+# several chunks (whether the exponent is right these matrices cannot show: REACHED)
 @pytest.mark.parametrize("n,d,m", [(1, 129, 40), (3, 143, 1), (2, 145, 600), (4, 176, 33), (2, 209, 80), (2, 305, 64), (2, 320, 30),
                                    (3, 337, 50), (2, 500, 17), (1, 1009, 40), (2, 1024, 12)])
 def test_powers_by_squaring_give_the_power_iterations_value(gpu, n, d, m):
@@ -344,7 +345,10 @@ def test_powers_by_squaring_give_the_power_iterations_value(gpu, n, d, m):
 
 # what the vector can come to when it is multiplied some fifty times by a power that is scaled by its trace: d times smaller at each product where all
 # eigenvalues are alike, and as large as it was where there is one
-@pytest.mark.parametrize("n,iterations", [(20, 573440), (40, 606208)])
+MANY_PRODUCTS = [(20, 573440), (40, 606208)]
+
+
+@pytest.mark.parametrize("n,iterations", MANY_PRODUCTS)
 def test_flat_spectrum_and_one_eigenvalue_under_many_products(gpu, n, iterations):
     torch, binding = gpu
     print(f"many products n={n} iterations={iterations}", flush=True)
@@ -360,3 +364,61 @@ def test_flat_spectrum_and_one_eigenvalue_under_many_products(gpu, n, iterations
         _, L, L_i = h.theory_stepsize(iterations)
         # fp32 entries of G
         np.testing.assert_allclose(list(L_i) + [L], 0.25 * d * float(np.float32(0.999)) ** 2, rtol=2.0 ** -23)
+
+
+# n, d (as many rows), the way and the numbers of iterations that go it: each form of the kernels, by columns (three to five per lane of the
+# resident one, a launch per step beyond), past a launch's 4096 iterations where the matrices' powers would take too much memory, and by squaring
+# at the ends of groups and strips with exponents of few and many bits
+REACHED = [
+    (48, 192, "iteration", (3, 7, 47)), (48, 192, "recurrence", (48, 100, 177)),
+    (48, 256, "iteration", (7, 47)), (48, 256, "recurrence", (48, 177, 178)),
+    (60, 320, "iteration", (7, 47)), (60, 320, "recurrence", (48, 178, 400)),
+    (48, 700, "iteration", (20, 47)), (48, 700, "recurrence", (48, 177, 178, 400)),
+    (48, 1023, "iteration", (40, 2823)), (48, 1023, "recurrence", (48, 178, 1000, 2822)),
+    (1300, 192, "iteration", (2823, 4096, 4097)), (700, 256, "iteration", (4096, 4097, 8300)), (450, 300, "iteration", (4096, 4097, 8300)),
+    (1, 129, "squaring", (100, 128, 129, 257, 1001)), (3, 143, "squaring", (100, 128, 129, 1001)), (2, 145, "squaring", (100, 128, 129, 1001)),
+    (4, 176, "squaring", (100, 128, 257, 1001)), (2, 209, "squaring", (100, 128, 129, 1001)), (2, 305, "squaring", (2, 65, 128, 129, 1001)),
+    (2, 320, "squaring", (2, 65, 128, 257, 1001)), (3, 337, "squaring", (65, 128, 129, 1001)), (2, 500, "squaring", (65, 128, 257, 1001)),
+    (1, 1009, "squaring", (65, 128, 129, 1001)), (2, 1024, "squaring", (65, 128, 257, 1001)),
+]
+
+
+def spread_eigenvalues(n, d, rng):
+    """[n][d] singular values: one eigenvalue of 1, many just below it, at distances for which 48 to a thousand iterations count."""
+    scale = rng.random((n, d)).astype(np.float32)
+    for row in range(n):
+        close = rng.permutation(d)[:d // 2]
+        scale[row, close] = 1.0 - 0.5 * rng.choice([0.02, 0.005, 0.002, 0.0005], close.size)
+        scale[row, close[0]] = 1.0
+    return scale
+
+
+def estimates(eigenvalues, steps):
+    """As diagonal_power, all rows at once: the eigenvalues' powers by logarithms (at 8300 iterations good to 1e-12)."""
+    v = np.array([start_vector(eigenvalues.shape[1], row) for row in range(eigenvalues.shape[0])])
+    top = eigenvalues.max(1, keepdims=True)
+    y = v * np.exp((steps - 1) * np.log(eigenvalues / top))
+    return np.linalg.norm(eigenvalues * y, axis=1) / np.linalg.norm(y, axis=1)
+
+
+@pytest.mark.parametrize("n,d,way,iterations", REACHED)
+def test_each_way_gives_the_power_iterations_value(gpu, n, d, way, iterations):
+    torch, binding = gpu
+    print(f"{way} n={n} d={d}", flush=True)
+    scale = spread_eigenvalues(n, d, np.random.default_rng(n + d)) * np.float32(np.sqrt(d))
+    A = torch.diag_embed(to_gpu(torch, scale))              # A_i^T A_i / m diagonal: one product per entry, exact in fp64
+    diagonals = scale.astype(np.float64) ** 2 / d
+    rounded = np.vstack([diagonals, diagonals.mean(0)]).astype(np.float32).astype(np.float64)
+    with binding.EF21(n, d, 1, 0.1) as h:
+        h.set_problem_dense(A, torch.zeros((n, d), device="cuda"), 0.0)
+        for steps in iterations:
+            _, L, L_i = h.theory_stepsize(steps)
+            got = 4.0 * np.array(list(L_i) + [L])
+            # fp64 on both sides from the same fp32 matrix; the start vectors may differ, see test_recurrence_gives_the_power_iterations_value,
+            # and the fewer the iterations the wider the eigenvalues that count: all of them, at most
+            rtol = 2.4e-8 if steps >= 48 else 2.0 ** -23
+            want = estimates(rounded, steps)
+            np.testing.assert_allclose(got, want, rtol=rtol, err_msg=f"{steps} iterations")
+            if steps <= 1001:                               # one iteration more or less would show, in the workers' values
+                for other in (steps - 1, steps + 1):
+                    assert np.median(np.abs(estimates(rounded, other) / want - 1.0)[:n]) > 2 * rtol, (steps, other)

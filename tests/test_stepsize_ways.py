@@ -60,3 +60,12 @@ def test_the_faster_way_on_the_matrices_is_taken(ways):
 def test_up_to_128_columns_nothing_is_squared(ways):
     names = ways([(n, 500, d, t) for n in (1, 20, 300) for d in (1, 64, 128) for t in (1, 47, 48, 2822, 2823, 10**6)])
     assert "squaring" not in names
+
+
+def test_the_gpu_tests_reach_the_ways_they_are_for(ways):
+    """test_gpu_stepsize.py names for its shapes the way that each goes: a rule that sends them elsewhere would empty it."""
+    from test_gpu_stepsize import MANY_PRODUCTS, REACHED
+    cases = [(n, d, d, t, way) for n, d, way, iterations in REACHED for t in iterations]
+    cases += [(n, 1024, 1024, t, "squaring") for n, t in MANY_PRODUCTS]
+    names = ways([case[:4] for case in cases])
+    assert names == [case[4] for case in cases], [(case, name) for case, name in zip(cases, names) if name != case[4]]
