@@ -649,14 +649,7 @@ static int enqueue_gram_product(ef21_ctx *c, const float *v, int64_t v_stride, f
     return EF21_OK;
 }
 
-// Whether the power iteration runs on Gram matrices; the handle's workspace for them is then large enough.  It is
-// grown on demand; where there is no memory for it the iteration runs with A.
-static bool use_gram(ef21_ctx *c, int32_t iterations, int32_t *squarings) {
-    if (c->kind != kDense) return false;
-    const ef21::GramWay way = ef21::gram_way(c->n, c->m, c->d, iterations);
-    const size_t bytes = way.bytes;
-    if (bytes == 0) return false;
-    *squarings = way.squarings;
+static bool reserve_gram(ef21_ctx *c, size_t bytes) {
     if (bytes <= c->gram_bytes) return true;
     (void)hipStreamSynchronize(c->stream);           // an error shows again at the call's own wait
     (void)hipFree(c->gram_ws);
@@ -668,6 +661,35 @@ static bool use_gram(ef21_ctx *c, int32_t iterations, int32_t *squarings) {
         return false;
     }
     c->gram_bytes = bytes;
+    return true;
+}
+
+// Whether the power iteration runs on Gram matrices, and by how many squarings (GramWay); the handle's workspace for them is then large
+// enough.  It is grown on demand; where there is no memory for the powers the matrices alone are tried, and without memory
+// for these the iteration runs with A.  What the handle has is kept as long as it would do for the matrices: a call that is refused the
+// larger one would otherwise give back and take the smaller one each time.
+static bool use_gram(ef21_ctx *c, int32_t iterations, int32_t *squarings) {
+    if (c->kind != kDense) return false;
+    ef21::GramWay way = ef21::gram_way(c->n, c->m, c->d, iterations);
+    if (way.squarings >= 0 && way.bytes > c->gram_bytes) {
+        const ef21::GramWay plain = ef21::gram_way(c->n, c->m, c->d, iterations, false);
+        if (plain.bytes > 0 && plain.bytes <= c->gram_bytes) {
+            void *larger = nullptr;
+            if (hipMalloc(&larger, way.bytes) == hipSuccess) {
+                (void)hipStreamSynchronize(c->stream);
+                (void)hipFree(c->gram_ws);
+                c->gram_ws = larger;
+                c->gram_bytes = way.bytes;
+            } else {
+                (void)hipGetLastError();
+                way = plain;
+            }
+        } else if (!reserve_gram(c, way.bytes)) {
+            way = plain;
+        }
+    }
+    if (way.bytes == 0 || !reserve_gram(c, way.bytes)) return false;
+    *squarings = way.squarings;
     return true;
 }
 

@@ -154,14 +154,15 @@ inline double plain_us(int32_t n, const GramPlan &p, int64_t d, int32_t iteratio
 // us, by the recurrence and by squaring: n = 16, m = 2000, d = 200 204 and 179; 25, 800, 250 204 and 212; 20, 2487, 300 317 and 289; 32, 1400, 330
 // 563 and 373; 10, 3000, 500 581 and 419; 3, 2000, 700 528 and 325; 2, 7500, 1000 796 and 656; 15, 1000, 1000 1154 and 1560; 1000 iterations of
 // 20, 2487, 300 660 and 363; 20 of them 225 and 236.  Up to 128 columns the host's dozen launches are what counts: 4, 250, 100 95 and 101.
-inline GramWay gram_way(int32_t n, int64_t m, int64_t d, int32_t iterations) {
+// squaring == false: without it, for a caller that has no memory for its workspace (six times the recurrence's per entry of G).
+inline GramWay gram_way(int32_t n, int64_t m, int64_t d, int32_t iterations, bool squaring = true) {
     GramWay way;
     if (d > kGramMax || n > 65534) return way;
     const GramPlan p = gram_plan(n, m, d);
     const size_t plain = gram_layout(n, p, false, nullptr, nullptr), squared = gram_layout(n, p, true, nullptr, nullptr);
     int32_t squarings = -1;
     double with_g = 1e30;
-    if (d >= kSquareLeast && iterations > 1 && squared <= kGramWsMax) {
+    if (squaring && d >= kSquareLeast && iterations > 1 && squared <= kGramWsMax) {
         const double us = squaring_us(n, p, d, iterations, &squarings);
         if (1.05 * us + 3.0 < plain_us(n, p, d, iterations)) with_g = us;
         else squarings = -1;

@@ -422,3 +422,40 @@ def test_each_way_gives_the_power_iterations_value(gpu, n, d, way, iterations):
             if steps <= 1001:                               # one iteration more or less would show, in the workers' values
                 for other in (steps - 1, steps + 1):
                     assert np.median(np.abs(estimates(rounded, other) / want - 1.0)[:n]) > 2 * rtol, (steps, other)
+
+
+def test_without_memory_for_the_powers_the_matrices_are_used(gpu):
+    """Squaring takes 24 bytes per entry of the matrices, the recurrence four and their tiles: 403 and 133 MB here.  With 250 MB left on the card a
+    call goes by the recurrence, not back to a thousand passes over A, and the next one in the workspace that is there."""
+    torch, binding = gpu
+    n, d, iterations = 15, 1024, 1000
+    scale = spread_eigenvalues(n, d, np.random.default_rng(5)) * np.float32(np.sqrt(d))
+    A = torch.diag_embed(to_gpu(torch, scale))
+    diagonals = scale.astype(np.float64) ** 2 / d
+    rounded = np.vstack([diagonals, diagonals.mean(0)]).astype(np.float32).astype(np.float64)
+    with binding.EF21(n, d, 1, 0.1) as h:
+        h.set_problem_dense(A, torch.zeros((n, d), device="cuda"), 0.0)
+
+        def call(steps):
+            before = torch.cuda.mem_get_info()[0]
+            _, L, L_i = h.theory_stepsize(steps)
+            np.testing.assert_allclose(4.0 * np.array(list(L_i) + [L]), estimates(rounded, steps), rtol=2.4e-8)
+            taken = before - torch.cuda.mem_get_info()[0]
+            print(f"{steps} iterations, {before >> 20} MB there, {taken >> 20} taken", flush=True)
+            return taken
+        torch.cuda.synchronize()
+        torch.cuda.empty_cache()
+        hogs = []
+        try:
+            for _ in range(5):                              # one large one leaves more than was asked for
+                free = torch.cuda.mem_get_info()[0]
+                if free > 270 << 20:
+                    hogs.append(torch.empty(free - (250 << 20), dtype=torch.uint8, device="cuda"))
+            assert 150 << 20 < torch.cuda.mem_get_info()[0] < 350 << 20
+            assert 90 << 20 < call(iterations) < 160 << 20          # of 127; the runtime has some megabytes of its own
+            assert call(iterations) < 8 << 20
+            assert call(100) < 8 << 20
+        finally:
+            hogs.clear()
+            torch.cuda.empty_cache()
+        assert 200 << 20 < call(iterations) < 320 << 20         # by squaring again: the larger workspace for the smaller one
