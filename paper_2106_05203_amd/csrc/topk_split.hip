@@ -22,7 +22,7 @@
 //
 // The guess can be wrong: fewer than k candidates, T beyond the histogram's window, or a crowded bin (more
 // than kTieCap entries, i.e. very many equal magnitudes at the threshold).  After a warm start the count kernel's workgroups
-// collect such a row again from the sample, and the last one of them counts it; a row that still fails is selected
+// collect such a row again from the sample and then count it; a row that still fails is selected
 // by the exact one-workgroup algorithm on the original data (one workgroup of the count or the emit kernel), so the
 // result never depends on the guess.  Slots have the capacity of their piece, so any input fits.
 #include <algorithm>
@@ -85,8 +85,7 @@ constexpr uint32_t kWarmBelow = 1u << 20;
 // failed guess costs twice the call.  After a fall, half an octave of margin brings two to seven times the candidates
 // instead; after either, a window of two octaves (bins of 2^12 keys) or one, unless T's bin would be crowded, costs next to nothing.  The first
 // ten steps, us each, before and now: EF21 on n = 8, d = 10^6, k = 10^4 52 and 47; n = 5, d = 10^6, k = 50 000 67 and 51; n = 8, d = 11.2 million,
-// k = 112 000 347 and 279.  (Where every row's guess fails at every step, scales a thousand apart in turn: n = 8, d = 10^5, k = 3000 37 and 43;
-// n = 8, d = 10^6, k = 10^4 78 and 96; n = 4, d = 3 million, k = 200 000 131 and 243, most of it the count by one workgroup per row.)
+// k = 112 000 347 and 279.
 constexpr uint32_t kMoved = 1u << 19, kWarmBelowWide = 1u << 22, kWideEntries = 256u;
 constexpr uint32_t kWideStart = 0x100u;      // flag in RowInfo::warm_s: the wide margin, which takes a window of an octave
 __device__ __forceinline__ uint32_t warm_start(int64_t k, int64_t d, uint32_t in_bin, uint32_t used, bool before, uint32_t T_before, uint32_t T, bool errors) {
@@ -118,17 +117,19 @@ struct __attribute__((aligned(64))) RowInfo {     // one cache line per row
     uint32_t use2;                // the count kernel collected this row again: its histogram is hist_b
     uint32_t warm_used;           // the first pass started from a remembered threshold
     uint32_t failed;              // kRowFailed: the row went to the exact one-workgroup algorithm in the count kernel;
-                                  // kRowCrowded: T's bin holds more than kTieCap candidates (see tie_min, tie_max)
+                                  // kRowCrowded: T's bin holds more than kTieCap candidates (see tie_min, tie_max);
+                                  // kRowPending: not known yet
     uint32_t bin_a, need_a;       // bin of T; entries still needed from that bin
     uint32_t ntie;                // length of the tie list
-    uint32_t arrived;             // workgroups of the count kernel that have collected the row again (zero between calls)
+    uint32_t arrived;             // workgroups of the count kernel that have collected the row again, then also the slot
+                                  // blocks that have been taken to be counted
     uint32_t warm_T[kWarmSlots];  // threshold T of the last call (also with warm == 0)
     uint32_t warm_s[kWarmSlots];  // bin width for the next warm start from it, with kWideStart; 0: there is none to start from
     uint32_t tie_min, tie_max;    // crowded bin: smallest and largest key in it.  Equal: T is that key (many equal
                                   // magnitudes at the threshold, e.g. zeros), no ranking needed.  Different: the
                                   // exact one-workgroup algorithm, in the emit kernel.
 };
-enum { kRowFine = 0, kRowFailed = 1, kRowCrowded = 2 };
+enum { kRowFine = 0, kRowFailed = 1, kRowCrowded = 2, kRowPending = 3 };
 static_assert(sizeof(RowInfo) == 64, "one cache line");
 
 // How a sample is read, from k and d alone (set on the host: double precision in every wavefront cost half a microsecond).
@@ -439,7 +440,7 @@ __device__ __forceinline__ void drain_ring(const Ring &ring, uint32_t flushed, u
 // one, else from the sample; kSecondPass: a row whose warm start failed, from the sample, into hist_b (in the count kernel).
 // ADD != kNoAdd (kWarmPass): the rows are a + add_scale * add, written over a on the way.  A sample would find some entries of the row
 // old and some new, so a row without a remembered threshold collects nothing here and is left to the count kernel.
-// All kBlk threads of the workgroup must call; s, rings and wg_total are the workgroup's.
+// All kBlk threads of the workgroup must call; s and rings are the workgroup's.
 template <bool DIFF, int MODE, bool RESID, int ADD, class Ring>
 __device__ __forceinline__ void collect_rows(const TopkArgs &p, const Ws &w, RowShared &s, Ring (&rings)[kBlkWaves]) {
     const int64_t row = blockIdx.y, d = p.d;
@@ -483,6 +484,8 @@ __device__ __forceinline__ void collect_rows(const TopkArgs &p, const Ws &w, Row
             info->tie_min = 0xffffffffu;
             info->tie_max = 0u;
             info->warm_used = warm || ADD ? 1u : 0u;
+            info->failed = kRowPending;
+            info->arrived = 0u;
         }
     }
     for (int i = threadIdx.x; i < kHistBins; i += kBlk) s.hist[i] = 0u;
@@ -618,6 +621,8 @@ __global__ __launch_bounds__(kBlk) void split_collect_pair_kernel(TopkArgs pm, W
         info_m->key_lo = fm.key_lo; info_m->shift = fm.shift; info_m->use2 = 0u; info_m->ntie = 0u;
         info_m->tie_min = 0xffffffffu; info_m->tie_max = 0u;
         info_m->warm_used = warm_m ? 1u : 0u;
+        info_m->failed = info_p->failed = kRowPending;
+        info_m->arrived = info_p->arrived = 0u;
         info_p->key_lo = fp.key_lo; info_p->shift = fp.shift; info_p->use2 = 0u; info_p->ntie = 0u;
         info_p->tie_min = 0xffffffffu; info_p->tie_max = 0u;
         info_p->warm_used = warm_pl ? 1u : 0u;
@@ -788,10 +793,17 @@ __device__ void rescue_row(RowShared &rs, const TopkArgs &p, const Ws &w, int64_
 // the last of 255 others for a few microseconds, here and in the emit kernel, since a unit holds one of them: step of
 // n = 15, d = 5 million, k = 50000 10.1 and 40.6 us in the two kernels, 6.7 and 31.7 without.)
 //
-// A row whose warm start failed is collected again from the sample instead, by all its workgroups, into hist_b; the one that is done
-// last counts all of its slots.  Nobody waits.  (As a launch of its own, which nearly always ended at once, the second pass took 3.8 to 4.6 us of
+// A row whose warm start failed is collected again from the sample instead, by all its workgroups, into hist_b; the one that is done last looks
+// for T's bin in it and says what it is, and then all that are still there count the slots, a block of them at a time.  Nobody has to be
+// there: a workgroup waits for the bin for kPatience at most and then ends, and what the others have not taken the last one counts.
+// Where every row's guess fails at every step (differences a thousand times larger and smaller in turn), us a step by itself, as a launch of its own and
+// here: n = 8, d = 10^5, k = 3000 43 and 46; n = 8, d = 10^6, k = 10^4 80 and 80; n = 4, d = 3 million, k = 200 000 132 and 131; n = 8, d = 11.2 million,
+// k = 112 000 587 and 493; n = 1, d = 12 million, k = 77 000 136 and 138.  With the row's slots counted by the last workgroup alone, one after the other, n =
+// 4, d = 3 million took 243, and differences that shrink to three fifths from step to step, n = 1, d = 8 million, k = 60 000, 304 against 96.
+// (As a launch of its own, which nearly always ended at once, the second pass took 3.8 to 4.6 us of
 // every warm call: n = 8, d = 10^5, k = 3000 26.6 us a step with it, 24.5 so; n = 8, d = 10^6, k = 10^4 38.7 and 36.2; EF on n = 5, d = 10^6, k =
 // 50 000 44.4 and 42.1; EF21+ on n = 5, d = 10^6 55.2 and 53.0.)
+constexpr uint64_t kPatience = 2000;             // of the clock's 100 MHz: 20 us, some times what the last one is late by
 struct CountShared {
     RowShared rs;
     uint32_t wave[kCandWaves], out[4], last;
@@ -853,46 +865,71 @@ __device__ __forceinline__ void count_rows(const TopkArgs &p, const Ws &w, Count
         crowded = found && lds_out[2] > (uint32_t)kTieCap;             // too many to list: see RowInfo::tie_min
         return found;
     };
-    auto record = [&](bool failed) {
-        info->failed = failed ? kRowFailed : (crowded ? kRowCrowded : kRowFine);
-        info->bin_a = bin_a;
-        info->need_a = need_a;
-    };
-    const bool failed = !find_bin();
-    if (failed && ri.warm_used) {
+    auto state = [&](bool found) { return found ? (crowded ? kRowCrowded : kRowFine) : kRowFailed; };
+    const bool found = find_bin(), again = !found && ri.warm_used != 0u;
+    if (again) {
         __syncthreads();                         // lds_out has been read
         collect_rows<DIFF, kSecondPass, DIFF && SUMS, kNoAdd>(p, w, rs, rings);
-        if (!draw_ticket(&info->arrived, gridDim.x, &sh.last)) return;
-        if (tid == 0) info->arrived = 0u;
-        key_lo = info->key_lo2;
-        shift = info->shift2;
+        if (draw_ticket(&info->arrived, gridDim.x, &sh.last)) {
+            key_lo = info->key_lo2;
+            shift = info->shift2;
 #pragma unroll
-        for (int j = 0; j < kPerThread; ++j) {
-            uint32_t *bin = w.hist_b + row * kHistBins + kHistBins - 1 - (tid * kPerThread + j);
-            h[j] = *bin;
-            *bin = 0u;                           // consumed: zero for the next time
-        }
-        const bool found = find_bin();
-        if (tid == 0) record(!found);
-        if (!found) {
-            rescue_row<DIFF, UPDATE, SUMS>(rs, p, w, row, widest_warm(p.k, p.d));
-            return;
+            for (int j = 0; j < kPerThread; ++j) {
+                uint32_t *bin = w.hist_b + row * kHistBins + kHistBins - 1 - (tid * kPerThread + j);
+                h[j] = *bin;
+                *bin = 0u;                       // consumed: zero for the next time
+            }
+            const bool found_now = find_bin();
+            if (tid == 0) {
+                info->bin_a = bin_a;
+                info->need_a = need_a;
+                __hip_atomic_store(&info->failed, (uint32_t)state(found_now), __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            if (!found_now) {
+                rescue_row<DIFF, UPDATE, SUMS>(rs, p, w, row, widest_warm(p.k, p.d));
+                return;
+            }
+        } else {
+            if (tid == 0) {
+                const uint64_t since = wall_clock64();
+                uint32_t now;
+                while ((now = __hip_atomic_load(&info->failed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) == kRowPending &&
+                       wall_clock64() - since < kPatience)
+                    __builtin_amdgcn_s_sleep(4);
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+                lds_out[3] = now;
+            }
+            __syncthreads();
+            const uint32_t now = lds_out[3];
+            if (now == kRowPending || now == kRowFailed) return;
+            key_lo = info->key_lo2;
+            shift = info->shift2;
+            bin_a = info->bin_a;
+            crowded = now == kRowCrowded;
         }
     } else {
-        if (blockIdx.x == 0 && tid == 0) record(failed);
-        if (failed) {
+        if (blockIdx.x == 0 && tid == 0) {
+            info->failed = state(found);
+            info->bin_a = bin_a;
+            info->need_a = need_a;
+        }
+        if (!found) {
             if (blockIdx.x == 0) rescue_row<DIFF, UPDATE, SUMS>(rs, p, w, row, widest_warm(p.k, p.d));
             return;
         }
     }
-    const bool again = failed;
     uint2 *tie = w.tie + row * kTieCap;
     uint32_t key_min = 0xffffffffu, key_max = 0u;
-    // this wavefront's slot, or every sixteenth one of the row
-    for (int64_t s = again ? wave : slot_no; s < w.nslot; s += again ? kCandWaves : w.nslot) {
+    for (int64_t s = slot_no;;) {                // this wavefront's slot, or those of the blocks that the workgroup takes
         if (again) {
-            cnt = w.slot_cnt[row * w.nslot + s];
-            slot = w.cand + (row * w.nslot + s) * w.L;
+            __syncthreads();                     // lds_out[3] has been read
+            if (tid == 0) lds_out[3] = atomicAdd(&info->arrived, 1u) - gridDim.x;
+            __syncthreads();
+            const uint32_t block = lds_out[3];
+            if (block >= gridDim.x) break;
+            s = (int64_t)block * kCandWaves + wave;
+            cnt = s < w.nslot ? w.slot_cnt[row * w.nslot + s] : 0u;
+            slot = w.cand + (row * w.nslot + (s < w.nslot ? s : 0)) * w.L;
         }
         uint32_t above = 0, inbin = 0;
         for (uint32_t j0 = 0; j0 < cnt; j0 += kWave * kPre) {
@@ -920,10 +957,11 @@ __device__ __forceinline__ void count_rows(const TopkArgs &p, const Ws &w, Count
                 }
             }
         }
-        if (lane == 0) {
+        if (lane == 0 && s < w.nslot) {
             w.slot_above[row * w.nslot + s] = above;
             if (crowded) w.slot_inbin[row * w.nslot + s] = inbin;
         }
+        if (!again) break;
     }
     if (crowded) {
 #pragma unroll

@@ -942,3 +942,29 @@ def test_mean_of_few_rows_reads_each_once(gpu):
                 times[n] = best
     print(times, flush=True)
     assert times[2] <= 0.9 * times[20], times
+
+
+@pytest.mark.parametrize("n,d,k", [(1, 8_000_000, 60_000), (4, 3_000_000, 200_000)])
+def test_steps_with_a_wrong_guess_are_not_much_longer(gpu, n, d, k):
+    """Every remembered threshold is wrong where the differences shrink to three fifths from step to step (half an octave is allowed for).  The rows are read
+    once more then and all workgroups count the candidates: 1.7 to 1.8 times a step with a right guess.  Counted by one workgroup per row it was 3.4 to 5.7."""
+    torch, binding = gpu
+    rows = torch.randn((n, d), device="cuda", generator=torch.Generator("cuda").manual_seed(d))
+    zero, x = torch.zeros((n, d), device="cuda"), torch.zeros(d, device="cuda")
+    median = {}
+    with binding.EF21(n, d, k, 0.1) as h:
+        for factor in (1.0, 0.6, 1.0, 0.6):
+            times = []
+            for t in range(12):
+                grad = rows * factor ** t
+                h.set_state(x, zero)                        # the differences are these values
+                torch.cuda.synchronize()
+                start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+                start.record()
+                h.step(grad)
+                end.record()
+                end.synchronize()
+                times.append(1000 * start.elapsed_time(end))
+            median[factor] = float(np.median(times[2:]))
+    print(n, d, k, median, flush=True)
+    assert median[0.6] <= 2.2 * median[1.0], median
