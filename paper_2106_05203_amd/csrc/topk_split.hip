@@ -86,12 +86,15 @@ constexpr uint32_t kWarmBelow = 1u << 20;
 // instead; after either, a window of two octaves (bins of 2^12 keys) or one, unless T's bin would be crowded, costs next to nothing.  The first
 // ten steps, us each, before and now: EF21 on n = 8, d = 10^6, k = 10^4 52 and 47; n = 5, d = 10^6, k = 50 000 67 and 51; n = 8, d = 11.2 million,
 // k = 112 000 347 and 279.
+// Not where the bin was crowded, with equal magnitudes then (crowded): a wider one can take in different ones beside them, and that row goes to the
+// exact algorithm (2 million of 3 million equal, 100 000 others 2560 keys away: 9.5 ms a step, 0.11 without).
 constexpr uint32_t kMoved = 1u << 19, kWarmBelowWide = 1u << 22, kWideEntries = 256u;
 constexpr uint32_t kWideStart = 0x100u;      // flag in RowInfo::warm_s: the wide margin, which takes a window of an octave
-__device__ __forceinline__ uint32_t warm_start(int64_t k, int64_t d, uint32_t in_bin, uint32_t used, bool before, uint32_t T_before, uint32_t T, bool errors) {
-    uint32_t s = warm_shift(k, d, in_bin, used);
+__device__ __forceinline__ uint32_t warm_start(int64_t k, int64_t d, bool crowded, uint32_t in_bin, uint32_t used, bool before, uint32_t T_before, uint32_t T,
+                                               bool errors) {
+    uint32_t s = warm_shift(k, d, crowded ? kBinEntries : in_bin, used);              // crowded: no wider (narrower would not help)
     const bool fell = !before || T + kMoved < T_before, rose = !before || T > T_before + kMoved;
-    if (fell || rose) {
+    if (!crowded && (fell || rose)) {
         // (EF21's falling threshold comes to where the entries are closer together: two octaves took a third more time in a run that had kept
         // all entries; the errors of EF fall when a run starts again, and grow then)
         for (uint32_t wide = before && fell && !errors ? 11u : 12u; wide > s && wide > 10u; --wide)
@@ -1172,8 +1175,7 @@ __device__ __forceinline__ void emit_rows(const TopkArgs &p, const Ws &w, EmitSh
         const int mem = p.warm > 0 ? p.warm - 1 : 0;
         static_assert(kWarmSlots == 1, "mem is zero; as an index it would put ri into scratch memory");
         info->warm_T[mem] = T;
-        // a crowded bin of equal keys: no wider the next time (narrower would not help)
-        info->warm_s[mem] = p.warm > 0 ? warm_start(p.k, p.d, crowded ? kBinEntries : ntie, ri.use2 != 0u ? ri.shift2 : ri.shift,
+        info->warm_s[mem] = p.warm > 0 ? warm_start(p.k, p.d, crowded, ntie, ri.use2 != 0u ? ri.shift2 : ri.shift,
                                                     ri.warm_s[0] != 0u, ri.warm_T[0], T, UPDATE == kClearUpdate) : 0u;
     }
 

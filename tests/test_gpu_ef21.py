@@ -968,3 +968,41 @@ def test_steps_with_a_wrong_guess_are_not_much_longer(gpu, n, d, k):
             median[factor] = float(np.median(times[2:]))
     print(n, d, k, median, flush=True)
     assert median[0.6] <= 2.2 * median[1.0], median
+
+
+def test_many_equal_magnitudes_beside_different_ones(gpu, oracle):
+    """2 million entries of one magnitude at the threshold and 100 000 of another just above it, 2560 keys away: a bin of 2^11 keys or less holds
+    the equal ones alone and needs no ranking, one of 2^12 holds both and sends the row to the exact algorithm, some fifty times as long.  After a
+    first or moved threshold the bins may get wider, but not where the bin was crowded."""
+    torch, binding = gpu
+    n, d, k = 1, 3_000_000, 200_000
+    rng = np.random.default_rng(17)
+    where = rng.permutation(d)
+    keys = []
+    for t in range(6):
+        low = np.float32(0.3).view(np.uint32) // 4096 * 4096 - t * (3 << 18)          # 3 / 32 of an octave lower at every step
+        bits = rng.integers(1, 1 << 24, d).astype(np.uint32)                          # next to nothing
+        bits[where[:2_000_000]] = low
+        bits[where[2_000_000:2_100_000]] = low + 2560
+        keys.append(bits.view(np.float32) * np.where(rng.random(d) < 0.5, np.float32(1), np.float32(-1)))
+    dev = [to_gpu(torch, v[None]) for v in keys]
+    zero, x = torch.zeros((n, d), device="cuda"), torch.zeros(d, device="cuda")
+    times = np.full(len(dev), np.inf)
+    for repeat in range(3):
+        with binding.EF21(n, d, k, 0.1) as h:
+            for t, grad in enumerate(dev):
+                h.set_state(x, zero)                        # the differences are these values
+                torch.cuda.synchronize()
+                start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+                start.record()
+                h.step(grad)
+                end.record()
+                end.synchronize()
+                times[t] = min(times[t], 1000 * start.elapsed_time(end))
+                if repeat == 0:
+                    idx, val = (a.cpu().numpy() for a in h.get_messages())
+                    ref_idx, ref_val = oracle.topk(keys[t].astype(np.float64), k)
+                    assert np.array_equal(idx[0], ref_idx), t
+                    assert same_bits(val[0], ref_val.astype(np.float32)), t
+    print(times, flush=True)
+    assert times[1:].max() <= 5 * np.median(times), times
