@@ -579,13 +579,14 @@ int ef21_set_state(ef21_handle h, const float *x, const float *g_i, const float 
     const size_t db = sizeof(float) * (size_t)d;
     const ef21::CopyList list{{x, g_i, g}, {h->x, h->g_i, h->g}, {x ? d : 0, g_i ? nd : 0, g ? d : 0}};
     const bool with_mean = g_i && !g;
-    if ((with_mean ? ef21::mean_rows_copies(h->n, d) : ef21::copy_arrays_applies(list)) && copies_by_kernel(h, x, d) && copies_by_kernel(h, g_i, nd) &&
+    const ef21::CopyWay way = ef21::copy_arrays_way(list, nd + 2 * d);
+    if ((with_mean ? ef21::mean_rows_copies(h->n, d) : way != ef21::CopyWay::kMemcpy) && copies_by_kernel(h, x, d) && copies_by_kernel(h, g_i, nd) &&
         copies_by_kernel(h, g, d)) {
         hipError_t st;
         if (with_mean) {
             st = ef21::launch_mean_rows(g_i, h->g, h->n, d, h->stream, h->g_i, x, x ? h->x : nullptr);
         } else {
-            st = ef21::launch_copy_arrays(list, h->stream);
+            st = ef21::launch_copy_arrays(list, way == ef21::CopyWay::kStreamed, h->stream);
             if (st == hipSuccess && !g) st = ef21::launch_mean_rows(h->g_i, h->g, h->n, d, h->stream);
         }
         if (st != hipSuccess) return fail_hip(st, "state kernel launch");
@@ -607,8 +608,9 @@ int ef21_get_state(ef21_handle h, float *x, float *g_i, float *g) {
     const int64_t d = h->d, nd = (int64_t)h->n * d;
     const size_t db = sizeof(float) * (size_t)d;
     const ef21::CopyList list{{h->x, h->g_i, h->g}, {x, g_i, g}, {x ? d : 0, g_i ? nd : 0, g ? d : 0}};
-    if (ef21::copy_arrays_applies(list) && copies_by_kernel(h, x, d) && copies_by_kernel(h, g_i, nd) && copies_by_kernel(h, g, d)) {
-        hipError_t st = ef21::launch_copy_arrays(list, h->stream);
+    const ef21::CopyWay way = ef21::copy_arrays_way(list, nd + 2 * d);
+    if (way != ef21::CopyWay::kMemcpy && copies_by_kernel(h, x, d) && copies_by_kernel(h, g_i, nd) && copies_by_kernel(h, g, d)) {
+        hipError_t st = ef21::launch_copy_arrays(list, way == ef21::CopyWay::kStreamed, h->stream);
         if (st != hipSuccess) return fail_hip(st, "state kernel launch");
         return EF21_OK;
     }

@@ -6,6 +6,8 @@
 
 #include <mutex>
 
+#include "copy_way.h"
+
 namespace ef21 {
 
 // Runs `setup` once per HIP device, with that device current: for attributes of a kernel (such as its dynamic LDS
@@ -169,8 +171,8 @@ struct CopyList {
     float *dst[3];
     int64_t count[3];
 };
-bool copy_arrays_applies(const CopyList &c);       // false: hipMemcpyAsync is the faster way
-hipError_t launch_copy_arrays(const CopyList &c, hipStream_t stream);
+CopyWay copy_arrays_way(const CopyList &c, int64_t state);       // state: see copy_way
+hipError_t launch_copy_arrays(const CopyList &c, bool streamed, hipStream_t stream);
 
 // `loss` below: the per-row loss of the linear model (LossKind in device_utils.h): logistic (eq. (9)) or squared.
 // kLossHalfSquare (z^2 / 2, no target) is internal: its gradient is (1/m) A_i^T A_i x, the product the power

@@ -14,13 +14,8 @@ constexpr int kThreads = 256;
 // 5.8 and 9.1; 100 x 2000 8.0 and 12.5; 100 x 50000 11.1 and 29.2; 8 x 65536 5.7 and 5.6; 8 x 200000 6.7 and 5.6, and without the
 // copy 5.6 and 4.3; 8 x 1000003 17.7 and 17.3, without 13.6 and 5.7.
 constexpr int64_t kMeanFewCols = 65536;
-// Arrays of this many entries in all and more are copied past the caches, a block per 2048 entries; shorter ones through them, by
-// one block per compute unit, and one short array alone is left to hipMemcpyAsync (copy_arrays_applies).  A step and the copy of x,
-// us, by hipMemcpyAsync, through the caches and past them: n = 8, d = 10^6 38.3, 39.0 and 39.8; n = 4, d = 6 million 82.8, 83.4 and
-// 86.3; d = 9 million 113.2, 114.5 and 114.0; n = 8, d = 11.2 million 229.5, 230.0 and 225.0; EF21+ on n = 5, d = 11.5 million 287,
-// 282 and 270.
+// Past the caches a block copies 2048 entries, through them a block per compute unit its share (copy_way.h says which).
 constexpr int kCopyThreads = 512, kCopyBlocks = 256;
-constexpr int64_t kCopyStream = (int64_t)10 << 20;
 constexpr int64_t kMeanStream = (int64_t)64 << 20;   // entries of the 256 MB cache
 
 // x_j <- x_j - gamma g_j as one fused multiply-add per coordinate (a single rounding).
@@ -638,17 +633,15 @@ hipError_t launch_mean_rows(const float *g_i, float *g, int32_t n, int64_t d, hi
     return hipGetLastError();
 }
 
-bool copy_arrays_applies(const CopyList &c) {
+CopyWay copy_arrays_way(const CopyList &c, int64_t state) {
     const int64_t entries = c.count[0] + c.count[1] + c.count[2];
-    const bool one = entries == std::max(c.count[0], std::max(c.count[1], c.count[2]));
-    return !one || entries >= kCopyStream;
+    return copy_way(state, entries, entries == std::max(c.count[0], std::max(c.count[1], c.count[2])));
 }
 
-hipError_t launch_copy_arrays(const CopyList &c, hipStream_t stream) {
+hipError_t launch_copy_arrays(const CopyList &c, bool streamed, hipStream_t stream) {
     const int64_t entries = c.count[0] + c.count[1] + c.count[2], per = kCopyThreads * 4;
     if (entries == 0) return hipSuccess;
     const int64_t blocks = (entries + per - 1) / per;
-    const bool streamed = entries >= kCopyStream;
     const dim3 grid((unsigned)std::min<int64_t>(blocks, streamed ? 1 << 20 : kCopyBlocks)), block(kCopyThreads);
     if (streamed) hipLaunchKernelGGL(copy_arrays_kernel<true>, grid, block, 0, stream, c);
     else hipLaunchKernelGGL(copy_arrays_kernel<false>, grid, block, 0, stream, c);
