@@ -262,7 +262,7 @@ int ef21_get_choices(ef21_handle h, int32_t *branch, double *distortions);
  * ef21_set_timing and ef21_get_timing wait for the stream.  ms[EF21_K_COUNT] receives the
  * accumulated milliseconds per class and launches[EF21_K_COUNT] the number of intervals (either
  * may be NULL); reset != 0 clears the sums.  Classes, in order (names from ef21_kernel_name):
- * grad_main, grad_aux, topk_row, topk_collect, topk_select, topk_refine, topk_count, topk_emit,
+ * grad_main, grad_aux, topk_row, topk_collect, topk_select, topk_refine (no kernel; the number stays), topk_count, topk_emit,
  * model_step, plus (what is particular to Algorithm 3), small_step (the one-launch iteration).
  */
 enum { EF21_K_COUNT = 11 };

@@ -35,8 +35,8 @@ enum KernelId {
     K_GRAD_AUX,        // partial-sum reduction / regulariser
     K_TOPK_ROW,        // one-workgroup-per-row Top-k (+ fused update)
     K_TOPK_COLLECT,    // long rows: the pass over the row that collects candidates
-    K_TOPK_SELECT,     // long rows, small k: per-row select + emission on the candidates (+ fused update)
-    K_TOPK_REFINE,     // no kernel at present
+    K_TOPK_SELECT,     // long rows, k = 1: the message of the running maximum (+ fused update)
+    K_TOPK_REFINE,     // no kernel: callers' arrays are laid out by these numbers
     K_TOPK_COUNT,      // long rows, large k: per-slot counts
     K_TOPK_EMIT,       // long rows, large k: ordered emission (+ fused update)
     K_MODEL_STEP,      // g <- g + mean of the messages and / or x <- x - gamma g

@@ -36,6 +36,7 @@ struct RowShared {
     uint32_t cand_key[kRankMax];
     uint32_t cand_idx[kRankMax];
     uint32_t cand_rank[kRankMax];   // low half: gathered entries with a larger key; high half: equal key, lower position
+                                    // (short_row_topk: their sum, the entries that go before)
 };
 static_assert(kRankMax <= 0xffff, "two counts of at most kRankMax share one word");
 

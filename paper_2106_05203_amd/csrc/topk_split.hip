@@ -51,7 +51,8 @@ static_assert(kCandThreads == kRowThreads && kBlk == kRowThreads, "the rescue ru
 // above key_lo: the window is one octave (2^23 keys).  After a warm start key_lo is kWarmBelow keys (1/8 octave,
 // 8.3 %) below the previous T and the window half an octave, so a threshold between 0.92 and 1.3 times the
 // previous one is found by the first pass: narrower bins, fewer entries to rank.  A candidate costs little (an
-// 8-byte store), a failed guess a second pass over the row, hence the generous margin.
+// 8-byte store), a failed guess a second pass over the row, hence the generous margin; where T has just moved both are wider, see
+// warm_start.
 // That is where many entries are kept.  Where few are, T of a heavy-tailed row lies up to an octave above the sample's
 // bound, and a row that failed so once starts from a sample, and can fail again, in every later call (n = 15, d = 5
 // million, k = 5000, Student-t gradients: 13 ms an iteration against 0.14, all of it the exact algorithm on one row), so
