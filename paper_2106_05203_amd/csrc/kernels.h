@@ -160,8 +160,7 @@ hipError_t launch_aggregate(const int32_t *idx, const float *val, int32_t n, int
                             bool from_zero = false);
 
 // g = (1/n) sum_i g_i (input line of Algorithm 2), summed in worker order; in the same launch, if rows_out != nullptr, rows_out <-
-// g_i and, if x_out != nullptr as well, x_out [d] <- x.
-bool mean_rows_copies(int32_t n, int64_t d);       // false: hipMemcpyAsync and the mean alone are the faster way
+// g_i and, if x_out != nullptr as well, x_out [d] <- x (a caller does not ask for copies where mean_way says kMemcpy).
 hipError_t launch_mean_rows(const float *g_i, float *g, int32_t n, int64_t d, hipStream_t stream, float *rows_out = nullptr,
                             const float *x = nullptr, float *x_out = nullptr);
 

@@ -10,13 +10,8 @@ namespace ef21 {
 namespace {
 
 constexpr int kThreads = 256;
-// A column per thread up to this length of a row, beyond it four.  The mean with a copy of the rows, us, one and four: 20 x 123
-// 5.8 and 9.1; 100 x 2000 8.0 and 12.5; 100 x 50000 11.1 and 29.2; 8 x 65536 5.7 and 5.6; 8 x 200000 6.7 and 5.6, and without the
-// copy 5.6 and 4.3; 8 x 1000003 17.7 and 17.3, without 13.6 and 5.7.
-constexpr int64_t kMeanFewCols = 65536;
 // Past the caches a block copies 2048 entries, through them a block per compute unit its share (copy_way.h says which).
 constexpr int kCopyThreads = 512, kCopyBlocks = 256;
-constexpr int64_t kMeanStream = (int64_t)64 << 20;   // entries of the 256 MB cache
 
 // x_j <- x_j - gamma g_j as one fused multiply-add per coordinate (a single rounding).
 __global__ __launch_bounds__(kThreads) void model_step_kernel(float *__restrict__ x, const float *__restrict__ g,
@@ -44,8 +39,7 @@ __global__ __launch_bounds__(kThreads) void model_step_vec4_kernel(float4 *__res
 
 // The rows' mean, and on the way a copy of the rows (rows_out) and of one more vector (x_out <- x) for ef21_set_state, which
 // took a launch each and read the rows twice.  Per coordinate the workers in order, in fp64, rounded once.  FLIGHT workers' loads
-// in flight: up to eight where a thread has four columns (with eight for two workers, six of them the second one's again, 2 x 28 million
-// took 269 us, see launch_mean_rows), up to 32 where it has one: short rows have few threads, and there the waits for memory
+// in flight: up to eight where a thread has four columns, up to 32 where it has one: short rows have few threads, and there the waits for memory
 // are all there is (20 x 123, the three things in 4 launches 9.4 us, in this one 3.0; with 32 for any number of workers, the last one's read again,
 // 2 x 2000 took 2.9 against 2.0 and the mean alone 0.9 more than the kernel before).  Rows may start at any 4-byte address.
 struct RowsOut {
@@ -53,7 +47,7 @@ struct RowsOut {
     const float *x;              // with x_out, or nullptr
     float *x_out;
 };
-enum RowsCopy { kNoCopy = 0, kCopy = 1, kCopyStreamed = 2 /* past the caches, see launch_mean_rows */ };
+enum RowsCopy { kNoCopy = 0, kCopy = 1, kCopyStreamed = 2, kNoCopyStreamed = 3 };      // streamed: past the caches, see mean_way
 template <int VEC, int COPY, int FLIGHT>
 __global__ __launch_bounds__(kThreads) void mean_rows_kernel(const float *__restrict__ g_i, float *__restrict__ g,
                                                              int32_t n, int64_t d, RowsOut out) {
@@ -67,7 +61,7 @@ __global__ __launch_bounds__(kThreads) void mean_rows_kernel(const float *__rest
             for (int u = 0; u < FLIGHT; ++u) {      // a worker past the end re-reads the last one, unused
                 const float *at = g_i + (int64_t)(i0 + u < n ? i0 + u : n - 1) * d + j;
                 if constexpr (W == 4) {
-                    const float4 t = stream_load4_any(at);
+                    const float4 t = COPY != kNoCopy ? stream_load4_any(at) : load4_any(at);
                     v[u][0] = t.x, v[u][1] = t.y, v[u][2] = t.z, v[u][3] = t.w;
                 } else {
                     v[u][0] = *at;
@@ -78,7 +72,7 @@ __global__ __launch_bounds__(kThreads) void mean_rows_kernel(const float *__rest
                 if (i0 + u < n) {
 #pragma unroll
                     for (int t = 0; t < W; ++t) s[t] += (double)v[u][t];
-                    if constexpr (COPY != kNoCopy) {
+                    if constexpr (COPY == kCopy || COPY == kCopyStreamed) {
                         float *to = out.rows + (int64_t)(i0 + u) * d + j;
                         if constexpr (W != 4) *to = v[u][0];
                         else if constexpr (COPY == kCopyStreamed) stream_store4_any(to, make_float4(v[u][0], v[u][1], v[u][2], v[u][3]));
@@ -90,7 +84,7 @@ __global__ __launch_bounds__(kThreads) void mean_rows_kernel(const float *__rest
 #pragma unroll
         for (int t = 0; t < W; ++t) {
             g[j + t] = (float)(s[t] / (double)n);
-            if (COPY != kNoCopy && out.x_out) out.x_out[j + t] = out.x[j + t];
+            if ((COPY == kCopy || COPY == kCopyStreamed) && out.x_out) out.x_out[j + t] = out.x[j + t];
         }
     };
     for (int64_t j = ((int64_t)blockIdx.x * kThreads + threadIdx.x) * VEC; j < d; j += stride) {
@@ -593,26 +587,18 @@ hipError_t launch_hbm_copy(void *dst, const void *src, int64_t n16, hipStream_t 
     return hipGetLastError();
 }
 
-// set_state and a step of one worker, us, by hipMemcpyAsync and a mean, and in one launch: d = 300 000 49 and 40, 2 million 58 and 53,
-// 20 million 232 and 235, 80 million 849 and 860.
-bool mean_rows_copies(int32_t n, int64_t d) { return n > 1 || d < kCopyStream; }
-
 hipError_t launch_mean_rows(const float *g_i, float *g, int32_t n, int64_t d, hipStream_t stream, float *rows_out,
                             const float *x, float *x_out) {
     const RowsOut out{rows_out, x, x_out};
-    // A column per thread as long as that leaves compute units idle.  Rows that the last cache cannot hold are copied past it: what it
-    // kept of them would have to be written back while the first step reads.  set_state and a step, us, kept and past the caches: 20 x
-    // 1.5 million 141 and 150; 8 x 5 million 172 and 180; 8 x 7 million 240 and 236; 2 x 28 million 394 and 378; 3 x 20 million 353 and 342;
-    // 8 x 11.2 million 413 and 374 (452 by hipMemcpyAsync and a mean).
-    const bool few = d <= kMeanFewCols, streamed = ((int64_t)n + 2) * d > kMeanStream;       // with x and g
+    const MeanWay way = mean_way(n, d, rows_out != nullptr);
 #define EF21_MEAN(VEC, COPY, FLIGHT)                                                                                    \
     hipLaunchKernelGGL((mean_rows_kernel<VEC, COPY, FLIGHT>), dim3(grid_for((d + VEC - 1) / VEC, 8192)), dim3(kThreads), 0, stream, \
                        g_i, g, n, d, out)
-#define EF21_MEAN4(COPY)                   \
-    do {                                   \
+#define EF21_MEAN4(COPY) \
+    do { \
         if (n <= 2) EF21_MEAN(4, COPY, 2); \
         else if (n <= 4) EF21_MEAN(4, COPY, 4); \
-        else EF21_MEAN(4, COPY, 8);        \
+        else EF21_MEAN(4, COPY, 8); \
     } while (0)
 #define EF21_MEAN1(COPY) \
     do { \
@@ -622,10 +608,11 @@ hipError_t launch_mean_rows(const float *g_i, float *g, int32_t n, int64_t d, hi
         else if (n <= 16) EF21_MEAN(1, COPY, 16); \
         else EF21_MEAN(1, COPY, 32); \
     } while (0)
-    if (rows_out && few) EF21_MEAN1(kCopy);
-    else if (rows_out && streamed) EF21_MEAN4(kCopyStreamed);
+    if (way == MeanWay::kColumn && rows_out) EF21_MEAN1(kCopy);
+    else if (way == MeanWay::kColumn) EF21_MEAN1(kNoCopy);
+    else if (way == MeanWay::kQuadStreamed && rows_out) EF21_MEAN4(kCopyStreamed);
+    else if (way == MeanWay::kQuadStreamed) EF21_MEAN4(kNoCopyStreamed);
     else if (rows_out) EF21_MEAN4(kCopy);
-    else if (few) EF21_MEAN1(kNoCopy);
     else EF21_MEAN4(kNoCopy);
 #undef EF21_MEAN1
 #undef EF21_MEAN4

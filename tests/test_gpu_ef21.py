@@ -804,10 +804,12 @@ def test_order_of_the_sum_of_messages(gpu, n, d, k):
 
 @pytest.mark.parametrize("n,d,offset", [(1, 1, 0), (4, 3, 1), (3, 1023, 0), (33, 1025, 3), (65, 257, 2), (2, 4096, 0), (7, 65537, 1),
                                         (151, 70001, 0), (151, 70001, 1), (9, 65536, 1),
-                                        (2, 65539, 1), (3, 70001, 0), (1, 65537, 3), (2, 16_777_219, 1)])
+                                        (2, 65539, 1), (3, 70001, 0), (1, 65537, 3), (2, 16_777_219, 1),
+                                        (1, 262_145, 0), (3, 262_147, 2), (3, 8_000_003, 1), (5, 6_000_001, 0), (4, 12_000_001, 3), (6, 9_000_002, 0), (3, 20_200_003, 1)])
 def test_state_in_and_out(gpu, n, d, offset):
-    """set_state and get_state move every entry, from and to any 4-byte address, on both sides of the lengths from which the mean's
-    threads have four columns (of two, four or eight workers at once) and the copies go past the caches; g is the fp64 mean in worker order, rounded once."""
+    """set_state and get_state move every entry, from and to any 4-byte address, on both sides of the sizes from which the mean's
+    threads have four columns (of two, four or eight workers at once) and the copies go past the caches (csrc/copy_way.h); g is the fp64 mean in worker
+    order, rounded once."""
     torch, binding = gpu
     rng = np.random.default_rng(n + d)
     sizes = {"x": d, "g_i": n * d, "g": d}
