@@ -80,7 +80,7 @@ __device__ __forceinline__ uint32_t warm_shift(int64_t k, int64_t d, uint32_t in
     return s;
 }
 constexpr uint32_t kWarmBelow = 1u << 20;
-// A threshold that has just moved by more than a sixteenth of an octave, or that is the first one, may well move again by more than that
+// A threshold that has just moved by more than three quarters of that, or that is the first one, may well move again by more than it
 // allows.  The steps of EF21 from a fresh state on gradients that stay alike keep k entries more each: at k = 5 per
 // cent of a Gaussian row T falls by 16 per cent, then 12, 11, 10 ..; the errors of EF grow from zero by 100 per cent, 50, 33 ..; and a
 // failed guess costs twice the call.  After a fall, half an octave of margin brings two to seven times the candidates
@@ -89,7 +89,9 @@ constexpr uint32_t kWarmBelow = 1u << 20;
 // k = 112 000 347 and 279.
 // Not where the bin was crowded, with equal magnitudes then (crowded): a wider one can take in different ones beside them, and that row goes to the
 // exact algorithm (2 million of 3 million equal, 100 000 others 2560 keys away: 9.5 ms a step, 0.11 without).
-constexpr uint32_t kMoved = 1u << 19, kWarmBelowWide = 1u << 22, kWideEntries = 256u;
+// (From half of the margin on, thresholds that fall by ever less got the wide one for nothing: n = 20, d = 5 million, k = 50 000, the sixth and the eighth step from a
+// fresh state on two gradients in turn 312 us each, 258 so.)
+constexpr uint32_t kMoved = 3u << 18, kWarmBelowWide = 1u << 22, kWideEntries = 256u;
 constexpr uint32_t kWideStart = 0x100u;      // flag in RowInfo::warm_s: the wide margin, which takes a window of an octave
 __device__ __forceinline__ uint32_t warm_start(int64_t k, int64_t d, bool crowded, uint32_t in_bin, uint32_t used, bool before, uint32_t T_before, uint32_t T,
                                                bool errors) {

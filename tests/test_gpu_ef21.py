@@ -1008,3 +1008,27 @@ def test_many_equal_magnitudes_beside_different_ones(gpu, oracle):
                     assert same_bits(val[0], ref_val.astype(np.float32)), t
     print(times, flush=True)
     assert times[1:].max() <= 5 * np.median(times), times
+
+
+def test_steps_whose_threshold_falls_a_little_are_not_longer(gpu):
+    """From a fresh state on two gradients in turn the threshold falls by some seven hundredths of an octave at the sixth and the eighth step, which the usual
+    margin of an eighth allows for; with the margin for thresholds that fall by more these steps took a fifth longer than the tenth."""
+    torch, binding = gpu
+    n, d, k = 20, 5_000_000, 50_000
+    pool = [torch.randn((n, d), device="cuda", generator=torch.Generator("cuda").manual_seed(t)) for t in range(3)]
+    x = torch.zeros(d, device="cuda")
+    times = np.full((5, 12), np.inf)
+    with binding.EF21(n, d, k, 0.1) as h:
+        for repeat in range(5):
+            h.set_state(x, pool[2])
+            for t in range(12):
+                start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+                torch.cuda.synchronize()
+                start.record()
+                h.step(pool[t % 2])
+                end.record()
+                end.synchronize()
+                times[repeat, t] = 1000 * start.elapsed_time(end)
+    best = times.min(0)
+    print(best, flush=True)
+    assert max(best[5], best[7]) <= 1.1 * best[9], best
