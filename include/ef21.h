@@ -174,7 +174,8 @@ int ef21_set_minibatch(ef21_handle h, const int32_t *rows, int64_t tau);
  * or as many as make a thousand tiles in all; by squaring 24 (n + 1) d'^2, or 16 (n + 1) d'^2 + 4 n c d' (d' + 32) where that is more,
  * and 16 (n + 1) (d' + 96)) and some ten thousand for alignment, never more than 1 GiB, which the handle
  * keeps until ef21_destroy (while a larger one is being allocated, what is there stays if it would do without squaring).
- * Where there is no memory for squaring a call goes without it; where there is none for the matrices, and for all other problems, it iterates with the problem itself, a step two passes
+ * Where there is no memory for squaring a call goes without it; where there is none for the matrices, and for all other problems, it iterates with the
+ * problem itself, a step two passes
  * of the gradient kernels over it: the first one
  * on a handle allocates (n + 2) d floats that the handle keeps, and every one overwrites the handle's gradient buffer.
  * EF21_ESTATE without a problem; EF21_EINVAL: iterations outside [1, 10^6]; EF21_ENOMEM.

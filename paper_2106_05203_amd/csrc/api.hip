@@ -580,8 +580,8 @@ int ef21_set_state(ef21_handle h, const float *x, const float *g_i, const float 
     const ef21::CopyList list{{x, g_i, g}, {h->x, h->g_i, h->g}, {x ? d : 0, g_i ? nd : 0, g ? d : 0}};
     const bool with_mean = g_i && !g;
     const ef21::CopyWay way = ef21::copy_arrays_way(list, nd + 2 * d);
-    if ((with_mean ? ef21::mean_way(h->n, d, true) != ef21::MeanWay::kMemcpy : way != ef21::CopyWay::kMemcpy) && copies_by_kernel(h, x, d) && copies_by_kernel(h, g_i, nd) &&
-        copies_by_kernel(h, g, d)) {
+    const bool by_kernel = with_mean ? ef21::mean_way(h->n, d, true) != ef21::MeanWay::kMemcpy : way != ef21::CopyWay::kMemcpy;
+    if (by_kernel && copies_by_kernel(h, x, d) && copies_by_kernel(h, g_i, nd) && copies_by_kernel(h, g, d)) {
         hipError_t st;
         if (with_mean) {
             st = ef21::launch_mean_rows(g_i, h->g, h->n, d, h->stream, h->g_i, x, x ? h->x : nullptr);
